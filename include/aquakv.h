@@ -396,6 +396,19 @@ int aquakv_fit_predictor(int32_t dtype, int64_t tokens, const void* x0, int32_t 
                          const void* Y, int32_t d_out, double rate, void* W, double* W64, float* bias,
                          void* workspace, size_t workspace_bytes, void* stream);
 
+/*
+ * aquakv_copy_ranges -- n device-to-device copies in as few launches as possible (128 ranges each): what a cache manager
+ * around the calls above moves (new tokens of all layers and sequences into sinks and recent-token buffers, Sect. 3.3;
+ * codes to the sequences' ranges).  `ranges`: HOST array, read before the call returns; its pointers are device memory,
+ * any alignment (16 bytes is the fast one).  No destination may overlap a source or another destination.
+ */
+typedef struct aquakv_copy_range {
+  void* dst;
+  const void* src;
+  size_t bytes;
+} aquakv_copy_range;
+int aquakv_copy_ranges(const aquakv_copy_range* ranges, int32_t n, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -6,6 +6,7 @@ Importing this module without the built library raises: there is no fallback.
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 from typing import Optional
@@ -40,7 +41,7 @@ EXPORTS = [
     "aquakv_encode_keys", "aquakv_encode_values", "aquakv_decode_values",
     "aquakv_fit_workspace_bytes", "aquakv_fit_predictor",
     "aquakv_softmax", "aquakv_weighted_workspace_bytes", "aquakv_decode_values_weighted", "aquakv_decode_values_attend",
-    "aquakv_attend_raw",
+    "aquakv_attend_raw", "aquakv_copy_ranges",
 ]
 
 
@@ -97,7 +98,8 @@ _lib.aquakv_weighted_workspace_bytes.argtypes = [_LP, ctypes.c_int32, ctypes.c_i
 _lib.aquakv_decode_values_weighted.argtypes = [_LP, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32] + [_P] * 8 + [ctypes.c_size_t, _P]
 _lib.aquakv_decode_values_attend.argtypes = [_LP, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32] + [_P] * 9 + [ctypes.c_size_t, _P]
 _lib.aquakv_attend_raw.argtypes = [ctypes.c_int32] * 5 + [_P, _P, _P, _P, _P, ctypes.c_float, _P, _P, ctypes.c_int32, _P]
-for _n in ("aquakv_attend_raw", "aquakv_softmax", "aquakv_decode_values_weighted", "aquakv_decode_values_attend", "aquakv_predict", "aquakv_quantize", "aquakv_dequantize", "aquakv_encode_layer", "aquakv_decode_layer",
+_lib.aquakv_copy_ranges.argtypes = [_P, ctypes.c_int32, _P]
+for _n in ("aquakv_copy_ranges", "aquakv_attend_raw", "aquakv_softmax", "aquakv_decode_values_weighted", "aquakv_decode_values_attend", "aquakv_predict", "aquakv_quantize", "aquakv_dequantize", "aquakv_encode_layer", "aquakv_decode_layer",
            "aquakv_decode_attn_scores", "aquakv_decode_attn_scores_rope", "aquakv_decode_attn_scores_folded",
            "aquakv_decode_attn_scores_folded_static", "aquakv_encode_keys", "aquakv_encode_values",
            "aquakv_decode_values", "aquakv_fit_predictor"):
@@ -369,6 +371,12 @@ def aquakv_attend_raw(dtype, batch: int, tokens: int, kv_heads: int, q_heads: in
     _check(_lib.aquakv_attend_raw(code, batch, tokens, kv_heads, q_heads, _ptr(K), _ptr(V), _ptr(q), _ptr(rope_cos),
                                   _ptr(rope_sin), score_scale, _ptr(out), _ptr(row_stats),
                                   int(bool(accumulate)), _stream(stream)))
+
+
+def aquakv_copy_ranges(ranges, stream=None) -> None:
+    """ranges: flat sequence of addresses and sizes, (dst, src, bytes) per copy."""
+    flat = array.array("Q", ranges)
+    _check(_lib.aquakv_copy_ranges(flat.buffer_info()[0], len(flat) // 3, _stream(stream)))
 
 
 def aquakv_fit_workspace_bytes(d_in: int, d_out: int) -> int:

@@ -740,6 +740,18 @@ int aquakv_fit_predictor(int32_t dtype, int64_t tokens, const void* x0, int32_t 
   return AQUAKV_OK;
 }
 
+int aquakv_copy_ranges(const aquakv_copy_range* ranges, int32_t n, void* stream) {
+  if (n < 0) return fail(AQUAKV_EINVAL, "n=%d", n);
+  if (n == 0) return AQUAKV_OK;
+  if (ranges == nullptr) return fail(AQUAKV_ENULL, "ranges is NULL");
+  static_assert(sizeof(aquakv_copy_range) == sizeof(aquakv::CopyRange), "same layout");
+  for (int32_t i = 0; i < n; ++i)
+    if (ranges[i].bytes != 0 && (ranges[i].dst == nullptr || ranges[i].src == nullptr))
+      return fail(AQUAKV_ENULL, "range %d has a NULL pointer", i);
+  HIP_TRY(aquakv::launch_copy_ranges(reinterpret_cast<const aquakv::CopyRange*>(ranges), n, static_cast<hipStream_t>(stream)));
+  return AQUAKV_OK;
+}
+
 size_t aquakv_scores_workspace_bytes(const aquakv_layer* L, int32_t batch, int32_t q_heads) {
   if (check_layer(L) != AQUAKV_OK || batch < 1 || q_heads < 1) return 0;
   if (L->dtype != AQUAKV_BF16 || is_wide(L) || !aquakv::folded_scores_supported(L->kv_heads, L->d_in_k, q_heads)) return 0;

@@ -126,4 +126,9 @@ hipError_t launch_fit_predictor(int dtype, int64_t tokens, const void* x0, int d
                                 int d_out, double rate, void* W, double* W64, float* bias, void* workspace,
                                 hipStream_t stream);
 
+// Device-to-device copies of n byte ranges, kCopyRangesPerLaunch per launch (3 KiB of kernel arguments).
+struct CopyRange { void* dst; const void* src; size_t bytes; };
+constexpr int kCopyRangesPerLaunch = 128;
+hipError_t launch_copy_ranges(const CopyRange* ranges, int n, hipStream_t stream);
+
 }  // namespace aquakv
