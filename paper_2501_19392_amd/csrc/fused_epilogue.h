@@ -97,7 +97,7 @@ __device__ __forceinline__ void dequantize_across_heads(const WideCodes<NCW>& wc
 // Grouped-query scores of one decoded key row of kv head `head` (the quad's 4 x 32 values in v, unrounded):
 //   scores[b, qh, t] = score_scale * sum_d q[b, qh, d] * round_bf16(v)[d]   for the q_heads / H query heads of the head,
 // the key rotated by its position t first when rope_cos is given (caches that hold keys from before the rotary
-// embedding, Sect. 3.3).  Row index rowc = b * seq_len + t.
+// embedding, Sect. 3.3).  The row is token t of sequence b.
 // q_lds (nullable): the queries of this row's sequence for the query heads of `head`, staged by the caller as fp32,
 // kQueryLdsStride floats per query head, quad position q at float q * kQueryLdsQuad (stage_queries below); the same
 // values as in memory, so the same bits either way.
@@ -130,14 +130,13 @@ struct QueryStage {
   }
 };
 
-__device__ __forceinline__ void score_row(float (&v)[32], int q, int head, int H, int q_heads, int seq_len, int64_t rowc,
-                                          bool active, const bf16_t* __restrict__ qv, float score_scale,
+__device__ __forceinline__ void score_row(float (&v)[32], int q, int head, int H, int q_heads, int64_t b, int64_t t,
+                                          int seq_len, bool active, const bf16_t* __restrict__ qv, float score_scale,
                                           float* __restrict__ scores, const float* __restrict__ rope_cos,
                                           const float* __restrict__ rope_sin, const float* q_lds = nullptr) {
 #pragma unroll
   for (int r = 0; r < 32; ++r) v[r] = Storage<bf16_t>::round(v[r]);      // score the stored keys
   const int rep = q_heads / H;
-  const int64_t b = rowc / seq_len, t = rowc % seq_len;
   if (rope_cos != nullptr) rope128(v, q, rope_cos + t * (kGroup / 2), rope_sin + t * (kGroup / 2));
   for (int r = 0; r < rep; ++r) {
     const int qh = head * rep + r;

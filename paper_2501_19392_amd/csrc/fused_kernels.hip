@@ -12,6 +12,7 @@
 // Arithmetic is the same as in the stand-alone kernels (same main loop, same group bodies,
 // prediction carried in fp32), so fused and unfused paths give identical bits.
 #include "fused_epilogue.h"
+#include "fused_tile.h"
 #include "gemm_core.h"
 #include "kernels.h"
 
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(WAVES * 64) void fused_kernel(
         }
       }
       if constexpr (MODE == kScores)
-        score_row(v, q, head, H, q_heads, seq_len, rowc, active, qv, score_scale, scores, rope_cos, rope_sin,
+        score_row(v, q, head, H, q_heads, rowc / seq_len, rowc % seq_len, seq_len, active, qv, score_scale, scores, rope_cos, rope_sin,
                   queries.staged ? q_lds : nullptr);
     }
   };
@@ -338,12 +339,57 @@ hipError_t launch(int n_codewords, const void* x0, int d0, const void* x1, int d
   return hipGetLastError();
 }
 
+// Rows per tile (fused_tile.h) of a launch over n_seq sequences of seq_len rows (one sequence for encode and decode);
+// 0: the tiles of 256 rows x one or two heads.
+//
+// A CU holds one workgroup, so what counts is the rounds of workgroups over the CUs and the rows of a round.  Ranges that
+// fill the chip in one round take the smallest tile that still does: encode of 1024 tokens x 8 heads (keys / values) 11.1 /
+// 15.9 us on 32 rows, 11.8 / 17.8 on 64, 18.1 / 26 on 128, 23 / 32 on 256; 2048 tokens: 13.2 / 19.7 on 64 against 24 / 33.7;
+// 4096 tokens: 20.6 / 28.8 on 128 against 26.1 / 35.  Beyond that 320 rows x one head fill the gap where the tiles of 256
+// rows start a round they hardly use (10007 tokens: 41.1 / 57.8 us against 45.6 / 62.4; 20000 tokens: 81 / 115 against
+// 87 / 122): taken when its rounds cost less, a round being 41 us on 320 rows, 29 us on 256 rows (33 the first) and 54 us on
+// 256 rows x two heads (K = 1024, encode; decode has the same proportions).
+int tile_rows(int64_t n_seq, int64_t seq_len, int D, bool two_heads) {
+  constexpr int64_t kCUs = 256;                      // MI355X
+  const int64_t H = D / BN;
+  const auto tiles = [&](int64_t rows) { return n_seq * ((seq_len + rows - 1) / rows) * H; };
+  const auto rounds = [&](int64_t t) { return (t + kCUs - 1) / kCUs; };
+  for (const int rows : {32, 64, 128})
+    if (tiles(rows) <= kCUs) return rows;
+  const int64_t all = (n_seq * seq_len + BM - 1) / BM;    // tiles of 256 rows may straddle sequences
+  int64_t other = 29 * rounds(all * H) + 4;
+  if (two_heads && D % 256 == 0 && 54 * rounds(all * H / 2) < other) other = 54 * rounds(all * H / 2);
+  return 41 * rounds(tiles(320)) < other ? 320 : 0;
+}
+hipError_t launch_rows(int rows, int mode, int n_codewords, bool wide, int n_seq, const TileArgs& a, hipStream_t stream) {
+  if (rows == 32) return launch_tile_32(mode, n_codewords, wide, n_seq, a, stream);
+  if (rows == 64) return launch_tile_64(mode, n_codewords, wide, n_seq, a, stream);
+  if (rows == 128) return launch_tile_128(mode, n_codewords, wide, n_seq, a, stream);
+  return launch_tile_320(mode, n_codewords, wide, n_seq, a, stream);
+}
+TileArgs tile_args(const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias, const int8_t* signs,
+                   const float* codebook, int D) {
+  TileArgs a = {};
+  a.x0 = static_cast<const bf16_t*>(x0); a.d0 = d0;
+  a.x1 = static_cast<const bf16_t*>(x1); a.d1 = d1;
+  a.W = static_cast<const bf16_t*>(W); a.bias = bias;
+  a.signs = signs; a.codebook = codebook; a.D = D;
+  return a;
+}
+
 }  // namespace
 
 hipError_t launch_fused_encode(int n_codewords, const void* x0, int d0, const void* x1, int d1, const void* W,
                                const float* bias, const int8_t* signs, const float* codebook, const void* table,
                                const void* X, uint8_t* codes, uint16_t* scales, void* Xhat, int64_t T, int D,
                                hipStream_t stream) {
+  if (T == 0) return hipSuccess;
+  if (const int rows = tile_rows(1, T, D, true)) {
+    TileArgs a = tile_args(x0, d0, x1, d1, W, bias, signs, codebook, D);
+    a.table = static_cast<const uint32_t*>(table); a.X = static_cast<const bf16_t*>(X);
+    a.codes = codes; a.scales = scales; a.Xhat = static_cast<bf16_t*>(Xhat); a.seq_len = (int)T;
+    return launch_rows(rows, kTileEncode, n_codewords, false, 1, a, stream);
+  }
   if (two_heads_pays(T, D))
     return launch_fused_encode_two_heads(n_codewords, x0, d0, x1, d1, W, bias, signs, codebook, table, X, codes, scales,
                                          Xhat, T, D, stream);
@@ -354,6 +400,13 @@ hipError_t launch_fused_encode(int n_codewords, const void* x0, int d0, const vo
 hipError_t launch_fused_decode(int n_codewords, const void* x0, int d0, const void* x1, int d1, const void* W,
                                const float* bias, const int8_t* signs, const float* codebook, const uint8_t* codes,
                                const uint16_t* scales, void* Xhat, int64_t T, int D, bool wide, hipStream_t stream) {
+  if (T == 0) return hipSuccess;
+  if (const int rows = tile_rows(1, T, D, true)) {
+    TileArgs a = tile_args(x0, d0, x1, d1, W, bias, signs, codebook, D);
+    a.codes = const_cast<uint8_t*>(codes); a.scales = const_cast<uint16_t*>(scales);
+    a.Xhat = static_cast<bf16_t*>(Xhat); a.seq_len = (int)T;
+    return launch_rows(rows, kTileDecode, n_codewords, wide, 1, a, stream);
+  }
   if (two_heads_pays(T, D))
     return launch_fused_decode_two_heads(n_codewords, x0, d0, x1, d1, W, bias, signs, codebook, codes, scales, Xhat, T, D,
                                          wide, stream);
@@ -367,6 +420,14 @@ hipError_t launch_fused_scores(int n_codewords, const void* x0, int d0, const vo
                                const uint16_t* scales, const void* q, float score_scale, float* scores, void* Khat_out,
                                int seq_len, int q_heads, int64_t T, int D, const float* rope_cos, const float* rope_sin,
                                bool wide, hipStream_t stream) {
+  if (T == 0) return hipSuccess;
+  if (const int rows = tile_rows(T / seq_len, seq_len, D, !wide)) {
+    TileArgs a = tile_args(x0, d0, nullptr, 0, W, bias, signs, codebook, D);
+    a.codes = const_cast<uint8_t*>(codes); a.scales = const_cast<uint16_t*>(scales);
+    a.Xhat = static_cast<bf16_t*>(Khat_out); a.seq_len = seq_len; a.q = static_cast<const bf16_t*>(q);
+    a.q_heads = q_heads; a.score_scale = score_scale; a.scores = scores; a.rope_cos = rope_cos; a.rope_sin = rope_sin;
+    return launch_rows(rows, kTileScores, n_codewords, wide, (int)(T / seq_len), a, stream);
+  }
   // (groups across the heads: the scoring variant of the large tile spills and is slower than this one, 120 against 109 us)
   if (!wide && two_heads_pays(T, D))
     return launch_fused_scores_two_heads(n_codewords, x0, d0, W, bias, signs, codebook, codes, scales, q, score_scale,

@@ -1,0 +1,216 @@
+// Fused predictor kernels (Alg. "encode" / "decode" of the AQUA-KV paper: predictor of Sect. 3.2, backbone of Sect. 2) on
+// tiles of 32, 64, 128 or 320 token rows x one kv head (which one: tile_rows in fused_kernels.hip).
+//
+// Same main-loop bits (gemm_tile.h), same group bodies, hence the same results.  The epilogue parks up to 128 rows of the
+// tile at a time (64 with four waves) and works on them 16 groups per wave, one group per quad of lanes.
+#pragma once
+#include "fused_epilogue.h"
+#include "gemm_tile.h"
+#include "kernels.h"
+
+namespace aquakv {
+
+enum TileMode : int { kTileEncode = 0, kTileDecode = 1, kTileScores = 2, kTilePredict = 3 };
+
+struct TileArgs {
+  const bf16_t* x0;
+  const bf16_t* x1;
+  const bf16_t* W;
+  const float* bias;
+  const int8_t* signs;
+  const float* codebook;
+  const uint32_t* table;
+  const bf16_t* X;
+  uint8_t* codes;
+  uint16_t* scales;
+  bf16_t* Xhat;
+  float* P;                       // kTilePredict: the prediction, [T, D]
+  const bf16_t* q;
+  const float* rope_cos;
+  const float* rope_sin;
+  float* scores;
+  float score_scale;
+  int d0, d1, D, q_heads;
+  int seq_len;                    // rows per sequence (one sequence: all rows)
+  int tiles_per_seq;              // tiles never straddle sequences
+};
+
+template <int NCW, int MODE, int MB, bool WIDE>
+__global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(MB == 1 ? 1 : 2))) void fused_tile_kernel(const TileArgs a) {
+  using S = Tile<MB>;
+  static_assert(!WIDE || MODE != kTileEncode, "the quantizer needs the whole group: groups across the heads are not fused");
+  constexpr int kParkRows = S::kRows < 16 * S::kWaves ? S::kRows : 16 * S::kWaves;   // one pass of 16 groups per wave
+  constexpr int kParks = (S::kRows + kParkRows - 1) / kParkRows;
+  constexpr int kParkBlocks = kParkRows / 32 / S::WM;           // blocks of a wave's accumulators per park
+  constexpr bool kEpilogue = MODE != kTilePredict;
+  constexpr int kEpilogueBytes = kEpilogue ? (int)sizeof(Lds) + kParkRows * kLdP * 4 : 0;
+  constexpr int kBytes = kEpilogueBytes > S::kLdsBytes ? kEpilogueBytes : S::kLdsBytes;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[kBytes];
+  Lds& cl = *reinterpret_cast<Lds*>(smem);                      // grid and table at the start of the LDS (codec_core.h)
+  float* const park = reinterpret_cast<float*>(smem + sizeof(Lds));
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int H = a.D / kGroup;
+  // Which tile: while the predictor is larger than the rows (T <= D), the tiles of a head stay together on one XCD
+  // (consecutive workgroups go to consecutive XCDs, so the plain order does that for 8 heads) and each XCD's L2 fetches
+  // one head's slice of W once; beyond that the tiles of a row block stay together (remap_block).
+  const int nblocks = (int)gridDim.x;
+  const int logical = nblocks * S::kRows <= a.D * H ? (int)blockIdx.x : remap_block(blockIdx.x, nblocks);
+  const int head = logical % H, tile_m = logical / H;
+  const int b = tile_m / a.tiles_per_seq, t0 = (tile_m % a.tiles_per_seq) * S::kRows;
+  const int left = a.seq_len - t0;
+  const int n_rows = left < S::kRows ? left : S::kRows;         // valid rows of this tile
+  const int64_t m0 = (int64_t)b * a.seq_len + t0;               // its first row
+  const int n0 = head * kGroup;
+  const int q = lane & 3;
+
+  // everything the epilogue reads from memory is requested before the main loop and waits in registers
+  constexpr bool kEnc = MODE == kTileEncode;
+  constexpr bool kWideGrid = WIDE && !is_rtn(NCW) && kEpilogue;
+  struct In { u32x4 x[kEnc ? 4 : 1]; CodeWords w; };
+  // several parks: the inputs of the first are requested ahead of the main loop, those of each next one during the one
+  // before (the accumulators leave no registers for more)
+  In in[2];
+  WideCodes<NCW> wide[kWideGrid ? 2 : 1];
+  float cb_a = 0.f, cb_b = 0.f;
+  TableRegs<S::kThreads> table_regs;
+  const bool use_table = kEnc && !is_rtn(NCW) && a.table != nullptr;
+  constexpr int kGridPoints = is_rtn(NCW) || !kEpilogue ? 0 : NCW;
+  static_assert(kGridPoints <= S::kThreads, "one grid point per thread");
+  u32x2 qreg = {0, 0};
+  const int rep = MODE == kTileScores ? a.q_heads / H : 0;
+  const auto fetch = [&](int h) {
+    const int lrow = h * kParkRows + wave * 16 + (lane >> 2);
+    const int64_t row = m0 + (lrow < n_rows ? lrow : n_rows - 1);
+    if constexpr (kEnc) {
+      const u32x4* src = reinterpret_cast<const u32x4*>(a.X + row * a.D + n0 + q * kValsPerLane);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) in[h & 1].x[k] = src[k];
+    } else {
+      in[h & 1].w = request_words<NCW, WIDE>(a.codes, a.scales, row * H + head, q);
+      if constexpr (kWideGrid) request_wide_codes<NCW>(a.codes, row, q, wide[h & 1]);
+    }
+  };
+  if constexpr (kEpilogue) {
+    if ((int)threadIdx.x < kGridPoints) { cb_a = a.codebook[2 * threadIdx.x]; cb_b = a.codebook[2 * threadIdx.x + 1]; }
+    if (use_table) table_regs.request(a.table);
+    if constexpr (MODE == kTileScores) {
+      // the queries of this head (at most 8 x 128, adjacent in memory), 4 values per thread
+      if ((int)threadIdx.x * 4 < rep * kGroup)
+        qreg = *reinterpret_cast<const u32x2*>(a.q + ((int64_t)b * a.q_heads + head * rep) * kGroup + threadIdx.x * 4);
+    }
+    fetch(0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+
+  f32x16 acc[S::MI];
+  TileLoop<MB>::run(smem, a.x0 + m0 * a.d0, a.d0, a.d1 ? a.x1 + m0 * a.d1 : a.x1, a.d1,
+                    a.W + (int64_t)n0 * (a.d0 + a.d1), n_rows - 1, acc);
+
+  const int wm = wave / S::WN, wn = wave % S::WN;
+  const int frow = lane & 31, fk = lane >> 5;
+  const float bv = a.bias != nullptr ? a.bias[n0 + wn * 32 + frow] : 0.f;
+
+  if constexpr (!kEpilogue) {
+#pragma unroll
+    for (int i = 0; i < S::MI; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int lrow = S::block_row(i, wm) + (r >> 2) * 8 + fk * 4 + (r & 3);
+        if (lrow < n_rows) a.P[(m0 + lrow) * a.D + n0 + wn * 32 + frow] = acc[i][r] + bv;
+      }
+    return;
+  } else {
+    float sf[32] = {};
+    if constexpr (!is_rtn(NCW)) load_signs(a.signs, head, q, sf);
+    float* const q_lds = reinterpret_cast<float*>(cl.table);    // (no cell table in scores mode)
+    __syncthreads();                                            // every wave is done reading the ring
+    if ((int)threadIdx.x < kGridPoints)
+      cl.cb[threadIdx.x] = make_float4(cb_a, cb_b, -0.5f * (cb_a * cb_a + cb_b * cb_b), 0.f);
+    if (use_table) table_regs.store(cl.table);
+    if constexpr (MODE == kTileScores) {
+      if ((int)threadIdx.x * 4 < rep * kGroup) {
+        const int e = threadIdx.x * 4, qh = e / kGroup, d = e % kGroup;
+        f32x4 f;
+        f.x = __uint_as_float(qreg.x << 16); f.y = __uint_as_float(qreg.x & 0xffff0000u);
+        f.z = __uint_as_float(qreg.y << 16); f.w = __uint_as_float(qreg.y & 0xffff0000u);
+        *reinterpret_cast<f32x4*>(q_lds + qh * kQueryLdsStride + (d / kValsPerLane) * kQueryLdsQuad + d % kValsPerLane) = f;
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < kParks; ++h) {
+      if (h > 0) __syncthreads();                               // the previous rows have been consumed
+      const int here = S::kRows - h * kParkRows < kParkRows ? S::kRows - h * kParkRows : kParkRows;   // rows of this park
+#pragma unroll
+      for (int k = 0; k < kParkBlocks; ++k) {
+        const int i = h * kParkBlocks + k;
+        if (i >= S::MI) break;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          park[(S::block_row(k, wm) + (r >> 2) * 8 + fk * 4 + (r & 3)) * kLdP + park_col(wn * 32 + frow)] = acc[i][r] + bv;
+      }
+      if (h + 1 < kParks) fetch(h + 1);
+      __syncthreads();
+      if (wave * 16 < here) {                                   // (a park of fewer rows: the first waves)
+        const int prow = wave * 16 + (lane >> 2), lrow = h * kParkRows + prow;
+        const bool active = lrow < n_rows;
+        const int64_t rowc = m0 + (active ? lrow : n_rows - 1);
+        const int64_t gid = rowc * H + head;
+        const int64_t off = rowc * a.D + n0 + q * kValsPerLane;
+        float p[32], v[32];
+        read_parked(park + prow * kLdP, q, p);
+        if constexpr (kEnc) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) unpack_bf16x8(in[h & 1].x[k], &v[8 * k]);
+          quantize_group<NCW>(v, p, sf, q, cl.cb, use_table ? cl.table : nullptr, active, gid, a.codes, a.scales,
+                              a.Xhat != nullptr);
+        } else if constexpr (kWideGrid) {
+          dequantize_across_heads<NCW>(wide[h & 1], in[h & 1].w.scale, head, q, p, sf, cl.cb, v);
+        } else {
+          dequantize_words<NCW>(in[h & 1].w, p, sf, q, cl.cb, v);
+        }
+        if (a.Xhat != nullptr && active) Storage<bf16_t>::store32(a.Xhat + off, v);
+        if constexpr (MODE == kTileScores)
+          score_row(v, q, head, H, a.q_heads, b, t0 + (active ? lrow : n_rows - 1), a.seq_len, active, a.q, a.score_scale,
+                    a.scores, a.rope_cos, a.rope_sin, q_lds);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
+// rows per tile 32, 64, 128 or 320 (one translation unit each); a.tiles_per_seq is filled in
+#define AQUAKV_TILE_LAUNCHER(ROWS) \
+  hipError_t launch_tile_##ROWS(int mode, int n_codewords, bool wide, int n_seq, const TileArgs& a, hipStream_t stream)
+AQUAKV_TILE_LAUNCHER(32);
+AQUAKV_TILE_LAUNCHER(64);
+AQUAKV_TILE_LAUNCHER(128);
+AQUAKV_TILE_LAUNCHER(320);
+
+template <int MB>
+hipError_t launch_tile(int mode, int n_codewords, bool wide, int n_seq, TileArgs a, hipStream_t stream) {
+  using S = Tile<MB>;
+  a.tiles_per_seq = (a.seq_len + S::kRows - 1) / S::kRows;
+  const unsigned blocks = (unsigned)((int64_t)n_seq * a.tiles_per_seq * (a.D / kGroup));
+#define AQUAKV_TILE(N, MODE, WIDE) fused_tile_kernel<N, MODE, MB, WIDE><<<blocks, S::kThreads, 0, stream>>>(a)
+#define AQUAKV_TILE_N(MODE, WIDE)                                  \
+  do {                                                             \
+    if (n_codewords == kRtn2) AQUAKV_TILE(kRtn2, MODE, WIDE);      \
+    else if (n_codewords == kRtn4) AQUAKV_TILE(kRtn4, MODE, WIDE); \
+    else if (n_codewords == 16) AQUAKV_TILE(16, MODE, WIDE);       \
+    else if (n_codewords == 64) AQUAKV_TILE(64, MODE, WIDE);       \
+    else AQUAKV_TILE(256, MODE, WIDE);                             \
+  } while (0)
+  if (mode == kTilePredict) AQUAKV_TILE(16, kTilePredict, false);
+  else if (mode == kTileEncode) AQUAKV_TILE_N(kTileEncode, false);
+  else if (mode == kTileDecode && wide) AQUAKV_TILE_N(kTileDecode, true);
+  else if (mode == kTileDecode) AQUAKV_TILE_N(kTileDecode, false);
+  else if (wide) AQUAKV_TILE_N(kTileScores, true);
+  else AQUAKV_TILE_N(kTileScores, false);
+#undef AQUAKV_TILE_N
+#undef AQUAKV_TILE
+  return hipGetLastError();
+}
+
+}  // namespace aquakv

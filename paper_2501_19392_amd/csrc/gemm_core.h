@@ -27,6 +27,16 @@ constexpr int kMainLoopLdsBytes = kStages * kStageBytes;
 // same K order per output element, so they give identical bits.
 constexpr int kGemmThreads = 256;                // the 4-wave shape (stand-alone predictor kernel)
 
+// After the last MFMA of a main loop: its results reach the accumulators 8 passes (32 cycles) later, and vector
+// instructions that read them sooner see old values.  The compiler counts these wait states, but was seen to miss a short
+// path (the branch around an absent bias: the last registers of the accumulators were read too early), so every main
+// loop ends with them spelled out.
+__device__ __forceinline__ void settle_accumulators() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // 16-byte chunk `ch` (0..7) of LDS row `row`.  A row is 128 B = half of the 64 banks, so even
 // and odd rows already sit in different bank halves; the chunk is XOR-swizzled with row/2 so
 // that the 16 lanes served together by a 128-bit fragment read (16 consecutive rows, same
@@ -235,6 +245,7 @@ __device__ __forceinline__ void gemm_mainloop(unsigned char* lds_base, const bf1
   }
   mma8(f[2], [&](int) {});                           // (nk-1, steps 2 and 3)
   mma8(f[3], [&](int) {});
+  settle_accumulators();
 }
 
 }  // namespace aquakv

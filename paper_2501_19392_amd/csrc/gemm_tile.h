@@ -1,0 +1,204 @@
+// bf16 MFMA main loop of the linear predictors (Sect. 3.2 of the AQUA-KV paper) for tiles of 32, 64, 128 or 320 token
+// rows x 128 outputs (one kv head): the shapes a launch picks from so that its tiles fill the CUs evenly.
+//
+// Same instruction (v_mfma_f32_32x32x16_bf16), operand orientation, swizzled LDS layout, direct-to-LDS loads and K order
+// per output as gemm_core.h, hence the same bits.  One workgroup per CU (64 rows and fewer: sometimes two).
+//   * Up to 64 rows: four waves split the 128 columns, every wave holds all rows.  Such a tile is bound by the stream of
+//     operands from L2, (rows + 128) x 128 bytes per k-tile of 64, most of it W: a deep ring of k-tiles in LDS keeps it
+//     coming, and a wave reads the fragments of a whole k-tile ahead (its steps of 16 k are one or two MFMAs long).
+//     Measured with 32 rows: 0.18 us per k-tile = 57 bytes per cycle into a CU, of 64; a 256-row tile takes 0.6 to 0.9.
+//   * From 128 rows on: eight waves (two per SIMD) as 2 x 4, wave (wm, wn) holds columns 32 wn ... and every second block
+//     of 32 rows: (MI + 1) / MI operand reads per MFMA, MI = rows / 64.
+#pragma once
+#include "gemm_core.h"
+
+namespace aquakv {
+
+template <int MB> struct TileShape;                   // MB = 32-row blocks of the tile
+template <> struct TileShape<1> { static constexpr int kStages = 7; };       // x 20 KiB
+template <> struct TileShape<2> { static constexpr int kStages = 3; };       // x 24 KiB: two workgroups fit a CU
+template <> struct TileShape<4> { static constexpr int kStages = 4; };       // x 32 KiB
+template <> struct TileShape<10> { static constexpr int kStages = 2; };      // x 56 KiB
+template <int MB> struct Tile : TileShape<MB> {
+  static constexpr int kRows = 32 * MB;
+  static constexpr int WM = MB < 4 ? 1 : 2, WN = 4;
+  static constexpr int kWaves = WM * WN, kThreads = kWaves * 64;
+  static constexpr int MI = MB / WM;                  // 32-row blocks per wave
+  static constexpr int kAhead = MB < 4 ? 4 : 1;       // fragments are read this many steps of 16 k ahead
+  static constexpr int kATile = kRows * kRowBytes;
+  static constexpr int kStage = kATile + 128 * kRowBytes;
+  static constexpr int kLdsBytes = TileShape<MB>::kStages * kStage;
+  // first row of block i of the waves with this wm
+  static constexpr int block_row(int i, int wm) { return (i * WM + wm) * 32; }
+};
+
+// s_waitcnt vmcnt(n) lgkmcnt(0), n < 64
+template <int N> __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14)); }
+
+// acc[i]: the 32 x 32 block at rows block_row(i, wm), columns 32 wn of the tile, wm = wave / 4, wn = wave % 4 (layout inside
+// the block as in gemm_core.h).  x0 / x1 point at the tile's first row; `last`: index of its last valid row (rows behind it
+// are read as that row).  W points at the tile's first output row.  Requires K = d0 + d1 a multiple of 128, d0 of 64.
+// Ends with every LDS read of the calling wave returned; the caller puts a barrier before it reuses the LDS.
+// The counts of loads in flight assume that nothing but this loop issues global loads while it runs.
+template <int MB> struct TileLoop {
+  using S = Tile<MB>;
+  static __device__ __forceinline__ void run(unsigned char* lds_base, const bf16_t* __restrict__ x0, int d0,
+                                             const bf16_t* __restrict__ x1, int d1, const bf16_t* __restrict__ W, int last,
+                                             f32x16 (&acc)[S::MI]);
+};
+template <int MB>
+__device__ __forceinline__ void TileLoop<MB>::run(unsigned char* lds_base, const bf16_t* __restrict__ x0, int d0,
+                                                  const bf16_t* __restrict__ x1, int d1, const bf16_t* __restrict__ W,
+                                                  int last, f32x16 (&acc)[S::MI]) {
+  constexpr int kRowsPerPiece = S::kThreads / 8;      // tile rows one load instruction of the workgroup fills
+  constexpr int kPieceBytes = S::kThreads * 16;
+  constexpr int kA = S::kRows / kRowsPerPiece, kB = 128 / kRowsPerPiece, kPieces = kA + kB;
+  constexpr int kStages = S::kStages, kAhead = S::kAhead, MI = S::MI;
+  constexpr int kBufs = kAhead == 1 ? 2 : kAhead;
+  static_assert(kA * kRowsPerPiece == S::kRows && kPieces * (kStages - 1) < 64, "whole pieces; vmcnt range");
+  typedef __attribute__((address_space(3))) unsigned char* lptr_t;
+  typedef const __attribute__((address_space(1))) char* gptr_t;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / S::WN, wn = wave % S::WN;
+  const int K = d0 + d1, nk = K / BK;
+
+  const int ch16 = ((tid & 7) ^ ((tid >> 4) & 7)) * 16;
+  int rowc[kA];
+#pragma unroll
+  for (int pc = 0; pc < kA; ++pc) {
+    const int row = (tid >> 3) + pc * kRowsPerPiece;
+    rowc[pc] = row < last ? row : last;
+  }
+  const uint32_t offW = (uint32_t)(tid >> 3) * (uint32_t)(K * 2) + ch16;
+  const auto uniform_ptr = [](const char* p) {
+    const uint64_t u = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+    return (gptr_t)(((uint64_t)hi << 32) | lo);
+  };
+  const lptr_t lds3 = (lptr_t)lds_base;
+  auto load_piece = [&](int kt, int stage_off, int pc) {
+    const int k0 = kt * BK;
+    const lptr_t dst = lds3 + (stage_off + wave * 1024 + pc * kPieceBytes);     // x pieces fill the A tile, W pieces follow
+    if (pc < kA) {
+      const bool second = k0 >= d0;
+      const int ld2 = __builtin_amdgcn_readfirstlane((second ? d1 : d0) * 2);
+      const gptr_t xb = uniform_ptr(reinterpret_cast<const char*>(second ? x1 : x0) + (int64_t)(second ? k0 - d0 : k0) * 2);
+      __builtin_amdgcn_global_load_lds(xb + ((uint32_t)__umul24(rowc[pc], ld2) + ch16), dst, 16, 0, 0);
+    } else {
+      const gptr_t wb = uniform_ptr(reinterpret_cast<const char*>(W) + ((int64_t)k0 * 2 + (int64_t)(pc - kA) * kRowsPerPiece * K * 2));
+      __builtin_amdgcn_global_load_lds(wb + offW, dst, 16, 0, 0);
+    }
+  };
+
+  struct Frag { bf16x8 v[MI + 1]; };
+  const int frow = lane & 31, fk = lane >> 5;
+  auto frag_piece = [&](int stage_off, int ks, Frag& f, int pc) {
+    const int off = pc < MI ? lds_off(S::block_row(pc, wm) + frow, ks * 2 + fk) : S::kATile + lds_off(wn * 32 + frow, ks * 2 + fk);
+    f.v[pc] = *reinterpret_cast<const bf16x8*>(lds_base + stage_off + off);
+  };
+  auto read_frag = [&](int stage_off, int ks, Frag& f) {
+#pragma unroll
+    for (int pc = 0; pc <= MI; ++pc) frag_piece(stage_off, ks, f, MI - pc);     // the W fragment first
+  };
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+  // the MFMAs of one step; extra(m) is issued right behind MFMA m (sched_barrier keeps the order)
+  auto mma = [&](const Frag& f, auto&& extra) {
+#pragma unroll
+    for (int m = 0; m < MI; ++m) {
+      acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v[m], f.v[MI], acc[m], 0, 0, 0);
+      extra(m);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // at most `tiles` newer k-tiles may still be on their way (loads complete in issue order)
+  auto wait_tiles = [&](int tiles) {
+    if (tiles <= 0) wait_loads<0>();
+    else if (tiles == 1) wait_loads<kPieces>();
+    else if (kStages > 4 && tiles == 2) wait_loads<2 * kPieces % 64>();
+    else if (kStages > 5 && tiles == 3) wait_loads<3 * kPieces % 64>();
+    else if (kStages > 6 && tiles == 4) wait_loads<4 * kPieces % 64>();
+    else wait_loads<(kStages - 2) * kPieces>();
+  };
+  auto meet = [&] {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  const int first = nk < kStages ? nk : kStages;
+#pragma unroll
+  for (int t = 0; t < kStages; ++t)
+    if (t < first) {
+#pragma unroll
+      for (int pc = 0; pc < kPieces; ++pc) load_piece(t, t * S::kStage, pc);
+    }
+  // tile 0 has landed: `first` - 1 newer ones may be out
+  if (first == kStages) wait_loads<(kStages - 1) * kPieces>();
+  else wait_tiles(first - 1);
+  meet();
+  Frag f[kBufs];
+#pragma unroll
+  for (int s = 0; s < kAhead; ++s) read_frag(0, s, f[s]);
+  __builtin_amdgcn_sched_barrier(0);
+
+  // k-tile t sits in the stage at `cur`, t + 1 in the one at `nxt`.  Before the step that first reads k-tile t + 1 it is
+  // published; by then every wave's reads of tile t have returned, so its stage takes tile t + kStages.
+  auto tile = [&](int t, int cur, int nxt, bool has_next, bool steady, bool do_load) {
+    const auto publish = [&] {
+      if (steady) wait_loads<(kStages - 2) * kPieces>();
+      else wait_tiles(nk - 2 - t);
+      meet();
+    };
+    if constexpr (kAhead == 4) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        if (s == 0 && has_next) {
+          publish();
+          if (do_load) {
+#pragma unroll
+            for (int pc = 0; pc < kPieces; ++pc) load_piece(t + kStages, cur, pc);
+          }
+        }
+        mma(f[s], [](int) {});
+        if (has_next) read_frag(nxt, s, f[s]);        // behind the MFMAs that used this buffer
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < 3; ++s)
+        mma(f[s & 1], [&](int m) {
+          if (2 * m <= MI) frag_piece(cur, s + 1, f[(s + 1) & 1], MI - 2 * m);
+          if (2 * m + 1 <= MI) frag_piece(cur, s + 1, f[(s + 1) & 1], MI - 2 * m - 1);
+        });
+      if (has_next) publish();
+      constexpr int kItems = MI + 1 + kPieces, kPerMma = (kItems + MI - 1) / MI;
+      mma(f[1], [&](int m) {
+#pragma unroll
+        for (int e = m * kPerMma; e < (m + 1) * kPerMma && e < kItems; ++e) {
+          if (e <= MI) { if (has_next) frag_piece(nxt, 0, f[0], MI - e); }
+          else if (do_load) load_piece(t + kStages, cur, e - MI - 1);
+        }
+      });
+    }
+  };
+  const auto step = [](int s) { return s + S::kStage == S::kLdsBytes ? 0 : s + S::kStage; };
+  int cur = 0, nxt = S::kStage, t = 0;
+  for (; t + kStages < nk; ++t) {
+    tile(t, cur, nxt, true, true, true);
+    cur = nxt; nxt = step(nxt);
+  }
+  for (; t + 1 < nk; ++t) {
+    tile(t, cur, nxt, true, false, false);
+    cur = nxt; nxt = step(nxt);
+  }
+  tile(t, cur, nxt, false, false, false);
+  settle_accumulators();
+}
+
+}  // namespace aquakv

@@ -172,6 +172,7 @@ __device__ __forceinline__ void gemm_mainloop_token_slab(unsigned char* lds_base
   tile(t, cur, true, false);                               // the last two tiles: nothing left to load
   cur ^= kSlabStageBytes;
   tile(t + 1, cur, false, false);
+  settle_accumulators();
 }
 
 }  // namespace aquakv

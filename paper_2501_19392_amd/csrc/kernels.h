@@ -58,8 +58,9 @@ hipError_t launch_fused_scores(int n_codewords, const void* x0, int d0, const vo
                                bool wide, hipStream_t stream);
 
 // The same on tiles of 256 tokens x two heads (D a multiple of 256; wide: decode only): same bits, a faster main
-// loop, half as many workgroups.  launch_fused_decode / launch_fused_scores take this form by themselves when
-// two_heads_pays(T, D): when the larger tile costs no extra round over the CUs.
+// loop, half as many workgroups.  launch_fused_encode / _decode / _scores take this form by themselves for ranges that
+// fill the chip more than once (below that: fused_tile.h) when two_heads_pays(T, D): when the larger tile costs no extra
+// round over the CUs.
 bool two_heads_pays(int64_t T, int D);
 hipError_t launch_fused_encode_two_heads(int n_codewords, const void* x0, int d0, const void* x1, int d1, const void* W,
                                          const float* bias, const int8_t* signs, const float* codebook, const void* table,

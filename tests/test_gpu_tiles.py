@@ -1,0 +1,99 @@
+"""Tiles of 32, 64, 128 and 320 token rows (short ranges, and ranges that leave a round of the large tiles nearly empty):
+encode, decode and the scoring call against the stage calls (aquakv_predict, aquakv_quantize, aquakv_dequantize), bit for
+bit, at the edges of every tile, with and without bias, for predictors as narrow as two k-tiles, all quantizers and both groupings."""
+import pytest
+import torch
+
+from tests import parity_utils as U
+
+pytestmark = pytest.mark.gpu
+bits = lambda t: t.contiguous().view(torch.uint8)
+
+
+def layer(H, dk, quantizer, rht_group=None, bias=True):
+    D = H * 128
+    kw = dict(rtn_bits=int(quantizer[3:])) if quantizer.startswith("rtn") else {}
+    if rht_group:
+        kw["rht_group"] = rht_group
+    n = 16 if quantizer.startswith("rtn") else int(quantizer[1:])
+    g = torch.Generator().manual_seed(6)
+    bk, bv = (torch.randn(D, generator=g) * 0.3 if bias else None for _ in range(2))
+    return U.make_layers(H, "bf16", n, layer_idx=1, w_k=U.random_weights(D, dk, 21, 0.7),
+                         w_v=U.random_weights(D, dk + D, 22, 0.7), b_k=bk, b_v=bv, **kw)[1]
+
+
+CASES = [(8, 1024, T) for T in (1, 31, 33, 1024, 1025, 1089, 2048, 2049, 2177, 4096, 8449)] + [
+    (3, 128, 2700), (3, 128, 33), (16, 256, 700), (1, 384, 8200), (8, 192 * 2, 129)]
+
+
+@pytest.mark.parametrize("H,dk,T", CASES)
+@pytest.mark.parametrize("quantizer,rht_group", [("n16", None), ("n64", None), ("n256", None), ("rtn2", None), ("rtn4", None),
+                                                 ("n16", 1024), ("n64", 1024), ("rtn4", 1024)])
+def test_tiles_give_the_bits_of_the_stage_calls(H, dk, T, quantizer, rht_group):
+    from paper_2501_19392_amd import binding as B
+    if rht_group and H != 8:
+        pytest.skip("groups across heads are built for 8 heads")
+    print(f"case tiles H={H} dk={dk} T={T} {quantizer} group={rht_group}", flush=True)
+    lg, D = layer(H, dk, quantizer, rht_group, bias=T % 2 == 1), H * 128
+    g = torch.Generator(device="cuda").manual_seed(300 + T)
+    mk = lambda w: torch.randn(T, w, generator=g, device="cuda").bfloat16()
+    K, V = mk(D).view(T, H, 128), mk(D).view(T, H, 128)
+    Kp, Vp = mk(dk), mk(dk)
+    poison = lambda *ts: [t.view(torch.uint8).fill_(0xAB) for t in ts]
+    (kc, ks), (vc, vs) = lg.alloc_codes(T), lg.alloc_codes(T)
+    Kh, Vh, Kd, Vd = (lg.alloc_kv(T) for _ in range(4))
+    poison(kc, ks, vc, vs, Kh, Vh, Kd, Vd)
+    ws = lg.alloc_workspace(T)
+    B.aquakv_encode_layer(lg, T, K, V, Kp, Vp, kc, ks, vc, vs, Kh, Vh, ws)
+    B.aquakv_decode_layer(lg, T, kc, ks, vc, vs, Kp, Vp, Kd, Vd, ws)
+    P = torch.empty(T, D, dtype=torch.float32, device="cuda")
+    for which, x0, x1, X, codes, scales, hat, dec in ((B.AQUAKV_KEY, Kp, None, K, kc, ks, Kh, Kd),
+                                                      (B.AQUAKV_VALUE, Vp, Kh, V, vc, vs, Vh, Vd)):
+        c2, s2 = lg.alloc_codes(T)
+        h2, d2 = lg.alloc_kv(T), lg.alloc_kv(T)
+        B.aquakv_predict(lg, which, T, x0, x1, P)
+        B.aquakv_quantize(lg, which, T, X, P, c2, s2, h2)
+        B.aquakv_dequantize(lg, which, T, c2, s2, P, d2)
+        torch.cuda.synchronize()
+        for name, a, b in (("codes", codes, c2), ("scales", scales, s2), ("encode", hat, h2), ("decode", dec, d2)):
+            assert torch.equal(bits(a), bits(b)), (which, name)
+
+
+@pytest.mark.parametrize("H,dk,batch,S", [(8, 1024, 1, 1), (8, 1024, 3, 33), (8, 1024, 5, 100), (8, 1024, 2, 1000),
+                                          (8, 1024, 3, 1100), (8, 1024, 1, 8449), (3, 128, 2, 65)])
+@pytest.mark.parametrize("quantizer,rht_group", [("n16", None), ("rtn2", None), ("n256", 1024)])
+def test_scores_of_a_batch_are_those_of_its_sequences(H, dk, batch, S, quantizer, rht_group):
+    from paper_2501_19392_amd import binding as B
+    if rht_group and H != 8:
+        pytest.skip("groups across heads are built for 8 heads")
+    print(f"case tile scores H={H} batch={batch} S={S} {quantizer} group={rht_group}", flush=True)
+    lg, D, T, QH = layer(H, dk, quantizer, rht_group, bias=S % 2 == 1), H * 128, batch * S, 4 * H
+    g = torch.Generator(device="cuda").manual_seed(70 + T)
+    K = torch.randn(T, H, 128, generator=g, device="cuda").bfloat16()
+    Kp = torch.randn(T, dk, generator=g, device="cuda").bfloat16()
+    q = torch.randn(batch, QH, 128, generator=g, device="cuda").bfloat16()
+    ang = torch.arange(S, device="cuda")[:, None] * 0.3 ** torch.arange(64, device="cuda")[None]
+    cos, sin = ang.cos().float().contiguous(), ang.sin().float().contiguous()
+    kc, ks = lg.alloc_codes(T)
+    Kh, Ko, ws = lg.alloc_kv(T), lg.alloc_kv(T), lg.alloc_workspace(T)
+    B.aquakv_encode_keys(lg, T, K, Kp, kc, ks, Kh, ws)
+    for rope in (None, (cos, sin)):
+        got = torch.full((batch, QH, S), float("nan"), device="cuda")
+        call = (lambda n, c, s, p, qq, out, ko: B.aquakv_decode_attn_scores(lg, n, S, QH, c, s, p, qq, 0.125, out, ko, ws)) if rope is None \
+            else (lambda n, c, s, p, qq, out, ko: B.aquakv_decode_attn_scores_rope(lg, n, S, QH, c, s, p, qq, cos, sin, 0.125, out, ko, ws))
+        call(batch, kc, ks, Kp, q, got, Ko)
+        torch.cuda.synchronize()
+        assert torch.equal(bits(Ko), bits(Kh))
+        keys = Kh.float().view(batch, S, H, 128)
+        if rope is not None:
+            a, b = keys[..., :64], keys[..., 64:]
+            c, s = cos[None, :, None], sin[None, :, None]
+            keys = torch.cat([a * c - b * s, b * c + a * s], -1)
+        want = (q.float().view(batch, H, 4, 1, 128) * keys.permute(0, 2, 1, 3)[:, :, None]).sum(-1).view(batch, QH, S) * 0.125
+        assert torch.allclose(got, want, rtol=1e-4, atol=1e-4 * want.abs().max().item())
+        for i in range(batch):
+            one = torch.empty(1, QH, S, device="cuda")
+            rows = slice(i * S, (i + 1) * S)
+            call(1, kc[rows].clone(), ks[rows].clone(), Kp[rows].clone(), q[i:i + 1].clone(), one, None)
+            torch.cuda.synchronize()
+            assert torch.equal(one[0], got[i]), i
