@@ -186,6 +186,11 @@ inline void* at(void* base, int64_t row, size_t row_bytes) {
   return base == nullptr ? nullptr : static_cast<unsigned char*>(base) + row * row_bytes;
 }
 
+// a tensor to be recovered from its codes
+inline aquakv::QuantizeIo coded(const int8_t* signs, const void* codes, const void* scales, void* hat) {
+  return {nullptr, signs, static_cast<uint8_t*>(const_cast<void*>(codes)), static_cast<uint16_t*>(const_cast<void*>(scales)), hat};
+}
+
 // ---- one chunk of rows [r0, r0 + n) of one tensor; pointers are the tensors' bases -------------------------------
 // keys of Alg. "encode":  K_pred = f_key(Khat_prev);  K_q = Q(K - K_pred);  khat_dst (chunk-local, nullable) = Q^-1(K_q) + K_pred
 int encode_keys_chunk(const aquakv_layer* L, const Plan& pl, int64_t r0, int64_t n, const void* K, const void* Khat_prev,
@@ -207,10 +212,10 @@ int encode_keys_chunk(const aquakv_layer* L, const Plan& pl, int64_t r0, int64_t
   if (has_k)
     HIP_TRY(aquakv::launch_predict(L->dtype, at(Khat_prev, r0, (size_t)L->d_in_k * pl.eb), L->d_in_k, nullptr, 0, L->w_k,
                                    L->b_k, Pbuf, n, pl.D, stream));
-  HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), at(K, r0, row), has_k ? Pbuf : nullptr, L->signs_k, L->codebook,
-                                  L->search_table, static_cast<uint8_t*>(at(k_codes, r0, pl.code_row)),
-                                  static_cast<uint16_t*>(at(k_scales, r0, srow)), khat_dst, n, L->kv_heads, is_wide(L),
-                                  stream));
+  const aquakv::QuantizeIo io = {at(K, r0, row), L->signs_k, static_cast<uint8_t*>(at(k_codes, r0, pl.code_row)),
+                                 static_cast<uint16_t*>(at(k_scales, r0, srow)), khat_dst};
+  HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), &io, 1, has_k ? Pbuf : nullptr, L->codebook, L->search_table, n,
+                                  L->kv_heads, is_wide(L), stream));
   return AQUAKV_OK;
 }
 
@@ -237,10 +242,10 @@ int encode_values_chunk(const aquakv_layer* L, const Plan& pl, int64_t r0, int64
   if (has_v)
     HIP_TRY(aquakv::launch_predict(L->dtype, at(Vhat_prev, r0, (size_t)(L->d_in_v - D) * pl.eb), L->d_in_v - D, khat_src, D,
                                    L->w_v, L->b_v, Pbuf, n, D, stream));
-  HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), at(V, r0, row), has_v ? Pbuf : nullptr, L->signs_v, L->codebook,
-                                  L->search_table, static_cast<uint8_t*>(at(v_codes, r0, pl.code_row)),
-                                  static_cast<uint16_t*>(at(v_scales, r0, srow)), at(Vhat, r0, row), n, L->kv_heads,
-                                  is_wide(L), stream));
+  const aquakv::QuantizeIo io = {at(V, r0, row), L->signs_v, static_cast<uint8_t*>(at(v_codes, r0, pl.code_row)),
+                                 static_cast<uint16_t*>(at(v_scales, r0, srow)), at(Vhat, r0, row)};
+  HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), &io, 1, has_v ? Pbuf : nullptr, L->codebook, L->search_table, n,
+                                  L->kv_heads, is_wide(L), stream));
   return AQUAKV_OK;
 }
 
@@ -260,9 +265,9 @@ int decode_keys_chunk(const aquakv_layer* L, const Plan& pl, int64_t r0, int64_t
   if (has_k)
     HIP_TRY(aquakv::launch_predict(L->dtype, at(Khat_prev, r0, (size_t)L->d_in_k * pl.eb), L->d_in_k, nullptr, 0, L->w_k,
                                    L->b_k, Pbuf, n, pl.D, stream));
-  HIP_TRY(aquakv::launch_dequantize(L->dtype, quantizer_id(L), static_cast<const uint8_t*>(at(k_codes, r0, pl.code_row)),
-                                    static_cast<const uint16_t*>(at(k_scales, r0, srow)), has_k ? Pbuf : nullptr, L->signs_k,
-                                    L->codebook, at(Khat, r0, row), n, L->kv_heads, is_wide(L), stream));
+  const aquakv::QuantizeIo io = coded(L->signs_k, at(k_codes, r0, pl.code_row), at(k_scales, r0, srow), at(Khat, r0, row));
+  HIP_TRY(aquakv::launch_dequantize(L->dtype, quantizer_id(L), &io, 1, has_k ? Pbuf : nullptr, L->codebook, n, L->kv_heads,
+                                    is_wide(L), stream));
   return AQUAKV_OK;
 }
 
@@ -284,9 +289,9 @@ int decode_values_chunk(const aquakv_layer* L, const Plan& pl, int64_t r0, int64
   if (has_v)
     HIP_TRY(aquakv::launch_predict(L->dtype, at(Vhat_prev, r0, (size_t)(L->d_in_v - D) * pl.eb), L->d_in_v - D,
                                    at(Khat, r0, row), D, L->w_v, L->b_v, Pbuf, n, D, stream));
-  HIP_TRY(aquakv::launch_dequantize(L->dtype, quantizer_id(L), static_cast<const uint8_t*>(at(v_codes, r0, pl.code_row)),
-                                    static_cast<const uint16_t*>(at(v_scales, r0, srow)), has_v ? Pbuf : nullptr, L->signs_v,
-                                    L->codebook, at(Vhat, r0, row), n, L->kv_heads, is_wide(L), stream));
+  const aquakv::QuantizeIo io = coded(L->signs_v, at(v_codes, r0, pl.code_row), at(v_scales, r0, srow), at(Vhat, r0, row));
+  HIP_TRY(aquakv::launch_dequantize(L->dtype, quantizer_id(L), &io, 1, has_v ? Pbuf : nullptr, L->codebook, n, L->kv_heads,
+                                    is_wide(L), stream));
   return AQUAKV_OK;
 }
 
@@ -368,9 +373,9 @@ int aquakv_quantize(const aquakv_layer* L, int which, int64_t tokens, const void
   CHECK(check_ptr(codes, "codes", true));
   CHECK(check_scales(L, scales, "scales", true));
   CHECK(check_ptr(Xhat, "Xhat", false));
-  HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), X, P, which == AQUAKV_KEY ? L->signs_k : L->signs_v,
-                                  L->codebook, L->search_table, codes, scales, Xhat, tokens, L->kv_heads, is_wide(L),
-                                  static_cast<hipStream_t>(stream)));
+  const aquakv::QuantizeIo io = {X, which == AQUAKV_KEY ? L->signs_k : L->signs_v, codes, scales, Xhat};
+  HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), &io, 1, P, L->codebook, L->search_table, tokens, L->kv_heads,
+                                  is_wide(L), static_cast<hipStream_t>(stream)));
   return AQUAKV_OK;
 }
 
@@ -383,9 +388,9 @@ int aquakv_dequantize(const aquakv_layer* L, int which, int64_t tokens, const ui
   CHECK(check_scales(L, scales, "scales", true));
   CHECK(check_ptr(P, "P", false));
   CHECK(check_ptr(Xhat, "Xhat", true));
-  HIP_TRY(aquakv::launch_dequantize(L->dtype, quantizer_id(L), codes, scales, P,
-                                    which == AQUAKV_KEY ? L->signs_k : L->signs_v, L->codebook, Xhat, tokens,
-                                    L->kv_heads, is_wide(L), static_cast<hipStream_t>(stream)));
+  const aquakv::QuantizeIo io = coded(which == AQUAKV_KEY ? L->signs_k : L->signs_v, codes, scales, Xhat);
+  HIP_TRY(aquakv::launch_dequantize(L->dtype, quantizer_id(L), &io, 1, P, L->codebook, tokens, L->kv_heads, is_wide(L),
+                                    static_cast<hipStream_t>(stream)));
   return AQUAKV_OK;
 }
 
@@ -431,6 +436,17 @@ int aquakv_encode_layer(const aquakv_layer* L, int64_t tokens, const void* K, co
   for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk) {
     const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;
     void* khat_dst = Khat != nullptr ? at(Khat, r0, row) : (has_v ? khat_tmp : nullptr);
+    if (!has_k && !has_v) {                                 // nothing passes from the keys to the values: one launch
+      const size_t srow = scale_row_bytes(L);
+      const aquakv::QuantizeIo io[2] = {
+          {at(K, r0, row), L->signs_k, static_cast<uint8_t*>(at(k_codes, r0, pl.code_row)),
+           static_cast<uint16_t*>(at(k_scales, r0, srow)), khat_dst},
+          {at(V, r0, row), L->signs_v, static_cast<uint8_t*>(at(v_codes, r0, pl.code_row)),
+           static_cast<uint16_t*>(at(v_scales, r0, srow)), at(Vhat, r0, row)}};
+      HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), io, 2, nullptr, L->codebook, L->search_table, n, L->kv_heads,
+                                      is_wide(L), stream));
+      continue;
+    }
     CHECK(encode_keys_chunk(L, pl, r0, n, K, Khat_prev, k_codes, k_scales, khat_dst, Pbuf, stream));
     CHECK(encode_values_chunk(L, pl, r0, n, V, Vhat_prev, khat_dst, v_codes, v_scales, Vhat, Pbuf, stream));
   }
@@ -472,6 +488,14 @@ int aquakv_decode_layer(const aquakv_layer* L, int64_t tokens, const uint8_t* k_
 
   for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk) {
     const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;
+    if (!has_k && want_v && !has_v) {                       // no predictors: keys and values in one launch
+      const size_t row = (size_t)pl.D * pl.eb, srow = scale_row_bytes(L);
+      const aquakv::QuantizeIo io[2] = {
+          coded(L->signs_k, at(k_codes, r0, pl.code_row), at(k_scales, r0, srow), at(Khat, r0, row)),
+          coded(L->signs_v, at(v_codes, r0, pl.code_row), at(v_scales, r0, srow), at(Vhat, r0, row))};
+      HIP_TRY(aquakv::launch_dequantize(L->dtype, quantizer_id(L), io, 2, nullptr, L->codebook, n, L->kv_heads, is_wide(L), stream));
+      continue;
+    }
     CHECK(decode_keys_chunk(L, pl, r0, n, k_codes, k_scales, Khat_prev, Khat, Pbuf, stream));
     if (want_v) CHECK(decode_values_chunk(L, pl, r0, n, v_codes, v_scales, Vhat_prev, Khat, Vhat, Pbuf, stream));
   }

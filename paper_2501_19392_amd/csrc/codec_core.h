@@ -86,17 +86,20 @@ template <int SHIFT> __device__ __forceinline__ float4 grid_entry(const float4* 
   return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(cb) + ((uint32_t)slot << (4 - SHIFT)));
 }
 
-// Table search: score the (up to 4, ascending, last one repeated) candidates of the cell; returns the winner's slot.
-// Sets `crowded` if the cell lists too many points; the caller then redoes those of the lane's
-// sub-vectors from the cell's overflow list, or with the full search (rare; keeps the hot path small).
+// The table entry of the cell of y.
 template <int NCW>
-__device__ __forceinline__ int search_cell(float y0, float y1, const float4* cb, const uint32_t* table,
-                                           bool& crowded) {
-  constexpr int SH = Slot<NCW>::kShift;
+__device__ __forceinline__ uint32_t cell_entry(float y0, float y1, const uint32_t* table) {
   const float fx = __builtin_amdgcn_fmed3f(__fmaf_rn(y0, cell_scale(NCW), 0.5f * kCells), 0.0f, kCells - 0.5f);
   const float fy = __builtin_amdgcn_fmed3f(__fmaf_rn(y1, cell_scale(NCW), 0.5f * kCells), 0.0f, kCells - 0.5f);
-  const uint32_t e = table[(int)fy * kCells + (int)fx];
-  crowded = e >= crowded_threshold(NCW);
+  return table[(int)fy * kCells + (int)fx];
+}
+
+// Table search: score the (up to 4, ascending, last one repeated) candidates of the cell entry; returns the winner's slot.
+// If the cell lists too many points (entry >= crowded_threshold) the result is void: the caller then redoes the
+// sub-vector from the cell's overflow list, or with the full search (rare; keeps the hot path small).
+template <int NCW>
+__device__ __forceinline__ int search_cell(float y0, float y1, uint32_t e, const float4* cb) {
+  constexpr int SH = Slot<NCW>::kShift;
   int slot = e & 0xff;
   float best = score(y0, y1, grid_entry<SH>(cb, slot));
   constexpr int kCand = NCW == 16 ? 3 : 4;       // the builder marks cells of a 16-point grid with more than 3
@@ -111,128 +114,89 @@ __device__ __forceinline__ int search_cell(float y0, float y1, const float4* cb,
   return slot;
 }
 
-// Full search (the definition: all n points, lowest index wins ties) for the sub-vectors of this lane whose bit is
-// set in `mask`; writes their slots (grid points in the outer, rolled loop and 8 sub-vectors at a time, so that code
-// and live registers stay small).
-template <int NCW>
-__device__ __forceinline__ void search_full_masked(const float (&v)[32], float inv, const float4* cb, uint32_t mask,
-                                                   int (&idx)[16]) {
+// Full search (the definition: all n points, lowest index wins ties) of N sub-vectors: their slots.
+template <int NCW, int N>
+__device__ __forceinline__ void search_full(const float (&y)[2 * N], const float4* cb, int (&slot)[N]) {
+  float best[N];
+  const float4 c0 = cb[0];
+#pragma unroll
+  for (int k = 0; k < N; ++k) { best[k] = score(y[2 * k], y[2 * k + 1], c0); slot[k] = 0; }
 #pragma unroll 1
-  for (int half = 0; half < 2; ++half) {
-    float y[16], best[8];
-    int bi[8];
-    const float4 c0 = cb[0];
+  for (int j = 1; j < NCW; ++j) {
+    const float4 cj = cb[j];
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
-      // select this half's values without dynamic register indexing
-      y[2 * m] = (half ? v[16 + 2 * m] : v[2 * m]) * inv;
-      y[2 * m + 1] = (half ? v[16 + 2 * m + 1] : v[2 * m + 1]) * inv;
-      best[m] = score(y[2 * m], y[2 * m + 1], c0);
-      bi[m] = 0;
-    }
-#pragma unroll 1
-    for (int j = 1; j < NCW; ++j) {
-      const float4 cj = cb[j];
-#pragma unroll
-      for (int m = 0; m < 8; ++m) {
-        const float s = score(y[2 * m], y[2 * m + 1], cj);
-        const bool better = s > best[m];
-        best[m] = better ? s : best[m];
-        bi[m] = better ? (j << Slot<NCW>::kShift) : bi[m];
-      }
-    }
-#pragma unroll
-    for (int m = 0; m < 8; ++m) {
-      const bool take = (mask >> (8 * half + m)) & 1;
-      if (half) idx[8 + m] = take ? bi[m] : idx[8 + m];
-      else idx[m] = take ? bi[m] : idx[m];
+    for (int k = 0; k < N; ++k) {
+      const float s = score(y[2 * k], y[2 * k + 1], cj);
+      const bool better = s > best[k];
+      best[k] = better ? s : best[k];
+      slot[k] = better ? (j << Slot<NCW>::kShift) : slot[k];
     }
   }
 }
 
-// The sub-vectors of this lane whose bit is set in `mask` sit in crowded cells: those whose cell has an overflow list
-// are decided among the list's candidates (ascending, strict comparison: the lowest index wins ties, as in the full
-// search); those without get their bit in the returned mask and are left to search_full_masked.
+// A sub-vector in a crowded cell (low: the entry's lowest byte, naming its overflow list): decided among the list's
+// candidates (ascending, strict comparison: the lowest index wins ties, as in the full search), or by the full search
+// if the cell has no list.
 template <int NCW>
-__device__ __forceinline__ uint32_t search_overflow_masked(const float (&v)[32], float inv, const float4* cb,
-                                                           const uint32_t* table, uint32_t mask, int (&idx)[16]) {
+__device__ __forceinline__ int search_crowded(float y0, float y1, uint32_t low, const float4* cb, const uint32_t* table) {
   constexpr int SH = Slot<NCW>::kShift;
-  uint32_t full = 0;
-#pragma unroll 1
-  for (int half = 0; half < 2; ++half) {
-#pragma unroll
-    for (int m = 0; m < 8; ++m) {
-      const bool mine = (mask >> (8 * half + m)) & 1;
-      if (__builtin_amdgcn_ballot_w64(mine) != 0) {                  // somebody in the wave
-        const float y0 = (half ? v[16 + 2 * m] : v[2 * m]) * inv, y1 = (half ? v[16 + 2 * m + 1] : v[2 * m + 1]) * inv;
-        const float fx = __builtin_amdgcn_fmed3f(__fmaf_rn(y0, cell_scale(NCW), 0.5f * kCells), 0.0f, kCells - 0.5f);
-        const float fy = __builtin_amdgcn_fmed3f(__fmaf_rn(y1, cell_scale(NCW), 0.5f * kCells), 0.0f, kCells - 0.5f);
-        const uint32_t low = table[(int)fy * kCells + (int)fx] & 0xffu;
-        const bool listed = mine && low != slot_top(NCW);
-        full |= (mine && !listed) ? 1u << (8 * half + m) : 0u;
-        const uint32_t* list = table + kCellWords + 2 * (listed ? (int)(low >> SH) : 0);
-        // two rounds of four candidates: the four grid points of a round are fetched together (a loop over single
-        // candidates would wait for LDS eight times in a row); rolled, because this path is rare and its size is not
-        int slot = (int)(list[0] & 0xff);
-        float best = score(y0, y1, grid_entry<SH>(cb, slot));
-#pragma unroll 1
-        for (int rnd = 0; rnd < 2; ++rnd) {
-          const uint32_t w = list[rnd];
-          float4 c[4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) c[k] = grid_entry<SH>(cb, (int)((w >> (8 * k)) & 0xff));
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {                     // (the first candidate again in round 0: a tie, no change)
-            const float sc = score(y0, y1, c[k]);
-            const bool better = sc > best;
-            best = better ? sc : best;
-            slot = better ? (int)((w >> (8 * k)) & 0xff) : slot;
-          }
-          // a list ends in repeats of its last candidate: no second round if no lane of the wave has more than four
-          if (__builtin_amdgcn_ballot_w64(listed && list[1] != (w >> 24) * 0x01010101u) == 0) break;
-        }
-        if (half) idx[8 + m] = listed ? slot : idx[8 + m];
-        else idx[m] = listed ? slot : idx[m];
-      }
-    }
+  if (low == slot_top(NCW)) {
+    const float y[2] = {y0, y1};
+    int all[1];
+    search_full<NCW, 1>(y, cb, all);
+    return all[0];
   }
-  return full;
+  const uint32_t* list = table + kCellWords + 2 * (int)(low >> SH);
+  int slot = (int)(list[0] & 0xff);
+  float best = score(y0, y1, grid_entry<SH>(cb, slot));
+  // two rounds of four candidates: the four grid points of a round are fetched together (a loop over single
+  // candidates would wait for LDS eight times in a row); rolled, because this path is rare and its size is not
+#pragma unroll 1
+  for (int rnd = 0; rnd < 2; ++rnd) {
+    const uint32_t w = list[rnd];
+    float4 c[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c[k] = grid_entry<SH>(cb, (int)((w >> (8 * k)) & 0xff));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {                     // (the first candidate again in round 0: a tie, no change)
+      const float sc = score(y0, y1, c[k]);
+      const bool better = sc > best;
+      best = better ? sc : best;
+      slot = better ? (int)((w >> (8 * k)) & 0xff) : slot;
+    }
+    // a list ends in repeats of its last candidate: no second round if no lane here has more than four
+    if (list[1] == (w >> 24) * 0x01010101u) break;
+  }
+  return slot;
 }
 
-// 16 codes of c bits per lane = 4c contiguous bytes of the group's little-endian bit string.  `slot`: the 16 slots.
+// A lane's 16 codes of c bits are 4c contiguous bytes of the group's little-endian bit string, c / 2 words.
+// Adds the code of sub-vector m (0..15, compile time) to them, given its slot.
 template <int NCW>
-__device__ __forceinline__ void store_codes(uint8_t* __restrict__ codes, int64_t gid, int q, const int (&slot)[16]) {
+__device__ __forceinline__ void pack_code(uint32_t (&d)[4], int m, int slot) {
   constexpr int c = CodeBits<NCW>::c;
   constexpr int SH = Slot<NCW>::kShift;
+  if constexpr (c == 4) {
+    const int pos = 4 * (m & 7);                     // the index j = slot >> SH goes to bit `pos`
+    d[m >> 3] |= pos >= SH ? (uint32_t)slot << (pos - SH) : (uint32_t)slot >> (SH - pos);
+  } else {
+    static_assert(c == 4 || SH == 0, "slots of the larger grids are indices");
+    const int bit = c * m, w = bit >> 5, sh = bit & 31;
+    d[w] |= (uint32_t)slot << sh;
+    if (sh + c > 32) d[w + 1] |= (uint32_t)slot >> (32 - sh);
+  }
+}
+template <int NCW>
+__device__ __forceinline__ void store_codes(uint8_t* __restrict__ codes, int64_t gid, int q, const uint32_t (&d)[4]) {
+  constexpr int c = CodeBits<NCW>::c;
   uint32_t* dst = reinterpret_cast<uint32_t*>(codes + gid * (kGroup / 2 * c / 8) + q * (2 * c));
   if constexpr (c == 4) {
-    uint32_t d[2] = {0, 0};
-#pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      const int pos = 4 * (m & 7);                   // the index j = slot >> SH goes to bit `pos`
-      d[m >> 3] |= pos >= SH ? (uint32_t)slot[m] << (pos - SH) : (uint32_t)slot[m] >> (SH - pos);
-    }
     u32x2 v; v.x = d[0]; v.y = d[1];
     *reinterpret_cast<u32x2*>(dst) = v;
   } else if constexpr (c == 6) {
-    static_assert(c != 6 || SH == 0, "slots of the larger grids are indices");
-    uint32_t d[3] = {0, 0, 0};
-#pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      const int bit = 6 * m, w = bit >> 5, sh = bit & 31;
-      d[w] |= (uint32_t)slot[m] << sh;
-      if (sh > 26) d[w + 1] |= (uint32_t)slot[m] >> (32 - sh);
-    }
     dst[0] = d[0]; dst[1] = d[1]; dst[2] = d[2];
   } else {
-    static_assert(c != 8 || SH == 0, "slots of the larger grids are indices");
-    u32x4 v;
-    uint32_t d[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w)
-      d[w] = (uint32_t)slot[4 * w] | ((uint32_t)slot[4 * w + 1] << 8) | ((uint32_t)slot[4 * w + 2] << 16) |
-             ((uint32_t)slot[4 * w + 3] << 24);
-    v.x = d[0]; v.y = d[1]; v.z = d[2]; v.w = d[3];
+    u32x4 v; v.x = d[0]; v.y = d[1]; v.z = d[2]; v.w = d[3];
     *reinterpret_cast<u32x4*>(dst) = v;
   }
 }
@@ -263,13 +227,12 @@ __device__ __forceinline__ float half_bits_to_float(uint16_t h) {
   return static_cast<float>(__builtin_bit_cast(_Float16, h));
 }
 
-// slots (SHIFT = Slot<NCW>::kShift) or indices (SHIFT = 0) of the lane's 16 grid points -> the points times `scale`
-// (recon_scale(sigma16, lane): the input of the inverse transform)
-template <int SHIFT = 0>
-__device__ __forceinline__ void gather_zhat(const int (&slot)[16], float scale, const float4* cb, float (&z)[32]) {
+// indices of the lane's 16 grid points -> the points times `scale` (recon_scale(sigma16, lane): the input of the inverse
+// transform)
+__device__ __forceinline__ void gather_zhat(const int (&idx)[16], float scale, const float4* cb, float (&z)[32]) {
 #pragma unroll
   for (int m = 0; m < 16; ++m) {
-    const float4 cw = grid_entry<SHIFT>(cb, slot[m]);
+    const float4 cw = cb[idx[m]];
     z[2 * m] = cw.x * scale;
     z[2 * m + 1] = cw.y * scale;
   }
@@ -438,32 +401,55 @@ __device__ __forceinline__ void quantize_group(float (&v)[32], const float (&p)[
   const float s16 = static_cast<float>(s16h);
   const float inv = s16 > 0.f ? Rot<WIDE>::sign(l) * __fdiv_rn(Rot<WIDE>::kNorm, s16) : 0.f;   // also undoes the lane sign
 
-  int idx[16];                                            // slots (Slot<NCW>)
-  if (table != nullptr) {
-    uint32_t crowded_mask = 0;
+  // Four sub-vectors at a time: their candidates are in flight together, the codes are packed and (want_hat) the grid
+  // points take the place of the rotated values at once, so no more than four slots are ever held.  (All 16 at a time
+  // kept the kernels at 256 registers, two waves per SIMD.)
+  const float rs = recon_scale<WIDE>(s16, l);
+  uint32_t words[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      bool crowded;
-      idx[m] = search_cell<NCW>(v[2 * m] * inv, v[2 * m + 1] * inv, cb, table, crowded);
-      crowded_mask |= crowded ? 1u << m : 0u;
-    }
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(crowded_mask != 0) != 0, 0)) {
-      const uint32_t full_mask = search_overflow_masked<NCW>(v, inv, cb, table, crowded_mask, idx);
-      if (__builtin_amdgcn_ballot_w64(full_mask != 0) != 0) search_full_masked<NCW>(v, inv, cb, full_mask, idx);
-    }
-  } else {
+  for (int m0 = 0; m0 < 16; m0 += 4) {
+    float y[8];
 #pragma unroll
-    for (int m = 0; m < 16; ++m) idx[m] = 0;
-    search_full_masked<NCW>(v, inv, cb, 0xffffu, idx);      // the definition: scan all n points
+    for (int i = 0; i < 8; ++i) y[i] = v[2 * m0 + i] * inv;
+    int slot[4];
+    if (table != nullptr) {
+      uint32_t e[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) e[k] = cell_entry<NCW>(y[2 * k], y[2 * k + 1], table);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) slot[k] = search_cell<NCW>(y[2 * k], y[2 * k + 1], e[k], cb);
+      const uint32_t top = max(max(e[0], e[1]), max(e[2], e[3]));
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(top >= crowded_threshold(NCW)) != 0, 0)) {
+#pragma unroll 1
+        for (int k = 0; k < 4; ++k) {                // rolled: the path is rare, its size is not
+          const uint32_t ek = k == 0 ? e[0] : k == 1 ? e[1] : k == 2 ? e[2] : e[3];
+          if (ek < crowded_threshold(NCW)) continue;
+          const float y0 = k == 0 ? y[0] : k == 1 ? y[2] : k == 2 ? y[4] : y[6];
+          const float y1 = k == 0 ? y[1] : k == 1 ? y[3] : k == 2 ? y[5] : y[7];
+          const int j = search_crowded<NCW>(y0, y1, ek & 0xffu, cb, table);
+          slot[0] = k == 0 ? j : slot[0]; slot[1] = k == 1 ? j : slot[1];
+          slot[2] = k == 2 ? j : slot[2]; slot[3] = k == 3 ? j : slot[3];
+        }
+      }
+    } else {
+      search_full<NCW, 4>(y, cb, slot);              // the definition: scan all n points
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) pack_code<NCW>(words, m0 + k, slot[k]);
+    if (want_hat) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float2 cw = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(cb) + ((uint32_t)slot[k] << (4 - Slot<NCW>::kShift)));
+        v[2 * (m0 + k)] = cw.x * rs;
+        v[2 * (m0 + k) + 1] = cw.y * rs;
+      }
+    }
   }
   if (active) {
-    store_codes<NCW>(codes, gid, q, idx);
+    store_codes<NCW>(codes, gid, q, words);
     if (l == 0) scales[WIDE ? gid >> 3 : gid] = __builtin_bit_cast(uint16_t, s16h);
   }
-  if (want_hat) {
-    gather_zhat<Slot<NCW>::kShift>(idx, recon_scale<WIDE>(s16, l), cb, v);
-    reconstruct<WIDE>(v, l, sf, p);
-  }
+  if (want_hat) reconstruct<WIDE>(v, l, sf, p);
 }
 
 // the lane's share of a group's codes (and of its scales) as the kernels hold them between request and use

@@ -19,13 +19,22 @@ constexpr int kThreads = 256;
 constexpr int kGroupsPerBlock = kThreads / kLanesPerGroup;   // 64
 
 // ------------------------------------------------------------------ quantize
-template <typename T, int NCW, bool WIDE>
-__global__ __launch_bounds__(kThreads) void quantize_kernel(const T* X, const float* __restrict__ P,
-                                                            const int8_t* __restrict__ signs,
-                                                            const float* __restrict__ codebook,
-                                                            const uint32_t* __restrict__ table,
-                                                            uint8_t* __restrict__ codes, uint16_t* __restrict__ scales,
-                                                            T* Xhat, int64_t n_groups, int H) {
+// blockIdx.y: which of the one or two tensors of the launch (QuantizeIo in kernels.h; the keys and the values of a layer
+// without predictors do not depend on each other, and together they fill the chip better).
+//
+// Bound by vector issue and, with it, by how many waves a SIMD holds to cover the look-ups' LDS latency.  Without a
+// prediction (PRED false) the kernel fits 168 registers = three waves per SIMD, since quantize_group holds four sub-vectors
+// at a time; with one (32 more values, and the next round's 32) it stays at two.  8192 tokens, 256-point grid, groups of
+// 1024, keys and values: 2 x 53 us as two launches of one wave per SIMD.
+template <typename T, int NCW, bool WIDE, bool PRED>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED || sizeof(T) == 4 ? 2 : 3))) void quantize_kernel(
+    const QuantizeIo io0, const QuantizeIo io1, const float* __restrict__ P, const float* __restrict__ codebook,
+    const uint32_t* __restrict__ table, int64_t n_groups, int H) {
+  const T* const X = static_cast<const T*>(blockIdx.y ? io1.X : io0.X);
+  T* const Xhat = static_cast<T*>(blockIdx.y ? io1.Xhat : io0.Xhat);
+  const int8_t* const signs = blockIdx.y ? io1.signs : io0.signs;
+  uint8_t* const codes = blockIdx.y ? io1.codes : io0.codes;
+  uint16_t* const scales = blockIdx.y ? io1.scales : io0.scales;
   __shared__ Lds lds;
   stage_lds<NCW>(lds, codebook, table);
   const int q = threadIdx.x & 3;
@@ -39,7 +48,7 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const T* X, const fl
   // The rows (and the fp32 prediction) of the next round are requested before the current round is worked on: with two
   // waves per SIMD nothing else hides the latency of these loads.
   constexpr int kXQuads = sizeof(T) == 2 ? 4 : 8;
-  struct Rows { u32x4 x[kXQuads]; f32x4 p[8]; };
+  struct Rows { u32x4 x[kXQuads]; f32x4 p[PRED ? 8 : 1]; };
   const auto request = [&](int64_t g0, Rows& r) {
     int64_t gid = g0 + (threadIdx.x >> 2);
     gid = gid < n_groups ? gid : n_groups - 1;
@@ -47,7 +56,7 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const T* X, const fl
     const u32x4* src = reinterpret_cast<const u32x4*>(X + off);
 #pragma unroll
     for (int k = 0; k < kXQuads; ++k) r.x[k] = src[k];
-    if (P != nullptr) {
+    if constexpr (PRED) {
 #pragma unroll
       for (int k = 0; k < 8; ++k) r.p[k] = reinterpret_cast<const f32x4*>(P + off)[k];
     }
@@ -76,7 +85,7 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const T* X, const fl
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      const f32x4 a = P != nullptr ? cur.p[k] : f32x4{0.f, 0.f, 0.f, 0.f};
+      const f32x4 a = PRED ? cur.p[PRED ? k : 0] : f32x4{0.f, 0.f, 0.f, 0.f};
       p[4 * k] = a.x; p[4 * k + 1] = a.y; p[4 * k + 2] = a.z; p[4 * k + 3] = a.w;
     }
     if constexpr (!is_rtn(NCW)) {
@@ -90,13 +99,15 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const T* X, const fl
 }
 
 // ------------------------------------------------------------------ dequantize
+// blockIdx.y: which of the one or two tensors of the launch (X unused)
 template <typename T, int NCW, bool WIDE>
-__global__ __launch_bounds__(kThreads) void dequantize_kernel(const uint8_t* __restrict__ codes,
-                                                              const uint16_t* __restrict__ scales,
+__global__ __launch_bounds__(kThreads) void dequantize_kernel(const QuantizeIo io0, const QuantizeIo io1,
                                                               const float* __restrict__ P,
-                                                              const int8_t* __restrict__ signs,
-                                                              const float* __restrict__ codebook, T* __restrict__ Xhat,
-                                                              int64_t n_groups, int H) {
+                                                              const float* __restrict__ codebook, int64_t n_groups, int H) {
+  const uint8_t* __restrict__ const codes = blockIdx.y ? io1.codes : io0.codes;
+  const uint16_t* __restrict__ const scales = blockIdx.y ? io1.scales : io0.scales;
+  const int8_t* __restrict__ const signs = blockIdx.y ? io1.signs : io0.signs;
+  T* __restrict__ const Xhat = static_cast<T*>(blockIdx.y ? io1.Xhat : io0.Xhat);
   __shared__ float4 cb[is_rtn(NCW) ? 1 : NCW];
   load_codebook<NCW>(codebook, cb);
   __syncthreads();
@@ -315,17 +326,18 @@ __global__ __launch_bounds__(1024) void build_overflow_kernel(const float* __res
   }
 }
 
-// Workgroups per CU (256 CUs), the kernels grid-stride.  The quantizer holds two workgroups per CU (registers) and stages
-// 21 KiB of grid and cell table per workgroup, more than the 16 KiB of rows of one round: with exactly the resident
-// number of workgroups the staging is paid once and the request of the next round's rows has a next round to run ahead
-// of (measured at 32768 tokens: 52 us against 67 us with 16 per CU).  The inverse stages 256 B and runs four waves per
-// SIMD; four workgroups per CU were the best of 2 / 4 / 8 / 16 at 32768 tokens (25.7 against 29 us with 16).
-constexpr int kQuantizeWgPerCu = 2;
+// Workgroups per CU (256 CUs), the kernels grid-stride.  The quantizer stages 21 KiB of grid and cell table per workgroup,
+// more than the 16 KiB of rows of one round: with at most the resident number of workgroups the staging is paid once and
+// the request of the next round's rows has a next round to run ahead of (measured at 32768 tokens: 52 us against 67 us with
+// 16 per CU).  The inverse stages 256 B and runs four waves per SIMD; four workgroups per CU were the best of 2 / 4 / 8 / 16
+// at 32768 tokens (25.7 against 29 us with 16).  Below that number the rounds are shared out evenly.
+constexpr int kQuantizeWgPerCu = 2, kQuantizePlainWgPerCu = 3;     // with a prediction, without
 constexpr int kDequantizeWgPerCu = 4;
-inline unsigned blocks_for(int64_t n_groups, int per_cu) {
+inline unsigned blocks_for(int64_t n_groups, int per_cu, int tensors = 1) {
   const int64_t need = (n_groups + kGroupsPerBlock - 1) / kGroupsPerBlock;
-  const int64_t cap = 256 * per_cu;
-  return (unsigned)(need < cap ? need : cap);
+  const int64_t cap = 256 * per_cu / tensors;
+  const int64_t rounds = (need + cap - 1) / cap;
+  return (unsigned)((need + rounds - 1) / rounds);
 }
 
 }  // namespace
@@ -363,26 +375,32 @@ hipError_t launch_build_search_table(const float* codebook, int n_codewords, voi
   return hipGetLastError();
 }
 
-hipError_t launch_quantize(int dtype, int n_codewords, const void* X, const float* P, const int8_t* signs,
-                           const float* codebook, const void* table, uint8_t* codes, uint16_t* scales, void* Xhat,
-                           int64_t T_, int H, bool wide, hipStream_t stream) {
+hipError_t launch_quantize(int dtype, int n_codewords, const QuantizeIo* io, int tensors, const float* P,
+                           const float* codebook, const void* table, int64_t T_, int H, bool wide, hipStream_t stream) {
   const int64_t n_groups = T_ * H;
   if (n_groups == 0) return hipSuccess;
-  AQUAKV_DISPATCH(dtype, n_codewords, wide,
-                  (quantize_kernel<T, N, W><<<blocks_for(n_groups, kQuantizeWgPerCu), kThreads, 0, stream>>>(
-                      static_cast<const T*>(X), P, signs, codebook, static_cast<const uint32_t*>(table), codes, scales,
-                      static_cast<T*>(Xhat), n_groups, H)));
+  if (tensors != 1 && P != nullptr) return hipErrorInvalidValue;
+  const QuantizeIo& other = io[tensors - 1];
+  const uint32_t* tab = static_cast<const uint32_t*>(table);
+  const int per_cu = P != nullptr || dtype != kBF16 ? kQuantizeWgPerCu : kQuantizePlainWgPerCu;
+  const dim3 grid(blocks_for(n_groups, per_cu, tensors), (unsigned)tensors);
+  if (P != nullptr)
+    AQUAKV_DISPATCH(dtype, n_codewords, wide, (quantize_kernel<T, N, W, true><<<grid, kThreads, 0, stream>>>(
+                                                  io[0], other, P, codebook, tab, n_groups, H)));
+  else
+    AQUAKV_DISPATCH(dtype, n_codewords, wide, (quantize_kernel<T, N, W, false><<<grid, kThreads, 0, stream>>>(
+                                                  io[0], other, P, codebook, tab, n_groups, H)));
   return hipGetLastError();
 }
 
-hipError_t launch_dequantize(int dtype, int n_codewords, const uint8_t* codes, const uint16_t* scales, const float* P,
-                             const int8_t* signs, const float* codebook, void* Xhat, int64_t T_, int H, bool wide,
-                             hipStream_t stream) {
+hipError_t launch_dequantize(int dtype, int n_codewords, const QuantizeIo* io, int tensors, const float* P,
+                             const float* codebook, int64_t T_, int H, bool wide, hipStream_t stream) {
   const int64_t n_groups = T_ * H;
   if (n_groups == 0) return hipSuccess;
-  AQUAKV_DISPATCH(dtype, n_codewords, wide,
-                  (dequantize_kernel<T, N, W><<<blocks_for(n_groups, kDequantizeWgPerCu), kThreads, 0, stream>>>(
-                      codes, scales, P, signs, codebook, static_cast<T*>(Xhat), n_groups, H)));
+  if (tensors != 1 && P != nullptr) return hipErrorInvalidValue;
+  const dim3 grid(blocks_for(n_groups, kDequantizeWgPerCu, tensors), (unsigned)tensors);
+  AQUAKV_DISPATCH(dtype, n_codewords, wide, (dequantize_kernel<T, N, W><<<grid, kThreads, 0, stream>>>(
+                                                io[0], io[tensors - 1], P, codebook, n_groups, H)));
   return hipGetLastError();
 }
 

@@ -12,20 +12,26 @@ enum Dtype : int { kBF16 = 0, kFP32 = 1 };
 hipError_t launch_predict(int dtype, const void* x0, int d0, const void* x1, int d1, const void* W,
                           const float* bias, float* P, int64_t T, int D, hipStream_t stream);
 
-// Q(X - P): codes, scales and (optionally) the reconstruction.  rows = T, H heads of 128.
+// One tensor of a quantize / dequantize launch; rows of H heads of 128.
+struct QuantizeIo {
+  const void* X;              // quantize: the values
+  const int8_t* signs;
+  uint8_t* codes;             // written by quantize, read by dequantize
+  uint16_t* scales;
+  void* Xhat;                 // reconstruction (quantize: nullable)
+};
+// Q(X - P): codes, scales and (optionally) the reconstruction of io[0 .. tensors - 1] (1 or 2; 2 only without P), T rows each.
 // wide: rotation groups of 1024 = the whole token (H must be 8), scales [T] instead of [T, H].
 // `table` (nullable): nearest-grid-point search table from launch_build_search_table.
-hipError_t launch_quantize(int dtype, int n_codewords, const void* X, const float* P, const int8_t* signs,
-                           const float* codebook, const void* table, uint8_t* codes, uint16_t* scales, void* Xhat,
-                           int64_t T, int H, bool wide, hipStream_t stream);
+hipError_t launch_quantize(int dtype, int n_codewords, const QuantizeIo* io, int tensors, const float* P,
+                           const float* codebook, const void* table, int64_t T, int H, bool wide, hipStream_t stream);
 
 // 64 x 64 cells x 4 candidate bytes = 16 KiB, and 128 overflow lists of 8 candidate bytes.
 constexpr size_t kSearchTableBytes = (64 * 64 + 2 * 128) * 4;     // cell entries + overflow lists (codec_core.h)
 hipError_t launch_build_search_table(const float* codebook, int n_codewords, void* table, hipStream_t stream);
 
-hipError_t launch_dequantize(int dtype, int n_codewords, const uint8_t* codes, const uint16_t* scales, const float* P,
-                             const int8_t* signs, const float* codebook, void* Xhat, int64_t T, int H, bool wide,
-                             hipStream_t stream);
+hipError_t launch_dequantize(int dtype, int n_codewords, const QuantizeIo* io, int tensors, const float* P,
+                             const float* codebook, int64_t T, int H, bool wide, hipStream_t stream);
 
 // scores[b, qh, t] for rows [row0, row0 + rows) of the flattened [batch*seq_len] axis.
 // codes/scales/P/Khat_out point at row `row0`; q and scores at their tensor bases.
