@@ -376,7 +376,8 @@ __device__ __forceinline__ void rtn_quantize_group(float (&v)[32], const float (
 // `l` is the lane's index inside its rotation group: lane % 4 for groups of 128 (WIDE = false, one
 // scale per head group), lane % 32 for groups of 1024 = the whole token (WIDE = true, kv_heads = 8, one
 // scale per token at scales[gid / 8]).  The code bytes have the same layout in both cases.
-template <int NCW, bool WIDE = false>
+// BATCH: sub-vectors searched together.
+template <int NCW, bool WIDE = false, int BATCH = 4>
 __device__ __forceinline__ void quantize_group(float (&v)[32], const float (&p)[32], const float (&sf)[32], int l,
                                                const float4* cb, const uint32_t* table, bool active, int64_t gid,
                                                uint8_t* __restrict__ codes, uint16_t* __restrict__ scales,
@@ -401,44 +402,48 @@ __device__ __forceinline__ void quantize_group(float (&v)[32], const float (&p)[
   const float s16 = static_cast<float>(s16h);
   const float inv = s16 > 0.f ? Rot<WIDE>::sign(l) * __fdiv_rn(Rot<WIDE>::kNorm, s16) : 0.f;   // also undoes the lane sign
 
-  // Four sub-vectors at a time: their candidates are in flight together, the codes are packed and (want_hat) the grid
-  // points take the place of the rotated values at once, so no more than four slots are ever held.  (All 16 at a time
-  // kept the kernels at 256 registers, two waves per SIMD.)
+  // BATCH sub-vectors at a time: their candidates are in flight together, the codes are packed and (want_hat) the grid
+  // points take the place of the rotated values at once, so no more than BATCH slots are ever held.  (All 16 at a time
+  // kept the stand-alone kernels at 256 registers, two waves per SIMD.)
   const float rs = recon_scale<WIDE>(s16, l);
   uint32_t words[4] = {0, 0, 0, 0};
 #pragma unroll
-  for (int m0 = 0; m0 < 16; m0 += 4) {
-    float y[8];
+  for (int m0 = 0; m0 < 16; m0 += BATCH) {
+    float y[2 * BATCH];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) y[i] = v[2 * m0 + i] * inv;
-    int slot[4];
+    for (int i = 0; i < 2 * BATCH; ++i) y[i] = v[2 * m0 + i] * inv;
+    int slot[BATCH];
     if (table != nullptr) {
-      uint32_t e[4];
+      uint32_t e[BATCH], top = 0;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) e[k] = cell_entry<NCW>(y[2 * k], y[2 * k + 1], table);
+      for (int k = 0; k < BATCH; ++k) e[k] = cell_entry<NCW>(y[2 * k], y[2 * k + 1], table);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) slot[k] = search_cell<NCW>(y[2 * k], y[2 * k + 1], e[k], cb);
-      const uint32_t top = max(max(e[0], e[1]), max(e[2], e[3]));
+      for (int k = 0; k < BATCH; ++k) slot[k] = search_cell<NCW>(y[2 * k], y[2 * k + 1], e[k], cb);
+#pragma unroll
+      for (int k = 0; k < BATCH; ++k) top = max(top, e[k]);
       if (__builtin_expect(__builtin_amdgcn_ballot_w64(top >= crowded_threshold(NCW)) != 0, 0)) {
 #pragma unroll 1
-        for (int k = 0; k < 4; ++k) {                // rolled: the path is rare, its size is not
-          const uint32_t ek = k == 0 ? e[0] : k == 1 ? e[1] : k == 2 ? e[2] : e[3];
+        for (int k = 0; k < BATCH; ++k) {            // rolled: the path is rare, its size is not
+          uint32_t ek = 0;
+          float y0 = 0.f, y1 = 0.f;
+#pragma unroll
+          for (int i = 0; i < BATCH; ++i) {          // (no dynamic register indexing)
+            ek = k == i ? e[i] : ek; y0 = k == i ? y[2 * i] : y0; y1 = k == i ? y[2 * i + 1] : y1;
+          }
           if (ek < crowded_threshold(NCW)) continue;
-          const float y0 = k == 0 ? y[0] : k == 1 ? y[2] : k == 2 ? y[4] : y[6];
-          const float y1 = k == 0 ? y[1] : k == 1 ? y[3] : k == 2 ? y[5] : y[7];
           const int j = search_crowded<NCW>(y0, y1, ek & 0xffu, cb, table);
-          slot[0] = k == 0 ? j : slot[0]; slot[1] = k == 1 ? j : slot[1];
-          slot[2] = k == 2 ? j : slot[2]; slot[3] = k == 3 ? j : slot[3];
+#pragma unroll
+          for (int i = 0; i < BATCH; ++i) slot[i] = k == i ? j : slot[i];
         }
       }
     } else {
-      search_full<NCW, 4>(y, cb, slot);              // the definition: scan all n points
+      search_full<NCW, BATCH>(y, cb, slot);          // the definition: scan all n points
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) pack_code<NCW>(words, m0 + k, slot[k]);
+    for (int k = 0; k < BATCH; ++k) pack_code<NCW>(words, m0 + k, slot[k]);
     if (want_hat) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
+      for (int k = 0; k < BATCH; ++k) {
         const float2 cw = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(cb) + ((uint32_t)slot[k] << (4 - Slot<NCW>::kShift)));
         v[2 * (m0 + k)] = cw.x * rs;
         v[2 * (m0 + k) + 1] = cw.y * rs;

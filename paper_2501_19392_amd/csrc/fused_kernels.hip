@@ -164,7 +164,7 @@ __global__ __launch_bounds__(WAVES * 64) void fused_kernel(
     if constexpr (MODE == kEncode) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) unpack_bf16x8(in.x[k], &v[8 * k]);
-      quantize_group<NCW>(v, p, sf, q, cl.cb, use_table ? cl.table : nullptr, active, gid, codes, scales,
+      quantize_group<NCW, false, 8>(v, p, sf, q, cl.cb, use_table ? cl.table : nullptr, active, gid, codes, scales,
                           Xhat != nullptr);
       if (Xhat != nullptr && active) Storage<bf16_t>::store32(Xhat + off, v);
     } else {
