@@ -191,10 +191,36 @@ inline aquakv::QuantizeIo coded(const int8_t* signs, const void* codes, const vo
   return {nullptr, signs, static_cast<uint8_t*>(const_cast<void*>(codes)), static_cast<uint16_t*>(const_cast<void*>(scales)), hat};
 }
 
+// Encode of n rows of one tensor with rotation groups across the 8 heads.  The kernel that owns whole tokens walks all of W in
+// every workgroup of 64 tokens: 100 us however few tokens there are.  Short ranges therefore run as predictor (on the tiles
+// of short ranges, fp32 predictions into the workspace) and stand-alone quantizer, in pieces of as many rows as the workspace
+// holds predictions for (`room` bytes): kWideSplitRows is where the two cost the same.
+constexpr int64_t kWideSplitRows = 4096;
+int encode_wide(const aquakv_layer* L, const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias,
+                const int8_t* signs, const void* X, uint8_t* codes, uint16_t* scales, void* Xhat, int64_t n, int D, float* ws,
+                size_t room, hipStream_t stream) {
+  const size_t eb = elem_bytes(L->dtype), row = (size_t)D * eb;
+  const int64_t fit = (int64_t)(room / ((size_t)D * sizeof(float)));
+  const int64_t pieces = fit > 0 ? (n + fit - 1) / fit : 0, piece = pieces > 0 ? (n + pieces - 1) / pieces : 0;
+  if (n > kWideSplitRows || pieces == 0 || pieces > 4 || !aquakv::tile_predict_fits(piece, D)) {
+    HIP_TRY(aquakv::launch_fused_encode_wide(quantizer_id(L), x0, d0, x1, d1, W, ws, bias, signs, L->codebook, L->search_table, X,
+                                             codes, scales, Xhat, n, D, stream));
+    return AQUAKV_OK;
+  }
+  for (int64_t r = 0; r < n; r += piece) {
+    const int64_t m = n - r < piece ? n - r : piece;
+    HIP_TRY(aquakv::launch_tile_predict(at(x0, r, d0 * eb), d0, at(x1, r, d1 * eb), d1, W, bias, ws, m, D, stream));
+    const aquakv::QuantizeIo io = {at(X, r, row), signs, codes + r * (int64_t)(D / 2 * code_bits(L) / 8),
+                                   static_cast<uint16_t*>(at(scales, r, scale_row_bytes(L))), at(Xhat, r, row)};
+    HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), &io, 1, ws, L->codebook, L->search_table, m, L->kv_heads, true, stream));
+  }
+  return AQUAKV_OK;
+}
+
 // ---- one chunk of rows [r0, r0 + n) of one tensor; pointers are the tensors' bases -------------------------------
 // keys of Alg. "encode":  K_pred = f_key(Khat_prev);  K_q = Q(K - K_pred);  khat_dst (chunk-local, nullable) = Q^-1(K_q) + K_pred
 int encode_keys_chunk(const aquakv_layer* L, const Plan& pl, int64_t r0, int64_t n, const void* K, const void* Khat_prev,
-                      uint8_t* k_codes, uint16_t* k_scales, void* khat_dst, float* Pbuf, hipStream_t stream) {
+                      uint8_t* k_codes, uint16_t* k_scales, void* khat_dst, float* Pbuf, size_t room, hipStream_t stream) {
   const bool has_k = L->d_in_k != 0;
   const size_t row = (size_t)pl.D * pl.eb, srow = scale_row_bytes(L);
   if (has_k && pl.fused) {
@@ -202,11 +228,10 @@ int encode_keys_chunk(const aquakv_layer* L, const Plan& pl, int64_t r0, int64_t
     uint8_t* const kc = static_cast<uint8_t*>(at(k_codes, r0, pl.code_row));
     uint16_t* const ks = static_cast<uint16_t*>(at(k_scales, r0, srow));
     if (is_wide(L))
-      HIP_TRY(aquakv::launch_fused_encode_wide(quantizer_id(L), x0, L->d_in_k, nullptr, 0, L->w_k, Pbuf, L->b_k, L->signs_k,
-                                               L->codebook, L->search_table, at(K, r0, row), kc, ks, khat_dst, n, pl.D, stream));
-    else
-      HIP_TRY(aquakv::launch_fused_encode(quantizer_id(L), x0, L->d_in_k, nullptr, 0, L->w_k, L->b_k, L->signs_k, L->codebook,
-                                          L->search_table, at(K, r0, row), kc, ks, khat_dst, n, pl.D, stream));
+      return encode_wide(L, x0, L->d_in_k, nullptr, 0, L->w_k, L->b_k, L->signs_k, at(K, r0, row), kc, ks, khat_dst, n, pl.D, Pbuf,
+                         room, stream);
+    HIP_TRY(aquakv::launch_fused_encode(quantizer_id(L), x0, L->d_in_k, nullptr, 0, L->w_k, L->b_k, L->signs_k, L->codebook,
+                                        L->search_table, at(K, r0, row), kc, ks, khat_dst, n, pl.D, stream));
     return AQUAKV_OK;
   }
   if (has_k)
@@ -222,7 +247,7 @@ int encode_keys_chunk(const aquakv_layer* L, const Plan& pl, int64_t r0, int64_t
 // values of Alg. "encode":  V_pred = f_value([Vhat_prev; Khat]);  V_q = Q(V - V_pred);  khat_src is chunk-local
 int encode_values_chunk(const aquakv_layer* L, const Plan& pl, int64_t r0, int64_t n, const void* V, const void* Vhat_prev,
                         const void* khat_src, uint8_t* v_codes, uint16_t* v_scales, void* Vhat, float* Pbuf,
-                        hipStream_t stream) {
+                        size_t room, hipStream_t stream) {
   const bool has_v = L->d_in_v != 0;
   const int D = pl.D;
   const size_t row = (size_t)D * pl.eb, srow = scale_row_bytes(L);
@@ -231,12 +256,10 @@ int encode_values_chunk(const aquakv_layer* L, const Plan& pl, int64_t r0, int64
     uint8_t* const vc = static_cast<uint8_t*>(at(v_codes, r0, pl.code_row));
     uint16_t* const vs = static_cast<uint16_t*>(at(v_scales, r0, srow));
     if (is_wide(L))
-      HIP_TRY(aquakv::launch_fused_encode_wide(quantizer_id(L), x0, L->d_in_v - D, khat_src, D, L->w_v, Pbuf, L->b_v,
-                                               L->signs_v, L->codebook, L->search_table, at(V, r0, row), vc, vs,
-                                               at(Vhat, r0, row), n, D, stream));
-    else
-      HIP_TRY(aquakv::launch_fused_encode(quantizer_id(L), x0, L->d_in_v - D, khat_src, D, L->w_v, L->b_v, L->signs_v,
-                                          L->codebook, L->search_table, at(V, r0, row), vc, vs, at(Vhat, r0, row), n, D, stream));
+      return encode_wide(L, x0, L->d_in_v - D, khat_src, D, L->w_v, L->b_v, L->signs_v, at(V, r0, row), vc, vs, at(Vhat, r0, row),
+                         n, D, Pbuf, room, stream);
+    HIP_TRY(aquakv::launch_fused_encode(quantizer_id(L), x0, L->d_in_v - D, khat_src, D, L->w_v, L->b_v, L->signs_v,
+                                        L->codebook, L->search_table, at(V, r0, row), vc, vs, at(Vhat, r0, row), n, D, stream));
     return AQUAKV_OK;
   }
   if (has_v)
@@ -447,8 +470,10 @@ int aquakv_encode_layer(const aquakv_layer* L, int64_t tokens, const void* K, co
                                       is_wide(L), stream));
       continue;
     }
-    CHECK(encode_keys_chunk(L, pl, r0, n, K, Khat_prev, k_codes, k_scales, khat_dst, Pbuf, stream));
-    CHECK(encode_values_chunk(L, pl, r0, n, V, Vhat_prev, khat_dst, v_codes, v_scales, Vhat, Pbuf, stream));
+    // (the temporary Khat behind the predictions is free when the caller asks for Khat)
+    const size_t room = pl.p_bytes + (Khat != nullptr || !has_v ? pl.khat_bytes : 0);
+    CHECK(encode_keys_chunk(L, pl, r0, n, K, Khat_prev, k_codes, k_scales, khat_dst, Pbuf, room, stream));
+    CHECK(encode_values_chunk(L, pl, r0, n, V, Vhat_prev, khat_dst, v_codes, v_scales, Vhat, Pbuf, room, stream));
   }
   return AQUAKV_OK;
 }
@@ -532,7 +557,7 @@ int aquakv_encode_keys(const aquakv_layer* L, int64_t tokens, const void* K, con
   for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk) {
     const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;
     CHECK(encode_keys_chunk(L, pl, r0, n, K, Khat_prev, k_codes, k_scales, at(Khat, r0, row), static_cast<float*>(workspace),
-                            static_cast<hipStream_t>(stream_)));
+                            pl.p_bytes, static_cast<hipStream_t>(stream_)));
   }
   return AQUAKV_OK;
 }
@@ -568,7 +593,7 @@ int aquakv_encode_values(const aquakv_layer* L, int64_t tokens, const void* V, c
   for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk) {
     const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;
     CHECK(encode_values_chunk(L, pl, r0, n, V, Vhat_prev, at(Khat, r0, row), v_codes, v_scales, Vhat,
-                              static_cast<float*>(workspace), static_cast<hipStream_t>(stream_)));
+                              static_cast<float*>(workspace), pl.p_bytes, static_cast<hipStream_t>(stream_)));
   }
   return AQUAKV_OK;
 }

@@ -52,7 +52,7 @@ __host__ __device__ constexpr uint32_t crowded_entry(int n, uint32_t L) {
 __host__ __device__ constexpr int ovf_capacity(int n) { return n == 16 ? 15 : (n - 1 < kOvfLists ? n - 1 : kOvfLists); }
 
 // Quantizer ids, the NCW template argument everywhere: 16 / 64 / 256 = a grid of that many points in R^2;
-// kRtn2 / kRtn4 = the uniform round-to-nearest backbone with 2 / 4 bits per value (see rtn_quantize_group).
+// kRtn2 / kRtn4 = the uniform round-to-nearest backbone with 2 / 4 bits per value (see rtn_quantize_residual).
 constexpr int kRtn2 = 2, kRtn4 = 4;
 __host__ __device__ constexpr bool is_rtn(int id) { return id < 16; }
 
@@ -321,18 +321,17 @@ __device__ __forceinline__ uint32_t rtn_load_meta(const uint16_t* __restrict__ s
   return reinterpret_cast<const uint32_t*>(scales)[WIDE ? gid >> 3 : gid * 2 + (q >> 1)];
 }
 
-// Q(x - p) for the 32 values this lane holds of head group gid; same contract as quantize_group below
+// Q of the residuals of the 32 values this lane holds of head group gid; same contract as quantize_residual below
 // (`l`: lane % 4, or with WIDE lane % 32: the group is then the whole token of 8 heads, one (step, zero) per token).
 template <int BITS, bool WIDE = false>
-__device__ __forceinline__ void rtn_quantize_group(float (&v)[32], const float (&p)[32], int l, bool active, int64_t gid,
-                                                   uint8_t* __restrict__ codes, uint16_t* __restrict__ scales,
-                                                   bool want_hat) {
+__device__ __forceinline__ void rtn_quantize_residual(float (&v)[32], int l, bool active, int64_t gid,
+                                                      uint8_t* __restrict__ codes, uint16_t* __restrict__ scales,
+                                                      bool want_hat) {
   const int q = l & 3;
   constexpr float kTop = (float)((1 << BITS) - 1);
   float lo = 0.f, hi = 0.f;
 #pragma unroll
   for (int r = 0; r < 32; ++r) {
-    v[r] -= p[r];
     lo = fminf(lo, v[r]);
     hi = fmaxf(hi, v[r]);
   }
@@ -365,29 +364,28 @@ __device__ __forceinline__ void rtn_quantize_group(float (&v)[32], const float (
   }
   if (want_hat) {
 #pragma unroll
-    for (int r = 0; r < 32; ++r) v[r] = __fmaf_rn((float)code[r] - zf, s16, p[r]);
+    for (int r = 0; r < 32; ++r) v[r] = ((float)code[r] - zf) * s16;     // exact: small integer x fp16
   }
 }
 
 // ------------------------------------------------------------------ group bodies
-// Q(x - p) for the 32 coordinates this lane holds of head group `gid` (= token * H + head).  On entry
-// v = x; on exit v holds the (unrounded) reconstruction p + Q^-1(codes) if `want_hat`.  Codes and the
+// Q of the residuals v = x - p of the 32 coordinates this lane holds of head group `gid` (= token * H + head).  On exit
+// v holds, if `want_hat`, what finish_hat turns into the (unrounded) reconstruction p + Q^-1(codes).  Codes and the
 // scale are stored when `active` (inactive lanes only keep the cross-lane exchanges in step).
 // `l` is the lane's index inside its rotation group: lane % 4 for groups of 128 (WIDE = false, one
 // scale per head group), lane % 32 for groups of 1024 = the whole token (WIDE = true, kv_heads = 8, one
 // scale per token at scales[gid / 8]).  The code bytes have the same layout in both cases.
 // BATCH: sub-vectors searched together.
 template <int NCW, bool WIDE = false, int BATCH = 4>
-__device__ __forceinline__ void quantize_group(float (&v)[32], const float (&p)[32], const float (&sf)[32], int l,
-                                               const float4* cb, const uint32_t* table, bool active, int64_t gid,
-                                               uint8_t* __restrict__ codes, uint16_t* __restrict__ scales,
-                                               bool want_hat) {
+__device__ __forceinline__ void quantize_residual(float (&v)[32], const float (&sf)[32], int l, const float4* cb,
+                                                  const uint32_t* table, bool active, int64_t gid,
+                                                  uint8_t* __restrict__ codes, uint16_t* __restrict__ scales, bool want_hat) {
   if constexpr (is_rtn(NCW)) {
-    rtn_quantize_group<NCW, WIDE>(v, p, l, active, gid, codes, scales, want_hat);
+    rtn_quantize_residual<NCW, WIDE>(v, l, active, gid, codes, scales, want_hat);
     return;
   }
 #pragma unroll
-  for (int r = 0; r < 32; ++r) v[r] = (v[r] - p[r]) * sf[r];                              // s * (x - p), exact product
+  for (int r = 0; r < 32; ++r) v[r] *= sf[r];                                             // s * (x - p), exact product
   const int q = l & 3;
   Rot<WIDE>::wht(v, l);                                   // w = +-H u (unnormalised, lane sign pending)
 
@@ -454,7 +452,23 @@ __device__ __forceinline__ void quantize_group(float (&v)[32], const float (&p)[
     store_codes<NCW>(codes, gid, q, words);
     if (l == 0) scales[WIDE ? gid >> 3 : gid] = __builtin_bit_cast(uint16_t, s16h);
   }
-  if (want_hat) reconstruct<WIDE>(v, l, sf, p);
+  if (want_hat) Rot<WIDE>::iwht(v, l);
+}
+// the reconstruction from quantize_residual's v and the prediction
+template <int NCW>
+__device__ __forceinline__ void finish_hat(float (&v)[32], const float (&sf)[32], const float (&p)[32]) {
+#pragma unroll
+  for (int r = 0; r < 32; ++r) v[r] = is_rtn(NCW) ? v[r] + p[r] : __fmaf_rn(v[r], sf[r], p[r]);
+}
+// Q(x - p): on entry v = x, on exit p + Q^-1(codes) if `want_hat`
+template <int NCW, bool WIDE = false, int BATCH = 4>
+__device__ __forceinline__ void quantize_group(float (&v)[32], const float (&p)[32], const float (&sf)[32], int l,
+                                               const float4* cb, const uint32_t* table, bool active, int64_t gid,
+                                               uint8_t* __restrict__ codes, uint16_t* __restrict__ scales, bool want_hat) {
+#pragma unroll
+  for (int r = 0; r < 32; ++r) v[r] -= p[r];
+  quantize_residual<NCW, WIDE, BATCH>(v, sf, l, cb, table, active, gid, codes, scales, want_hat);
+  if (want_hat) finish_hat<NCW>(v, sf, p);
 }
 
 // the lane's share of a group's codes (and of its scales) as the kernels hold them between request and use

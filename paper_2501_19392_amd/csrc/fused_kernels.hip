@@ -379,6 +379,17 @@ TileArgs tile_args(const void* x0, int d0, const void* x1, int d1, const void* W
 
 }  // namespace
 
+bool tile_predict_fits(int64_t T, int D) { return ((T + 127) / 128) * (D / BN) <= 256; }
+
+hipError_t launch_tile_predict(const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias, float* P,
+                               int64_t T, int D, hipStream_t stream) {
+  if (T == 0) return hipSuccess;
+  if (!tile_predict_fits(T, D)) return hipErrorInvalidValue;
+  TileArgs a = tile_args(x0, d0, x1, d1, W, bias, nullptr, nullptr, D);
+  a.P = P; a.seq_len = (int)T;
+  return launch_rows(tile_rows(1, T, D, false), kTilePredict, 16, false, 1, a, stream);
+}
+
 hipError_t launch_fused_encode(int n_codewords, const void* x0, int d0, const void* x1, int d1, const void* W,
                                const float* bias, const int8_t* signs, const float* codebook, const void* table,
                                const void* X, uint8_t* codes, uint16_t* scales, void* Xhat, int64_t T, int D,

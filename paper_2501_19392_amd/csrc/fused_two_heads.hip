@@ -141,7 +141,16 @@ __global__ __launch_bounds__(kWaves2 * 64) void fused_two_heads_kernel(
       if constexpr (kEnc) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) unpack_bf16x8(ip.x[k], &v[8 * k]);
-        quantize_group<NCW>(v, p, sf, q, cl.cb, use_table ? cl.table : nullptr, active, gid, codes, scales, Xhat != nullptr);
+        // the prediction is read from the parked row again for the reconstruction instead of being held through the search:
+        // 32 registers fewer beside the other block's 64 accumulators
+#pragma unroll
+        for (int r = 0; r < 32; ++r) v[r] -= p[r];
+        quantize_residual<NCW>(v, sf, q, cl.cb, use_table ? cl.table : nullptr, active, gid, codes, scales, Xhat != nullptr);
+        if (Xhat != nullptr) {
+          asm volatile("" ::: "memory");
+          read_parked(wl + lrow * kLdP, q, p);
+          finish_hat<NCW>(v, sf, p);
+        }
       } else if constexpr (kWideGrid) {
         const WideCodes<NCW> wc = wide_codes;
         if (pi + 1 < kPasses) fetch_wide(pi + 1, wide_codes);

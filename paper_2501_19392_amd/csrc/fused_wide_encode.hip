@@ -17,8 +17,7 @@ namespace {
 
 constexpr int kHalfRows = 32;
 constexpr int kParkBytes = kHalfRows * kSlabCols * 4;                  // 128 KiB
-constexpr int kWideEpilogueBytes = (int)sizeof(Lds) + kParkBytes;      // grid + table, then the parked half
-constexpr int kWideLdsBytes = kWideEpilogueBytes > kSlabLdsBytes ? kWideEpilogueBytes : kSlabLdsBytes;
+constexpr int kWideLdsBytes = (int)sizeof(Lds) + kParkBytes;           // grid + table, then the parked half
 static_assert(kWideLdsBytes <= 160 * 1024, "LDS of one CU");
 
 // Float index of column `col` of parked row `row`.  A lane of the quantizer reads 8 consecutive 16-byte slots (32 of
@@ -33,16 +32,17 @@ __device__ __forceinline__ int park_index(int row, int col) {
   return row * kSlabCols + ((s << 2) | (col & 3));
 }
 
-// W [1024, K] -> k-tile after k-tile of 32 k, each the 64 KiB LDS image of its tile (gemm_token_slab.h): 16-byte chunk
-// ch of row r of k-tile kt goes to byte kt * 64 KiB + slab_lds_off(r, ch).  One thread per chunk.
+// W [1024, K] -> the main loop's fragments in the order of use (slab_w_off).  One thread per 16-byte chunk, 16 consecutive
+// threads reading 256 bytes of a row.
 __global__ __launch_bounds__(256) void retile_w_kernel(const bf16_t* __restrict__ W, bf16_t* __restrict__ Wt, int K) {
-  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;          // (kt, r, slot) with slot fastest
-  const int slot = (int)(id & 3), r = (int)((id >> 2) & (kSlabCols - 1));
-  const int64_t kt = id >> 12;
-  if (kt >= K / kSlabBK) return;
-  const int ch = slot ^ ((r >> 2) & 3);
-  const u32x4 v = *reinterpret_cast<const u32x4*>(W + (int64_t)r * K + kt * kSlabBK + ch * 8);
-  *reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(Wt) + kt * kSlabBTileBytes + r * kSlabRowBytes + slot * 16) = v;
+  const int blocks_k = K / 128;                                        // blocks of 16 chunks along a row
+  const int id = (int)blockIdx.x * 256 + (int)threadIdx.x;             // (row / 16, chunk block, row % 16, chunk) with chunk fastest
+  const int c = id & 15, r = (id >> 4) & 15;
+  const int blk = id >> 8, kb = blk % blocks_k, row = (blk / blocks_k) * 16 + r;
+  if (row >= kSlabCols) return;
+  const int chunk = kb * 16 + c;
+  const u32x4 v = *reinterpret_cast<const u32x4*>(W + (int64_t)row * K + chunk * 8);
+  *reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(Wt) + slab_w_off(row, chunk)) = v;
 }
 
 template <int NCW>
@@ -56,13 +56,14 @@ __global__ __launch_bounds__(kSlabWaves * 64) void fused_wide_encode_kernel(
   constexpr int kThreadsW = kSlabWaves * 64;
   constexpr int H = kSlabCols / kGroup;                                // 8
   const bool use_table = !is_rtn(NCW) && table != nullptr;     // (a round-to-nearest layer's grid pointers are never read)
-  // grid and cell table: requested now, kept in registers while the main loop owns the LDS
-  constexpr int kGridPoints = is_rtn(NCW) ? 0 : NCW;
-  static_assert(kGridPoints <= kThreadsW, "one grid point per thread");
-  float cb_a = 0.f, cb_b = 0.f;
-  TableRegs<kThreadsW> table_regs;
-  if ((int)threadIdx.x < kGridPoints) { cb_a = codebook[2 * threadIdx.x]; cb_b = codebook[2 * threadIdx.x + 1]; }
-  if (use_table) table_regs.request(table);
+  // the main loop's ring of token rows lies where the parked rows go, so grid and cell table are staged at once
+  static_assert(kSlabLdsBytes <= kParkBytes, "the ring fits where the predictions are parked");
+  load_codebook<NCW>(codebook, cl.cb);
+  if (use_table) {
+    TableRegs<kThreadsW> table_regs;
+    table_regs.request(table);
+    table_regs.store(cl.table);
+  }
 
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -81,16 +82,24 @@ __global__ __launch_bounds__(kSlabWaves * 64) void fused_wide_encode_kernel(
     for (int k = 0; k < 4; ++k) in.x[k] = src[k];
   };
   In in_next;
+  const auto read_p = [&](int prow, float (&p)[32]) {            // this lane's 32 predictions of parked row prow
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const f32x4 a = *reinterpret_cast<const f32x4*>(park + park_index(prow, l * kValsPerLane + 4 * k));
+      p[4 * k] = a.x; p[4 * k + 1] = a.y; p[4 * k + 2] = a.z; p[4 * k + 3] = a.w;
+    }
+  };
 
   f32x16 acc[2][4];
-  gemm_mainloop_token_slab(smem, x0, d0, x1, d1, Wt, T, m0, acc, [&] { fetch(0, 0, in_next); });
+  gemm_mainloop_token_slab(smem + sizeof(Lds), x0, d0, x1, d1, Wt, T, m0, acc);
+  fetch(0, 0, in_next);
 
   float sf[32] = {};
   if constexpr (!is_rtn(NCW)) load_signs(signs, head, q, sf);
 
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
-    if (half == 1) __syncthreads();                  // every wave is done reading the first half's rows
+    __syncthreads();                                 // every wave is done reading the ring, or the first half's rows
     {
       const int frow = lane & 31, fk = lane >> 5;
 #pragma unroll
@@ -103,11 +112,6 @@ __global__ __launch_bounds__(kSlabWaves * 64) void fused_wide_encode_kernel(
           park[park_index(prow, col)] = acc[half][j][r] + bv;
         }
       }
-    }
-    if (half == 0) {                                 // the ring is free: grid and table
-      if ((int)threadIdx.x < kGridPoints)
-        cl.cb[threadIdx.x] = make_float4(cb_a, cb_b, -0.5f * (cb_a * cb_a + cb_b * cb_b), 0.f);
-      if (use_table) table_regs.store(cl.table);
     }
     __syncthreads();                                 // a token's 32 lanes read columns parked by all 8 waves
 
@@ -123,16 +127,19 @@ __global__ __launch_bounds__(kSlabWaves * 64) void fused_wide_encode_kernel(
       const int64_t gid = rowc * H + head;
       const int64_t off = rowc * kSlabCols + l * kValsPerLane;
       float p[32], v[32];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const f32x4 a = *reinterpret_cast<const f32x4*>(park + park_index(prow, l * kValsPerLane + 4 * k));
-        p[4 * k] = a.x; p[4 * k + 1] = a.y; p[4 * k + 2] = a.z; p[4 * k + 3] = a.w;
-      }
+      read_p(prow, p);
 #pragma unroll
       for (int k = 0; k < 4; ++k) unpack_bf16x8(in.x[k], &v[8 * k]);
-      quantize_group<NCW, true>(v, p, sf, l, cl.cb, use_table ? cl.table : nullptr, active, gid, codes, scales,
-                                Xhat != nullptr);
-      if (Xhat != nullptr && active) Storage<bf16_t>::store32(Xhat + off, v);
+#pragma unroll
+      for (int r = 0; r < 32; ++r) v[r] -= p[r];
+      quantize_residual<NCW, true>(v, sf, l, cl.cb, use_table ? cl.table : nullptr, active, gid, codes, scales, Xhat != nullptr);
+      if (Xhat != nullptr) {
+        // the prediction is read again instead of being held through the search (32 registers)
+        asm volatile("" ::: "memory");
+        read_p(prow, p);
+        finish_hat<NCW>(v, sf, p);
+        if (active) Storage<bf16_t>::store32(Xhat + off, v);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
   }
