@@ -17,7 +17,7 @@ namespace {
 
 constexpr int kHalfRows = 32;
 constexpr int kParkBytes = kHalfRows * kSlabCols * 4;                  // 128 KiB
-constexpr int kWideLdsBytes = (int)sizeof(Lds) + kParkBytes;           // grid + table, then the parked half
+constexpr int kWideLdsBytes = (int)sizeof(Lds) + (kParkBytes > kSlabLdsBytes ? kParkBytes : kSlabLdsBytes);   // grid + table, then ring / parked half
 static_assert(kWideLdsBytes <= 160 * 1024, "LDS of one CU");
 
 // Float index of column `col` of parked row `row`.  A lane of the quantizer reads 8 consecutive 16-byte slots (32 of
@@ -56,8 +56,7 @@ __global__ __launch_bounds__(kSlabWaves * 64) void fused_wide_encode_kernel(
   constexpr int kThreadsW = kSlabWaves * 64;
   constexpr int H = kSlabCols / kGroup;                                // 8
   const bool use_table = !is_rtn(NCW) && table != nullptr;     // (a round-to-nearest layer's grid pointers are never read)
-  // the main loop's ring of token rows lies where the parked rows go, so grid and cell table are staged at once
-  static_assert(kSlabLdsBytes <= kParkBytes, "the ring fits where the predictions are parked");
+  // the main loop's rings lie where the parked rows go, behind grid and cell table: those are staged at once
   load_codebook<NCW>(codebook, cl.cb);
   if (use_table) {
     TableRegs<kThreadsW> table_regs;

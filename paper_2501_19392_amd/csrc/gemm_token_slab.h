@@ -4,13 +4,14 @@
 // all 8 heads of a token in one workgroup.
 //
 // Same instruction (v_mfma_f32_32x32x16_bf16), operand orientation and K order per output as gemm_core.h, hence the
-// same bits.  Every workgroup streams the whole of W from L2, and each row of W is multiplied by one wave only, so W does not
-// go through LDS: a wave loads its fragments straight into registers, three steps of 16 k ahead, from a re-tiled copy
-// (retile_w_kernel in fused_wide_encode.hip writes it into the call's workspace; a few microseconds for 2 - 4 MiB) that
-// holds them in the order of use, 1 KiB of consecutive bytes per fragment.  Only the 64 token rows (8 KiB per k-tile of 64)
-// are shared by the waves and staged in LDS.  Bound by what a CU takes from L2: 32 KiB of W per step of 16 k at some 57
-// bytes per cycle are 575 cycles, against 512 cycles of matrix work for the two waves of a SIMD.  (With W staged in LDS the
-// loop took 2560 cycles per 32 k.)
+// same bits.  Every workgroup streams the whole of W, and each row of W is multiplied by one wave only: a wave loads its own
+// fragments, kSlabAhead steps of 16 k ahead, from a re-tiled copy (retile_w_kernel in fused_wide_encode.hip writes it into the
+// call's workspace; a few microseconds for 2 - 4 MiB) that holds them in the order of use, 1 KiB of consecutive bytes per
+// fragment.  Half of them go straight to registers, the other half to a ring of its own in LDS, because neither has room for
+// what must be in flight: the workgroups of an XCD walk W in step, so every step waits for L2 to fetch it once (some 2700
+// cycles), and 57 bytes per cycle into a CU over that time are 150 KiB.  Only the 64 token rows (8 KiB per k-tile of 64) are
+// shared by the waves.  Three steps ahead in registers alone: 1000 cycles per step; two k-tiles of 32 through LDS: 1280.
+// The matrix work of the two waves of a SIMD is 512 cycles per step, 32 KiB at 57 bytes per cycle 575.
 #pragma once
 #include "gemm_core.h"
 
@@ -20,8 +21,11 @@ constexpr int kSlabRows = 64;                          // token rows of a tile
 constexpr int kSlabCols = 1024;                        // outputs of a tile = 8 heads x 128
 constexpr int kSlabWaves = 8;
 constexpr int kSlabStageBytes = kSlabRows * kRowBytes; // 8 KiB: a k-tile of 64 of the token rows
-constexpr int kSlabStages = 4;
-constexpr int kSlabLdsBytes = kSlabStages * kSlabStageBytes;
+constexpr int kSlabStages = 3;
+constexpr int kSlabAhead = 6;                          // steps of 16 k between the request of a W fragment and its use
+constexpr int kSlabSlots = kSlabAhead + 1;             // ring of W fragments in LDS, per wave: 2 KiB a step
+constexpr int kSlabRingBytes = kSlabSlots * 2048;
+constexpr int kSlabLdsBytes = kSlabStages * kSlabStageBytes + kSlabWaves * kSlabRingBytes;      // 136 KiB
 constexpr int kSlabStepBytes = kSlabCols * 16 * 2;     // W of one step of 16 k in the re-tiled copy
 // Byte of the 16-byte chunk of W row `row` (0..1023), inputs 8 chunk ... + 7, in the re-tiled copy: fragment
 // (step = chunk / 2, head, block of 32 rows), lane = row % 32 + 32 (chunk % 2).
@@ -34,9 +38,9 @@ __host__ __device__ constexpr int64_t slab_w_off(int row, int chunk) {
 // `lds_base` points at kSlabLdsBytes bytes of LDS.  The caller puts a barrier before it reuses the LDS.  Requires
 // K = d0 + d1 a multiple of 128, d0 of 64.  `Wt`: the re-tiled copy of the 1024 x K weights.
 //
-// Schedule.  k-tile t of the token rows lives in stage t % 4; wave w loads its rows 8 w ... (one instruction per k-tile), two
+// Schedule.  k-tile t of the token rows lives in stage t % 3; wave w loads its rows 8 w ... (one instruction per k-tile), two
 // k-tiles ahead.  A k-tile is four steps; in step s:
-//   MFMAs (t, s)   + reads of the row fragments of the next step   + loads of the W fragments three steps ahead
+//   MFMAs (t, s)   + LDS reads of the next step's fragments   + requests of the W fragments kSlabAhead steps ahead
 // and before step 3 the barrier that publishes k-tile t + 1.
 __device__ __forceinline__ void gemm_mainloop_token_slab(unsigned char* lds_base, const bf16_t* __restrict__ x0, int d0,
                                                          const bf16_t* __restrict__ x1, int d1,
@@ -59,28 +63,40 @@ __device__ __forceinline__ void gemm_mainloop_token_slab(unsigned char* lds_base
     return (gptr_t)(((uint64_t)hi << 32) | lo);
   };
   const lptr_t lds3 = (lptr_t)lds_base;
-  auto load_rows = [&](int kt) {
+  auto load_rows = [&](int kt, int stage_off) {
     const int k0 = kt * BK;
     const bool second = k0 >= d0;
     const int ld2 = __builtin_amdgcn_readfirstlane((second ? d1 : d0) * 2);
     const gptr_t base = uniform_ptr(reinterpret_cast<const char*>(second ? x1 : x0) +
                                     (m0 * ld2 + (int64_t)(second ? k0 - d0 : k0) * 2));
-    __builtin_amdgcn_global_load_lds(base + ((uint32_t)__umul24(rowc, ld2) + ch16),
-                                     lds3 + ((kt & (kSlabStages - 1)) * kSlabStageBytes + wave * 1024), 16, 0, 0);
+    __builtin_amdgcn_global_load_lds(base + ((uint32_t)__umul24(rowc, ld2) + ch16), lds3 + (stage_off + wave * 1024), 16, 0, 0);
   };
+  // W of a step: blocks 0, 1 of this wave's head to LDS (the wave's ring), blocks 2, 3 to registers, in this order: when the
+  // registers have arrived, so have the LDS ones (loads complete in issue order)
   const uint32_t offW = (uint32_t)(wave * 4096 + lane * 16);
-  struct WFrag { bf16x8 v[4]; };
-  auto load_w = [&](int step, WFrag& f) {
+  const int ring0 = kSlabStages * kSlabStageBytes + wave * kSlabRingBytes;
+  struct WRegs { bf16x8 v[2]; };
+  auto load_w = [&](int step, int slot_off, WRegs& f) {
     const gptr_t base = uniform_ptr(reinterpret_cast<const char*>(Wt) + (int64_t)step * kSlabStepBytes);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) f.v[j] = *reinterpret_cast<const __attribute__((address_space(1))) bf16x8*>(base + offW + j * 1024);
+    for (int j = 0; j < 2; ++j)
+      __builtin_amdgcn_global_load_lds(base + (offW + (uint32_t)(j * 1024)), lds3 + (ring0 + slot_off + j * 1024), 16, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      f.v[j] = *reinterpret_cast<const __attribute__((address_space(1))) bf16x8*>(base + offW + (2 + j) * 1024);
+    __builtin_amdgcn_sched_barrier(0);
   };
   const int frow = lane & 31, fk = lane >> 5;
   struct XFrag { bf16x8 v[2]; };
-  auto read_x = [&](int kt, int ks, XFrag& f) {
+  auto read_x = [&](int stage_off, int ks, XFrag& f) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-      f.v[i] = *reinterpret_cast<const bf16x8*>(lds_base + (kt & (kSlabStages - 1)) * kSlabStageBytes + lds_off(i * 32 + frow, ks * 2 + fk));
+      f.v[i] = *reinterpret_cast<const bf16x8*>(lds_base + stage_off + lds_off(i * 32 + frow, ks * 2 + fk));
+  };
+  auto read_w = [&](int slot_off, WRegs& f) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) f.v[j] = *reinterpret_cast<const bf16x8*>(lds_base + ring0 + slot_off + j * 1024 + lane * 16);
   };
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -94,44 +110,59 @@ __device__ __forceinline__ void gemm_mainloop_token_slab(unsigned char* lds_base
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
+  const auto next_slot = [](int s) { return s + 2048 == kSlabRingBytes ? 0 : s + 2048; };
 
-  load_rows(0);
-  load_rows(1);                                        // nk >= 2
-  __builtin_amdgcn_sched_barrier(0);                   // (the count below wants them older than the fragment loads)
-  WFrag w[4];
-  load_w(0, w[0]);
-  load_w(1, w[1]);
-  load_w(2, w[2]);
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(0x0f70 | 12);             // vmcnt(12): both k-tiles of this wave's rows have landed
+  load_rows(0, 0);
+  load_rows(1, kSlabStageBytes);                       // nk >= 2
+  __builtin_amdgcn_sched_barrier(0);                   // (the counts below want them older than the fragment loads)
+  WRegs w[8];                                          // registers of step n: w[n % 8]
+#pragma unroll
+  for (int n = 0; n < kSlabAhead; ++n) load_w(n < nsteps ? n : nsteps - 1, n * 2048, w[n]);      // nsteps >= 8
+  __builtin_amdgcn_s_waitcnt(0x0f70 | ((4 * (kSlabAhead - 1)) & 15) | (((4 * (kSlabAhead - 1)) >> 4) << 14));   // rows and step 0 have landed
   meet();
   XFrag x[2];
-  read_x(0, 0, x[0]);
+  WRegs wl[2];
+  int cur = 0, nxt = kSlabStageBytes, far = 2 * kSlabStageBytes;      // stages of k-tiles t, t + 1, t + 2
+  int read_slot = 0, load_slot = kSlabAhead * 2048;
+  read_x(cur, 0, x[0]);
+  read_w(read_slot, wl[0]);
   __builtin_amdgcn_sched_barrier(0);
 
-  for (int t = 0; t < nk; ++t) {
-    if (t + 2 < nk) load_rows(t + 2);                  // its stage held k-tile t - 2, read by all before the last barrier
+  for (int t2 = 0; t2 < nk; t2 += 2) {                 // two k-tiles = eight steps at a time (nk is even)
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      if (s == 3 && t + 1 < nk) {
-        // Publish k-tile t + 1.  This wave's rows of it were requested a k-tile ago, before 16 of the fragment loads issued
-        // since; at most 12 of those (three steps) and the rows of t + 2 may still be out.
-        __builtin_amdgcn_s_waitcnt(0x0070 | 13);       // vmcnt(13) lgkmcnt(0)
-        meet();
-      }
-      const int step = 4 * t + s;
-      const WFrag& wf = w[s];
-      const XFrag& xf = x[s & 1];
-      if (s < 3) read_x(t, s + 1, x[(s + 1) & 1]);
-      else if (t + 1 < nk) read_x(t + 1, 0, x[0]);
+    for (int u = 0; u < 8; ++u) {
+      const int t = t2 + (u >> 2), s = u & 3, step = 4 * t2 + u;
+      const auto mma = [&](int m) {
+        const int i = m & 1, j = m >> 1;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[u & 1].v[i], j < 2 ? wl[u & 1].v[j] : w[u].v[j - 2], acc[i][j], 0, 0, 0);
+      };
+      // The memory work of a step goes behind its first two MFMAs: the compiler waits for every outstanding LDS read before
+      // the first of them (it cannot count reads beside direct-to-LDS loads), so none for the next step may be out by then.
+      mma(0);
+      mma(1);
+      __builtin_amdgcn_sched_barrier(0);
+      // (the stage of k-tile t + 2 held k-tile t - 1: every wave had its last reads back before k-tile t was published)
+      if (s == 0 && t + 2 < nk) load_rows(t + 2, far);
       // (behind the last step the loads repeat it: the count of loads in flight stays the same)
-      load_w(step + 3 < nsteps ? step + 3 : nsteps - 1, w[(s + 3) & 3]);
+      load_w(step + kSlabAhead < nsteps ? step + kSlabAhead : nsteps - 1, load_slot, w[(u + kSlabAhead) & 7]);
+      load_slot = next_slot(load_slot);
+      // The next step's fragments have landed when at most the loads of the kSlabAhead - 1 steps behind it are out (4 each).
+      // In step 3 that covers this wave's rows of k-tile t + 1 as well: requested seven steps ago, they are older.
+      __builtin_amdgcn_s_waitcnt(0x0f70 | ((4 * (kSlabAhead - 1)) & 15) | (((4 * (kSlabAhead - 1)) >> 4) << 14));
+      asm volatile("" ::: "memory");
+      read_slot = next_slot(read_slot);
+      if (s == 3 && t + 1 < nk) {
+        meet();                                        // (its reads of k-tile t returned before the MFMAs above)
+        read_x(nxt, 0, x[(u + 1) & 1]);
+        const int old = cur;
+        cur = nxt; nxt = far; far = old;
+      } else if (s < 3) {
+        read_x(cur, s + 1, x[(u + 1) & 1]);
+      }
+      read_w(read_slot, wl[(u + 1) & 1]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v[i], wf.v[j], acc[i][j], 0, 0, 0);
+      for (int m = 2; m < 8; ++m) mma(m);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
