@@ -86,33 +86,53 @@ template <int SHIFT> __device__ __forceinline__ float4 grid_entry(const float4* 
   return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(cb) + ((uint32_t)slot << (4 - SHIFT)));
 }
 
-// The table entry of the cell of y.
+// LDS byte offset (inside the table) of the cell of y.  Both coordinates go to [0, 1] over the cells' range, are clamped and
+// converted to 16 bits by one instruction, and the top six bits of each are the cell.  Against exact cells the edges sit up
+// to 6.1e-5 off (65535 / 65536 and the rounding to nearest), inside the 1e-4 by which the builder enlarges every cell when
+// it lists candidates, so the candidate sets still hold and the codes are the same.  Six vector instructions per
+// sub-vector; clamping, truncating and combining the coordinates one by one takes nine.
+template <int NCW>
+__device__ __forceinline__ uint32_t cell_offset(float y0, float y1) {
+  const float inv_range = cell_scale(NCW) / kCells;
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  const u16x2 c = __builtin_amdgcn_cvt_pknorm_u16(__fmaf_rn(y0, inv_range, 0.5f), __fmaf_rn(y1, inv_range, 0.5f));
+  const uint32_t d = __builtin_bit_cast(uint32_t, c);
+  // byte 0: x cell and two spare bits (bits 8 .. 15 of d); byte 1: y cell (bits 26 .. 31 of d)
+  return __builtin_amdgcn_perm(d >> 18, d, 0x0c0c0501u) & 0x3ffcu;
+}
+static_assert(kCells == 64, "six bits per coordinate");
 template <int NCW>
 __device__ __forceinline__ uint32_t cell_entry(float y0, float y1, const uint32_t* table) {
-  const float fx = __builtin_amdgcn_fmed3f(__fmaf_rn(y0, cell_scale(NCW), 0.5f * kCells), 0.0f, kCells - 0.5f);
-  const float fy = __builtin_amdgcn_fmed3f(__fmaf_rn(y1, cell_scale(NCW), 0.5f * kCells), 0.0f, kCells - 0.5f);
-  return table[(int)fy * kCells + (int)fx];
+  return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(table) + cell_offset<NCW>(y0, y1));
 }
 
-// Table search: score the (up to 4, ascending, last one repeated) candidates of the cell entry; returns the winner's slot.
-// If the cell lists too many points (entry >= crowded_threshold) the result is void: the caller then redoes the
-// sub-vector from the cell's overflow list, or with the full search (rare; keeps the hot path small).
-template <int NCW>
-__device__ __forceinline__ int search_cell(float y0, float y1, uint32_t e, const float4* cb) {
-  constexpr int SH = Slot<NCW>::kShift;
-  int slot = e & 0xff;
-  float best = score(y0, y1, grid_entry<SH>(cb, slot));
-  constexpr int kCand = NCW == 16 ? 3 : 4;       // the builder marks cells of a 16-point grid with more than 3
+// Table search of one sub-vector from the (up to 4, ascending, last one repeated) candidates its cell entry lists, fetched
+// beforehand; returns the winner's slot.  If the cell lists too many points (entry >= crowded_threshold) the result is
+// void: the caller then redoes the sub-vector from the cell's overflow list, or with the full search (rare; keeps the hot
+// path small).
+template <int NCW> struct Candidates {
+  static constexpr int kCand = NCW == 16 ? 3 : 4;       // the builder marks cells of a 16-point grid with more than 3
+  float c[kCand][3];
+  __device__ __forceinline__ void fetch(uint32_t e, const float4* cb) {
 #pragma unroll
-  for (int k = 1; k < kCand; ++k) {
-    const int j = (e >> (8 * k)) & 0xff;
-    const float s = score(y0, y1, grid_entry<SH>(cb, j));
-    const bool better = s > best;                // duplicates of the last candidate never win
-    best = better ? s : best;
-    slot = better ? j : slot;
+    for (int k = 0; k < kCand; ++k) {
+      const float4 g = grid_entry<Slot<NCW>::kShift>(cb, (int)((e >> (8 * k)) & 0xff));
+      c[k][0] = g.x; c[k][1] = g.y; c[k][2] = g.z;
+    }
   }
-  return slot;
-}
+  __device__ __forceinline__ int winner(float y0, float y1, uint32_t e) const {
+    int slot = e & 0xff;
+    float best = score(y0, y1, make_float4(c[0][0], c[0][1], c[0][2], 0.f));
+#pragma unroll
+    for (int k = 1; k < kCand; ++k) {
+      const float s = score(y0, y1, make_float4(c[k][0], c[k][1], c[k][2], 0.f));
+      const bool better = s > best;              // duplicates of the last candidate never win
+      best = better ? s : best;
+      slot = better ? (int)((e >> (8 * k)) & 0xff) : slot;
+    }
+    return slot;
+  }
+};
 
 // Full search (the definition: all n points, lowest index wins ties) of N sub-vectors: their slots.
 template <int NCW, int N>
@@ -415,8 +435,20 @@ __device__ __forceinline__ void quantize_residual(float (&v)[32], const float (&
       uint32_t e[BATCH], top = 0;
 #pragma unroll
       for (int k = 0; k < BATCH; ++k) e[k] = cell_entry<NCW>(y[2 * k], y[2 * k + 1], table);
+      if constexpr (BATCH > 4) {                     // registers to spare: all candidates requested before any is scored
+        Candidates<NCW> cand[BATCH];
 #pragma unroll
-      for (int k = 0; k < BATCH; ++k) slot[k] = search_cell<NCW>(y[2 * k], y[2 * k + 1], e[k], cb);
+        for (int k = 0; k < BATCH; ++k) cand[k].fetch(e[k], cb);
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) slot[k] = cand[k].winner(y[2 * k], y[2 * k + 1], e[k]);
+      } else {
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) {
+          Candidates<NCW> cand;
+          cand.fetch(e[k], cb);
+          slot[k] = cand.winner(y[2 * k], y[2 * k + 1], e[k]);
+        }
+      }
 #pragma unroll
       for (int k = 0; k < BATCH; ++k) top = max(top, e[k]);
       if (__builtin_expect(__builtin_amdgcn_ballot_w64(top >= crowded_threshold(NCW)) != 0, 0)) {

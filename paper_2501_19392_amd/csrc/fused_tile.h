@@ -163,7 +163,7 @@ __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per
         if constexpr (kEnc) {
 #pragma unroll
           for (int k = 0; k < 4; ++k) unpack_bf16x8(in[h & 1].x[k], &v[8 * k]);
-          quantize_group<NCW, false, 8>(v, p, sf, q, cl.cb, use_table ? cl.table : nullptr, active, gid, a.codes, a.scales,
+          quantize_group<NCW, false, S::MI < 5 ? 8 : 4>(v, p, sf, q, cl.cb, use_table ? cl.table : nullptr, active, gid, a.codes, a.scales,
                               a.Xhat != nullptr);
         } else if constexpr (kWideGrid) {
           dequantize_across_heads<NCW>(wide[h & 1], in[h & 1].w.scale, head, q, p, sf, cl.cb, v);
