@@ -392,13 +392,13 @@ def cpu_baseline(cfg, n_codewords, rows, q_heads, n_layers, rtn_bits=0):
                       f"({dt:.1f} s of CPU time; cost is linear in rows and layers)"}
 
 
-PEAK_FP64_TFLOPS = 78.6          # MI355X fp64 vector
+PEAK_FP64_TFLOPS = 78.6          # MI355X fp64, vector and matrix
 
 
 def calibration_path(args, device):
     """Calibration of the predictors (Alg. "Calibration") on the Llama-3.2-3B KV shape: a step = for every predicted
     layer fit f_key, encode the keys, fit f_value, encode the values (paper_2501_19392_amd.calibrate).  Reported
-    per layer; the roofline entry is the fit call (fp64 FMA arithmetic; FLOPs of the two Gram products, the
+    per layer; the roofline entry is the fit call (fp64 matrix cores; FLOPs of the two Gram products, the
     factorisation and the solves)."""
     import torch
     from paper_2501_19392_amd import binding as B
