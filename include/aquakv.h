@@ -411,6 +411,48 @@ typedef struct aquakv_copy_range {
 } aquakv_copy_range;
 int aquakv_copy_ranges(const aquakv_copy_range* ranges, int32_t n, void* stream);
 
+/*
+ * aquakv_attend_cache -- attention of one new token per sequence over a whole cache (Alg. "Inference", Sect. 3.3): for every
+ * layer in order, recover the compressed ranges of all sequences, then out = softmax(score_scale * q K^T) V over sinks,
+ * compressed past and recent tokens of the query's own sequence, whose token t has position t.  n_sink, n_compressed, n_recent:
+ * HOST arrays [batch] of the tokens there are; every sequence must have at least one.  Sequence b's codes, scales (and raw_k /
+ * raw_v) start at row b * capacity, its sinks at row b * sink_rows, its recent tokens at row b * recent_rows.
+ * rope_cos / rope_sin (both NULL, or device fp32 [tokens, 64]): the keys are held from before the rotary embedding, as in
+ * aquakv_decode_attn_scores_rope.  `hat`: HOST array of four device buffers, K and V of even layers, K and V of odd layers, each
+ * with room for the compressed tokens of all sequences: layer l is recovered into pair l % 2 and read for layer l + 1.
+ * `staged` (needed when batch > 1): room for the compressed tokens of all sequences in the layout of the layer's code and scale
+ * tensors, where they are put one behind the other.  `workspace`: aquakv_attend_cache_workspace_bytes() bytes, 0 for an
+ * unsupported configuration.  Nothing is kept from call to call.
+ */
+typedef struct aquakv_cache_layer {
+  const aquakv_layer* layer;              /* NULL: the layer's compressed range is held in the storage dtype */
+  const uint8_t* k_codes;                 /* [batch * capacity, ...] as written by aquakv_encode_layer */
+  const uint16_t* k_scales;
+  const uint8_t* v_codes;
+  const uint16_t* v_scales;
+  uint8_t* staged_k_codes;                /* batch > 1 */
+  uint16_t* staged_k_scales;
+  uint8_t* staged_v_codes;
+  uint16_t* staged_v_scales;
+  const void* raw_k;                      /* layer == NULL: [batch * capacity, kv_heads, 128] */
+  const void* raw_v;
+  const void* sink_k;                     /* [batch, sink_rows, kv_heads, 128] */
+  const void* sink_v;
+  const void* recent_k;                   /* [batch, recent_rows, kv_heads, 128] */
+  const void* recent_v;
+  const void* q;                          /* [batch, q_heads, 128] */
+  float* out;                             /* fp32 [batch, q_heads, 128] */
+} aquakv_cache_layer;
+typedef struct aquakv_cache_shape {
+  int32_t dtype, kv_heads, q_heads, batch, sink_rows, recent_rows;
+  int64_t capacity;
+} aquakv_cache_shape;
+size_t aquakv_attend_cache_workspace_bytes(const aquakv_cache_layer* layers, int32_t n_layers, const aquakv_cache_shape* shape);
+int aquakv_attend_cache(const aquakv_cache_layer* layers, int32_t n_layers, const aquakv_cache_shape* shape,
+                        const int32_t* n_sink, const int32_t* n_compressed, const int32_t* n_recent,
+                        const float* rope_cos, const float* rope_sin, float score_scale, void* const* hat,
+                        void* workspace, size_t workspace_bytes, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

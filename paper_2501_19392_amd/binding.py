@@ -41,7 +41,7 @@ EXPORTS = [
     "aquakv_encode_keys", "aquakv_encode_values", "aquakv_decode_values",
     "aquakv_fit_workspace_bytes", "aquakv_fit_predictor",
     "aquakv_softmax", "aquakv_weighted_workspace_bytes", "aquakv_decode_values_weighted", "aquakv_decode_values_attend",
-    "aquakv_attend_raw", "aquakv_copy_ranges",
+    "aquakv_attend_raw", "aquakv_copy_ranges", "aquakv_attend_cache_workspace_bytes", "aquakv_attend_cache",
 ]
 
 
@@ -54,6 +54,17 @@ class aquakv_layer(ctypes.Structure):
         ("w_k", ctypes.c_void_p), ("b_k", ctypes.c_void_p), ("w_v", ctypes.c_void_p), ("b_v", ctypes.c_void_p),
         ("search_table", ctypes.c_void_p),
     ]
+
+
+class aquakv_cache_layer(ctypes.Structure):
+    _fields_ = [("layer", ctypes.POINTER(aquakv_layer))] + [(n, ctypes.c_void_p) for n in (
+        "k_codes", "k_scales", "v_codes", "v_scales", "staged_k_codes", "staged_k_scales", "staged_v_codes", "staged_v_scales",
+        "raw_k", "raw_v", "sink_k", "sink_v", "recent_k", "recent_v", "q", "out")]
+
+
+class aquakv_cache_shape(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("dtype", "kv_heads", "q_heads", "batch", "sink_rows", "recent_rows")] + [
+        ("capacity", ctypes.c_int64)]
 
 
 _P = ctypes.c_void_p
@@ -99,7 +110,11 @@ _lib.aquakv_decode_values_weighted.argtypes = [_LP, ctypes.c_int32, ctypes.c_int
 _lib.aquakv_decode_values_attend.argtypes = [_LP, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32] + [_P] * 9 + [ctypes.c_size_t, _P]
 _lib.aquakv_attend_raw.argtypes = [ctypes.c_int32] * 5 + [_P, _P, _P, _P, _P, ctypes.c_float, _P, _P, ctypes.c_int32, _P]
 _lib.aquakv_copy_ranges.argtypes = [_P, ctypes.c_int32, _P]
-for _n in ("aquakv_copy_ranges", "aquakv_attend_raw", "aquakv_softmax", "aquakv_decode_values_weighted", "aquakv_decode_values_attend", "aquakv_predict", "aquakv_quantize", "aquakv_dequantize", "aquakv_encode_layer", "aquakv_decode_layer",
+_CLP, _CSP = ctypes.POINTER(aquakv_cache_layer), ctypes.POINTER(aquakv_cache_shape)
+_lib.aquakv_attend_cache_workspace_bytes.restype = ctypes.c_size_t
+_lib.aquakv_attend_cache_workspace_bytes.argtypes = [_CLP, ctypes.c_int32, _CSP]
+_lib.aquakv_attend_cache.argtypes = [_CLP, ctypes.c_int32, _CSP] + [_P] * 5 + [ctypes.c_float, _P, _P, ctypes.c_size_t, _P]
+for _n in ("aquakv_attend_cache", "aquakv_copy_ranges", "aquakv_attend_raw", "aquakv_softmax", "aquakv_decode_values_weighted", "aquakv_decode_values_attend", "aquakv_predict", "aquakv_quantize", "aquakv_dequantize", "aquakv_encode_layer", "aquakv_decode_layer",
            "aquakv_decode_attn_scores", "aquakv_decode_attn_scores_rope", "aquakv_decode_attn_scores_folded",
            "aquakv_decode_attn_scores_folded_static", "aquakv_encode_keys", "aquakv_encode_values",
            "aquakv_decode_values", "aquakv_fit_predictor"):
@@ -377,6 +392,33 @@ def aquakv_copy_ranges(ranges, stream=None) -> None:
     """ranges: flat sequence of addresses and sizes, (dst, src, bytes) per copy."""
     flat = array.array("Q", ranges)
     _check(_lib.aquakv_copy_ranges(flat.buffer_info()[0], len(flat) // 3, _stream(stream)))
+
+
+def cache_layers(entries):
+    """The layer array of aquakv_attend_cache.  entries: per layer (Layer or None, {field: tensor or None})."""
+    arr = (aquakv_cache_layer * len(entries))()
+    for e, (layer, fields) in zip(arr, entries):
+        if layer is not None:
+            e.layer = ctypes.pointer(layer.c if isinstance(layer, Layer) else layer)
+        for name, x in fields.items():
+            setattr(e, name, _ptr(x))
+    return arr
+
+
+def aquakv_attend_cache_workspace_bytes(layers, shape) -> int:
+    return _lib.aquakv_attend_cache_workspace_bytes(layers, len(layers), ctypes.byref(shape))
+
+
+def aquakv_attend_cache(layers, shape, n_sink, n_compressed, n_recent, score_scale: float, hat, workspace, rope_cos=None,
+                        rope_sin=None, stream=None) -> None:
+    """layers: cache_layers(...), with q set; n_*: token counts per sequence; hat: the four recovery buffers."""
+    n = len(n_sink)
+    counts = array.array("i", [*n_sink, *n_compressed, *n_recent])
+    at = counts.buffer_info()[0]
+    hats = array.array("Q", [_ptr(h) or 0 for h in hat])
+    w, wb = _ws(workspace)
+    _check(_lib.aquakv_attend_cache(layers, len(layers), ctypes.byref(shape), at, at + 4 * n, at + 8 * n, _ptr(rope_cos),
+                                    _ptr(rope_sin), score_scale, hats.buffer_info()[0], w, wb, _stream(stream)))
 
 
 def aquakv_fit_workspace_bytes(d_in: int, d_out: int) -> int:

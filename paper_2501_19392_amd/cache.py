@@ -29,7 +29,7 @@ This class is bookkeeping only: every number is produced by the C-ABI calls (`aq
 """
 from __future__ import annotations
 
-from typing import Dict, Iterator, List, Optional, Sequence, Tuple
+from typing import Iterator, List, Optional, Sequence, Tuple
 
 import torch
 
@@ -72,11 +72,11 @@ class AquaKVCache:
         self._flush_in = [(raw(R), raw(R)) for _ in range(2)] if batch > 1 else None
         self._flush_codes = [None if l is None or batch == 1 else (l.alloc_codes(R, device), l.alloc_codes(R, device))
                              for l in self.layers]
-        # recovery: [sinks | compressed | buffer] of one layer and sequence (sweep), or the compressed ranges of a
-        # group of sequences (attend): two ping-pong pairs
+        # recovery: [sinks | compressed | buffer] of one layer and sequence (sweep), or the compressed ranges of all
+        # sequences (attend, which puts their codes one behind the other first): two ping-pong pairs
         self._view = [(raw(max(max_tokens, batch * C)), raw(max(max_tokens, batch * C))) for _ in range(2)]
         self._view_ws = biggest(lambda l: l.alloc_workspace(batch * C, device))
-        self._group_codes = [None if l is None or batch == 1 else (l.alloc_codes(batch * C, device), l.alloc_codes(batch * C, device))
+        self._staged = [None if l is None or batch == 1 else (l.alloc_codes(batch * C, device), l.alloc_codes(batch * C, device))
                              for l in self.layers]
         self._ns, self._nc, self._nb = [0] * batch, [0] * batch, [0] * batch
         self._attend = None                 # buffers of attend(), sized on first use (they depend on the query heads)
@@ -317,102 +317,52 @@ class AquaKVCache:
         """queries[l]: the new token's queries at layer l in the storage dtype, [q_heads, head_dim] for a single
         sequence, [batch, q_heads, head_dim] otherwise.  Returns one fp32 tensor of the same shape per layer:
         softmax(score_scale * q K^T) V over sinks, compressed past and buffer of the query's own sequence.
-        One sweep over the layers per group of sequences with equally long compressed ranges; the recovered tensors
-        of layer l feed layer l + 1 as in `sweep`.
+        One sweep over the layers for all sequences (aquakv_attend_cache); the recovered tensors of layer l feed
+        layer l + 1 as in `sweep`.
         rope = (cos, sin), device fp32 [>= n_tokens, head_dim / 2]: the cache holds keys from before the rotary
         embedding (Sect. 3.3, the paper's default); the key of token t of a sequence is rotated by row t on the fly,
         the queries are taken as already rotated, and what is recovered for the next layer stays unrotated."""
         if any(s + c + b == 0 for s, c, b in zip(self._ns, self._nc, self._nb)):
             raise ValueError("nothing cached")
-        H, g, dt, NB = self._H, self._g, self._dt, self.batch
         single = queries[0].dim() == 2
-        if single and NB != 1:
+        if single and self.batch != 1:
             raise ValueError("a batched cache takes [batch, q_heads, head_dim]")
-        qs = [q[None] if single else q for q in queries]
-        QH = qs[0].shape[1]
-        if self._attend is None or self._attend["q_heads"] != QH:
-            coded = [l for l in self.layers if l is not None]
-            self._attend = dict(
-                q_heads=QH,
-                scores=torch.empty(NB * QH * self._C, dtype=torch.float32, device=self._device),
-                out=[torch.empty(NB, QH, g, dtype=torch.float32, device=self._device) for _ in self.layers],
-                group_out=torch.empty(NB, QH, g, dtype=torch.float32, device=self._device),
-                group_q=torch.empty(NB, QH, g, dtype=dt, device=self._device),
-                stats=torch.empty(NB, QH, 2, dtype=torch.float32, device=self._device),
-                ws=max((l.alloc_weighted_workspace(NB, self._C, QH, self._device) for l in coded), key=lambda t: t.numel()))
+        QH = queries[0].shape[-2]
+        if self._attend is None or self._attend["shape"].q_heads != QH:
+            self._attend = self._attend_state(QH)
         A = self._attend
-        step = 4096                                              # tokens per aquakv_attend_raw call
+        shape = (QH, self._g) if single else (self.batch, QH, self._g)
+        for entry, q in zip(A["layers"], queries, strict=True):
+            if q.shape != shape or q.dtype != self._dt:
+                raise ValueError(f"queries must be {list(shape)}, {self._dt}")
+            entry.q = q.data_ptr() if q.is_contiguous() else None
+        # queries with gaps are copied; they must live until the call has been queued
+        kept = [q.contiguous() for q in queries] if any(e.q is None for e in A["layers"]) else queries
+        for entry, q in zip(A["layers"], kept):
+            entry.q = q.data_ptr()
         cos, sin = rope if rope is not None else (None, None)
-        rows = lambda t, a, n: None if t is None else t[a:a + n]  # the angles of tokens a ... a + n - 1
-        C = self._C
-        groups: Dict[int, List[int]] = {}
-        for b in range(NB):
-            groups.setdefault(self._nc[b], []).append(b)
-        for c, members in groups.items():
-            n = len(members)
-            direct = n == 1                                      # one sequence: its own ranges, nothing is gathered
-            in_place = members == list(range(NB))                # the whole batch in order: results need no scatter
-            first = members[0] * C
-            s0 = self._ns[members[0]]                            # compressed tokens exist only behind full sinks
-            Kp = Vp = None
-            for l, lay in enumerate(self.layers):
-                q = qs[l] if in_place else A["group_q"][:n]
-                if not in_place:
-                    for i, b in enumerate(members):
-                        q[i].copy_(qs[l][b])
-                out = A["out"][l] if in_place else A["group_out"][:n]
-                stats = A["stats"][:n]
-                have = False
-                K, V = (t[:n * c] for t in self._view[l & 1])
-                if c and lay is None:                            # compressed range kept in 16 bits
-                    for i, b in enumerate(members):
-                        Kb, Vb = self.raw[l][0][b * C:b * C + c], self.raw[l][1][b * C:b * C + c]
-                        for r0 in range(0, c, step):
-                            m = min(step, c - r0)
-                            B.aquakv_attend_raw(dt, 1, m, H, QH, Kb[r0:r0 + m], Vb[r0:r0 + m], q[i:i + 1], score_scale,
-                                                out[i:i + 1], stats[i:i + 1], r0 > 0,
-                                                rope_cos=rows(cos, s0 + r0, m), rope_sin=rows(sin, s0 + r0, m))
-                        if not direct:
-                            K[i * c:(i + 1) * c].copy_(Kb); V[i * c:(i + 1) * c].copy_(Vb)
-                    Kp, Vp = (self.raw[l][0][first:first + c], self.raw[l][1][first:first + c]) if direct else (K, V)
-                    have = True
-                elif c:
-                    (kc, ks), (vc, vs) = self.codes[l]
-                    if direct:
-                        kc, ks, vc, vs = (t[first:first + c] for t in (kc, ks, vc, vs))
-                    else:
-                        staged = [t[:n * c] for pair in self._group_codes[l] for t in pair]
-                        for i, b in enumerate(members):
-                            for dst, src in zip(staged, (kc, ks, vc, vs)):
-                                dst[i * c:(i + 1) * c].copy_(src[b * C:b * C + c])
-                        kc, ks, vc, vs = staged
-                    scores = A["scores"][:n * QH * c].view(n, QH, c)
-                    if rope is None:
-                        B.aquakv_decode_attn_scores(lay, n, c, QH, kc, ks, Kp, q, score_scale, scores, K, self._view_ws)
-                    else:
-                        B.aquakv_decode_attn_scores_rope(lay, n, c, QH, kc, ks, Kp, q, rows(cos, s0, c), rows(sin, s0, c),
-                                                         score_scale, scores, K, self._view_ws)
-                    B.aquakv_decode_values_attend(lay, n, c, QH, vc, vs, Vp, K, scores, V, out, stats, A["ws"])
-                    Kp, Vp = K, V
-                    have = True
-                for i, b in enumerate(members):
-                    s, nb = self._ns[b], self._nb[b]
-                    mine = have
-                    if s:
-                        B.aquakv_attend_raw(dt, 1, s, H, QH, self.sink[l][0][b, :s], self.sink[l][1][b, :s], q[i:i + 1],
-                                            score_scale, out[i:i + 1], stats[i:i + 1], mine,
-                                            rope_cos=rows(cos, 0, s), rope_sin=rows(sin, 0, s))
-                        mine = True
-                    for r0 in range(0, nb, step):
-                        m = min(step, nb - r0)
-                        B.aquakv_attend_raw(dt, 1, m, H, QH, self.buf[l][0][b, r0:r0 + m], self.buf[l][1][b, r0:r0 + m],
-                                            q[i:i + 1], score_scale, out[i:i + 1], stats[i:i + 1], mine,
-                                            rope_cos=rows(cos, s + c + r0, m), rope_sin=rows(sin, s + c + r0, m))
-                        mine = True
-                if not in_place:
-                    for i, b in enumerate(members):
-                        A["out"][l][b].copy_(out[i])
+        B.aquakv_attend_cache(A["layers"], A["shape"], self._ns, self._nc, self._nb, score_scale, A["hat"], A["ws"], cos, sin)
         return [o[0] if single else o for o in A["out"]]
+
+    def _attend_state(self, q_heads: int) -> dict:
+        """What attend() passes on every call for this number of query heads."""
+        out = [torch.empty(self.batch, q_heads, self._g, dtype=torch.float32, device=self._device) for _ in self.layers]
+        entries = []
+        for l, lay in enumerate(self.layers):
+            fields = dict(sink_k=self.sink[l][0], sink_v=self.sink[l][1], recent_k=self.buf[l][0], recent_v=self.buf[l][1], out=out[l])
+            if lay is None:
+                fields.update(raw_k=self.raw[l][0], raw_v=self.raw[l][1])
+            else:
+                names = ("k_codes", "k_scales", "v_codes", "v_scales")
+                fields.update(zip(names, (t for pair in self.codes[l] for t in pair)))
+                if self._staged[l] is not None:
+                    fields.update(zip(("staged_" + n for n in names), (t for pair in self._staged[l] for t in pair)))
+            entries.append((lay, fields))
+        layers = B.cache_layers(entries)
+        shape = B.aquakv_cache_shape(B._dtype_code(self._dt), self._H, q_heads, self.batch, max(self.sink_tokens, 1),
+                                     self.buffer_tokens, self._C)
+        ws = torch.empty(B.aquakv_attend_cache_workspace_bytes(layers, shape), dtype=torch.uint8, device=self._device)
+        return dict(layers=layers, shape=shape, out=out, ws=ws, hat=[t for pair in self._view for t in pair])
 
     def stored_bytes(self) -> int:
         """Bytes the cache content occupies (all layers, all sequences): 16-bit sinks and buffer, packed codes and

@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <mutex>
+#include <vector>
 
 #include "../../include/aquakv.h"
 #include "kernels.h"
@@ -947,6 +948,209 @@ int aquakv_decode_attn_scores_rope(const aquakv_layer* L, int32_t batch, int32_t
   CHECK(check_ptr(rope_sin, "rope_sin", true));
   return decode_attn_scores(L, batch, seq_len, q_heads, k_codes, k_scales, Khat_prev, q, rope_cos, rope_sin, score_scale,
                             scores, Khat_out, workspace, workspace_bytes, stream_, kFormDefinition);
+}
+
+}  // extern "C"
+
+// ---- attention over a whole cache ----------------------------------------------------------------------------
+namespace {
+int64_t attend_pieces(int64_t tokens) { return (tokens + aquakv::kAttendPiece - 1) / aquakv::kAttendPiece; }
+size_t attend_layer_bytes(int64_t pieces, int32_t q_heads) {      // sums and soft-max statistics of one layer
+  return ((size_t)pieces * q_heads * (128 + 2) * sizeof(float) + 255) & ~(size_t)255;
+}
+constexpr size_t kAttendRoom = (size_t)32 << 20;                  // of partial results before they are merged
+int check_cache(const aquakv_cache_layer* layers, int32_t n_layers, const aquakv_cache_shape* sh) {
+  if (layers == nullptr || sh == nullptr) return fail(AQUAKV_ENULL, "layers / shape is NULL");
+  if (n_layers < 1) return fail(AQUAKV_EINVAL, "n_layers=%d", n_layers);
+  if (sh->dtype != AQUAKV_BF16 && sh->dtype != AQUAKV_FP32) return fail(AQUAKV_EINVAL, "dtype=%d", sh->dtype);
+  if (sh->kv_heads < 1 || sh->kv_heads > 4096 || sh->q_heads < 1 || sh->q_heads % sh->kv_heads || sh->q_heads > 65536)
+    return fail(AQUAKV_EINVAL, "q_heads=%d must be a multiple of kv_heads=%d", sh->q_heads, sh->kv_heads);
+  if (sh->batch < 1 || sh->sink_rows < 0 || sh->recent_rows < 0 || sh->capacity < 0)
+    return fail(AQUAKV_EINVAL, "batch=%d sink_rows=%d recent_rows=%d capacity=%lld", sh->batch, sh->sink_rows, sh->recent_rows,
+                (long long)sh->capacity);
+  if (sh->capacity + sh->sink_rows + sh->recent_rows > 0x7fffffff - aquakv::kAttendPiece)
+    return fail(AQUAKV_EUNSUPPORTED, "capacity=%lld", (long long)sh->capacity);
+  for (int32_t l = 0; l < n_layers; ++l) {
+    const aquakv_layer* L = layers[l].layer;
+    if (L == nullptr) continue;
+    CHECK(check_layer(L));
+    if (L->kv_heads != sh->kv_heads || L->dtype != sh->dtype)
+      return fail(AQUAKV_EINVAL, "layer %d: kv_heads=%d dtype=%d differ from the cache's", l, L->kv_heads, L->dtype);
+  }
+  return AQUAKV_OK;
+}
+size_t attend_decode_bytes(const aquakv_cache_layer* layers, int32_t n_layers, int64_t tokens) {
+  size_t most = 16;
+  for (int32_t l = 0; l < n_layers && tokens > 0; ++l) {
+    if (layers[l].layer == nullptr) continue;
+    const Plan pl = make_plan(layers[l].layer, tokens);
+    most = pl.p_bytes + pl.khat_bytes > most ? pl.p_bytes + pl.khat_bytes : most;
+  }
+  return (most + 255) & ~(size_t)255;
+}
+}  // namespace
+
+extern "C" {
+
+size_t aquakv_attend_cache_workspace_bytes(const aquakv_cache_layer* layers, int32_t n_layers, const aquakv_cache_shape* sh) {
+  if (check_cache(layers, n_layers, sh) != AQUAKV_OK) return 0;
+  const size_t one = attend_layer_bytes(sh->batch * attend_pieces(sh->sink_rows + sh->capacity + sh->recent_rows), sh->q_heads);
+  const size_t fit = one < kAttendRoom ? kAttendRoom / one : 1;
+  return attend_decode_bytes(layers, n_layers, sh->batch * sh->capacity) + one * (fit < (size_t)n_layers ? fit : n_layers);
+}
+
+int aquakv_attend_cache(const aquakv_cache_layer* layers, int32_t n_layers, const aquakv_cache_shape* sh, const int32_t* n_sink,
+                        const int32_t* n_compressed, const int32_t* n_recent, const float* rope_cos, const float* rope_sin,
+                        float score_scale, void* const* hat, void* workspace, size_t workspace_bytes, void* stream_) {
+  CHECK(check_cache(layers, n_layers, sh));
+  if (n_sink == nullptr || n_compressed == nullptr || n_recent == nullptr || hat == nullptr)
+    return fail(AQUAKV_ENULL, "n_sink / n_compressed / n_recent / hat is NULL");
+  if ((rope_cos == nullptr) != (rope_sin == nullptr)) return fail(AQUAKV_ENULL, "rope_cos and rope_sin go together");
+  CHECK(check_ptr(rope_cos, "rope_cos", false));
+  CHECK(check_ptr(rope_sin, "rope_sin", false));
+  const int NB = sh->batch;
+  const size_t row = (size_t)sh->kv_heads * 128 * elem_bytes(sh->dtype);
+  int64_t compressed = 0, pieces = 0;
+  bool any_sink = false, any_recent = false;
+  int first = -1, last = -1;                      // sequences with compressed tokens
+  bool adjacent = true;                           // their ranges lie one behind the other as they are
+  for (int b = 0; b < NB; ++b) {
+    if (n_sink[b] < 0 || n_sink[b] > sh->sink_rows || n_compressed[b] < 0 || n_compressed[b] > sh->capacity || n_recent[b] < 0 ||
+        n_recent[b] > sh->recent_rows)
+      return fail(AQUAKV_EINVAL, "sequence %d: %d + %d + %d tokens do not fit the cache", b, n_sink[b], n_compressed[b], n_recent[b]);
+    const int64_t n = (int64_t)n_sink[b] + n_compressed[b] + n_recent[b];
+    if (n == 0) return fail(AQUAKV_EINVAL, "sequence %d: nothing cached", b);
+    any_sink |= n_sink[b] != 0;
+    any_recent |= n_recent[b] != 0;
+    if (n_compressed[b] != 0) {
+      if (first < 0) first = b;
+      else if (last != b - 1 || n_compressed[last] != sh->capacity) adjacent = false;
+      last = b;
+    }
+    compressed += n_compressed[b];
+    pieces += attend_pieces(n);
+  }
+  if (pieces > 0x7fffffff / sh->kv_heads) return fail(AQUAKV_EUNSUPPORTED, "%lld pieces of the sequences", (long long)pieces);
+  const size_t decode_bytes = attend_decode_bytes(layers, n_layers, compressed);
+  const size_t one = attend_layer_bytes(pieces, sh->q_heads);
+  CHECK(check_ptr(workspace, "workspace", true));
+  if (workspace_bytes < decode_bytes + one)
+    return fail(AQUAKV_EWORKSPACE, "workspace %zu B < required %zu B", workspace_bytes, decode_bytes + one);
+  const int hold = (int)((workspace_bytes - decode_bytes) / one < aquakv::kAttendMergeLayers ? (workspace_bytes - decode_bytes) / one
+                                                                                      : aquakv::kAttendMergeLayers);
+  for (int i = 0; i < 4; ++i) CHECK(check_ptr(hat[i], "hat", compressed != 0));
+  for (int32_t l = 0; l < n_layers; ++l) {
+    const aquakv_cache_layer& c = layers[l];
+    CHECK(check_ptr(c.sink_k, "sink_k", any_sink));
+    CHECK(check_ptr(c.sink_v, "sink_v", any_sink));
+    CHECK(check_ptr(c.recent_k, "recent_k", any_recent));
+    CHECK(check_ptr(c.recent_v, "recent_v", any_recent));
+    CHECK(check_ptr(c.q, "q", true));
+    CHECK(check_ptr(c.out, "out", true));
+    if (c.layer == nullptr) {
+      CHECK(check_ptr(c.raw_k, "raw_k", compressed != 0));
+      CHECK(check_ptr(c.raw_v, "raw_v", compressed != 0));
+    } else if (compressed != 0) {
+      CHECK(check_ptr(c.k_codes, "k_codes", true));
+      CHECK(check_scales(c.layer, c.k_scales, "k_scales", true));
+      CHECK(check_ptr(c.v_codes, "v_codes", true));
+      CHECK(check_scales(c.layer, c.v_scales, "v_scales", true));
+      if (!adjacent) {
+        CHECK(check_ptr(c.staged_k_codes, "staged_k_codes", true));
+        CHECK(check_scales(c.layer, c.staged_k_scales, "staged_k_scales", true));
+        CHECK(check_ptr(c.staged_v_codes, "staged_v_codes", true));
+        CHECK(check_scales(c.layer, c.staged_v_scales, "staged_v_scales", true));
+      }
+    }
+  }
+  hipStream_t stream = static_cast<hipStream_t>(stream_);
+  const int64_t first_row = first * sh->capacity;
+
+  // the ranges of the sequences one behind the other
+  std::vector<aquakv::CopyRange> copies;
+  const auto gather = [&](void* dst, const void* src, size_t row_bytes) {
+    int64_t to = 0;
+    for (int b = first; b <= last; ++b) {
+      if (n_compressed[b] == 0) continue;
+      copies.push_back({at(dst, to, row_bytes), at(src, b * sh->capacity, row_bytes), n_compressed[b] * row_bytes});
+      to += n_compressed[b];
+    }
+  };
+  if (compressed != 0 && !adjacent) {
+    for (int32_t l = 0; l < n_layers; ++l) {
+      const aquakv_cache_layer& c = layers[l];
+      if (c.layer == nullptr) continue;
+      const size_t crow = make_plan(c.layer, 1).code_row, srow = scale_row_bytes(c.layer);
+      gather(c.staged_k_codes, c.k_codes, crow);
+      gather(c.staged_k_scales, c.k_scales, srow);
+      gather(c.staged_v_codes, c.v_codes, crow);
+      gather(c.staged_v_scales, c.v_scales, srow);
+    }
+    HIP_TRY(aquakv::launch_copy_ranges(copies.data(), (int)copies.size(), stream));
+  }
+  float* const part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + decode_bytes);
+  const int64_t part_elems = pieces * sh->q_heads * 128, layer_elems = (int64_t)(one / sizeof(float));
+  const void *Kp = nullptr, *Vp = nullptr;
+  int held = 0;
+  for (int32_t l = 0; l < n_layers; ++l) {
+    const aquakv_cache_layer& c = layers[l];
+    void *K = hat[2 * (l & 1)], *V = hat[2 * (l & 1) + 1];
+    if (compressed != 0 && c.layer != nullptr) {
+      const size_t crow = make_plan(c.layer, 1).code_row, srow = scale_row_bytes(c.layer);
+      const auto codes = [&](const uint8_t* own, const uint8_t* staged) {
+        return adjacent ? static_cast<const uint8_t*>(at(own, first_row, crow)) : staged;
+      };
+      const auto scales = [&](const uint16_t* own, const uint16_t* staged) {
+        return adjacent ? static_cast<const uint16_t*>(at(own, first_row, srow)) : staged;
+      };
+      CHECK(aquakv_decode_layer(c.layer, compressed, codes(c.k_codes, c.staged_k_codes), scales(c.k_scales, c.staged_k_scales),
+                                codes(c.v_codes, c.staged_v_codes), scales(c.v_scales, c.staged_v_scales), Kp, Vp, K, V, workspace,
+                                decode_bytes, stream));
+      Kp = K; Vp = V;
+    } else if (compressed != 0 && adjacent) {
+      Kp = at(c.raw_k, first_row, row); Vp = at(c.raw_v, first_row, row);
+    } else if (compressed != 0) {
+      copies.clear();
+      gather(K, c.raw_k, row);
+      gather(V, c.raw_v, row);
+      HIP_TRY(aquakv::launch_copy_ranges(copies.data(), (int)copies.size(), stream));
+      Kp = K; Vp = V;
+    }
+    aquakv::AttendCacheArgs a = {};
+    a.sink_k = c.sink_k; a.sink_v = c.sink_v; a.compressed_k = Kp; a.compressed_v = Vp; a.recent_k = c.recent_k; a.recent_v = c.recent_v;
+    a.q = c.q; a.rope_cos = rope_cos; a.rope_sin = rope_sin;
+    a.part = part + held * layer_elems; a.stats = a.part + part_elems;
+    a.scale = score_scale;
+    a.kv_heads = sh->kv_heads; a.q_heads = sh->q_heads; a.sink_rows = sh->sink_rows; a.recent_rows = sh->recent_rows;
+    const bool merge = ++held == hold || l + 1 == n_layers;
+    int64_t from = 0;
+    int piece = 0;
+    for (int b0 = 0; b0 < NB; b0 += aquakv::kAttendSeqs) {
+      a.seq0 = b0;
+      a.pieces.n_seq = NB - b0 < aquakv::kAttendSeqs ? NB - b0 : aquakv::kAttendSeqs;
+      for (int i = 0; i < a.pieces.n_seq; ++i) {
+        const int b = b0 + i;
+        a.pieces.first[i] = piece;
+        a.n_sink[i] = n_sink[b]; a.n_compressed[i] = n_compressed[b];
+        a.n_tokens[i] = n_sink[b] + n_compressed[b] + n_recent[b];
+        a.compressed_row[i] = from;
+        from += n_compressed[b];
+        piece += (int)attend_pieces(a.n_tokens[i]);
+      }
+      a.pieces.first[a.pieces.n_seq] = piece;
+      HIP_TRY(aquakv::launch_attend_cache(sh->dtype, a, stream));
+      if (merge) {
+        aquakv::MergeArgs m = {};
+        m.part = part; m.stats = part + part_elems;
+        m.part_layer = m.stats_layer = layer_elems;
+        m.q_heads = sh->q_heads; m.seq0 = b0; m.pieces = a.pieces;
+        for (int i = 0; i < held; ++i) m.out[i] = layers[l + 1 - held + i].out;
+        HIP_TRY(aquakv::launch_merge_pieces(m, held, stream));
+      }
+    }
+    if (merge) held = 0;
+  }
+  return AQUAKV_OK;
 }
 
 }  // extern "C"

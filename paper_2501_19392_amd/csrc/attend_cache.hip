@@ -1,0 +1,259 @@
+// Attention of one new token per sequence over a cache (Alg. "Inference", Sect. 3.3 of the AQUA-KV paper): over sinks, recovered
+// compressed past and recent-token buffer of every sequence of a batch, whatever their lengths, in one launch per layer and one
+// more that merges the pieces of several layers.  (Separate launches per sequence, and per kind of token, were 2.5 ms a token for
+// 4 sequences of 1020 - 1800 tokens and 8 layers; now 0.56 ms, of which the recovery of the compressed tokens is 0.46 ms.)
+//
+// The tokens of a sequence are numbered through, [sinks | compressed | recent], and cut into pieces of 64; a workgroup takes
+// one piece of one kv head for all its query heads, so the split follows the tokens there are and no sequence waits for another.
+// A token's place in memory is picked row by row, and its number is its position for the rotary embedding.
+// All sums run in a fixed order, so a call gives the same bits every time.
+#include "device_utils.h"
+#include "kernels.h"
+
+namespace aquakv {
+namespace {
+
+constexpr int kThreads = 256;
+constexpr int kPasses = kAttendPiece / 16;            // 16 lanes per token, 16 tokens per pass of the workgroup
+static_assert(kPasses == 4, "a quad of lanes shares the exponentials of its four tokens");
+constexpr int kMaxRep = 8;                            // query heads worked on at a time
+
+template <int C> __device__ __forceinline__ float dpp(float x) {      // x of the lane that DPP control C names
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), C, 0xf, 0xf, true));
+}
+// The sum over the 16 lanes of a token; every lane gets it (fixed order).
+__device__ __forceinline__ float sum16(float x) {
+  x = quad_sum(x);
+  x = x + dpp<0x141>(x);                              // row_half_mirror: the other quad of the 8
+  return x + dpp<0x140>(x);                           // row_mirror: the other 8
+}
+
+// Reductions over the four groups of 16 lanes of a wave (a wave's tokens of one pass).  The gfx950 lane swaps exchange halves
+// between two registers, v_permlane32_swap the upper 32 lanes of the first with the lower 32 of the second, v_permlane16_swap
+// the odd groups of the first with the even ones of the second: adding the pair reduces two values at once, and they cost no
+// trip through LDS as shuffles do.
+__device__ __forceinline__ float fold32(float x, float y) {      // lanes < 32: x over both halves, lanes >= 32: y
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float fold16(float x, float y) {      // even groups: x over the pair of groups, odd groups: y
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float max_quad(float x) {
+  x = fmaxf(x, dpp<0xb1>(x));                          // quad_perm 1 0 3 2
+  return fmaxf(x, dpp<0x4e>(x));                       // quad_perm 2 3 0 1
+}
+__device__ __forceinline__ float max_groups(float x) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// Lane l of a token holds coordinates 4 l ... and 64 + 4 l ... of the key (pairs of the rotary embedding) and 8 l ... of the value.
+template <typename T> struct Row;
+template <> struct Row<bf16_t> {
+  u32x2 lo, hi;
+  u32x4 v;
+  __device__ __forceinline__ void load(const bf16_t* k, const bf16_t* val, int l) {
+    lo = *reinterpret_cast<const u32x2*>(k + 4 * l);
+    hi = *reinterpret_cast<const u32x2*>(k + 64 + 4 * l);
+    v = *reinterpret_cast<const u32x4*>(val + 8 * l);
+  }
+  static __device__ __forceinline__ void unpack4(const u32x2& u, float (&f)[8], int at) {
+    f[at] = __uint_as_float(u.x << 16); f[at + 1] = __uint_as_float(u.x & 0xffff0000u);
+    f[at + 2] = __uint_as_float(u.y << 16); f[at + 3] = __uint_as_float(u.y & 0xffff0000u);
+  }
+  __device__ __forceinline__ void key(float (&f)[8]) const { unpack4(lo, f, 0); unpack4(hi, f, 4); }
+  __device__ __forceinline__ void value(float (&f)[8]) const { unpack_bf16x8(v, f); }
+};
+template <> struct Row<float> {
+  f32x4 lo, hi, v0, v1;
+  __device__ __forceinline__ void load(const float* k, const float* val, int l) {
+    lo = *reinterpret_cast<const f32x4*>(k + 4 * l);
+    hi = *reinterpret_cast<const f32x4*>(k + 64 + 4 * l);
+    v0 = *reinterpret_cast<const f32x4*>(val + 8 * l);
+    v1 = *reinterpret_cast<const f32x4*>(val + 8 * l + 4);
+  }
+  static __device__ __forceinline__ void put4(const f32x4& u, float (&f)[8], int at) {
+    f[at] = u.x; f[at + 1] = u.y; f[at + 2] = u.z; f[at + 3] = u.w;
+  }
+  __device__ __forceinline__ void key(float (&f)[8]) const { put4(lo, f, 0); put4(hi, f, 4); }
+  __device__ __forceinline__ void value(float (&f)[8]) const { put4(v0, f, 0); put4(v1, f, 4); }
+};
+
+// blockIdx.x = piece * kv heads + head.  All rows of the piece are requested at once; thread (ts = tid / 16, l = tid % 16) owns
+// tokens ts, ts + 16, ... of it.  Every wave takes the soft-max of its own tokens, so the waves meet once, to merge.
+// part[piece, q_heads, 128]: sums with weights exp(score - maximum); stats[piece, q_heads, 2]: maximum and sum of the weights.
+// Bound by the instructions per query head, hence the sharing of exponentials in a quad and the lane swaps: 5640 tokens in four
+// sequences, 8 kv heads, 32 query heads, rotary embedding: 9.8 us; 11.5 us with an exponential per lane and the values unpacked
+// per query head, 18 us also with shuffles through LDS and pieces of 128 (two workgroups per CU).  128 tokens: 6 us, which is
+// launch and memory latency.
+template <typename T>
+__global__ __launch_bounds__(kThreads, 2) void attend_cache_kernel(const AttendCacheArgs a) {
+  __shared__ float q_lds[kMaxRep][kGroup];
+  __shared__ float sums[4][kMaxRep][kGroup];
+  __shared__ float wave_stats[4][kMaxRep][2];
+  const int head = blockIdx.x % a.kv_heads, piece = a.pieces.first[0] + (int)blockIdx.x / a.kv_heads;
+  int b = 0;
+  for (int step = kAttendSeqs / 2; step > 0; step >>= 1)
+    if (b + step < a.pieces.n_seq && a.pieces.first[b + step] <= piece) b += step;
+  const int rep = a.q_heads / a.kv_heads;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int ts = threadIdx.x >> 4, l = threadIdx.x & 15;
+  const int t0 = (piece - a.pieces.first[b]) * kAttendPiece;
+  const int ns = a.n_sink[b], nc = a.n_compressed[b], n = a.n_tokens[b];
+  const int64_t row_elems = (int64_t)a.kv_heads * kGroup;
+  const int64_t seq = a.seq0 + b;
+
+  Row<T> rows[kPasses];
+#pragma unroll
+  for (int p = 0; p < kPasses; ++p) {
+    int t = t0 + p * 16 + ts;
+    t = t < n ? t : n - 1;                             // beyond the end: weight 0 below
+    const void *kb = a.sink_k, *vb = a.sink_v;
+    int64_t row = seq * a.sink_rows + t;
+    if (t >= ns) { kb = a.compressed_k; vb = a.compressed_v; row = a.compressed_row[b] + t - ns; }
+    if (t >= ns + nc) { kb = a.recent_k; vb = a.recent_v; row = seq * a.recent_rows + t - ns - nc; }
+    const int64_t off = row * row_elems + head * kGroup;
+    rows[p].load(static_cast<const T*>(kb) + off, static_cast<const T*>(vb) + off, l);
+  }
+  f32x4 cs[kPasses], sn[kPasses];
+  if (a.rope_cos != nullptr) {
+#pragma unroll
+    for (int p = 0; p < kPasses; ++p) {
+      int t = t0 + p * 16 + ts;
+      t = t < n ? t : n - 1;
+      cs[p] = *reinterpret_cast<const f32x4*>(a.rope_cos + (int64_t)t * 64 + 4 * l);
+      sn[p] = *reinterpret_cast<const f32x4*>(a.rope_sin + (int64_t)t * 64 + 4 * l);
+    }
+  }
+  float k[kPasses][8], v[kPasses][8];
+  for (int r0 = 0; r0 < rep; r0 += kMaxRep) {
+    const int nr = rep - r0 < kMaxRep ? rep - r0 : kMaxRep;
+    const int qh0 = head * rep + r0;
+    const T* qp = static_cast<const T*>(a.q) + (seq * a.q_heads + qh0) * kGroup;
+    for (int e = threadIdx.x; e < nr * kGroup; e += kThreads) q_lds[e / kGroup][e % kGroup] = static_cast<float>(qp[e]);
+    __syncthreads();
+    if (r0 == 0) {
+#pragma unroll
+      for (int p = 0; p < kPasses; ++p) {
+        rows[p].key(k[p]);
+        rows[p].value(v[p]);
+        if (a.rope_cos != nullptr) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float x0 = k[p][i], x1 = k[p][4 + i];
+            k[p][i] = __fmaf_rn(x0, cs[p][i], -(x1 * sn[p][i]));
+            k[p][4 + i] = __fmaf_rn(x1, cs[p][i], x0 * sn[p][i]);
+          }
+        }
+      }
+    }
+#pragma unroll 1
+    for (int r = 0; r < nr; ++r) {
+      const f32x4 q0 = *reinterpret_cast<const f32x4*>(&q_lds[r][4 * l]), q1 = *reinterpret_cast<const f32x4*>(&q_lds[r][64 + 4 * l]);
+      const float q[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+      float s[kPasses];
+#pragma unroll
+      for (int p = 0; p < kPasses; ++p) {
+        float d = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) d = __fmaf_rn(q[i], k[p][i], d);
+        s[p] = sum16(d) * a.scale;
+      }
+      // the 16 lanes of a token hold the same four scores: each takes the exponential of one, and the quad passes them round
+      float mine = lane & 1 ? s[1] : s[0];
+      const float upper = lane & 1 ? s[3] : s[2];
+      mine = lane & 2 ? upper : mine;
+      if (t0 + (lane & 3) * 16 + ts >= n) mine = -INFINITY;
+      const float m = max_groups(max_quad(mine));
+      const float shift = m == -INFINITY ? 0.f : m;    // a wave without tokens
+      const float weight = expf(mine - shift);
+      float sum = quad_sum(weight), acc[8] = {};
+#pragma unroll
+      for (int p = 0; p < kPasses; ++p) {
+        const float e = p == 0 ? dpp<0x00>(weight) : p == 1 ? dpp<0x55>(weight) : p == 2 ? dpp<0xaa>(weight) : dpp<0xff>(weight);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] = __fmaf_rn(e, v[p][i], acc[i]);
+      }
+      sum = fold32(sum, sum);
+      sum = fold16(sum, sum);
+      // lane group g ends with coordinates 4 (g / 2) + 2 (g % 2) ... of the lane's eight
+      float f[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) f[i] = fold32(acc[i], acc[4 + i]);
+      f32x2 o;
+      o.x = fold16(f[0], f[2]);
+      o.y = fold16(f[1], f[3]);
+      *reinterpret_cast<f32x2*>(&sums[wave][r][8 * l + 2 * (lane >> 4)]) = o;
+      if (lane == 0) { wave_stats[wave][r][0] = m; wave_stats[wave][r][1] = sum; }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < nr * kGroup; e += kThreads) {
+      const int r = e / kGroup, d = e % kGroup;
+      const float M = fmaxf(fmaxf(wave_stats[0][r][0], wave_stats[1][r][0]), fmaxf(wave_stats[2][r][0], wave_stats[3][r][0]));
+      float sum = 0.f, den = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const float f = expf(wave_stats[w][r][0] - M);
+        sum = __fmaf_rn(f, sums[w][r][d], sum);
+        den = __fmaf_rn(f, wave_stats[w][r][1], den);
+      }
+      const int64_t row = (int64_t)piece * a.q_heads + qh0 + r;
+      a.part[row * kGroup + d] = sum;
+      if (d == 0) { a.stats[row * 2] = M; a.stats[row * 2 + 1] = den; }
+    }
+    __syncthreads();                                   // LDS is free for the next query heads
+  }
+}
+
+// out[layer][b, qh, d] = sum_c e^(m_c - M) part_c / sum_c e^(m_c - M) l_c over the pieces c of sequence b, M = max_c m_c.
+// blockIdx = (b * q_heads + qh, layer); thread = (dim, parity of the piece).
+__global__ __launch_bounds__(kThreads) void merge_pieces_kernel(const MergeArgs a) {
+  __shared__ float red[kThreads];
+  __shared__ float den2[2];
+  const int b = blockIdx.x / a.q_heads, qh = blockIdx.x % a.q_heads;
+  const int c0 = a.pieces.first[b], c1 = a.pieces.first[b + 1];
+  const float* const part = a.part + blockIdx.y * a.part_layer + qh * kGroup;
+  const float* const stats = a.stats + blockIdx.y * a.stats_layer + qh * 2;
+  const int d = threadIdx.x & (kGroup - 1), par = threadIdx.x >> 7;
+  float m = -INFINITY;
+  for (int c = c0 + threadIdx.x; c < c1; c += kThreads) m = fmaxf(m, stats[(int64_t)c * a.q_heads * 2]);
+#pragma unroll
+  for (int s = 1; s < 64; s <<= 1) m = fmaxf(m, __shfl_xor(m, s));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  const float M = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  __syncthreads();
+  float sum = 0.f, den = 0.f;
+#pragma unroll 8
+  for (int c = c0 + par; c < c1; c += 2) {
+    const float e = expf(stats[(int64_t)c * a.q_heads * 2] - M);
+    sum = __fmaf_rn(e, part[(int64_t)c * a.q_heads * kGroup + d], sum);
+    den = __fmaf_rn(e, stats[(int64_t)c * a.q_heads * 2 + 1], den);
+  }
+  red[threadIdx.x] = sum;
+  if (d == 0) den2[par] = den;
+  __syncthreads();
+  if (par == 0) a.out[blockIdx.y][((a.seq0 + b) * a.q_heads + qh) * kGroup + d] = (red[d] + red[kGroup + d]) / (den2[0] + den2[1]);
+}
+
+}  // namespace
+
+hipError_t launch_attend_cache(int dtype, const AttendCacheArgs& a, hipStream_t stream) {
+  const unsigned blocks = (unsigned)((int64_t)(a.pieces.first[a.pieces.n_seq] - a.pieces.first[0]) * a.kv_heads);
+  if (blocks == 0) return hipSuccess;
+  if (dtype == kBF16) attend_cache_kernel<bf16_t><<<blocks, kThreads, 0, stream>>>(a);
+  else attend_cache_kernel<float><<<blocks, kThreads, 0, stream>>>(a);
+  return hipGetLastError();
+}
+
+hipError_t launch_merge_pieces(const MergeArgs& a, int layers, hipStream_t stream) {
+  if (layers == 0 || a.pieces.n_seq == 0) return hipSuccess;
+  merge_pieces_kernel<<<dim3((unsigned)(a.pieces.n_seq * a.q_heads), (unsigned)layers), kThreads, 0, stream>>>(a);
+  return hipGetLastError();
+}
+
+}  // namespace aquakv

@@ -128,6 +128,38 @@ hipError_t launch_folded_scores(int n_codewords, const void* Khat_prev, const vo
                                 const uint16_t* scales, const void* q, float score_scale, float* scores, void* workspace,
                                 int batch, int seq_len, int q_heads, hipStream_t stream);
 
+// Attention over the caches of up to kAttendSeqs sequences (attend_cache.hip).  Sequence b of the launch has pieces
+// [first[b], first[b + 1]) of kAttendPiece tokens each, numbered over the whole batch.
+constexpr int kAttendPiece = 64;
+constexpr int kAttendSeqs = 64;                   // sequences per launch: their counts travel in the kernel arguments
+constexpr int kAttendMergeLayers = 32;            // layers merged per launch
+struct Pieces {
+  int n_seq;
+  int first[kAttendSeqs + 1];
+};
+struct AttendCacheArgs {
+  const void *sink_k, *sink_v, *compressed_k, *compressed_v, *recent_k, *recent_v;    // rows of kv_heads x 128
+  const void* q;                                  // [batch, q_heads, 128]
+  const float *rope_cos, *rope_sin;               // nullable, [tokens, 64]
+  float *part, *stats;                            // [pieces, q_heads, 128], [pieces, q_heads, 2]
+  float scale;
+  int kv_heads, q_heads, sink_rows, recent_rows;  // rows per sequence of the sink and recent tensors
+  int64_t seq0;                                   // the launch's first sequence
+  int n_sink[kAttendSeqs], n_compressed[kAttendSeqs], n_tokens[kAttendSeqs];
+  int64_t compressed_row[kAttendSeqs];            // first row of a sequence's compressed range
+  Pieces pieces;
+};
+hipError_t launch_attend_cache(int dtype, const AttendCacheArgs& a, hipStream_t stream);
+struct MergeArgs {
+  const float *part, *stats;
+  int64_t part_layer, stats_layer;                // elements from one layer to the next
+  int q_heads;
+  int64_t seq0;
+  float* out[kAttendMergeLayers];
+  Pieces pieces;
+};
+hipError_t launch_merge_pieces(const MergeArgs& a, int layers, hipStream_t stream);
+
 // Ridge least-squares fit of a predictor, W [d_out, d0 + d1] = argmin || [x0 | x1] W^T - Y ||^2 + lambda ||W||^2 with
 // lambda = rate * trace(X^T X) / d_in, in fp64 through the normal equations.  d0, d1, d_out multiples of 64.
 // `workspace`: fit_workspace_bytes(d0 + d1, d_out).  W64 (nullable): the unrounded solution [d_out, d_in].

@@ -1,0 +1,87 @@
+"""aquakv_attend_cache through the cache manager: attention of one new token per sequence against a plain soft-max in fp64 over the
+tensors that the manager's own sweep recovers.  Lengths at the edges of the 64-token pieces, sequences with and without
+compressed tokens side by side, ranges that need not be gathered, more sequences than one launch takes, layers in the storage
+dtype, every number of query heads per kv head, and a workspace that holds one layer's partial results."""
+import pytest
+import torch
+
+from paper_2501_19392_amd import synth
+from tests import parity_utils as U
+
+pytestmark = pytest.mark.gpu
+
+
+def plain_attention(q, K, V, scale, rope):
+    """q [QH, 128], K, V [n, H, 128] -> [QH, 128] in fp64"""
+    q, K, V = q.double(), K.double(), V.double()
+    if rope is not None:
+        c, s = (t[:K.shape[0], None].double() for t in rope)
+        lo, hi = K[..., :64], K[..., 64:]
+        K = torch.cat([lo * c - hi * s, hi * c + lo * s], -1)
+    rep = q.shape[0] // K.shape[1]
+    K, V = K.repeat_interleave(rep, 1), V.repeat_interleave(rep, 1)
+    p = torch.softmax((K * q[None]).sum(-1) * scale, 0)
+    return (p[..., None] * V).sum(0)
+
+
+@pytest.mark.parametrize("dtype,H,QH,sinks,recent,lengths,raw_layers,rope", [
+    ("bf16", 8, 32, 4, 16, [63, 64, 65, 5], (), True), ("bf16", 8, 8, 4, 16, [128, 129, 1, 191], (1,), False),
+    ("fp32", 2, 16, 0, 8, [64, 72, 9], (0,), True), ("bf16", 2, 2, 3, 100, [100, 320, 17], (), True),
+    ("bf16", 1, 3, 2, 6, [8 + i % 25 for i in range(70)], (), True), ("bf16", 4, 20, 4, 16, [260], (2,), True),
+    ("bf16", 8, 64, 4, 32, [4 + 64 + 7] * 3, (), False), ("fp32", 1, 8, 4, 8, [3], (), False)])
+def test_attend_over_ragged_caches(dtype, H, QH, sinks, recent, lengths, raw_layers, rope):
+    from paper_2501_19392_amd.cache import AquaKVCache
+    print(f"case attend cache dtype={dtype} H={H} QH={QH} sinks={sinks} recent={recent} lengths={lengths[:8]} raw={raw_layers} "
+          f"rope={rope}", flush=True)
+    L, NB, n, D = 3, len(lengths), max(lengths), H * 128
+    sd = synth.torch_dtype(dtype)
+    gen = torch.Generator().manual_seed(n + QH)
+    layers, kv, qs = [], [], []
+    for l in range(L):
+        w = [None, None]
+        if l > 0:
+            w = [0.3 * torch.randn(D, d, generator=gen) / d ** 0.5 for d in (D, 2 * D)]
+        lay = U.make_layers(H, dtype, 16, layer_idx=l, w_k=w[0], w_v=w[1])[1]
+        layers.append(None if l in raw_layers else lay)
+        kv.append(tuple(torch.randn(NB, n, H, 128, generator=gen).to(sd).cuda() for _ in range(2)))
+        qs.append((2.0 * torch.randn(NB, QH, 128, generator=gen)).to(sd).cuda())
+    tables = tuple(f(torch.rand(n, 64, generator=gen) * 6).float().cuda() for f in (torch.cos, torch.sin)) if rope else None
+    cache = AquaKVCache(layers, max_tokens=n, sink_tokens=sinks, buffer_tokens=recent, batch=NB)
+    single = NB == 1
+    cache.append([(K[0], V[0]) if single else (K, V) for K, V in kv], lengths=None if single else lengths)
+    scale = 128 ** -0.5
+    got = [o.clone().view(NB, QH, 128) for o in cache.attend([q[0] if single else q for q in qs], scale, tables)]
+    # the same with room for the partial results of one layer only
+    whole = cache._attend["ws"]
+    per_layer = (sum(-(-t // 64) for t in lengths) * QH * 130 * 4 + 255) // 256 * 256
+    codec = max([lay.alloc_workspace(NB * cache._C).numel() for lay in layers if lay is not None])
+    cache._attend["ws"] = torch.empty((codec + 255) // 256 * 256 + per_layer, dtype=torch.uint8, device="cuda")
+    again = [o.clone().view(NB, QH, 128) for o in cache.attend([q[0] if single else q for q in qs], scale, tables)]
+    cache._attend["ws"] = whole
+    for l in range(L):
+        assert torch.equal(got[l], again[l])
+    for b in range(NB):
+        for l, K, V in cache.sweep(b):
+            want = plain_attention(qs[l][b], K, V, scale, tables)
+            err = (got[l][b].double() - want).abs().max() / V.double().square().mean().sqrt()
+            assert err < 1e-5, (b, l, float(err))
+
+
+def test_attend_refuses_what_does_not_fit():
+    from paper_2501_19392_amd import binding as B
+    from paper_2501_19392_amd.cache import AquaKVCache
+    lay = U.make_layers(1, "bf16", 16)[1]
+    cache = AquaKVCache([lay], max_tokens=40, sink_tokens=4, buffer_tokens=8)
+    kv = torch.randn(40, 1, 128).bfloat16().cuda()
+    with pytest.raises(ValueError):
+        cache.attend([kv[0].contiguous()], 1.0)                        # nothing cached
+    cache.append([(kv, kv)])
+    with pytest.raises(ValueError):
+        cache.attend([kv[0].float()], 1.0)
+    cache.attend([kv[0].contiguous()], 1.0)
+    A = cache._attend
+    for bad in (dict(n_sink=[5]), dict(n_compressed=[41]), dict(n_recent=[9]), dict(n_sink=[0], n_compressed=[0], n_recent=[0]),
+                dict(workspace=A["ws"][:256])):
+        args = dict(n_sink=[4], n_compressed=[32], n_recent=[4], workspace=A["ws"]) | bad
+        with pytest.raises(B.AquaKVError):
+            B.aquakv_attend_cache(A["layers"], A["shape"], score_scale=1.0, hat=A["hat"], **args)
