@@ -49,38 +49,63 @@ class AquaKVCache:
         lay0 = next(l for l in self.layers if l is not None)
         H, g, dt = lay0.kv_heads, lay0.head_dim, lay0.dtype
         self._H, self._g, self._dt = H, g, dt
-        raw = lambda *shape: torch.empty(*shape, H, g, dtype=dt, device=device)
-        self._row_bytes = H * g * torch.empty(0, dtype=dt).element_size()      # one token's keys (or values)
-        S = max(sink_tokens, 1)
-        self.sink = [(raw(batch, S), raw(batch, S)) for _ in self.layers]
-        self.buf = [(raw(batch, buffer_tokens), raw(batch, buffer_tokens)) for _ in self.layers]
+        L, S, R, buf = len(self.layers), max(sink_tokens, 1), batch * buffer_tokens, buffer_tokens
         cap = max(max_tokens - sink_tokens, 0) // buffer_tokens * buffer_tokens      # the compressed range grows by whole buffers
         self.capacity = cap
         C = max(cap, 1)
         self._C = C
+        # A cache is made per request, so what it costs counts: tensors of one shape are slices of one allocation, and the
+        # addresses that every append needs are worked out here.
+        raws = lambda n, *shape: torch.empty(n, *shape, H, g, dtype=dt, device=device).unbind(0)
+        pairs = lambda ts: list(zip(ts[::2], ts[1::2]))
+        self._like = torch.empty(0, dtype=dt, device=device)
+        self._row_bytes = H * g * self._like.element_size()                          # one token's keys (or values)
+        self.sink = pairs(raws(2 * L, batch, S))
+        self.buf = pairs(raws(2 * L, batch, buf))
         # sequence b owns tokens [b * C, (b + 1) * C) of the code tensors (and of the 16-bit tensors of a layer given as None)
-        self.codes = [None if l is None else (l.alloc_codes(batch * C, device), l.alloc_codes(batch * C, device))
-                      for l in self.layers]
-        self.raw = [(raw(batch * C), raw(batch * C)) if l is None else None for l in self.layers]
-        coded = [l for l in self.layers if l is not None]
-        biggest = lambda make: max((make(l) for l in coded), key=lambda t: t.numel())
+        self.codes = self._alloc_codes(batch * C, device)
+        raw = iter(pairs(raws(2 * sum(l is None for l in self.layers), batch * C)))
+        self.raw = [next(raw) if l is None else None for l in self.layers]
         # flush: reconstructions of the flushed tokens, two ping-pong pairs (layer l - 1 feeds layer l); with several
         # sequences also the gathered buffers and the codes before they are scattered to their sequences
-        R = batch * buffer_tokens
-        self._flush_hat = [(raw(R), raw(R)) for _ in range(2)]
-        self._flush_ws = biggest(lambda l: l.alloc_workspace(R, device))
-        self._flush_in = [(raw(R), raw(R)) for _ in range(2)] if batch > 1 else None
-        self._flush_codes = [None if l is None or batch == 1 else (l.alloc_codes(R, device), l.alloc_codes(R, device))
-                             for l in self.layers]
+        self._flush_hat = pairs(raws(4, R))
+        self._flush_ws = self._alloc_workspace(R, device)
+        self._flush_in = pairs(raws(4, R)) if batch > 1 else None
+        self._flush_codes = self._alloc_codes(R, device) if batch > 1 else [None] * L
         # recovery: [sinks | compressed | buffer] of one layer and sequence (sweep), or the compressed ranges of all
         # sequences (attend, which puts their codes one behind the other first): two ping-pong pairs
-        self._view = [(raw(max(max_tokens, batch * C)), raw(max(max_tokens, batch * C))) for _ in range(2)]
-        self._view_ws = biggest(lambda l: l.alloc_workspace(batch * C, device))
-        self._staged = [None if l is None or batch == 1 else (l.alloc_codes(batch * C, device), l.alloc_codes(batch * C, device))
-                             for l in self.layers]
+        self._view = pairs(raws(4, max(max_tokens, batch * C)))
+        self._view_ws = self._alloc_workspace(batch * C, device)
+        self._staged = self._alloc_codes(batch * C, device) if batch > 1 else [None] * L
+        self._sink_at, self._buf_at = ([t.data_ptr() for pair in ts for t in pair] for ts in (self.sink, self.buf))
+        # per layer the four code tensors' (address, bytes per token)
+        self._codes_at = [None if c is None else [(t.data_ptr(), t[0].nbytes) for pair in c for t in pair] for c in self.codes]
         self._ns, self._nc, self._nb = [0] * batch, [0] * batch, [0] * batch
         self._attend = None                 # buffers of attend(), sized on first use (they depend on the query heads)
         self._device = device
+
+    def _alloc_codes(self, tokens: int, device) -> list:
+        """((k codes, k scales), (v codes, v scales)) per layer, None where the layer is; layers of one format share two
+        allocations."""
+        kinds = {}
+        for l, lay in enumerate(self.layers):
+            if lay is not None:
+                kinds.setdefault((lay.n_codewords, lay.rtn_bits, lay.rht_group), []).append(l)
+        out = [None] * len(self.layers)
+        for members in kinds.values():
+            codes, scales = self.layers[members[0]].alloc_codes(2 * len(members) * tokens, device)
+            both = list(zip(codes.split(tokens), scales.split(tokens)))
+            for i, l in enumerate(members):
+                out[l] = (both[2 * i], both[2 * i + 1])
+        return out
+
+    def _alloc_workspace(self, tokens: int, device) -> torch.Tensor:
+        """For encoding and decoding `tokens` tokens at any layer; with groups across the heads also room for the predictions
+        of a short range, which is then encoded in one piece."""
+        d = self._H * self._g
+        need = {(l.n_codewords, l.rtn_bits, l.rht_group, l.c.d_in_k, l.c.d_in_v): l for l in self.layers if l is not None}
+        size = max(B.aquakv_workspace_bytes(l, tokens) + (min(tokens, 4096) * d * 4 if l.rht_group == d and self._H > 1 else 0) for l in need.values())
+        return torch.empty(max(size, 16), dtype=torch.uint8, device=device)
 
     # ------------------------------------------------------------------ counts
     def _count(self, per_seq: List[int]):
@@ -109,17 +134,20 @@ class AquaKVCache:
         (default: all t)."""
         if len(kv) != len(self.layers):
             raise ValueError("one (K, V) pair per layer")
-        if kv[0][0].dim() == 3:
-            if self.batch != 1:
-                raise ValueError("a batched cache takes [batch, t, kv_heads, head_dim]")
-            kv = [(K[None], V[None]) for K, V in kv]
-        t = kv[0][0].shape[1]
+        first = kv[0][0]
+        single = first.dim() == 3
+        if single and self.batch != 1:
+            raise ValueError("a batched cache takes [batch, t, kv_heads, head_dim]")
+        t = first.shape[0] if single else first.shape[1]
         n = [t] * self.batch if lengths is None else [int(x) for x in lengths]
-        if len(n) != self.batch or kv[0][0].shape[0] != self.batch or any(x < 0 or x > t for x in n):
+        if len(n) != self.batch or (not single and first.shape[0] != self.batch) or any(x < 0 or x > t for x in n):
             raise ValueError("one length per sequence, each at most the tokens given")
         if any(self._ns[b] + self._nc[b] + self._nb[b] + n[b] > self.max_tokens for b in range(self.batch)):
             raise ValueError("cache is full")
-        kv = [(self._rows(K, t), self._rows(V, t)) for K, V in kv]
+        # the sources: (address, bytes from sequence to sequence) per layer, keys then values; `kept` holds what was made here
+        kept = [self._rows(x, t) for pair in kv for x in pair]
+        es = self._like.element_size()
+        src = [(x.data_ptr(), x.stride(0) * es if x.dim() == 4 else 0) for x in kept]
         # Per sequence: sinks first, then what tops up a buffer that already holds tokens, then whole buffers' worth of
         # tokens, which need no stop in the buffer, then the rest into the (by now empty) buffer.  The tokens land where
         # filling and flushing buffer after buffer would put them; what changes is that a prompt is quantized in one call
@@ -130,13 +158,13 @@ class AquaKVCache:
             pos, left = 0, n[b]
             take = min(self.sink_tokens - self._ns[b], left)
             if take > 0:
-                self._store(now, self.sink, self._ns[b], kv, b, pos, take)
+                self._store(now, self._sink_at, max(self.sink_tokens, 1), self._ns[b], src, b, pos, take)
                 self._ns[b] += take
                 pos, left = pos + take, left - take
             r, dst = self.buffer_tokens, now
             if self._nb[b] and left:
                 take = min(r - self._nb[b], left)
-                self._store(now, self.buf, self._nb[b], kv, b, pos, take)
+                self._store(now, self._buf_at, r, self._nb[b], src, b, pos, take)
                 self._nb[b] += take
                 pos, left = pos + take, left - take
                 if self._nb[b] == r:
@@ -147,38 +175,41 @@ class AquaKVCache:
                 direct.append((b, pos, whole))
                 pos, left = pos + whole, left - whole
             if left:
-                self._store(dst, self.buf, 0, kv, b, pos, left)
+                self._store(dst, self._buf_at, r, 0, src, b, pos, left)
                 self._nb[b] = left if dst is now else r + left
         if now:
             B.aquakv_copy_ranges(now)
         if full:
             self._flush(full)
         if direct:
-            self._encode_direct(kv, direct)
+            self._encode_direct(src, direct)
         if later:
             B.aquakv_copy_ranges(later)
 
     def _rows(self, x: torch.Tensor, t: int) -> torch.Tensor:
-        """x as [batch, t, kv_heads, head_dim] in the storage dtype on the cache's device, every sequence's tokens one
-        contiguous block."""
-        H, g, like = self._H, self._g, self.sink[0][0]
-        if x.dtype != self._dt or x.device != like.device or tuple(x.shape) != (self.batch, t, H, g):
+        """x in the storage dtype on the cache's device, every sequence's tokens one contiguous block: as it is
+        ([t, kv_heads, head_dim], [batch, t, kv_heads, head_dim]) or a copy."""
+        H, g, like = self._H, self._g, self._like
+        one = x.dim() == 3
+        if x.dtype != like.dtype or x.device != like.device or x.shape != ((t, H, g) if one else (self.batch, t, H, g)):
             x = x.to(device=like.device, dtype=self._dt).expand(self.batch, t, H, g)
-        st, es = x.stride(), x.element_size()
-        if st[3] != 1 or st[2] != g or (t > 1 and st[1] != H * g) or (x.data_ptr() | st[0] * es) & 15:
-            x = x.clone(memory_format=torch.contiguous_format)
+            one = False
+        if not (x.is_contiguous() and x.data_ptr() & 15 == 0):
+            st = x.stride() if not one else (0, *x.stride())
+            if st[3] != 1 or st[2] != g or (t > 1 and st[1] != H * g) or (x.data_ptr() | st[0] * x.element_size()) & 15:
+                x = x.clone(memory_format=torch.contiguous_format)
         return x
 
-    def _store(self, out: List[int], dst, at: int, kv, b: int, pos: int, take: int) -> None:
-        """Adds the copies of tokens pos ... pos + take - 1 of sequence b, every layer, to row `at` of dst[l][0 / 1][b]."""
+    def _store(self, out: List[int], dst: List[int], rows: int, at: int, src, b: int, pos: int, take: int) -> None:
+        """Adds the copies of tokens pos ... pos + take - 1 of sequence b, every layer, to row `at` of the sequence's `rows`
+        rows of dst."""
         row = self._row_bytes
-        for pair, into in zip(kv, dst):
-            for x, d in zip(pair, into):
-                es = x.element_size()
-                out += (d.data_ptr() + b * d.stride(0) * es + at * row, x.data_ptr() + b * x.stride(0) * es + pos * row, take * row)
+        to, pos, size = (b * rows + at) * row, pos * row, take * row
+        for d, (x, seq) in zip(dst, src):
+            out += (d + to, x + b * seq + pos, size)
 
-    def _encode_direct(self, kv, pieces: List[Tuple[int, int, int]]) -> None:
-        """pieces: (sequence, first token in kv, tokens): whole buffers' worth of tokens that go from the caller's tensors
+    def _encode_direct(self, src, pieces: List[Tuple[int, int, int]]) -> None:
+        """pieces: (sequence, first token in src, tokens): whole buffers' worth of tokens that go from the caller's tensors
         to the compressed range, all sequences in one aquakv_encode_layer call per layer (at most kDirectTokens tokens at a
         time, which bounds the scratch)."""
         r, C, row = self.buffer_tokens, self._C, self._row_bytes
@@ -195,43 +226,42 @@ class AquaKVCache:
                 self._nc[b] += take
                 pos, left, room = pos + take, left - take, room - take
         biggest = max(sum(p[3] for p in c) for c in chunks)
-        like = self.sink[0][0]
-        scratch = lambda: torch.empty(biggest, self._H, self._g, dtype=self._dt, device=like.device)
-        hat = [(scratch(), scratch()) for _ in range(2)]               # layer l - 1 feeds layer l
-        stage = [(scratch(), scratch()) for _ in range(2)] if any(len(c) > 1 for c in chunks) else None
+        gather = any(len(c) > 1 for c in chunks)
+        scratch = torch.empty(8 if gather else 4, biggest * row, dtype=torch.uint8, device=self._like.device)
+        at = scratch.data_ptr()
+        hat = [(at + 2 * i * biggest * row, at + (2 * i + 1) * biggest * row) for i in range(2)]     # layer l - 1 feeds layer l
+        stage = [(k + 4 * biggest * row, v + 4 * biggest * row) for k, v in hat]
         for c in chunks:
             N = sum(p[3] for p in c)
             Kp = Vp = None
             for l, lay in enumerate(self.layers):
-                if len(c) == 1:
-                    b, pos, at, _ = c[0]
-                    Xk, Xv = (x[b, pos:pos + N] for x in kv[l])
-                else:
-                    Xk, Xv = (x[:N] for x in stage[l & 1])
+                Xs = [x + c[0][0] * seq + c[0][1] * row for x, seq in src[2 * l:2 * l + 2]]
+                if len(c) > 1:
                     jobs, to = [], 0
                     for b, pos, _, m in c:
-                        for X, x in ((Xk, kv[l][0]), (Xv, kv[l][1])):
-                            jobs += (X.data_ptr() + to * row, x.data_ptr() + b * x.stride(0) * x.element_size() + pos * row, m * row)
+                        for X, (x, seq) in zip(stage[l & 1], src[2 * l:2 * l + 2]):
+                            jobs += (X + to * row, x + b * seq + pos * row, m * row)
                         to += m
                     B.aquakv_copy_ranges(jobs)
+                    Xs = stage[l & 1]
                 if lay is None:                                        # kept in 16 bits
                     jobs, to = [], 0
-                    for _, _, at, m in c:
-                        for X, store in ((Xk, self.raw[l][0]), (Xv, self.raw[l][1])):
-                            jobs += (store.data_ptr() + at * row, X.data_ptr() + to * row, m * row)
+                    for _, _, first, m in c:
+                        for X, store in zip(Xs, self.raw[l]):
+                            jobs += (store.data_ptr() + first * row, X + to * row, m * row)
                         to += m
                     B.aquakv_copy_ranges(jobs)
-                    Kp, Vp = Xk, Xv
+                    Kp, Vp = Xs
                     continue
-                Kh, Vh = (x[:N] for x in hat[l & 1])
-                stores = [s for pair in self.codes[l] for s in pair]
+                Kh, Vh = hat[l & 1]
                 if len(c) == 1:
-                    out = [s[at:at + N] for s in stores]
+                    out = [p + c[0][2] * size for p, size in self._codes_at[l]]
                 else:
+                    stores = [s for pair in self.codes[l] for s in pair]
                     out = [torch.empty(N, *s.shape[1:], dtype=s.dtype, device=s.device) for s in stores]
-                B.aquakv_encode_layer(lay, N, Xk, Xv, Kp, Vp, *out, Kh, Vh, self._view_ws)
+                B.aquakv_encode_layer(lay, N, *Xs, Kp, Vp, *out, Kh, Vh, self._view_ws)
                 if len(c) > 1:
-                    self._scatter(stores, out, [(at, m) for _, _, at, m in c])
+                    self._scatter(stores, out, [(first, m) for _, _, first, m in c])
                 Kp, Vp = Kh, Vh
 
     @staticmethod
@@ -259,7 +289,7 @@ class AquaKVCache:
         Kp = Vp = None
         for l, lay in enumerate(self.layers):
             if whole:
-                Xk, Xv = (x.view(n * r, self._H, self._g) for x in self.buf[l])
+                Xk, Xv = self.buf[l]
             else:
                 Xk, Xv = (x[:n * r] for x in self._flush_in[l & 1])
                 jobs: List[int] = []
@@ -268,15 +298,15 @@ class AquaKVCache:
                         jobs += (X.data_ptr() + i * r * row, x.data_ptr() + b * r * row, r * row)
                 B.aquakv_copy_ranges(jobs)
             if lay is None:                                  # kept in 16 bits: stored as is, feeds the next layer exactly
-                self._scatter(self.raw[l], (Xk, Xv), parts)
+                self._scatter(self.raw[l], (Xk.view(-1, self._H, self._g), Xv.view(-1, self._H, self._g)), parts)
                 Kp, Vp = Xk, Xv
                 continue
-            stores = [s for pair in self.codes[l] for s in pair]
-            Kh, Vh = (t[:n * r] for t in self._flush_hat[l & 1])
+            Kh, Vh = (t.data_ptr() for t in self._flush_hat[l & 1])
             if single:
                 at = self._nc[0]
-                out = [s[at:at + r] for s in stores]
+                out = [p + at * size for p, size in self._codes_at[l]]
             else:
+                stores = [s for pair in self.codes[l] for s in pair]
                 out = [s[:n * r] for pair in self._flush_codes[l] for s in pair]
             B.aquakv_encode_layer(lay, n * r, Xk, Xv, Kp, Vp, *out, Kh, Vh, self._flush_ws)
             if not single:

@@ -139,6 +139,17 @@ int check_no_alias(const Range* outs, int n_out, const Range* ins, int n_in, con
   return AQUAKV_OK;
 }
 
+// How much of the workspace a call may use beyond what it needs: all of it, unless the part behind the first `need` bytes lies
+// over the call's other buffers (it was never promised to be scratch by callers that pass one large arena).
+size_t usable_workspace(void* workspace, size_t need, size_t bytes, const Range* outs, int n_out, const Range* ins, int n_in) {
+  const Range all = {workspace, bytes, ""};
+  for (int i = 0; i < n_out; ++i)
+    if (outs[i].p != workspace && overlap(all, outs[i])) return need;
+  for (int j = 0; j < n_in; ++j)
+    if (overlap(all, ins[j])) return need;
+  return bytes;
+}
+
 #define CHECK(expr)                      \
   do {                                   \
     const int s_ = (expr);               \
@@ -442,6 +453,7 @@ int aquakv_encode_layer(const aquakv_layer* L, int64_t tokens, const void* K, co
     return fail(AQUAKV_EWORKSPACE, "workspace %zu B < required %zu B", workspace_bytes, pl.p_bytes + pl.khat_bytes);
 
   const size_t row = (size_t)pl.D * pl.eb;
+  size_t usable;
   {
     const size_t t = (size_t)tokens, crow = pl.code_row, srow = scale_row_bytes(L);
     const Range outs[] = {{Khat, t * row, "Khat"}, {Vhat, t * row, "Vhat"}, {k_codes, t * crow, "k_codes"},
@@ -451,11 +463,14 @@ int aquakv_encode_layer(const aquakv_layer* L, int64_t tokens, const void* K, co
                          {Vhat_prev, has_v ? t * (L->d_in_v - pl.D) * pl.eb : 0, "Vhat_prev"}};
     const void* const inplace[] = {K, V, nullptr, nullptr, nullptr, nullptr, nullptr};
     CHECK(check_no_alias(outs, 7, ins, 4, inplace));
+    usable = usable_workspace(workspace, pl.p_bytes + pl.khat_bytes, workspace_bytes, outs, 7, ins, 4);
   }
 
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   float* Pbuf = static_cast<float*>(workspace);
-  void* khat_tmp = static_cast<unsigned char*>(workspace) + pl.p_bytes;
+  // predictions at the front, the temporary Khat (if one is needed) at the back
+  const size_t room = Khat != nullptr || !has_v ? usable : (usable - pl.khat_bytes) & ~(size_t)15;
+  void* khat_tmp = static_cast<unsigned char*>(workspace) + room;
 
   for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk) {
     const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;
@@ -471,8 +486,6 @@ int aquakv_encode_layer(const aquakv_layer* L, int64_t tokens, const void* K, co
                                       is_wide(L), stream));
       continue;
     }
-    // (the temporary Khat behind the predictions is free when the caller asks for Khat)
-    const size_t room = pl.p_bytes + (Khat != nullptr || !has_v ? pl.khat_bytes : 0);
     CHECK(encode_keys_chunk(L, pl, r0, n, K, Khat_prev, k_codes, k_scales, khat_dst, Pbuf, room, stream));
     CHECK(encode_values_chunk(L, pl, r0, n, V, Vhat_prev, khat_dst, v_codes, v_scales, Vhat, Pbuf, room, stream));
   }
@@ -547,6 +560,7 @@ int aquakv_encode_keys(const aquakv_layer* L, int64_t tokens, const void* K, con
     if (workspace_bytes < pl.p_bytes) return fail(AQUAKV_EWORKSPACE, "workspace %zu B < required %zu B", workspace_bytes, pl.p_bytes);
   }
   const size_t row = (size_t)pl.D * pl.eb;
+  size_t room;
   {
     const size_t t = (size_t)tokens;
     const Range outs[] = {{Khat, t * row, "Khat"}, {k_codes, t * pl.code_row, "k_codes"},
@@ -554,11 +568,12 @@ int aquakv_encode_keys(const aquakv_layer* L, int64_t tokens, const void* K, con
     const Range ins[] = {{K, t * row, "K"}, {Khat_prev, t * L->d_in_k * pl.eb, "Khat_prev"}};
     const void* const inplace[] = {K, nullptr, nullptr, nullptr};
     CHECK(check_no_alias(outs, 4, ins, 2, inplace));
+    room = pl.p_bytes == 0 ? 0 : usable_workspace(workspace, pl.p_bytes, workspace_bytes, outs, 4, ins, 2);
   }
   for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk) {
     const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;
     CHECK(encode_keys_chunk(L, pl, r0, n, K, Khat_prev, k_codes, k_scales, at(Khat, r0, row), static_cast<float*>(workspace),
-                            pl.p_bytes, static_cast<hipStream_t>(stream_)));
+                            room, static_cast<hipStream_t>(stream_)));
   }
   return AQUAKV_OK;
 }
@@ -582,6 +597,7 @@ int aquakv_encode_values(const aquakv_layer* L, int64_t tokens, const void* V, c
     if (workspace_bytes < pl.p_bytes) return fail(AQUAKV_EWORKSPACE, "workspace %zu B < required %zu B", workspace_bytes, pl.p_bytes);
   }
   const size_t row = (size_t)pl.D * pl.eb;
+  size_t room;
   {
     const size_t t = (size_t)tokens;
     const Range outs[] = {{Vhat, t * row, "Vhat"}, {v_codes, t * pl.code_row, "v_codes"},
@@ -590,11 +606,12 @@ int aquakv_encode_values(const aquakv_layer* L, int64_t tokens, const void* V, c
                          {Khat, has_v ? t * row : 0, "Khat"}};
     const void* const inplace[] = {V, nullptr, nullptr, nullptr};
     CHECK(check_no_alias(outs, 4, ins, 3, inplace));
+    room = pl.p_bytes == 0 ? 0 : usable_workspace(workspace, pl.p_bytes, workspace_bytes, outs, 4, ins, 3);
   }
   for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk) {
     const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;
     CHECK(encode_values_chunk(L, pl, r0, n, V, Vhat_prev, at(Khat, r0, row), v_codes, v_scales, Vhat,
-                              static_cast<float*>(workspace), pl.p_bytes, static_cast<hipStream_t>(stream_)));
+                              static_cast<float*>(workspace), room, static_cast<hipStream_t>(stream_)));
   }
   return AQUAKV_OK;
 }
