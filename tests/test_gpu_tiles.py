@@ -1,4 +1,4 @@
-"""Tiles of 32, 64, 128 and 320 token rows (short ranges, and ranges that leave a round of the large tiles nearly empty):
+"""Tiles of 32, 64, 128, 192 and 320 token rows (short ranges, and ranges that leave a round of the large tiles nearly empty):
 encode, decode and the scoring call against the stage calls (aquakv_predict, aquakv_quantize, aquakv_dequantize), bit for
 bit, at the edges of every tile, with and without bias, for predictors as narrow as two k-tiles, all quantizers and both groupings."""
 import pytest
@@ -22,7 +22,7 @@ def layer(H, dk, quantizer, rht_group=None, bias=True):
                          w_v=U.random_weights(D, dk + D, 22, 0.7), b_k=bk, b_v=bv, **kw)[1]
 
 
-CASES = [(8, 1024, T) for T in (1, 31, 33, 1024, 1025, 1089, 2048, 2049, 2177, 4096, 8449)] + [
+CASES = [(8, 1024, T) for T in (1, 31, 33, 1024, 1025, 1089, 2048, 2049, 2177, 4096, 4097, 4289, 6144, 6145, 8449)] + [
     (3, 128, 2700), (3, 128, 33), (16, 256, 700), (1, 384, 8200), (8, 192 * 2, 129)]
 
 
@@ -59,8 +59,38 @@ def test_tiles_give_the_bits_of_the_stage_calls(H, dk, T, quantizer, rht_group):
             assert torch.equal(bits(a), bits(b)), (which, name)
 
 
+@pytest.mark.parametrize("T", [1, 1024, 1025, 4095, 4096, 4097])
+@pytest.mark.parametrize("quantizer", ["n16", "n256", "rtn2"])
+def test_groups_across_heads_whatever_the_workspace_holds(T, quantizer):
+    """Encode with the predictions in pieces (the required workspace), in one piece (a larger one), and with the temporary keys in
+    the workspace too: the same codes, equal to those of the stage calls; nothing behind the workspace is touched."""
+    from paper_2501_19392_amd import binding as B
+    print(f"case wide workspace T={T} {quantizer}", flush=True)
+    lg, D = layer(8, 1024, quantizer, 1024, bias=T % 2 == 1), 1024
+    g = torch.Generator(device="cuda").manual_seed(T)
+    K, V, Kp, Vp = (torch.randn(T, D, generator=g, device="cuda").bfloat16() for _ in range(4))
+    P = torch.empty(T, D, dtype=torch.float32, device="cuda")
+    (kc, ks), (vc, vs) = lg.alloc_codes(T), lg.alloc_codes(T)
+    Kh, Vh = lg.alloc_kv(T), lg.alloc_kv(T)
+    for which, x0, x1, X, c, s, hat in ((B.AQUAKV_KEY, Kp, None, K, kc, ks, Kh), (B.AQUAKV_VALUE, Vp, Kh, V, vc, vs, Vh)):
+        B.aquakv_predict(lg, which, T, x0, x1, P)
+        B.aquakv_quantize(lg, which, T, X, P, c, s, hat)
+    want = [bits(t) for t in (kc, ks, vc, vs, Vh, Kh)]
+    need = lg.alloc_workspace(T).numel()
+    for extra in (0, 1040, 3 * T * D, 5 * T * D + (8 << 20)):
+        for with_keys in (True, False):
+            arena = torch.full((need + extra + 4096,), 0xCD, dtype=torch.uint8, device="cuda")
+            (kc, ks), (vc, vs) = lg.alloc_codes(T), lg.alloc_codes(T)
+            Kh, Vh = lg.alloc_kv(T), lg.alloc_kv(T)
+            B.aquakv_encode_layer(lg, T, K, V, Kp, Vp, kc, ks, vc, vs, Kh if with_keys else None, Vh, arena[:need + extra])
+            torch.cuda.synchronize()
+            for name, a, b in zip(("k_codes", "k_scales", "v_codes", "v_scales", "Vhat", "Khat"), (kc, ks, vc, vs, Vh, Kh), want):
+                assert (name == "Khat" and not with_keys) or torch.equal(bits(a), b), (extra, with_keys, name)
+            assert bool((arena[need + extra:] == 0xCD).all())
+
+
 @pytest.mark.parametrize("H,dk,batch,S", [(8, 1024, 1, 1), (8, 1024, 3, 33), (8, 1024, 5, 100), (8, 1024, 2, 1000),
-                                          (8, 1024, 3, 1100), (8, 1024, 1, 8449), (3, 128, 2, 65)])
+                                          (8, 1024, 3, 1100), (8, 1024, 5, 1100), (8, 1024, 1, 8449), (3, 128, 2, 65)])
 @pytest.mark.parametrize("quantizer,rht_group", [("n16", None), ("rtn2", None), ("n256", 1024)])
 def test_scores_of_a_batch_are_those_of_its_sequences(H, dk, batch, S, quantizer, rht_group):
     from paper_2501_19392_amd import binding as B
