@@ -6,7 +6,6 @@
 #include <string.h>
 
 #include <mutex>
-#include <vector>
 
 #include "../../include/aquakv.h"
 #include "kernels.h"
@@ -1084,26 +1083,35 @@ int aquakv_attend_cache(const aquakv_cache_layer* layers, int32_t n_layers, cons
   const int64_t first_row = first * sh->capacity;
 
   // the ranges of the sequences one behind the other
-  std::vector<aquakv::CopyRange> copies;
+  aquakv::CopyRange copies[aquakv::kCopyRangesPerLaunch];        // one launch's worth at a time: nothing is allocated here
+  int n_copies = 0;
+  const auto send = [&]() {
+    const int n = n_copies;
+    n_copies = 0;
+    return n == 0 ? hipSuccess : aquakv::launch_copy_ranges(copies, n, stream);
+  };
   const auto gather = [&](void* dst, const void* src, size_t row_bytes) {
     int64_t to = 0;
     for (int b = first; b <= last; ++b) {
       if (n_compressed[b] == 0) continue;
-      copies.push_back({at(dst, to, row_bytes), at(src, b * sh->capacity, row_bytes), n_compressed[b] * row_bytes});
+      if (n_copies == aquakv::kCopyRangesPerLaunch)
+        if (const hipError_t e = send()) return e;
+      copies[n_copies++] = {at(dst, to, row_bytes), at(src, b * sh->capacity, row_bytes), n_compressed[b] * row_bytes};
       to += n_compressed[b];
     }
+    return hipSuccess;
   };
   if (compressed != 0 && !adjacent) {
     for (int32_t l = 0; l < n_layers; ++l) {
       const aquakv_cache_layer& c = layers[l];
       if (c.layer == nullptr) continue;
       const size_t crow = make_plan(c.layer, 1).code_row, srow = scale_row_bytes(c.layer);
-      gather(c.staged_k_codes, c.k_codes, crow);
-      gather(c.staged_k_scales, c.k_scales, srow);
-      gather(c.staged_v_codes, c.v_codes, crow);
-      gather(c.staged_v_scales, c.v_scales, srow);
+      HIP_TRY(gather(c.staged_k_codes, c.k_codes, crow));
+      HIP_TRY(gather(c.staged_k_scales, c.k_scales, srow));
+      HIP_TRY(gather(c.staged_v_codes, c.v_codes, crow));
+      HIP_TRY(gather(c.staged_v_scales, c.v_scales, srow));
     }
-    HIP_TRY(aquakv::launch_copy_ranges(copies.data(), (int)copies.size(), stream));
+    HIP_TRY(send());
   }
   float* const part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + decode_bytes);
   const int64_t part_elems = pieces * sh->q_heads * 128, layer_elems = (int64_t)(one / sizeof(float));
@@ -1127,10 +1135,9 @@ int aquakv_attend_cache(const aquakv_cache_layer* layers, int32_t n_layers, cons
     } else if (compressed != 0 && adjacent) {
       Kp = at(c.raw_k, first_row, row); Vp = at(c.raw_v, first_row, row);
     } else if (compressed != 0) {
-      copies.clear();
-      gather(K, c.raw_k, row);
-      gather(V, c.raw_v, row);
-      HIP_TRY(aquakv::launch_copy_ranges(copies.data(), (int)copies.size(), stream));
+      HIP_TRY(gather(K, c.raw_k, row));
+      HIP_TRY(gather(V, c.raw_v, row));
+      HIP_TRY(send());
       Kp = K; Vp = V;
     }
     aquakv::AttendCacheArgs a = {};
