@@ -67,6 +67,7 @@ template <> struct Row<bf16_t> {
   }
   __device__ __forceinline__ void key(float (&f)[8]) const { unpack4(lo, f, 0); unpack4(hi, f, 4); }
   __device__ __forceinline__ void value(float (&f)[8]) const { unpack_bf16x8(v, f); }
+  __device__ __forceinline__ void no_value() { v = u32x4{0, 0, 0, 0}; }
 };
 template <> struct Row<float> {
   f32x4 lo, hi, v0, v1;
@@ -81,6 +82,7 @@ template <> struct Row<float> {
   }
   __device__ __forceinline__ void key(float (&f)[8]) const { put4(lo, f, 0); put4(hi, f, 4); }
   __device__ __forceinline__ void value(float (&f)[8]) const { put4(v0, f, 0); put4(v1, f, 4); }
+  __device__ __forceinline__ void no_value() { v0 = v1 = f32x4{0.f, 0.f, 0.f, 0.f}; }
 };
 
 // blockIdx.x = piece * kv heads + head.  All rows of the piece are requested at once; thread (ts = tid / 16, l = tid % 16) owns
@@ -128,6 +130,11 @@ __global__ __launch_bounds__(kThreads, 2) void attend_cache_kernel(const AttendC
       cs[p] = *reinterpret_cast<const f32x4*>(a.rope_cos + (int64_t)t * 64 + 4 * l);
       sn[p] = *reinterpret_cast<const f32x4*>(a.rope_sin + (int64_t)t * 64 + 4 * l);
     }
+  }
+  if (t0 + kAttendPiece > n) {                         // beyond the end: the last token's values again, and 0 x infinity is no 0
+#pragma unroll
+    for (int p = 0; p < kPasses; ++p)
+      if (t0 + p * 16 + ts >= n) rows[p].no_value();
   }
   float k[kPasses][8], v[kPasses][8];
   for (int r0 = 0; r0 < rep; r0 += kMaxRep) {
@@ -194,10 +201,11 @@ __global__ __launch_bounds__(kThreads, 2) void attend_cache_kernel(const AttendC
     for (int e = threadIdx.x; e < nr * kGroup; e += kThreads) {
       const int r = e / kGroup, d = e % kGroup;
       const float M = fmaxf(fmaxf(wave_stats[0][r][0], wave_stats[1][r][0]), fmaxf(wave_stats[2][r][0], wave_stats[3][r][0]));
+      const float shift = M == -INFINITY ? 0.f : M;    // every score of the piece is -inf: it weighs nothing in the merge
       float sum = 0.f, den = 0.f;
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
-        const float f = expf(wave_stats[w][r][0] - M);
+        const float f = expf(wave_stats[w][r][0] - shift);
         sum = __fmaf_rn(f, sums[w][r][d], sum);
         den = __fmaf_rn(f, wave_stats[w][r][1], den);
       }

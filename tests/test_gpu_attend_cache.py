@@ -67,6 +67,31 @@ def test_attend_over_ragged_caches(dtype, H, QH, sinks, recent, lengths, raw_lay
             assert err < 1e-5, (b, l, float(err))
 
 
+@pytest.mark.parametrize("n", [65, 130])
+@pytest.mark.parametrize("what", ["values of the last token", "scores of a piece"])
+def test_infinities_stay_where_they_are(n, what):
+    """Tokens behind the end of a sequence and pieces whose scores are all -inf add nothing, not 0 x infinity."""
+    from paper_2501_19392_amd.cache import AquaKVCache
+    print(f"case attend infinities n={n} {what}", flush=True)
+    lay = U.make_layers(1, "bf16", 16)[1]
+    cache = AquaKVCache([lay], max_tokens=n, sink_tokens=0, buffer_tokens=256)          # everything in the buffer
+    gen = torch.Generator().manual_seed(n)
+    K, V = (torch.randn(n, 1, 128, generator=gen).bfloat16().cuda() for _ in range(2))
+    q = torch.randn(1, 128, generator=gen).bfloat16().cuda().abs()
+    if what == "scores of a piece":
+        K[64 * ((n - 1) // 64):, :, 3] = float("-inf")
+    else:
+        V[-1, 0, 5] = float("inf")
+    cache.append([(K, V)])
+    got = cache.attend([q], 128 ** -0.5)[0].double()
+    want = plain_attention(q, K, V, 128 ** -0.5, None) if what == "scores of a piece" else \
+        plain_attention(q, K, V.nan_to_num(posinf=0.0), 128 ** -0.5, None)
+    if what != "scores of a piece":
+        want[0, 5] = float("inf")
+    ok = torch.isclose(got, want, rtol=0, atol=1e-5 * V.double().nan_to_num(posinf=0.0).square().mean().sqrt().item())
+    assert ok.all(), (got[~ok], want[~ok])
+
+
 def test_attend_refuses_what_does_not_fit():
     from paper_2501_19392_amd import binding as B
     from paper_2501_19392_amd.cache import AquaKVCache

@@ -1,4 +1,4 @@
-"""Tiles of 32, 64, 128, 192 and 320 token rows (short ranges, and ranges that leave a round of the large tiles nearly empty):
+"""Tiles of 32, 64, 128 and 320 token rows (short ranges, and ranges that leave a round of the large tiles nearly empty):
 encode, decode and the scoring call against the stage calls (aquakv_predict, aquakv_quantize, aquakv_dequantize), bit for
 bit, at the edges of every tile, with and without bias, for predictors as narrow as two k-tiles, all quantizers and both groupings."""
 import pytest
