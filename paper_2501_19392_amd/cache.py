@@ -11,18 +11,15 @@ which has no predictor, with the 4-bit grid), and a layer given as None is kept 
 stored as they are and feed the next layer's predictors).
 
 `attend` is the block call of Alg. "Inference" for one new token per sequence as far as the cache is concerned: per
-layer the soft-max attention of that token's queries over everything cached.  The compressed range is scored and
-summed by the decode kernels themselves (`aquakv_decode_attn_scores` with the keys as output,
-`aquakv_decode_values_attend`), the sinks and the buffer by `aquakv_attend_raw`, which merges its share into the
-running result.
+layer the soft-max attention of that token's queries over everything cached, in one native call for all layers and
+sequences (`aquakv_attend_cache`).
 
 Batch.  Every sequence has its own sinks, buffer and compressed range (lengths may differ).  All sequences whose
 buffer fills during one `append` are quantized together: ONE `aquakv_encode_layer` per layer over
-(number of full buffers) x r tokens.  `attend` treats the sequences that hold the same number of compressed tokens as
-one batch of the decode calls (`batch` x `seq_len` is what those calls take); in lock-step decoding from prompts of
-one length that is the whole batch.  Codes of a sequence are contiguous in its own range of the code tensors, so a
-group of several sequences is first gathered into one token-major staging range (codes are an eighth of the bytes the
-decode call moves).
+(number of full buffers) x r tokens; whole buffers' worth of a prompt go from the caller's tensors to the compressed
+range directly.  Codes of a sequence are contiguous in its own range of the code tensors; `attend` recovers a layer of
+all sequences at once, from codes that are first put one behind the other in a staging range unless they already are
+(codes are an eighth of the bytes the recovery moves).
 
 This class is bookkeeping only: every number is produced by the C-ABI calls (`aquakv_encode_layer`,
 `aquakv_decode_layer`, the attention calls above); torch tensors are the device memory they work on.

@@ -89,9 +89,9 @@ template <> struct Row<float> {
 // tokens ts, ts + 16, ... of it.  Every wave takes the soft-max of its own tokens, so the waves meet once, to merge.
 // part[piece, q_heads, 128]: sums with weights exp(score - maximum); stats[piece, q_heads, 2]: maximum and sum of the weights.
 // Bound by the instructions per query head, hence the sharing of exponentials in a quad and the lane swaps: 5640 tokens in four
-// sequences, 8 kv heads, 32 query heads, rotary embedding: 9.8 us; 11.5 us with an exponential per lane and the values unpacked
-// per query head, 18 us also with shuffles through LDS and pieces of 128 (two workgroups per CU).  128 tokens: 6 us, which is
-// launch and memory latency.
+// sequences, 8 kv heads, 32 query heads, rotary embedding: 9.8 us (12 us inside the sweep, in a trace); 11.5 us with an
+// exponential per lane and the values unpacked per query head, 18 us also with shuffles through LDS and pieces of 128 (two
+// workgroups per CU).  128 tokens: 6 us, which is launch and memory latency.
 template <typename T>
 __global__ __launch_bounds__(kThreads, 2) void attend_cache_kernel(const AttendCacheArgs a) {
   __shared__ float q_lds[kMaxRep][kGroup];
