@@ -423,6 +423,7 @@ int aquakv_copy_ranges(const aquakv_copy_range* ranges, int32_t n, void* stream)
  * rope_cos / rope_sin (both NULL, or device fp32 [tokens, 64]): the keys are held from before the rotary embedding, as in
  * aquakv_decode_attn_scores_rope.  `hat`: HOST array of four device buffers, K and V of even layers, K and V of odd layers, each
  * with room for the compressed tokens of all sequences: layer l is recovered into pair l % 2 and read for layer l + 1.
+ * Hence a layer's predictors, if it has any, take the vectors of one layer: d_in_k = kv_heads * 128, d_in_v = twice that.
  * `staged` (needed when batch > 1): room for the compressed tokens of all sequences in the layout of the layer's code and scale
  * tensors, where they are put one behind the other.  `workspace`: aquakv_attend_cache_workspace_bytes() bytes, 0 for an
  * unsupported configuration.  Nothing is kept from call to call.

@@ -992,6 +992,11 @@ int check_cache(const aquakv_cache_layer* layers, int32_t n_layers, const aquakv
     CHECK(check_layer(L));
     if (L->kv_heads != sh->kv_heads || L->dtype != sh->dtype)
       return fail(AQUAKV_EINVAL, "layer %d: kv_heads=%d dtype=%d differ from the cache's", l, L->kv_heads, L->dtype);
+    // the inputs of a predictor are rows of the previous layer in `hat` (or raw_k / raw_v): kv_heads * 128 values each
+    const int32_t D = L->kv_heads * L->head_dim;
+    if ((L->d_in_k != 0 && L->d_in_k != D) || (L->d_in_v != 0 && L->d_in_v != 2 * D))
+      return fail(AQUAKV_EINVAL, "layer %d: predictors of %d and %d inputs, a cache of %d heads needs %d and %d", l, L->d_in_k,
+                  L->d_in_v, L->kv_heads, D, 2 * D);
   }
   return AQUAKV_OK;
 }
