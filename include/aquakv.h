@@ -427,6 +427,8 @@ int aquakv_copy_ranges(const aquakv_copy_range* ranges, int32_t n, void* stream)
  * `staged` (needed when batch > 1): room for the compressed tokens of all sequences in the layout of the layer's code and scale
  * tensors, where they are put one behind the other.  `workspace`: aquakv_attend_cache_workspace_bytes() bytes, 0 for an
  * unsupported configuration.  Nothing is kept from call to call.
+ * Nothing that the call writes (out, hat, staged, the workspace) may overlap anything else it is given: AQUAKV_EINVAL, like every
+ * other fault in the arguments before anything is launched.
  */
 typedef struct aquakv_cache_layer {
   const aquakv_layer* layer;              /* NULL: the layer's compressed range is held in the storage dtype */

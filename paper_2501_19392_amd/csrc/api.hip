@@ -5,7 +5,10 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
+#include <memory>
 #include <mutex>
+#include <new>
 
 #include "../../include/aquakv.h"
 #include "kernels.h"
@@ -134,6 +137,23 @@ int check_no_alias(const Range* outs, int n_out, const Range* ins, int n_in, con
     }
     for (int j = i + 1; j < n_out; ++j)
       if (overlap(outs[i], outs[j])) return fail(AQUAKV_EINVAL, "%s overlaps %s", outs[i].name, outs[j].name);
+  }
+  return AQUAKV_OK;
+}
+
+// The same over the many buffers of a call on a whole cache: no buffer that is written may overlap any other one.  In order of
+// address, a range overlaps an earlier one iff it starts before the furthest end so far, of any range if it is written itself,
+// else of the written ones.
+struct CacheRange { uintptr_t begin, end; const char* name; int32_t layer; bool written; };
+int check_disjoint(CacheRange* r, int64_t n) {
+  std::sort(r, r + n, [](const CacheRange& a, const CacheRange& b) { return a.begin < b.begin; });
+  const CacheRange *any = nullptr, *written = nullptr;      // the ones that reach furthest
+  for (int64_t i = 0; i < n; ++i) {
+    const CacheRange* before = r[i].written ? any : written;
+    if (before != nullptr && r[i].begin < before->end)
+      return fail(AQUAKV_EINVAL, "%s of layer %d overlaps %s of layer %d", r[i].name, r[i].layer, before->name, before->layer);
+    if (any == nullptr || r[i].end > any->end) any = r + i;
+    if (r[i].written && (written == nullptr || r[i].end > written->end)) written = r + i;
   }
   return AQUAKV_OK;
 }
@@ -1009,6 +1029,69 @@ size_t attend_decode_bytes(const aquakv_cache_layer* layers, int32_t n_layers, i
   }
   return (most + 255) & ~(size_t)255;
 }
+// What an aquakv_attend_cache call reads and writes: nothing that it writes may lie over anything else.  Sorted once: comparing
+// every pair would cost more than the launches of many layers.
+int check_cache_buffers(const aquakv_cache_layer* layers, int32_t n_layers, const aquakv_cache_shape* sh, const int32_t* n_sink,
+                        const int32_t* n_compressed, const int32_t* n_recent, const float* rope_cos, const float* rope_sin,
+                        void* const* hat, const void* workspace, size_t workspace_used, int64_t compressed, bool adjacent) {
+  const size_t row = (size_t)sh->kv_heads * 128 * elem_bytes(sh->dtype);
+  const int64_t most = (int64_t)n_layers * 14 + 7;
+  const std::unique_ptr<CacheRange[]> ranges(new (std::nothrow) CacheRange[most]);
+  if (ranges == nullptr) return fail(AQUAKV_EINVAL, "no host memory to check %d layers", n_layers);
+  int64_t n = 0, tokens = 0;
+  const auto add = [&](const void* p, size_t first, size_t bytes, const char* name, int32_t layer, bool written) {
+    const uintptr_t begin = reinterpret_cast<uintptr_t>(p) + first;
+    if (p != nullptr && bytes != 0) ranges[n++] = {begin, begin + bytes, name, layer, written};
+  };
+  // rows from the first token there is to the last one, of `each` rows per sequence
+  struct Span { size_t first = 0, rows = 0; };
+  const auto span = [&](const int32_t* count, int64_t each) {
+    Span s;
+    for (int b = 0; b < sh->batch; ++b) {
+      if (count[b] == 0) continue;
+      if (s.rows == 0) s.first = (size_t)(b * each);
+      s.rows = (size_t)(b * each + count[b]) - s.first;
+    }
+    return s;
+  };
+  const Span sink = span(n_sink, sh->sink_rows), held = span(n_compressed, sh->capacity), recent = span(n_recent, sh->recent_rows);
+  for (int b = 0; b < sh->batch; ++b)
+    tokens = std::max(tokens, (int64_t)n_sink[b] + n_compressed[b] + n_recent[b]);
+  const size_t heads = (size_t)sh->batch * sh->q_heads * 128;
+  bool hat_used[2] = {false, false};
+  for (int32_t l = 0; l < n_layers; ++l) {
+    const aquakv_cache_layer& c = layers[l];
+    add(c.sink_k, sink.first * row, sink.rows * row, "sink_k", l, false);
+    add(c.sink_v, sink.first * row, sink.rows * row, "sink_v", l, false);
+    add(c.recent_k, recent.first * row, recent.rows * row, "recent_k", l, false);
+    add(c.recent_v, recent.first * row, recent.rows * row, "recent_v", l, false);
+    add(c.q, 0, heads * elem_bytes(sh->dtype), "q", l, false);
+    add(c.out, 0, heads * sizeof(float), "out", l, true);
+    if (compressed == 0) continue;
+    hat_used[l & 1] |= c.layer != nullptr || !adjacent;
+    if (c.layer == nullptr) {
+      add(c.raw_k, held.first * row, held.rows * row, "raw_k", l, false);
+      add(c.raw_v, held.first * row, held.rows * row, "raw_v", l, false);
+      continue;
+    }
+    const size_t crow = make_plan(c.layer, 1).code_row, srow = scale_row_bytes(c.layer);
+    add(c.k_codes, held.first * crow, held.rows * crow, "k_codes", l, false);
+    add(c.k_scales, held.first * srow, held.rows * srow, "k_scales", l, false);
+    add(c.v_codes, held.first * crow, held.rows * crow, "v_codes", l, false);
+    add(c.v_scales, held.first * srow, held.rows * srow, "v_scales", l, false);
+    if (adjacent) continue;
+    add(c.staged_k_codes, 0, compressed * crow, "staged_k_codes", l, true);
+    add(c.staged_k_scales, 0, compressed * srow, "staged_k_scales", l, true);
+    add(c.staged_v_codes, 0, compressed * crow, "staged_v_codes", l, true);
+    add(c.staged_v_scales, 0, compressed * srow, "staged_v_scales", l, true);
+  }
+  for (int i = 0; i < 4; ++i)
+    if (hat_used[i >> 1]) add(hat[i], 0, compressed * row, "hat", i >> 1, true);
+  add(workspace, 0, workspace_used, "workspace", 0, true);
+  add(rope_cos, 0, tokens * 64 * sizeof(float), "rope_cos", 0, false);
+  add(rope_sin, 0, tokens * 64 * sizeof(float), "rope_sin", 0, false);
+  return check_disjoint(ranges.get(), n);
+}
 }  // namespace
 
 extern "C" {
@@ -1084,6 +1167,10 @@ int aquakv_attend_cache(const aquakv_cache_layer* layers, int32_t n_layers, cons
       }
     }
   }
+  if (compressed != 0 && layers[0].layer != nullptr && (layers[0].layer->d_in_k != 0 || layers[0].layer->d_in_v != 0))
+    return fail(AQUAKV_ENULL, "layer 0 has predictors, but no layer comes before it");
+  CHECK(check_cache_buffers(layers, n_layers, sh, n_sink, n_compressed, n_recent, rope_cos, rope_sin, hat, workspace,
+                            decode_bytes + one * (size_t)(hold < n_layers ? hold : n_layers), compressed, adjacent));
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   const int64_t first_row = first * sh->capacity;
 

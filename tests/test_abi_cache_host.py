@@ -56,3 +56,71 @@ def test_predictors_of_another_width_than_the_cache_are_refused(kw):
     assert c.need == 0
     assert c.status(workspace_bytes=64 * MiB) == B.AQUAKV_EINVAL
     assert Call([layer(first=True), layer()]).need > 0 and Call([layer(first=True), layer(d_in_k=0)]).need > 0
+
+
+def test_a_first_layer_with_predictors_is_refused_before_any_launch():
+    c = Call([layer(), layer()])
+    assert c.status() == B.AQUAKV_ENULL and "layer 0" in B.aquakv_last_error()
+
+
+WRITTEN = ["out", "staged_k_codes", "staged_k_scales", "staged_v_codes", "staged_v_scales"]
+READ = ["q", "sink_k", "sink_v", "recent_k", "recent_v", "k_codes", "k_scales", "v_codes", "v_scales", "raw_k", "raw_v"]
+
+
+def stack():
+    return Call([layer(first=True), None, layer()])
+
+
+@pytest.mark.parametrize("written", WRITTEN + ["hat0", "hat1", "hat2", "hat3", "workspace"])
+@pytest.mark.parametrize("other", WRITTEN + READ + ["hat0", "hat3", "workspace", "rope0", "rope1"])
+def test_what_is_written_overlaps_nothing(written, other):
+    """The last byte of `other` at the first byte of `written`, layer 2 on the written side, layer 0 (or 1) on the other."""
+    c = stack()
+    at = 1 << 45
+    used = dict(q=2 * QH * 256, out=2 * QH * 512, hat=256 * 2 * D, workspace=4096)
+    used |= {n: ((CAP + 128 if "raw" in n else (SINKS * 2 if "sink" in n else RECENT + 7)) * 2 * D) for n in READ if n[:3] in ("raw", "sin", "rec")}
+    used |= {n: (CAP + 128) * (256 if "codes" in n else 16) for n in FIELDS}
+    used |= {"staged_" + n: 256 * (256 if "codes" in n else 16) for n in FIELDS}
+    if other == written:
+        pytest.skip("one buffer")
+
+    def put(name, where, l):
+        if name == "workspace":
+            c.workspace = where
+        elif name[:3] == "hat":
+            c.hat[int(name[3])] = where
+        elif name[:4] == "rope":
+            c.rope = tuple(where if i == int(name[4]) else x for i, x in enumerate(c.rope))
+        else:
+            setattr(c.layers[l], name, where)
+
+    put(written, at, 2)
+    size = used.get(other.rstrip("0123"), (SINKS + 128 + 7) * 256)          # rope: rows of the longest sequence
+    put(other, at - size // 16 * 16 + 16, 1 if other[:3] == "raw" else 0)
+    assert c.status() == B.AQUAKV_EINVAL, B.aquakv_last_error()
+    assert "overlaps" in B.aquakv_last_error()
+
+
+@pytest.mark.parametrize("kw,want", [
+    (dict(n_sink=[SINKS, SINKS + 1]), B.AQUAKV_EINVAL), (dict(n_compressed=[CAP + 1, 0]), B.AQUAKV_EINVAL),
+    (dict(n_recent=[-1, 0]), B.AQUAKV_EINVAL), (dict(n_sink=[0, 4], n_compressed=[0, 128], n_recent=[0, 7]), B.AQUAKV_EINVAL),
+    (dict(workspace_bytes=4096), B.AQUAKV_EWORKSPACE)])
+def test_counts_and_workspace_of_a_cache_are_checked(kw, want):
+    assert stack().status(**kw) == want
+
+
+@pytest.mark.parametrize("name", WRITTEN + READ)
+@pytest.mark.parametrize("value", [None, 1])
+def test_every_buffer_of_a_cache_is_required_and_aligned(name, value):
+    c = stack()
+    entry = c.layers[1 if name[:3] == "raw" else 2]
+    setattr(entry, name, None if value is None else getattr(entry, name) + 1)
+    assert c.status() == (B.AQUAKV_ENULL if value is None else B.AQUAKV_EALIGN)
+
+
+def test_copy_ranges_checks_its_list():
+    B.aquakv_copy_ranges([])
+    for bad in ([0, 1 << 40, 16], [1 << 40, 0, 16], [0, 0, 0, 1 << 40, 0, 1]):
+        with pytest.raises(B.AquaKVError) as e:
+            B.aquakv_copy_ranges(bad)
+        assert e.value.status == B.AQUAKV_ENULL
