@@ -150,38 +150,46 @@ class AquaKVCache:
         # filling and flushing buffer after buffer would put them; what changes is that a prompt is quantized in one call
         # per layer over all its whole buffers instead of one call per 128 tokens (2436 tokens, 8 layers: 25.2 ms as 19
         # flushes per layer).
+        # The counts move once everything has been queued: until then the tokens go to rows that are not counted (but for the
+        # very last copy), so an append that fails can be made again.
+        ns, nc, nb = list(self._ns), list(self._nc), list(self._nb)
         now, later, full, direct = [], [], [], []
         for b in range(self.batch):
             pos, left = 0, n[b]
-            take = min(self.sink_tokens - self._ns[b], left)
+            take = min(self.sink_tokens - ns[b], left)
             if take > 0:
-                self._store(now, self._sink_at, max(self.sink_tokens, 1), self._ns[b], src, b, pos, take)
-                self._ns[b] += take
+                self._store(now, self._sink_at, max(self.sink_tokens, 1), ns[b], src, b, pos, take)
+                ns[b] += take
                 pos, left = pos + take, left - take
             r, dst = self.buffer_tokens, now
-            if self._nb[b] and left:
-                take = min(r - self._nb[b], left)
-                self._store(now, self._buf_at, r, self._nb[b], src, b, pos, take)
-                self._nb[b] += take
+            if nb[b] and left:
+                take = min(r - nb[b], left)
+                self._store(now, self._buf_at, r, nb[b], src, b, pos, take)
+                nb[b] += take
                 pos, left = pos + take, left - take
-                if self._nb[b] == r:
-                    full.append(b)
+                if nb[b] == r:
+                    full.append((b, nc[b]))
+                    nc[b] += r
+                    nb[b] = 0
                     dst = later                      # the buffer is free again once it has been flushed
             whole = left // r * r
             if whole:
-                direct.append((b, pos, whole))
+                direct.append((b, pos, nc[b], whole))
+                nc[b] += whole
                 pos, left = pos + whole, left - whole
             if left:
                 self._store(dst, self._buf_at, r, 0, src, b, pos, left)
-                self._nb[b] = left if dst is now else r + left
+                nb[b] = left
+        plan = self._plan_direct(direct) if direct else None       # allocates, hence ahead of the first launch
         if now:
             B.aquakv_copy_ranges(now)
         if full:
             self._flush(full)
-        if direct:
-            self._encode_direct(src, direct)
+        if plan is not None:
+            self._encode_direct(src, plan)
         if later:
             B.aquakv_copy_ranges(later)
+        self._ns, self._nc, self._nb = ns, nc, nb
 
     def _rows(self, x: torch.Tensor, t: int) -> torch.Tensor:
         """x in the storage dtype on the cache's device, every sequence's tokens one contiguous block: as it is
@@ -205,29 +213,47 @@ class AquaKVCache:
         for d, (x, seq) in zip(dst, src):
             out += (d + to, x + b * seq + pos, size)
 
-    def _encode_direct(self, src, pieces: List[Tuple[int, int, int]]) -> None:
-        """pieces: (sequence, first token in src, tokens): whole buffers' worth of tokens that go from the caller's tensors
-        to the compressed range, all sequences in one aquakv_encode_layer call per layer (at most kDirectTokens tokens at a
-        time, which bounds the scratch)."""
-        r, C, row = self.buffer_tokens, self._C, self._row_bytes
-        limit = max(self.kDirectTokens // r, 1) * r
-        chunk, room = [], limit
-        chunks = [chunk]
-        for b, pos, left in pieces:
-            while left:
-                if not room:
-                    chunk, room = [], limit
-                    chunks.append(chunk)
-                take = min(left, room)
-                chunk.append((b, pos, b * C + self._nc[b], take))      # ..., first row of its compressed range, tokens
-                self._nc[b] += take
-                pos, left, room = pos + take, left - take, room - take
+    def _plan_direct(self, pieces: List[Tuple[int, int, int, int]]) -> tuple:
+        """pieces: (sequence, first token in the source, first row of the sequence's compressed range, tokens): whole buffers'
+        worth of tokens that go from the caller's tensors to the compressed range.  -> (chunks of pieces, one
+        aquakv_encode_layer call per layer each, and the addresses of their scratch: reconstructions, gathered tokens, codes
+        per layer before they are scattered).  A chunk has at most kDirectTokens tokens, which bounds the scratch; where not
+        even that can be allocated, the buffers of the flush serve, with fewer tokens per chunk."""
+        r, row = self.buffer_tokens, self._row_bytes
+
+        def cut(limit):
+            chunks, room = [[]], limit
+            for b, pos, at, left in pieces:
+                while left:
+                    if not room:
+                        chunks.append([])
+                        room = limit
+                    take = min(left, room)
+                    chunks[-1].append((b, pos, b * self._C + at, take))
+                    pos, at, left, room = pos + take, at + take, left - take, room - take
+            return chunks
+
+        chunks = cut(max(self.kDirectTokens // r, 1) * r)
         biggest = max(sum(p[3] for p in c) for c in chunks)
         gather = any(len(c) > 1 for c in chunks)
-        scratch = torch.empty(8 if gather else 4, biggest * row, dtype=torch.uint8, device=self._like.device)
-        at = scratch.data_ptr()
-        hat = [(at + 2 * i * biggest * row, at + (2 * i + 1) * biggest * row) for i in range(2)]     # layer l - 1 feeds layer l
-        stage = [(k + 4 * biggest * row, v + 4 * biggest * row) for k, v in hat]
+        # rows of codes and scales, the widest layer's
+        width = [max(p[i][1] for p in self._codes_at if p is not None) for i in range(4)] if gather else []
+        sizes = [biggest * row] * (8 if gather else 4) + [(biggest * w + 15) // 16 * 16 for w in width]
+        try:
+            scratch = torch.empty(sum(sizes), dtype=torch.uint8, device=self._like.device)
+        except torch.OutOfMemoryError:
+            pair = lambda ts: [tuple(t.data_ptr() for t in p) for p in ts]
+            own = [None if c is None else [s.data_ptr() for p in c for s in p] for c in self._flush_codes]
+            return cut(self.batch * r), pair(self._flush_hat), pair(self._flush_in or []), own, None
+        at = [scratch.data_ptr()]
+        for size in sizes:
+            at.append(at[-1] + size)
+        return chunks, [at[0:2], at[2:4]], [at[4:6], at[6:8]], [at[8:12]] * len(self.layers), scratch
+
+    def _encode_direct(self, src, plan: tuple) -> None:
+        """The chunks of _plan_direct, each from the first layer to the last."""
+        row = self._row_bytes
+        chunks, hat, stage, staged, _ = plan                           # layer l - 1 feeds layer l: two pairs of hat and stage
         for c in chunks:
             N = sum(p[3] for p in c)
             Kp = Vp = None
@@ -242,78 +268,63 @@ class AquaKVCache:
                     B.aquakv_copy_ranges(jobs)
                     Xs = stage[l & 1]
                 if lay is None:                                        # kept in 16 bits
-                    jobs, to = [], 0
-                    for _, _, first, m in c:
-                        for X, store in zip(Xs, self.raw[l]):
-                            jobs += (store.data_ptr() + first * row, X + to * row, m * row)
-                        to += m
-                    B.aquakv_copy_ranges(jobs)
+                    self._scatter([(t.data_ptr(), row) for t in self.raw[l]], Xs, [p[2:] for p in c])
                     Kp, Vp = Xs
                     continue
                 Kh, Vh = hat[l & 1]
-                if len(c) == 1:
-                    out = [p + c[0][2] * size for p, size in self._codes_at[l]]
-                else:
-                    stores = [s for pair in self.codes[l] for s in pair]
-                    out = [torch.empty(N, *s.shape[1:], dtype=s.dtype, device=s.device) for s in stores]
+                out = [p + c[0][2] * size for p, size in self._codes_at[l]] if len(c) == 1 else staged[l]
                 B.aquakv_encode_layer(lay, N, *Xs, Kp, Vp, *out, Kh, Vh, self._view_ws)
                 if len(c) > 1:
-                    self._scatter(stores, out, [(first, m) for _, _, first, m in c])
+                    self._scatter(self._codes_at[l], out, [p[2:] for p in c])
                 Kp, Vp = Kh, Vh
 
     @staticmethod
-    def _scatter(stores, staged, parts: List[Tuple[int, int]], jobs: Optional[List[int]] = None) -> None:
-        """staged[k] rows, part after part, to rows at ... of stores[k]; added to `jobs`, or copied at once without."""
+    def _scatter(stores, sources, parts: List[Tuple[int, int]], jobs: Optional[List[int]] = None) -> None:
+        """The rows at address sources[k], part after part, to rows at ... of stores[k] = (address, bytes per row); added to
+        `jobs`, or copied at once without."""
         own = [] if jobs is None else jobs
-        for store, src in zip(stores, staged):
-            row = src[0].nbytes
-            to, frm = store.data_ptr(), src.data_ptr()
+        for (to, row), frm in zip(stores, sources):
             for at, m in parts:
                 own += (to + at * row, frm, m * row)
                 frm += m * row
         if jobs is None:
             B.aquakv_copy_ranges(own)
 
-    def _flush(self, full: List[int]) -> None:
-        """The full buffers of the sequences `full` are quantized together from the first layer to the last; each
-        sequence's codes land behind its own compressed range."""
+    def _flush(self, full: List[Tuple[int, int]]) -> None:
+        """The full buffers of the sequences `full` = (sequence, tokens in its compressed range) are quantized together from
+        the first layer to the last; each sequence's codes land behind its own compressed range."""
         r, C, n = self.buffer_tokens, self._C, len(full)
         row = self._row_bytes
         single = self.batch == 1
         whole = n == self.batch                              # the buffers of all sequences are one contiguous tensor
-        parts = [(b * C + self._nc[b], r) for b in full]
+        parts = [(b * C + at, r) for b, at in full]
         scatter: List[int] = []
         Kp = Vp = None
         for l, lay in enumerate(self.layers):
             if whole:
                 Xk, Xv = self.buf[l]
             else:
-                Xk, Xv = (x[:n * r] for x in self._flush_in[l & 1])
+                Xk, Xv = self._flush_in[l & 1]
                 jobs: List[int] = []
                 for X, x in ((Xk, self.buf[l][0]), (Xv, self.buf[l][1])):
-                    for i, b in enumerate(full):
+                    for i, (b, _) in enumerate(full):
                         jobs += (X.data_ptr() + i * r * row, x.data_ptr() + b * r * row, r * row)
                 B.aquakv_copy_ranges(jobs)
             if lay is None:                                  # kept in 16 bits: stored as is, feeds the next layer exactly
-                self._scatter(self.raw[l], (Xk.view(-1, self._H, self._g), Xv.view(-1, self._H, self._g)), parts)
+                self._scatter([(t.data_ptr(), row) for t in self.raw[l]], (Xk.data_ptr(), Xv.data_ptr()), parts)
                 Kp, Vp = Xk, Xv
                 continue
             Kh, Vh = (t.data_ptr() for t in self._flush_hat[l & 1])
             if single:
-                at = self._nc[0]
-                out = [p + at * size for p, size in self._codes_at[l]]
+                out = [p + full[0][1] * size for p, size in self._codes_at[l]]
             else:
-                stores = [s for pair in self.codes[l] for s in pair]
-                out = [s[:n * r] for pair in self._flush_codes[l] for s in pair]
+                out = [s.data_ptr() for pair in self._flush_codes[l] for s in pair]
             B.aquakv_encode_layer(lay, n * r, Xk, Xv, Kp, Vp, *out, Kh, Vh, self._flush_ws)
             if not single:
-                self._scatter(stores, out, parts, scatter)
+                self._scatter(self._codes_at[l], out, parts, scatter)
             Kp, Vp = Kh, Vh
         if scatter:                                          # the codes of all layers in one go
             B.aquakv_copy_ranges(scatter)
-        for b in full:
-            self._nc[b] += r
-            self._nb[b] -= r                                 # (append counts tokens behind the flushed ones already)
 
     # ------------------------------------------------------------------ recovery of one sequence
     def sweep(self, seq: int = 0) -> Iterator[Tuple[int, torch.Tensor, torch.Tensor]]:

@@ -1,0 +1,190 @@
+"""The bookkeeping of the cache manager on the CPU: which token goes to which row, in which calls, and what is left after a call that
+failed.  The two native calls are replaced by stand-ins on host memory: copies by memmove, the encoder by an arithmetic of its
+own, row by row, in which every output depends on the row's K, V and previous reconstructions.  A plain loop over the tokens
+of one sequence says what has to be where."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2501_19392_amd import binding as B
+from paper_2501_19392_amd.cache import AquaKVCache
+
+H, G = 2, 128
+D = H * G
+SINKS, RECENT = 3, 4
+
+
+def make_layer(first=False):
+    w = [None, None] if first else [torch.zeros(D, D), torch.zeros(D, 2 * D)]
+    return B.Layer(H, G, torch.zeros(16, 2), torch.ones(D), torch.ones(D), torch.float32, w_k=w[0], w_v=w[1])
+
+
+LAYER0, LAYER = make_layer(first=True), make_layer()
+
+
+def rows(x, n, width, dtype):
+    """n x width array over the memory of a tensor or an address"""
+    if isinstance(x, torch.Tensor):
+        x = x.data_ptr()
+    size = n * width * np.dtype(dtype).itemsize
+    return np.frombuffer((ctypes.c_char * size).from_address(x), dtype).reshape(n, width)
+
+
+def arithmetic(K, V, Kp, Vp):
+    """-> codes and scales of both, Khat, Vhat of rows of D floats"""
+    Kh = np.round(K * 4) / 4 + (0 if Kp is None else 0.5 * Kp)
+    Vh = np.round(V * 8) / 8 + 0.25 * Kh + (0 if Vp is None else 0.5 * Vp)
+    out = []
+    for x in (Kh, Vh):
+        f = x.astype(np.float32)
+        out += [f.view(np.uint8)[:, 5:5 + H * 32].copy(), f.view(np.int16)[:, 2:2 + H].copy()]
+    return out, Kh.astype(np.float32), Vh.astype(np.float32)
+
+
+class Calls:
+    """Stand-ins for the native calls; the `fail_at`-th one raises."""
+    def __init__(self, monkeypatch):
+        self.n, self.fail_at, self.encoded = 0, None, []
+        monkeypatch.setattr(B, "aquakv_copy_ranges", self.copy_ranges)
+        monkeypatch.setattr(B, "aquakv_encode_layer", self.encode_layer)
+
+    def count(self):
+        self.n += 1
+        if self.fail_at is not None and self.n > self.fail_at:
+            raise B.AquaKVError(B.AQUAKV_EHIP)
+
+    def copy_ranges(self, flat):
+        self.count()
+        flat = list(flat)
+        for dst, src, size in zip(flat[::3], flat[1::3], flat[2::3]):
+            ctypes.memmove(dst, src, size)
+
+    def encode_layer(self, lay, N, K, V, Kp, Vp, kc, ks, vc, vs, Kh, Vh, ws):
+        self.count()
+        self.encoded.append(N)
+        assert (Kp is None) == (Vp is None) == (lay.c.d_in_k == 0)
+        assert ws.nbytes >= B.aquakv_workspace_bytes(lay, N)
+        x = [None if p is None else rows(p, N, D, np.float32) for p in (K, V, Kp, Vp)]
+        codes, Kr, Vr = arithmetic(*x)
+        for dst, c, width, dt in zip((kc, ks, vc, vs), codes, (H * 32, H) * 2, (np.uint8, np.int16) * 2):
+            rows(dst, N, width, dt)[:] = c
+        rows(Kh, N, D, np.float32)[:] = Kr
+        rows(Vh, N, D, np.float32)[:] = Vr
+
+
+@pytest.fixture
+def calls(monkeypatch):
+    return Calls(monkeypatch)
+
+
+def new_cache(layers, batch, max_tokens, **kw):
+    cache = AquaKVCache(layers, max_tokens=max_tokens, sink_tokens=SINKS, buffer_tokens=RECENT, batch=batch, device="cpu", **kw)
+    for t in [x for part in (cache.sink, cache.buf, cache.raw) for p in part if p is not None for x in p] + \
+             [x for c in cache.codes if c is not None for p in c for x in p]:
+        t.zero_()
+    return cache
+
+
+def stream(layers, batch, tokens, seed=0):
+    gen = torch.Generator().manual_seed(seed)
+    return [tuple(torch.randn(batch, tokens, H, G, generator=gen) for _ in range(2)) for _ in layers]
+
+
+def content(cache):
+    """What a cache holds, sequence by sequence and layer by layer: counts, sinks, compressed range, recent tokens."""
+    out = []
+    for b in range(cache.batch):
+        ns, nc, nb = cache._ns[b], cache._nc[b], cache._nb[b]
+        seq = [(ns, nc, nb)]
+        for l in range(len(cache.layers)):
+            held = cache.raw[l] if cache.raw[l] is not None else [t for p in cache.codes[l] for t in p]
+            seq.append([t[b, :ns].numpy().copy() for t in cache.sink[l]] + [t[b, :nb].numpy().copy() for t in cache.buf[l]] +
+                       [t[b * cache._C:b * cache._C + nc].numpy().copy() for t in held])
+        out.append(seq)
+    return out
+
+
+def expected(layers, kv, lengths):
+    out = []
+    for b, n in enumerate(lengths):
+        ns = min(n, SINKS)
+        nc = (n - ns) // RECENT * RECENT
+        seq, Kp, Vp = [(ns, nc, n - ns - nc)], None, None
+        for lay, (K, V) in zip(layers, kv):
+            Kc, Vc = (x[b, ns:ns + nc].reshape(nc, D).numpy() for x in (K, V))
+            if lay is None:
+                held, Kp, Vp = [x.reshape(nc, H, G) for x in (Kc, Vc)], Kc, Vc
+            else:
+                held, Kp, Vp = arithmetic(Kc, Vc, Kp, Vp)
+                held = [h.reshape(nc, H, 32) if h.dtype == np.uint8 else h for h in held]
+            seq.append([x[b, :ns].numpy() for x in (K, V)] + [x[b, ns + nc:n].numpy() for x in (K, V)] + held)
+        out.append(seq)
+    return out
+
+
+def check(cache, kv, lengths):
+    got, want = content(cache), expected(cache.layers, kv, lengths)
+    for b, (g, w) in enumerate(zip(got, want, strict=True)):
+        assert g[0] == w[0], b
+        for l, (gl, wl) in enumerate(zip(g[1:], w[1:], strict=True)):
+            for i, (x, y) in enumerate(zip(gl, wl, strict=True)):
+                assert np.array_equal(x, y), (b, l, i)
+
+
+STACKS = {"coded": [LAYER0, LAYER, LAYER], "raw first": [None, LAYER, LAYER], "raw inside": [LAYER0, None, LAYER]}
+
+
+@pytest.mark.parametrize("stack", STACKS)
+@pytest.mark.parametrize("batch", [1, 3])
+def test_an_append_that_fails_can_be_made_again(calls, stack, batch):
+    """Whichever of its native calls fails, an append leaves the counts and everything counted as they were, and the same
+    append made again gives what it would have given at once."""
+    layers, first = STACKS[stack], [9, 3 + 4 + 2, 2][:batch]
+    then = [15, 2, 20][:batch]                     # tops up, flushes, goes on directly, ends in the buffer
+    kv = stream(layers, batch, 40)
+
+    def pieces(a, n):
+        return [tuple(torch.stack([x[b, a[b]:a[b] + max(n)] for b in range(batch)]) for x in p) for p in kv]
+
+    def filled():
+        cache = new_cache(layers, batch, 40)
+        cache.append(pieces([0] * batch, first), lengths=first)
+        return cache
+
+    cache = filled()
+    calls.n = 0
+    cache.append(pieces(first, then), lengths=then)
+    total = calls.n
+    check(cache, kv, [a + b for a, b in zip(first, then)])
+    assert total > 4
+    for k in range(total):
+        cache = filled()
+        before = content(cache)
+        calls.n, calls.fail_at = 0, k
+        with pytest.raises(B.AquaKVError):
+            cache.append(pieces(first, then), lengths=then)
+        calls.fail_at = None
+        for x, y in zip(before, content(cache), strict=True):
+            assert x[0] == y[0]
+            assert all(np.array_equal(p, q) for r, s in zip(x[1:], y[1:]) for p, q in zip(r, s))
+        cache.append(pieces(first, then), lengths=then)
+        check(cache, kv, [a + b for a, b in zip(first, then)])
+
+
+@pytest.mark.parametrize("stack", STACKS)
+@pytest.mark.parametrize("batch", [1, 3])
+def test_without_memory_for_scratch_a_prompt_goes_through_the_flush_buffers(calls, monkeypatch, stack, batch):
+    layers, lengths = STACKS[stack], [40, 17, 5][:batch]
+    kv = stream(layers, batch, 40, seed=1)
+    cache = new_cache(layers, batch, 40)
+
+    def no_memory(*a, **kw):
+        raise torch.OutOfMemoryError("no memory")
+
+    with monkeypatch.context() as m:
+        m.setattr(torch, "empty", no_memory)
+        cache.append(kv, lengths=lengths)
+    check(cache, kv, lengths)
+    assert max(calls.encoded) <= batch * RECENT
