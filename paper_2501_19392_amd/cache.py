@@ -128,7 +128,8 @@ class AquaKVCache:
     def append(self, kv: Sequence[Tuple[torch.Tensor, torch.Tensor]], lengths: Optional[Sequence[int]] = None) -> None:
         """kv[l] = (K, V) of the new tokens at layer l in the storage dtype: [t, kv_heads, head_dim] for a single
         sequence, [batch, t, kv_heads, head_dim] otherwise; `lengths[b]` <= t tokens of sequence b are taken
-        (default: all t)."""
+        (default: all t).  Tensors of another dtype or device, and such with gaps, are copied.  If the call fails, the cache
+        is what it was."""
         if len(kv) != len(self.layers):
             raise ValueError("one (K, V) pair per layer")
         first = kv[0][0]
@@ -142,7 +143,8 @@ class AquaKVCache:
         if any(self._ns[b] + self._nc[b] + self._nb[b] + n[b] > self.max_tokens for b in range(self.batch)):
             raise ValueError("cache is full")
         # the sources: (address, bytes from sequence to sequence) per layer, keys then values; `kept` holds what was made here
-        kept = [self._rows(x, t) for pair in kv for x in pair]
+        most = max(n)
+        kept = [self._rows(x, t, most) for pair in kv for x in pair]
         es = self._like.element_size()
         src = [(x.data_ptr(), x.stride(0) * es if x.dim() == 4 else 0) for x in kept]
         # Per sequence: sinks first, then what tops up a buffer that already holds tokens, then whole buffers' worth of
@@ -191,11 +193,14 @@ class AquaKVCache:
             B.aquakv_copy_ranges(later)
         self._ns, self._nc, self._nb = ns, nc, nb
 
-    def _rows(self, x: torch.Tensor, t: int) -> torch.Tensor:
+    def _rows(self, x: torch.Tensor, t: int, most: int) -> torch.Tensor:
         """x in the storage dtype on the cache's device, every sequence's tokens one contiguous block: as it is
-        ([t, kv_heads, head_dim], [batch, t, kv_heads, head_dim]) or a copy."""
+        ([t, kv_heads, head_dim], [batch, t, kv_heads, head_dim]) or a copy.  `most` tokens are taken at most: a tensor may
+        hold another number of rows (or sequences) than the first layer's keys, as long as those are among them."""
         H, g, like = self._H, self._g, self._like
         one = x.dim() == 3
+        if x.shape != ((t, H, g) if one else (self.batch, t, H, g)):
+            x, t = x[:most] if one else x[:self.batch, :most], most
         if x.dtype != like.dtype or x.device != like.device or x.shape != ((t, H, g) if one else (self.batch, t, H, g)):
             x = x.to(device=like.device, dtype=self._dt).expand(self.batch, t, H, g)
             one = False

@@ -188,3 +188,20 @@ def test_without_memory_for_scratch_a_prompt_goes_through_the_flush_buffers(call
         cache.append(kv, lengths=lengths)
     check(cache, kv, lengths)
     assert max(calls.encoded) <= batch * RECENT
+
+
+@pytest.mark.parametrize("batch,lengths", [(1, None), (1, [19]), (3, [19, 4, 11]), (3, None)])
+def test_tensors_with_more_or_fewer_rows_than_the_first_layers_keys(calls, batch, lengths):
+    """Only the tokens that are taken have to be there: values and later layers may hold more rows (and sequences), or fewer."""
+    layers, t = [LAYER0, LAYER, LAYER], 21
+    full = stream(layers, batch + 1, 30, seed=2)
+    taken = [t] * batch if lengths is None else lengths
+    sizes = [(t, 30), (max(taken), 25), (22, max(taken))]
+    kv = [tuple(x[:batch if (l, i) == (0, 0) else batch + i, :m].contiguous() for i, (x, m) in enumerate(zip(p, s)))
+          for l, (p, s) in enumerate(zip(full, sizes))]
+    cache = new_cache(layers, batch, 40)
+    cache.append([tuple(x[0] for x in p) for p in kv] if batch == 1 else kv, lengths=lengths)
+    check(cache, full, taken)
+    with pytest.raises(RuntimeError):                    # a token that is not there
+        short = [tuple(x[0, :max(taken) - 1] if batch == 1 else x[:, :max(taken) - 1] for x in p) for p in kv[1:]]
+        new_cache(layers, batch, 40).append([tuple(x[0] if batch == 1 else x for x in kv[0])] + short, lengths=lengths)
