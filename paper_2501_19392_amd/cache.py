@@ -51,8 +51,7 @@ class AquaKVCache:
         self.capacity = cap
         C = max(cap, 1)
         self._C = C
-        # A cache is made per request, so what it costs counts: tensors of one shape are slices of one allocation, and the
-        # addresses that every append needs are worked out here.
+        # A cache is made per request, so what it costs counts: tensors of one shape are slices of one allocation.
         raws = lambda n, *shape: torch.empty(n, *shape, H, g, dtype=dt, device=device).unbind(0)
         pairs = lambda ts: list(zip(ts[::2], ts[1::2]))
         self._like = torch.empty(0, dtype=dt, device=device)
@@ -74,9 +73,6 @@ class AquaKVCache:
         self._view = pairs(raws(4, max(max_tokens, batch * C)))
         self._view_ws = self._alloc_workspace(batch * C, device)
         self._staged = self._alloc_codes(batch * C, device) if batch > 1 else [None] * L
-        self._sink_at, self._buf_at = ([t.data_ptr() for pair in ts for t in pair] for ts in (self.sink, self.buf))
-        # per layer the four code tensors' (address, bytes per token)
-        self._codes_at = [None if c is None else [(t.data_ptr(), t[0].nbytes) for pair in c for t in pair] for c in self.codes]
         self._ns, self._nc, self._nb = [0] * batch, [0] * batch, [0] * batch
         self._attend = None                 # buffers of attend(), sized on first use (they depend on the query heads)
         self._device = device
@@ -124,6 +120,17 @@ class AquaKVCache:
     def n_tokens(self):
         return self._count([s + c + b for s, c, b in zip(self._ns, self._nc, self._nb)])
 
+    # ------------------------------------------------------------------ addresses
+    # Taken from the tensors on every call: sink, buf, codes and raw may be replaced by others of the same layout (a cache
+    # that is read back, say), and none of their addresses is kept.
+    @staticmethod
+    def _addresses(pairs) -> List[int]:
+        return [t.data_ptr() for pair in pairs for t in pair]
+
+    def _codes_at(self, l: int) -> List[Tuple[int, int]]:
+        """(address, bytes per token) of the four code tensors of layer l"""
+        return [(t.data_ptr(), t.stride(0) * t.element_size()) for pair in self.codes[l] for t in pair]
+
     # ------------------------------------------------------------------ append / flush
     def append(self, kv: Sequence[Tuple[torch.Tensor, torch.Tensor]], lengths: Optional[Sequence[int]] = None) -> None:
         """kv[l] = (K, V) of the new tokens at layer l in the storage dtype: [t, kv_heads, head_dim] for a single
@@ -156,17 +163,19 @@ class AquaKVCache:
         # very last copy), so an append that fails can be made again.
         ns, nc, nb = list(self._ns), list(self._nc), list(self._nb)
         now, later, full, direct = [], [], [], []
+        buf_at, sink_at = self._addresses(self.buf), None
         for b in range(self.batch):
             pos, left = 0, n[b]
             take = min(self.sink_tokens - ns[b], left)
             if take > 0:
-                self._store(now, self._sink_at, max(self.sink_tokens, 1), ns[b], src, b, pos, take)
+                sink_at = sink_at or self._addresses(self.sink)
+                self._store(now, sink_at, max(self.sink_tokens, 1), ns[b], src, b, pos, take)
                 ns[b] += take
                 pos, left = pos + take, left - take
             r, dst = self.buffer_tokens, now
             if nb[b] and left:
                 take = min(r - nb[b], left)
-                self._store(now, self._buf_at, r, nb[b], src, b, pos, take)
+                self._store(now, buf_at, r, nb[b], src, b, pos, take)
                 nb[b] += take
                 pos, left = pos + take, left - take
                 if nb[b] == r:
@@ -180,7 +189,7 @@ class AquaKVCache:
                 nc[b] += whole
                 pos, left = pos + whole, left - whole
             if left:
-                self._store(dst, self._buf_at, r, 0, src, b, pos, left)
+                self._store(dst, buf_at, r, 0, src, b, pos, left)
                 nb[b] = left
         plan = self._plan_direct(direct) if direct else None       # allocates, hence ahead of the first launch
         if now:
@@ -242,13 +251,14 @@ class AquaKVCache:
         biggest = max(sum(p[3] for p in c) for c in chunks)
         gather = any(len(c) > 1 for c in chunks)
         # rows of codes and scales, the widest layer's
-        width = [max(p[i][1] for p in self._codes_at if p is not None) for i in range(4)] if gather else []
+        coded = [self._codes_at(l) for l, c in enumerate(self.codes) if c is not None] if gather else []
+        width = [max(p[i][1] for p in coded) for i in range(4)] if gather else []
         sizes = [biggest * row] * (8 if gather else 4) + [(biggest * w + 15) // 16 * 16 for w in width]
         try:
             scratch = torch.empty(sum(sizes), dtype=torch.uint8, device=self._like.device)
         except torch.OutOfMemoryError:
             pair = lambda ts: [tuple(t.data_ptr() for t in p) for p in ts]
-            own = [None if c is None else [s.data_ptr() for p in c for s in p] for c in self._flush_codes]
+            own = [None if c is None else self._addresses(c) for c in self._flush_codes]
             return cut(self.batch * r), pair(self._flush_hat), pair(self._flush_in or []), own, None
         at = [scratch.data_ptr()]
         for size in sizes:
@@ -277,10 +287,11 @@ class AquaKVCache:
                     Kp, Vp = Xs
                     continue
                 Kh, Vh = hat[l & 1]
-                out = [p + c[0][2] * size for p, size in self._codes_at[l]] if len(c) == 1 else staged[l]
+                stores = self._codes_at(l)
+                out = [p + c[0][2] * size for p, size in stores] if len(c) == 1 else staged[l]
                 B.aquakv_encode_layer(lay, N, *Xs, Kp, Vp, *out, Kh, Vh, self._view_ws)
                 if len(c) > 1:
-                    self._scatter(self._codes_at[l], out, [p[2:] for p in c])
+                    self._scatter(stores, out, [p[2:] for p in c])
                 Kp, Vp = Kh, Vh
 
     @staticmethod
@@ -321,12 +332,12 @@ class AquaKVCache:
                 continue
             Kh, Vh = (t.data_ptr() for t in self._flush_hat[l & 1])
             if single:
-                out = [p + full[0][1] * size for p, size in self._codes_at[l]]
+                out = [p + full[0][1] * size for p, size in self._codes_at(l)]
             else:
-                out = [s.data_ptr() for pair in self._flush_codes[l] for s in pair]
+                out = self._addresses(self._flush_codes[l])
             B.aquakv_encode_layer(lay, n * r, Xk, Xv, Kp, Vp, *out, Kh, Vh, self._flush_ws)
             if not single:
-                self._scatter(self._codes_at[l], out, parts, scatter)
+                self._scatter(self._codes_at(l), out, parts, scatter)
             Kp, Vp = Kh, Vh
         if scatter:                                          # the codes of all layers in one go
             B.aquakv_copy_ranges(scatter)
@@ -371,8 +382,9 @@ class AquaKVCache:
         if single and self.batch != 1:
             raise ValueError("a batched cache takes [batch, q_heads, head_dim]")
         QH = queries[0].shape[-2]
-        if self._attend is None or self._attend["shape"].q_heads != QH:
-            self._attend = self._attend_state(QH)
+        held = self._held()
+        if self._attend is None or self._attend["shape"].q_heads != QH or self._attend["held"] != held:
+            self._attend = dict(self._attend_state(QH), held=held)
         A = self._attend
         shape = (QH, self._g) if single else (self.batch, QH, self._g)
         for entry, q in zip(A["layers"], queries, strict=True):
@@ -386,6 +398,12 @@ class AquaKVCache:
         cos, sin = rope if rope is not None else (None, None)
         B.aquakv_attend_cache(A["layers"], A["shape"], self._ns, self._nc, self._nb, score_scale, A["hat"], A["ws"], cos, sin)
         return [o[0] if single else o for o in A["out"]]
+
+    def _held(self) -> tuple:
+        """What attend() passes on by address: the layers' descriptors and where everything that is cached lies."""
+        return ([None if lay is None else lay.c for lay in self.layers],
+                self._addresses(self.sink), self._addresses(self.buf), self._addresses(p for p in self.raw if p is not None),
+                [t.data_ptr() for c in self.codes if c is not None for pair in c for t in pair])
 
     def _attend_state(self, q_heads: int) -> dict:
         """What attend() passes on every call for this number of query heads."""

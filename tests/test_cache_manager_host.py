@@ -205,3 +205,41 @@ def test_tensors_with_more_or_fewer_rows_than_the_first_layers_keys(calls, batch
     with pytest.raises(RuntimeError):                    # a token that is not there
         short = [tuple(x[0, :max(taken) - 1] if batch == 1 else x[:, :max(taken) - 1] for x in p) for p in kv[1:]]
         new_cache(layers, batch, 40).append([tuple(x[0] if batch == 1 else x for x in kv[0])] + short, lengths=lengths)
+
+
+@pytest.mark.parametrize("stack", STACKS)
+@pytest.mark.parametrize("batch", [1, 3])
+def test_replaced_tensors_are_the_ones_that_are_used(calls, monkeypatch, stack, batch):
+    """Sinks, buffers, codes and 16-bit ranges replaced by copies between two calls: append and attend go by the copies."""
+    layers, n = STACKS[stack], 34
+    kv = stream(layers, batch, n, seed=3)
+    cache, seen = new_cache(layers, batch, n), []
+    monkeypatch.setattr(B, "aquakv_attend_cache", lambda entries, *a, **kw: seen.append([
+        [getattr(e, f) for f in ("sink_k", "recent_v", "k_codes", "v_scales", "raw_k")] for e in entries]))
+    q = [torch.zeros(batch, 2 * H, G) for _ in layers]
+
+    def replace():
+        for part in (cache.sink, cache.buf, cache.raw, cache.codes):
+            for l, p in enumerate(part):
+                if p is not None:
+                    part[l] = tuple(tuple(t.clone() for t in x) if isinstance(x, tuple) else x.clone() for x in p)
+                    for x in p:                              # the old ones are gone
+                        for t in x if isinstance(x, tuple) else (x,):
+                            t.fill_(77)
+
+    def lies():
+        return [[cache.sink[l][0].data_ptr(), cache.buf[l][1].data_ptr()] +
+                ([None, None, cache.raw[l][0].data_ptr()] if lay is None else
+                 [cache.codes[l][0][0].data_ptr(), cache.codes[l][1][1].data_ptr(), None]) for l, lay in enumerate(layers)]
+
+    at = 0
+    for step in (2, 3, 11, 1, 1, 16):
+        cache.append([tuple(x[:, at:at + step] for x in p) for p in kv])
+        at += step
+        cache.attend([x[0] for x in q] if batch == 1 else q, 1.0)
+        assert seen[-1] == lies()
+        replace()
+        cache.attend([x[0] for x in q] if batch == 1 else q, 1.0)
+        assert seen[-1] == lies()
+    assert at == n
+    check(cache, kv, [n] * batch)
