@@ -369,7 +369,8 @@ class AquaKVCache:
     # ------------------------------------------------------------------ attention of one new token per sequence
     def attend(self, queries: Sequence[torch.Tensor], score_scale: float, rope=None) -> List[torch.Tensor]:
         """queries[l]: the new token's queries at layer l in the storage dtype, [q_heads, head_dim] for a single
-        sequence, [batch, q_heads, head_dim] otherwise.  Returns one fp32 tensor of the same shape per layer:
+        sequence, [batch, q_heads, head_dim] otherwise.  Queries on another device and such with gaps are copied; those of
+        another dtype are converted for a batch and refused for a single sequence.  Returns one fp32 tensor of the same shape per layer:
         softmax(score_scale * q K^T) V over sinks, compressed past and buffer of the query's own sequence.
         One sweep over the layers for all sequences (aquakv_attend_cache); the recovered tensors of layer l feed
         layer l + 1 as in `sweep`.
@@ -387,17 +388,24 @@ class AquaKVCache:
             self._attend = dict(self._attend_state(QH), held=held)
         A = self._attend
         shape = (QH, self._g) if single else (self.batch, QH, self._g)
-        for entry, q in zip(A["layers"], queries, strict=True):
-            if q.shape != shape or q.dtype != self._dt:
-                raise ValueError(f"queries must be {list(shape)}, {self._dt}")
-            entry.q = q.data_ptr() if q.is_contiguous() else None
-        # queries with gaps are copied; they must live until the call has been queued
-        kept = [q.contiguous() for q in queries] if any(e.q is None for e in A["layers"]) else queries
+        if len(queries) < len(self.layers):
+            raise ValueError("queries of every layer are needed")
+        kept = [self._query(q, shape) for q in queries[:len(self.layers)]]      # copies must live until the call has been queued
         for entry, q in zip(A["layers"], kept):
             entry.q = q.data_ptr()
         cos, sin = rope if rope is not None else (None, None)
         B.aquakv_attend_cache(A["layers"], A["shape"], self._ns, self._nc, self._nb, score_scale, A["hat"], A["ws"], cos, sin)
         return [o[0] if single else o for o in A["out"]]
+
+    def _query(self, q: torch.Tensor, shape: Tuple[int, ...]) -> torch.Tensor:
+        like = self._like
+        if len(shape) == 3 and q.dim() == 3 and q.shape[0] > shape[0]:
+            q = q[:shape[0]]                                 # more sequences than the cache has
+        if q.shape != shape or (q.dtype != like.dtype and self.batch == 1):
+            raise ValueError(f"queries must be {list(shape)}, {self._dt}")
+        if q.dtype != like.dtype or q.device != like.device:
+            q = q.to(device=like.device, dtype=like.dtype)
+        return q if q.is_contiguous() and q.data_ptr() & 15 == 0 else q.clone(memory_format=torch.contiguous_format)
 
     def _held(self) -> tuple:
         """What attend() passes on by address: the layers' descriptors and where everything that is cached lies."""

@@ -243,3 +243,34 @@ def test_replaced_tensors_are_the_ones_that_are_used(calls, monkeypatch, stack, 
         assert seen[-1] == lies()
     assert at == n
     check(cache, kv, [n] * batch)
+
+
+@pytest.mark.parametrize("batch", [1, 3])
+def test_queries_that_are_copied_and_queries_that_are_refused(calls, monkeypatch, batch):
+    layers, QH = [LAYER0, LAYER], 2 * H
+    cache, seen = new_cache(layers, batch, 9), []
+    monkeypatch.setattr(B, "aquakv_attend_cache", lambda entries, *a, **kw: seen.append(
+        [rows(e.q, batch * QH, G, np.float32).copy() for e in entries]))
+    cache.append(stream(layers, batch, 5))
+    gen = torch.Generator().manual_seed(4)
+    q = [torch.randn(batch + 2, QH, G, generator=gen) for _ in range(3)]
+
+    def passed(make):
+        cache.attend([make(x) for x in q], 1.0)
+        for got, x in zip(seen[-1], q[:2], strict=True):
+            assert np.array_equal(got, x[:batch].reshape(-1, G).numpy())
+
+    passed(lambda x: x[0] if batch == 1 else x[:batch])                                  # one more than there are layers
+    passed(lambda x: x)                                                                   # more sequences than the cache has
+    passed(lambda x: x[:batch].transpose(1, 2).contiguous().transpose(1, 2))              # gaps
+    passed(lambda x: torch.cat([torch.zeros(1), x[:batch].flatten()])[1:].view(batch, QH, G))        # not 16-byte aligned
+    if batch > 1:
+        passed(lambda x: x.double())
+    else:
+        with pytest.raises(ValueError):
+            cache.attend([x[0].double() for x in q], 1.0)
+    for bad in (lambda x: x[:, :, 1:], lambda x: x[:0]):
+        with pytest.raises(ValueError):
+            cache.attend([bad(x) for x in q], 1.0)
+    with pytest.raises(ValueError):
+        cache.attend([x[:batch] for x in q[:1]], 1.0)
