@@ -140,9 +140,12 @@ int aquakv_build_search_table(const float* codebook, int32_t vq_dim, int32_t n_c
  * chunk of rows (fp32 layers) or the re-tiled predictor weights (bf16 layers with
  * rotation groups across the heads; nothing for the other bf16 layers); behind it
  * a temporary Khat for one chunk of rows when the caller does not ask for one.
- * More is used where it helps: with rotation groups across the heads, short ranges
- * (up to 4096 rows) are encoded in as few pieces as there is room for fp32
- * predictions (kv_heads * head_dim * 4 bytes per row). */
+ * More is used where it helps, if workspace_bytes says that it is there: with
+ * rotation groups across the heads, short ranges (up to 4096 rows) are encoded in as
+ * few pieces as there is room for fp32 predictions, at most kv_heads * head_dim * 4
+ * bytes per row beyond what is needed and never over buffers of the call or of the
+ * layer.  So what lies within workspace_bytes belongs to the call while it runs:
+ * calls that run at the same time need workspaces that do not overlap. */
 size_t aquakv_workspace_bytes(const aquakv_layer* layer, int64_t tokens);
 
 /* Which of the two large tiles the fused bf16 kernels (predictor of Sect. 3.2 with the quantizer or its inverse inside: aquakv_encode_layer,

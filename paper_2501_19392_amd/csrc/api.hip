@@ -158,17 +158,6 @@ int check_disjoint(CacheRange* r, int64_t n) {
   return AQUAKV_OK;
 }
 
-// How much of the workspace a call may use beyond what it needs: all of it, unless the part behind the first `need` bytes lies
-// over the call's other buffers (it was never promised to be scratch by callers that pass one large arena).
-size_t usable_workspace(void* workspace, size_t need, size_t bytes, const Range* outs, int n_out, const Range* ins, int n_in) {
-  const Range all = {workspace, bytes, ""};
-  for (int i = 0; i < n_out; ++i)
-    if (outs[i].p != workspace && overlap(all, outs[i])) return need;
-  for (int j = 0; j < n_in; ++j)
-    if (overlap(all, ins[j])) return need;
-  return bytes;
-}
-
 #define CHECK(expr)                      \
   do {                                   \
     const int s_ = (expr);               \
@@ -210,6 +199,32 @@ Plan make_plan(const aquakv_layer* L, int64_t tokens) {
   return pl;
 }
 
+// Encode of rotation groups across the 8 heads: ranges of up to kWideSplitRows rows are quantized from fp32 predictions in the
+// workspace (encode_wide), in as few pieces as there is room for them.
+constexpr int64_t kWideSplitRows = 4096;
+
+// Bytes of the workspace an encode call over `tokens` rows uses: the `need` bytes every caller provides, and where more
+// predictions help up to as much as those of all rows take.  Not if the bytes behind the first `need` lie over the call's other
+// buffers or the layer's parameters: an arena's owner may state all that is left of it.
+size_t usable_workspace(const aquakv_layer* L, const Plan& pl, int64_t tokens, void* workspace, size_t need, size_t bytes,
+                        const Range* outs, int n_out, const Range* ins, int n_in) {
+  if (!pl.fused || !is_wide(L) || (L->d_in_k == 0 && L->d_in_v == 0) || tokens > kWideSplitRows) return need;
+  const size_t most = need + (size_t)tokens * pl.D * sizeof(float);
+  const Range all = {workspace, bytes < most ? bytes : most, ""};
+  const size_t D = (size_t)pl.D, points = is_rtn(L) ? 0 : (size_t)L->n_codewords;
+  const Range params[] = {{L->w_k, D * L->d_in_k * pl.eb, ""}, {L->w_v, D * L->d_in_v * pl.eb, ""}, {L->b_k, D * sizeof(float), ""},
+                          {L->b_v, D * sizeof(float), ""}, {L->signs_k, points ? D : 0, ""}, {L->signs_v, points ? D : 0, ""},
+                          {L->codebook, points * 2 * sizeof(float), ""},
+                          {L->search_table, points ? aquakv::kSearchTableBytes : 0, ""}};
+  for (const Range& r : params)
+    if (overlap(all, r)) return need;
+  for (int i = 0; i < n_out; ++i)
+    if (outs[i].p != workspace && overlap(all, outs[i])) return need;
+  for (int j = 0; j < n_in; ++j)
+    if (overlap(all, ins[j])) return need;
+  return all.n;
+}
+
 inline const void* at(const void* base, int64_t row, size_t row_bytes) {
   return base == nullptr ? nullptr : static_cast<const unsigned char*>(base) + row * row_bytes;
 }
@@ -226,7 +241,6 @@ inline aquakv::QuantizeIo coded(const int8_t* signs, const void* codes, const vo
 // every workgroup of 64 tokens: 100 us however few tokens there are.  Short ranges therefore run as predictor (on the tiles
 // of short ranges, fp32 predictions into the workspace) and stand-alone quantizer, in pieces of as many rows as the workspace
 // holds predictions for (`room` bytes): kWideSplitRows is where the two cost the same.
-constexpr int64_t kWideSplitRows = 4096;
 int encode_wide(const aquakv_layer* L, const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias,
                 const int8_t* signs, const void* X, uint8_t* codes, uint16_t* scales, void* Xhat, int64_t n, int D, float* ws,
                 size_t room, hipStream_t stream) {
@@ -482,7 +496,7 @@ int aquakv_encode_layer(const aquakv_layer* L, int64_t tokens, const void* K, co
                          {Vhat_prev, has_v ? t * (L->d_in_v - pl.D) * pl.eb : 0, "Vhat_prev"}};
     const void* const inplace[] = {K, V, nullptr, nullptr, nullptr, nullptr, nullptr};
     CHECK(check_no_alias(outs, 7, ins, 4, inplace));
-    usable = usable_workspace(workspace, pl.p_bytes + pl.khat_bytes, workspace_bytes, outs, 7, ins, 4);
+    usable = usable_workspace(L, pl, tokens, workspace, pl.p_bytes + pl.khat_bytes, workspace_bytes, outs, 7, ins, 4);
   }
 
   hipStream_t stream = static_cast<hipStream_t>(stream_);
@@ -587,7 +601,7 @@ int aquakv_encode_keys(const aquakv_layer* L, int64_t tokens, const void* K, con
     const Range ins[] = {{K, t * row, "K"}, {Khat_prev, t * L->d_in_k * pl.eb, "Khat_prev"}};
     const void* const inplace[] = {K, nullptr, nullptr, nullptr};
     CHECK(check_no_alias(outs, 4, ins, 2, inplace));
-    room = pl.p_bytes == 0 ? 0 : usable_workspace(workspace, pl.p_bytes, workspace_bytes, outs, 4, ins, 2);
+    room = pl.p_bytes == 0 ? 0 : usable_workspace(L, pl, tokens, workspace, pl.p_bytes, workspace_bytes, outs, 4, ins, 2);
   }
   for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk) {
     const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;
@@ -625,7 +639,7 @@ int aquakv_encode_values(const aquakv_layer* L, int64_t tokens, const void* V, c
                          {Khat, has_v ? t * row : 0, "Khat"}};
     const void* const inplace[] = {V, nullptr, nullptr, nullptr};
     CHECK(check_no_alias(outs, 4, ins, 3, inplace));
-    room = pl.p_bytes == 0 ? 0 : usable_workspace(workspace, pl.p_bytes, workspace_bytes, outs, 4, ins, 3);
+    room = pl.p_bytes == 0 ? 0 : usable_workspace(L, pl, tokens, workspace, pl.p_bytes, workspace_bytes, outs, 4, ins, 3);
   }
   for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk) {
     const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;

@@ -127,3 +127,37 @@ def test_scores_of_a_batch_are_those_of_its_sequences(H, dk, batch, S, quantizer
             call(1, kc[rows].clone(), ks[rows].clone(), Kp[rows].clone(), q[i:i + 1].clone(), one, None)
             torch.cuda.synchronize()
             assert torch.equal(one[0], got[i]), i
+
+
+@pytest.mark.parametrize("name", ["w_k", "w_v", "b_k", "b_v", "codebook", "signs_k", "signs_v", "search_table"])
+def test_parameters_behind_the_needed_workspace_are_left_alone(name):
+    """One arena: the workspace is stated as all that is left of it, and a parameter of the layer lies in that rest."""
+    from paper_2501_19392_amd import binding as B
+    T, D = 2100, 1024                                  # does not fit the needed workspace in one piece
+    print(f"case arena with {name}", flush=True)
+    lg = layer(8, 1024, "n16", 1024)
+    if lg.search_table is None:
+        lg.search_table = B.build_search_table(lg.codebook)
+        lg.c.search_table = lg.search_table.data_ptr()
+    g = torch.Generator(device="cuda").manual_seed(5)
+    K, V, Kp, Vp = (torch.randn(T, D, generator=g, device="cuda").bfloat16() for _ in range(4))
+
+    def encode(workspace, khat):
+        codes = [t for _ in range(2) for t in lg.alloc_codes(T)]
+        Kh, Vh = lg.alloc_kv(T), lg.alloc_kv(T)
+        B.aquakv_encode_layer(lg, T, K, V, Kp, Vp, *codes, Kh if khat else None, Vh, workspace)
+        torch.cuda.synchronize()
+        return codes + [Vh]
+
+    want = encode(lg.alloc_workspace(T), True)
+    x = bits(getattr(lg, name)).flatten()
+    need = lg.alloc_workspace(T).numel()
+    for khat, at in ((True, need), (False, need), (False, need + (4 << 20))):
+        arena = torch.zeros(need + (12 << 20), dtype=torch.uint8, device="cuda")
+        arena[at:at + x.numel()] = x
+        setattr(lg.c, name, arena.data_ptr() + at)
+        got = encode(arena, khat)
+        assert torch.equal(arena[at:at + x.numel()], x)
+        for a, b in zip(got, want, strict=True):
+            assert torch.equal(bits(a), bits(b))
+        setattr(lg.c, name, getattr(lg, name).data_ptr())
