@@ -274,3 +274,54 @@ def test_queries_that_are_copied_and_queries_that_are_refused(calls, monkeypatch
             cache.attend([bad(x) for x in q], 1.0)
     with pytest.raises(ValueError):
         cache.attend([x[:batch] for x in q[:1]], 1.0)
+
+
+@pytest.mark.parametrize("stack", STACKS)
+@pytest.mark.parametrize("batch,lengths", [(1, [43]), (3, [43, 9, 30]), (3, [3, 43, 2]), (4, [11, 11, 11, 11])])
+@pytest.mark.parametrize("limit", [1, RECENT, 3 * RECENT + 1, 7 * RECENT])
+def test_prompts_longer_than_one_call_takes(calls, stack, batch, lengths, limit):
+    """Chunks with one piece (written in place) and with several (gathered and scattered), sequences cut between chunks, scratch
+    used again by the next chunk; with an empty cache and behind tokens that are already in the buffer."""
+    layers, n = STACKS[stack], max(lengths) + 6
+    kv = stream(layers, batch, n, seed=6)
+    for head in (0, 5):                                  # 5: the sinks and two tokens in the buffer
+        cache = new_cache(layers, batch, n)
+        cache.kDirectTokens = limit
+        calls.encoded.clear()
+        if head:
+            cache.append([tuple(x[:, :head] for x in p) for p in kv])
+        cache.append([tuple(x[:, head:] for x in p) for p in kv], lengths=lengths)
+        check(cache, kv, [head + m for m in lengths])
+        flushed = sum(1 for m in lengths if head and SINKS < head < SINKS + RECENT <= head + m)
+        assert max(calls.encoded, default=0) <= max(limit // RECENT * RECENT, RECENT, flushed * RECENT)
+
+
+@pytest.mark.parametrize("batch", [1, 3])
+@pytest.mark.parametrize("what", ["dtype", "gaps between tokens", "gaps between heads", "heads by stride", "unaligned", "one head for all",
+                                  "odd batch stride"])
+def test_sources_that_have_to_be_copied(calls, what, batch):
+    layers, n = [LAYER0, LAYER], 25
+    kv = stream(layers, batch, n, seed=7)
+    if what == "one head for all":
+        kv = [tuple(x[:, :, :1].expand(batch, n, H, G).contiguous() for x in p) for p in kv]
+
+    def source(x):
+        if what == "dtype":
+            return x.double()
+        if what == "gaps between tokens":
+            return torch.cat([x, x + 1], -2)[:, :, :H]
+        if what == "gaps between heads":
+            return torch.cat([x, x + 1], -1)[..., :G]
+        if what == "heads by stride":
+            return x.transpose(1, 2).contiguous().transpose(1, 2)
+        if what == "unaligned":
+            return torch.cat([torch.zeros(3), x.flatten()])[3:].view(x.shape)
+        if what == "odd batch stride":
+            return torch.cat([x.flatten(1), torch.zeros(batch, 1)], 1)[:, :-1].view(x.shape)
+        return x[:, :, :1]
+
+    for mix in (False, True):                            # every tensor, or the first layer's as they are
+        cache = new_cache(layers, batch, n)
+        src = [tuple(x if mix and l == 0 else source(x) for x in p) for l, p in enumerate(kv)]
+        cache.append([tuple(x[0] for x in p) for p in src] if batch == 1 else src)
+        check(cache, kv, [n] * batch)
