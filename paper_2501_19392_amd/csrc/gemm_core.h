@@ -27,12 +27,21 @@ constexpr int kMainLoopLdsBytes = kStages * kStageBytes;
 // same K order per output element, so they give identical bits.
 constexpr int kGemmThreads = 256;                // the 4-wave shape (stand-alone predictor kernel)
 
-// After the last MFMA of a main loop: its results reach the accumulators 8 passes (32 cycles) later, and vector
-// instructions that read them sooner see old values.  The compiler counts these wait states, but was seen to miss a short
-// path (the branch around an absent bias: the last registers of the accumulators were read too early), so every main
-// loop ends with them spelled out.
-__device__ __forceinline__ void settle_accumulators() {
+// After the last MFMA of a main loop: its results reach the accumulators 8 passes (32 cycles) later, and vector instructions
+// that read them sooner see old values.  The compiler keeps 12 wait states there, but not on every path: where a branch and its
+// other side meet again before the first read, it counts them on one of the two sides only.  Seen with ROCm 7.2 in the scoring
+// kernels of the round-to-nearest backbone on tiles of 32 rows without a bias (fused_tile_kernel<2 or 4, kTileScores, 1, ..>):
+// s_cmp, v_and, s_cbranch, v_mov, s_nop 0 between the last MFMA and the first v_accvgpr_read, 5 states, the longer side being
+// the one that loads the bias.  So every main loop ends with the states spelled out.  An empty asm statement per block takes one
+// of its values first: nothing else keeps the MFMAs, which touch no memory, from sinking past the wait into a later block.
+__device__ __forceinline__ void tie_accumulators(const f32x16& acc) { asm volatile("" ::"v"(acc[0])); }
+template <typename T, int N> __device__ __forceinline__ void tie_accumulators(const T (&acc)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) tie_accumulators(acc[i]);
+}
+template <typename T> __device__ __forceinline__ void settle_accumulators(const T& acc) {
   __builtin_amdgcn_sched_barrier(0);
+  tie_accumulators(acc);
   asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
 }
@@ -245,7 +254,7 @@ __device__ __forceinline__ void gemm_mainloop(unsigned char* lds_base, const bf1
   }
   mma8(f[2], [&](int) {});                           // (nk-1, steps 2 and 3)
   mma8(f[3], [&](int) {});
-  settle_accumulators();
+  settle_accumulators(acc);
 }
 
 }  // namespace aquakv

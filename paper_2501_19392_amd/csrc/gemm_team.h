@@ -246,7 +246,7 @@ __device__ __forceinline__ void gemm_team_mainloop(unsigned char* lds_base, cons
   }
   mma8(f[2], [&](int) {});
   mma8(f[3], [&](int) {});
-  settle_accumulators();
+  settle_accumulators(acc);
 }
 
 }  // namespace aquakv

@@ -198,7 +198,7 @@ __device__ __forceinline__ void TileLoop<MB>::run(unsigned char* lds_base, const
     cur = nxt; nxt = step(nxt);
   }
   tile(t, cur, nxt, false, false, false);
-  settle_accumulators();
+  settle_accumulators(acc);
 }
 
 }  // namespace aquakv

@@ -168,7 +168,7 @@ __device__ __forceinline__ void gemm_mainloop_token_slab(unsigned char* lds_base
   }
   // the repeated loads of the last steps may still be on their way into the rings, which the caller is about to reuse
   __builtin_amdgcn_s_waitcnt(0x0f70);
-  settle_accumulators();
+  settle_accumulators(acc);
 }
 
 }  // namespace aquakv

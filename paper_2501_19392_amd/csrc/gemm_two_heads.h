@@ -168,7 +168,7 @@ __device__ __forceinline__ void gemm_mainloop_two_heads(unsigned char* lds_base,
   tile(t, cur, true, false);                               // the last two tiles: nothing left to load
   cur ^= kStage2Bytes;
   tile(t + 1, cur, false, false);
-  settle_accumulators();
+  settle_accumulators(acc);
 }
 
 }  // namespace aquakv
