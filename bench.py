@@ -638,7 +638,7 @@ def stage_rooflines(B, layers, Ks, Vs, buf, q, T, q_heads, reps):
             prev = (Kh, Vh)
 
     flops = sum(2.0 * T * D * (lay.c.d_in_k + lay.c.d_in_v) for lay in layers[1:])
-    two = B.aquakv_fused_tile_heads(lay1, T) == 2
+    two = B.aquakv_fused_tile_heads(lay1, T) == 2       # (the configurations here are ranges that do run on the 256-row tiles)
     ms = timed(lambda: sweep("encode"), reps)
     fused_wide = wide and getattr(B, "WIDE_ENCODE_FUSED", False)
     entry("encode (predicted layers)", "predict_bf16_kernel + quantize_kernel (groups across heads)" if wide and not fused_wide

@@ -348,7 +348,9 @@ hipError_t launch(int n_codewords, const void* x0, int d0, const void* x1, int d
 // 4096 tokens: 20.6 / 28.8 on 128 against 26.1 / 35.  Beyond that 320 rows x one head fill the gap where the tiles of 256
 // rows start a round they hardly use (10007 tokens: 41.1 / 57.8 us against 45.6 / 62.4; 20000 tokens: 81 / 115 against
 // 87 / 122): taken when its rounds cost less, a round being 41 us on 320 rows, 29 us on 256 rows (33 the first) and 54 us on
-// 256 rows x two heads (K = 1024, encode; decode has the same proportions).
+// 256 rows x two heads (K = 1024, encode).  Decode has the same proportions, keys and values together, against tiles of 256 rows:
+// 1024 tokens 21.7 us (43.1), 2048 26.2 (43.5), 4096 40.1 (45.5), 10240 75.6 (80.4), 18000 139.5 (161.2); so have the scoring
+// calls (18.2 against 23.7 us at 4096) and fewer heads (1, 2, 4: no size from 4000 rows on was slower than on 256 rows).
 int tile_rows(int64_t n_seq, int64_t seq_len, int D, bool two_heads) {
   constexpr int64_t kCUs = 256;                      // MI355X
   const int64_t H = D / BN;
