@@ -28,7 +28,8 @@ def plain_attention(q, K, V, scale, rope):
     ("bf16", 8, 32, 4, 16, [63, 64, 65, 5], (), True), ("bf16", 8, 8, 4, 16, [128, 129, 1, 191], (1,), False),
     ("fp32", 2, 16, 0, 8, [64, 72, 9], (0,), True), ("bf16", 2, 2, 3, 100, [100, 320, 17], (), True),
     ("bf16", 1, 3, 2, 6, [8 + i % 25 for i in range(70)], (), True), ("bf16", 4, 20, 4, 16, [260], (2,), True),
-    ("bf16", 8, 64, 4, 32, [4 + 64 + 7] * 3, (), False), ("fp32", 1, 8, 4, 8, [3], (), False)])
+    ("bf16", 8, 64, 4, 32, [4 + 64 + 7] * 3, (), False), ("fp32", 1, 8, 4, 8, [3], (), False),
+    ("bf16", 2, 34, 4, 16, [150, 20], (), True)])                  # 17 query heads per kv head: in passes of 8, 8 and 1
 def test_attend_over_ragged_caches(dtype, H, QH, sinks, recent, lengths, raw_layers, rope):
     from paper_2501_19392_amd.cache import AquaKVCache
     print(f"case attend cache dtype={dtype} H={H} QH={QH} sinks={sinks} recent={recent} lengths={lengths[:8]} raw={raw_layers} "
