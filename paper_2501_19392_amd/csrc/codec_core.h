@@ -190,8 +190,8 @@ __device__ __forceinline__ int search_crowded(float y0, float y1, uint32_t low, 
   return slot;
 }
 
-// A lane's 16 codes of c bits are 4c contiguous bytes of the group's little-endian bit string, c / 2 words.
-// Adds the code of sub-vector m (0..15, compile time) to them, given its slot.
+// A lane's 16 codes of c bits are 4c contiguous bytes of the group's little-endian bit string, c / 2 words (8 codes: half of
+// that).  Adds the code of sub-vector m (compile time) to them, given its slot.
 template <int NCW>
 __device__ __forceinline__ void pack_code(uint32_t (&d)[4], int m, int slot) {
   constexpr int c = CodeBits<NCW>::c;
@@ -206,11 +206,22 @@ __device__ __forceinline__ void pack_code(uint32_t (&d)[4], int m, int slot) {
     if (sh + c > 32) d[w + 1] |= (uint32_t)slot >> (32 - sh);
   }
 }
-template <int NCW>
+// N values per lane = c N / 16 code bytes, at position q of the group
+template <int NCW, int N>
 __device__ __forceinline__ void store_codes(uint8_t* __restrict__ codes, int64_t gid, int q, const uint32_t (&d)[4]) {
   constexpr int c = CodeBits<NCW>::c;
-  uint32_t* dst = reinterpret_cast<uint32_t*>(codes + gid * (kGroup / 2 * c / 8) + q * (2 * c));
-  if constexpr (c == 4) {
+  uint8_t* const at = codes + gid * (kGroup / 2 * c / 8) + q * (N / 16 * c);
+  uint32_t* dst = reinterpret_cast<uint32_t*>(at);
+  if constexpr (N == 16 && c == 4) {
+    dst[0] = d[0];
+  } else if constexpr (N == 16 && c == 6) {            // 6 bytes from a multiple of 6: the word among them that is aligned
+    const bool odd = q & 1;
+    *reinterpret_cast<uint32_t*>(at + (odd ? 2 : 0)) = odd ? (d[0] >> 16) | (d[1] << 16) : d[0];
+    *reinterpret_cast<uint16_t*>(at + (odd ? 0 : 4)) = (uint16_t)(odd ? d[0] : d[1]);
+  } else if constexpr (N == 16) {
+    u32x2 v; v.x = d[0]; v.y = d[1];
+    *reinterpret_cast<u32x2*>(dst) = v;
+  } else if constexpr (c == 4) {
     u32x2 v; v.x = d[0]; v.y = d[1];
     *reinterpret_cast<u32x2*>(dst) = v;
   } else if constexpr (c == 6) {
@@ -221,17 +232,17 @@ __device__ __forceinline__ void store_codes(uint8_t* __restrict__ codes, int64_t
   }
 }
 
-// the 4c code bytes of a lane, as loaded into (the first c/2 dwords of) a register quad -> 16 indices
-template <int NCW>
-__device__ __forceinline__ void unpack_codes(const u32x4 raw, int (&idx)[16]) {
+// the code bytes of a lane, as loaded into (the first dwords of) a register quad -> 16 or 8 indices
+template <int NCW, int M>
+__device__ __forceinline__ void unpack_codes(const u32x4 raw, int (&idx)[M]) {
   constexpr int c = CodeBits<NCW>::c;
   const uint32_t d[4] = {raw.x, raw.y, raw.z, raw.w};
   if constexpr (c == 4) {
 #pragma unroll
-    for (int m = 0; m < 16; ++m) idx[m] = (d[m >> 3] >> (4 * (m & 7))) & 15;
+    for (int m = 0; m < M; ++m) idx[m] = (d[m >> 3] >> (4 * (m & 7))) & 15;
   } else if constexpr (c == 6) {
 #pragma unroll
-    for (int m = 0; m < 16; ++m) {
+    for (int m = 0; m < M; ++m) {
       const int bit = 6 * m, w = bit >> 5, sh = bit & 31;
       uint32_t x = d[w] >> sh;
       if (sh > 26) x |= d[w + 1] << (32 - sh);
@@ -239,7 +250,7 @@ __device__ __forceinline__ void unpack_codes(const u32x4 raw, int (&idx)[16]) {
     }
   } else {
 #pragma unroll
-    for (int m = 0; m < 16; ++m) idx[m] = (d[m >> 2] >> (8 * (m & 3))) & 255;
+    for (int m = 0; m < M; ++m) idx[m] = (d[m >> 2] >> (8 * (m & 3))) & 255;
   }
 }
 
@@ -247,11 +258,12 @@ __device__ __forceinline__ float half_bits_to_float(uint16_t h) {
   return static_cast<float>(__builtin_bit_cast(_Float16, h));
 }
 
-// indices of the lane's 16 grid points -> the points times `scale` (recon_scale(sigma16, lane): the input of the inverse
+// indices of the lane's grid points -> the points times `scale` (recon_scale(sigma16, lane): the input of the inverse
 // transform)
-__device__ __forceinline__ void gather_zhat(const int (&idx)[16], float scale, const float4* cb, float (&z)[32]) {
+template <int M>
+__device__ __forceinline__ void gather_zhat(const int (&idx)[M], float scale, const float4* cb, float (&z)[2 * M]) {
 #pragma unroll
-  for (int m = 0; m < 16; ++m) {
+  for (int m = 0; m < M; ++m) {
     const float4 cw = cb[idx[m]];
     z[2 * m] = cw.x * scale;
     z[2 * m + 1] = cw.y * scale;
@@ -304,15 +316,17 @@ template <int THREADS> struct TableRegs {
 // lo = min(0, min r), hi = max(0, max r), step = (hi - lo) / (2^b - 1) stored as fp16, zero = round(-lo / step),
 // code = clamp(round(r / step) + zero, 0, 2^b - 1) with the stored step, rounding half to even.  Stored per
 // group: (fp16 step, 16-bit zero point), i.e. `scales` holds two uint16 per group, [T, H, 2 groups, 2].
-// Codes: b bits per value in channel order, little-endian: the lane's 32 values are 4b contiguous bytes.
-template <int BITS>
-__device__ __forceinline__ void rtn_store_codes(uint8_t* __restrict__ codes, int64_t gid, int q, const uint32_t (&code)[32]) {
-  uint32_t* dst = reinterpret_cast<uint32_t*>(codes + gid * (kGroup * BITS / 8) + q * (4 * BITS));
-  constexpr int kPerWord = 32 / BITS;
-  uint32_t d[BITS] = {};
+// Codes: b bits per value in channel order, little-endian: the lane's N values are N b / 8 contiguous bytes.
+template <int BITS, int N>
+__device__ __forceinline__ void rtn_store_codes(uint8_t* __restrict__ codes, int64_t gid, int q, const uint32_t (&code)[N]) {
+  uint32_t* dst = reinterpret_cast<uint32_t*>(codes + gid * (kGroup * BITS / 8) + q * (N / 8 * BITS));
+  constexpr int kPerWord = 32 / BITS, kWords = N / kPerWord;
+  uint32_t d[kWords] = {};
 #pragma unroll
-  for (int r = 0; r < 32; ++r) d[r / kPerWord] |= code[r] << (BITS * (r % kPerWord));
-  if constexpr (BITS == 2) {
+  for (int r = 0; r < N; ++r) d[r / kPerWord] |= code[r] << (BITS * (r % kPerWord));
+  if constexpr (kWords == 1) {
+    dst[0] = d[0];
+  } else if constexpr (kWords == 2) {
     u32x2 v; v.x = d[0]; v.y = d[1];
     *reinterpret_cast<u32x2*>(dst) = v;
   } else {
@@ -321,42 +335,43 @@ __device__ __forceinline__ void rtn_store_codes(uint8_t* __restrict__ codes, int
   }
 }
 
-// the lane's code bytes (first BITS dwords of `raw`) and its group's (step, zero) word -> p + (code - zero) * step
-template <int BITS>
-__device__ __forceinline__ void rtn_reconstruct(const u32x4 raw, uint32_t meta, const float (&p)[32], float (&v)[32]) {
+// the lane's code bytes (first dwords of `raw`) and its group's (step, zero) word -> p + (code - zero) * step
+template <int BITS, int N>
+__device__ __forceinline__ void rtn_reconstruct(const u32x4 raw, uint32_t meta, const float (&p)[N], float (&v)[N]) {
   const uint32_t d[4] = {raw.x, raw.y, raw.z, raw.w};
   constexpr int kPerWord = 32 / BITS;
   const float s16 = half_bits_to_float((uint16_t)(meta & 0xffffu));
   const int zero = (int)(meta >> 16);
 #pragma unroll
-  for (int r = 0; r < 32; ++r) {
+  for (int r = 0; r < N; ++r) {
     const int code = (int)((d[r / kPerWord] >> (BITS * (r % kPerWord))) & ((1u << BITS) - 1u));
     v[r] = __fmaf_rn((float)(code - zero), s16, p[r]);     // the product is exact: small integer x fp16
   }
 }
 
 // the (step, zero) word of the lane's group: two groups of 64 per head, or (WIDE, 8 heads) one group per token
-template <bool WIDE = false>
+template <bool WIDE = false, int N = 32>
 __device__ __forceinline__ uint32_t rtn_load_meta(const uint16_t* __restrict__ scales, int64_t gid, int q) {
-  return reinterpret_cast<const uint32_t*>(scales)[WIDE ? gid >> 3 : gid * 2 + (q >> 1)];
+  return reinterpret_cast<const uint32_t*>(scales)[WIDE ? gid >> 3 : gid * 2 + q / (64 / N)];
 }
 
-// Q of the residuals of the 32 values this lane holds of head group gid; same contract as quantize_residual below
-// (`l`: lane % 4, or with WIDE lane % 32: the group is then the whole token of 8 heads, one (step, zero) per token).
-template <int BITS, bool WIDE = false>
-__device__ __forceinline__ void rtn_quantize_residual(float (&v)[32], int l, bool active, int64_t gid,
+// Q of the residuals of the N values this lane holds of head group gid; same contract as quantize_residual below
+// (`l`: group_pos, or with WIDE lane % 32: the group is then the whole token of 8 heads, one (step, zero) per token).
+template <int BITS, bool WIDE = false, int N>
+__device__ __forceinline__ void rtn_quantize_residual(float (&v)[N], int l, bool active, int64_t gid,
                                                       uint8_t* __restrict__ codes, uint16_t* __restrict__ scales,
                                                       bool want_hat) {
-  const int q = l & 3;
+  const int q = WIDE ? l & 3 : l;
   constexpr float kTop = (float)((1 << BITS) - 1);
   float lo = 0.f, hi = 0.f;
 #pragma unroll
-  for (int r = 0; r < 32; ++r) {
+  for (int r = 0; r < N; ++r) {
     lo = fminf(lo, v[r]);
     hi = fmaxf(hi, v[r]);
   }
   lo = fminf(lo, quad_xor<1>(lo));
   hi = fmaxf(hi, quad_xor<1>(hi));
+  if constexpr (N == 16) { lo = fminf(lo, quad_xor<2>(lo)); hi = fmaxf(hi, quad_xor<2>(hi)); }
   if constexpr (WIDE) {
     lo = fminf(lo, quad_xor<2>(lo));    hi = fmaxf(hi, quad_xor<2>(hi));
     lo = fminf(lo, swizzle_xor<4>(lo)); hi = fmaxf(hi, swizzle_xor<4>(hi));
@@ -369,9 +384,9 @@ __device__ __forceinline__ void rtn_quantize_residual(float (&v)[32], int l, boo
   const bool ok = s16 > 0.f;
   const float inv = ok ? __fdiv_rn(1.0f, s16) : 0.f;
   const float zf = ok ? __builtin_amdgcn_fmed3f(__builtin_rintf(__fdiv_rn(-lo, s16)), 0.f, kTop) : 0.f;
-  uint32_t code[32];
+  uint32_t code[N];
 #pragma unroll
-  for (int r = 0; r < 32; ++r)
+  for (int r = 0; r < N; ++r)
     code[r] = (uint32_t)__builtin_amdgcn_fmed3f(__builtin_rintf(v[r] * inv) + zf, 0.f, kTop);
   if (active) {
     rtn_store_codes<BITS>(codes, gid, q, code);
@@ -379,25 +394,25 @@ __device__ __forceinline__ void rtn_quantize_residual(float (&v)[32], int l, boo
     if constexpr (WIDE) {
       if (l == 0) reinterpret_cast<uint32_t*>(scales)[gid >> 3] = word;
     } else {
-      if ((q & 1) == 0) reinterpret_cast<uint32_t*>(scales)[gid * 2 + (q >> 1)] = word;
+      if (q % (64 / N) == 0) reinterpret_cast<uint32_t*>(scales)[gid * 2 + q / (64 / N)] = word;
     }
   }
   if (want_hat) {
 #pragma unroll
-    for (int r = 0; r < 32; ++r) v[r] = ((float)code[r] - zf) * s16;     // exact: small integer x fp16
+    for (int r = 0; r < N; ++r) v[r] = ((float)code[r] - zf) * s16;     // exact: small integer x fp16
   }
 }
 
 // ------------------------------------------------------------------ group bodies
-// Q of the residuals v = x - p of the 32 coordinates this lane holds of head group `gid` (= token * H + head).  On exit
+// Q of the residuals v = x - p of the N coordinates this lane holds of head group `gid` (= token * H + head).  On exit
 // v holds, if `want_hat`, what finish_hat turns into the (unrounded) reconstruction p + Q^-1(codes).  Codes and the
 // scale are stored when `active` (inactive lanes only keep the cross-lane exchanges in step).
-// `l` is the lane's index inside its rotation group: lane % 4 for groups of 128 (WIDE = false, one
+// `l` is the lane's position inside its rotation group: group_pos for groups of 128 (WIDE = false, one
 // scale per head group), lane % 32 for groups of 1024 = the whole token (WIDE = true, kv_heads = 8, one
 // scale per token at scales[gid / 8]).  The code bytes have the same layout in both cases.
 // BATCH: sub-vectors searched together.
-template <int NCW, bool WIDE = false, int BATCH = 4>
-__device__ __forceinline__ void quantize_residual(float (&v)[32], const float (&sf)[32], int l, const float4* cb,
+template <int NCW, bool WIDE = false, int BATCH = 4, int N>
+__device__ __forceinline__ void quantize_residual(float (&v)[N], const float (&sf)[N], int l, const float4* cb,
                                                   const uint32_t* table, bool active, int64_t gid,
                                                   uint8_t* __restrict__ codes, uint16_t* __restrict__ scales, bool want_hat) {
   if constexpr (is_rtn(NCW)) {
@@ -405,14 +420,11 @@ __device__ __forceinline__ void quantize_residual(float (&v)[32], const float (&
     return;
   }
 #pragma unroll
-  for (int r = 0; r < 32; ++r) v[r] *= sf[r];                                             // s * (x - p), exact product
-  const int q = l & 3;
+  for (int r = 0; r < N; ++r) v[r] *= sf[r];                                             // s * (x - p), exact product
+  const int q = WIDE ? l & 3 : l;
   Rot<WIDE>::wht(v, l);                                   // w = +-H u (unnormalised, lane sign pending)
 
-  float ss = 0.f;
-#pragma unroll
-  for (int r = 0; r < 32; ++r) ss = __fmaf_rn(v[r], v[r], ss);
-  ss = Rot<WIDE>::sum(ss);
+  const float ss = Rot<WIDE>::square_sum(v, l);
   // z = w / sqrt(g)  =>  rms(z) = sqrt(sum w^2) / g
   float sigma = __fsqrt_rn(ss) * Rot<WIDE>::kInvG;
   sigma = fminf(sigma, 65504.0f);
@@ -426,7 +438,7 @@ __device__ __forceinline__ void quantize_residual(float (&v)[32], const float (&
   const float rs = recon_scale<WIDE>(s16, l);
   uint32_t words[4] = {0, 0, 0, 0};
 #pragma unroll
-  for (int m0 = 0; m0 < 16; m0 += BATCH) {
+  for (int m0 = 0; m0 < N / 2; m0 += BATCH) {
     float y[2 * BATCH];
 #pragma unroll
     for (int i = 0; i < 2 * BATCH; ++i) y[i] = v[2 * m0 + i] * inv;
@@ -481,24 +493,24 @@ __device__ __forceinline__ void quantize_residual(float (&v)[32], const float (&
     }
   }
   if (active) {
-    store_codes<NCW>(codes, gid, q, words);
+    store_codes<NCW, N>(codes, gid, q, words);
     if (l == 0) scales[WIDE ? gid >> 3 : gid] = __builtin_bit_cast(uint16_t, s16h);
   }
   if (want_hat) Rot<WIDE>::iwht(v, l);
 }
 // the reconstruction from quantize_residual's v and the prediction
-template <int NCW>
-__device__ __forceinline__ void finish_hat(float (&v)[32], const float (&sf)[32], const float (&p)[32]) {
+template <int NCW, int N>
+__device__ __forceinline__ void finish_hat(float (&v)[N], const float (&sf)[N], const float (&p)[N]) {
 #pragma unroll
-  for (int r = 0; r < 32; ++r) v[r] = is_rtn(NCW) ? v[r] + p[r] : __fmaf_rn(v[r], sf[r], p[r]);
+  for (int r = 0; r < N; ++r) v[r] = is_rtn(NCW) ? v[r] + p[r] : __fmaf_rn(v[r], sf[r], p[r]);
 }
 // Q(x - p): on entry v = x, on exit p + Q^-1(codes) if `want_hat`
-template <int NCW, bool WIDE = false, int BATCH = 4>
-__device__ __forceinline__ void quantize_group(float (&v)[32], const float (&p)[32], const float (&sf)[32], int l,
+template <int NCW, bool WIDE = false, int BATCH = 4, int N>
+__device__ __forceinline__ void quantize_group(float (&v)[N], const float (&p)[N], const float (&sf)[N], int l,
                                                const float4* cb, const uint32_t* table, bool active, int64_t gid,
                                                uint8_t* __restrict__ codes, uint16_t* __restrict__ scales, bool want_hat) {
 #pragma unroll
-  for (int r = 0; r < 32; ++r) v[r] -= p[r];
+  for (int r = 0; r < N; ++r) v[r] -= p[r];
   quantize_residual<NCW, WIDE, BATCH>(v, sf, l, cb, table, active, gid, codes, scales, want_hat);
   if (want_hat) finish_hat<NCW>(v, sf, p);
 }
@@ -506,13 +518,25 @@ __device__ __forceinline__ void quantize_group(float (&v)[32], const float (&p)[
 // the lane's share of a group's codes (and of its scales) as the kernels hold them between request and use
 struct CodeWords { u32x4 code; uint32_t scale; };   // scale: fp16 bits (grids) or (step, zero point) (round-to-nearest)
 
-// requests the code bytes of quad position q of group gid (4 c bytes: the lane's 16 sub-vectors)
-template <int NCW>
+// requests the code bytes of position q of group gid (c / 4 bytes per sub-vector: the lane's N / 2 sub-vectors)
+template <int NCW, int N = 32>
 __device__ __forceinline__ u32x4 request_codes(const uint8_t* __restrict__ codes, int64_t gid, int q) {
   constexpr int c = CodeBits<NCW>::c;
-  const uint32_t* src = reinterpret_cast<const uint32_t*>(codes + gid * (kGroup / 2 * c / 8) + q * (2 * c));
+  const uint8_t* const at = codes + gid * (kGroup / 2 * c / 8) + q * (N / 16 * c);
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(at);
   u32x4 out = {0, 0, 0, 0};
-  if constexpr (c == 4) {
+  if constexpr (N == 16 && c == 4) {
+    out.x = src[0];
+  } else if constexpr (N == 16 && c == 6) {            // 6 bytes from a multiple of 6, whose 2-byte part comes last or first
+    const bool odd = q & 1;
+    const uint32_t w = *reinterpret_cast<const uint32_t*>(at + (odd ? 2 : 0));
+    const uint32_t h = *reinterpret_cast<const uint16_t*>(at + (odd ? 0 : 4));
+    out.x = odd ? h | (w << 16) : w;
+    out.y = odd ? w >> 16 : h;
+  } else if constexpr (N == 16) {
+    const u32x2 v2 = *reinterpret_cast<const u32x2*>(src);
+    out.x = v2.x; out.y = v2.y;
+  } else if constexpr (c == 4) {
     const u32x2 v2 = *reinterpret_cast<const u32x2*>(src);
     out.x = v2.x; out.y = v2.y;
   } else if constexpr (c == 6) {
@@ -523,25 +547,25 @@ __device__ __forceinline__ u32x4 request_codes(const uint8_t* __restrict__ codes
   return out;
 }
 
-// the words of quad position l % 4 of head group gid (WIDE: one scale word per token, at gid / 8)
-template <int NCW, bool WIDE = false>
+// the words of position q of head group gid (WIDE: one scale word per token, at gid / 8)
+template <int NCW, bool WIDE = false, int N = 32>
 __device__ __forceinline__ CodeWords request_words(const uint8_t* __restrict__ codes, const uint16_t* __restrict__ scales,
                                                    int64_t gid, int q) {
   CodeWords w;
-  w.code = request_codes<NCW>(codes, gid, q);
-  if constexpr (is_rtn(NCW)) w.scale = rtn_load_meta<WIDE>(scales, gid, q);
+  w.code = request_codes<NCW, N>(codes, gid, q);
+  if constexpr (is_rtn(NCW)) w.scale = rtn_load_meta<WIDE, N>(scales, gid, q);
   else w.scale = scales[WIDE ? gid >> 3 : gid];
   return w;
 }
 
-// Q^-1(codes) + p from the words requested earlier (unrounded, in v); l: lane % 4, or with WIDE lane % 32
-template <int NCW, bool WIDE = false>
-__device__ __forceinline__ void dequantize_words(const CodeWords& w, const float (&p)[32], const float (&sf)[32], int l,
-                                                 const float4* cb, float (&v)[32]) {
+// Q^-1(codes) + p from the words requested earlier (unrounded, in v); l: group_pos, or with WIDE lane % 32
+template <int NCW, bool WIDE = false, int N>
+__device__ __forceinline__ void dequantize_words(const CodeWords& w, const float (&p)[N], const float (&sf)[N], int l,
+                                                 const float4* cb, float (&v)[N]) {
   if constexpr (is_rtn(NCW)) {
     rtn_reconstruct<NCW>(w.code, w.scale, p, v);
   } else {
-    int idx[16];
+    int idx[N / 2];
     unpack_codes<NCW>(w.code, idx);
     gather_zhat(idx, recon_scale<WIDE>(half_bits_to_float((uint16_t)w.scale), l), cb, v);
     reconstruct<WIDE>(v, l, sf, p);

@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED |
     }
     quantize_group<NCW, WIDE>(v, p, sf, WIDE ? (int)(threadIdx.x & 31) : q, lds.cb, table != nullptr ? lds.table : nullptr,
                               active, gid, codes, scales, Xhat != nullptr);
-    if (Xhat != nullptr && active) Storage<T>::store32(Xhat + off, v);
+    if (Xhat != nullptr && active) Storage<T>::store(Xhat + off, v);
     cur = nxt;
   }
 }
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(const QuantizeIo i
 
     float p[32], z[32];
     if (P != nullptr) {
-      load32_f32(P + off, p);
+      load_f32(P + off, p);
     } else {
 #pragma unroll
       for (int r = 0; r < 32; ++r) p[r] = 0.f;
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(const QuantizeIo i
       if (!fixed_head) load_signs(signs, (int)(gid % H), q, sf);     // (a 64-bit remainder: kept off the common path)
     }
     dequantize_words<NCW, WIDE>(cur, p, sf, WIDE ? (int)(threadIdx.x & 31) : q, cb, z);
-    if (active) Storage<T>::store32(Xhat + off, z);
+    if (active) Storage<T>::store(Xhat + off, z);
     cur = nxt;
   }
 }
@@ -194,7 +194,7 @@ __global__ __launch_bounds__(kThreads) void attn_scores_kernel(
 
     float p[32], z[32];
     if (P != nullptr) {
-      load32_f32(P + off, p);
+      load_f32(P + off, p);
     } else {
 #pragma unroll
       for (int r = 0; r < 32; ++r) p[r] = 0.f;
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(kThreads) void attn_scores_kernel(
     }
     dequantize_words<NCW, WIDE>(cur, p, sf, WIDE ? (int)(threadIdx.x & 31) : q, cb, z);
     cur = nxt;
-    if (Khat_out != nullptr && active) Storage<T>::store32(Khat_out + off, z);
+    if (Khat_out != nullptr && active) Storage<T>::store(Khat_out + off, z);
 #pragma unroll
     for (int r = 0; r < 32; ++r) z[r] = Storage<T>::round(z[r]);      // score the stored keys
     if (rope_cos != nullptr) rope128(z, q, rope_cos + t * (kGroup / 2), rope_sin + t * (kGroup / 2));   // cached before RoPE
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(kThreads) void attn_scores_kernel(
     for (int r = 0; r < rep; ++r) {
       const int qh = head * rep + r;
       float qv[32];
-      Storage<T>::load32(qv_ + ((int64_t)b * q_heads + qh) * kGroup + q * kValsPerLane, qv);
+      Storage<T>::load(qv_ + ((int64_t)b * q_heads + qh) * kGroup + q * kValsPerLane, qv);
       float acc = 0.f;
 #pragma unroll
       for (int i = 0; i < 32; ++i) acc = __fmaf_rn(qv[i], z[i], acc);

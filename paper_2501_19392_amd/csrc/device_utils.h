@@ -8,6 +8,10 @@
 // butterfly stages then run inside a lane and only two cross lanes, both as
 // DPP quad permutes that fold into the add.  Every global access is a 128-bit
 // load/store and the packed codes of a lane are contiguous bytes.
+//
+// Narrow form (tiles of few rows, whose waves would otherwise leave half of a CU idle): a group is held by EIGHT lanes, 16
+// consecutive values each.  The functions below take the lane's values as an array of N = 32 or 16 and do the same operations
+// in the same order per value, so both forms give the same bits.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -29,16 +33,16 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 template <typename T> struct Storage;
 
 template <> struct Storage<float> {
-  static __device__ __forceinline__ void load32(const float* p, float (&v)[32]) {
+  template <int N> static __device__ __forceinline__ void load(const float* p, float (&v)[N]) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
+    for (int c = 0; c < N / 4; ++c) {
       const f32x4 a = reinterpret_cast<const f32x4*>(p)[c];
       v[4 * c] = a.x; v[4 * c + 1] = a.y; v[4 * c + 2] = a.z; v[4 * c + 3] = a.w;
     }
   }
-  static __device__ __forceinline__ void store32(float* p, const float (&v)[32]) {
+  template <int N> static __device__ __forceinline__ void store(float* p, const float (&v)[N]) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
+    for (int c = 0; c < N / 4; ++c) {
       f32x4 a;
       a.x = v[4 * c]; a.y = v[4 * c + 1]; a.z = v[4 * c + 2]; a.w = v[4 * c + 3];
       reinterpret_cast<f32x4*>(p)[c] = a;
@@ -48,9 +52,9 @@ template <> struct Storage<float> {
 };
 
 template <> struct Storage<bf16_t> {
-  static __device__ __forceinline__ void load32(const bf16_t* p, float (&v)[32]) {
+  template <int N> static __device__ __forceinline__ void load(const bf16_t* p, float (&v)[N]) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < N / 8; ++c) {
       const u32x4 r = reinterpret_cast<const u32x4*>(p)[c];
       const uint32_t w[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
@@ -67,9 +71,9 @@ template <> struct Storage<bf16_t> {
     f.x = lo; f.y = hi;
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));   // one packed RNE convert
   }
-  static __device__ __forceinline__ void store32(bf16_t* p, const float (&v)[32]) {
+  template <int N> static __device__ __forceinline__ void store(bf16_t* p, const float (&v)[N]) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < N / 8; ++c) {
       u32x4 r;
       r.x = pack2(v[8 * c], v[8 * c + 1]); r.y = pack2(v[8 * c + 2], v[8 * c + 3]);
       r.z = pack2(v[8 * c + 4], v[8 * c + 5]); r.w = pack2(v[8 * c + 6], v[8 * c + 7]);
@@ -91,7 +95,7 @@ __device__ __forceinline__ void unpack_bf16x8(const u32x4 r, float* v) {
   }
 }
 
-__device__ __forceinline__ void load32_f32(const float* p, float (&v)[32]) { Storage<float>::load32(p, v); }
+template <int N> __device__ __forceinline__ void load_f32(const float* p, float (&v)[N]) { Storage<float>::load(p, v); }
 
 // ---------------------------------------------------------------- cross-lane moves inside a quad
 // Value of `x` held by lane (lane ^ MASK), MASK in {1, 2}: DPP quad_perm.
@@ -109,6 +113,33 @@ __device__ __forceinline__ float quad_sum(float x) {
   return x;
 }
 
+// ---------------------------------------------------------------- eight lanes per group
+// Position (0..7: coordinates 16 pos ... 16 pos + 15) of a lane among the eight of a group.  The upper four lanes hold their
+// blocks in reverse, so that the partner whose position differs in bit 2 is lane ^ 7, which a DPP row_half_mirror reads
+// (there is no control for lane ^ 4); the positions that differ in bits 0 and 1 are lane ^ 1 and lane ^ 2 as in a quad.
+__device__ __forceinline__ int octet_pos(int lane) { return (lane & 7) ^ ((lane & 4) ? 3 : 0); }
+__device__ __forceinline__ float octet_mirror(float x) {      // value of lane ^ 7
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x141 /* row_half_mirror */, 0xF, 0xF, true));
+}
+// Position of `lane` in its group of 4 (N = 32) or 8 (N = 16) lanes.
+template <int N> __device__ __forceinline__ int group_pos(int lane) { return N == 32 ? lane & 3 : octet_pos(lane); }
+
+// sum_r a[r] * b[r] over the group, every lane gets it.  Fixed order, the same for both widths: one chain of multiply-adds over
+// each 32 consecutive coordinates, then the four chains pairwise.  With 16 values per lane the chain passes through two lanes.
+template <int N> __device__ __forceinline__ float group_dot(const float (&a)[N], const float (&b)[N], int pos) {
+  float s = 0.f;
+#pragma unroll
+  for (int r = 0; r < N; ++r) s = __fmaf_rn(a[r], b[r], s);
+  if constexpr (N == 32) return quad_sum(s);
+  float t = quad_xor<1>(s);
+#pragma unroll
+  for (int r = 0; r < N; ++r) t = __fmaf_rn(a[r], b[r], t);
+  const float first = quad_xor<1>(t);
+  t = (pos & 1) ? t : first;
+  t = t + quad_xor<2>(t);
+  return t + octet_mirror(t);
+}
+
 // ---------------------------------------------------------------- 128-point WHT
 // v[r] is coordinate 32*q + r of the group (q = lane % 4).  Unnormalised Sylvester-order
 // transform: coordinate bits 0..4 are butterflied in registers, bits 5..6 across the quad.
@@ -124,28 +155,25 @@ __device__ __forceinline__ float quad_sum(float x) {
 // v_fmac_f32 with a DPP quad permute on its first source (dst += permuted(dst) * s).  A DPP
 // read of a register written by the VALU instruction just before it needs two idle issue
 // slots; the compiler cannot see into the block, so each block of 16 starts with them.
-#define AQUAKV_FMAC_DPP(i, perm) "v_fmac_f32_dpp %" #i ", %" #i ", %16 quad_perm:" perm " row_mask:0xf bank_mask:0xf\n\t"
+#define AQUAKV_FMAC_DPP(i, perm) "v_fmac_f32_dpp %" #i ", %" #i ", %16 " perm " row_mask:0xf bank_mask:0xf\n\t"
 #define AQUAKV_FMAC_DPP16(perm)                                                                               \
   "s_nop 1\n\t" AQUAKV_FMAC_DPP(0, perm) AQUAKV_FMAC_DPP(1, perm) AQUAKV_FMAC_DPP(2, perm) AQUAKV_FMAC_DPP(3, perm)  \
   AQUAKV_FMAC_DPP(4, perm) AQUAKV_FMAC_DPP(5, perm) AQUAKV_FMAC_DPP(6, perm) AQUAKV_FMAC_DPP(7, perm)               \
   AQUAKV_FMAC_DPP(8, perm) AQUAKV_FMAC_DPP(9, perm) AQUAKV_FMAC_DPP(10, perm) AQUAKV_FMAC_DPP(11, perm)             \
   AQUAKV_FMAC_DPP(12, perm) AQUAKV_FMAC_DPP(13, perm) AQUAKV_FMAC_DPP(14, perm) AQUAKV_FMAC_DPP(15, perm)
-template <int MASK> __device__ __forceinline__ void wht_quad_stage(float (&v)[32], float s) {
-  static_assert(MASK == 1 || MASK == 2, "mask");
+#define AQUAKV_FMAC_ARGS                                                                                              \
+  : "+v"(v[b]), "+v"(v[b + 1]), "+v"(v[b + 2]), "+v"(v[b + 3]), "+v"(v[b + 4]), "+v"(v[b + 5]), "+v"(v[b + 6]),        \
+    "+v"(v[b + 7]), "+v"(v[b + 8]), "+v"(v[b + 9]), "+v"(v[b + 10]), "+v"(v[b + 11]), "+v"(v[b + 12]),                 \
+    "+v"(v[b + 13]), "+v"(v[b + 14]), "+v"(v[b + 15])                                                                  \
+  : "v"(s)
+// MASK 1, 2: partner lane ^ MASK; 7: lane ^ 7
+template <int MASK, int N> __device__ __forceinline__ void wht_lane_stage(float (&v)[N], float s) {
+  static_assert((MASK == 1 || MASK == 2 || MASK == 7) && N % 16 == 0, "mask");
 #pragma unroll
-  for (int b = 0; b < 32; b += 16) {
-    if constexpr (MASK == 1)
-      asm(AQUAKV_FMAC_DPP16("[1,0,3,2]")
-          : "+v"(v[b]), "+v"(v[b + 1]), "+v"(v[b + 2]), "+v"(v[b + 3]), "+v"(v[b + 4]), "+v"(v[b + 5]), "+v"(v[b + 6]),
-            "+v"(v[b + 7]), "+v"(v[b + 8]), "+v"(v[b + 9]), "+v"(v[b + 10]), "+v"(v[b + 11]), "+v"(v[b + 12]),
-            "+v"(v[b + 13]), "+v"(v[b + 14]), "+v"(v[b + 15])
-          : "v"(s));
-    else
-      asm(AQUAKV_FMAC_DPP16("[2,3,0,1]")
-          : "+v"(v[b]), "+v"(v[b + 1]), "+v"(v[b + 2]), "+v"(v[b + 3]), "+v"(v[b + 4]), "+v"(v[b + 5]), "+v"(v[b + 6]),
-            "+v"(v[b + 7]), "+v"(v[b + 8]), "+v"(v[b + 9]), "+v"(v[b + 10]), "+v"(v[b + 11]), "+v"(v[b + 12]),
-            "+v"(v[b + 13]), "+v"(v[b + 14]), "+v"(v[b + 15])
-          : "v"(s));
+  for (int b = 0; b < N; b += 16) {
+    if constexpr (MASK == 1) asm(AQUAKV_FMAC_DPP16("quad_perm:[1,0,3,2]") AQUAKV_FMAC_ARGS);
+    else if constexpr (MASK == 2) asm(AQUAKV_FMAC_DPP16("quad_perm:[2,3,0,1]") AQUAKV_FMAC_ARGS);
+    else asm(AQUAKV_FMAC_DPP16("row_half_mirror") AQUAKV_FMAC_ARGS);
   }
 }
 
@@ -155,12 +183,13 @@ __device__ __forceinline__ float quad_sign(int q) { return (q == 1 || q == 2) ? 
 // (Rot::sign; free when the input is built with a per-lane scale anyway); with s = -1 on the lower and +1 on the upper
 // lane of a cross-lane stage, v + s * partner is then the true butterfly on both lanes, (-a) + s (-b) being -(a + s b)
 // exactly, and nothing is left pending on the output.
-template <bool INV = false> __device__ __forceinline__ void wht128(float (&v)[32], int q) {
+// q: the lane's position in its group (group_pos).
+template <bool INV = false, int N> __device__ __forceinline__ void wht128(float (&v)[N], int q) {
   constexpr float up = INV ? 1.0f : -1.0f;               // s on the lane that holds the 1-bit
 #pragma unroll
-  for (int h = 1; h < 32; h <<= 1) {
+  for (int h = 1; h < N; h <<= 1) {
 #pragma unroll
-    for (int r = 0; r < 32; ++r) {
+    for (int r = 0; r < N; ++r) {
       if ((r & h) == 0) {
         const float a = v[r], b = v[r + h];
         v[r] = a + b;
@@ -168,8 +197,9 @@ template <bool INV = false> __device__ __forceinline__ void wht128(float (&v)[32
       }
     }
   }
-  wht_quad_stage<1>(v, (q & 1) ? up : -up);
-  wht_quad_stage<2>(v, (q & 2) ? up : -up);
+  wht_lane_stage<1>(v, (q & 1) ? up : -up);
+  wht_lane_stage<2>(v, (q & 2) ? up : -up);
+  if constexpr (N == 16) wht_lane_stage<7>(v, (q & 4) ? up : -up);
 }
 
 // ---------------------------------------------------------------- 1024-point WHT (rotation group = whole token)
@@ -209,32 +239,38 @@ __device__ __forceinline__ float token_sum(float x) {
 template <bool WIDE> struct Rot {
   static constexpr float kNorm = WIDE ? 0.03125f : kRsqrtG;            // 1 / sqrt(g)
   static constexpr float kInvG = WIDE ? 1.0f / 1024 : 1.0f / kGroup;
-  static __device__ __forceinline__ void wht(float (&v)[32], int l) {
-    wht128(v, l & 3);
+  template <int N> static __device__ __forceinline__ void wht(float (&v)[N], int l) {
+    static_assert(!WIDE || N == 32, "groups across the heads: 32 values per lane");
+    wht128(v, WIDE ? l & 3 : l);
     if constexpr (WIDE) wht1024_tail(v, l);
   }
   // The same transform (H_8 (x) H_128 is symmetric) with the stages across the heads first, used for the inverse:
   // a kernel that holds one head of a token per quad and fetches the other heads' grid points itself can then
   // reproduce it bit for bit by adding the 8 heads in the same tree, ((0 1)(2 3))((4 5)(6 7)), before its own wht128.
   // Inverse-side convention (see wht128): input pre-multiplied by sign(l), true output.
-  static __device__ __forceinline__ void iwht(float (&v)[32], int l) {
+  template <int N> static __device__ __forceinline__ void iwht(float (&v)[N], int l) {
     if constexpr (WIDE) wht1024_tail<true>(v, l);
-    wht128<true>(v, l & 3);
+    wht128<true>(v, WIDE ? l & 3 : l);
   }
   // sign pending on the lane's values after wht(): -1 for every cross-lane stage in which the lane was the upper one
-  static __device__ __forceinline__ float sign(int l) {
-    const int bits = WIDE ? (l & 31) : (l & 3);
-    return (__builtin_popcount(bits) & 1) ? -1.0f : 1.0f;
+  // (`l` has one bit per stage)
+  static __device__ __forceinline__ float sign(int l) { return (__builtin_popcount(l) & 1) ? -1.0f : 1.0f; }
+  // sum of the squares of the group's values
+  template <int N> static __device__ __forceinline__ float square_sum(const float (&v)[N], int l) {
+    if constexpr (!WIDE) return group_dot(v, v, l);
+    float ss = 0.f;
+#pragma unroll
+    for (int r = 0; r < N; ++r) ss = __fmaf_rn(v[r], v[r], ss);
+    return token_sum(ss);
   }
-  static __device__ __forceinline__ float sum(float x) { return WIDE ? token_sum(x) : quad_sum(x); }
 };
 
-// the 32 RHT signs this lane needs as +-1.0f: multiplying by them is exact, so s * x costs one multiplication and
+// the RHT signs this lane needs as +-1.0f: multiplying by them is exact, so s * x costs one multiplication and
 // s * w + p one fused multiply-add that rounds exactly like the addition p +- w
-__device__ __forceinline__ void load_signs(const int8_t* signs, int head, int q, float (&sf)[32]) {
-  const u32x4* src = reinterpret_cast<const u32x4*>(signs + head * kGroup + q * kValsPerLane);
+template <int N> __device__ __forceinline__ void load_signs(const int8_t* signs, int head, int q, float (&sf)[N]) {
+  const u32x4* src = reinterpret_cast<const u32x4*>(signs + head * kGroup + q * N);
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
+  for (int c = 0; c < N / 16; ++c) {
     const u32x4 raw = src[c];
     const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
@@ -255,25 +291,29 @@ template <bool WIDE = false> __device__ __forceinline__ float recon_scale(float 
   return s16 * (Rot<WIDE>::sign(l) * Rot<WIDE>::kNorm);
 }
 // z: grid points scaled by recon_scale (rotated domain) -> p + Q^-1(codes)
-template <bool WIDE = false>
-__device__ __forceinline__ void reconstruct(float (&z)[32], int l, const float (&sf)[32], const float (&p)[32]) {
+template <bool WIDE = false, int N>
+__device__ __forceinline__ void reconstruct(float (&z)[N], int l, const float (&sf)[N], const float (&p)[N]) {
   Rot<WIDE>::iwht(z, l);
 #pragma unroll
-  for (int r = 0; r < 32; ++r) z[r] = __fmaf_rn(z[r], sf[r], p[r]);
+  for (int r = 0; r < N; ++r) z[r] = __fmaf_rn(z[r], sf[r], p[r]);
 }
 
-// Rotary embedding (RoFormer) of the 32 coordinates this lane holds of a 128-long head vector.  Coordinate d is
-// paired with d + 64, which is the same register of lane q ^ 2; `cos_t` / `sin_t` point at the 64 angles of the
-// token's position.  x'_d = x_d cos - x_{d+64} sin,  x'_{d+64} = x_{d+64} cos + x_d sin.
-__device__ __forceinline__ void rope128(float (&v)[32], int q, const float* __restrict__ cos_t,
+// Rotary embedding (RoFormer) of the coordinates this lane holds of a 128-long head vector.  Coordinate d is
+// paired with d + 64, which is the same register of the lane whose position differs in the uppermost bit; `cos_t` / `sin_t`
+// point at the 64 angles of the token's position.  x'_d = x_d cos - x_{d+64} sin,  x'_{d+64} = x_{d+64} cos + x_d sin.
+template <int N>
+__device__ __forceinline__ void rope128(float (&v)[N], int q, const float* __restrict__ cos_t,
                                         const float* __restrict__ sin_t) {
-  float c[32], s[32];
-  load32_f32(cos_t + 32 * (q & 1), c);
-  load32_f32(sin_t + 32 * (q & 1), s);
-  const float sgn = (q & 2) ? 1.0f : -1.0f;
+  constexpr int kUpper = 64 / N;                         // the position's uppermost bit
+  float c[N], s[N];
+  load_f32(cos_t + N * (q & (kUpper - 1)), c);
+  load_f32(sin_t + N * (q & (kUpper - 1)), s);
+  const float sgn = (q & kUpper) ? 1.0f : -1.0f;
 #pragma unroll
-  for (int r = 0; r < 32; ++r) {
-    const float partner = quad_xor<2>(v[r]);
+  for (int r = 0; r < N; ++r) {
+    float partner;
+    if constexpr (N == 32) partner = quad_xor<2>(v[r]);
+    else partner = octet_mirror(v[r]);
     v[r] = __fmaf_rn(v[r], c[r], sgn * (partner * s[r]));
   }
 }

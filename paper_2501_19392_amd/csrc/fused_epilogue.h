@@ -13,9 +13,11 @@ constexpr int kLdP = kGroup + 4;                    // padded fp32 row of a park
 // its k-th load; q and q+2 would be 128 B = half the banks apart and collide with the next
 // rows, so the upper half of the row has its slots XOR-ed by 4: the 16 lanes served together
 // (4 rows x 4 lanes) then touch all 64 banks once.
-__device__ __forceinline__ constexpr int park_col(int col) {
+// With eight lanes per group (N = 16) lane q reads slots 4q + k: a row's 8 lanes fall on every fourth slot of the banks twice,
+// and the other row the 16 lanes come from one slot further, so there the upper half is XOR-ed by 2.
+template <int N = 32> __device__ __forceinline__ constexpr int park_col(int col) {
   const int slot = col >> 2;
-  return (((slot & 16) ? (slot ^ 4) : slot) << 2) | (col & 3);
+  return (((slot & 16) ? (slot ^ (N == 32 ? 4 : 2)) : slot) << 2) | (col & 3);
 }
 
 // One 32 x 128 block of a wave's accumulators (+ bias) -> rows 0..31 at `dst` (row stride kLdP floats).  acc[j]: the
@@ -31,37 +33,37 @@ __device__ __forceinline__ void park_block(float* dst, const f32x16 (&acc)[4], c
     }
 }
 
-// the 32 predictions of quad position q of a parked row
-__device__ __forceinline__ void read_parked(const float* rowp, int q, float (&p)[32]) {
+// the N predictions of position q of a parked row
+template <int N> __device__ __forceinline__ void read_parked(const float* rowp, int q, float (&p)[N]) {
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const f32x4 a = *reinterpret_cast<const f32x4*>(rowp + park_col(q * kValsPerLane + 4 * k));
+  for (int k = 0; k < N / 4; ++k) {
+    const f32x4 a = *reinterpret_cast<const f32x4*>(rowp + park_col<N>(q * N + 4 * k));
     p[4 * k] = a.x; p[4 * k + 1] = a.y; p[4 * k + 2] = a.z; p[4 * k + 3] = a.w;
   }
 }
 
-// Rotation groups of 1024 = the whole token of 8 heads (Sect. 4.1), decoded by a quad that holds ONE head of the token:
-// the code words of the lane's 16 sub-vector slots in each of the 8 heads ...
+// Rotation groups of 1024 = the whole token of 8 heads (Sect. 4.1), decoded by the lanes that hold ONE head of the token:
+// the code words of the lane's N / 2 sub-vector slots in each of the 8 heads ...
 template <int NCW> struct WideCodes { u32x4 h[8]; };
-template <int NCW>
+template <int NCW, int N = 32>
 __device__ __forceinline__ void request_wide_codes(const uint8_t* __restrict__ codes, int64_t row, int q, WideCodes<NCW>& wc) {
 #pragma unroll
-  for (int hh = 0; hh < 8; ++hh) wc.h[hh] = request_codes<NCW>(codes, row * 8 + hh, q);
+  for (int hh = 0; hh < 8; ++hh) wc.h[hh] = request_codes<NCW, N>(codes, row * 8 + hh, q);
 }
 // ... and Q^-1 + p from them (grids): the grid points of the 8 heads, added as the stages across the heads of the
 // 1024-point transform add them for head `head`, ((0 +- 1) +- (2 +- 3)) +- ((4 +- 5) +- (6 +- 7)), minus where the
 // head's bit of that level is set (the tree of Rot<true>::iwht, so the same bits as the stand-alone kernels), then the
-// quad's own 128-point stages, sign and prediction.  scale_word: the token's fp16 scale.
-template <int NCW>
+// head's own 128-point stages, sign and prediction.  scale_word: the token's fp16 scale.
+template <int NCW, int N>
 __device__ __forceinline__ void dequantize_across_heads(const WideCodes<NCW>& wc, uint32_t scale_word, int head, int q,
-                                                        const float (&p)[32], const float (&sf)[32], const float4* cb,
-                                                        float (&v)[32]) {
-  const float s16 = recon_scale<true>(half_bits_to_float((uint16_t)scale_word), q);   // the quad's two lane bits only
+                                                        const float (&p)[N], const float (&sf)[N], const float4* cb,
+                                                        float (&v)[N]) {
+  const float s16 = recon_scale<true>(half_bits_to_float((uint16_t)scale_word), q);   // the stages inside the head only
   const float g0 = (head & 1) ? -1.0f : 1.0f, g1 = (head & 2) ? -1.0f : 1.0f, g2 = (head & 4) ? -1.0f : 1.0f;
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
+  for (int half = 0; half < N / 16; ++half) {
     const auto zhat_half = [&](int hh, float (&z)[16]) {
-      int idx[16];
+      int idx[N / 2];
       unpack_codes<NCW>(wc.h[hh], idx);
 #pragma unroll
       for (int m = 0; m < 8; ++m) {
@@ -91,10 +93,10 @@ __device__ __forceinline__ void dequantize_across_heads(const WideCodes<NCW>& wc
   }
   wht128<true>(v, q);
 #pragma unroll
-  for (int r = 0; r < 32; ++r) v[r] = __fmaf_rn(v[r], sf[r], p[r]);
+  for (int r = 0; r < N; ++r) v[r] = __fmaf_rn(v[r], sf[r], p[r]);
 }
 
-// Grouped-query scores of one decoded key row of kv head `head` (the quad's 4 x 32 values in v, unrounded):
+// Grouped-query scores of one decoded key row of kv head `head` (the lanes of the group hold its 128 values in v, unrounded):
 //   scores[b, qh, t] = score_scale * sum_d q[b, qh, d] * round_bf16(v)[d]   for the q_heads / H query heads of the head,
 // the key rotated by its position t first when rope_cos is given (caches that hold keys from before the rotary
 // embedding, Sect. 3.3).  The row is token t of sequence b.
@@ -130,31 +132,29 @@ struct QueryStage {
   }
 };
 
-__device__ __forceinline__ void score_row(float (&v)[32], int q, int head, int H, int q_heads, int64_t b, int64_t t,
+template <int N>
+__device__ __forceinline__ void score_row(float (&v)[N], int q, int head, int H, int q_heads, int64_t b, int64_t t,
                                           int seq_len, bool active, const bf16_t* __restrict__ qv, float score_scale,
                                           float* __restrict__ scores, const float* __restrict__ rope_cos,
                                           const float* __restrict__ rope_sin, const float* q_lds = nullptr) {
 #pragma unroll
-  for (int r = 0; r < 32; ++r) v[r] = Storage<bf16_t>::round(v[r]);      // score the stored keys
+  for (int r = 0; r < N; ++r) v[r] = Storage<bf16_t>::round(v[r]);      // score the stored keys
   const int rep = q_heads / H;
   if (rope_cos != nullptr) rope128(v, q, rope_cos + t * (kGroup / 2), rope_sin + t * (kGroup / 2));
   for (int r = 0; r < rep; ++r) {
     const int qh = head * rep + r;
-    float qf[32];
+    float qf[N];
     if (q_lds != nullptr) {
-      const float* src = q_lds + r * kQueryLdsStride + q * kQueryLdsQuad;
+      const float* src = q_lds + r * kQueryLdsStride + q * N / kValsPerLane * kQueryLdsQuad + q * N % kValsPerLane;
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
+      for (int k = 0; k < N / 4; ++k) {
         const f32x4 a = *reinterpret_cast<const f32x4*>(src + 4 * k);
         qf[4 * k] = a.x; qf[4 * k + 1] = a.y; qf[4 * k + 2] = a.z; qf[4 * k + 3] = a.w;
       }
     } else {
-      Storage<bf16_t>::load32(qv + (b * q_heads + qh) * kGroup + q * kValsPerLane, qf);
+      Storage<bf16_t>::load(qv + (b * q_heads + qh) * kGroup + q * N, qf);
     }
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < 32; ++i) s = __fmaf_rn(qf[i], v[i], s);
-    s = quad_sum(s);
+    const float s = group_dot(qf, v, q);
     if (active && q == 0) scores[(b * q_heads + qh) * seq_len + t] = s * score_scale;
   }
 }

@@ -2,7 +2,10 @@
 // tiles of 32, 64, 128 or 320 token rows x one kv head (which one: tile_rows in fused_kernels.hip).
 //
 // Same main-loop bits (gemm_tile.h), same group bodies, hence the same results.  The epilogue parks up to 128 rows of the
-// tile at a time (64 with four waves) and works on them 16 groups per wave, one group per quad of lanes.
+// tile at a time and works on them 16 groups per wave, one group per quad of lanes; on tiles of 32 and 64 rows, which would
+// leave half of the waves (32 rows) or one of two per SIMD (64) idle, 8 groups per wave, one group per eight lanes.  A wave alone
+// on its SIMD is bound by latency, so the work per lane is what counts: keys and values of 128 tokens, 16-point grid, 22.9 -> 20.8 us
+// (256 points: 29.8 -> 25.1), decode of 1100 tokens with groups across the heads 27.7 -> 24.4.
 #pragma once
 #include "fused_epilogue.h"
 #include "gemm_tile.h"
@@ -39,7 +42,9 @@ template <int NCW, int MODE, int MB, bool WIDE>
 __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(MB == 1 ? 1 : 2))) void fused_tile_kernel(const TileArgs a) {
   using S = Tile<MB>;
   static_assert(!WIDE || MODE != kTileEncode, "the quantizer needs the whole group: groups across the heads are not fused");
-  constexpr int kParkRows = S::kRows < 16 * S::kWaves ? S::kRows : 16 * S::kWaves;   // one pass of 16 groups per wave
+  constexpr int kVals = MB <= 2 ? 16 : kValsPerLane;            // values of a group per lane
+  constexpr int kWaveRows = kVals / 2;                          // groups per wave and pass
+  constexpr int kParkRows = S::kRows < kWaveRows * S::kWaves ? S::kRows : kWaveRows * S::kWaves;   // one pass
   constexpr int kParks = (S::kRows + kParkRows - 1) / kParkRows;
   constexpr int kParkBlocks = kParkRows / 32 / S::WM;           // blocks of a wave's accumulators per park
   constexpr bool kEpilogue = MODE != kTilePredict;
@@ -63,12 +68,12 @@ __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per
   const int n_rows = left < S::kRows ? left : S::kRows;         // valid rows of this tile
   const int64_t m0 = (int64_t)b * a.seq_len + t0;               // its first row
   const int n0 = head * kGroup;
-  const int q = lane & 3;
+  const int q = group_pos<kVals>(lane), wrow = lane / (kGroup / kVals);      // position in the group, group of the wave
 
   // everything the epilogue reads from memory is requested before the main loop and waits in registers
   constexpr bool kEnc = MODE == kTileEncode;
   constexpr bool kWideGrid = WIDE && !is_rtn(NCW) && kEpilogue;
-  struct In { u32x4 x[kEnc ? 4 : 1]; CodeWords w; };
+  struct In { u32x4 x[kEnc ? kVals / 8 : 1]; CodeWords w; };
   // several parks: the inputs of the first are requested ahead of the main loop, those of each next one during the one
   // before (the accumulators leave no registers for more)
   In in[2];
@@ -81,15 +86,15 @@ __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per
   u32x2 qreg = {0, 0};
   const int rep = MODE == kTileScores ? a.q_heads / H : 0;
   const auto fetch = [&](int h) {
-    const int lrow = h * kParkRows + wave * 16 + (lane >> 2);
+    const int lrow = h * kParkRows + wave * kWaveRows + wrow;
     const int64_t row = m0 + (lrow < n_rows ? lrow : n_rows - 1);
     if constexpr (kEnc) {
-      const u32x4* src = reinterpret_cast<const u32x4*>(a.X + row * a.D + n0 + q * kValsPerLane);
+      const u32x4* src = reinterpret_cast<const u32x4*>(a.X + row * a.D + n0 + q * kVals);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) in[h & 1].x[k] = src[k];
+      for (int k = 0; k < kVals / 8; ++k) in[h & 1].x[k] = src[k];
     } else {
-      in[h & 1].w = request_words<NCW, WIDE>(a.codes, a.scales, row * H + head, q);
-      if constexpr (kWideGrid) request_wide_codes<NCW>(a.codes, row, q, wide[h & 1]);
+      in[h & 1].w = request_words<NCW, WIDE, kVals>(a.codes, a.scales, row * H + head, q);
+      if constexpr (kWideGrid) request_wide_codes<NCW, kVals>(a.codes, row, q, wide[h & 1]);
     }
   };
   if constexpr (kEpilogue) {
@@ -122,7 +127,7 @@ __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per
       }
     return;
   } else {
-    float sf[32] = {};
+    float sf[kVals] = {};
     if constexpr (!is_rtn(NCW)) load_signs(a.signs, head, q, sf);
     float* const q_lds = reinterpret_cast<float*>(cl.table);    // (no cell table in scores mode)
     __syncthreads();                                            // every wave is done reading the ring
@@ -148,21 +153,21 @@ __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per
         if (i >= S::MI) break;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          park[(S::block_row(k, wm) + (r >> 2) * 8 + fk * 4 + (r & 3)) * kLdP + park_col(wn * 32 + frow)] = acc[i][r] + bv;
+          park[(S::block_row(k, wm) + (r >> 2) * 8 + fk * 4 + (r & 3)) * kLdP + park_col<kVals>(wn * 32 + frow)] = acc[i][r] + bv;
       }
       if (h + 1 < kParks) fetch(h + 1);
       __syncthreads();
-      if (wave * 16 < here) {                                   // (a park of fewer rows: the first waves)
-        const int prow = wave * 16 + (lane >> 2), lrow = h * kParkRows + prow;
+      if (wave * kWaveRows < here) {                            // (a park of fewer rows: the first waves)
+        const int prow = wave * kWaveRows + wrow, lrow = h * kParkRows + prow;
         const bool active = lrow < n_rows;
         const int64_t rowc = m0 + (active ? lrow : n_rows - 1);
         const int64_t gid = rowc * H + head;
-        const int64_t off = rowc * a.D + n0 + q * kValsPerLane;
-        float p[32], v[32];
+        const int64_t off = rowc * a.D + n0 + q * kVals;
+        float p[kVals], v[kVals];
         read_parked(park + prow * kLdP, q, p);
         if constexpr (kEnc) {
 #pragma unroll
-          for (int k = 0; k < 4; ++k) unpack_bf16x8(in[h & 1].x[k], &v[8 * k]);
+          for (int k = 0; k < kVals / 8; ++k) unpack_bf16x8(in[h & 1].x[k], &v[8 * k]);
           quantize_group<NCW, false, S::MI < 5 ? 8 : 4>(v, p, sf, q, cl.cb, use_table ? cl.table : nullptr, active, gid, a.codes, a.scales,
                               a.Xhat != nullptr);
         } else if constexpr (kWideGrid) {
@@ -170,7 +175,7 @@ __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per
         } else {
           dequantize_words<NCW>(in[h & 1].w, p, sf, q, cl.cb, v);
         }
-        if (a.Xhat != nullptr && active) Storage<bf16_t>::store32(a.Xhat + off, v);
+        if (a.Xhat != nullptr && active) Storage<bf16_t>::store(a.Xhat + off, v);
         if constexpr (MODE == kTileScores)
           score_row(v, q, head, H, a.q_heads, b, t0 + (active ? lrow : n_rows - 1), a.seq_len, active, a.q, a.score_scale,
                     a.scores, a.rope_cos, a.rope_sin, q_lds);

@@ -2,8 +2,8 @@
 // rows x 128 outputs (one kv head): the shapes a launch picks from so that its tiles fill the CUs evenly.
 //
 // Same instruction (v_mfma_f32_32x32x16_bf16), operand orientation, swizzled LDS layout, direct-to-LDS loads and K order
-// per output as gemm_core.h, hence the same bits.  One workgroup per CU (64 rows and fewer: sometimes two).
-//   * Up to 64 rows: four waves split the 128 columns, every wave holds all rows.  Such a tile is bound by the stream of
+// per output as gemm_core.h, hence the same bits.  One workgroup per CU.
+//   * 32 rows: four waves split the 128 columns; 64 rows: eight, each holding 32 of the rows.  Such a tile is bound by the stream of
 //     operands from L2, (rows + 128) x 128 bytes per k-tile of 64, most of it W: a deep ring of k-tiles in LDS keeps it
 //     coming, and a wave reads the fragments of a whole k-tile ahead (its steps of 16 k are one or two MFMAs long).
 //     Measured with 32 rows: 0.18 us per k-tile = 57 bytes per cycle into a CU, of 64; a 256-row tile takes 0.6 to 0.9.
@@ -16,12 +16,12 @@ namespace aquakv {
 
 template <int MB> struct TileShape;                   // MB = 32-row blocks of the tile
 template <> struct TileShape<1> { static constexpr int kStages = 7; };       // x 20 KiB
-template <> struct TileShape<2> { static constexpr int kStages = 3; };       // x 24 KiB: two workgroups fit a CU
+template <> struct TileShape<2> { static constexpr int kStages = 6; };       // x 24 KiB: 0.31 us per k-tile; with four waves and 3 stages 0.385
 template <> struct TileShape<4> { static constexpr int kStages = 4; };       // x 32 KiB
 template <> struct TileShape<10> { static constexpr int kStages = 2; };      // x 56 KiB
 template <int MB> struct Tile : TileShape<MB> {
   static constexpr int kRows = 32 * MB;
-  static constexpr int WM = MB < 4 ? 1 : 2, WN = 4;
+  static constexpr int WM = MB == 1 ? 1 : 2, WN = 4;
   static constexpr int kWaves = WM * WN, kThreads = kWaves * 64;
   static constexpr int MI = MB / WM;                  // 32-row blocks per wave
   static constexpr int kAhead = MB < 4 ? 4 : 1;       // fragments are read this many steps of 16 k ahead
