@@ -139,7 +139,8 @@ int aquakv_build_search_table(const float* codebook, int32_t vq_dim, int32_t n_c
  * rows (0 on invalid arguments).  Its front part holds the fp32 predictions of one
  * chunk of rows (fp32 layers) or the re-tiled predictor weights (bf16 layers with
  * rotation groups across the heads; nothing for the other bf16 layers); behind it
- * a temporary Khat for one chunk of rows when the caller does not ask for one.
+ * a temporary Khat for one chunk of rows when the caller does not ask for one (calls
+ * over few rows keep partial sums there, and in Vhat, until they have finished).
  * More is used where it helps, if workspace_bytes says that it is there: with
  * rotation groups across the heads, short ranges (up to 4096 rows) are encoded in as
  * few pieces as there is room for fp32 predictions, at most kv_heads * head_dim * 4

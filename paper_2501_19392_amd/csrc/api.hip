@@ -203,6 +203,22 @@ Plan make_plan(const aquakv_layer* L, int64_t tokens) {
 // workspace (encode_wide), in as few pieces as there is room for them.
 constexpr int64_t kWideSplitRows = 4096;
 
+// Whether `all` lies over none of the call's buffers (outs: without the workspace it is part of) nor the layer's parameters.
+bool clear_of(const aquakv_layer* L, const Plan& pl, const Range& all, const Range* outs, int n_out, const Range* ins, int n_in) {
+  const size_t D = (size_t)pl.D, points = is_rtn(L) ? 0 : (size_t)L->n_codewords;
+  const Range params[] = {{L->w_k, D * L->d_in_k * pl.eb, ""}, {L->w_v, D * L->d_in_v * pl.eb, ""}, {L->b_k, D * sizeof(float), ""},
+                          {L->b_v, D * sizeof(float), ""}, {L->signs_k, points ? D : 0, ""}, {L->signs_v, points ? D : 0, ""},
+                          {L->codebook, points * 2 * sizeof(float), ""},
+                          {L->search_table, points ? aquakv::kSearchTableBytes : 0, ""}};
+  for (const Range& r : params)
+    if (overlap(all, r)) return false;
+  for (int i = 0; i < n_out; ++i)
+    if (overlap(all, outs[i])) return false;
+  for (int j = 0; j < n_in; ++j)
+    if (overlap(all, ins[j])) return false;
+  return true;
+}
+
 // Bytes of the workspace an encode call over `tokens` rows uses: the `need` bytes every caller provides, and where more
 // predictions help up to as much as those of all rows take.  Not if the bytes behind the first `need` lie over the call's other
 // buffers or the layer's parameters: an arena's owner may state all that is left of it.
@@ -211,18 +227,11 @@ size_t usable_workspace(const aquakv_layer* L, const Plan& pl, int64_t tokens, v
   if (!pl.fused || !is_wide(L) || (L->d_in_k == 0 && L->d_in_v == 0) || tokens > kWideSplitRows) return need;
   const size_t most = need + (size_t)tokens * pl.D * sizeof(float);
   const Range all = {workspace, bytes < most ? bytes : most, ""};
-  const size_t D = (size_t)pl.D, points = is_rtn(L) ? 0 : (size_t)L->n_codewords;
-  const Range params[] = {{L->w_k, D * L->d_in_k * pl.eb, ""}, {L->w_v, D * L->d_in_v * pl.eb, ""}, {L->b_k, D * sizeof(float), ""},
-                          {L->b_v, D * sizeof(float), ""}, {L->signs_k, points ? D : 0, ""}, {L->signs_v, points ? D : 0, ""},
-                          {L->codebook, points * 2 * sizeof(float), ""},
-                          {L->search_table, points ? aquakv::kSearchTableBytes : 0, ""}};
-  for (const Range& r : params)
-    if (overlap(all, r)) return need;
-  for (int i = 0; i < n_out; ++i)
-    if (outs[i].p != workspace && overlap(all, outs[i])) return need;
-  for (int j = 0; j < n_in; ++j)
-    if (overlap(all, ins[j])) return need;
-  return all.n;
+  return clear_of(L, pl, all, outs, n_out, ins, n_in) ? all.n : need;
+}
+// Keys and values of `tokens` rows can run as launch_fused_layer, given room for half of its sums and, in Vhat, for the other half.
+inline bool layer_at_once(const aquakv_layer* L, const Plan& pl, int64_t tokens, const void* V, const void* Vhat) {
+  return pl.fused && L->d_in_k != 0 && L->d_in_v != 0 && Vhat != nullptr && Vhat != V && aquakv::fused_layer_fits(tokens, pl.D);
 }
 
 inline const void* at(const void* base, int64_t row, size_t row_bytes) {
@@ -487,6 +496,7 @@ int aquakv_encode_layer(const aquakv_layer* L, int64_t tokens, const void* K, co
 
   const size_t row = (size_t)pl.D * pl.eb;
   size_t usable;
+  bool at_once;
   {
     const size_t t = (size_t)tokens, crow = pl.code_row, srow = scale_row_bytes(L);
     const Range outs[] = {{Khat, t * row, "Khat"}, {Vhat, t * row, "Vhat"}, {k_codes, t * crow, "k_codes"},
@@ -496,7 +506,10 @@ int aquakv_encode_layer(const aquakv_layer* L, int64_t tokens, const void* K, co
                          {Vhat_prev, has_v ? t * (L->d_in_v - pl.D) * pl.eb : 0, "Vhat_prev"}};
     const void* const inplace[] = {K, V, nullptr, nullptr, nullptr, nullptr, nullptr};
     CHECK(check_no_alias(outs, 7, ins, 4, inplace));
-    usable = usable_workspace(L, pl, tokens, workspace, pl.p_bytes + pl.khat_bytes, workspace_bytes, outs, 7, ins, 4);
+    usable = usable_workspace(L, pl, tokens, workspace, pl.p_bytes + pl.khat_bytes, workspace_bytes, outs, 6, ins, 4);
+    // (with a Khat to write to, the room of a temporary one is free; it may have been stated over the layer's parameters)
+    at_once = Khat != nullptr && !is_wide(L) && layer_at_once(L, pl, tokens, V, Vhat) &&
+              clear_of(L, pl, {workspace, t * row, ""}, outs, 6, ins, 4);
   }
 
   hipStream_t stream = static_cast<hipStream_t>(stream_);
@@ -505,6 +518,12 @@ int aquakv_encode_layer(const aquakv_layer* L, int64_t tokens, const void* K, co
   const size_t room = Khat != nullptr || !has_v ? usable : (usable - pl.khat_bytes) & ~(size_t)15;
   void* khat_tmp = static_cast<unsigned char*>(workspace) + room;
 
+  if (at_once) {
+    const aquakv::FusedTensor k = {Khat_prev, nullptr, L->d_in_k, 0, L->w_k, L->b_k, L->signs_k, K, k_codes, k_scales, Khat};
+    const aquakv::FusedTensor v = {Vhat_prev, Khat, L->d_in_v - pl.D, pl.D, L->w_v, L->b_v, L->signs_v, V, v_codes, v_scales, Vhat};
+    HIP_TRY(aquakv::launch_fused_layer(true, quantizer_id(L), L->codebook, L->search_table, k, v, workspace, tokens, pl.D, false, stream));
+    return AQUAKV_OK;
+  }
   for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk) {
     const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;
     void* khat_dst = Khat != nullptr ? at(Khat, r0, row) : (has_v ? khat_tmp : nullptr);
@@ -546,6 +565,7 @@ int aquakv_decode_layer(const aquakv_layer* L, int64_t tokens, const uint8_t* k_
   if (workspace_bytes < pl.p_bytes + pl.khat_bytes)
     return fail(AQUAKV_EWORKSPACE, "workspace %zu B < required %zu B", workspace_bytes, pl.p_bytes + pl.khat_bytes);
 
+  bool at_once;
   {
     const size_t t = (size_t)tokens, row = (size_t)pl.D * pl.eb, crow = pl.code_row, srow = scale_row_bytes(L);
     const Range outs[] = {{Khat, t * row, "Khat"}, {Vhat, t * row, "Vhat"}, {workspace, pl.p_bytes, "workspace"}};
@@ -554,9 +574,18 @@ int aquakv_decode_layer(const aquakv_layer* L, int64_t tokens, const uint8_t* k_
                          {k_codes, t * crow, "k_codes"}, {v_codes, want_v ? t * crow : 0, "v_codes"},
                          {k_scales, t * srow, "k_scales"}, {v_scales, want_v ? t * srow : 0, "v_scales"}};
     CHECK(check_no_alias(outs, 3, ins, 6));
+    at_once = layer_at_once(L, pl, tokens, nullptr, Vhat) && clear_of(L, pl, {workspace, t * row, ""}, outs, 2, ins, 6);
   }
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   float* Pbuf = static_cast<float*>(workspace);
+  if (at_once) {
+    const aquakv::FusedTensor k = {Khat_prev, nullptr, L->d_in_k, 0, L->w_k, L->b_k, L->signs_k, nullptr,
+                                   const_cast<uint8_t*>(k_codes), const_cast<uint16_t*>(k_scales), Khat};
+    const aquakv::FusedTensor v = {Vhat_prev, Khat, L->d_in_v - pl.D, pl.D, L->w_v, L->b_v, L->signs_v, nullptr,
+                                   const_cast<uint8_t*>(v_codes), const_cast<uint16_t*>(v_scales), Vhat};
+    HIP_TRY(aquakv::launch_fused_layer(false, quantizer_id(L), L->codebook, nullptr, k, v, workspace, tokens, pl.D, is_wide(L), stream));
+    return AQUAKV_OK;
+  }
 
   for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk) {
     const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;
@@ -601,7 +630,7 @@ int aquakv_encode_keys(const aquakv_layer* L, int64_t tokens, const void* K, con
     const Range ins[] = {{K, t * row, "K"}, {Khat_prev, t * L->d_in_k * pl.eb, "Khat_prev"}};
     const void* const inplace[] = {K, nullptr, nullptr, nullptr};
     CHECK(check_no_alias(outs, 4, ins, 2, inplace));
-    room = pl.p_bytes == 0 ? 0 : usable_workspace(L, pl, tokens, workspace, pl.p_bytes, workspace_bytes, outs, 4, ins, 2);
+    room = pl.p_bytes == 0 ? 0 : usable_workspace(L, pl, tokens, workspace, pl.p_bytes, workspace_bytes, outs, 3, ins, 2);
   }
   for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk) {
     const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;
@@ -639,7 +668,7 @@ int aquakv_encode_values(const aquakv_layer* L, int64_t tokens, const void* V, c
                          {Khat, has_v ? t * row : 0, "Khat"}};
     const void* const inplace[] = {V, nullptr, nullptr, nullptr};
     CHECK(check_no_alias(outs, 4, ins, 3, inplace));
-    room = pl.p_bytes == 0 ? 0 : usable_workspace(L, pl, tokens, workspace, pl.p_bytes, workspace_bytes, outs, 4, ins, 3);
+    room = pl.p_bytes == 0 ? 0 : usable_workspace(L, pl, tokens, workspace, pl.p_bytes, workspace_bytes, outs, 3, ins, 3);
   }
   for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk) {
     const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;

@@ -374,12 +374,38 @@ TileArgs tile_args(const void* x0, int d0, const void* x1, int d1, const void* W
   TileArgs a = {};
   a.x0 = static_cast<const bf16_t*>(x0); a.d0 = d0;
   a.x1 = static_cast<const bf16_t*>(x1); a.d1 = d1;
-  a.W = static_cast<const bf16_t*>(W); a.bias = bias;
+  a.W = static_cast<const bf16_t*>(W); a.bias = bias; a.ldw = d0 + d1;
   a.signs = signs; a.codebook = codebook; a.D = D;
   return a;
 }
 
 }  // namespace
+
+// Tiles of 32 rows for both products on the CUs at once.  With tiles of 64 rows for the first launch, up to twice the rows,
+// 600 tokens of 8 heads take 24.3 us to encode against 22.9 one after the other, 1000 tokens 25.5 against 23.8.
+bool fused_layer_fits(int64_t T, int D) { return 2 * ((T + 31) / 32) * (D / BN) <= 256; }
+
+hipError_t launch_fused_layer(bool encode, int n_codewords, const float* codebook, const void* table, const FusedTensor& keys,
+                              const FusedTensor& values, void* sums, int64_t T, int D, bool wide, hipStream_t stream) {
+  if (T == 0) return hipSuccess;
+  if (!fused_layer_fits(T, D) || (encode && wide) || values.Xhat == nullptr || values.Xhat == values.X) return hipErrorInvalidValue;
+  const auto args = [&](const FusedTensor& t) {
+    TileArgs a = tile_args(t.x0, t.d0, t.x1, t.d1, t.W, t.bias, t.signs, codebook, D);
+    a.table = static_cast<const uint32_t*>(table); a.X = static_cast<const bf16_t*>(t.X);
+    a.codes = t.codes; a.scales = t.scales; a.Xhat = static_cast<bf16_t*>(t.Xhat); a.seq_len = (int)T;
+    return a;
+  };
+  const int mode = encode ? kTileEncode : kTileDecode;
+  TileArgs first = args(values), rest = args(values);
+  first.d1 = 0; first.x1 = nullptr;
+  rest.x0 = rest.x1; rest.d0 = rest.d1; rest.x1 = nullptr; rest.d1 = 0; rest.W += values.d0;
+  for (TileArgs* a : {&first, &rest}) {
+    a->sums_hi = static_cast<uint16_t*>(values.Xhat);
+    a->sums_lo = static_cast<uint16_t*>(sums);
+  }
+  if (const hipError_t e = launch_tile_pair(mode, n_codewords, wide, args(keys), first, stream)) return e;
+  return launch_tile_rest(mode, n_codewords, wide, rest, stream);
+}
 
 bool tile_predict_fits(int64_t T, int D) { return ((T + 127) / 128) * (D / BN) <= 256; }
 

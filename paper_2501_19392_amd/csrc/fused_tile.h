@@ -36,10 +36,21 @@ struct TileArgs {
   int d0, d1, D, q_heads;
   int seq_len;                    // rows per sequence (one sequence: all rows)
   int tiles_per_seq;              // tiles never straddle sequences
+  int ldw;                        // row stride of W
+  // sums of a product over the first part of its inputs, in two halves of 16 bits, [T, D] each
+  uint16_t* sums_hi;
+  uint16_t* sums_lo;
 };
-
-template <int NCW, int MODE, int MB, bool WIDE>
-__global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(MB == 1 ? 1 : 2))) void fused_tile_kernel(const TileArgs a) {
+// Two products in one launch: the first `blocks` workgroups work on job[0], the others store the sums of job[1] and nothing else.
+struct TilePair {
+  TileArgs job[2];
+  int blocks;
+};
+// What is done about sums: nothing, the product goes on from those that are there, or `keep` says whether they alone are wanted.
+enum TileSums : int { kNoSums = 0, kUseSums = 1, kKeepSums = 2 };
+// workgroup `block` of the `nblocks` that work on `a`
+template <int NCW, int MODE, int MB, bool WIDE, int SUMS>
+__device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nblocks, bool keep) {
   using S = Tile<MB>;
   static_assert(!WIDE || MODE != kTileEncode, "the quantizer needs the whole group: groups across the heads are not fused");
   constexpr int kVals = MB <= 2 ? 16 : kValsPerLane;            // values of a group per lane
@@ -60,8 +71,7 @@ __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per
   // Which tile: while the predictor is larger than the rows (T <= D), the tiles of a head stay together on one XCD
   // (consecutive workgroups go to consecutive XCDs, so the plain order does that for 8 heads) and each XCD's L2 fetches
   // one head's slice of W once; beyond that the tiles of a row block stay together (remap_block).
-  const int nblocks = (int)gridDim.x;
-  const int logical = nblocks * S::kRows <= a.D * H ? (int)blockIdx.x : remap_block(blockIdx.x, nblocks);
+  const int logical = nblocks * S::kRows <= a.D * H ? block : remap_block(block, nblocks);
   const int head = logical % H, tile_m = logical / H;
   const int b = tile_m / a.tiles_per_seq, t0 = (tile_m % a.tiles_per_seq) * S::kRows;
   const int left = a.seq_len - t0;
@@ -97,7 +107,27 @@ __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per
       if constexpr (kWideGrid) request_wide_codes<NCW, kVals>(a.codes, row, q, wide[h & 1]);
     }
   };
-  if constexpr (kEpilogue) {
+  const int wm = wave / S::WN, wn = wave % S::WN;
+  f32x16 acc[S::MI];
+  const int frow = lane & 31, fk = lane >> 5;
+  // element of [T, D] in register r of block i
+  const auto sum_at = [&](int i, int r) {
+    const int lrow = S::block_row(i, wm) + (r >> 2) * 8 + fk * 4 + (r & 3);
+    return (m0 + (lrow < n_rows ? lrow : n_rows - 1)) * a.D + n0 + wn * 32 + frow;
+  };
+  uint16_t hi[S::MI][16], lo[S::MI][16];
+  if constexpr (SUMS == kUseSums) {
+#pragma unroll
+    for (int i = 0; i < S::MI; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { hi[i][r] = a.sums_hi[sum_at(i, r)]; lo[i][r] = a.sums_lo[sum_at(i, r)]; }
+  } else {
+#pragma unroll
+    for (int i = 0; i < S::MI; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+  }
+  if (kEpilogue && !(SUMS == kKeepSums && keep)) {
     if ((int)threadIdx.x < kGridPoints) { cb_a = a.codebook[2 * threadIdx.x]; cb_b = a.codebook[2 * threadIdx.x + 1]; }
     if (use_table) table_regs.request(a.table);
     if constexpr (MODE == kTileScores) {
@@ -109,12 +139,30 @@ __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per
   }
   __builtin_amdgcn_sched_barrier(0);
 
-  f32x16 acc[S::MI];
-  TileLoop<MB>::run(smem, a.x0 + m0 * a.d0, a.d0, a.d1 ? a.x1 + m0 * a.d1 : a.x1, a.d1,
-                    a.W + (int64_t)n0 * (a.d0 + a.d1), n_rows - 1, acc);
+  const int ldw = SUMS == kNoSums ? a.d0 + a.d1 : a.ldw;
+  TileLoop<MB>::run(smem, a.x0 + m0 * a.d0, a.d0, a.d1 ? a.x1 + m0 * a.d1 : a.x1, a.d1, a.W + (int64_t)n0 * ldw, ldw, n_rows - 1,
+                    acc, [&] {
+    if constexpr (SUMS == kUseSums) {
+#pragma unroll
+      for (int i = 0; i < S::MI; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][r] = __uint_as_float(((uint32_t)hi[i][r] << 16) | lo[i][r]);
+    }
+  });
+  if (SUMS == kKeepSums && keep) {
+#pragma unroll
+    for (int i = 0; i < S::MI; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const uint32_t u = __float_as_uint(acc[i][r]);
+        if (S::block_row(i, wm) + (r >> 2) * 8 + fk * 4 + (r & 3) < n_rows) {
+          a.sums_hi[sum_at(i, r)] = (uint16_t)(u >> 16);
+          a.sums_lo[sum_at(i, r)] = (uint16_t)u;
+        }
+      }
+    return;
+  }
 
-  const int wm = wave / S::WN, wn = wave % S::WN;
-  const int frow = lane & 31, fk = lane >> 5;
   const float bv = a.bias != nullptr ? a.bias[n0 + wn * 32 + frow] : 0.f;
 
   if constexpr (!kEpilogue) {
@@ -185,20 +233,33 @@ __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per
   }
 }
 
-// rows per tile 32, 64, 128 or 320 (one translation unit each); a.tiles_per_seq is filled in
+template <int NCW, int MODE, int MB, bool WIDE, int SUMS>
+__global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(MB == 1 ? 1 : 2))) void fused_tile_kernel(const TileArgs a) {
+  fused_tile<NCW, MODE, MB, WIDE, SUMS>(a, (int)blockIdx.x, (int)gridDim.x, false);
+}
+// (a kernel of its own: picking the job puts another round of scalar loads ahead of everything, 0.4 us)
+template <int NCW, int MODE, int MB, bool WIDE>
+__global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(MB == 1 ? 1 : 2))) void fused_tile_pair_kernel(const TilePair pair) {
+  const int second = (int)blockIdx.x >= pair.blocks;
+  // read from where they were passed (an index into a copy would put them in scratch)
+  TileArgs a;
+  __builtin_memcpy(&a, (const char*)__builtin_amdgcn_kernarg_segment_ptr() + second * (int)sizeof(TileArgs), sizeof(TileArgs));
+  fused_tile<NCW, MODE, MB, WIDE, kKeepSums>(a, (int)blockIdx.x - (second ? pair.blocks : 0), second ? (int)gridDim.x - pair.blocks : pair.blocks,
+                                             second != 0);
+}
+
+// rows per tile 32, 64, 128 or 320 (one translation unit each); tiles_per_seq is filled in
 #define AQUAKV_TILE_LAUNCHER(ROWS) \
   hipError_t launch_tile_##ROWS(int mode, int n_codewords, bool wide, int n_seq, const TileArgs& a, hipStream_t stream)
 AQUAKV_TILE_LAUNCHER(32);
 AQUAKV_TILE_LAUNCHER(64);
 AQUAKV_TILE_LAUNCHER(128);
 AQUAKV_TILE_LAUNCHER(320);
+// Tiles of 32 rows, encode or decode: `a` beside a second product of the same number of rows whose sums are stored, and a product
+// that goes on from stored sums.
+hipError_t launch_tile_pair(int mode, int n_codewords, bool wide, const TileArgs& a, const TileArgs& sums, hipStream_t stream);
+hipError_t launch_tile_rest(int mode, int n_codewords, bool wide, const TileArgs& a, hipStream_t stream);
 
-template <int MB>
-hipError_t launch_tile(int mode, int n_codewords, bool wide, int n_seq, TileArgs a, hipStream_t stream) {
-  using S = Tile<MB>;
-  a.tiles_per_seq = (a.seq_len + S::kRows - 1) / S::kRows;
-  const unsigned blocks = (unsigned)((int64_t)n_seq * a.tiles_per_seq * (a.D / kGroup));
-#define AQUAKV_TILE(N, MODE, WIDE) fused_tile_kernel<N, MODE, MB, WIDE><<<blocks, S::kThreads, 0, stream>>>(a)
 #define AQUAKV_TILE_N(MODE, WIDE)                                  \
   do {                                                             \
     if (n_codewords == kRtn2) AQUAKV_TILE(kRtn2, MODE, WIDE);      \
@@ -207,13 +268,19 @@ hipError_t launch_tile(int mode, int n_codewords, bool wide, int n_seq, TileArgs
     else if (n_codewords == 64) AQUAKV_TILE(64, MODE, WIDE);       \
     else AQUAKV_TILE(256, MODE, WIDE);                             \
   } while (0)
+
+template <int MB>
+hipError_t launch_tile(int mode, int n_codewords, bool wide, int n_seq, TileArgs a, hipStream_t stream) {
+  using S = Tile<MB>;
+  a.tiles_per_seq = (a.seq_len + S::kRows - 1) / S::kRows;
+  const unsigned blocks = (unsigned)((int64_t)n_seq * a.tiles_per_seq * (a.D / kGroup));
+#define AQUAKV_TILE(N, MODE, WIDE) fused_tile_kernel<N, MODE, MB, WIDE, kNoSums><<<blocks, S::kThreads, 0, stream>>>(a)
   if (mode == kTilePredict) AQUAKV_TILE(16, kTilePredict, false);
   else if (mode == kTileEncode) AQUAKV_TILE_N(kTileEncode, false);
   else if (mode == kTileDecode && wide) AQUAKV_TILE_N(kTileDecode, true);
   else if (mode == kTileDecode) AQUAKV_TILE_N(kTileDecode, false);
   else if (wide) AQUAKV_TILE_N(kTileScores, true);
   else AQUAKV_TILE_N(kTileScores, false);
-#undef AQUAKV_TILE_N
 #undef AQUAKV_TILE
   return hipGetLastError();
 }

@@ -37,19 +37,22 @@ template <int N> __device__ __forceinline__ void wait_loads() { __builtin_amdgcn
 
 // acc[i]: the 32 x 32 block at rows block_row(i, wm), columns 32 wn of the tile, wm = wave / 4, wn = wave % 4 (layout inside
 // the block as in gemm_core.h).  x0 / x1 point at the tile's first row; `last`: index of its last valid row (rows behind it
-// are read as that row).  W points at the tile's first output row.  Requires K = d0 + d1 a multiple of 128, d0 of 64.
+// are read as that row).  W points at the tile's first output row, rows ldw apart.  start() fills acc with the sums to start from
+// once the first k-tile has landed, and with it every load issued before.  Requires K = d0 + d1 a multiple of 128, d0 of 64.
 // Ends with every LDS read of the calling wave returned; the caller puts a barrier before it reuses the LDS.
 // The counts of loads in flight assume that nothing but this loop issues global loads while it runs.
 template <int MB> struct TileLoop {
   using S = Tile<MB>;
+  template <typename Start>
   static __device__ __forceinline__ void run(unsigned char* lds_base, const bf16_t* __restrict__ x0, int d0,
-                                             const bf16_t* __restrict__ x1, int d1, const bf16_t* __restrict__ W, int last,
-                                             f32x16 (&acc)[S::MI]);
+                                             const bf16_t* __restrict__ x1, int d1, const bf16_t* __restrict__ W, int ldw,
+                                             int last, f32x16 (&acc)[S::MI], Start&& start);
 };
 template <int MB>
+template <typename Start>
 __device__ __forceinline__ void TileLoop<MB>::run(unsigned char* lds_base, const bf16_t* __restrict__ x0, int d0,
                                                   const bf16_t* __restrict__ x1, int d1, const bf16_t* __restrict__ W,
-                                                  int last, f32x16 (&acc)[S::MI]) {
+                                                  int ldw, int last, f32x16 (&acc)[S::MI], Start&& start) {
   constexpr int kRowsPerPiece = S::kThreads / 8;      // tile rows one load instruction of the workgroup fills
   constexpr int kPieceBytes = S::kThreads * 16;
   constexpr int kA = S::kRows / kRowsPerPiece, kB = 128 / kRowsPerPiece, kPieces = kA + kB;
@@ -70,7 +73,7 @@ __device__ __forceinline__ void TileLoop<MB>::run(unsigned char* lds_base, const
     const int row = (tid >> 3) + pc * kRowsPerPiece;
     rowc[pc] = row < last ? row : last;
   }
-  const uint32_t offW = (uint32_t)(tid >> 3) * (uint32_t)(K * 2) + ch16;
+  const uint32_t offW = (uint32_t)(tid >> 3) * (uint32_t)(ldw * 2) + ch16;
   const auto uniform_ptr = [](const char* p) {
     const uint64_t u = reinterpret_cast<uint64_t>(p);
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u);
@@ -87,7 +90,7 @@ __device__ __forceinline__ void TileLoop<MB>::run(unsigned char* lds_base, const
       const gptr_t xb = uniform_ptr(reinterpret_cast<const char*>(second ? x1 : x0) + (int64_t)(second ? k0 - d0 : k0) * 2);
       __builtin_amdgcn_global_load_lds(xb + ((uint32_t)__umul24(rowc[pc], ld2) + ch16), dst, 16, 0, 0);
     } else {
-      const gptr_t wb = uniform_ptr(reinterpret_cast<const char*>(W) + ((int64_t)k0 * 2 + (int64_t)(pc - kA) * kRowsPerPiece * K * 2));
+      const gptr_t wb = uniform_ptr(reinterpret_cast<const char*>(W) + ((int64_t)k0 * 2 + (int64_t)(pc - kA) * kRowsPerPiece * ldw * 2));
       __builtin_amdgcn_global_load_lds(wb + offW, dst, 16, 0, 0);
     }
   };
@@ -102,10 +105,6 @@ __device__ __forceinline__ void TileLoop<MB>::run(unsigned char* lds_base, const
 #pragma unroll
     for (int pc = 0; pc <= MI; ++pc) frag_piece(stage_off, ks, f, MI - pc);     // the W fragment first
   };
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
   // the MFMAs of one step; extra(m) is issued right behind MFMA m (sched_barrier keeps the order)
   auto mma = [&](const Frag& f, auto&& extra) {
 #pragma unroll
@@ -145,6 +144,8 @@ __device__ __forceinline__ void TileLoop<MB>::run(unsigned char* lds_base, const
   Frag f[kBufs];
 #pragma unroll
   for (int s = 0; s < kAhead; ++s) read_frag(0, s, f[s]);
+  __builtin_amdgcn_sched_barrier(0);
+  start();
   __builtin_amdgcn_sched_barrier(0);
 
   // k-tile t sits in the stage at `cur`, t + 1 in the one at `nxt`.  Before the step that first reads k-tile t + 1 it is

@@ -161,3 +161,39 @@ def test_parameters_behind_the_needed_workspace_are_left_alone(name):
         for a, b in zip(got, want, strict=True):
             assert torch.equal(bits(a), bits(b))
         setattr(lg.c, name, getattr(lg, name).data_ptr())
+
+
+@pytest.mark.parametrize("T", [1, 130, 511, 512, 513])
+@pytest.mark.parametrize("quantizer,rht_group", [("n16", None), ("n64", None), ("rtn4", None), ("n256", 1024)])
+def test_keys_and_values_of_few_rows_at_once(T, quantizer, rht_group):
+    """Up to 512 rows of 8 heads the keys' launch takes half of the values' product along, whose sums wait in the workspace and in
+    Vhat: the bits of the halves called one after the other, which do not run that way, for every choice of outputs (without Khat,
+    or with Vhat over V, the layer call does not either), and the least workspace there may be, with parameters behind it."""
+    from paper_2501_19392_amd import binding as B
+    print(f"case at once T={T} {quantizer} group={rht_group}", flush=True)
+    lg, D = layer(8, 1024, quantizer, rht_group, bias=T % 2 == 1), 1024
+    g = torch.Generator(device="cuda").manual_seed(900 + T)
+    K, V, Kp, Vp = (torch.randn(T, 8, 128, generator=g, device="cuda").bfloat16() for _ in range(4))
+    need = B.aquakv_workspace_bytes(lg, T)
+    new = lambda: [*lg.alloc_codes(T), *lg.alloc_codes(T)]
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    want, Kh, Vh = new(), lg.alloc_kv(T), lg.alloc_kv(T)
+    B.aquakv_encode_keys(lg, T, K, Kp, want[0], want[1], Kh, ws)
+    B.aquakv_encode_values(lg, T, V, Vp, Kh, want[2], want[3], Vh, ws)
+    arena = torch.full((need + lg.w_v.numel() * 2,), 0xCD, dtype=torch.uint8, device="cuda")
+    arena[need:] = bits(lg.w_v).flatten()
+    lg.c.w_v = arena.data_ptr() + need
+    for keys, values in (("own", "own"), ("own", "in place"), ("in place", "own"), (None, "own"), ("own", None)):
+        got, k, v = new(), K.clone(), V.clone()
+        kh = {"own": lg.alloc_kv(T), "in place": k, None: None}[keys]
+        vh = {"own": lg.alloc_kv(T), "in place": v, None: None}[values]
+        B.aquakv_encode_layer(lg, T, k, v, Kp, Vp, *got, kh, vh, arena[:need])
+        torch.cuda.synchronize()
+        for a, b in list(zip(got, want)) + [(kh, Kh), (vh, Vh)]:
+            assert a is None or torch.equal(bits(a), bits(b)), (keys, values)
+    for size in (need, arena.numel()):                # (the rest of the arena stated too: the parameter in it stays)
+        kd, vd = lg.alloc_kv(T), lg.alloc_kv(T)
+        B.aquakv_decode_layer(lg, T, *want, Kp, Vp, kd, vd, arena[:size])
+        torch.cuda.synchronize()
+        assert torch.equal(bits(kd), bits(Kh)) and torch.equal(bits(vd), bits(Vh))
+    assert torch.equal(arena[need:], bits(lg.w_v).flatten())
