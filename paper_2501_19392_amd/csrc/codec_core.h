@@ -15,6 +15,8 @@
 // entry in the LDS copy of the grid, which still fits a byte of a table entry and is the address the look-up
 // needs; for the larger grids the index j itself.
 #pragma once
+#include <type_traits>
+
 #include "device_utils.h"
 
 namespace aquakv {
@@ -356,12 +358,12 @@ __device__ __forceinline__ uint32_t rtn_load_meta(const uint16_t* __restrict__ s
 }
 
 // Q of the residuals of the N values this lane holds of head group gid; same contract as quantize_residual below
-// (`l`: group_pos, or with WIDE lane % 32: the group is then the whole token of 8 heads, one (step, zero) per token).
+// (`l`: group_pos, or with WIDE token_pos: the group is then the whole token of 8 heads, one (step, zero) per token).
 template <int BITS, bool WIDE = false, int N>
 __device__ __forceinline__ void rtn_quantize_residual(float (&v)[N], int l, bool active, int64_t gid,
                                                       uint8_t* __restrict__ codes, uint16_t* __restrict__ scales,
                                                       bool want_hat) {
-  const int q = WIDE ? l & 3 : l;
+  const int q = WIDE ? l & (kGroup / N - 1) : l;
   constexpr float kTop = (float)((1 << BITS) - 1);
   float lo = 0.f, hi = 0.f;
 #pragma unroll
@@ -373,10 +375,19 @@ __device__ __forceinline__ void rtn_quantize_residual(float (&v)[N], int l, bool
   hi = fmaxf(hi, quad_xor<1>(hi));
   if constexpr (N == 16) { lo = fminf(lo, quad_xor<2>(lo)); hi = fmaxf(hi, quad_xor<2>(hi)); }
   if constexpr (WIDE) {
-    lo = fminf(lo, quad_xor<2>(lo));    hi = fmaxf(hi, quad_xor<2>(hi));
-    lo = fminf(lo, swizzle_xor<4>(lo)); hi = fmaxf(hi, swizzle_xor<4>(hi));
-    lo = fminf(lo, row_xor8(lo));       hi = fmaxf(hi, row_xor8(hi));
-    lo = fminf(lo, swizzle_xor<16>(lo)); hi = fmaxf(hi, swizzle_xor<16>(hi));
+    const auto fold = [&](float lo2, float hi2) { lo = fminf(lo, lo2); hi = fmaxf(hi, hi2); };
+    fold(quad_xor<2>(lo), quad_xor<2>(hi));
+    fold(octet_mirror(lo), octet_mirror(hi));
+    fold(row_xor8(lo), row_xor8(hi));
+    const auto far = [&](auto mask) {
+      float a = lo, b = lo, c = hi, d = hi;
+      swap_lanes<mask()>(a, b);
+      swap_lanes<mask()>(c, d);
+      lo = fminf(a, b);
+      hi = fmaxf(c, d);
+    };
+    far(std::integral_constant<int, 16>());
+    if constexpr (N == 16) far(std::integral_constant<int, 32>());
   }
   const float step = fminf(__fdiv_rn(hi - lo, kTop), 65504.0f);
   const _Float16 s16h = static_cast<_Float16>(step);      // round to nearest even
@@ -408,20 +419,23 @@ __device__ __forceinline__ void rtn_quantize_residual(float (&v)[N], int l, bool
 // v holds, if `want_hat`, what finish_hat turns into the (unrounded) reconstruction p + Q^-1(codes).  Codes and the
 // scale are stored when `active` (inactive lanes only keep the cross-lane exchanges in step).
 // `l` is the lane's position inside its rotation group: group_pos for groups of 128 (WIDE = false, one
-// scale per head group), lane % 32 for groups of 1024 = the whole token (WIDE = true, kv_heads = 8, one
+// scale per head group), token_pos for groups of 1024 = the whole token (WIDE = true, kv_heads = 8, one
 // scale per token at scales[gid / 8]).  The code bytes have the same layout in both cases.
-// BATCH: sub-vectors searched together.
-template <int NCW, bool WIDE = false, int BATCH = 4, int N>
+// BATCH: sub-vectors searched together.  searched() is called behind the search, when registers are free again.
+struct Nothing { __device__ __forceinline__ void operator()() const {} };
+template <int NCW, bool WIDE = false, int BATCH = 4, int N, typename Searched = Nothing>
 __device__ __forceinline__ void quantize_residual(float (&v)[N], const float (&sf)[N], int l, const float4* cb,
                                                   const uint32_t* table, bool active, int64_t gid,
-                                                  uint8_t* __restrict__ codes, uint16_t* __restrict__ scales, bool want_hat) {
+                                                  uint8_t* __restrict__ codes, uint16_t* __restrict__ scales, bool want_hat,
+                                                  Searched&& searched = Nothing()) {
   if constexpr (is_rtn(NCW)) {
     rtn_quantize_residual<NCW, WIDE>(v, l, active, gid, codes, scales, want_hat);
+    searched();
     return;
   }
 #pragma unroll
   for (int r = 0; r < N; ++r) v[r] *= sf[r];                                             // s * (x - p), exact product
-  const int q = WIDE ? l & 3 : l;
+  const int q = WIDE ? l & (kGroup / N - 1) : l;
   Rot<WIDE>::wht(v, l);                                   // w = +-H u (unnormalised, lane sign pending)
 
   const float ss = Rot<WIDE>::square_sum(v, l);
@@ -496,6 +510,7 @@ __device__ __forceinline__ void quantize_residual(float (&v)[N], const float (&s
     store_codes<NCW, N>(codes, gid, q, words);
     if (l == 0) scales[WIDE ? gid >> 3 : gid] = __builtin_bit_cast(uint16_t, s16h);
   }
+  searched();
   if (want_hat) Rot<WIDE>::iwht(v, l);
 }
 // the reconstruction from quantize_residual's v and the prediction
@@ -558,7 +573,7 @@ __device__ __forceinline__ CodeWords request_words(const uint8_t* __restrict__ c
   return w;
 }
 
-// Q^-1(codes) + p from the words requested earlier (unrounded, in v); l: group_pos, or with WIDE lane % 32
+// Q^-1(codes) + p from the words requested earlier (unrounded, in v); l: group_pos, or with WIDE token_pos
 template <int NCW, bool WIDE = false, int N>
 __device__ __forceinline__ void dequantize_words(const CodeWords& w, const float (&p)[N], const float (&sf)[N], int l,
                                                  const float4* cb, float (&v)[N]) {

@@ -16,6 +16,7 @@ namespace aquakv {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kQuantizeVals = 16;                            // values per lane in the quantizer
 constexpr int kGroupsPerBlock = kThreads / kLanesPerGroup;   // 64
 
 // ------------------------------------------------------------------ quantize
@@ -27,7 +28,7 @@ constexpr int kGroupsPerBlock = kThreads / kLanesPerGroup;   // 64
 // at a time; with one (32 more values, and the next round's 32) it stays at two.  8192 tokens, 256-point grid, groups of
 // 1024, keys and values: 2 x 53 us as two launches of one wave per SIMD.
 template <typename T, int NCW, bool WIDE, bool PRED>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED || sizeof(T) == 4 ? 2 : 3))) void quantize_kernel(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED ? 3 : 4))) void quantize_kernel(
     const QuantizeIo io0, const QuantizeIo io1, const float* __restrict__ P, const float* __restrict__ codebook,
     const uint32_t* __restrict__ table, int64_t n_groups, int H) {
   const T* const X = static_cast<const T*>(blockIdx.y ? io1.X : io0.X);
@@ -37,64 +38,80 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED |
   uint16_t* const scales = blockIdx.y ? io1.scales : io0.scales;
   __shared__ Lds lds;
   stage_lds<NCW>(lds, codebook, table);
-  const int q = threadIdx.x & 3;
+  constexpr int N = kQuantizeVals, kLanes = kGroup / N, kGroups = kThreads / kLanes;       // lanes per group, groups per round
+  const int l = WIDE ? token_pos<N>(threadIdx.x) : group_pos<N>(threadIdx.x), q = l & (kLanes - 1), slot = threadIdx.x / kLanes;
   // A thread meets the same head in every round of the grid-stride loop when the stride is a multiple of H (it is
   // for the power-of-two head counts in use): the signs are then fetched once.
-  float sf[32] = {};
-  const bool fixed_head = kGroupsPerBlock % H == 0;
+  float sf[N] = {};
+  const bool fixed_head = kGroups % H == 0;
   if constexpr (!is_rtn(NCW)) {
-    if (fixed_head) load_signs(signs, (int)((blockIdx.x * (unsigned)kGroupsPerBlock + (threadIdx.x >> 2)) % (unsigned)H), q, sf);
+    if (fixed_head) load_signs(signs, (int)((blockIdx.x * (unsigned)kGroups + slot) % (unsigned)H), q, sf);
   }
-  // The rows (and the fp32 prediction) of the next round are requested before the current round is worked on: with two
-  // waves per SIMD nothing else hides the latency of these loads.
-  constexpr int kXQuads = sizeof(T) == 2 ? 4 : 8;
-  struct Rows { u32x4 x[kXQuads]; f32x4 p[PRED ? 8 : 1]; };
+  // The rows (and the fp32 prediction) of the next round are requested behind this round's search: the inverse transform and the
+  // stores hide some of their latency, the other waves of the SIMD the rest.  The prediction is read again for the reconstruction
+  // instead of being held through the search (32 registers).
+  constexpr int kXQuads = N * sizeof(T) / 16, kPQuads = PRED ? N / 4 : 1;
+  struct Rows { u32x4 x[kXQuads]; f32x4 p[kPQuads]; };
+  const auto request_p = [&](int64_t off, f32x4 (&r)[kPQuads]) {
+    if constexpr (PRED) {
+#pragma unroll
+      for (int k = 0; k < N / 4; ++k) r[k] = reinterpret_cast<const f32x4*>(P + off)[k];
+    }
+  };
+  const auto unpack_p = [&](const f32x4 (&r)[kPQuads], float (&p)[N]) {
+#pragma unroll
+    for (int k = 0; k < N / 4; ++k) {
+      const f32x4 a = PRED ? r[k % kPQuads] : f32x4{0.f, 0.f, 0.f, 0.f};
+      p[4 * k] = a.x; p[4 * k + 1] = a.y; p[4 * k + 2] = a.z; p[4 * k + 3] = a.w;
+    }
+  };
   const auto request = [&](int64_t g0, Rows& r) {
-    int64_t gid = g0 + (threadIdx.x >> 2);
+    int64_t gid = g0 + slot;
     gid = gid < n_groups ? gid : n_groups - 1;
-    const int64_t off = gid * kGroup + q * kValsPerLane;
+    const int64_t off = gid * kGroup + q * N;
     const u32x4* src = reinterpret_cast<const u32x4*>(X + off);
 #pragma unroll
     for (int k = 0; k < kXQuads; ++k) r.x[k] = src[k];
-    if constexpr (PRED) {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) r.p[k] = reinterpret_cast<const f32x4*>(P + off)[k];
-    }
+    request_p(off, r.p);
   };
-  const int64_t stride = (int64_t)gridDim.x * kGroupsPerBlock;
-  Rows cur;
-  if ((int64_t)blockIdx.x * kGroupsPerBlock < n_groups) request((int64_t)blockIdx.x * kGroupsPerBlock, cur);
-  for (int64_t g0 = (int64_t)blockIdx.x * kGroupsPerBlock; g0 < n_groups; g0 += stride) {
-    Rows nxt;
-    if (g0 + stride < n_groups) request(g0 + stride, nxt);
-    int64_t gid = g0 + (threadIdx.x >> 2);
+  const int64_t stride = (int64_t)gridDim.x * kGroups;
+  Rows rows;
+  if ((int64_t)blockIdx.x * kGroups < n_groups) request((int64_t)blockIdx.x * kGroups, rows);
+  for (int64_t g0 = (int64_t)blockIdx.x * kGroups; g0 < n_groups; g0 += stride) {
+    int64_t gid = g0 + slot;
     const bool active = gid < n_groups;
     if (!active) gid = n_groups - 1;                      // keep every lane in the DPP exchanges
-    const int64_t off = gid * kGroup + q * kValsPerLane;
+    const int64_t off = gid * kGroup + q * N;
 
-    float v[32], p[32];
+    float v[N], p[N];
     if constexpr (sizeof(T) == 2) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) unpack_bf16x8(cur.x[k], &v[8 * k]);
+      for (int k = 0; k < kXQuads; ++k) unpack_bf16x8(rows.x[k], &v[8 * k]);
     } else {
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        v[4 * k] = __uint_as_float(cur.x[k].x); v[4 * k + 1] = __uint_as_float(cur.x[k].y);
-        v[4 * k + 2] = __uint_as_float(cur.x[k].z); v[4 * k + 3] = __uint_as_float(cur.x[k].w);
+      for (int k = 0; k < N / 4; ++k) {
+        v[4 * k] = __uint_as_float(rows.x[k].x); v[4 * k + 1] = __uint_as_float(rows.x[k].y);
+        v[4 * k + 2] = __uint_as_float(rows.x[k].z); v[4 * k + 3] = __uint_as_float(rows.x[k].w);
       }
     }
+    unpack_p(rows.p, p);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const f32x4 a = PRED ? cur.p[PRED ? k : 0] : f32x4{0.f, 0.f, 0.f, 0.f};
-      p[4 * k] = a.x; p[4 * k + 1] = a.y; p[4 * k + 2] = a.z; p[4 * k + 3] = a.w;
-    }
+    for (int r = 0; r < N; ++r) v[r] -= p[r];
     if constexpr (!is_rtn(NCW)) {
       if (!fixed_head) load_signs(signs, (int)(gid % H), q, sf);     // (a 64-bit remainder: kept off the common path)
     }
-    quantize_group<NCW, WIDE>(v, p, sf, WIDE ? (int)(threadIdx.x & 31) : q, lds.cb, table != nullptr ? lds.table : nullptr,
-                              active, gid, codes, scales, Xhat != nullptr);
-    if (Xhat != nullptr && active) Storage<T>::store(Xhat + off, v);
-    cur = nxt;
+    f32x4 again[kPQuads];
+    quantize_residual<NCW, WIDE>(v, sf, l, lds.cb, table != nullptr ? lds.table : nullptr, active, gid, codes, scales,
+                                 Xhat != nullptr, [&] {
+      asm volatile("" ::: "memory");                      // (not the registers of the first read)
+      if (Xhat != nullptr) request_p(off, again);
+      if (g0 + stride < n_groups) request(g0 + stride, rows);
+    });
+    if (Xhat != nullptr) {
+      unpack_p(again, p);
+      finish_hat<NCW>(v, sf, p);
+      if (active) Storage<T>::store(Xhat + off, v);
+    }
   }
 }
 
@@ -111,7 +128,7 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(const QuantizeIo i
   __shared__ float4 cb[is_rtn(NCW) ? 1 : NCW];
   load_codebook<NCW>(codebook, cb);
   __syncthreads();
-  const int q = threadIdx.x & 3;
+  const int l = WIDE ? token_pos<32>(threadIdx.x) : (int)threadIdx.x & 3, q = l & 3;
   // A thread meets the same head in every round of the grid-stride loop when the stride is a multiple of H (it is
   // for the power-of-two head counts in use): the signs are then fetched once.
   float sf[32] = {};
@@ -146,7 +163,7 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(const QuantizeIo i
     if constexpr (!is_rtn(NCW)) {
       if (!fixed_head) load_signs(signs, (int)(gid % H), q, sf);     // (a 64-bit remainder: kept off the common path)
     }
-    dequantize_words<NCW, WIDE>(cur, p, sf, WIDE ? (int)(threadIdx.x & 31) : q, cb, z);
+    dequantize_words<NCW, WIDE>(cur, p, sf, l, cb, z);
     if (active) Storage<T>::store(Xhat + off, z);
     cur = nxt;
   }
@@ -163,7 +180,7 @@ __global__ __launch_bounds__(kThreads) void attn_scores_kernel(
   __shared__ float4 cb[is_rtn(NCW) ? 1 : NCW];
   load_codebook<NCW>(codebook, cb);
   __syncthreads();
-  const int q = threadIdx.x & 3;
+  const int l = WIDE ? token_pos<32>(threadIdx.x) : (int)threadIdx.x & 3, q = l & 3;
   // A thread meets the same head in every round of the grid-stride loop when the stride is a multiple of H (it is
   // for the power-of-two head counts in use): the signs are then fetched once.
   float sf[32] = {};
@@ -202,7 +219,7 @@ __global__ __launch_bounds__(kThreads) void attn_scores_kernel(
     if constexpr (!is_rtn(NCW)) {
       if (!fixed_head) load_signs(signs, (int)(gid % H), q, sf);     // (a 64-bit remainder: kept off the common path)
     }
-    dequantize_words<NCW, WIDE>(cur, p, sf, WIDE ? (int)(threadIdx.x & 31) : q, cb, z);
+    dequantize_words<NCW, WIDE>(cur, p, sf, l, cb, z);
     cur = nxt;
     if (Khat_out != nullptr && active) Storage<T>::store(Khat_out + off, z);
 #pragma unroll
@@ -331,10 +348,10 @@ __global__ __launch_bounds__(1024) void build_overflow_kernel(const float* __res
 // the request of the next round's rows has a next round to run ahead of (measured at 32768 tokens: 52 us against 67 us with
 // 16 per CU).  The inverse stages 256 B and runs four waves per SIMD; four workgroups per CU were the best of 2 / 4 / 8 / 16
 // at 32768 tokens (25.7 against 29 us with 16).  Below that number the rounds are shared out evenly.
-constexpr int kQuantizeWgPerCu = 2, kQuantizePlainWgPerCu = 3;     // with a prediction, without
+constexpr int kQuantizeWgPerCu = 3, kQuantizePlainWgPerCu = 4;     // with a prediction, without
 constexpr int kDequantizeWgPerCu = 4;
-inline unsigned blocks_for(int64_t n_groups, int per_cu, int tensors = 1) {
-  const int64_t need = (n_groups + kGroupsPerBlock - 1) / kGroupsPerBlock;
+inline unsigned blocks_for(int64_t n_groups, int per_cu, int tensors = 1, int groups_per_block = kGroupsPerBlock) {
+  const int64_t need = (n_groups + groups_per_block - 1) / groups_per_block;
   const int64_t cap = 256 * per_cu / tensors;
   const int64_t rounds = (need + cap - 1) / cap;
   return (unsigned)((need + rounds - 1) / rounds);
@@ -382,8 +399,8 @@ hipError_t launch_quantize(int dtype, int n_codewords, const QuantizeIo* io, int
   if (tensors != 1 && P != nullptr) return hipErrorInvalidValue;
   const QuantizeIo& other = io[tensors - 1];
   const uint32_t* tab = static_cast<const uint32_t*>(table);
-  const int per_cu = P != nullptr || dtype != kBF16 ? kQuantizeWgPerCu : kQuantizePlainWgPerCu;
-  const dim3 grid(blocks_for(n_groups, per_cu, tensors), (unsigned)tensors);
+  const int per_cu = P != nullptr ? kQuantizeWgPerCu : kQuantizePlainWgPerCu;
+  const dim3 grid(blocks_for(n_groups, per_cu, tensors, kThreads * kQuantizeVals / kGroup), (unsigned)tensors);
   if (P != nullptr)
     AQUAKV_DISPATCH(dtype, n_codewords, wide, (quantize_kernel<T, N, W, true><<<grid, kThreads, 0, stream>>>(
                                                   io[0], other, P, codebook, tab, n_groups, H)));

@@ -124,19 +124,24 @@ __device__ __forceinline__ float octet_mirror(float x) {      // value of lane ^
 // Position of `lane` in its group of 4 (N = 32) or 8 (N = 16) lanes.
 template <int N> __device__ __forceinline__ int group_pos(int lane) { return N == 32 ? lane & 3 : octet_pos(lane); }
 
-// sum_r a[r] * b[r] over the group, every lane gets it.  Fixed order, the same for both widths: one chain of multiply-adds over
-// each 32 consecutive coordinates, then the four chains pairwise.  With 16 values per lane the chain passes through two lanes.
-template <int N> __device__ __forceinline__ float group_dot(const float (&a)[N], const float (&b)[N], int pos) {
+// sum_r a[r] * b[r] over 32 consecutive coordinates as one chain of multiply-adds; with 16 values per lane it passes through two
+// lanes, and both get it.
+template <int N> __device__ __forceinline__ float chain_dot(const float (&a)[N], const float (&b)[N], int pos) {
   float s = 0.f;
 #pragma unroll
   for (int r = 0; r < N; ++r) s = __fmaf_rn(a[r], b[r], s);
-  if constexpr (N == 32) return quad_sum(s);
+  if constexpr (N == 32) return s;
   float t = quad_xor<1>(s);
 #pragma unroll
   for (int r = 0; r < N; ++r) t = __fmaf_rn(a[r], b[r], t);
-  const float first = quad_xor<1>(t);
-  t = (pos & 1) ? t : first;
-  t = t + quad_xor<2>(t);
+  const float second = quad_xor<1>(t);
+  return (pos & 1) ? t : second;
+}
+// ... over the group, every lane gets it.  Fixed order, the same for both widths: the four chains pairwise.
+template <int N> __device__ __forceinline__ float group_dot(const float (&a)[N], const float (&b)[N], int pos) {
+  const float s = chain_dot(a, b, pos);
+  if constexpr (N == 32) return quad_sum(s);
+  const float t = s + quad_xor<2>(s);
   return t + octet_mirror(t);
 }
 
@@ -166,14 +171,15 @@ template <int N> __device__ __forceinline__ float group_dot(const float (&a)[N],
     "+v"(v[b + 7]), "+v"(v[b + 8]), "+v"(v[b + 9]), "+v"(v[b + 10]), "+v"(v[b + 11]), "+v"(v[b + 12]),                 \
     "+v"(v[b + 13]), "+v"(v[b + 14]), "+v"(v[b + 15])                                                                  \
   : "v"(s)
-// MASK 1, 2: partner lane ^ MASK; 7: lane ^ 7
+// partner lane ^ MASK
 template <int MASK, int N> __device__ __forceinline__ void wht_lane_stage(float (&v)[N], float s) {
-  static_assert((MASK == 1 || MASK == 2 || MASK == 7) && N % 16 == 0, "mask");
+  static_assert((MASK == 1 || MASK == 2 || MASK == 7 || MASK == 8) && N % 16 == 0, "mask");
 #pragma unroll
   for (int b = 0; b < N; b += 16) {
     if constexpr (MASK == 1) asm(AQUAKV_FMAC_DPP16("quad_perm:[1,0,3,2]") AQUAKV_FMAC_ARGS);
     else if constexpr (MASK == 2) asm(AQUAKV_FMAC_DPP16("quad_perm:[2,3,0,1]") AQUAKV_FMAC_ARGS);
-    else asm(AQUAKV_FMAC_DPP16("row_half_mirror") AQUAKV_FMAC_ARGS);
+    else if constexpr (MASK == 7) asm(AQUAKV_FMAC_DPP16("row_half_mirror") AQUAKV_FMAC_ARGS);
+    else asm(AQUAKV_FMAC_DPP16("row_ror:8") AQUAKV_FMAC_ARGS);
   }
 }
 
@@ -203,45 +209,67 @@ template <bool INV = false, int N> __device__ __forceinline__ void wht128(float 
 }
 
 // ---------------------------------------------------------------- 1024-point WHT (rotation group = whole token)
-// A token's 1024 values (8 heads x 128) sit in 32 consecutive lanes, lane j holding coordinates 32 j ... 32 j + 31,
-// i.e. 8 quads that each hold one head.  H_1024 = H_8 (x) H_128: after wht128 inside every quad, three more
-// butterfly stages pair lanes j and j ^ 4, j ^ 8, j ^ 16.  Same multiply-add form and pending lane sign as the
-// quad stages; lane ^ 8 is a DPP row rotation by 8, lane ^ 4 and lane ^ 16 go through ds_swizzle.
-template <int XOR_MASK> __device__ __forceinline__ float swizzle_xor(float x) {
-  static_assert(XOR_MASK == 4 || XOR_MASK == 16, "mask");
-  // bit-mask mode: lane' = ((lane & 0x1f) | 0) ^ XOR_MASK within each group of 32 lanes
-  return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), (XOR_MASK << 10) | 0x1f));
-}
+// A token's 1024 values (8 heads x 128) sit in 1024 / N consecutive lanes, N each: 8 quads, or 8 times eight lanes, that each hold
+// one head.  H_1024 = H_8 (x) H_128: after wht128 inside every head, three more butterfly stages pair the positions (token_pos:
+// N pos ... are the lane's coordinates) that differ in the three upper bits.  Lanes with bit 2 set hold their blocks in reverse, as
+// in octet_pos, so the partners of bits 2 and 3 are lane ^ 7 and lane ^ 8: DPP multiply-adds like the quad stages, with the same
+// pending lane sign.  For bits 4 and 5 v_permlane16_swap and v_permlane32_swap bring both values of a butterfly into one lane (they
+// exchange the odd rows of 16 lanes, or the upper half of the lanes, of one register with the even rows, or the lower half, of
+// another), for two registers at a time, and back: two instructions per value, no pending sign.  (ds_swizzle, which took bits 2
+// and 4 before, made a third of the quantizer's LDS instructions.)
+template <int N> __device__ __forceinline__ int token_pos(int lane) { return (lane & (1024 / N - 1)) ^ ((lane & 4) ? 3 : 0); }
 __device__ __forceinline__ float row_xor8(float x) {     // value of lane ^ 8 (rotation by 8 within a row of 16)
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128 /* row_ror:8 */, 0xF, 0xF, true));
 }
-template <bool INV = false> __device__ __forceinline__ void wht1024_tail(float (&v)[32], int lane32) {
-  constexpr float up = INV ? 1.0f : -1.0f;               // as in wht128
-  const float s4 = (lane32 & 4) ? up : -up, s8 = (lane32 & 8) ? up : -up, s16 = (lane32 & 16) ? up : -up;
-#pragma unroll
-  for (int r = 0; r < 32; ++r) v[r] = __fmaf_rn(swizzle_xor<4>(v[r]), s4, v[r]);
-#pragma unroll
-  for (int r = 0; r < 32; ++r) v[r] = __fmaf_rn(row_xor8(v[r]), s8, v[r]);
-#pragma unroll
-  for (int r = 0; r < 32; ++r) v[r] = __fmaf_rn(swizzle_xor<16>(v[r]), s16, v[r]);
+// MASK 16: odd rows of x <-> even rows of y; 32: upper half of x <-> lower half of y
+template <int MASK> __device__ __forceinline__ void swap_lanes(float& x, float& y) {
+  static_assert(MASK == 16 || MASK == 32, "mask");
+  const uint32_t xi = __float_as_uint(x), yi = __float_as_uint(y);
+  const auto r = MASK == 16 ? __builtin_amdgcn_permlane16_swap(xi, yi, false, false) : __builtin_amdgcn_permlane32_swap(xi, yi, false, false);
+  x = __uint_as_float(r[0]);
+  y = __uint_as_float(r[1]);
 }
-// sum over the 32 lanes of a token; every lane gets the total (fixed order)
-__device__ __forceinline__ float token_sum(float x) {
-  x = quad_sum(x);
-  x = x + swizzle_xor<4>(x);
+template <int MASK, int N> __device__ __forceinline__ void wht_swap_stage(float (&v)[N]) {
+#pragma unroll
+  for (int r = 0; r < N / 2; ++r) {
+    float a = v[r], b = v[r + N / 2];
+    swap_lanes<MASK>(a, b);
+    v[r] = a + b;
+    v[r + N / 2] = a - b;
+    swap_lanes<MASK>(v[r], v[r + N / 2]);
+  }
+}
+template <bool INV = false, int N> __device__ __forceinline__ void wht1024_tail(float (&v)[N], int pos) {
+  constexpr float up = INV ? 1.0f : -1.0f;               // as in wht128
+  if constexpr (N == 32) wht_lane_stage<7>(v, (pos & 4) ? up : -up);      // (N = 16: bit 2 is a coordinate of the head)
+  wht_lane_stage<8>(v, (pos & 8) ? up : -up);
+  wht_swap_stage<16>(v);
+  if constexpr (N == 16) wht_swap_stage<32>(v);
+}
+// x of this lane combined with that of the lane whose position differs in bits 4 / 5
+template <int MASK> __device__ __forceinline__ float far_sum(float x) {
+  float y = x;
+  swap_lanes<MASK>(x, y);
+  return x + y;
+}
+// The sum over the lanes of a token of a value that is the same on the lanes of 32 consecutive coordinates; every lane gets the
+// total (fixed order, the same for both widths).
+template <int N> __device__ __forceinline__ float token_sum(float x) {
+  if constexpr (N == 32) x = x + quad_xor<1>(x);
+  x = x + quad_xor<2>(x);
+  x = x + octet_mirror(x);
   x = x + row_xor8(x);
-  x = x + swizzle_xor<16>(x);
-  return x;
+  x = far_sum<16>(x);
+  return N == 16 ? far_sum<32>(x) : x;
 }
 
 // Rotation group layouts.  WIDE = false: one group = one head = a quad of lanes (g = 128).  WIDE = true: one group =
-// the whole token vector of 8 heads = 32 lanes (g = 1024).  `l` is the lane's index inside its token (0..31).
+// the whole token vector of 8 heads = 1024 / N lanes (g = 1024).  `l` is the lane's position: group_pos, or token_pos.
 template <bool WIDE> struct Rot {
   static constexpr float kNorm = WIDE ? 0.03125f : kRsqrtG;            // 1 / sqrt(g)
   static constexpr float kInvG = WIDE ? 1.0f / 1024 : 1.0f / kGroup;
   template <int N> static __device__ __forceinline__ void wht(float (&v)[N], int l) {
-    static_assert(!WIDE || N == 32, "groups across the heads: 32 values per lane");
-    wht128(v, WIDE ? l & 3 : l);
+    wht128(v, WIDE ? l & (kGroup / N - 1) : l);
     if constexpr (WIDE) wht1024_tail(v, l);
   }
   // The same transform (H_8 (x) H_128 is symmetric) with the stages across the heads first, used for the inverse:
@@ -250,18 +278,15 @@ template <bool WIDE> struct Rot {
   // Inverse-side convention (see wht128): input pre-multiplied by sign(l), true output.
   template <int N> static __device__ __forceinline__ void iwht(float (&v)[N], int l) {
     if constexpr (WIDE) wht1024_tail<true>(v, l);
-    wht128<true>(v, WIDE ? l & 3 : l);
+    wht128<true>(v, WIDE ? l & (kGroup / N - 1) : l);
   }
   // sign pending on the lane's values after wht(): -1 for every cross-lane stage in which the lane was the upper one
-  // (`l` has one bit per stage)
-  static __device__ __forceinline__ float sign(int l) { return (__builtin_popcount(l) & 1) ? -1.0f : 1.0f; }
+  // (`l` has one bit per stage; the swapping ones of wht1024_tail leave none)
+  static __device__ __forceinline__ float sign(int l) { return (__builtin_popcount(WIDE ? l & 15 : l) & 1) ? -1.0f : 1.0f; }
   // sum of the squares of the group's values
   template <int N> static __device__ __forceinline__ float square_sum(const float (&v)[N], int l) {
     if constexpr (!WIDE) return group_dot(v, v, l);
-    float ss = 0.f;
-#pragma unroll
-    for (int r = 0; r < N; ++r) ss = __fmaf_rn(v[r], v[r], ss);
-    return token_sum(ss);
+    return token_sum<N>(chain_dot(v, v, l));
   }
 };
 

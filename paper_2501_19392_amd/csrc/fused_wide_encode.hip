@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kSlabWaves * 64) void fused_wide_encode_kernel(
   const int wave = threadIdx.x >> 6;
   const int64_t m0 = (int64_t)blockIdx.x * kSlabRows;
   // the quantizer's view: 16 tokens per pass, 32 consecutive lanes per token
-  const int l = threadIdx.x & 31;                    // lane inside its token: head l / 4, quad position l % 4
+  const int l = token_pos<32>(threadIdx.x);              // position in its token: head l / 4, quad position l % 4
   const int tslot = threadIdx.x >> 5;                // token of the pass, 0..15
   const int head = l >> 2, q = l & 3;
 
