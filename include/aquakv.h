@@ -139,11 +139,12 @@ int aquakv_build_search_table(const float* codebook, int32_t vq_dim, int32_t n_c
  * rows (0 on invalid arguments).  Its front part holds the fp32 predictions of one
  * chunk of rows (fp32 layers) or the re-tiled predictor weights (bf16 layers with
  * rotation groups across the heads; nothing for the other bf16 layers); behind it
- * a temporary Khat for one chunk of rows when the caller does not ask for one (calls
- * over few rows keep partial sums there, and in Vhat, until they have finished).
+ * a temporary Khat for one chunk of rows when the caller does not ask for one (or partial
+ * sums and predictions of the call, halves of which lie in Khat / Vhat until it has finished).
  * More is used where it helps, if workspace_bytes says that it is there: with
- * rotation groups across the heads, short ranges (up to 4096 rows) are encoded in as
- * few pieces as there is room for fp32 predictions, at most kv_heads * head_dim * 4
+ * rotation groups across the heads, a Khat or Vhat that is not asked for, or is over K or V, has no
+ * room for half of the predictions, and ranges of up to 12288 rows are then encoded in as
+ * few pieces as there is room for all of them, at most kv_heads * head_dim * 4
  * bytes per row beyond what is needed and never over buffers of the call or of the
  * layer.  So what lies within workspace_bytes belongs to the call while it runs:
  * calls that run at the same time need workspaces that do not overlap. */

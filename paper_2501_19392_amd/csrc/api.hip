@@ -199,9 +199,9 @@ Plan make_plan(const aquakv_layer* L, int64_t tokens) {
   return pl;
 }
 
-// Encode of rotation groups across the 8 heads: ranges of up to kWideSplitRows rows are quantized from fp32 predictions in the
-// workspace (encode_wide), in as few pieces as there is room for them.
-constexpr int64_t kWideSplitRows = 4096;
+// Encode of rotation groups across the 8 heads (encode_wide): rows that the kernel of whole tokens takes in one round over the
+// CUs, and up to how many left over from its rounds are quantized from fp32 predictions.
+constexpr int64_t kWideRoundRows = 16384, kWideSplitRows = 12288;
 
 // Whether `all` lies over none of the call's buffers (outs: without the workspace it is part of) nor the layer's parameters.
 bool clear_of(const aquakv_layer* L, const Plan& pl, const Range& all, const Range* outs, int n_out, const Range* ins, int n_in) {
@@ -247,26 +247,31 @@ inline aquakv::QuantizeIo coded(const int8_t* signs, const void* codes, const vo
 }
 
 // Encode of n rows of one tensor with rotation groups across the 8 heads.  The kernel that owns whole tokens walks all of W in
-// every workgroup of 64 tokens: 100 us however few tokens there are.  Short ranges therefore run as predictor (on the tiles
-// of short ranges, fp32 predictions into the workspace) and stand-alone quantizer, in pieces of as many rows as the workspace
-// holds predictions for (`room` bytes): kWideSplitRows is where the two cost the same.
+// every workgroup of 64 tokens, so a round of it over the CUs costs the same however few of them it fills.  It takes whole rounds;
+// what is left over runs as predictor and stand-alone quantizer if that is cheaper than another round: predictions in fp32, half
+// of each row in the workspace (`room` bytes) and half in the row of Xhat that comes to lie over it, or, without an Xhat of its
+// own, all of it in the workspace; in pieces of as many rows as there is room for.  Keys and values, us, predictions against rounds of
+// whole tokens alone: 4096 rows 64 / 140, 8192 111 / 141, 10007 140 / 149, 12288 145 / 151, 14000 164 / 156; 20000 226 / 296.
 int encode_wide(const aquakv_layer* L, const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias,
                 const int8_t* signs, const void* X, uint8_t* codes, uint16_t* scales, void* Xhat, int64_t n, int D, float* ws,
                 size_t room, hipStream_t stream) {
   const size_t eb = elem_bytes(L->dtype), row = (size_t)D * eb;
-  const int64_t fit = (int64_t)(room / ((size_t)D * sizeof(float)));
-  const int64_t pieces = fit > 0 ? (n + fit - 1) / fit : 0, piece = pieces > 0 ? (n + pieces - 1) / pieces : 0;
-  if (n > kWideSplitRows || pieces == 0 || pieces > 4 || !aquakv::tile_predict_fits(piece, D)) {
+  const int64_t rest = n % kWideRoundRows;
+  const bool halves = Xhat != nullptr && Xhat != X;
+  const int64_t fit = (int64_t)(room / (halves ? row : (size_t)D * sizeof(float)));
+  const int64_t pieces = fit > 0 ? (rest + fit - 1) / fit : 0, piece = pieces > 0 ? (rest + pieces - 1) / pieces : 0;
+  const int64_t whole = rest > kWideSplitRows || pieces == 0 || pieces > 4 ? n : n - rest;
+  if (whole != 0)
     HIP_TRY(aquakv::launch_fused_encode_wide(quantizer_id(L), x0, d0, x1, d1, W, ws, bias, signs, L->codebook, L->search_table, X,
-                                             codes, scales, Xhat, n, D, stream));
-    return AQUAKV_OK;
-  }
-  for (int64_t r = 0; r < n; r += piece) {
+                                             codes, scales, Xhat, whole, D, stream));
+  for (int64_t r = whole; r < n; r += piece) {
     const int64_t m = n - r < piece ? n - r : piece;
-    HIP_TRY(aquakv::launch_tile_predict(at(x0, r, d0 * eb), d0, at(x1, r, d1 * eb), d1, W, bias, ws, m, D, stream));
+    const aquakv::Prediction P = halves ? aquakv::Prediction{static_cast<float*>(at(Xhat, r, row)), ws, D / 2, D / 2}
+                                        : aquakv::Prediction::contiguous(ws, D);
+    HIP_TRY(aquakv::launch_tile_predict(at(x0, r, d0 * eb), d0, at(x1, r, d1 * eb), d1, W, bias, P, m, D, stream));
     const aquakv::QuantizeIo io = {at(X, r, row), signs, codes + r * (int64_t)(D / 2 * code_bits(L) / 8),
                                    static_cast<uint16_t*>(at(scales, r, scale_row_bytes(L))), at(Xhat, r, row)};
-    HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), &io, 1, ws, L->codebook, L->search_table, m, L->kv_heads, true, stream));
+    HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), &io, 1, &P, L->codebook, L->search_table, m, L->kv_heads, true, stream));
   }
   return AQUAKV_OK;
 }
@@ -293,7 +298,8 @@ int encode_keys_chunk(const aquakv_layer* L, const Plan& pl, int64_t r0, int64_t
                                    L->b_k, Pbuf, n, pl.D, stream));
   const aquakv::QuantizeIo io = {at(K, r0, row), L->signs_k, static_cast<uint8_t*>(at(k_codes, r0, pl.code_row)),
                                  static_cast<uint16_t*>(at(k_scales, r0, srow)), khat_dst};
-  HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), &io, 1, has_k ? Pbuf : nullptr, L->codebook, L->search_table, n,
+  const aquakv::Prediction P = aquakv::Prediction::contiguous(Pbuf, pl.D);
+  HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), &io, 1, has_k ? &P : nullptr, L->codebook, L->search_table, n,
                                   L->kv_heads, is_wide(L), stream));
   return AQUAKV_OK;
 }
@@ -321,7 +327,8 @@ int encode_values_chunk(const aquakv_layer* L, const Plan& pl, int64_t r0, int64
                                    L->w_v, L->b_v, Pbuf, n, D, stream));
   const aquakv::QuantizeIo io = {at(V, r0, row), L->signs_v, static_cast<uint8_t*>(at(v_codes, r0, pl.code_row)),
                                  static_cast<uint16_t*>(at(v_scales, r0, srow)), at(Vhat, r0, row)};
-  HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), &io, 1, has_v ? Pbuf : nullptr, L->codebook, L->search_table, n,
+  const aquakv::Prediction P = aquakv::Prediction::contiguous(Pbuf, D);
+  HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), &io, 1, has_v ? &P : nullptr, L->codebook, L->search_table, n,
                                   L->kv_heads, is_wide(L), stream));
   return AQUAKV_OK;
 }
@@ -451,7 +458,8 @@ int aquakv_quantize(const aquakv_layer* L, int which, int64_t tokens, const void
   CHECK(check_scales(L, scales, "scales", true));
   CHECK(check_ptr(Xhat, "Xhat", false));
   const aquakv::QuantizeIo io = {X, which == AQUAKV_KEY ? L->signs_k : L->signs_v, codes, scales, Xhat};
-  HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), &io, 1, P, L->codebook, L->search_table, tokens, L->kv_heads,
+  const aquakv::Prediction pred = aquakv::Prediction::contiguous(P, L->kv_heads * L->head_dim);
+  HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), &io, 1, P != nullptr ? &pred : nullptr, L->codebook, L->search_table, tokens, L->kv_heads,
                                   is_wide(L), static_cast<hipStream_t>(stream)));
   return AQUAKV_OK;
 }

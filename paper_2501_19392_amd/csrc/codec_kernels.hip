@@ -29,7 +29,7 @@ constexpr int kGroupsPerBlock = kThreads / kLanesPerGroup;   // 64
 // 1024, keys and values: 2 x 53 us as two launches of one wave per SIMD.
 template <typename T, int NCW, bool WIDE, bool PRED>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED ? 3 : 4))) void quantize_kernel(
-    const QuantizeIo io0, const QuantizeIo io1, const float* __restrict__ P, const float* __restrict__ codebook,
+    const QuantizeIo io0, const QuantizeIo io1, const Prediction P, const float* __restrict__ codebook,
     const uint32_t* __restrict__ table, int64_t n_groups, int H) {
   const T* const X = static_cast<const T*>(blockIdx.y ? io1.X : io0.X);
   T* const Xhat = static_cast<T*>(blockIdx.y ? io1.Xhat : io0.Xhat);
@@ -52,10 +52,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED ?
   // instead of being held through the search (32 registers).
   constexpr int kXQuads = N * sizeof(T) / 16, kPQuads = PRED ? N / 4 : 1;
   struct Rows { u32x4 x[kXQuads]; f32x4 p[kPQuads]; };
-  const auto request_p = [&](int64_t off, f32x4 (&r)[kPQuads]) {
+  // (groups across the heads: 8 heads, a lane meets the same one in every round and so one half of the predictions)
+  const int p_col = (l / kLanes) * kGroup + q * N;
+  const float* const p_half = p_col < P.split ? P.first + p_col : P.second + (p_col - P.split);
+  const auto request_p = [&](int64_t gid, f32x4 (&r)[kPQuads]) {
     if constexpr (PRED) {
+      const float* const src = WIDE ? p_half + (gid >> 3) * P.stride : P.first + (gid * kGroup + q * N);
 #pragma unroll
-      for (int k = 0; k < N / 4; ++k) r[k] = reinterpret_cast<const f32x4*>(P + off)[k];
+      for (int k = 0; k < N / 4; ++k) r[k] = reinterpret_cast<const f32x4*>(src)[k];
     }
   };
   const auto unpack_p = [&](const f32x4 (&r)[kPQuads], float (&p)[N]) {
@@ -72,7 +76,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED ?
     const u32x4* src = reinterpret_cast<const u32x4*>(X + off);
 #pragma unroll
     for (int k = 0; k < kXQuads; ++k) r.x[k] = src[k];
-    request_p(off, r.p);
+    request_p(gid, r.p);
   };
   const int64_t stride = (int64_t)gridDim.x * kGroups;
   Rows rows;
@@ -104,11 +108,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED ?
     quantize_residual<NCW, WIDE>(v, sf, l, lds.cb, table != nullptr ? lds.table : nullptr, active, gid, codes, scales,
                                  Xhat != nullptr, [&] {
       asm volatile("" ::: "memory");                      // (not the registers of the first read)
-      if (Xhat != nullptr) request_p(off, again);
+      if (Xhat != nullptr) request_p(gid, again);
       if (g0 + stride < n_groups) request(g0 + stride, rows);
     });
     if (Xhat != nullptr) {
       unpack_p(again, p);
+      if constexpr (WIDE && PRED) {                       // a wave's rows of P may lie under those it writes: all of it has been read
+#pragma unroll
+        for (int r = 0; r < N; ++r) asm volatile("" ::"v"(p[r]) : "memory");
+      }
       finish_hat<NCW>(v, sf, p);
       if (active) Storage<T>::store(Xhat + off, v);
     }
@@ -392,21 +400,22 @@ hipError_t launch_build_search_table(const float* codebook, int n_codewords, voi
   return hipGetLastError();
 }
 
-hipError_t launch_quantize(int dtype, int n_codewords, const QuantizeIo* io, int tensors, const float* P,
+hipError_t launch_quantize(int dtype, int n_codewords, const QuantizeIo* io, int tensors, const Prediction* P,
                            const float* codebook, const void* table, int64_t T_, int H, bool wide, hipStream_t stream) {
   const int64_t n_groups = T_ * H;
   if (n_groups == 0) return hipSuccess;
   if (tensors != 1 && P != nullptr) return hipErrorInvalidValue;
+  if (P != nullptr && !wide && P->second != P->first + P->split) return hipErrorInvalidValue;      // (read as contiguous)
   const QuantizeIo& other = io[tensors - 1];
   const uint32_t* tab = static_cast<const uint32_t*>(table);
   const int per_cu = P != nullptr ? kQuantizeWgPerCu : kQuantizePlainWgPerCu;
   const dim3 grid(blocks_for(n_groups, per_cu, tensors, kThreads * kQuantizeVals / kGroup), (unsigned)tensors);
   if (P != nullptr)
     AQUAKV_DISPATCH(dtype, n_codewords, wide, (quantize_kernel<T, N, W, true><<<grid, kThreads, 0, stream>>>(
-                                                  io[0], other, P, codebook, tab, n_groups, H)));
+                                                  io[0], other, *P, codebook, tab, n_groups, H)));
   else
     AQUAKV_DISPATCH(dtype, n_codewords, wide, (quantize_kernel<T, N, W, false><<<grid, kThreads, 0, stream>>>(
-                                                  io[0], other, P, codebook, tab, n_groups, H)));
+                                                  io[0], other, Prediction{}, codebook, tab, n_groups, H)));
   return hipGetLastError();
 }
 

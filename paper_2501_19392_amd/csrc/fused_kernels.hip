@@ -407,15 +407,14 @@ hipError_t launch_fused_layer(bool encode, int n_codewords, const float* codeboo
   return launch_tile_rest(mode, n_codewords, wide, rest, stream);
 }
 
-bool tile_predict_fits(int64_t T, int D) { return ((T + 127) / 128) * (D / BN) <= 256; }
-
-hipError_t launch_tile_predict(const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias, float* P,
+hipError_t launch_tile_predict(const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias, const Prediction& P,
                                int64_t T, int D, hipStream_t stream) {
   if (T == 0) return hipSuccess;
-  if (!tile_predict_fits(T, D)) return hipErrorInvalidValue;
+  const int rows = tile_rows(1, T, D, true);
+  if (rows == 0) return launch_predict_two_heads(x0, d0, x1, d1, W, bias, P, T, D, stream);
   TileArgs a = tile_args(x0, d0, x1, d1, W, bias, nullptr, nullptr, D);
   a.P = P; a.seq_len = (int)T;
-  return launch_rows(tile_rows(1, T, D, false), kTilePredict, 16, false, 1, a, stream);
+  return launch_rows(rows, kTilePredict, 16, false, 1, a, stream);
 }
 
 hipError_t launch_fused_encode(int n_codewords, const void* x0, int d0, const void* x1, int d1, const void* W,

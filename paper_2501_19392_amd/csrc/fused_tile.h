@@ -27,7 +27,7 @@ struct TileArgs {
   uint8_t* codes;
   uint16_t* scales;
   bf16_t* Xhat;
-  float* P;                       // kTilePredict: the prediction, [T, D]
+  Prediction P;                   // kTilePredict
   const bf16_t* q;
   const float* rope_cos;
   const float* rope_sin;
@@ -166,12 +166,13 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
   const float bv = a.bias != nullptr ? a.bias[n0 + wn * 32 + frow] : 0.f;
 
   if constexpr (!kEpilogue) {
+    float* const out = (n0 < a.P.split ? a.P.first + n0 : a.P.second + (n0 - a.P.split)) + wn * 32 + frow;
 #pragma unroll
     for (int i = 0; i < S::MI; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int lrow = S::block_row(i, wm) + (r >> 2) * 8 + fk * 4 + (r & 3);
-        if (lrow < n_rows) a.P[(m0 + lrow) * a.D + n0 + wn * 32 + frow] = acc[i][r] + bv;
+        if (lrow < n_rows) out[(m0 + lrow) * a.P.stride] = acc[i][r] + bv;
       }
     return;
   } else {

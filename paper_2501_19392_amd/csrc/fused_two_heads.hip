@@ -172,6 +172,39 @@ __global__ __launch_bounds__(kWaves2 * 64) void fused_two_heads_kernel(
   }
 }
 
+// The prediction alone, in fp32 (a quantizer launch of its own follows: groups across the heads).
+__global__ __launch_bounds__(kWaves2 * 64) void predict_two_heads_kernel(const bf16_t* __restrict__ x0, int d0,
+                                                                         const bf16_t* __restrict__ x1, int d1,
+                                                                         const bf16_t* __restrict__ W, const float* __restrict__ bias,
+                                                                         const Prediction P, int64_t T, int D) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[kMainLoop2LdsBytes];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int H2 = D / BN2;
+  const int logical = remap_block(blockIdx.x, gridDim.x);
+  const int tile_m = logical / H2, pair = logical % H2;
+  const int64_t m0 = (int64_t)tile_m * BM2;
+  const int nw = (2 * pair + (wave & 1)) * kGroup;
+  const int64_t mw = m0 + (wave >> 1) * 64;
+  const int frow = lane & 31, fk = lane >> 5;
+  f32x16 acc[2][4];
+  gemm_mainloop_two_heads(smem, x0, d0, x1, d1, W, T, m0, pair * BN2, acc, [] {});
+  float bv[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) bv[j] = bias != nullptr ? bias[nw + j * 32 + frow] : 0.f;
+  float* const out = nw < P.split ? P.first + nw : P.second + (nw - P.split);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int64_t row = mw + i * 32 + (r >> 2) * 8 + fk * 4 + (r & 3);
+      if (row < T) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out[row * P.stride + j * 32 + frow] = acc[i][j][r] + bv[j];
+      }
+    }
+}
+
 template <int MODE>
 hipError_t launch2(int n_codewords, const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias,
                    const int8_t* signs, const float* codebook, const void* table, const void* X, uint8_t* codes,
@@ -214,6 +247,16 @@ bool two_heads_pays(int64_t T, int D) {
   const int64_t big = ((T + BM2 - 1) / BM2) * (D / BN2);
   const int64_t rounds_big = (big + kCUs - 1) / kCUs, rounds_small = (2 * big + kCUs - 1) / kCUs;
   return 2 * rounds_big <= rounds_small;
+}
+
+hipError_t launch_predict_two_heads(const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias, const Prediction& P,
+                                    int64_t T, int D, hipStream_t stream) {
+  if (T == 0) return hipSuccess;
+  if (D % BN2 != 0) return hipErrorInvalidValue;
+  const unsigned blocks = (unsigned)(((T + BM2 - 1) / BM2) * (D / BN2));
+  predict_two_heads_kernel<<<blocks, kWaves2 * 64, 0, stream>>>(static_cast<const bf16_t*>(x0), d0, static_cast<const bf16_t*>(x1), d1,
+                                                                static_cast<const bf16_t*>(W), bias, P, T, D);
+  return hipGetLastError();
 }
 
 hipError_t launch_fused_decode_two_heads(int n_codewords, const void* x0, int d0, const void* x1, int d1, const void* W,

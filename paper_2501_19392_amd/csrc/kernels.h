@@ -20,10 +20,21 @@ struct QuantizeIo {
   uint16_t* scales;
   void* Xhat;                 // reconstruction (quantize: nullable)
 };
+// fp32 predictions [T, D], row t: outputs [0, split) at first + t * stride and the others at second + t * stride.  (Groups across
+// the heads keep them in two halves, one of them in the rows of Xhat that the quantizer will write: contiguous() is the plain form.)
+struct Prediction {
+  float *first, *second;
+  int64_t stride;
+  int split;
+  static Prediction contiguous(const float* P, int D) {
+    return {const_cast<float*>(P), const_cast<float*>(P) + D / 2, D, D / 2};
+  }
+};
 // Q(X - P): codes, scales and (optionally) the reconstruction of io[0 .. tensors - 1] (1 or 2; 2 only without P), T rows each.
 // wide: rotation groups of 1024 = the whole token (H must be 8), scales [T] instead of [T, H].
 // `table` (nullable): nearest-grid-point search table from launch_build_search_table.
-hipError_t launch_quantize(int dtype, int n_codewords, const QuantizeIo* io, int tensors, const float* P,
+// wide: P may share its rows with Xhat (2 T D bytes of it, in the halves form): a wave reads its token's before it writes it.
+hipError_t launch_quantize(int dtype, int n_codewords, const QuantizeIo* io, int tensors, const Prediction* P,
                            const float* codebook, const void* table, int64_t T, int H, bool wide, hipStream_t stream);
 
 // 64 x 64 cells x 4 candidate bytes = 16 KiB, and 128 overflow lists of 8 candidate bytes.
@@ -48,9 +59,9 @@ hipError_t launch_fused_encode(int n_codewords, const void* x0, int d0, const vo
                                const float* bias, const int8_t* signs, const float* codebook, const void* table,
                                const void* X, uint8_t* codes, uint16_t* scales, void* Xhat, int64_t T, int D,
                                hipStream_t stream);
-// P[T, D] of launch_predict (bf16, same bits) on the tiles of short ranges (fused_tile.h); T at most 128 rows per 256 / (D / 128) tiles.
-bool tile_predict_fits(int64_t T, int D);
-hipError_t launch_tile_predict(const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias, float* P,
+// The prediction of launch_predict (bf16, same bits) on whichever tiles of the fused forms suit the number of rows; P.split a multiple
+// of 256 (D a multiple of 256) or of 128.
+hipError_t launch_tile_predict(const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias, const Prediction& P,
                                int64_t T, int D, hipStream_t stream);
 // The encoder for rotation groups of 1024 (8 heads): a workgroup owns 64 tokens x all heads.  `w_retiled`: device scratch of
 // 1024 * (d0 + d1) * 2 bytes, 16-byte aligned, that the call fills with the weights in the order its main loop reads them.
@@ -93,6 +104,8 @@ hipError_t launch_fused_layer(bool encode, int n_codewords, const float* codeboo
 // fill the chip more than once (below that: fused_tile.h) when two_heads_pays(T, D): when the larger tile costs no extra
 // round over the CUs.
 bool two_heads_pays(int64_t T, int D);
+hipError_t launch_predict_two_heads(const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias, const Prediction& P,
+                                    int64_t T, int D, hipStream_t stream);
 hipError_t launch_fused_encode_two_heads(int n_codewords, const void* x0, int d0, const void* x1, int d1, const void* W,
                                          const float* bias, const int8_t* signs, const float* codebook, const void* table,
                                          const void* X, uint8_t* codes, uint16_t* scales, void* Xhat, int64_t T, int D,

@@ -197,3 +197,38 @@ def test_keys_and_values_of_few_rows_at_once(T, quantizer, rht_group):
         torch.cuda.synchronize()
         assert torch.equal(bits(kd), bits(Kh)) and torch.equal(bits(vd), bits(Vh))
     assert torch.equal(arena[need:], bits(lg.w_v).flatten())
+
+
+@pytest.mark.parametrize("T", [2049, 12288, 12289, 16384, 16417])
+@pytest.mark.parametrize("quantizer", ["n16", "n64", "rtn2"])
+def test_groups_across_heads_over_the_rounds_of_whole_tokens(T, quantizer):
+    """Long ranges: rounds of the kernel that owns whole tokens, and the rows left over from predictions whose halves lie in the
+    workspace and in the rows of the reconstruction (its own, over the input, or none): the bits of the stage calls."""
+    from paper_2501_19392_amd import binding as B
+    print(f"case wide rounds T={T} {quantizer}", flush=True)
+    lg, D = layer(8, 1024, quantizer, 1024, bias=T % 2 == 1), 1024
+    g = torch.Generator(device="cuda").manual_seed(T)
+    K, V, Kp, Vp = (torch.randn(T, 8, 128, generator=g, device="cuda").bfloat16() for _ in range(4))
+    P = torch.empty(T, D, dtype=torch.float32, device="cuda")
+    new = lambda: [*lg.alloc_codes(T), *lg.alloc_codes(T)]
+    want, Kh, Vh = new(), lg.alloc_kv(T), lg.alloc_kv(T)
+    for which, x0, x1, X, c, s, hat in ((B.AQUAKV_KEY, Kp, None, K, *want[:2], Kh), (B.AQUAKV_VALUE, Vp, Kh, V, *want[2:], Vh)):
+        B.aquakv_predict(lg, which, T, x0, x1, P)
+        B.aquakv_quantize(lg, which, T, X, P, c, s, hat)
+    need = B.aquakv_workspace_bytes(lg, T)
+    for keys, values in (("own", "own"), ("in place", "own"), ("own", "in place"), (None, None)):
+        arena = torch.full((need + 4096,), 0xCD, dtype=torch.uint8, device="cuda")
+        got, k, v = new(), K.clone(), V.clone()
+        kh = {"own": lg.alloc_kv(T), "in place": k, None: None}[keys]
+        vh = {"own": lg.alloc_kv(T), "in place": v, None: None}[values]
+        B.aquakv_encode_layer(lg, T, k, v, Kp, Vp, *got, kh, vh, arena[:need])
+        torch.cuda.synchronize()
+        for a, b in list(zip(got, want)) + [(kh, Kh), (vh, Vh)]:
+            assert a is None or torch.equal(bits(a), bits(b)), (keys, values)
+        assert bool((arena[need:] == 0xCD).all())
+    kh = lg.alloc_kv(T)                               # the halves, with the least workspace they need
+    got, ws = new(), torch.empty(D * 2 * D * 2, dtype=torch.uint8, device="cuda")
+    B.aquakv_encode_keys(lg, T, K, Kp, got[0], got[1], kh, ws)
+    B.aquakv_encode_values(lg, T, V, Vp, kh, got[2], got[3], None, ws)
+    torch.cuda.synchronize()
+    assert all(torch.equal(bits(a), bits(b)) for a, b in zip(got, want)) and torch.equal(bits(kh), bits(Kh))
