@@ -1258,22 +1258,52 @@ int aquakv_attend_cache(const aquakv_cache_layer* layers, int32_t n_layers, cons
   }
   float* const part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + decode_bytes);
   const int64_t part_elems = pieces * sh->q_heads * 128, layer_elems = (int64_t)(one / sizeof(float));
+  // where layer l's codes and scales are read (k_codes, k_scales, v_codes, v_scales), and its recovered tensors go
+  struct Coded { const uint8_t* k_codes; const uint16_t* k_scales; const uint8_t* v_codes; const uint16_t* v_scales; };
+  const auto coded_at = [&](int32_t l) {
+    const aquakv_cache_layer& c = layers[l];
+    if (!adjacent) return Coded{c.staged_k_codes, c.staged_k_scales, c.staged_v_codes, c.staged_v_scales};
+    const size_t crow = make_plan(c.layer, 1).code_row, srow = scale_row_bytes(c.layer);
+    return Coded{static_cast<const uint8_t*>(at(c.k_codes, first_row, crow)), static_cast<const uint16_t*>(at(c.k_scales, first_row, srow)),
+                 static_cast<const uint8_t*>(at(c.v_codes, first_row, crow)), static_cast<const uint16_t*>(at(c.v_scales, first_row, srow))};
+  };
+  // The keys of a layer need the keys before, not its values: where a launch for one tensor leaves CUs idle, the values of layer l
+  // and the keys of layer l + 1 are recovered together.  The keys go to the buffer of layer l - 1's, whose last reader has been queued.
+  const auto with_next = [&](int32_t l) {
+    const aquakv_layer *a = layers[l].layer, *b = l + 1 < n_layers ? layers[l + 1].layer : nullptr;
+    return a != nullptr && b != nullptr && a->dtype == AQUAKV_BF16 && a->d_in_v != 0 && b->d_in_k != 0 && quantizer_id(a) == quantizer_id(b) &&
+           is_wide(a) == is_wide(b) && aquakv::fused_decode_pair_pays(compressed, a->kv_heads * 128);
+  };
   const void *Kp = nullptr, *Vp = nullptr;
   int held = 0;
+  bool have_keys = false;                                        // of this layer, from the launch of the one before
   for (int32_t l = 0; l < n_layers; ++l) {
     const aquakv_cache_layer& c = layers[l];
     void *K = hat[2 * (l & 1)], *V = hat[2 * (l & 1) + 1];
     if (compressed != 0 && c.layer != nullptr) {
-      const size_t crow = make_plan(c.layer, 1).code_row, srow = scale_row_bytes(c.layer);
-      const auto codes = [&](const uint8_t* own, const uint8_t* staged) {
-        return adjacent ? static_cast<const uint8_t*>(at(own, first_row, crow)) : staged;
-      };
-      const auto scales = [&](const uint16_t* own, const uint16_t* staged) {
-        return adjacent ? static_cast<const uint16_t*>(at(own, first_row, srow)) : staged;
-      };
-      CHECK(aquakv_decode_layer(c.layer, compressed, codes(c.k_codes, c.staged_k_codes), scales(c.k_scales, c.staged_k_scales),
-                                codes(c.v_codes, c.staged_v_codes), scales(c.v_scales, c.staged_v_scales), Kp, Vp, K, V, workspace,
-                                decode_bytes, stream));
+      const Coded in = coded_at(l);
+      const bool pair = with_next(l);
+      if (!have_keys && !pair) {
+        CHECK(aquakv_decode_layer(c.layer, compressed, in.k_codes, in.k_scales, in.v_codes, in.v_scales, Kp, Vp, K, V, workspace,
+                                  decode_bytes, stream));
+      } else {
+        if (!have_keys)
+          CHECK(aquakv_decode_layer(c.layer, compressed, in.k_codes, in.k_scales, nullptr, nullptr, Kp, nullptr, K, nullptr, workspace,
+                                    decode_bytes, stream));
+        if (pair) {
+          const aquakv_layer *a = c.layer, *b = layers[l + 1].layer;
+          const Coded next = coded_at(l + 1);
+          const int D = a->kv_heads * 128;
+          const aquakv::FusedTensor v = {Vp, K, a->d_in_v - D, D, a->w_v, a->b_v, a->signs_v, nullptr, const_cast<uint8_t*>(in.v_codes),
+                                         const_cast<uint16_t*>(in.v_scales), V};
+          const aquakv::FusedTensor k = {K, nullptr, b->d_in_k, 0, b->w_k, b->b_k, b->signs_k, nullptr, const_cast<uint8_t*>(next.k_codes),
+                                         const_cast<uint16_t*>(next.k_scales), hat[2 * (~l & 1)]};
+          HIP_TRY(aquakv::launch_fused_decode_pair(quantizer_id(a), a->codebook, v, b->codebook, k, compressed, D, is_wide(a), stream));
+        } else {
+          CHECK(aquakv_decode_values(c.layer, compressed, in.v_codes, in.v_scales, Vp, K, V, workspace, decode_bytes, stream));
+        }
+      }
+      have_keys = pair;
       Kp = K; Vp = V;
     } else if (compressed != 0 && adjacent) {
       Kp = at(c.raw_k, first_row, row); Vp = at(c.raw_v, first_row, row);

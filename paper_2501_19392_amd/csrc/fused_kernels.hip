@@ -379,7 +379,40 @@ TileArgs tile_args(const void* x0, int d0, const void* x1, int d1, const void* W
   return a;
 }
 
+TileArgs tensor_args(const FusedTensor& t, const float* codebook, int64_t T, int D) {
+  TileArgs a = tile_args(t.x0, t.d0, t.x1, t.d1, t.W, t.bias, t.signs, codebook, D);
+  a.X = static_cast<const bf16_t*>(t.X);
+  a.codes = t.codes; a.scales = t.scales; a.Xhat = static_cast<bf16_t*>(t.Xhat); a.seq_len = (int)T;
+  return a;
+}
+
+// Rows per tile for values and keys of T rows in one launch (launch_fused_decode_pair), 0: two launches are as good.
+//
+// A launch for one tensor of few rows is bound by the latency of its k-tiles and leaves CUs idle, so the other tensor's tiles come
+// for little: the smallest tile with which both fit the CUs in one round (2048 rows of 8 heads), and tiles of 128 rows up to half a
+// round more.  Attention over a cache of six layers, us a token, apart / together: 300 tokens 145 / 115, 1100 155 / 138, 2000 192 / 177,
+// 2 x 1500 236 / 219.  From there on the CUs that a launch leaves idle are worth less than the clock it gains by them: tiles of 256
+// rows at 5376 rows, which would fill the chip with both, 561 / 582 us for eight layers, tiles of 320 rows 557 / 570.
+int pair_rows(int64_t T, int D) {
+  const int64_t H = D / BN;
+  for (const int rows : {32, 64, 128})
+    if (2 * ((T + rows - 1) / rows) * H <= (rows == 128 ? 384 : 256)) return rows;
+  return 0;
+}
+
 }  // namespace
+
+bool fused_decode_pair_pays(int64_t T, int D) { return pair_rows(T, D) != 0; }
+hipError_t launch_fused_decode_pair(int n_codewords, const float* values_codebook, const FusedTensor& values, const float* keys_codebook,
+                                    const FusedTensor& keys, int64_t T, int D, bool wide, hipStream_t stream) {
+  if (T == 0) return hipSuccess;
+  const TileArgs v = tensor_args(values, values_codebook, T, D), k = tensor_args(keys, keys_codebook, T, D);
+  const int rows = pair_rows(T, D);
+  if (rows == 32) return launch_pair_32(kTileDecode, n_codewords, wide, v, k, stream);
+  if (rows == 64) return launch_pair_64(kTileDecode, n_codewords, wide, v, k, stream);
+  if (rows == 128) return launch_pair_128(kTileDecode, n_codewords, wide, v, k, stream);
+  return hipErrorInvalidValue;
+}
 
 // Tiles of 32 rows for both products on the CUs at once.  With tiles of 64 rows for the first launch, up to twice the rows,
 // 600 tokens of 8 heads take 24.3 us to encode against 22.9 one after the other, 1000 tokens 25.5 against 23.8.
@@ -390,9 +423,8 @@ hipError_t launch_fused_layer(bool encode, int n_codewords, const float* codeboo
   if (T == 0) return hipSuccess;
   if (!fused_layer_fits(T, D) || (encode && wide) || values.Xhat == nullptr || values.Xhat == values.X) return hipErrorInvalidValue;
   const auto args = [&](const FusedTensor& t) {
-    TileArgs a = tile_args(t.x0, t.d0, t.x1, t.d1, t.W, t.bias, t.signs, codebook, D);
-    a.table = static_cast<const uint32_t*>(table); a.X = static_cast<const bf16_t*>(t.X);
-    a.codes = t.codes; a.scales = t.scales; a.Xhat = static_cast<bf16_t*>(t.Xhat); a.seq_len = (int)T;
+    TileArgs a = tensor_args(t, codebook, T, D);
+    a.table = static_cast<const uint32_t*>(table);
     return a;
   };
   const int mode = encode ? kTileEncode : kTileDecode;
@@ -403,7 +435,7 @@ hipError_t launch_fused_layer(bool encode, int n_codewords, const float* codeboo
     a->sums_hi = static_cast<uint16_t*>(values.Xhat);
     a->sums_lo = static_cast<uint16_t*>(sums);
   }
-  if (const hipError_t e = launch_tile_pair(mode, n_codewords, wide, args(keys), first, stream)) return e;
+  if (const hipError_t e = launch_pair_32(mode, n_codewords, wide, args(keys), first, stream)) return e;
   return launch_tile_rest(mode, n_codewords, wide, rest, stream);
 }
 

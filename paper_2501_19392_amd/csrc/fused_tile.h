@@ -41,7 +41,8 @@ struct TileArgs {
   uint16_t* sums_hi;
   uint16_t* sums_lo;
 };
-// Two products in one launch: the first `blocks` workgroups work on job[0], the others store the sums of job[1] and nothing else.
+// Two products in one launch: the first `blocks` workgroups work on job[0], the others on job[1], or (tiles of 32 rows) store the
+// sums of job[1] and nothing else if it has a place for them.
 struct TilePair {
   TileArgs job[2];
   int blocks;
@@ -245,8 +246,8 @@ __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per
   // read from where they were passed (an index into a copy would put them in scratch)
   TileArgs a;
   __builtin_memcpy(&a, (const char*)__builtin_amdgcn_kernarg_segment_ptr() + second * (int)sizeof(TileArgs), sizeof(TileArgs));
-  fused_tile<NCW, MODE, MB, WIDE, kKeepSums>(a, (int)blockIdx.x - (second ? pair.blocks : 0), second ? (int)gridDim.x - pair.blocks : pair.blocks,
-                                             second != 0);
+  fused_tile<NCW, MODE, MB, WIDE, MB == 1 ? kKeepSums : kNoSums>(a, (int)blockIdx.x - (second ? pair.blocks : 0),
+                                                                 second ? (int)gridDim.x - pair.blocks : pair.blocks, a.sums_hi != nullptr);
 }
 
 // rows per tile 32, 64, 128 or 320 (one translation unit each); tiles_per_seq is filled in
@@ -256,9 +257,13 @@ AQUAKV_TILE_LAUNCHER(32);
 AQUAKV_TILE_LAUNCHER(64);
 AQUAKV_TILE_LAUNCHER(128);
 AQUAKV_TILE_LAUNCHER(320);
-// Tiles of 32 rows, encode or decode: `a` beside a second product of the same number of rows whose sums are stored, and a product
-// that goes on from stored sums.
-hipError_t launch_tile_pair(int mode, int n_codewords, bool wide, const TileArgs& a, const TileArgs& sums, hipStream_t stream);
+// Two jobs of one mode and quantizer (TilePair): decode, and encode on tiles of 32 rows for sums.
+#define AQUAKV_PAIR_LAUNCHER(ROWS) \
+  hipError_t launch_pair_##ROWS(int mode, int n_codewords, bool wide, const TileArgs& a, const TileArgs& b, hipStream_t stream)
+AQUAKV_PAIR_LAUNCHER(32);
+AQUAKV_PAIR_LAUNCHER(64);
+AQUAKV_PAIR_LAUNCHER(128);
+// Tiles of 32 rows, encode or decode: a product that goes on from stored sums.
 hipError_t launch_tile_rest(int mode, int n_codewords, bool wide, const TileArgs& a, hipStream_t stream);
 
 #define AQUAKV_TILE_N(MODE, WIDE)                                  \
@@ -282,6 +287,30 @@ hipError_t launch_tile(int mode, int n_codewords, bool wide, int n_seq, TileArgs
   else if (mode == kTileDecode) AQUAKV_TILE_N(kTileDecode, false);
   else if (wide) AQUAKV_TILE_N(kTileScores, true);
   else AQUAKV_TILE_N(kTileScores, false);
+#undef AQUAKV_TILE
+  return hipGetLastError();
+}
+
+template <int MB>
+hipError_t launch_pair(int mode, int n_codewords, bool wide, const TileArgs& a, const TileArgs& b, hipStream_t stream) {
+  using S = Tile<MB>;
+  TilePair pair = {{a, b}, 0};
+  int blocks[2];
+  for (int i = 0; i < 2; ++i) {
+    TileArgs& job = pair.job[i];
+    job.tiles_per_seq = (job.seq_len + S::kRows - 1) / S::kRows;
+    blocks[i] = job.tiles_per_seq * (job.D / kGroup);
+  }
+  pair.blocks = blocks[0];
+#define AQUAKV_TILE(N, MODE, WIDE) fused_tile_pair_kernel<N, MODE, MB, WIDE><<<blocks[0] + blocks[1], S::kThreads, 0, stream>>>(pair)
+  if (mode == kTileDecode && wide) AQUAKV_TILE_N(kTileDecode, true);
+  else if (mode == kTileDecode) AQUAKV_TILE_N(kTileDecode, false);
+  else if constexpr (MB == 1) {
+    if (mode != kTileEncode || wide) return hipErrorInvalidValue;
+    AQUAKV_TILE_N(kTileEncode, false);
+  } else {
+    return hipErrorInvalidValue;
+  }
 #undef AQUAKV_TILE
   return hipGetLastError();
 }

@@ -96,6 +96,10 @@ struct FusedTensor {
   void* Xhat;
 };
 bool fused_layer_fits(int64_t T, int D);
+// Values of one layer and keys of the next one (which need nothing of those values), decoded in one launch; same quantizer.
+bool fused_decode_pair_pays(int64_t T, int D);
+hipError_t launch_fused_decode_pair(int n_codewords, const float* values_codebook, const FusedTensor& values, const float* keys_codebook,
+                                    const FusedTensor& keys, int64_t T, int D, bool wide, hipStream_t stream);
 hipError_t launch_fused_layer(bool encode, int n_codewords, const float* codebook, const void* table, const FusedTensor& keys,
                               const FusedTensor& values, void* sums, int64_t T, int D, bool wide, hipStream_t stream);
 

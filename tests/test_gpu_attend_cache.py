@@ -111,3 +111,34 @@ def test_attend_refuses_what_does_not_fit():
         args = dict(n_sink=[4], n_compressed=[32], n_recent=[4], workspace=A["ws"]) | bad
         with pytest.raises(B.AquaKVError):
             B.aquakv_attend_cache(A["layers"], A["shape"], score_scale=1.0, hat=A["hat"], **args)
+
+
+@pytest.mark.parametrize("rht_group", [None, 1024])
+@pytest.mark.parametrize("n", [1029, 2150, 3060, 3300])
+def test_values_and_next_keys_recovered_together(n, rht_group):
+    """Few compressed tokens: the values of a layer and the keys of the next one in one launch, on tiles of 32, 64 and 128 rows (and
+    not at all at the last length), layers of other quantizers and a 16-bit layer between them: the last two layers' recovered
+    tensors have the bits of the sweep, and every layer the attention over the tensors of the sweep."""
+    from paper_2501_19392_amd.cache import AquaKVCache
+    print(f"case recovered together n={n} group={rht_group}", flush=True)
+    H, QH, D = 8, 16, 1024
+    gen = torch.Generator().manual_seed(n)
+    kw = {"rht_group": rht_group} if rht_group else {}
+    layers, kv, qs = [], [], []
+    for l, points in enumerate((256, 16, 16, 64, None, 64, 64, 16)):
+        w = [None, None] if l == 0 else [0.3 * torch.randn(D, d, generator=gen) / d ** 0.5 for d in (D, 2 * D)]
+        layers.append(None if points is None else U.make_layers(H, "bf16", points, layer_idx=l, w_k=w[0], w_v=w[1], **kw)[1])
+        kv.append(tuple(torch.randn(n, H, 128, generator=gen).bfloat16().cuda() for _ in range(2)))
+        qs.append(torch.randn(QH, 128, generator=gen).bfloat16().cuda())
+    for count in (len(layers), len(layers) - 1):             # the last layer behind a pair, and behind none
+        cache = AquaKVCache(layers[:count], max_tokens=n, sink_tokens=4, buffer_tokens=64)
+        cache.append(kv[:count])
+        got = [o.clone() for o in cache.attend(qs[:count], 128 ** -0.5)]
+        c = cache.n_compressed
+        hat = [t[:c].clone() for t in cache._attend["hat"]]
+        for l, K, V in cache.sweep():
+            want = plain_attention(qs[l], K, V, 128 ** -0.5, None)
+            assert float((got[l].double() - want).abs().max() / V.double().square().mean().sqrt()) < 1e-5, l
+            if l >= count - 2:
+                for a, b in zip(hat[2 * (l & 1):2 * (l & 1) + 2], (K[4:4 + c], V[4:4 + c])):
+                    assert torch.equal(a.view(torch.int16), b.contiguous().view(torch.int16)), l
