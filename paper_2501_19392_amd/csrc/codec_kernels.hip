@@ -16,7 +16,7 @@ namespace aquakv {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kQuantizeVals = 16;                            // values per lane in the quantizer
+constexpr int kQuantizeVals = 16, kDequantizeVals = 16;      // values per lane
 constexpr int kGroupsPerBlock = kThreads / kLanesPerGroup;   // 64
 
 // ------------------------------------------------------------------ quantize
@@ -85,7 +85,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED ?
     int64_t gid = g0 + slot;
     const bool active = gid < n_groups;
     if (!active) gid = n_groups - 1;                      // keep every lane in the DPP exchanges
-    const int64_t off = gid * kGroup + q * N;
 
     float v[N], p[N];
     if constexpr (sizeof(T) == 2) {
@@ -118,13 +117,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED ?
         for (int r = 0; r < N; ++r) asm volatile("" ::"v"(p[r]) : "memory");
       }
       finish_hat<NCW>(v, sf, p);
-      if (active) Storage<T>::store(Xhat + off, v);
+      if (active) Storage<T>::store(Xhat + gid * kGroup + q * N, v);
     }
   }
 }
 
 // ------------------------------------------------------------------ dequantize
 // blockIdx.y: which of the one or two tensors of the launch (X unused)
+// Bound by its stores, of which a lane with 16 values makes half as scattered ones as with 32 (16-byte pieces of 32 or of 64 bytes
+// per lane: 5.6 against 3.3 TB/s), and by latency in few waves.  Keys and values without predictors, 16 points: 8192 tokens
+// 15.1 -> 11.1 us, 131072 229 -> 171; 256 points, groups across the heads: 18.4 -> 14.7, 263 -> 198.
 template <typename T, int NCW, bool WIDE>
 __global__ __launch_bounds__(kThreads) void dequantize_kernel(const QuantizeIo io0, const QuantizeIo io1,
                                                               const float* __restrict__ P,
@@ -136,43 +138,44 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(const QuantizeIo i
   __shared__ float4 cb[is_rtn(NCW) ? 1 : NCW];
   load_codebook<NCW>(codebook, cb);
   __syncthreads();
-  const int l = WIDE ? token_pos<32>(threadIdx.x) : (int)threadIdx.x & 3, q = l & 3;
+  constexpr int N = kDequantizeVals, kLanes = kGroup / N, kGroups = kThreads / kLanes;       // lanes per group, groups per round
+  const int l = WIDE ? token_pos<N>(threadIdx.x) : group_pos<N>(threadIdx.x), q = l & (kLanes - 1), slot = threadIdx.x / kLanes;
   // A thread meets the same head in every round of the grid-stride loop when the stride is a multiple of H (it is
   // for the power-of-two head counts in use): the signs are then fetched once.
-  float sf[32] = {};
-  const bool fixed_head = kGroupsPerBlock % H == 0;
+  float sf[N] = {};
+  const bool fixed_head = kGroups % H == 0;
   if constexpr (!is_rtn(NCW)) {
-    if (fixed_head) load_signs(signs, (int)((blockIdx.x * (unsigned)kGroupsPerBlock + (threadIdx.x >> 2)) % (unsigned)H), q, sf);
+    if (fixed_head) load_signs(signs, (int)((blockIdx.x * (unsigned)kGroups + slot) % (unsigned)H), q, sf);
   }
   // the code and scale words of the next round are requested before the current round is worked on
   const auto request = [&](int64_t g0) {
-    int64_t gid = g0 + (threadIdx.x >> 2);
+    int64_t gid = g0 + slot;
     gid = gid < n_groups ? gid : n_groups - 1;
-    return request_words<NCW, WIDE>(codes, scales, gid, q);
+    return request_words<NCW, WIDE, N>(codes, scales, gid, q);
   };
-  const int64_t stride = (int64_t)gridDim.x * kGroupsPerBlock;
+  const int64_t stride = (int64_t)gridDim.x * kGroups;
   CodeWords cur = {};
-  if ((int64_t)blockIdx.x * kGroupsPerBlock < n_groups) cur = request((int64_t)blockIdx.x * kGroupsPerBlock);
-  for (int64_t g0 = (int64_t)blockIdx.x * kGroupsPerBlock; g0 < n_groups; g0 += stride) {
+  if ((int64_t)blockIdx.x * kGroups < n_groups) cur = request((int64_t)blockIdx.x * kGroups);
+  for (int64_t g0 = (int64_t)blockIdx.x * kGroups; g0 < n_groups; g0 += stride) {
     CodeWords nxt = {};
     if (g0 + stride < n_groups) nxt = request(g0 + stride);
-    int64_t gid = g0 + (threadIdx.x >> 2);
+    int64_t gid = g0 + slot;
     const bool active = gid < n_groups;
     if (!active) gid = n_groups - 1;
-    const int64_t off = gid * kGroup + q * kValsPerLane;
+    const int64_t off = gid * kGroup + q * N;
 
-    float p[32], z[32];
+    float p[N], z[N];
     if (P != nullptr) {
       load_f32(P + off, p);
     } else {
 #pragma unroll
-      for (int r = 0; r < 32; ++r) p[r] = 0.f;
+      for (int r = 0; r < N; ++r) p[r] = 0.f;
     }
     if constexpr (!is_rtn(NCW)) {
       if (!fixed_head) load_signs(signs, (int)(gid % H), q, sf);     // (a 64-bit remainder: kept off the common path)
     }
     dequantize_words<NCW, WIDE>(cur, p, sf, l, cb, z);
-    if (active) Storage<T>::store(Xhat + off, z);
+    if (active) Storage<T>::store(Xhat + gid * kGroup + q * N, z);
     cur = nxt;
   }
 }
@@ -352,10 +355,10 @@ __global__ __launch_bounds__(1024) void build_overflow_kernel(const float* __res
 }
 
 // Workgroups per CU (256 CUs), the kernels grid-stride.  The quantizer stages 21 KiB of grid and cell table per workgroup,
-// more than the 16 KiB of rows of one round: with at most the resident number of workgroups the staging is paid once and
-// the request of the next round's rows has a next round to run ahead of (measured at 32768 tokens: 52 us against 67 us with
-// 16 per CU).  The inverse stages 256 B and runs four waves per SIMD; four workgroups per CU were the best of 2 / 4 / 8 / 16
-// at 32768 tokens (25.7 against 29 us with 16).  Below that number the rounds are shared out evenly.
+// more than the 8 KiB of rows of one round: with at most the resident number of workgroups the staging is paid once and
+// the request of the next round's rows has a next round to run ahead of.  The inverse stages 256 B to 4 KiB; keys and values of
+// 131072 tokens, 16 points: 171 us with four workgroups per CU, 178 with six or eight (of 8192 tokens 11.1 with any of them).
+// Below that number the rounds are shared out evenly.
 constexpr int kQuantizeWgPerCu = 3, kQuantizePlainWgPerCu = 4;     // with a prediction, without
 constexpr int kDequantizeWgPerCu = 4;
 inline unsigned blocks_for(int64_t n_groups, int per_cu, int tensors = 1, int groups_per_block = kGroupsPerBlock) {
@@ -424,7 +427,7 @@ hipError_t launch_dequantize(int dtype, int n_codewords, const QuantizeIo* io, i
   const int64_t n_groups = T_ * H;
   if (n_groups == 0) return hipSuccess;
   if (tensors != 1 && P != nullptr) return hipErrorInvalidValue;
-  const dim3 grid(blocks_for(n_groups, kDequantizeWgPerCu, tensors), (unsigned)tensors);
+  const dim3 grid(blocks_for(n_groups, kDequantizeWgPerCu, tensors, kThreads * kDequantizeVals / kGroup), (unsigned)tensors);
   AQUAKV_DISPATCH(dtype, n_codewords, wide, (dequantize_kernel<T, N, W><<<grid, kThreads, 0, stream>>>(
                                                 io[0], io[tensors - 1], P, codebook, n_groups, H)));
   return hipGetLastError();
