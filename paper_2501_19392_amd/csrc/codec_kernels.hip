@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED ?
         for (int r = 0; r < N; ++r) asm volatile("" ::"v"(p[r]) : "memory");
       }
       finish_hat<NCW>(v, sf, p);
-      if (active) Storage<T>::store(Xhat + gid * kGroup + q * N, v);
+      if (active) Storage<T>::template store<false>(Xhat + gid * kGroup, q, v);
     }
   }
 }
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(const QuantizeIo i
       if (!fixed_head) load_signs(signs, (int)(gid % H), q, sf);     // (a 64-bit remainder: kept off the common path)
     }
     dequantize_words<NCW, WIDE>(cur, p, sf, l, cb, z);
-    if (active) Storage<T>::store(Xhat + gid * kGroup + q * N, z);
+    if (active) Storage<T>::template store<false>(Xhat + gid * kGroup, q, z);
     cur = nxt;
   }
 }
@@ -232,7 +232,7 @@ __global__ __launch_bounds__(kThreads) void attn_scores_kernel(
     }
     dequantize_words<NCW, WIDE>(cur, p, sf, l, cb, z);
     cur = nxt;
-    if (Khat_out != nullptr && active) Storage<T>::store(Khat_out + off, z);
+    if (Khat_out != nullptr && active) Storage<T>::template store<WIDE>(Khat_out + gid * kGroup, q, z);
 #pragma unroll
     for (int r = 0; r < 32; ++r) z[r] = Storage<T>::round(z[r]);      // score the stored keys
     if (rope_cos != nullptr) rope128(z, q, rope_cos + t * (kGroup / 2), rope_sin + t * (kGroup / 2));   // cached before RoPE

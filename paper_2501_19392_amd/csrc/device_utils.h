@@ -32,6 +32,31 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 // ---------------------------------------------------------------- 32-value row access
 template <typename T> struct Storage;
 
+// Two-by-two exchange of 16-byte registers between lanes whose positions differ in MASK (1 or 2, inside a quad): the lane without
+// that bit keeps a and gets its partner's a for b, the other one keeps b and gets its partner's b for a.  REVERSED: the odd quads
+// hold their positions in reverse (token_pos).  One instruction per
+// dword: a conditional move whose other side comes through a DPP quad permute.  (Two idle issue slots ahead of a DPP read of a
+// register that was just written.)
+#define AQUAKV_CND_DPP(out, keep, far, perm) \
+  "v_cndmask_b32_dpp %" #out ", %" #far ", %" #keep ", vcc quad_perm:" perm " row_mask:0xf bank_mask:0xf\n\t"
+#define AQUAKV_EXCHANGE(perm)                                                                                             \
+  "s_mov_b64 vcc, %16\n\ts_nop 1\n\t" AQUAKV_CND_DPP(0, 8, 12, perm) AQUAKV_CND_DPP(1, 9, 13, perm)                      \
+  AQUAKV_CND_DPP(2, 10, 14, perm) AQUAKV_CND_DPP(3, 11, 15, perm) "s_not_b64 vcc, vcc\n\t" AQUAKV_CND_DPP(4, 12, 8, perm) \
+  AQUAKV_CND_DPP(5, 13, 9, perm) AQUAKV_CND_DPP(6, 14, 10, perm) AQUAKV_CND_DPP(7, 15, 11, perm)
+template <int MASK, bool REVERSED> __device__ __forceinline__ void quad_exchange(u32x4& a, u32x4& b) {
+  static_assert(MASK == 1 || MASK == 2, "mask");
+  const uint64_t without = 0x0101010101010101ull * (MASK == 1 ? (REVERSED ? 0xA5 : 0x55) : (REVERSED ? 0xC3 : 0x33));
+  uint32_t o[8];
+#define AQUAKV_EXCHANGE_ARGS                                                                                              \
+  : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4]), "=&v"(o[5]), "=&v"(o[6]), "=&v"(o[7])                  \
+  : "v"(a.x), "v"(a.y), "v"(a.z), "v"(a.w), "v"(b.x), "v"(b.y), "v"(b.z), "v"(b.w), "s"(without)                            \
+  : "vcc", "scc"
+  if constexpr (MASK == 1) asm(AQUAKV_EXCHANGE("[1,0,3,2]") AQUAKV_EXCHANGE_ARGS);
+  else asm(AQUAKV_EXCHANGE("[2,3,0,1]") AQUAKV_EXCHANGE_ARGS);
+  a = u32x4{o[0], o[1], o[2], o[3]};
+  b = u32x4{o[4], o[5], o[6], o[7]};
+}
+
 template <> struct Storage<float> {
   template <int N> static __device__ __forceinline__ void load(const float* p, float (&v)[N]) {
 #pragma unroll
@@ -40,7 +65,8 @@ template <> struct Storage<float> {
       v[4 * c] = a.x; v[4 * c + 1] = a.y; v[4 * c + 2] = a.z; v[4 * c + 3] = a.w;
     }
   }
-  template <int N> static __device__ __forceinline__ void store(float* p, const float (&v)[N]) {
+  template <bool REVERSED, int N> static __device__ __forceinline__ void store(float* row, int pos, const float (&v)[N]) {
+    float* const p = row + pos * N;
 #pragma unroll
     for (int c = 0; c < N / 4; ++c) {
       f32x4 a;
@@ -71,13 +97,30 @@ template <> struct Storage<bf16_t> {
     f.x = lo; f.y = hi;
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));   // one packed RNE convert
   }
-  template <int N> static __device__ __forceinline__ void store(bf16_t* p, const float (&v)[N]) {
+  // Values N pos ... of a row at p, the lanes of a quad holding consecutive positions.  Lanes that each store their own 64 bytes
+  // leave holes between the 16-byte pieces of one instruction, and such stores reach 2.5 TB/s where runs of 64 bytes reach 4.8
+  // (32 MiB; 128 MiB: 3.3 against 6.5).  So with 32 values per lane the quad's lanes exchange pieces first, one instruction per
+  // value: 64 bytes of a quad per store.  Decode of 32768 tokens 224 -> 212 us, encode 269 / 270 (bound by vector issue).  With 16
+  // values, 32 bytes per lane (3.7 and 5.6 TB/s), the exchange costs what it gains.
+  template <bool REVERSED, int N> static __device__ __forceinline__ void store(bf16_t* p, int pos, const float (&v)[N]) {
+    constexpr int kPieces = N / 8;
+    u32x4 r[kPieces];
 #pragma unroll
-    for (int c = 0; c < N / 8; ++c) {
-      u32x4 r;
-      r.x = pack2(v[8 * c], v[8 * c + 1]); r.y = pack2(v[8 * c + 2], v[8 * c + 3]);
-      r.z = pack2(v[8 * c + 4], v[8 * c + 5]); r.w = pack2(v[8 * c + 6], v[8 * c + 7]);
-      reinterpret_cast<u32x4*>(p)[c] = r;
+    for (int c = 0; c < kPieces; ++c) {
+      r[c].x = pack2(v[8 * c], v[8 * c + 1]); r[c].y = pack2(v[8 * c + 2], v[8 * c + 3]);
+      r[c].z = pack2(v[8 * c + 4], v[8 * c + 5]); r[c].w = pack2(v[8 * c + 6], v[8 * c + 7]);
+    }
+    if constexpr (kPieces == 4) {
+      quad_exchange<1, REVERSED>(r[0], r[1]);
+      quad_exchange<1, REVERSED>(r[2], r[3]);
+      quad_exchange<2, REVERSED>(r[0], r[2]);
+      quad_exchange<2, REVERSED>(r[1], r[3]);
+      bf16_t* const at = p + (pos & ~3) * N + (pos & 3) * 8;
+#pragma unroll
+      for (int c = 0; c < kPieces; ++c) *reinterpret_cast<u32x4*>(at + 32 * c) = r[c];
+    } else {
+#pragma unroll
+      for (int c = 0; c < kPieces; ++c) reinterpret_cast<u32x4*>(p + pos * N)[c] = r[c];
     }
   }
   static __device__ __forceinline__ float round(float x) {

@@ -158,7 +158,7 @@ __global__ __launch_bounds__(WAVES * 64) void fused_kernel(
     const bool active = row < T;
     const int64_t rowc = active ? row : T - 1;
     const int64_t gid = rowc * H + head;
-    const int64_t off = rowc * D + n0 + q * kValsPerLane;
+    const int64_t off = rowc * D + n0;
     float p[32], v[32];
     read_parked(wl + lrow * kLdP, q, p);
     if constexpr (MODE == kEncode) {
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(WAVES * 64) void fused_kernel(
       for (int k = 0; k < 4; ++k) unpack_bf16x8(in.x[k], &v[8 * k]);
       quantize_group<NCW, false, 8>(v, p, sf, q, cl.cb, use_table ? cl.table : nullptr, active, gid, codes, scales,
                           Xhat != nullptr);
-      if (Xhat != nullptr && active) Storage<bf16_t>::store(Xhat + off, v);
+      if (Xhat != nullptr && active) Storage<bf16_t>::store<false>(Xhat + off, q, v);
     } else {
       if constexpr (!WIDE || is_rtn(NCW)) {
         dequantize_words<NCW>(in.w, p, sf, q, cl.cb, v);
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(WAVES * 64) void fused_kernel(
         if (pass + 1 < kPasses) fetch_wide(pass + 1, wide_codes);
         dequantize_across_heads<NCW>(wc, in.w.scale, head, q, p, sf, cl.cb, v);
       }
-      if (Xhat != nullptr && active) Storage<bf16_t>::store(Xhat + off, v);
+      if (Xhat != nullptr && active) Storage<bf16_t>::store<false>(Xhat + off, q, v);
       if constexpr (MODE == kWeighted) {
         // every parked row of this pass has been read by now (no load may sink below this point): the decoded
         // rows, rounded as they are stored, go where the first pass's rows were

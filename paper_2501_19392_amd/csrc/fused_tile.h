@@ -212,7 +212,7 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
         const bool active = lrow < n_rows;
         const int64_t rowc = m0 + (active ? lrow : n_rows - 1);
         const int64_t gid = rowc * H + head;
-        const int64_t off = rowc * a.D + n0 + q * kVals;
+        const int64_t off = rowc * a.D + n0;
         float p[kVals], v[kVals];
         read_parked(park + prow * kLdP, q, p);
         if constexpr (kEnc) {
@@ -225,7 +225,7 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
         } else {
           dequantize_words<NCW>(in[h & 1].w, p, sf, q, cl.cb, v);
         }
-        if (a.Xhat != nullptr && active) Storage<bf16_t>::store(a.Xhat + off, v);
+        if (a.Xhat != nullptr && active) Storage<bf16_t>::store<false>(a.Xhat + off, q, v);
         if constexpr (MODE == kTileScores)
           score_row(v, q, head, H, a.q_heads, b, t0 + (active ? lrow : n_rows - 1), a.seq_len, active, a.q, a.score_scale,
                     a.scores, a.rope_cos, a.rope_sin, q_lds);

@@ -134,7 +134,7 @@ __global__ __launch_bounds__(kWaves2 * 64) void fused_two_heads_kernel(
       const int64_t row = mw + blk * 32 + lrow;
       const bool active = row < T;
       const int64_t rowc = active ? row : T - 1;
-      const int64_t off = rowc * D + nw + q * kValsPerLane;
+      const int64_t off = rowc * D + nw;
       const int64_t gid = rowc * H + head;
       float p[32], v[32];
       read_parked(wl + lrow * kLdP, q, p);
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kWaves2 * 64) void fused_two_heads_kernel(
       } else {
         dequantize_words<NCW>(ip.w, p, sf, q, cl.cb, v);
       }
-      if (Xhat != nullptr && active) Storage<bf16_t>::store(Xhat + off, v);
+      if (Xhat != nullptr && active) Storage<bf16_t>::store<false>(Xhat + off, q, v);
       if constexpr (MODE == kScores2)
         score_row(v, q, head, H, q_heads, rowc / seq_len, rowc % seq_len, seq_len, active, qv, score_scale, scores, rope_cos, rope_sin,
                   queries.staged ? q_lds + (wave & 1) * (q_heads / H) * kQueryLdsStride : nullptr);

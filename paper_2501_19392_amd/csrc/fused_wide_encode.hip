@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kSlabWaves * 64) void fused_wide_encode_kernel(
       const bool active = row < T;
       const int64_t rowc = active ? row : T - 1;
       const int64_t gid = rowc * H + head;
-      const int64_t off = rowc * kSlabCols + l * kValsPerLane;
+      const int64_t off = rowc * kSlabCols;
       float p[32], v[32];
       read_p(prow, p);
 #pragma unroll
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kSlabWaves * 64) void fused_wide_encode_kernel(
         asm volatile("" ::: "memory");
         read_p(prow, p);
         finish_hat<NCW>(v, sf, p);
-        if (active) Storage<bf16_t>::store(Xhat + off, v);
+        if (active) Storage<bf16_t>::store<true>(Xhat + off, l, v);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
