@@ -136,9 +136,9 @@ template <bool MAX> __device__ __forceinline__ float wave_reduce(float x) {
 // of the chunk and dims 8 l .. 8 l + 7; it reads its 8 row pieces once (all loads in flight together).  The query heads of the
 // group are taken R at a time: thread tid looks after token tid % 256 of heads tid / 256, tid / 256 + 2, whose weights go to LDS,
 // [token][head]; a row is then converted once for all of them; the 32 token classes are added across the lanes and through LDS.
-// This is the path for what the fused kernel does not cover (no predictor, fp32, ragged sequences).
-// Bound by latency for few chunks (two barriers per R heads besides the sums' one), by the rows it reads for many.  With a tree of
-// barriers per head and its 16 copies of every exponential: 13.4 us for 500 tokens of 32 query heads, 77 us for 16 x 3001 of 64.
+// Bound by latency for few chunks (two barriers per R heads besides the sums' one), by the rows it reads for many: 500 tokens of 32
+// query heads 5.3 us, 16 x 3001 of 64 46 us, 2 x 30000 of 24 36.5 us (3.4 TB/s).  With the query heads one by one, a tree of barriers
+// and 16 copies of every exponential each: 13.4, 77 and 50 us.
 // pstats (nullable): soft-max form, `weights` holds raw scores: the weights are exp(score - chunk maximum), and the
 // chunk's maximum and weight sum are written to pstats[chunk, qh, 2].
 constexpr int kWeightedThreads = 512, kWeightedWaves = kWeightedThreads / 64;
@@ -283,43 +283,64 @@ __global__ __launch_bounds__(kThreads) void combine_weighted_kernel(const float*
 // Soft-max form: chunk c carries sums taken with weights exp(score - m_c), its maximum m_c and weight sum l_c.
 // out = sum_c e^(m_c - M) part_c / sum_c e^(m_c - M) l_c with M = max_c m_c; row_stats (nullable) receives M and the
 // denominator.  Same thread layout as above; the three reductions over the chunks go through LDS in a fixed order.
+// Bound by the latency of what it reads, written by all XCDs just before: the first kHeld chunks of a thread (32 of a sequence: 8192
+// tokens) are requested at once, before the maximum over them is known, and the row of a workgroup is found with 32-bit divisions: the attention
+// of one query over 8192 tokens 65.8 us against 67.5 (all three launches); up to 2048 tokens, one chunk a thread, no difference.
+constexpr int kHeld = 4;
 __global__ __launch_bounds__(kThreads) void combine_softmax_kernel(const float* __restrict__ part, const float* __restrict__ pstats,
                                                                    float* __restrict__ out, float* __restrict__ row_stats,
                                                                    int chunks_per_seq, int q_heads) {
   __shared__ float red[8][32];
   __shared__ float den[8];
-  const int row = q_heads * kGroup;
   const int k = threadIdx.x >> 5, j32 = threadIdx.x & 31;
-  const int64_t i = (int64_t)blockIdx.x * 32 + j32;                     // the grid covers batch * q_heads * 128 outputs exactly
-  const int64_t b = i / row, j = i % row;
-  const int qh = (int)(j / kGroup);                                     // the same for the 32 outputs of a workgroup
-  const float* src = part + b * chunks_per_seq * row + j;
-  const float* st = pstats + (b * chunks_per_seq * q_heads + qh) * 2;
-  float mx = -INFINITY;
-  for (int c = k; c < chunks_per_seq; c += 8) mx = fmaxf(mx, st[(int64_t)c * q_heads * 2]);
+  const unsigned bqh = blockIdx.x / (kGroup / 32);                      // batch * q_heads rows of 128 outputs, 32 a workgroup
+  const unsigned b = bqh / (unsigned)q_heads, qh = bqh % (unsigned)q_heads;
+  const int d0 = (int)(blockIdx.x % (kGroup / 32)) * 32 + j32;
+  const int64_t stride = (int64_t)q_heads * kGroup, st_stride = (int64_t)q_heads * 2;      // from chunk to chunk
+  const float* const src = part + b * chunks_per_seq * stride + qh * kGroup + d0;
+  const float* const st = pstats + b * chunks_per_seq * st_stride + qh * 2;
+  float m[kHeld], l[kHeld], x[kHeld], mx = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < kHeld; ++u) {
+    const int c = min(k + 8 * u, chunks_per_seq - 1);                   // past the last one: loaded again and not used
+    m[u] = st[c * st_stride];
+    l[u] = st[c * st_stride + 1];
+    x[u] = src[c * stride];
+  }
+#pragma unroll
+  for (int u = 0; u < kHeld; ++u) mx = fmaxf(mx, m[u]);
+  for (int c = k + 8 * kHeld; c < chunks_per_seq; c += 8) mx = fmaxf(mx, st[c * st_stride]);
   red[k][j32] = mx;
   __syncthreads();
   float M = red[0][j32];
 #pragma unroll
   for (int w = 1; w < 8; ++w) M = fmaxf(M, red[w][j32]);
   __syncthreads();
-  float acc = 0.f, l = 0.f;
-  for (int c = k; c < chunks_per_seq; c += 8) {
-    const float e = expf(st[(int64_t)c * q_heads * 2] - M);
-    acc = __fmaf_rn(e, src[(int64_t)c * row], acc);
-    l = __fmaf_rn(e, st[(int64_t)c * q_heads * 2 + 1], l);
+  float acc = 0.f, weight = 0.f;
+#pragma unroll
+  for (int u = 0; u < kHeld; ++u) {
+    if (k + 8 * u < chunks_per_seq) {
+      const float e = expf(m[u] - M);
+      acc = __fmaf_rn(e, x[u], acc);
+      weight = __fmaf_rn(e, l[u], weight);
+    }
+  }
+  for (int c = k + 8 * kHeld; c < chunks_per_seq; c += 8) {
+    const float e = expf(st[c * st_stride] - M);
+    acc = __fmaf_rn(e, src[c * stride], acc);
+    weight = __fmaf_rn(e, st[c * st_stride + 1], weight);
   }
   red[k][j32] = acc;
-  if (j32 == 0) den[k] = l;
+  if (j32 == 0) den[k] = weight;
   __syncthreads();
   if (k == 0) {
     float sum = red[0][j32], d = den[0];
 #pragma unroll
     for (int w = 1; w < 8; ++w) { sum += red[w][j32]; d += den[w]; }
-    out[i] = sum / d;
-    if (row_stats != nullptr && j % kGroup == 0) {
-      row_stats[(b * q_heads + qh) * 2] = M;
-      row_stats[(b * q_heads + qh) * 2 + 1] = d;
+    out[(int64_t)bqh * kGroup + d0] = sum / d;
+    if (row_stats != nullptr && d0 == 0) {
+      row_stats[(int64_t)bqh * 2] = M;
+      row_stats[(int64_t)bqh * 2 + 1] = d;
     }
   }
 }
