@@ -21,11 +21,15 @@ constexpr int kMaxRep = 8;                            // query heads worked on a
 template <int C> __device__ __forceinline__ float dpp(float x) {      // x of the lane that DPP control C names
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), C, 0xf, 0xf, true));
 }
-// The sum over the 16 lanes of a token; every lane gets it (fixed order).
-__device__ __forceinline__ float sum16(float x) {
-  x = quad_sum(x);
-  x = x + dpp<0x141>(x);                              // row_half_mirror: the other quad of the 8
-  return x + dpp<0x140>(x);                           // row_mirror: the other 8
+// The sums over the 16 lanes of a token for the token of each pass, lane i of a quad getting that of pass i: two lanes exchange what
+// each sums for the other, so the work halves where a sum of all four in every lane repeats it.
+__device__ __forceinline__ float sum16(const float (&d)[kPasses], int lane) {
+  const bool odd = lane & 1, upper = lane & 2;
+  const float a = (odd ? d[1] : d[0]) + dpp<0xb1>(odd ? d[0] : d[1]);          // quad_perm 1 0 3 2
+  const float b = (odd ? d[3] : d[2]) + dpp<0xb1>(odd ? d[2] : d[3]);
+  float x = (upper ? b : a) + dpp<0x4e>(upper ? a : b);                        // quad_perm 2 3 0 1
+  x = x + dpp<0x128>(x);                              // row_ror:8; in this order all quads of the token end with the same bits
+  return x + dpp<0x124>(x);                           // row_ror:4
 }
 
 // Reductions over the four groups of 16 lanes of a wave (a wave's tokens of one pass).  The gfx950 lane swaps exchange halves
@@ -93,7 +97,7 @@ template <> struct Row<float> {
 // exponential per lane and the values unpacked per query head, 18 us also with shuffles through LDS and pieces of 128 (two
 // workgroups per CU).  128 tokens: 6 us, which is launch and memory latency.
 template <typename T>
-__global__ __launch_bounds__(kThreads, 2) void attend_cache_kernel(const AttendCacheArgs a) {
+__global__ __launch_bounds__(kThreads, 4) void attend_cache_kernel(const AttendCacheArgs a) {
   __shared__ float q_lds[kMaxRep][kGroup];
   __shared__ float sums[4][kMaxRep][kGroup];
   __shared__ float wave_stats[4][kMaxRep][2];
@@ -110,16 +114,26 @@ __global__ __launch_bounds__(kThreads, 2) void attend_cache_kernel(const AttendC
   const int64_t seq = a.seq0 + b;
 
   Row<T> rows[kPasses];
+  if (t0 >= ns && t0 + kAttendPiece <= ns + nc) {      // compressed tokens only: rows one after the other
+    const int64_t off = (a.compressed_row[b] + t0 - ns) * row_elems + head * kGroup;
+    const T *kb = static_cast<const T*>(a.compressed_k) + off, *vb = static_cast<const T*>(a.compressed_v) + off;
 #pragma unroll
-  for (int p = 0; p < kPasses; ++p) {
-    int t = t0 + p * 16 + ts;
-    t = t < n ? t : n - 1;                             // beyond the end: weight 0 below
-    const void *kb = a.sink_k, *vb = a.sink_v;
-    int64_t row = seq * a.sink_rows + t;
-    if (t >= ns) { kb = a.compressed_k; vb = a.compressed_v; row = a.compressed_row[b] + t - ns; }
-    if (t >= ns + nc) { kb = a.recent_k; vb = a.recent_v; row = seq * a.recent_rows + t - ns - nc; }
-    const int64_t off = row * row_elems + head * kGroup;
-    rows[p].load(static_cast<const T*>(kb) + off, static_cast<const T*>(vb) + off, l);
+    for (int p = 0; p < kPasses; ++p) {
+      const uint32_t at = (uint32_t)(p * 16 + ts) * (uint32_t)row_elems;
+      rows[p].load(kb + at, vb + at, l);
+    }
+  } else {
+#pragma unroll
+    for (int p = 0; p < kPasses; ++p) {
+      int t = t0 + p * 16 + ts;
+      t = t < n ? t : n - 1;                           // beyond the end: weight 0 below
+      const void *kb = a.sink_k, *vb = a.sink_v;
+      int64_t row = seq * a.sink_rows + t;
+      if (t >= ns) { kb = a.compressed_k; vb = a.compressed_v; row = a.compressed_row[b] + t - ns; }
+      if (t >= ns + nc) { kb = a.recent_k; vb = a.recent_v; row = seq * a.recent_rows + t - ns - nc; }
+      const int64_t off = row * row_elems + head * kGroup;
+      rows[p].load(static_cast<const T*>(kb) + off, static_cast<const T*>(vb) + off, l);
+    }
   }
   f32x4 cs[kPasses], sn[kPasses];
   if (a.rope_cos != nullptr) {
@@ -136,44 +150,41 @@ __global__ __launch_bounds__(kThreads, 2) void attend_cache_kernel(const AttendC
     for (int p = 0; p < kPasses; ++p)
       if (t0 + p * 16 + ts >= n) rows[p].no_value();
   }
+  const auto stage_queries = [&](int r0) {
+    const int nr = rep - r0 < kMaxRep ? rep - r0 : kMaxRep;
+    const T* qp = static_cast<const T*>(a.q) + (seq * a.q_heads + head * rep + r0) * kGroup;
+    for (int e = threadIdx.x; e < nr * kGroup; e += kThreads) q_lds[e / kGroup][e % kGroup] = static_cast<float>(qp[e]);
+  };
+  stage_queries(0);
   float k[kPasses][8], v[kPasses][8];
+#pragma unroll
+  for (int p = 0; p < kPasses; ++p) {
+    rows[p].key(k[p]);
+    rows[p].value(v[p]);
+    if (a.rope_cos != nullptr) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float x0 = k[p][i], x1 = k[p][4 + i];
+        k[p][i] = __fmaf_rn(x0, cs[p][i], -(x1 * sn[p][i]));
+        k[p][4 + i] = __fmaf_rn(x1, cs[p][i], x0 * sn[p][i]);
+      }
+    }
+  }
   for (int r0 = 0; r0 < rep; r0 += kMaxRep) {
     const int nr = rep - r0 < kMaxRep ? rep - r0 : kMaxRep;
     const int qh0 = head * rep + r0;
-    const T* qp = static_cast<const T*>(a.q) + (seq * a.q_heads + qh0) * kGroup;
-    for (int e = threadIdx.x; e < nr * kGroup; e += kThreads) q_lds[e / kGroup][e % kGroup] = static_cast<float>(qp[e]);
-    __syncthreads();
-    if (r0 == 0) {
-#pragma unroll
-      for (int p = 0; p < kPasses; ++p) {
-        rows[p].key(k[p]);
-        rows[p].value(v[p]);
-        if (a.rope_cos != nullptr) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float x0 = k[p][i], x1 = k[p][4 + i];
-            k[p][i] = __fmaf_rn(x0, cs[p][i], -(x1 * sn[p][i]));
-            k[p][4 + i] = __fmaf_rn(x1, cs[p][i], x0 * sn[p][i]);
-          }
-        }
-      }
-    }
+    __syncthreads();                                   // the queries are there, the sums of the heads before them read
 #pragma unroll 1
     for (int r = 0; r < nr; ++r) {
       const f32x4 q0 = *reinterpret_cast<const f32x4*>(&q_lds[r][4 * l]), q1 = *reinterpret_cast<const f32x4*>(&q_lds[r][64 + 4 * l]);
       const float q[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-      float s[kPasses];
+      float d[kPasses] = {};
 #pragma unroll
-      for (int p = 0; p < kPasses; ++p) {
-        float d = 0.f;
+      for (int p = 0; p < kPasses; ++p)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) d = __fmaf_rn(q[i], k[p][i], d);
-        s[p] = sum16(d) * a.scale;
-      }
-      // the 16 lanes of a token hold the same four scores: each takes the exponential of one, and the quad passes them round
-      float mine = lane & 1 ? s[1] : s[0];
-      const float upper = lane & 1 ? s[3] : s[2];
-      mine = lane & 2 ? upper : mine;
+        for (int i = 0; i < 8; ++i) d[p] = __fmaf_rn(q[i], k[p][i], d[p]);
+      // each lane of a quad takes the exponential of one of the token's four scores, and the quad passes them round
+      float mine = sum16(d, lane) * a.scale;
       if (t0 + (lane & 3) * 16 + ts >= n) mine = -INFINITY;
       const float m = max_groups(max_quad(mine));
       const float shift = m == -INFINITY ? 0.f : m;    // a wave without tokens
@@ -202,18 +213,19 @@ __global__ __launch_bounds__(kThreads, 2) void attend_cache_kernel(const AttendC
       const int r = e / kGroup, d = e % kGroup;
       const float M = fmaxf(fmaxf(wave_stats[0][r][0], wave_stats[1][r][0]), fmaxf(wave_stats[2][r][0], wave_stats[3][r][0]));
       const float shift = M == -INFINITY ? 0.f : M;    // every score of the piece is -inf: it weighs nothing in the merge
+      const float own = expf(wave_stats[lane & 3][r][0] - shift);        // r is the same in a wave: a factor per lane of a quad
+      const float f[4] = {dpp<0x00>(own), dpp<0x55>(own), dpp<0xaa>(own), dpp<0xff>(own)};
       float sum = 0.f, den = 0.f;
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
-        const float f = expf(wave_stats[w][r][0] - shift);
-        sum = __fmaf_rn(f, sums[w][r][d], sum);
-        den = __fmaf_rn(f, wave_stats[w][r][1], den);
+        sum = __fmaf_rn(f[w], sums[w][r][d], sum);
+        den = __fmaf_rn(f[w], wave_stats[w][r][1], den);
       }
       const int64_t row = (int64_t)piece * a.q_heads + qh0 + r;
       a.part[row * kGroup + d] = sum;
       if (d == 0) { a.stats[row * 2] = M; a.stats[row * 2 + 1] = den; }
     }
-    __syncthreads();                                   // LDS is free for the next query heads
+    if (r0 + kMaxRep < rep) stage_queries(r0 + kMaxRep);               // (read ahead of the last barrier)
   }
 }
 
