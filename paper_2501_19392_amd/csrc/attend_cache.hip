@@ -92,10 +92,11 @@ template <> struct Row<float> {
 // blockIdx.x = piece * kv heads + head.  All rows of the piece are requested at once; thread (ts = tid / 16, l = tid % 16) owns
 // tokens ts, ts + 16, ... of it.  Every wave takes the soft-max of its own tokens, so the waves meet once, to merge.
 // part[piece, q_heads, 128]: sums with weights exp(score - maximum); stats[piece, q_heads, 2]: maximum and sum of the weights.
-// Bound by the instructions per query head, hence the sharing of exponentials in a quad and the lane swaps: 5640 tokens in four
-// sequences, 8 kv heads, 32 query heads, rotary embedding: 9.8 us (12 us inside the sweep, in a trace); 11.5 us with an
-// exponential per lane and the values unpacked per query head, 18 us also with shuffles through LDS and pieces of 128 (two
-// workgroups per CU).  128 tokens: 6 us, which is launch and memory latency.
+// Bound by the instructions per query head and the workgroups per CU, hence the scores shared out in a quad, the lane swaps, the short
+// way to the addresses of compressed tokens only, and rows that are unpacked ahead of the loop (100 registers: four workgroups per
+// CU, where 166 left room for three).  8 kv heads, in a trace: four sequences of up to 1800 tokens, 32 query heads, rotary embedding
+// 11.3 us (13.1 with all four scores in every lane and 166 registers), 8000 tokens of 24 query heads 10.7 (13.7), 8 x 1000 tokens
+// of 64 query heads 17.5 (20.6).  200 tokens: 6.7 us, which is launch and memory latency.
 template <typename T>
 __global__ __launch_bounds__(kThreads, 4) void attend_cache_kernel(const AttendCacheArgs a) {
   __shared__ float q_lds[kMaxRep][kGroup];
@@ -230,34 +231,69 @@ __global__ __launch_bounds__(kThreads, 4) void attend_cache_kernel(const AttendC
 }
 
 // out[layer][b, qh, d] = sum_c e^(m_c - M) part_c / sum_c e^(m_c - M) l_c over the pieces c of sequence b, M = max_c m_c.
-// blockIdx = (b * q_heads + qh, layer); thread = (dim, parity of the piece).
+// blockIdx = (b * q_heads + qh, layer); thread (k = tid / 32, l = tid % 32) takes dims 4 l ... of pieces k, k + 8, ...
+// Bound by the latency of what it reads: the first kHeld pieces of a thread (2048 tokens of a sequence) are requested at once, before
+// the maximum over them is known, four more at a time after that.  8 layers of 32 query heads, 4 sequences of 1800 tokens 4.9 us,
+// 6 layers of 24 query heads, 8000 tokens 7.7 us; with a value per thread, every other piece each, 6.8 and 11.8 us.
+constexpr int kClasses = kThreads / 32, kHeld = 4;
 __global__ __launch_bounds__(kThreads) void merge_pieces_kernel(const MergeArgs a) {
-  __shared__ float red[kThreads];
-  __shared__ float den2[2];
+  __shared__ __align__(16) float red[kClasses][kGroup];
+  __shared__ float top[kClasses], den[kClasses];
   const int b = blockIdx.x / a.q_heads, qh = blockIdx.x % a.q_heads;
-  const int c0 = a.pieces.first[b], c1 = a.pieces.first[b + 1];
-  const float* const part = a.part + blockIdx.y * a.part_layer + qh * kGroup;
+  const int k = threadIdx.x >> 5, l = threadIdx.x & 31;
+  const int c0 = a.pieces.first[b] + k, c1 = a.pieces.first[b + 1];
+  const float* const part = a.part + blockIdx.y * a.part_layer + qh * kGroup + 4 * l;
   const float* const stats = a.stats + blockIdx.y * a.stats_layer + qh * 2;
-  const int d = threadIdx.x & (kGroup - 1), par = threadIdx.x >> 7;
-  float m = -INFINITY;
-  for (int c = c0 + threadIdx.x; c < c1; c += kThreads) m = fmaxf(m, stats[(int64_t)c * a.q_heads * 2]);
+  f32x4 x[kHeld];
+  f32x2 st[kHeld];                                     // maximum, sum of the weights
+  const auto request = [&](int c) {
 #pragma unroll
-  for (int s = 1; s < 64; s <<= 1) m = fmaxf(m, __shfl_xor(m, s));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    for (int u = 0; u < kHeld; ++u) {
+      st[u] = f32x2{-INFINITY, 0.f};
+      x[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (c + u * kClasses < c1) {
+        const int64_t row = (int64_t)(c + u * kClasses) * a.q_heads;
+        st[u] = *reinterpret_cast<const f32x2*>(stats + row * 2);
+        x[u] = *reinterpret_cast<const f32x4*>(part + row * kGroup);
+      }
+    }
+  };
+  request(c0);
+  float m = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < kHeld; ++u) m = fmaxf(m, st[u].x);
+#pragma unroll 4
+  for (int c = c0 + kHeld * kClasses; c < c1; c += kClasses) m = fmaxf(m, stats[(int64_t)c * a.q_heads * 2]);
+  if (l == 0) top[k] = m;
   __syncthreads();
-  const float M = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  __syncthreads();
-  float sum = 0.f, den = 0.f;
-#pragma unroll 8
-  for (int c = c0 + par; c < c1; c += 2) {
-    const float e = expf(stats[(int64_t)c * a.q_heads * 2] - M);
-    sum = __fmaf_rn(e, part[(int64_t)c * a.q_heads * kGroup + d], sum);
-    den = __fmaf_rn(e, stats[(int64_t)c * a.q_heads * 2 + 1], den);
+  float M = top[0];
+#pragma unroll
+  for (int w = 1; w < kClasses; ++w) M = fmaxf(M, top[w]);
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  float weight = 0.f;
+  for (int c = c0;;) {
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u) {
+      if (c + u * kClasses >= c1) break;
+      const float e = expf(st[u].x - M);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sum[i] = __fmaf_rn(e, x[u][i], sum[i]);
+      weight = __fmaf_rn(e, st[u].y, weight);
+    }
+    c += kHeld * kClasses;
+    if (c >= c1) break;
+    request(c);
   }
-  red[threadIdx.x] = sum;
-  if (d == 0) den2[par] = den;
+  *reinterpret_cast<f32x4*>(&red[k][4 * l]) = sum;
+  if (l == 0) den[k] = weight;
   __syncthreads();
-  if (par == 0) a.out[blockIdx.y][((a.seq0 + b) * a.q_heads + qh) * kGroup + d] = (red[d] + red[kGroup + d]) / (den2[0] + den2[1]);
+  const int d = threadIdx.x;
+  if (d < kGroup) {
+    float total = red[0][d], by = den[0];
+#pragma unroll
+    for (int w = 1; w < kClasses; ++w) { total += red[w][d]; by += den[w]; }
+    a.out[blockIdx.y][((a.seq0 + b) * a.q_heads + qh) * kGroup + d] = total / by;
+  }
 }
 
 }  // namespace
