@@ -313,3 +313,30 @@ def test_weighted_values_at_the_bench_shapes(B, S, QH):
     assert np.array_equal(U.np64(stats)[0, :, 0], sd.max(axis=1))
     Lw = np.exp(sd - sd.max(axis=1, keepdims=True)).sum(axis=1)
     assert np.all(np.abs(U.np64(stats)[0, :, 1] - Lw) <= 2e-5 * Lw)
+
+
+@pytest.mark.parametrize("S", [1, 7937, 8192, 8193, 12289])
+def test_soft_max_pieces_of_long_sequences_are_merged(B, S):
+    """One to 49 pieces of 256 tokens per sequence: 32 of them are requested by the merge at once, the rest one after the other."""
+    print(f"case merge of pieces S={S}", flush=True)
+    batch, QH = 2, 2
+    lay = U.make_layers(1, "bf16", 16)[1]
+    gen = torch.Generator().manual_seed(S)
+    codes, scales = lay.alloc_codes(batch * S)
+    codes.copy_(torch.randint(0, 256, codes.shape, generator=gen).to(codes.dtype))
+    scales.copy_(torch.ones(scales.shape).half().view(torch.int16))
+    s = (torch.randn(batch, QH, S, generator=gen) * 2.0 + torch.linspace(0, 3, S)).float().cuda()
+    out = torch.full((batch, QH, 128), float("nan"), dtype=torch.float32, device="cuda")
+    stats = torch.full((batch, QH, 2), float("nan"), dtype=torch.float32, device="cuda")
+    V = lay.alloc_kv(batch * S)
+    B.aquakv_decode_values_attend(lay, batch, S, QH, codes, scales, None, None, s, V, out, stats,
+                                  lay.alloc_weighted_workspace(batch, S, QH))
+    sync()
+    p = torch.softmax(s.double(), -1)
+    v = V.view(batch, S, 128).double()
+    # fp32 exponentials of differences up to some 20 (1e-6 relative each) and sums of 256 terms, then of the pieces
+    assert ((out.double() - p @ v).abs() <= 3e-5 * (p @ v.abs())).all()
+    top = s.amax(-1)
+    total = (s.double() - top[..., None]).exp().sum(-1)
+    assert torch.equal(stats[..., 0], top)
+    assert ((stats[..., 1].double() - total).abs() <= 2e-5 * total).all()
