@@ -1,7 +1,7 @@
 // Attention of one new token per sequence over a cache (Alg. "Inference", Sect. 3.3 of the AQUA-KV paper): over sinks, recovered
 // compressed past and recent-token buffer of every sequence of a batch, whatever their lengths, in one launch per layer and one
 // more that merges the pieces of several layers.  (Separate launches per sequence, and per kind of token, were 2.5 ms a token for
-// 4 sequences of 1020 - 1800 tokens and 8 layers; now 0.56 ms, of which the recovery of the compressed tokens is 0.46 ms.)
+// 4 sequences of 1020 - 1800 tokens and 8 layers; now 0.55 ms, of which the recovery of the compressed tokens is 0.45 ms.)
 //
 // The tokens of a sequence are numbered through, [sinks | compressed | recent], and cut into pieces of 64; a workgroup takes
 // one piece of one kv head for all its query heads, so the split follows the tokens there are and no sequence waits for another.

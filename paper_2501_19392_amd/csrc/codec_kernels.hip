@@ -5,10 +5,10 @@
 // nearest-grid-point search table.  These are the stand-alone forms (prediction
 // read from memory, or absent); the fused forms live in fused_kernels.hip.
 //
-// One head group (128 values) is held by a quad of lanes x 32 values (see device_utils.h);
-// a 256-thread block covers 64 head groups = 8 tokens of 8 heads per pass.  WIDE = true selects
+// One head group (128 values) is held by eight lanes x 16 values (see device_utils.h; the scores kernel: a quad x 32);
+// a 256-thread block covers 32 head groups = 4 tokens of 8 heads per pass.  WIDE = true selects
 // rotation groups of 1024 = the whole token (the grouping of the paper's experiments, Sect. 4.1):
-// the 8 quads of a token (32 consecutive lanes) then share three more butterfly stages and one scale.
+// the 64 lanes of a token = one wave then share three more butterfly stages and one scale.
 #include "codec_core.h"
 #include "kernels.h"
 
@@ -23,10 +23,11 @@ constexpr int kGroupsPerBlock = kThreads / kLanesPerGroup;   // 64
 // blockIdx.y: which of the one or two tensors of the launch (QuantizeIo in kernels.h; the keys and the values of a layer
 // without predictors do not depend on each other, and together they fill the chip better).
 //
-// Bound by vector issue and, with it, by how many waves a SIMD holds to cover the look-ups' LDS latency.  Without a
-// prediction (PRED false) the kernel fits 168 registers = three waves per SIMD, since quantize_group holds four sub-vectors
-// at a time; with one (32 more values, and the next round's 32) it stays at two.  8192 tokens, 256-point grid, groups of
-// 1024, keys and values: 2 x 53 us as two launches of one wave per SIMD.
+// Bound by vector issue and, with it, by how many waves a SIMD holds to cover the look-ups' LDS latency, hence 16 values per
+// lane: 113 to 120 registers = four waves per SIMD without a prediction (PRED false), 147 to 154 = three with one.  With 32 values
+// per lane it was three and two.  Keys and values of 8192 tokens, 256-point grid, groups of 1024: 36.6 us against 49.6; with
+// predictions in memory, 4096 tokens, 16 points, predictor included, 88.5 against 114.7.  Smaller code for the crowded cells, which
+// would let four or five waves in with a prediction, changed nothing: the issue slots are full.
 template <typename T, int NCW, bool WIDE, bool PRED>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED ? 3 : 4))) void quantize_kernel(
     const QuantizeIo io0, const QuantizeIo io1, const Prediction P, const float* __restrict__ codebook,

@@ -343,14 +343,14 @@ hipError_t launch(int n_codewords, const void* x0, int d0, const void* x1, int d
 // 0: the tiles of 256 rows x one or two heads.
 //
 // A CU holds one workgroup, so what counts is the rounds of workgroups over the CUs and the rows of a round.  Ranges that
-// fill the chip in one round take the smallest tile that still does: encode of 1024 tokens x 8 heads (keys / values) 11.1 /
-// 15.9 us on 32 rows, 11.8 / 17.8 on 64, 18.1 / 26 on 128, 23 / 32 on 256; 2048 tokens: 13.2 / 19.7 on 64 against 24 / 33.7;
-// 4096 tokens: 20.6 / 28.8 on 128 against 26.1 / 35.  Beyond that 320 rows x one head fill the gap where the tiles of 256
+// fill the chip in one round take the smallest tile that still does: keys and values of 1024 tokens x 8 heads 23.6 us to encode
+// on 32 rows, 27.0 on 64, 38.8 on 128 (decode 19.1, 22.3, 30.7); 2048 tokens 28.7 on 64 against 39.5 on 128 (24.3 against 31.1);
+// 4096 tokens, a tensor at a time: 20.6 / 28.8 on 128 against 26.1 / 35 on 256.  Beyond that 320 rows x one head fill the gap where the tiles of 256
 // rows start a round they hardly use (10007 tokens: 41.1 / 57.8 us against 45.6 / 62.4; 20000 tokens: 81 / 115 against
 // 87 / 122): taken when its rounds cost less, a round being 41 us on 320 rows, 29 us on 256 rows (33 the first) and 54 us on
-// 256 rows x two heads (K = 1024, encode).  Decode has the same proportions, keys and values together, against tiles of 256 rows:
-// 1024 tokens 21.7 us (43.1), 2048 26.2 (43.5), 4096 40.1 (45.5), 10240 75.6 (80.4), 18000 139.5 (161.2); so have the scoring
-// calls (18.2 against 23.7 us at 4096) and fewer heads (1, 2, 4: no size from 4000 rows on was slower than on 256 rows).
+// 256 rows x two heads (K = 1024, encode).  Decode has the same proportions, keys and values together, against tiles of 256 rows
+// (before rows were stored in runs of 64 bytes, which took 4096 tokens from 38.8 to 36.2 us): 4096 tokens 40.1 us (45.5), 10240 75.6
+// (80.4), 18000 139.5 (161.2); so have the scoring calls (18.2 against 23.7 us at 4096) and fewer heads (1, 2, 4: no size from 4000 rows on was slower than on 256 rows).
 int tile_rows(int64_t n_seq, int64_t seq_len, int D, bool two_heads) {
   constexpr int64_t kCUs = 256;                      // MI355X
   const int64_t H = D / BN;
