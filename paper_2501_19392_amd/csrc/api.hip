@@ -797,8 +797,13 @@ int decode_values_weighted(const aquakv_layer* L, int32_t batch, int32_t seq_len
       const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;
       CHECK(decode_values_chunk(L, pl, r0, n, v_codes, v_scales, Vhat_prev, Khat, Vhat, Pbuf, stream));
     }
-    HIP_TRY(aquakv::launch_weighted_values(L->dtype, Vhat, weights, part, pstats, batch, seq_len, L->kv_heads, q_heads,
-                                           stream));
+    // sequences of one chunk (up to 256 tokens): the sums are the result and the launch that merges them is
+    // saved: one layer of attention over 150 tokens 24.9 us against 27.2, 12 x 200 tokens 40.5 against 42.8
+    const bool whole = seq_len <= aquakv::kWeightedChunk;
+    const aquakv::WeightedForm form = !softmax ? aquakv::kWeightedGiven : whole ? aquakv::kWeightedWhole : aquakv::kWeightedSoftMax;
+    HIP_TRY(aquakv::launch_weighted_values(L->dtype, Vhat, weights, form, whole ? out : part, whole ? (softmax ? row_stats : nullptr) : pstats,
+                                           batch, seq_len, L->kv_heads, q_heads, stream));
+    if (whole) return AQUAKV_OK;
   }
   HIP_TRY(aquakv::launch_combine_weighted(part, pstats, out, softmax ? row_stats : nullptr, batch, seq_len, q_heads, stream));
   return AQUAKV_OK;

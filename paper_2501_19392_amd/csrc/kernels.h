@@ -137,9 +137,11 @@ hipError_t launch_fused_weighted(int n_codewords, const void* x0, int d0, const 
                                  const float* bias, const int8_t* signs, const float* codebook, const uint8_t* codes,
                                  const uint16_t* scales, void* Xhat, const float* weights, float* part, float* pstats,
                                  int seq_len, int q_heads, int64_t T, int D, bool wide, hipStream_t stream);
-// chunk sums over values already decoded to memory (any dtype, any seq_len)
-hipError_t launch_weighted_values(int dtype, const void* Vhat, const float* weights, float* part, float* pstats, int batch,
-                                  int seq_len, int H, int q_heads, hipStream_t stream);
+// Chunk sums over values already decoded to memory (any dtype, any seq_len): of given weights, in soft-max form, or in soft-max form
+// where a sequence is one chunk, which leaves nothing to combine: part and pstats (nullable) are out and row_stats then.
+enum WeightedForm : int { kWeightedGiven = 0, kWeightedSoftMax = 1, kWeightedWhole = 2 };
+hipError_t launch_weighted_values(int dtype, const void* Vhat, const float* weights, WeightedForm form, float* part, float* pstats,
+                                  int batch, int seq_len, int H, int q_heads, hipStream_t stream);
 hipError_t launch_combine_weighted(const float* part, const float* pstats, float* out, float* row_stats, int batch,
                                    int seq_len, int q_heads, hipStream_t stream);
 // Attention of one query per sequence over `tokens` (<= kAttendRawMaxTokens) keys / values in the storage dtype

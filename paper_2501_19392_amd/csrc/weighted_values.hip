@@ -139,13 +139,14 @@ template <bool MAX> __device__ __forceinline__ float wave_reduce(float x) {
 // Bound by latency for few chunks (two barriers per R heads besides the sums' one), by the rows it reads for many: 500 tokens of 32
 // query heads 5.3 us, 16 x 3001 of 64 46 us, 2 x 30000 of 24 36.5 us (3.4 TB/s).  With the query heads one by one, a tree of barriers
 // and 16 copies of every exponential each: 13.4, 77 and 50 us.
-// pstats (nullable): soft-max form, `weights` holds raw scores: the weights are exp(score - chunk maximum), and the
-// chunk's maximum and weight sum are written to pstats[chunk, qh, 2].
+// form kWeightedSoftMax: `weights` holds raw scores, the weights are exp(score - chunk maximum), and the chunk's maximum and weight
+// sum are written to pstats[chunk, qh, 2].  kWeightedWhole: the same where a sequence is one chunk; part and pstats (nullable then)
+// are the results, so the sums are divided by the weight sum here.
 constexpr int kWeightedThreads = 512, kWeightedWaves = kWeightedThreads / 64;
 template <typename T, int R>
 __global__ __launch_bounds__(kWeightedThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : 4))) void weighted_values_kernel(
     const T* __restrict__ Vhat, const float* __restrict__ weights,
-    float* __restrict__ part, float* __restrict__ pstats, int seq_len, int H, int q_heads, int chunks_per_seq) {
+    float* __restrict__ part, float* __restrict__ pstats, int seq_len, int H, int q_heads, int chunks_per_seq, WeightedForm form) {
   static_assert(kWeightedThreads == 2 * kWeightedChunk && (R == 1 || R == 2 || R == 4), "a thread: one token of every second head");
   constexpr int kIters = kWeightedChunk / (kWeightedThreads / 16), kPer = (R + 1) / 2;
   __shared__ __attribute__((aligned(16))) float w_lds[kWeightedChunk][R];
@@ -157,7 +158,7 @@ __global__ __launch_bounds__(kWeightedThreads) __attribute__((amdgpu_waves_per_e
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int ts = tid >> 4, l = tid & 15;
   const int t0 = chunk * kWeightedChunk;
-  const bool soft = pstats != nullptr;
+  const bool soft = form != kWeightedGiven;
   const T* vbase = Vhat + ((int64_t)b * seq_len * H + head) * kGroup + l * 8;
   Raw8<T> rows[kIters];
 #pragma unroll
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(kWeightedThreads) __attribute__((amdgpu_waves_per_e
     for (int k = 0; k < kPer; ++k)
       if (2 * k + half < R) w_lds[own][2 * k + half] = wt[k];
     __syncthreads();
-    if (soft && own == 0) {
+    if (pstats != nullptr && own == 0) {
 #pragma unroll
       for (int k = 0; k < kPer; ++k) {
         if (!here[k]) continue;
@@ -243,6 +244,13 @@ __global__ __launch_bounds__(kWeightedThreads) __attribute__((amdgpu_waves_per_e
       float sum = red[0][r][d];
 #pragma unroll
       for (int w = 1; w < kWeightedWaves; ++w) sum += red[w][r][d];
+      if (form == kWeightedWhole) {
+        const int k = r / 2, w0 = r % 2 * 4;
+        float total = wave_sum[w0][k];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) total += wave_sum[w0 + w][k];
+        sum /= total;
+      }
       part[((int64_t)piece * q_heads + head * rep + r0 + r) * kGroup + d] = sum;
     }
     // (the next heads' weights overwrite what was read ahead of the last barrier, their sums what is read ahead of the next one)
@@ -434,14 +442,15 @@ hipError_t launch_softmax_rows(const float* scores, float* probs, int64_t rows, 
   return hipGetLastError();
 }
 
-hipError_t launch_weighted_values(int dtype, const void* Vhat, const float* weights, float* part, float* pstats, int batch,
-                                  int seq_len, int H, int q_heads, hipStream_t stream) {
+hipError_t launch_weighted_values(int dtype, const void* Vhat, const float* weights, WeightedForm form, float* part, float* pstats,
+                                  int batch, int seq_len, int H, int q_heads, hipStream_t stream) {
   if (batch == 0 || seq_len == 0) return hipSuccess;
   const int chunks = (seq_len + kWeightedChunk - 1) / kWeightedChunk;
+  if (form == kWeightedWhole ? chunks != 1 : (pstats != nullptr) != (form == kWeightedSoftMax)) return hipErrorInvalidValue;
   const unsigned grid = (unsigned)((int64_t)batch * chunks * H);
   const int rep = q_heads / H;
 #define AQUAKV_WEIGHTED(T, R) \
-  weighted_values_kernel<T, R><<<grid, kWeightedThreads, 0, stream>>>(static_cast<const T*>(Vhat), weights, part, pstats, seq_len, H, q_heads, chunks)
+  weighted_values_kernel<T, R><<<grid, kWeightedThreads, 0, stream>>>(static_cast<const T*>(Vhat), weights, part, pstats, seq_len, H, q_heads, chunks, form)
 #define AQUAKV_WEIGHTED_R(T)               \
   do {                                     \
     if (rep == 1) AQUAKV_WEIGHTED(T, 1);   \

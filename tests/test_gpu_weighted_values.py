@@ -340,3 +340,36 @@ def test_soft_max_pieces_of_long_sequences_are_merged(B, S):
     total = (s.double() - top[..., None]).exp().sum(-1)
     assert torch.equal(stats[..., 0], top)
     assert ((stats[..., 1].double() - total).abs() <= 2e-5 * total).all()
+
+
+@pytest.mark.parametrize("S,H,QH", [(1, 2, 2), (33, 1, 7), (255, 2, 16), (256, 1, 4), (257, 1, 4)])
+@pytest.mark.parametrize("with_stats", [True, False])
+def test_sequences_of_one_piece_need_no_merge(B, S, H, QH, with_stats):
+    """Up to 256 tokens the sums over values in memory are the result; one more and there is something to merge."""
+    print(f"case one piece S={S} H={H} QH={QH} stats={with_stats}", flush=True)
+    batch = 3
+    lay = U.make_layers(H, "bf16", 16)[1]
+    gen = torch.Generator().manual_seed(S + QH)
+    codes, scales = lay.alloc_codes(batch * S)
+    codes.copy_(torch.randint(0, 256, codes.shape, generator=gen).to(codes.dtype))
+    scales.copy_(torch.ones(scales.shape).half().view(torch.int16))
+    s = (torch.randn(batch, QH, S, generator=gen) * 3.0).float().cuda()
+    out = torch.full((batch, QH, 128), float("nan"), dtype=torch.float32, device="cuda")
+    given = torch.full_like(out, float("nan"))
+    stats = torch.full((batch, QH, 2), float("nan"), dtype=torch.float32, device="cuda")
+    V = lay.alloc_kv(batch * S)
+    ws = lay.alloc_weighted_workspace(batch, S, QH)
+    B.aquakv_decode_values_attend(lay, batch, S, QH, codes, scales, None, None, s, V, out, stats if with_stats else None, ws)
+    B.aquakv_decode_values_weighted(lay, batch, S, QH, codes, scales, None, None, s, V, given, ws)
+    sync()
+    v = V.view(batch, S, H, 128).double().repeat_interleave(QH // H, 2).transpose(1, 2).contiguous()     # [batch, QH, S, 128]
+    p = torch.softmax(s.double(), -1)[..., None]
+    # as above; the given weights have no exponentials, and sums of 256 fp32 terms are within 256 x 2^-24
+    assert ((out.double() - (p * v).sum(2)).abs() <= 3e-5 * (p * v.abs()).sum(2)).all()
+    w = s.double()[..., None]
+    assert ((given.double() - (w * v).sum(2)).abs() <= 2e-5 * (w * v).abs().sum(2)).all()
+    if with_stats:
+        top = s.amax(-1)
+        total = (s.double() - top[..., None]).exp().sum(-1)
+        assert torch.equal(stats[..., 0], top)
+        assert ((stats[..., 1].double() - total).abs() <= 2e-5 * total).all()
