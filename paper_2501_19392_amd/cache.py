@@ -149,7 +149,8 @@ class AquaKVCache:
             raise ValueError("one length per sequence, each at most the tokens given")
         if any(self._ns[b] + self._nc[b] + self._nb[b] + n[b] > self.max_tokens for b in range(self.batch)):
             raise ValueError("cache is full")
-        # the sources: (address, bytes from sequence to sequence) per layer, keys then values; `kept` holds what was made here
+        # the sources: (address, bytes from sequence to sequence) per layer, keys then values.  `kept` holds the tensors behind the
+        # addresses until all calls have been queued: copies made here, and what `kv` may have made when it was asked.
         most = max(n)
         like, es = self._like, self._like.element_size()
         dtype, device, kept, src = like.dtype, like.device, [], []
@@ -162,6 +163,7 @@ class AquaKVCache:
                 if x.shape == usual and x.dtype is dtype and x.device == device and x.is_contiguous():
                     at = x.data_ptr()
                     if not at & 15:
+                        kept.append(x)
                         src.append((at, per_seq))
                         continue
                 x = self._rows(x, t, most)

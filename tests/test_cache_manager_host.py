@@ -325,3 +325,38 @@ def test_sources_that_have_to_be_copied(calls, what, batch):
         src = [tuple(x if mix and l == 0 else source(x) for x in p) for l, p in enumerate(kv)]
         cache.append([tuple(x[0] for x in p) for p in src] if batch == 1 else src)
         check(cache, kv, [n] * batch)
+
+
+@pytest.mark.parametrize("batch", [1, 3])
+@pytest.mark.parametrize("made", ["pairs", "tensors", "iterator"])
+def test_sources_made_on_access(calls, made, batch):
+    """Tensors that the given sequence makes when it is asked for them belong to nobody else: append holds them until all of its calls
+    have been queued."""
+    layers, n = [LAYER0, LAYER, LAYER], 25
+    kv = stream(layers, batch, n, seed=8)
+    new = lambda x: (x[0] if batch == 1 else x) * 1.0
+
+    class Pair:
+        def __init__(self, pair):
+            self.pair = pair
+
+        def __len__(self):
+            return 2
+
+        def __getitem__(self, i):
+            return new(self.pair[i])
+
+    class Made:
+        def __len__(self):
+            return len(kv)
+
+        def __getitem__(self, l):
+            return Pair(kv[l]) if made == "tensors" else tuple(new(x) for x in kv[l])
+
+        if made == "iterator":
+            def __iter__(self):
+                return (tuple(new(x) for x in p) for p in kv)
+
+    cache = new_cache(layers, batch, n)
+    cache.append(Made())
+    check(cache, kv, [n] * batch)
