@@ -202,7 +202,8 @@ template <int N> __device__ __forceinline__ float group_dot(const float (&a)[N],
 // The compiler does not fold the lane permute into a multiply-add, so the stage is written as
 // v_fmac_f32 with a DPP quad permute on its first source (dst += permuted(dst) * s).  A DPP
 // read of a register written by the VALU instruction just before it needs two idle issue
-// slots; the compiler cannot see into the block, so each block of 16 starts with them.
+// slots; the compiler cannot see into the block, so each block of 16 starts with them.  A lane swap (v_permlane16_swap) needs
+// them just as well, and the compiler does not count the block's writes: the stage that swaps follow (MASK 8) ends with them too.
 #define AQUAKV_FMAC_DPP(i, perm) "v_fmac_f32_dpp %" #i ", %" #i ", %16 " perm " row_mask:0xf bank_mask:0xf\n\t"
 #define AQUAKV_FMAC_DPP16(perm)                                                                               \
   "s_nop 1\n\t" AQUAKV_FMAC_DPP(0, perm) AQUAKV_FMAC_DPP(1, perm) AQUAKV_FMAC_DPP(2, perm) AQUAKV_FMAC_DPP(3, perm)  \
@@ -222,7 +223,7 @@ template <int MASK, int N> __device__ __forceinline__ void wht_lane_stage(float 
     if constexpr (MASK == 1) asm(AQUAKV_FMAC_DPP16("quad_perm:[1,0,3,2]") AQUAKV_FMAC_ARGS);
     else if constexpr (MASK == 2) asm(AQUAKV_FMAC_DPP16("quad_perm:[2,3,0,1]") AQUAKV_FMAC_ARGS);
     else if constexpr (MASK == 7) asm(AQUAKV_FMAC_DPP16("row_half_mirror") AQUAKV_FMAC_ARGS);
-    else asm(AQUAKV_FMAC_DPP16("row_ror:8") AQUAKV_FMAC_ARGS);
+    else asm(AQUAKV_FMAC_DPP16("row_ror:8") "s_nop 1" AQUAKV_FMAC_ARGS);
   }
 }
 

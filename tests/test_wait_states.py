@@ -1,6 +1,10 @@
-"""The built kernels keep the wait states between a matrix instruction and the vector instructions that read its result, on every path:
-a walk over the disassembly of libaquakv.so from each v_mfma_f32_32x32x16_bf16 (8 passes: 12 states, which is what the compiler keeps on
-the paths that it counts)."""
+"""The built kernels keep the wait states that the hardware does not, on every path: walks over the disassembly of libaquakv.so.
+
+* Between a matrix instruction and the vector instructions that read its result, from each v_mfma_f32_32x32x16_bf16 (8 passes: 12 states,
+  which is what the compiler keeps on the paths that it counts).
+* Between a vector instruction and the lane permutes (DPP) and lane swaps (v_permlane*) that read its result: 2 states.  The compiler
+  keeps them between instructions of its own and does not look into assembly, so blocks of assembly carry them at their edges.
+* LDS words that assembly requests and waits for later are left alone until they have arrived."""
 import os
 import re
 import shutil
@@ -65,18 +69,111 @@ def shortest(code, labels, start):
     return best
 
 
-def test_results_of_matrix_instructions_are_not_read_early(tmp_path):
+def permutes(op, args):
+    return op.startswith("v_permlane") or op.endswith("_dpp") or "quad_perm" in args or " row_" in args
+
+
+def results(op, args):
+    """Vector registers that a vector instruction writes; a lane swap writes both of its operands."""
+    if not op.startswith("v_") or op.startswith("v_mfma"):
+        return set()
+    return registers(",".join(args.split(",")[:2 if op.startswith("v_permlane") or op == "v_swap_b32" else 1]))
+
+
+def permuted_early(code, labels, start, states=2):
+    """Whether a lane permute or swap reads a result of the vector instruction at `start` before `states` have passed."""
+    result, paths = results(*code[start]), [(start + 1, 0)]
+    while paths:
+        at, w = paths.pop()
+        while at < len(code) and w < states and code[at][0] != "s_endpgm":
+            op, args = code[at]
+            if permutes(op, args) and registers(args) & result:
+                return True
+            w += int(args, 0) + 1 if op == "s_nop" else 1
+            if op == "s_branch" or op.startswith("s_cbranch"):
+                paths.append((labels[re.search(r"L\d+", args)[0]], w))
+                if op == "s_branch":
+                    break
+            at += 1
+    return False
+
+
+@pytest.fixture(scope="module")
+def built(tmp_path_factory):
+    """functions() of every code object in the library"""
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump")
+    tmp_path = tmp_path_factory.mktemp("objects")
     shutil.copy(B.LIB_PATH, tmp_path / "lib.so")
     subprocess.run([OBJDUMP, "--offloading", "lib.so"], cwd=tmp_path, check=True, capture_output=True)
-    checked = 0
+    out = []
     for obj in sorted(tmp_path.glob("lib.so.*gfx950")):
-        listing = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--symbolize-operands", str(obj)], check=True, capture_output=True,
-                                 text=True).stdout.splitlines()
-        for name, code, labels in functions(listing):
-            for i, (op, _) in enumerate(code):
-                if op == "v_mfma_f32_32x32x16_bf16":
-                    checked += 1
-                    assert shortest(code, labels, i) >= STATES, (name, i)
+        out += functions(subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--symbolize-operands", str(obj)], check=True, capture_output=True,
+                                        text=True).stdout.splitlines())
+    return out
+
+
+def test_results_of_matrix_instructions_are_not_read_early(built):
+    checked = 0
+    for name, code, labels in built:
+        for i, (op, _) in enumerate(code):
+            if op == "v_mfma_f32_32x32x16_bf16":
+                checked += 1
+                assert shortest(code, labels, i) >= STATES, (name, i)
     assert checked > 1000
+
+
+def test_results_of_vector_instructions_are_not_permuted_early(built):
+    swaps = 0
+    for name, code, labels in built:
+        near = [False] * (len(code) + 2)                 # a permute, or a branch that may lead to one, is among the next two
+        for i, (op, args) in enumerate(code):
+            swaps += op.startswith("v_permlane")
+            if permutes(op, args) or op.startswith(("s_branch", "s_cbranch")):
+                near[max(i - 1, 0)] = near[max(i - 2, 0)] = True
+        for i, (op, args) in enumerate(code):
+            if near[i] and results(op, args):
+                assert not permuted_early(code, labels, i), (name, i, code[i:i + 4])
+    assert swaps > 1000
+
+
+def test_assembly_ahead_of_lane_swaps_ends_with_wait_states(built):
+    """The stage of the transform that lane swaps follow: 16 multiply-adds in one block, whichever instruction comes after it."""
+    blocks = 0
+    for name, code, _ in built:
+        run = 0
+        for i, (op, args) in enumerate(code):
+            if op == "v_fmac_f32_dpp" and "row_ror:8" in args:
+                run += 1
+                if run % 16 == 0:
+                    blocks += 1
+                    assert code[i + 1][0] == "s_nop" and int(code[i + 1][1], 0) >= 1, (name, i, code[i:i + 3])
+    assert blocks > 10
+
+
+def test_lds_words_requested_by_assembly_are_left_alone(built):
+    """The main loop of the stand-alone predictor posts its count (ds_write_b32) and requests the team's four (ds_read_b128), which
+    arrive by the next wait for all of the LDS: nothing else reads or writes their registers before, whichever way the code goes."""
+    requests = 0
+    for name, code, labels in built:
+        if "predict_bf16_kernel" not in name:
+            continue
+        for i, (op, args) in enumerate(code):
+            if op != "ds_read_b128" or "offset" in args or not any(o == "ds_write_b32" for o, _ in code[max(i - 6, 0):i]):
+                continue
+            requests += 1
+            words, seen, paths = registers(args.split(",")[0]), set(), [i + 1]
+            while paths:
+                at = paths.pop()
+                while at not in seen:
+                    seen.add(at)
+                    op, args = code[at]
+                    if op == "s_waitcnt" and "lgkmcnt(0)" in args:
+                        break
+                    assert op != "s_endpgm" and not registers(args) & words, (name, i, at, code[at])
+                    if op == "s_branch" or op.startswith("s_cbranch"):
+                        paths.append(labels[re.search(r"L\d+", args)[0]])
+                        if op == "s_branch":
+                            break
+                    at += 1
+    assert requests >= 2
