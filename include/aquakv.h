@@ -136,11 +136,14 @@ int aquakv_build_search_table(const float* codebook, int32_t vq_dim, int32_t n_c
                               void* table, void* stream);
 
 /* Bytes of device workspace the three layer-level calls below need for `tokens`
- * rows (0 on invalid arguments).  Its front part holds the fp32 predictions of one
+ * rows (0 on invalid arguments).  Each of these calls, the decoding ones included, may
+ * write all of them.  They hold, from the front, the fp32 predictions of one
  * chunk of rows (fp32 layers) or the re-tiled predictor weights (bf16 layers with
- * rotation groups across the heads; nothing for the other bf16 layers); behind it
- * a temporary Khat for one chunk of rows when the caller does not ask for one (or partial
- * sums and predictions of the call, halves of which lie in Khat / Vhat until it has finished).
+ * rotation groups across the heads, encode); behind that a temporary Khat for one chunk
+ * of rows when the caller does not ask for one, or else predictions (groups across the
+ * heads).  Ranges of few rows of any bf16 layer put partial sums of the values at the
+ * front instead.  Of such predictions and sums the other half lies in Khat / Vhat until the
+ * call has finished.
  * More is used where it helps, if workspace_bytes says that it is there: with
  * rotation groups across the heads, a Khat or Vhat that is not asked for, or is over K or V, has no
  * room for half of the predictions, and ranges of up to 12288 rows are then encoded in as

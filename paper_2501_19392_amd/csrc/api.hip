@@ -219,15 +219,18 @@ bool clear_of(const aquakv_layer* L, const Plan& pl, const Range& all, const Ran
   return true;
 }
 
-// Bytes of the workspace an encode call over `tokens` rows uses: the `need` bytes every caller provides, and where more
-// predictions help up to as much as those of all rows take.  Not if the bytes behind the first `need` lie over the call's other
+// Bytes of the workspace an encode call over `tokens` rows uses: the `sure` bytes it cannot do without, the `need` bytes every caller
+// provides (the room of a temporary Khat holds predictions where there is a Khat to write to), and where more predictions help up to as
+// much as those of all rows take.  What lies behind the first `sure` bytes is left alone if any of it is over the call's other
 // buffers or the layer's parameters: an arena's owner may state all that is left of it.
-size_t usable_workspace(const aquakv_layer* L, const Plan& pl, int64_t tokens, void* workspace, size_t need, size_t bytes,
+size_t usable_workspace(const aquakv_layer* L, const Plan& pl, int64_t tokens, void* workspace, size_t sure, size_t need, size_t bytes,
                         const Range* outs, int n_out, const Range* ins, int n_in) {
-  if (!pl.fused || !is_wide(L) || (L->d_in_k == 0 && L->d_in_v == 0) || tokens > kWideSplitRows) return need;
-  const size_t most = need + (size_t)tokens * pl.D * sizeof(float);
-  const Range all = {workspace, bytes < most ? bytes : most, ""};
-  return clear_of(L, pl, all, outs, n_out, ins, n_in) ? all.n : need;
+  if (!pl.fused || !is_wide(L) || (L->d_in_k == 0 && L->d_in_v == 0)) return sure;
+  const size_t all = need + (size_t)tokens * pl.D * sizeof(float);
+  const size_t most = tokens > kWideSplitRows ? need : bytes < all ? bytes : all;
+  for (const size_t n : {most, need})
+    if (n > sure && clear_of(L, pl, {workspace, n, ""}, outs, n_out, ins, n_in)) return n;
+  return sure;
 }
 // Keys and values of `tokens` rows can run as launch_fused_layer, given room for half of its sums and, in Vhat, for the other half.
 inline bool layer_at_once(const aquakv_layer* L, const Plan& pl, int64_t tokens, const void* V, const void* Vhat) {
@@ -503,6 +506,7 @@ int aquakv_encode_layer(const aquakv_layer* L, int64_t tokens, const void* K, co
     return fail(AQUAKV_EWORKSPACE, "workspace %zu B < required %zu B", workspace_bytes, pl.p_bytes + pl.khat_bytes);
 
   const size_t row = (size_t)pl.D * pl.eb;
+  const bool khat_in_workspace = Khat == nullptr && has_v;
   size_t usable;
   bool at_once;
   {
@@ -514,8 +518,9 @@ int aquakv_encode_layer(const aquakv_layer* L, int64_t tokens, const void* K, co
                          {Vhat_prev, has_v ? t * (L->d_in_v - pl.D) * pl.eb : 0, "Vhat_prev"}};
     const void* const inplace[] = {K, V, nullptr, nullptr, nullptr, nullptr, nullptr};
     CHECK(check_no_alias(outs, 7, ins, 4, inplace));
-    usable = usable_workspace(L, pl, tokens, workspace, pl.p_bytes + pl.khat_bytes, workspace_bytes, outs, 6, ins, 4);
-    // (with a Khat to write to, the room of a temporary one is free; it may have been stated over the layer's parameters)
+    usable = usable_workspace(L, pl, tokens, workspace, pl.p_bytes + (khat_in_workspace ? pl.khat_bytes : 0), pl.p_bytes + pl.khat_bytes,
+                              workspace_bytes, outs, 6, ins, 4);
+    // (half of the sums goes where a temporary Khat would lie)
     at_once = Khat != nullptr && !is_wide(L) && layer_at_once(L, pl, tokens, V, Vhat) &&
               clear_of(L, pl, {workspace, t * row, ""}, outs, 6, ins, 4);
   }
@@ -523,7 +528,7 @@ int aquakv_encode_layer(const aquakv_layer* L, int64_t tokens, const void* K, co
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   float* Pbuf = static_cast<float*>(workspace);
   // predictions at the front, the temporary Khat (if one is needed) at the back
-  const size_t room = Khat != nullptr || !has_v ? usable : (usable - pl.khat_bytes) & ~(size_t)15;
+  const size_t room = khat_in_workspace ? (usable - pl.khat_bytes) & ~(size_t)15 : usable;
   void* khat_tmp = static_cast<unsigned char*>(workspace) + room;
 
   if (at_once) {
@@ -638,7 +643,7 @@ int aquakv_encode_keys(const aquakv_layer* L, int64_t tokens, const void* K, con
     const Range ins[] = {{K, t * row, "K"}, {Khat_prev, t * L->d_in_k * pl.eb, "Khat_prev"}};
     const void* const inplace[] = {K, nullptr, nullptr, nullptr};
     CHECK(check_no_alias(outs, 4, ins, 2, inplace));
-    room = pl.p_bytes == 0 ? 0 : usable_workspace(L, pl, tokens, workspace, pl.p_bytes, workspace_bytes, outs, 3, ins, 2);
+    room = pl.p_bytes == 0 ? 0 : usable_workspace(L, pl, tokens, workspace, pl.p_bytes, pl.p_bytes, workspace_bytes, outs, 3, ins, 2);
   }
   for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk) {
     const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;
@@ -676,7 +681,7 @@ int aquakv_encode_values(const aquakv_layer* L, int64_t tokens, const void* V, c
                          {Khat, has_v ? t * row : 0, "Khat"}};
     const void* const inplace[] = {V, nullptr, nullptr, nullptr};
     CHECK(check_no_alias(outs, 4, ins, 3, inplace));
-    room = pl.p_bytes == 0 ? 0 : usable_workspace(L, pl, tokens, workspace, pl.p_bytes, workspace_bytes, outs, 3, ins, 3);
+    room = pl.p_bytes == 0 ? 0 : usable_workspace(L, pl, tokens, workspace, pl.p_bytes, pl.p_bytes, workspace_bytes, outs, 3, ins, 3);
   }
   for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk) {
     const int64_t n = tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk;

@@ -163,6 +163,41 @@ def test_parameters_behind_the_needed_workspace_are_left_alone(name):
         setattr(lg.c, name, getattr(lg, name).data_ptr())
 
 
+@pytest.mark.parametrize("name,T,rht_group", [("b_v", 2100, 1024), ("w_v", 2100, 1024), ("w_k", 19000, 1024), ("search_table", 5000, 1024),
+                                              ("b_v", 300, None), ("codebook", 300, 1024)])
+def test_parameters_in_the_room_of_a_temporary_khat_are_left_alone(name, T, rht_group):
+    """With a Khat to write to, the workspace's room for a temporary one is not needed: a parameter of the layer may lie there, and
+    neither predictions nor sums of the call are put over it."""
+    from paper_2501_19392_amd import binding as B
+    D = 1024
+    print(f"case {name} in the room of Khat, T={T} group={rht_group}", flush=True)
+    lg = layer(8, 1024, "n16", rht_group)
+    if lg.search_table is None:
+        lg.search_table = B.build_search_table(lg.codebook)
+        lg.c.search_table = lg.search_table.data_ptr()
+    g = torch.Generator(device="cuda").manual_seed(T)
+    K, V, Kp, Vp = (torch.randn(T, D, generator=g, device="cuda").bfloat16() for _ in range(4))
+
+    def encode_decode(workspace):
+        codes = [t for _ in range(2) for t in lg.alloc_codes(T)]
+        hats = [lg.alloc_kv(T) for _ in range(4)]
+        B.aquakv_encode_layer(lg, T, K, V, Kp, Vp, *codes, *hats[:2], workspace)
+        B.aquakv_decode_layer(lg, T, *codes, Kp, Vp, *hats[2:], workspace)
+        torch.cuda.synchronize()
+        return codes + hats
+
+    want = encode_decode(lg.alloc_workspace(T))
+    x = bits(getattr(lg, name)).flatten()
+    arena = torch.zeros(B.aquakv_workspace_bytes(lg, T), dtype=torch.uint8, device="cuda")
+    at = arena.numel() - T * D * 2                     # behind the weights in another order, where there are such
+    arena[at:at + x.numel()] = x
+    setattr(lg.c, name, arena.data_ptr() + at)
+    got = encode_decode(arena)
+    assert torch.equal(arena[at:at + x.numel()], x)
+    for a, b in zip(got, want, strict=True):
+        assert torch.equal(bits(a), bits(b))
+
+
 @pytest.mark.parametrize("T", [1, 130, 511, 512, 513])
 @pytest.mark.parametrize("quantizer,rht_group", [("n16", None), ("n64", None), ("rtn4", None), ("n256", 1024)])
 def test_keys_and_values_of_few_rows_at_once(T, quantizer, rht_group):
