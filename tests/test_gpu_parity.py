@@ -94,6 +94,38 @@ def test_quantize_codes_scales_and_reconstruction(B, dtype, n, T, H, with_p, tab
                            Xhat.view(torch.int16 if dtype == "bf16" else torch.int32))
 
 
+@pytest.mark.parametrize("H,T", [(64, 385), (64, 1100), (24, 1400), (33, 1900), (61, 802), (61, 1070), (320, 110)])
+@pytest.mark.parametrize("dtype,with_p", [("bf16", True), ("fp32", False)])
+def test_signs_of_many_heads_over_several_rounds(B, dtype, H, T, with_p):
+    """Head counts that no workgroup's 32 groups are a multiple of: the launch's stride is one, or (61 heads: 802 tokens with a prediction,
+    1070 without) that would take more workgroups than are resident, and the signs are fetched in every round.  Rows from every round against the oracle, and all rows against calls of one round."""
+    print(f"case heads H={H} T={T} {dtype} with_p={with_p}", flush=True)
+    n = 16
+    lo, lg = U.make_layers(H, dtype, n, table=True)
+    X = storage_randn((T, H, 128), dtype, 14)
+    P = (storage_randn((T, H * 128), "fp32", 15) * 0.8).reshape(T, H, 128).contiguous() if with_p else None
+    codes, scales = lg.alloc_codes(T)
+    Xhat, X2 = lg.alloc_kv(T), lg.alloc_kv(T)
+    B.aquakv_quantize(lg, B.AQUAKV_KEY, T, X, P, codes, scales, Xhat)
+    B.aquakv_dequantize(lg, B.AQUAKV_KEY, T, codes, scales, P, X2)
+    sync()
+    assert torch.equal(bits(X2), bits(Xhat))
+    rows = torch.tensor(sorted({0, T // 3, T // 2, T - 40 if T > 40 else 0, T - 2, T - 1}))
+    at = rows.cuda()
+    p64 = 0.0 if P is None else U.np64(P[at])
+    rep = U.compare_quantizer_outputs(U.np64(X[at]) - p64, lo.signs_k, lo.codebook, codes[at].cpu().numpy(), scales[at].cpu().numpy(), n)
+    assert rep.other == 0, str(rep)
+    assert rep.code_mismatch <= max(2, rep.subvectors // 20000) and rep.scale_mismatch <= max(1, rep.groups // 500)
+    step = 384 * 32 // H                               # one round, however few workgroups are resident
+    for r in range(0, T, step):
+        m = min(step, T - r)
+        c1, s1 = lg.alloc_codes(m)
+        h1 = lg.alloc_kv(m)
+        B.aquakv_quantize(lg, B.AQUAKV_KEY, m, X[r:r + m], None if P is None else P[r:r + m], c1, s1, h1)
+        sync()
+        assert torch.equal(c1, codes[r:r + m]) and torch.equal(s1, scales[r:r + m]) and torch.equal(bits(h1), bits(Xhat[r:r + m])), r
+
+
 @pytest.mark.parametrize("dtype,n", [("fp32", 16), ("bf16", 64), ("bf16", 256)])
 def test_dequantize_random_codes(B, dtype, n):
     print(f"case dequantize dtype={dtype} n={n}", flush=True)
