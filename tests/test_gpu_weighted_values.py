@@ -373,3 +373,36 @@ def test_sequences_of_one_piece_need_no_merge(B, S, H, QH, with_stats):
         total = (s.double() - top[..., None]).exp().sum(-1)
         assert torch.equal(stats[..., 0], top)
         assert ((stats[..., 1].double() - total).abs() <= 2e-5 * total).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("S,QH", [(1, 1), (33, 3), (255, 4), (300, 8), (512, 2)])
+def test_infinite_values_of_the_last_token_are_counted_once(B, dtype, S, QH):
+    """The rows that a piece asks for behind the end of a sequence are the last token's again: if that one holds infinities, they come
+    out as its own term and nothing of them (0 x infinity) in any other.  512: no row behind the end."""
+    print(f"case infinite last values S={S} QH={QH} {dtype}", flush=True)
+    batch = 2
+    lay = U.make_layers(1, dtype, 16, rtn_bits=2)[1]
+    gen = torch.Generator().manual_seed(S)
+    codes, meta = lay.alloc_codes(batch * S)               # groups of 64 values: (fp16 step, zero point)
+    codes.copy_(torch.randint(0, 256, codes.shape, generator=gen).to(codes.dtype))
+    meta[..., 0] = int(np.float16(0.5).view(np.int16))
+    meta[..., 1] = 0
+    codes[S - 1::S, :, :16] = 0xFF                         # the first 64 values of every sequence's last token: 3 steps
+    meta[S - 1::S, 0, 0] = int(np.float16(np.inf).view(np.int16))
+    w = torch.randn(batch, QH, S, generator=gen).float()
+    w[:, :, -1] = w[:, :, -1].abs() + 0.5
+    w = w.cuda()
+    V = lay.alloc_kv(batch * S)
+    out, given = (torch.full((batch, QH, 128), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+    ws = lay.alloc_weighted_workspace(batch, S, QH)
+    B.aquakv_decode_values_attend(lay, batch, S, QH, codes, meta, None, None, w, V, out, None, ws)
+    B.aquakv_decode_values_weighted(lay, batch, S, QH, codes, meta, None, None, w, V, given, ws)
+    sync()
+    v = V.view(batch, S, 128).double()
+    assert bool(torch.isinf(v[:, -1, :64]).all()) and bool(torch.isfinite(v[:, :-1]).all()) and bool(torch.isfinite(v[:, :, 64:]).all())
+    for got, weights in ((out, torch.softmax(w.double(), -1)), (given, w.double())):
+        assert bool((got[..., :64] == float("inf")).all())
+        want, mag = (torch.matmul(a, b) for a, b in ((weights, v[..., 64:].contiguous()), (weights.abs(), v[..., 64:].abs().contiguous())))
+        # sums of up to 512 fp32 terms, exponentials as above
+        assert bool(((got[..., 64:].double() - want).abs() <= 3e-5 * mag).all())
