@@ -146,8 +146,8 @@ int aquakv_build_search_table(const float* codebook, int32_t vq_dim, int32_t n_c
  * call has finished.
  * More is used where it helps, if workspace_bytes says that it is there: with
  * rotation groups across the heads, a Khat or Vhat that is not asked for, or is over K or V, has no
- * room for half of the predictions, and ranges of up to 12288 rows are then encoded in as
- * few pieces as there is room for all of them, at most kv_heads * head_dim * 4
+ * room for half of the predictions, and ranges of up to 12288 rows may then be encoded in
+ * as few pieces as there is room for all of them, at most kv_heads * head_dim * 4
  * bytes per row beyond what is needed and never over buffers of the call or of the
  * layer.  So what lies within workspace_bytes belongs to the call while it runs:
  * calls that run at the same time need workspaces that do not overlap. */

@@ -200,7 +200,7 @@ Plan make_plan(const aquakv_layer* L, int64_t tokens) {
 }
 
 // Encode of rotation groups across the 8 heads (encode_wide): rows that the kernel of whole tokens takes in one round over the
-// CUs, and up to how many left over from its rounds are quantized from fp32 predictions.
+// CUs, and up to how many left over from its rounds may be quantized from fp32 predictions (wide_split_rows).
 constexpr int64_t kWideRoundRows = 16384, kWideSplitRows = 12288;
 
 // Whether `all` lies over none of the call's buffers (outs: without the workspace it is part of) nor the layer's parameters.
@@ -249,12 +249,26 @@ inline aquakv::QuantizeIo coded(const int8_t* signs, const void* codes, const vo
   return {nullptr, signs, static_cast<uint8_t*>(const_cast<void*>(codes)), static_cast<uint16_t*>(const_cast<void*>(scales)), hat};
 }
 
+// Up to how many rows predictions in `pieces` pieces are cheaper than another round of whole tokens; `ahead`: behind such rounds, where
+// inputs and predictions of a large range come from memory.  Every piece starts both launches anew, and the round costs more the
+// more points there are to search (uniform backbone: none).  Keys and values, us, predictions / whole tokens.  One piece: 16 points 4096 rows
+// 74 / 152, 8192 115 / 153, 12288 139 / 156, 13000 155 / 158 (uniform 60 / 111, 97 / 111, 117 / 117, 129 / 119); behind a round, with it,
+// 4096 rows 258 / 314, 9000 316 / 323, 12288 327 / 326 (uniform 201 / 234, 261 / 245, 273 / 251).  Two pieces of both tensors (in place):
+// 8192 138 / 145 (uniform 116 / 113, 7000: 110 / 112), 9000 199 / 144; behind a round (no Khat) 4096 289 / 315.  Three: 6000 147 / 153
+// (uniform 119 / 112), behind a round 336 / 317 (256 points 419 / 439).  Four: 7000 187 / 153; of the values alone 4096 130 / 146, behind a
+// round 299 / 290 (256 points 383 / 418).
+inline int64_t wide_split_rows(const aquakv_layer* L, bool ahead, int64_t pieces) {
+  constexpr int64_t rows[3][2][4] = {{{kWideSplitRows, 8192, 6144, 4096}, {kWideSplitRows, 4096, 3072, 0}},
+                                     {{kWideSplitRows, 8192, 6144, 4096}, {kWideSplitRows, 6144, 6144, 4096}},      // 256 points
+                                     {{kWideSplitRows, 7168, 4096, 4096}, {4096, 4096, 3072, 0}}};                  // uniform
+  return pieces < 1 || pieces > 4 ? 0 : rows[is_rtn(L) ? 2 : L->n_codewords == 256][ahead][pieces - 1];
+}
+
 // Encode of n rows of one tensor with rotation groups across the 8 heads.  The kernel that owns whole tokens walks all of W in
 // every workgroup of 64 tokens, so a round of it over the CUs costs the same however few of them it fills.  It takes whole rounds;
-// what is left over runs as predictor and stand-alone quantizer if that is cheaper than another round: predictions in fp32, half
-// of each row in the workspace (`room` bytes) and half in the row of Xhat that comes to lie over it, or, without an Xhat of its
-// own, all of it in the workspace; in pieces of as many rows as there is room for.  Keys and values, us, predictions against rounds of
-// whole tokens alone: 4096 rows 64 / 140, 8192 111 / 141, 10007 140 / 149, 12288 145 / 151, 14000 164 / 156; 20000 226 / 296.
+// what is left over runs as predictor and stand-alone quantizer if that is cheaper than another round (wide_split_rows): predictions in
+// fp32, half of each row in the workspace (`room` bytes) and half in the row of Xhat that comes to lie over it, or, without an Xhat of its
+// own, all of it in the workspace; in pieces of as many rows as there is room for.
 int encode_wide(const aquakv_layer* L, const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias,
                 const int8_t* signs, const void* X, uint8_t* codes, uint16_t* scales, void* Xhat, int64_t n, int D, float* ws,
                 size_t room, hipStream_t stream) {
@@ -263,7 +277,7 @@ int encode_wide(const aquakv_layer* L, const void* x0, int d0, const void* x1, i
   const bool halves = Xhat != nullptr && Xhat != X;
   const int64_t fit = (int64_t)(room / (halves ? row : (size_t)D * sizeof(float)));
   const int64_t pieces = fit > 0 ? (rest + fit - 1) / fit : 0, piece = pieces > 0 ? (rest + pieces - 1) / pieces : 0;
-  const int64_t whole = rest > kWideSplitRows || pieces == 0 || pieces > 4 ? n : n - rest;
+  const int64_t whole = rest > wide_split_rows(L, n != rest, pieces) ? n : n - rest;
   if (whole != 0)
     HIP_TRY(aquakv::launch_fused_encode_wide(quantizer_id(L), x0, d0, x1, d1, W, ws, bias, signs, L->codebook, L->search_table, X,
                                              codes, scales, Xhat, whole, D, stream));

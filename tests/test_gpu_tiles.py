@@ -267,3 +267,40 @@ def test_groups_across_heads_over_the_rounds_of_whole_tokens(T, quantizer):
     B.aquakv_encode_values(lg, T, V, Vp, kh, got[2], got[3], None, ws)
     torch.cuda.synchronize()
     assert all(torch.equal(bits(a), bits(b)) for a, b in zip(got, want)) and torch.equal(bits(kh), bits(Kh))
+
+
+@pytest.mark.parametrize("T,quantizer,keys,values,split", [
+    (8192, "n16", "in place", "in place", True), (8193, "n16", "in place", "in place", False),        # two pieces
+    (7168, "rtn2", "in place", "in place", True), (7169, "rtn2", "in place", "in place", False),
+    (11000, "n256", "in place", None, False), (16384 + 4097, "rtn4", "own", "own", False), (16384 + 4096, "rtn4", "own", "own", True),
+    (6144, "n64", None, "own", True), (6145, "n64", None, "own", False)])                             # three pieces, four
+def test_groups_across_heads_in_several_pieces(T, quantizer, keys, values, split):
+    """Where the workspace holds the predictions of few rows only, pieces of them are taken up to the range where a round of whole
+    tokens costs less: beyond it nothing is written behind the weights and the temporary Khat.  The bits of the stage calls either way."""
+    from paper_2501_19392_amd import binding as B
+    print(f"case pieces T={T} {quantizer} keys={keys} values={values}", flush=True)
+    lg, D = layer(8, 1024, quantizer, 1024, bias=T % 2 == 1), 1024
+    g = torch.Generator(device="cuda").manual_seed(T)
+    K, V, Kp, Vp = (torch.randn(T, 8, 128, generator=g, device="cuda").bfloat16() for _ in range(4))
+    P = torch.empty(T, D, dtype=torch.float32, device="cuda")
+    new = lambda: [*lg.alloc_codes(T), *lg.alloc_codes(T)]
+    want, Kh, Vh = new(), lg.alloc_kv(T), lg.alloc_kv(T)
+    for which, x0, x1, X, c, s, hat in ((B.AQUAKV_KEY, Kp, None, K, *want[:2], Kh), (B.AQUAKV_VALUE, Vp, Kh, V, *want[2:], Vh)):
+        B.aquakv_predict(lg, which, T, x0, x1, P)
+        B.aquakv_quantize(lg, which, T, X, P, c, s, hat)
+    arena = torch.full((B.aquakv_workspace_bytes(lg, T),), 0xCD, dtype=torch.uint8, device="cuda")
+    got, kh, vh = new(), {"own": Kh.clone(), "in place": K.clone(), None: None}[keys], {"own": Vh.clone(), "in place": V.clone(), None: None}[values]
+    k, v = (kh if keys == "in place" else K), (vh if values == "in place" else V)
+    B.aquakv_encode_layer(lg, T, k, v, Kp, Vp, *got, kh, vh, arena)
+    torch.cuda.synchronize()
+    for a, b in list(zip(got, want)) + [(kh, Kh), (vh, Vh)]:
+        assert a is None or torch.equal(bits(a), bits(b))
+    weights = D * 2 * D * 2                                # the predictors' in the order of the encoder's main loop
+    if keys is None:                                       # behind them the temporary Khat: the predictions lie among the weights'
+        hat = arena[weights:weights + T * D * 2].view(torch.int16).view(T, 8, 128)
+        assert torch.equal(hat, Kh.view(torch.int16))
+        lay = lg.w_v.flatten().view(torch.int16)
+        sorted_front = arena[:weights].view(torch.int16).sort().values
+        assert torch.equal(sorted_front, lay.sort().values) != split
+    else:
+        assert bool((arena[weights:] != 0xCD).any()) == split
