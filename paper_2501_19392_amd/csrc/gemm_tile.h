@@ -7,6 +7,8 @@
 //     operands from L2, (rows + 128) x 128 bytes per k-tile of 64, most of it W: a deep ring of k-tiles in LDS keeps it
 //     coming, and a wave reads the fragments of a whole k-tile ahead (its steps of 16 k are one or two MFMAs long).
 //     Measured with 32 rows: 0.18 us per k-tile = 57 bytes per cycle into a CU, of 64; a 256-row tile takes 0.6 to 0.9.
+//     The next loads are issued behind the first MFMA of a k-tile, which covers them: ahead of it, where the compiler put them while
+//     that was left to it, with two additions per fragment address, one tensor took 2 to 5 % longer (128 rows, uniform backbone, keys 7.34 -> 6.98 us).
 //   * From 128 rows on: eight waves (two per SIMD) as 2 x 4, wave (wm, wn) holds columns 32 wn ... and every second block
 //     of 32 rows: (MI + 1) / MI operand reads per MFMA, MI = rows / 64.
 #pragma once
@@ -97,9 +99,22 @@ __device__ __forceinline__ void TileLoop<MB>::run(unsigned char* lds_base, const
 
   struct Frag { bf16x8 v[MI + 1]; };
   const int frow = lane & 31, fk = lane >> 5;
+  auto frag_off = [&](int ks, int pc) { return lds_off((pc < MI ? S::block_row(pc, wm) : wn * 32) + frow, ks * 2 + fk); };
+  // Where waves read whole k-tiles ahead, a fragment's place in a stage is kept in a register (opaque: the compiler would share parts
+  // of them and add twice for each read).
+  int kept[kAhead == 4 ? 4 : 1][MI + 1];
+  if constexpr (kAhead == 4) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int pc = 0; pc <= MI; ++pc) {
+        kept[ks][pc] = frag_off(ks, pc);
+        asm("" : "+v"(kept[ks][pc]));
+      }
+  }
   auto frag_piece = [&](int stage_off, int ks, Frag& f, int pc) {
-    const int off = pc < MI ? lds_off(S::block_row(pc, wm) + frow, ks * 2 + fk) : S::kATile + lds_off(wn * 32 + frow, ks * 2 + fk);
-    f.v[pc] = *reinterpret_cast<const bf16x8*>(lds_base + stage_off + off);
+    const int off = kAhead == 4 ? kept[kAhead == 4 ? ks : 0][pc] : frag_off(ks, pc);
+    f.v[pc] = *reinterpret_cast<const bf16x8*>(lds_base + stage_off + off + (pc < MI ? 0 : S::kATile));
   };
   auto read_frag = [&](int stage_off, int ks, Frag& f) {
 #pragma unroll
@@ -159,14 +174,12 @@ __device__ __forceinline__ void TileLoop<MB>::run(unsigned char* lds_base, const
     if constexpr (kAhead == 4) {
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        if (s == 0 && has_next) {
-          publish();
-          if (do_load) {
-#pragma unroll
-            for (int pc = 0; pc < kPieces; ++pc) load_piece(t + kStages, cur, pc);
-          }
-        }
+        if (s == 0 && has_next) publish();
         mma(f[s], [](int) {});
+        if (s == 0 && do_load) {                      // behind the first MFMAs: their issue takes as long as one of those
+#pragma unroll
+          for (int pc = 0; pc < kPieces; ++pc) load_piece(t + kStages, cur, pc);
+        }
         if (has_next) read_frag(nxt, s, f[s]);        // behind the MFMAs that used this buffer
         __builtin_amdgcn_sched_barrier(0);
       }

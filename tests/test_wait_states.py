@@ -4,7 +4,9 @@
   which is what the compiler keeps on the paths that it counts).
 * Between a vector instruction and the lane permutes (DPP) and lane swaps (v_permlane*) that read its result: 2 states.  The compiler
   keeps them between instructions of its own and does not look into assembly, so blocks of assembly carry them at their edges.
-* LDS words that assembly requests and waits for later are left alone until they have arrived."""
+* LDS words that assembly requests and waits for later are left alone until they have arrived.
+
+One walk looks at an order that speed depends on and that the compiler is free to turn round."""
 import os
 import re
 import shutil
@@ -177,3 +179,22 @@ def test_lds_words_requested_by_assembly_are_left_alone(built):
                             break
                     at += 1
     assert requests >= 2
+
+
+def test_small_tiles_start_their_matrix_instructions_ahead_of_the_next_loads(built):
+    """In the steady loop of the tiles of 32 and 64 rows a wave has one chain of four matrix instructions per k-tile: the loads of a later
+    k-tile are issued behind the first of them, which covers them, and a fragment's address takes one addition."""
+    checked = 0
+    for name, code, labels in built:
+        if not re.search(r"fused_tile(_pair)?_kernelILi\d+ELi\dELi[12]E", name):
+            continue
+        starts = sorted({0, *labels.values(), len(code)})
+        for begin, end in zip(starts, starts[1:]):
+            ops = [op for op, _ in code[begin:end]]
+            mfma = [i for i, op in enumerate(ops) if op == "v_mfma_f32_32x32x16_bf16"]
+            loads = [i for i, op in enumerate(ops) if op.startswith("global_load_lds")]
+            if len(mfma) == 4 and loads and ops.count("ds_read_b128") == 8:
+                checked += 1
+                assert mfma[0] < loads[0], (name, begin)
+                assert ops.count("v_add_u32_e32") <= 8, (name, begin)
+    assert checked > 50
