@@ -19,6 +19,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kQuantizeVals = 16, kDequantizeVals = 16;      // values per lane
+constexpr int kCodesVals = 32;                               // ... of the quantizer that writes codes only
 constexpr int kGroupsPerBlock = kThreads / kLanesPerGroup;   // 64
 
 // ------------------------------------------------------------------ quantize
@@ -30,18 +31,24 @@ constexpr int kGroupsPerBlock = kThreads / kLanesPerGroup;   // 64
 // per lane it was three and two.  Keys and values of 8192 tokens, 256-point grid, groups of 1024: 36.6 us against 49.6; with
 // predictions in memory, 4096 tokens, 16 points, predictor included, 88.5 against 114.7.  Smaller code for the crowded cells, which
 // would let four or five waves in with a prediction, changed nothing: the issue slots are full.
-template <typename T, int NCW, bool WIDE, bool PRED>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED ? 3 : 4))) void quantize_kernel(
+//
+// CODES: no tensor of the launch wants its reconstruction (uniform backbone in bf16, without a prediction).  There is no search to
+// request behind, so the next rows are requested ahead of this round's work, and no scattered store; what counts is the group's
+// reductions and divisions per lane, hence 32 values.  Keys and values, 2 bits, groups across the heads, 35421 tokens: 27 us; 34 with
+// 16 values requested behind the work, 33 ahead of it.  (With reconstructions 8192 tokens take 12.2 us on 16 values, 13.9 on 32.)
+// Which launches: codes_pay.
+template <typename T, int NCW, bool WIDE, bool PRED, bool CODES>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED || CODES ? 3 : 4))) void quantize_kernel(
     const QuantizeIo io0, const QuantizeIo io1, const Prediction P, const float* __restrict__ codebook,
     const uint32_t* __restrict__ table, int64_t n_groups, int H, bool fixed_head) {
   const T* const X = static_cast<const T*>(blockIdx.y ? io1.X : io0.X);
-  T* const Xhat = static_cast<T*>(blockIdx.y ? io1.Xhat : io0.Xhat);
+  T* const Xhat = CODES ? nullptr : static_cast<T*>(blockIdx.y ? io1.Xhat : io0.Xhat);
   const int8_t* const signs = blockIdx.y ? io1.signs : io0.signs;
   uint8_t* const codes = blockIdx.y ? io1.codes : io0.codes;
   uint16_t* const scales = blockIdx.y ? io1.scales : io0.scales;
   __shared__ Lds lds;
   stage_lds<NCW>(lds, codebook, table);
-  constexpr int N = kQuantizeVals, kLanes = kGroup / N, kGroups = kThreads / kLanes;       // lanes per group, groups per round
+  constexpr int N = CODES ? kCodesVals : kQuantizeVals, kLanes = kGroup / N, kGroups = kThreads / kLanes;       // lanes per group, groups per round
   const int l = WIDE ? token_pos<N>(threadIdx.x) : group_pos<N>(threadIdx.x), q = l & (kLanes - 1), slot = threadIdx.x / kLanes;
   // (a thread meets the same head in every round of the grid-stride loop: the signs are fetched once)
   float sf[N] = {};
@@ -50,7 +57,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED ?
   }
   // The rows (and the fp32 prediction) of the next round are requested behind this round's search: the inverse transform and the
   // stores hide some of their latency, the other waves of the SIMD the rest.  The prediction is read again for the reconstruction
-  // instead of being held through the search (32 registers).
+  // instead of being held through the search (32 registers), but by the uniform backbone, which has registers to spare (4 bits, 35421
+  // tokens with predictions 51 us, 59 when it read them twice).
   constexpr int kXQuads = N * sizeof(T) / 16, kPQuads = PRED ? N / 4 : 1;
   struct Rows { u32x4 x[kXQuads]; f32x4 p[kPQuads]; };
   // (groups across the heads: 8 heads, a lane meets the same one in every round and so one half of the predictions)
@@ -99,6 +107,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED ?
       }
     }
     unpack_p(rows.p, p);
+    if (CODES && g0 + stride < n_groups) request(g0 + stride, rows);
 #pragma unroll
     for (int r = 0; r < N; ++r) v[r] -= p[r];
     if constexpr (!is_rtn(NCW)) {
@@ -108,11 +117,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED ?
     quantize_residual<NCW, WIDE>(v, sf, l, lds.cb, table != nullptr ? lds.table : nullptr, active, gid, codes, scales,
                                  Xhat != nullptr, [&] {
       asm volatile("" ::: "memory");                      // (not the registers of the first read)
-      if (Xhat != nullptr) request_p(gid, again);
-      if (g0 + stride < n_groups) request(g0 + stride, rows);
+      if (!is_rtn(NCW) && Xhat != nullptr) request_p(gid, again);
+      if (!CODES && g0 + stride < n_groups) request(g0 + stride, rows);
     });
     if (Xhat != nullptr) {
-      unpack_p(again, p);
+      if constexpr (!is_rtn(NCW)) unpack_p(again, p);
       if constexpr (WIDE && PRED) {                       // a wave's rows of P may lie under those it writes: all of it has been read
 #pragma unroll
         for (int r = 0; r < N; ++r) asm volatile("" ::"v"(p[r]) : "memory");
@@ -358,7 +367,13 @@ __global__ __launch_bounds__(1024) void build_overflow_kernel(const float* __res
 // the request of the next round's rows has a next round to run ahead of.  The inverse stages 256 B to 4 KiB; keys and values of
 // 131072 tokens, 16 points: 171 us with four workgroups per CU, 178 with six or eight (of 8192 tokens 11.1 with any of them).
 // Below that number the rounds are shared out evenly.
-constexpr int kQuantizeWgPerCu = 3, kQuantizePlainWgPerCu = 4;     // with a prediction, without
+//
+// 32 values per lane for codes alone (n_groups head groups in all tensors).  Groups across the heads: as soon as 16 values would take more
+// than a few waves per SIMD, two more reductions per lane then cost more than the waves cover (tokens of one tensor, 2 bits, us, 16 / 32
+// values: 1000 2.6 / 2.9, 2000 3.0 / 2.9, 6000 4.7 / 4.1, 28000 15.5 / 14.2).  Groups of one head need few reductions: over many rounds
+// only (keys and values: 1000 2.9 / 3.0, 10000 10.8 / 11.3, 16384 15.6 / 15.3, 20000 18.4 / 18.5, 21071 19.5 / 17.8, 131072 104 / 93).
+inline bool codes_pay(int64_t n_groups, bool wide) { return n_groups >= (wide ? 16384 : 262144); }
+constexpr int kQuantizeWgPerCu = 3, kQuantizePlainWgPerCu = 4, kCodesWgPerCu = 3;     // with a prediction, without, codes only
 constexpr int kDequantizeWgPerCu = 4;
 inline int64_t blocks_of_rounds(int64_t blocks, int64_t cap) {
   const int64_t rounds = (blocks + cap - 1) / cap;
@@ -420,15 +435,24 @@ hipError_t launch_quantize(int dtype, int n_codewords, const QuantizeIo* io, int
   if (P != nullptr && !wide && P->second != P->first + P->split) return hipErrorInvalidValue;      // (read as contiguous)
   const QuantizeIo& other = io[tensors - 1];
   const uint32_t* tab = static_cast<const uint32_t*>(table);
-  const int per_cu = P != nullptr ? kQuantizeWgPerCu : kQuantizePlainWgPerCu;
-  const Rounds r = rounds_for(n_groups, kThreads * kQuantizeVals / kGroup, H, per_cu, tensors);
+  const bool codes_only = is_rtn(n_codewords) && dtype == kBF16 && P == nullptr && io[0].Xhat == nullptr && other.Xhat == nullptr &&
+                          codes_pay(n_groups * tensors, wide);
+  const int per_cu = P != nullptr ? kQuantizeWgPerCu : codes_only ? kCodesWgPerCu : kQuantizePlainWgPerCu;
+  const Rounds r = rounds_for(n_groups, kThreads * (codes_only ? kCodesVals : kQuantizeVals) / kGroup, H, per_cu, tensors);
   const dim3 grid(r.blocks, (unsigned)tensors);
-  if (P != nullptr)
-    AQUAKV_DISPATCH(dtype, n_codewords, wide, (quantize_kernel<T, N, W, true><<<grid, kThreads, 0, stream>>>(
-                                                  io[0], other, *P, codebook, tab, n_groups, H, r.fixed_head)));
-  else
-    AQUAKV_DISPATCH(dtype, n_codewords, wide, (quantize_kernel<T, N, W, false><<<grid, kThreads, 0, stream>>>(
-                                                  io[0], other, Prediction{}, codebook, tab, n_groups, H, r.fixed_head)));
+#define AQUAKV_QUANTIZE(T, N, W, PRED, CODES, P) \
+  quantize_kernel<T, N, W, PRED, CODES><<<grid, kThreads, 0, stream>>>(io[0], other, P, codebook, tab, n_groups, H, r.fixed_head)
+  if (codes_only) {
+    if (n_codewords == kRtn2 && wide) AQUAKV_QUANTIZE(bf16_t, kRtn2, true, false, true, Prediction{});
+    else if (n_codewords == kRtn2) AQUAKV_QUANTIZE(bf16_t, kRtn2, false, false, true, Prediction{});
+    else if (wide) AQUAKV_QUANTIZE(bf16_t, kRtn4, true, false, true, Prediction{});
+    else AQUAKV_QUANTIZE(bf16_t, kRtn4, false, false, true, Prediction{});
+  } else if (P != nullptr) {
+    AQUAKV_DISPATCH(dtype, n_codewords, wide, (AQUAKV_QUANTIZE(T, N, W, true, false, *P)));
+  } else {
+    AQUAKV_DISPATCH(dtype, n_codewords, wide, (AQUAKV_QUANTIZE(T, N, W, false, false, Prediction{})));
+  }
+#undef AQUAKV_QUANTIZE
   return hipGetLastError();
 }
 

@@ -261,3 +261,29 @@ def test_rtn_groups_of_1024(B, dtype, bits):
         mag = 0.5 * np.einsum("qd,tqd->qt", np.abs(U.np64(q)[0]), np.abs(k64))
         assert np.all(np.abs(U.np64(scores)[0] - want) <= 4e-6 * mag + 1e-30)
         Kp, Vp = Kh, Vh
+
+
+@pytest.mark.parametrize("bits", [2, 4])
+@pytest.mark.parametrize("T,H,rht_group", [(300, 8, 0), (16385, 8, 0), (32769, 8, 0), (87383, 3, 0), (9, 8, 1024), (1025, 8, 1024), (2049, 8, 1024),
+                                           (13001, 8, 1024)])
+def test_codes_alone_are_the_codes_with_a_reconstruction(B, T, H, rht_group, bits):
+    """Without a prediction, a large launch that writes codes only holds 32 values per lane, one that also reconstructs 16: the same bytes,
+    of one tensor, of two, and of two of which one is reconstructed, on either side of the lines between them, in one round of workgroups
+    and in several, the last of them partly filled."""
+    print(f"case codes alone T={T} H={H} group={rht_group} bits={bits}", flush=True)
+    lg = B.Layer(H, 128, None, None, None, torch.bfloat16, rtn_bits=bits, rht_group=rht_group)
+    g = torch.Generator(device="cuda").manual_seed(T + H)
+    K, V = (torch.randn(T, H, 128, generator=g, device="cuda").bfloat16() for _ in range(2))
+    K[T // 2] = 0                                          # a group without a range
+    new = lambda: [t.fill_(0x55) for _ in range(2) for t in lg.alloc_codes(T)]
+    want, one, two, mixed = new(), new(), new(), new()
+    for X, c, s in ((K, *want[:2]), (V, *want[2:])):
+        B.aquakv_quantize(lg, B.AQUAKV_KEY, T, X, None, c, s, lg.alloc_kv(T))
+    for X, c, s in ((K, *one[:2]), (V, *one[2:])):
+        B.aquakv_quantize(lg, B.AQUAKV_KEY, T, X, None, c, s, None)
+    ws = lg.alloc_workspace(T)
+    B.aquakv_encode_layer(lg, T, K, V, None, None, *two, None, None, ws)
+    B.aquakv_encode_layer(lg, T, K, V, None, None, *mixed, lg.alloc_kv(T), None, ws)
+    torch.cuda.synchronize()
+    for got in (one, two, mixed):
+        assert all(torch.equal(a, b) for a, b in zip(got, want, strict=True))
