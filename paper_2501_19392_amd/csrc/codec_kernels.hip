@@ -50,10 +50,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED |
   stage_lds<NCW>(lds, codebook, table);
   constexpr int N = CODES ? kCodesVals : kQuantizeVals, kLanes = kGroup / N, kGroups = kThreads / kLanes;       // lanes per group, groups per round
   const int l = WIDE ? token_pos<N>(threadIdx.x) : group_pos<N>(threadIdx.x), q = l & (kLanes - 1), slot = threadIdx.x / kLanes;
-  // (a thread meets the same head in every round of the grid-stride loop: the signs are fetched once)
+  // (a thread meets the same head in every round of the grid-stride loop: the signs are fetched once.  One that is behind the end repeats
+  // the last group, with its signs: those of another head make a group that does not exist, whose search can take longer than any other's)
   float sf[N] = {};
   if constexpr (!is_rtn(NCW)) {
-    if (fixed_head) load_signs(signs, (int)((blockIdx.x * (unsigned)kGroups + slot) % (unsigned)H), q, sf);
+    const unsigned first = blockIdx.x * (unsigned)kGroups + slot;
+    if (fixed_head) load_signs(signs, (int)((first < n_groups ? first : (unsigned)(n_groups - 1)) % (unsigned)H), q, sf);
   }
   // The rows (and the fp32 prediction) of the next round are requested behind this round's search: the inverse transform and the
   // stores hide some of their latency, the other waves of the SIMD the rest.  The prediction is read again for the reconstruction
