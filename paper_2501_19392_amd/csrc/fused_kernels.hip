@@ -391,8 +391,8 @@ TileArgs tensor_args(const FusedTensor& t, const float* codebook, int64_t T, int
 // A launch for one tensor of few rows is bound by the latency of its k-tiles and leaves CUs idle, so the other tensor's tiles come
 // for little: the smallest tile with which both fit the CUs in one round (2048 rows of 8 heads), and tiles of 128 rows up to half a
 // round more.  Attention over a cache of six layers, us a token, apart / together: 300 tokens 145 / 115, 1100 155 / 138, 2000 192 / 177,
-// 2 x 1500 236 / 219.  From there on the CUs that a launch leaves idle are worth less than the clock it gains by them: tiles of 256
-// rows at 5376 rows, which would fill the chip with both, 561 / 582 us for eight layers, tiles of 320 rows 557 / 570.
+// 2 x 1500 236 / 219.  From there on both tensors in one launch take as many rounds as two launches: 5376 rows are twice 168 tiles of
+// 256 rows, 561 / 582 us for eight layers, or twice 136 of 320, 557 / 570.
 int pair_rows(int64_t T, int D) {
   const int64_t H = D / BN;
   for (const int rows : {32, 64, 128})
