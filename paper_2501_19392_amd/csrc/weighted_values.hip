@@ -142,9 +142,13 @@ template <bool MAX> __device__ __forceinline__ float wave_reduce(float x) {
 // form kWeightedSoftMax: `weights` holds raw scores, the weights are exp(score - chunk maximum), and the chunk's maximum and weight
 // sum are written to pstats[chunk, qh, 2].  kWeightedWhole: the same where a sequence is one chunk; part and pstats (nullable then)
 // are the results, so the sums are divided by the weight sum here.
+// WAVES: the waves per SIMD its registers leave room for.  Four of them are two workgroups per CU; fp32 values of four query heads at
+// once need 136 registers for themselves, so they get two waves in launches of up to a workgroup per CU and are squeezed into 128
+// beyond (three spilled): fp32, 4 query heads per kv head, two / four waves: 16 x 1000 tokens of 8 heads 42.7 / 41.0 us, 3 x 639 of 64
+// 43.8 / 41.0, but 3 x 2000 of 8 24.6 / 24.8 and 300 tokens 9.5 / 9.9.
 constexpr int kWeightedThreads = 512, kWeightedWaves = kWeightedThreads / 64;
-template <typename T, int R>
-__global__ __launch_bounds__(kWeightedThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : 4))) void weighted_values_kernel(
+template <typename T, int R, int WAVES>
+__global__ __launch_bounds__(kWeightedThreads) __attribute__((amdgpu_waves_per_eu(WAVES))) void weighted_values_kernel(
     const T* __restrict__ Vhat, const float* __restrict__ weights,
     float* __restrict__ part, float* __restrict__ pstats, int seq_len, int H, int q_heads, int chunks_per_seq, WeightedForm form) {
   static_assert(kWeightedThreads == 2 * kWeightedChunk && (R == 1 || R == 2 || R == 4), "a thread: one token of every second head");
@@ -449,17 +453,18 @@ hipError_t launch_weighted_values(int dtype, const void* Vhat, const float* weig
   if (form == kWeightedWhole ? chunks != 1 : (pstats != nullptr) != (form == kWeightedSoftMax)) return hipErrorInvalidValue;
   const unsigned grid = (unsigned)((int64_t)batch * chunks * H);
   const int rep = q_heads / H;
-#define AQUAKV_WEIGHTED(T, R) \
-  weighted_values_kernel<T, R><<<grid, kWeightedThreads, 0, stream>>>(static_cast<const T*>(Vhat), weights, part, pstats, seq_len, H, q_heads, chunks, form)
-#define AQUAKV_WEIGHTED_R(T)               \
-  do {                                     \
-    if (rep == 1) AQUAKV_WEIGHTED(T, 1);   \
-    else if (rep == 2) AQUAKV_WEIGHTED(T, 2); \
-    else AQUAKV_WEIGHTED(T, 4);            \
-  } while (0)
-  if (dtype == kBF16) AQUAKV_WEIGHTED_R(bf16_t);
-  else AQUAKV_WEIGHTED_R(float);
-#undef AQUAKV_WEIGHTED_R
+#define AQUAKV_WEIGHTED(T, R, WAVES) \
+  weighted_values_kernel<T, R, WAVES><<<grid, kWeightedThreads, 0, stream>>>(static_cast<const T*>(Vhat), weights, part, pstats, seq_len, H, q_heads, chunks, form)
+  if (dtype == kBF16) {
+    if (rep == 1) AQUAKV_WEIGHTED(bf16_t, 1, 4);
+    else if (rep == 2) AQUAKV_WEIGHTED(bf16_t, 2, 4);
+    else AQUAKV_WEIGHTED(bf16_t, 4, 4);
+  } else {
+    if (rep == 1) AQUAKV_WEIGHTED(float, 1, 2);
+    else if (rep == 2) AQUAKV_WEIGHTED(float, 2, 2);
+    else if (grid <= 256) AQUAKV_WEIGHTED(float, 4, 2);      // (CUs of an MI355X)
+    else AQUAKV_WEIGHTED(float, 4, 4);
+  }
 #undef AQUAKV_WEIGHTED
   return hipGetLastError();
 }

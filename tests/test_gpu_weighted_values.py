@@ -406,3 +406,36 @@ def test_infinite_values_of_the_last_token_are_counted_once(B, dtype, S, QH):
         want, mag = (torch.matmul(a, b) for a, b in ((weights, v[..., 64:].contiguous()), (weights.abs(), v[..., 64:].abs().contiguous())))
         # sums of up to 512 fp32 terms, exponentials as above
         assert bool(((got[..., 64:].double() - want).abs() <= 3e-5 * mag).all())
+
+
+@pytest.mark.parametrize("batch,S,QH", [(32, 300, 12), (33, 300, 12), (40, 513, 32)])
+def test_fp32_sums_of_more_workgroups_than_cus(B, batch, S, QH):
+    """fp32 values of three and more query heads per kv head: launches of more than 256 workgroups (batch x pieces of 256 tokens x 4 heads)
+    run in fewer registers.  The bits of a call per sequence, and the sums."""
+    print(f"case fp32 workgroups batch={batch} S={S} QH={QH}", flush=True)
+    H = 4
+    lay = U.make_layers(H, "fp32", 16)[1]
+    gen = torch.Generator().manual_seed(batch + S)
+    codes, scales = lay.alloc_codes(batch * S)
+    codes.copy_(torch.randint(0, 256, codes.shape, generator=gen).to(codes.dtype))
+    scales.copy_(torch.ones(scales.shape).half().view(torch.int16))
+    w = (torch.randn(batch, QH, S, generator=gen) * 2.0).float().cuda()
+    V = lay.alloc_kv(batch * S)
+    new = lambda n: torch.full((n, QH, 128), float("nan"), dtype=torch.float32, device="cuda")
+    out, given = new(batch), new(batch)
+    ws = lay.alloc_weighted_workspace(batch, S, QH)
+    B.aquakv_decode_values_attend(lay, batch, S, QH, codes, scales, None, None, w, V, out, None, ws)
+    B.aquakv_decode_values_weighted(lay, batch, S, QH, codes, scales, None, None, w, V, given, ws)
+    sync()
+    v = V.view(batch, S, H, 128).double().repeat_interleave(QH // H, 2).transpose(1, 2).contiguous()
+    # as above; sums of up to 513 fp32 terms are within 513 x 2^-24
+    for got, a, tol in ((out, torch.softmax(w.double(), -1), 3e-5), (given, w.double(), 3.1e-5)):
+        want, mag = (a[..., None] * v).sum(2), (a[..., None] * v).abs().sum(2)
+        assert ((got.double() - want).abs() <= tol * mag).all()
+    for b in (0, batch - 1):
+        o, g, r = new(1), new(1), slice(b * S, (b + 1) * S)
+        hat = lay.alloc_kv(S)
+        B.aquakv_decode_values_attend(lay, 1, S, QH, codes[r], scales[r], None, None, w[b:b + 1], hat, o, None, ws)
+        B.aquakv_decode_values_weighted(lay, 1, S, QH, codes[r], scales[r], None, None, w[b:b + 1], hat, g, ws)
+        sync()
+        assert torch.equal(o[0], out[b]) and torch.equal(g[0], given[b])
