@@ -434,7 +434,8 @@ int aquakv_copy_ranges(const aquakv_copy_range* ranges, int32_t n, void* stream)
  * Hence a layer's predictors, if it has any, take the vectors of one layer: d_in_k = kv_heads * 128, d_in_v = twice that.
  * `staged` (needed when batch > 1): room for the compressed tokens of all sequences in the layout of the layer's code and scale
  * tensors, where they are put one behind the other.  `workspace`: aquakv_attend_cache_workspace_bytes() bytes, 0 for an
- * unsupported configuration.  Nothing is kept from call to call.
+ * unsupported configuration (less is enough as long as it holds the recovery's workspace and one layer's partial results: the attention of
+ * a layer then runs in a launch of its own where it would otherwise run beside the recovery of the next one).  Nothing is kept from call to call.
  * Nothing that the call writes (out, hat, staged, the workspace) may overlap anything else it is given: AQUAKV_EINVAL, like every
  * other fault in the arguments before anything is launched.
  */

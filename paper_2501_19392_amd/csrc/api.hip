@@ -1104,6 +1104,13 @@ size_t attend_decode_bytes(const aquakv_cache_layer* layers, int32_t n_layers, i
   }
   return (most + 255) & ~(size_t)255;
 }
+// A third place for recovered keys: where the values of a layer and the keys of the next one are recovered in one launch, the
+// attention of the layer before runs beside them and still reads its keys.  (Longer ranges: never more than those such launches take.)
+size_t attend_keys_bytes(const aquakv_cache_shape* sh, int64_t tokens) {
+  if (sh->dtype != AQUAKV_BF16 || tokens <= 0) return 0;
+  const int64_t most = aquakv::fused_decode_pair_rows(sh->kv_heads * 128);
+  return ((size_t)(tokens < most ? tokens : most) * sh->kv_heads * 128 * elem_bytes(sh->dtype) + 255) & ~(size_t)255;
+}
 // What an aquakv_attend_cache call reads and writes: nothing that it writes may lie over anything else.  Sorted once: comparing
 // every pair would cost more than the launches of many layers.
 int check_cache_buffers(const aquakv_cache_layer* layers, int32_t n_layers, const aquakv_cache_shape* sh, const int32_t* n_sink,
@@ -1175,7 +1182,8 @@ size_t aquakv_attend_cache_workspace_bytes(const aquakv_cache_layer* layers, int
   if (check_cache(layers, n_layers, sh) != AQUAKV_OK) return 0;
   const size_t one = attend_layer_bytes(sh->batch * attend_pieces(sh->sink_rows + sh->capacity + sh->recent_rows), sh->q_heads);
   const size_t fit = one < kAttendRoom ? kAttendRoom / one : 1;
-  return attend_decode_bytes(layers, n_layers, sh->batch * sh->capacity) + one * (fit < (size_t)n_layers ? fit : n_layers);
+  return attend_decode_bytes(layers, n_layers, sh->batch * sh->capacity) + attend_keys_bytes(sh, sh->batch * sh->capacity) +
+         one * (fit < (size_t)n_layers ? fit : n_layers);
 }
 
 int aquakv_attend_cache(const aquakv_cache_layer* layers, int32_t n_layers, const aquakv_cache_shape* sh, const int32_t* n_sink,
@@ -1215,8 +1223,13 @@ int aquakv_attend_cache(const aquakv_cache_layer* layers, int32_t n_layers, cons
   CHECK(check_ptr(workspace, "workspace", true));
   if (workspace_bytes < decode_bytes + one)
     return fail(AQUAKV_EWORKSPACE, "workspace %zu B < required %zu B", workspace_bytes, decode_bytes + one);
-  const int hold = (int)((workspace_bytes - decode_bytes) / one < aquakv::kAttendMergeLayers ? (workspace_bytes - decode_bytes) / one
-                                                                                      : aquakv::kAttendMergeLayers);
+  // keys of the layers in three places in turn, where all are recovered, few enough rows for it, and the workspace has room for the third
+  bool three = sh->dtype == AQUAKV_BF16 && NB <= aquakv::kAttendSeqs && aquakv::fused_decode_pair_pays(compressed, sh->kv_heads * 128) &&
+               workspace_bytes >= decode_bytes + attend_keys_bytes(sh, compressed) + one;
+  for (int32_t l = 0; l < n_layers; ++l) three &= layers[l].layer != nullptr || !adjacent;
+  const size_t keys_bytes = three ? attend_keys_bytes(sh, compressed) : 0;
+  const size_t fit = (workspace_bytes - decode_bytes - keys_bytes) / one;
+  const int hold = (int)(fit < aquakv::kAttendMergeLayers ? fit : aquakv::kAttendMergeLayers);
   for (int i = 0; i < 4; ++i) CHECK(check_ptr(hat[i], "hat", compressed != 0));
   for (int32_t l = 0; l < n_layers; ++l) {
     const aquakv_cache_layer& c = layers[l];
@@ -1245,7 +1258,7 @@ int aquakv_attend_cache(const aquakv_cache_layer* layers, int32_t n_layers, cons
   if (compressed != 0 && layers[0].layer != nullptr && (layers[0].layer->d_in_k != 0 || layers[0].layer->d_in_v != 0))
     return fail(AQUAKV_ENULL, "layer 0 has predictors, but no layer comes before it");
   CHECK(check_cache_buffers(layers, n_layers, sh, n_sink, n_compressed, n_recent, rope_cos, rope_sin, hat, workspace,
-                            decode_bytes + one * (size_t)(hold < n_layers ? hold : n_layers), compressed, adjacent));
+                            decode_bytes + keys_bytes + one * (size_t)(hold < n_layers ? hold : n_layers), compressed, adjacent));
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   const int64_t first_row = first * sh->capacity;
 
@@ -1280,7 +1293,7 @@ int aquakv_attend_cache(const aquakv_cache_layer* layers, int32_t n_layers, cons
     }
     HIP_TRY(send());
   }
-  float* const part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + decode_bytes);
+  float* const part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + decode_bytes + keys_bytes);
   const int64_t part_elems = pieces * sh->q_heads * 128, layer_elems = (int64_t)(one / sizeof(float));
   // where layer l's codes and scales are read (k_codes, k_scales, v_codes, v_scales), and its recovered tensors go
   struct Coded { const uint8_t* k_codes; const uint16_t* k_scales; const uint8_t* v_codes; const uint16_t* v_scales; };
@@ -1292,40 +1305,117 @@ int aquakv_attend_cache(const aquakv_cache_layer* layers, int32_t n_layers, cons
                  static_cast<const uint8_t*>(at(c.v_codes, first_row, crow)), static_cast<const uint16_t*>(at(c.v_scales, first_row, srow))};
   };
   // The keys of a layer need the keys before, not its values: where a launch for one tensor leaves CUs idle, the values of layer l
-  // and the keys of layer l + 1 are recovered together.  The keys go to the buffer of layer l - 1's, whose last reader has been queued.
+  // and the keys of layer l + 1 are recovered together.  The last two layers' keys end in their own places of `hat` either way.
+  const int D = sh->kv_heads * 128;
+  const auto keys_at = [&](int32_t l) {
+    const int from_end = (n_layers - 1 - l) % 3;
+    if (!three) return hat[2 * (l & 1)];
+    return from_end == 2 ? static_cast<void*>(static_cast<unsigned char*>(workspace) + decode_bytes) : hat[2 * ((n_layers - 1 - from_end) & 1)];
+  };
   const auto with_next = [&](int32_t l) {
     const aquakv_layer *a = layers[l].layer, *b = l + 1 < n_layers ? layers[l + 1].layer : nullptr;
     return a != nullptr && b != nullptr && a->dtype == AQUAKV_BF16 && a->d_in_v != 0 && b->d_in_k != 0 && quantizer_id(a) == quantizer_id(b) &&
-           is_wide(a) == is_wide(b) && aquakv::fused_decode_pair_pays(compressed, a->kv_heads * 128);
+           is_wide(a) == is_wide(b) && aquakv::fused_decode_pair_pays(compressed, D);
+  };
+  const auto key_tensor = [&](int32_t l, const void* Kp, void* K) {
+    const aquakv_layer* const L = layers[l].layer;
+    const Coded in = coded_at(l);
+    return aquakv::FusedTensor{Kp, nullptr, L->d_in_k, 0, L->w_k, L->b_k, L->signs_k, nullptr, const_cast<uint8_t*>(in.k_codes),
+                               const_cast<uint16_t*>(in.k_scales), K};
+  };
+  const auto value_tensor = [&](int32_t l, const void* Vp, const void* K, void* V) {
+    const aquakv_layer* const L = layers[l].layer;
+    const Coded in = coded_at(l);
+    return aquakv::FusedTensor{Vp, K, D, D, L->w_v, L->b_v, L->signs_v, nullptr, const_cast<uint8_t*>(in.v_codes),
+                               const_cast<uint16_t*>(in.v_scales), V};
+  };
+  // The attention of a layer is not launched at once: it needs nothing of the next layer, and runs beside that one's recovery on the CUs
+  // that the tiles leave idle: beside values and next keys in one launch, or beside the keys (beside the values, whose launch takes
+  // longer, four sequences of 1800 tokens and 8 layers take 0.983 of the time of attention by itself, beside the keys 0.963).
+  // `waiting`: that of the layer before (only one launch's worth of sequences can wait).
+  aquakv::AttendCacheArgs waiting = {};
+  bool is_waiting = false;
+  int held = 0, done = 0;                                        // layers with partial results, and before them
+  const auto set_sequences = [&](int b0, aquakv::AttendCacheArgs& a, int64_t& from, int& piece) {
+    a.seq0 = b0;
+    a.pieces.n_seq = NB - b0 < aquakv::kAttendSeqs ? NB - b0 : aquakv::kAttendSeqs;
+    for (int i = 0; i < a.pieces.n_seq; ++i) {
+      const int b = b0 + i;
+      a.pieces.first[i] = piece;
+      a.n_sink[i] = n_sink[b]; a.n_compressed[i] = n_compressed[b];
+      a.n_tokens[i] = n_sink[b] + n_compressed[b] + n_recent[b];
+      a.compressed_row[i] = from;
+      from += n_compressed[b];
+      piece += (int)attend_pieces(a.n_tokens[i]);
+    }
+    a.pieces.first[a.pieces.n_seq] = piece;
+  };
+  // the layers held are merged once their partial results fill the room, or are the last
+  const auto merge = [&](const aquakv::AttendCacheArgs& a) {
+    aquakv::MergeArgs m = {};
+    m.part = part; m.stats = part + part_elems;
+    m.part_layer = m.stats_layer = layer_elems;
+    m.q_heads = sh->q_heads; m.seq0 = a.seq0; m.pieces = a.pieces;
+    for (int i = 0; i < held; ++i) m.out[i] = layers[done + i].out;
+    return aquakv::launch_merge_pieces(m, held, stream);
+  };
+  const auto merge_due = [&] { return held == hold || done + held == n_layers; };
+  const auto merged = [&] { done += held; held = 0; };
+  const auto attended = [&]() {                                  // `waiting` has been launched
+    is_waiting = false;
+    if (!merge_due()) return hipSuccess;
+    const hipError_t e = merge(waiting);
+    merged();
+    return e;
+  };
+  const auto attend_now = [&]() {
+    if (!is_waiting) return hipSuccess;
+    if (const hipError_t e = aquakv::launch_attend_cache(sh->dtype, waiting, stream)) return e;
+    return attended();
+  };
+  // n = 1 or 2 tensors on tiles, with the attention that waits if there is one
+  const auto decode_tiles = [&](const aquakv_layer* L, const aquakv::FusedTensor* t, const float* const* codebooks, int n) {
+    const aquakv::AttendCacheArgs none = {};
+    const hipError_t e = aquakv::launch_fused_decode_attend(quantizer_id(L), t, codebooks, n, compressed, D, is_wide(L),
+                                                            is_waiting ? waiting : none, stream);
+    return e != hipSuccess || !is_waiting ? e : attended();
+  };
+  const auto takes_attention = [&](const aquakv_layer* L, int32_t d_in) {
+    return is_waiting && L->dtype == AQUAKV_BF16 && d_in != 0 && aquakv::fused_decode_attend_fits(compressed, D);
   };
   const void *Kp = nullptr, *Vp = nullptr;
-  int held = 0;
   bool have_keys = false;                                        // of this layer, from the launch of the one before
   for (int32_t l = 0; l < n_layers; ++l) {
     const aquakv_cache_layer& c = layers[l];
-    void *K = hat[2 * (l & 1)], *V = hat[2 * (l & 1) + 1];
+    void *K = keys_at(l), *V = hat[2 * (l & 1) + 1];
     if (compressed != 0 && c.layer != nullptr) {
       const Coded in = coded_at(l);
       const bool pair = with_next(l);
-      if (!have_keys && !pair) {
-        CHECK(aquakv_decode_layer(c.layer, compressed, in.k_codes, in.k_scales, in.v_codes, in.v_scales, Kp, Vp, K, V, workspace,
-                                  decode_bytes, stream));
-      } else {
-        if (!have_keys)
+      if (!have_keys) {
+        if (takes_attention(c.layer, c.layer->d_in_k) && !(pair && three)) {
+          const aquakv::FusedTensor k = key_tensor(l, Kp, K);
+          HIP_TRY(decode_tiles(c.layer, &k, &c.layer->codebook, 1));
+          have_keys = true;
+        } else if (pair) {
           CHECK(aquakv_decode_layer(c.layer, compressed, in.k_codes, in.k_scales, nullptr, nullptr, Kp, nullptr, K, nullptr, workspace,
                                     decode_bytes, stream));
-        if (pair) {
-          const aquakv_layer *a = c.layer, *b = layers[l + 1].layer;
-          const Coded next = coded_at(l + 1);
-          const int D = a->kv_heads * 128;
-          const aquakv::FusedTensor v = {Vp, K, a->d_in_v - D, D, a->w_v, a->b_v, a->signs_v, nullptr, const_cast<uint8_t*>(in.v_codes),
-                                         const_cast<uint16_t*>(in.v_scales), V};
-          const aquakv::FusedTensor k = {K, nullptr, b->d_in_k, 0, b->w_k, b->b_k, b->signs_k, nullptr, const_cast<uint8_t*>(next.k_codes),
-                                         const_cast<uint16_t*>(next.k_scales), hat[2 * (~l & 1)]};
-          HIP_TRY(aquakv::launch_fused_decode_pair(quantizer_id(a), a->codebook, v, b->codebook, k, compressed, D, is_wide(a), stream));
+          have_keys = true;
         } else {
-          CHECK(aquakv_decode_values(c.layer, compressed, in.v_codes, in.v_scales, Vp, K, V, workspace, decode_bytes, stream));
+          HIP_TRY(attend_now());
+          CHECK(aquakv_decode_layer(c.layer, compressed, in.k_codes, in.k_scales, in.v_codes, in.v_scales, Kp, Vp, K, V, workspace,
+                                    decode_bytes, stream));
         }
+      }
+      if (pair) {
+        if (!three) HIP_TRY(attend_now());                       // (the keys it reads are about to be overwritten)
+        const aquakv::FusedTensor t[2] = {value_tensor(l, Vp, K, V), key_tensor(l + 1, K, keys_at(l + 1))};
+        const float* const codebooks[2] = {c.layer->codebook, layers[l + 1].layer->codebook};
+        HIP_TRY(decode_tiles(c.layer, t, codebooks, 2));
+      } else if (have_keys && takes_attention(c.layer, c.layer->d_in_v)) {
+        const aquakv::FusedTensor v = value_tensor(l, Vp, K, V);
+        HIP_TRY(decode_tiles(c.layer, &v, &c.layer->codebook, 1));
+      } else if (have_keys) {
+        CHECK(aquakv_decode_values(c.layer, compressed, in.v_codes, in.v_scales, Vp, K, V, workspace, decode_bytes, stream));
       }
       have_keys = pair;
       Kp = K; Vp = V;
@@ -1337,39 +1427,29 @@ int aquakv_attend_cache(const aquakv_cache_layer* layers, int32_t n_layers, cons
       HIP_TRY(send());
       Kp = K; Vp = V;
     }
+    HIP_TRY(attend_now());
     aquakv::AttendCacheArgs a = {};
     a.sink_k = c.sink_k; a.sink_v = c.sink_v; a.compressed_k = Kp; a.compressed_v = Vp; a.recent_k = c.recent_k; a.recent_v = c.recent_v;
     a.q = c.q; a.rope_cos = rope_cos; a.rope_sin = rope_sin;
     a.part = part + held * layer_elems; a.stats = a.part + part_elems;
     a.scale = score_scale;
     a.kv_heads = sh->kv_heads; a.q_heads = sh->q_heads; a.sink_rows = sh->sink_rows; a.recent_rows = sh->recent_rows;
-    const bool merge = ++held == hold || l + 1 == n_layers;
+    ++held;
     int64_t from = 0;
     int piece = 0;
-    for (int b0 = 0; b0 < NB; b0 += aquakv::kAttendSeqs) {
-      a.seq0 = b0;
-      a.pieces.n_seq = NB - b0 < aquakv::kAttendSeqs ? NB - b0 : aquakv::kAttendSeqs;
-      for (int i = 0; i < a.pieces.n_seq; ++i) {
-        const int b = b0 + i;
-        a.pieces.first[i] = piece;
-        a.n_sink[i] = n_sink[b]; a.n_compressed[i] = n_compressed[b];
-        a.n_tokens[i] = n_sink[b] + n_compressed[b] + n_recent[b];
-        a.compressed_row[i] = from;
-        from += n_compressed[b];
-        piece += (int)attend_pieces(a.n_tokens[i]);
-      }
-      a.pieces.first[a.pieces.n_seq] = piece;
-      HIP_TRY(aquakv::launch_attend_cache(sh->dtype, a, stream));
-      if (merge) {
-        aquakv::MergeArgs m = {};
-        m.part = part; m.stats = part + part_elems;
-        m.part_layer = m.stats_layer = layer_elems;
-        m.q_heads = sh->q_heads; m.seq0 = b0; m.pieces = a.pieces;
-        for (int i = 0; i < held; ++i) m.out[i] = layers[l + 1 - held + i].out;
-        HIP_TRY(aquakv::launch_merge_pieces(m, held, stream));
-      }
+    if (NB <= aquakv::kAttendSeqs) {
+      set_sequences(0, a, from, piece);
+      waiting = a;
+      is_waiting = true;
+      if (l + 1 == n_layers) HIP_TRY(attend_now());
+      continue;
     }
-    if (merge) held = 0;
+    for (int b0 = 0; b0 < NB; b0 += aquakv::kAttendSeqs) {
+      set_sequences(b0, a, from, piece);
+      HIP_TRY(aquakv::launch_attend_cache(sh->dtype, a, stream));
+      if (merge_due()) HIP_TRY(merge(a));
+    }
+    if (merge_due()) merged();
   }
   return AQUAKV_OK;
 }

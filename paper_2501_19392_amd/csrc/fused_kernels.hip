@@ -28,6 +28,11 @@ constexpr int kEpilogueLdsBytes = kPredBytes + (int)sizeof(Lds);
 constexpr int kFusedLdsBytes = kEpilogueLdsBytes > kMainLoopLdsBytes ? kEpilogueLdsBytes : kMainLoopLdsBytes;
 static_assert(kFusedLdsBytes <= 160 * 1024, "LDS of one CU");
 
+// 8 wavefronts per tile (two per SIMD): the main loop is bound by L2 -> LDS traffic either
+// way, and the second wave fills the issue slots the first leaves in the VALU-heavy epilogue
+// (measured: encode 10 % faster than with 4 wavefronts, decode unchanged).
+constexpr int kWaves = 8;
+
 enum Mode : int { kEncode = 0, kDecode = 1, kScores = 2, kWeighted = 3 };
 
 // kWeighted: a wave keeps the bf16 values it decodes (32 token rows x 128) in the part of its parked rows it has
@@ -47,8 +52,10 @@ typedef float f32_alias __attribute__((may_alias));
 // 256 tokens, so the inverse rotation's stages across the heads are taken on the grid points of all 8 heads, which
 // the lane fetches itself, added in the tree the stand-alone kernels use (Rot<true>::iwht), before its own 128-point
 // stages; the round-to-nearest backbone has no rotation and only reads its step and zero point per token.
-template <int NCW, int MODE, int WAVES, bool WIDE = false>
-__global__ __launch_bounds__(WAVES * 64) void fused_kernel(
+// Workgroup `block` of `nblocks`; smem: kFusedLdsBytes of LDS.
+template <int NCW, int MODE, int WAVES, bool WIDE>
+__device__ __forceinline__ void fused_body(
+    unsigned char* smem, int block, int nblocks,
     const bf16_t* __restrict__ x0, int d0, const bf16_t* __restrict__ x1, int d1, const bf16_t* __restrict__ W,
     const float* __restrict__ bias, const int8_t* __restrict__ signs, const float* __restrict__ codebook,
     const uint32_t* __restrict__ table, const bf16_t* X, uint8_t* codes, uint16_t* scales, bf16_t* Xhat,
@@ -56,7 +63,6 @@ __global__ __launch_bounds__(WAVES * 64) void fused_kernel(
     int D, const float* __restrict__ rope_cos, const float* __restrict__ rope_sin, const float* __restrict__ weights,
     float* __restrict__ part) {
   static_assert(!WIDE || MODE != kEncode, "the quantizer needs the whole group: groups across the heads are not fused");
-  __shared__ __attribute__((aligned(16))) unsigned char smem[kFusedLdsBytes];
   Lds& cl = *reinterpret_cast<Lds*>(smem);
   unsigned char* const park = smem + sizeof(Lds);          // the parked tile, each wave its own rows
   const bool use_table = MODE == kEncode && table != nullptr;
@@ -75,7 +81,7 @@ __global__ __launch_bounds__(WAVES * 64) void fused_kernel(
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int H = D / BN;
-  const int logical = remap_block(blockIdx.x, gridDim.x);
+  const int logical = remap_block(block, nblocks);
   const int tile_m = logical / H, head = logical % H;
   const int64_t m0 = (int64_t)tile_m * BM;
   const int n0 = head * BN;
@@ -299,6 +305,35 @@ __global__ __launch_bounds__(WAVES * 64) void fused_kernel(
   }
 }
 
+template <int NCW, int MODE, int WAVES, bool WIDE = false>
+__global__ __launch_bounds__(WAVES * 64) void fused_kernel(
+    const bf16_t* __restrict__ x0, int d0, const bf16_t* __restrict__ x1, int d1, const bf16_t* __restrict__ W,
+    const float* __restrict__ bias, const int8_t* __restrict__ signs, const float* __restrict__ codebook,
+    const uint32_t* __restrict__ table, const bf16_t* X, uint8_t* codes, uint16_t* scales, bf16_t* Xhat,
+    const bf16_t* __restrict__ qv, float score_scale, float* __restrict__ scores, int seq_len, int q_heads, int64_t T,
+    int D, const float* __restrict__ rope_cos, const float* __restrict__ rope_sin, const float* __restrict__ weights,
+    float* __restrict__ part) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[kFusedLdsBytes];
+  fused_body<NCW, MODE, WAVES, WIDE>(smem, (int)blockIdx.x, (int)gridDim.x, x0, d0, x1, d1, W, bias, signs, codebook, table, X, codes,
+                                     scales, Xhat, qv, score_scale, scores, seq_len, q_heads, T, D, rope_cos, rope_sin, weights, part);
+}
+
+// Decode of one tensor (job.pair.job[0]) with pieces of attention on the workgroups behind its tiles
+template <int NCW, bool WIDE>
+__global__ __launch_bounds__(kWaves * 64) void fused_attend_kernel(const TileAttend job) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[kFusedLdsBytes];
+  static_assert(kWaves * 64 / kAttendThreads * (int)sizeof(AttendLds) <= kFusedLdsBytes, "LDS of the pieces");
+  if ((int)blockIdx.x < job.tiles) {
+    const TileArgs& a = job.pair.job[0];
+    fused_body<NCW, kDecode, kWaves, WIDE>(smem, (int)blockIdx.x, job.tiles, a.x0, a.d0, a.x1, a.d1, a.W, a.bias, a.signs, a.codebook,
+                                           nullptr, nullptr, a.codes, a.scales, a.Xhat, nullptr, 0.f, nullptr, 1, 1, a.seq_len, a.D,
+                                           nullptr, nullptr, nullptr, nullptr);
+  } else {
+    const char* const args = (const char*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(TileAttend, attend);
+    attend_behind_tiles<kWaves * 64>(*(AttendCacheParam*)args, (int)blockIdx.x - job.tiles, smem);
+  }
+}
+
 // n_codewords: the quantizer id (grid size, or kRtn2 / kRtn4)
 template <int MODE>
 hipError_t launch(int n_codewords, const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias,
@@ -309,13 +344,6 @@ hipError_t launch(int n_codewords, const void* x0, int d0, const void* x1, int d
   if (T == 0) return hipSuccess;
   if (wide && (MODE == kEncode || D != 8 * BN)) return hipErrorInvalidValue;
   const unsigned blocks = (unsigned)(((T + BM - 1) / BM) * (D / BN));
-  // 8 wavefronts per tile (two per SIMD): the main loop is bound by L2 -> LDS traffic either
-  // way, and the second wave fills the issue slots the first leaves in the VALU-heavy epilogue
-  // (measured: encode 10 % faster than with 4 wavefronts, decode unchanged).
-#ifndef AQUAKV_FUSED_WAVES
-#define AQUAKV_FUSED_WAVES 8
-#endif
-  constexpr int kWaves = AQUAKV_FUSED_WAVES;
 #define AQUAKV_FUSED_W(N, WIDE)                                                                                  \
   fused_kernel<N, MODE, kWaves, WIDE><<<blocks, kWaves * 64, 0, stream>>>(                                       \
       static_cast<const bf16_t*>(x0), d0, static_cast<const bf16_t*>(x1), d1, static_cast<const bf16_t*>(W), bias, \
@@ -400,18 +428,46 @@ int pair_rows(int64_t T, int D) {
   return 0;
 }
 
+// What a decode launch with attention behind its tiles runs on, for n tensors of T rows: rows of a tile, 0: no such launch.
+//
+// The tiles come first and the pieces of attention go to CUs without a tile, or whose tile is done.  8 layers, us a token, attention in launches
+// of its own / beside the tiles.  Two tensors: 200 tokens 145 / 98, 1200 215 / 159, 2000 223 / 193, 3000 315 / 269, 8 x 200 161 / 120.
+// One tensor, as long as it leaves an eighth of the CUs without a tile: 3600 tokens (216 tiles of 128 rows) 361 / 347, 8 x 800 476 / 415,
+// 4 x 1800 (168 tiles of 256 rows) 502 / 484, 6000 tokens (184) 458 / 441.  With tiles on all CUs the pieces wait, and then run one or
+// two to a CU instead of four: 4200 tokens (256 tiles of 128 rows) 360 / 389, 8000 (248 of 256 rows) 550 / 559.
+constexpr int64_t kAttendTiles = 224;
+int attend_rows(int64_t T, int D, int n) {
+  if (n == 2) return pair_rows(T, D);
+  const int rows = tile_rows(1, T, D, true);
+  if (rows == 320 || (rows == 0 && two_heads_pays(T, D))) return 0;
+  const int64_t each = rows == 0 ? BM : rows;
+  return (T + each - 1) / each * (D / BN) <= kAttendTiles ? (int)each : 0;
+}
 }  // namespace
 
 bool fused_decode_pair_pays(int64_t T, int D) { return pair_rows(T, D) != 0; }
-hipError_t launch_fused_decode_pair(int n_codewords, const float* values_codebook, const FusedTensor& values, const float* keys_codebook,
-                                    const FusedTensor& keys, int64_t T, int D, bool wide, hipStream_t stream) {
-  if (T == 0) return hipSuccess;
-  const TileArgs v = tensor_args(values, values_codebook, T, D), k = tensor_args(keys, keys_codebook, T, D);
-  const int rows = pair_rows(T, D);
-  if (rows == 32) return launch_pair_32(kTileDecode, n_codewords, wide, v, k, stream);
-  if (rows == 64) return launch_pair_64(kTileDecode, n_codewords, wide, v, k, stream);
-  if (rows == 128) return launch_pair_128(kTileDecode, n_codewords, wide, v, k, stream);
-  return hipErrorInvalidValue;
+int64_t fused_decode_pair_rows(int D) { return 384 / 2 / (D / BN) * 128; }
+bool fused_decode_attend_fits(int64_t T, int D) { return attend_rows(T, D, 1) != 0; }
+hipError_t launch_fused_decode_attend(int n_codewords, const FusedTensor* tensors, const float* const* codebooks, int n, int64_t T, int D,
+                                      bool wide, const AttendCacheArgs& attend, hipStream_t stream) {
+  if (T == 0 || n < 1 || n > 2) return hipErrorInvalidValue;
+  TileArgs jobs[2];
+  for (int i = 0; i < n; ++i) jobs[i] = tensor_args(tensors[i], codebooks[i], T, D);
+  const int rows = attend_rows(T, D, n);
+  if (rows == 32) return launch_tile_attend_32(n_codewords, wide, jobs, n, attend, stream);
+  if (rows == 64) return launch_tile_attend_64(n_codewords, wide, jobs, n, attend, stream);
+  if (rows == 128) return launch_tile_attend_128(n_codewords, wide, jobs, n, attend, stream);
+  if (rows != BM) return hipErrorInvalidValue;
+  TileAttend args;
+  args.pair.job[0] = args.pair.job[1] = jobs[0];
+  args.tiles = args.pair.blocks = (int)((T + BM - 1) / BM) * (D / BN);
+  args.attend = attend;
+  const unsigned blocks = (unsigned)args.tiles + attend_workgroups(attend, kWaves * 64);
+#define AQUAKV_TILE(N, MODE, WIDE) fused_attend_kernel<N, WIDE><<<blocks, kWaves * 64, 0, stream>>>(args)
+  if (wide) AQUAKV_TILE_N(kTileDecode, true);
+  else AQUAKV_TILE_N(kTileDecode, false);
+#undef AQUAKV_TILE
+  return hipGetLastError();
 }
 
 // Tiles of 32 rows for both products on the CUs at once.  With tiles of 64 rows for the first launch, up to twice the rows,

@@ -7,6 +7,7 @@
 // on its SIMD is bound by latency, so the work per lane is what counts: keys and values of 128 tokens, 16-point grid, 22.9 -> 20.8 us
 // (256 points: 29.8 -> 25.1), decode of 1100 tokens with groups across the heads 27.7 -> 24.4.
 #pragma once
+#include "attend_piece.h"
 #include "fused_epilogue.h"
 #include "gemm_tile.h"
 #include "kernels.h"
@@ -49,20 +50,32 @@ struct TilePair {
 };
 // What is done about sums: nothing, the product goes on from those that are there, or `keep` says whether they alone are wanted.
 enum TileSums : int { kNoSums = 0, kUseSums = 1, kKeepSums = 2 };
-// workgroup `block` of the `nblocks` that work on `a`
+// Decode of one or two tensors (job[1] has `tiles` - pair.blocks workgroups) and, on the workgroups behind them, pieces of the attention of
+// a layer recovered before.
+struct TileAttend {
+  TilePair pair;
+  int tiles;
+  AttendCacheArgs attend;
+};
+// How an epilogue splits a tile, and the LDS it takes
+template <int MODE, int MB> struct TileEpilogue {
+  using S = Tile<MB>;
+  static constexpr int kVals = MB <= 2 ? 16 : kValsPerLane;            // values of a group per lane
+  static constexpr int kWaveRows = kVals / 2;                          // groups per wave and pass
+  static constexpr int kParkRows = S::kRows < kWaveRows * S::kWaves ? S::kRows : kWaveRows * S::kWaves;   // one pass
+  static constexpr int kBytes = MODE != kTilePredict ? (int)sizeof(Lds) + kParkRows * kLdP * 4 : 0;
+  static constexpr int kLdsBytes = kBytes > S::kLdsBytes ? kBytes : S::kLdsBytes;
+};
+// workgroup `block` of the `nblocks` that work on `a`; smem: TileEpilogue<MODE, MB>::kLdsBytes of LDS
 template <int NCW, int MODE, int MB, bool WIDE, int SUMS>
-__device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nblocks, bool keep) {
+__device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nblocks, bool keep, unsigned char* smem) {
   using S = Tile<MB>;
   static_assert(!WIDE || MODE != kTileEncode, "the quantizer needs the whole group: groups across the heads are not fused");
-  constexpr int kVals = MB <= 2 ? 16 : kValsPerLane;            // values of a group per lane
-  constexpr int kWaveRows = kVals / 2;                          // groups per wave and pass
-  constexpr int kParkRows = S::kRows < kWaveRows * S::kWaves ? S::kRows : kWaveRows * S::kWaves;   // one pass
+  using E = TileEpilogue<MODE, MB>;
+  constexpr int kVals = E::kVals, kWaveRows = E::kWaveRows, kParkRows = E::kParkRows;
   constexpr int kParks = (S::kRows + kParkRows - 1) / kParkRows;
   constexpr int kParkBlocks = kParkRows / 32 / S::WM;           // blocks of a wave's accumulators per park
   constexpr bool kEpilogue = MODE != kTilePredict;
-  constexpr int kEpilogueBytes = kEpilogue ? (int)sizeof(Lds) + kParkRows * kLdP * 4 : 0;
-  constexpr int kBytes = kEpilogueBytes > S::kLdsBytes ? kEpilogueBytes : S::kLdsBytes;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[kBytes];
   Lds& cl = *reinterpret_cast<Lds*>(smem);                      // grid and table at the start of the LDS (codec_core.h)
   float* const park = reinterpret_cast<float*>(smem + sizeof(Lds));
 
@@ -237,17 +250,44 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
 
 template <int NCW, int MODE, int MB, bool WIDE, int SUMS>
 __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(MB == 1 ? 1 : 2))) void fused_tile_kernel(const TileArgs a) {
-  fused_tile<NCW, MODE, MB, WIDE, SUMS>(a, (int)blockIdx.x, (int)gridDim.x, false);
+  __shared__ __attribute__((aligned(16))) unsigned char smem[TileEpilogue<MODE, MB>::kLdsBytes];
+  fused_tile<NCW, MODE, MB, WIDE, SUMS>(a, (int)blockIdx.x, (int)gridDim.x, false, smem);
+}
+// Workgroup blockIdx.x of a launch for two jobs, the first `blocks` of the `tiles` on job[0].  The job is read from where it was passed,
+// byte `at` of the kernel's arguments (an index into a copy would put them in scratch).
+template <int NCW, int MODE, int MB, bool WIDE, int SUMS>
+__device__ __forceinline__ void fused_tile_of_pair(int at, int blocks, int tiles, unsigned char* smem) {
+  const int second = (int)blockIdx.x >= blocks;
+  TileArgs a;
+  __builtin_memcpy(&a, (const char*)__builtin_amdgcn_kernarg_segment_ptr() + at + second * (int)sizeof(TileArgs), sizeof(TileArgs));
+  fused_tile<NCW, MODE, MB, WIDE, SUMS>(a, (int)blockIdx.x - (second ? blocks : 0), second ? tiles - blocks : blocks,
+                                        SUMS == kKeepSums && a.sums_hi != nullptr, smem);
 }
 // (a kernel of its own: picking the job puts another round of scalar loads ahead of everything, 0.4 us)
-template <int NCW, int MODE, int MB, bool WIDE>
-__global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(MB == 1 ? 1 : 2))) void fused_tile_pair_kernel(const TilePair pair) {
-  const int second = (int)blockIdx.x >= pair.blocks;
-  // read from where they were passed (an index into a copy would put them in scratch)
-  TileArgs a;
-  __builtin_memcpy(&a, (const char*)__builtin_amdgcn_kernarg_segment_ptr() + second * (int)sizeof(TileArgs), sizeof(TileArgs));
-  fused_tile<NCW, MODE, MB, WIDE, MB == 1 ? kKeepSums : kNoSums>(a, (int)blockIdx.x - (second ? pair.blocks : 0),
-                                                                 second ? (int)gridDim.x - pair.blocks : pair.blocks, a.sums_hi != nullptr);
+template <int NCW, int MODE, bool WIDE>
+__global__ __launch_bounds__(Tile<1>::kThreads) __attribute__((amdgpu_waves_per_eu(1))) void fused_tile_pair_kernel(const TilePair pair) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[TileEpilogue<MODE, 1>::kLdsBytes];
+  fused_tile_of_pair<NCW, MODE, 1, WIDE, kKeepSums>(0, pair.blocks, (int)gridDim.x, smem);
+}
+// The pieces of a launch that workgroup `block` of those behind its tiles takes: one per kAttendThreads threads.
+template <int THREADS>
+__device__ __forceinline__ void attend_behind_tiles(AttendCacheParam& a, int block, unsigned char* smem) {
+  constexpr int kPer = THREADS / kAttendThreads;
+  const int part = __builtin_amdgcn_readfirstlane(threadIdx.x / kAttendThreads);
+  const int items = (a.pieces.first[a.pieces.n_seq] - a.pieces.first[0]) * a.kv_heads, item = block * kPer + part;
+  attend_piece<bf16_t>(a, item < items ? item : items - 1, (int)threadIdx.x % kAttendThreads, item < items,
+                       reinterpret_cast<AttendLds*>(smem)[part]);
+}
+template <int NCW, int MB, bool WIDE>
+__global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(MB == 1 ? 1 : 2))) void fused_tile_attend_kernel(const TileAttend job) {
+  constexpr int kTileBytes = TileEpilogue<kTileDecode, MB>::kLdsBytes, kAttendBytes = Tile<MB>::kThreads / kAttendThreads * (int)sizeof(AttendLds);
+  __shared__ __attribute__((aligned(16))) unsigned char smem[kTileBytes > kAttendBytes ? kTileBytes : kAttendBytes];
+  if ((int)blockIdx.x < job.tiles) {
+    fused_tile_of_pair<NCW, kTileDecode, MB, WIDE, kNoSums>((int)offsetof(TileAttend, pair), job.pair.blocks, job.tiles, smem);
+  } else {
+    const char* const args = (const char*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(TileAttend, attend);
+    attend_behind_tiles<Tile<MB>::kThreads>(*(AttendCacheParam*)args, (int)blockIdx.x - job.tiles, smem);
+  }
 }
 
 // rows per tile 32, 64, 128 or 320 (one translation unit each); tiles_per_seq is filled in
@@ -257,12 +297,15 @@ AQUAKV_TILE_LAUNCHER(32);
 AQUAKV_TILE_LAUNCHER(64);
 AQUAKV_TILE_LAUNCHER(128);
 AQUAKV_TILE_LAUNCHER(320);
-// Two jobs of one mode and quantizer (TilePair): decode, and encode on tiles of 32 rows for sums.
-#define AQUAKV_PAIR_LAUNCHER(ROWS) \
-  hipError_t launch_pair_##ROWS(int mode, int n_codewords, bool wide, const TileArgs& a, const TileArgs& b, hipStream_t stream)
-AQUAKV_PAIR_LAUNCHER(32);
-AQUAKV_PAIR_LAUNCHER(64);
-AQUAKV_PAIR_LAUNCHER(128);
+// Two jobs of one mode and quantizer (TilePair), decode or encode, the second for sums if it has a place for them.
+hipError_t launch_pair_32(int mode, int n_codewords, bool wide, const TileArgs& a, const TileArgs& b, hipStream_t stream);
+// Decode of n = 1 or 2 jobs of one quantizer with pieces of attention behind their tiles (no pieces: those of no sequence).
+#define AQUAKV_TILE_ATTEND_LAUNCHER(ROWS)                                                                                  \
+  hipError_t launch_tile_attend_##ROWS(int n_codewords, bool wide, const TileArgs* jobs, int n, const AttendCacheArgs& attend, \
+                                       hipStream_t stream)
+AQUAKV_TILE_ATTEND_LAUNCHER(32);
+AQUAKV_TILE_ATTEND_LAUNCHER(64);
+AQUAKV_TILE_ATTEND_LAUNCHER(128);
 // Tiles of 32 rows, encode or decode: a product that goes on from stored sums.
 hipError_t launch_tile_rest(int mode, int n_codewords, bool wide, const TileArgs& a, hipStream_t stream);
 
@@ -291,26 +334,30 @@ hipError_t launch_tile(int mode, int n_codewords, bool wide, int n_seq, TileArgs
   return hipGetLastError();
 }
 
+// fills in the jobs' tiles, returns how many there are
 template <int MB>
-hipError_t launch_pair(int mode, int n_codewords, bool wide, const TileArgs& a, const TileArgs& b, hipStream_t stream) {
-  using S = Tile<MB>;
-  TilePair pair = {{a, b}, 0};
-  int blocks[2];
+int pair_jobs(TilePair& pair, const TileArgs* jobs, int n) {
+  int tiles = 0;
   for (int i = 0; i < 2; ++i) {
     TileArgs& job = pair.job[i];
-    job.tiles_per_seq = (job.seq_len + S::kRows - 1) / S::kRows;
-    blocks[i] = job.tiles_per_seq * (job.D / kGroup);
+    job = jobs[i < n ? i : 0];
+    job.tiles_per_seq = (job.seq_len + Tile<MB>::kRows - 1) / Tile<MB>::kRows;
+    if (i < n) tiles += job.tiles_per_seq * (job.D / kGroup);
+    if (i == 0) pair.blocks = tiles;
   }
-  pair.blocks = blocks[0];
-#define AQUAKV_TILE(N, MODE, WIDE) fused_tile_pair_kernel<N, MODE, MB, WIDE><<<blocks[0] + blocks[1], S::kThreads, 0, stream>>>(pair)
-  if (mode == kTileDecode && wide) AQUAKV_TILE_N(kTileDecode, true);
-  else if (mode == kTileDecode) AQUAKV_TILE_N(kTileDecode, false);
-  else if constexpr (MB == 1) {
-    if (mode != kTileEncode || wide) return hipErrorInvalidValue;
-    AQUAKV_TILE_N(kTileEncode, false);
-  } else {
-    return hipErrorInvalidValue;
-  }
+  return tiles;
+}
+
+template <int MB>
+hipError_t launch_tile_attend(int n_codewords, bool wide, const TileArgs* jobs, int n, const AttendCacheArgs& attend, hipStream_t stream) {
+  using S = Tile<MB>;
+  TileAttend args;
+  args.tiles = pair_jobs<MB>(args.pair, jobs, n);
+  args.attend = attend;
+  const unsigned blocks = (unsigned)args.tiles + attend_workgroups(attend, S::kThreads);
+#define AQUAKV_TILE(N, MODE, WIDE) fused_tile_attend_kernel<N, MB, WIDE><<<blocks, S::kThreads, 0, stream>>>(args)
+  if (wide) AQUAKV_TILE_N(kTileDecode, true);
+  else AQUAKV_TILE_N(kTileDecode, false);
 #undef AQUAKV_TILE
   return hipGetLastError();
 }

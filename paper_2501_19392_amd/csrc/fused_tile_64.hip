@@ -5,6 +5,6 @@ namespace aquakv {
 
 AQUAKV_TILE_LAUNCHER(64) { return launch_tile<2>(mode, n_codewords, wide, n_seq, a, stream); }
 
-AQUAKV_PAIR_LAUNCHER(64) { return launch_pair<2>(mode, n_codewords, wide, a, b, stream); }
+AQUAKV_TILE_ATTEND_LAUNCHER(64) { return launch_tile_attend<2>(n_codewords, wide, jobs, n, attend, stream); }
 
 }  // namespace aquakv

@@ -98,8 +98,13 @@ struct FusedTensor {
 bool fused_layer_fits(int64_t T, int D);
 // Values of one layer and keys of the next one (which need nothing of those values), decoded in one launch; same quantizer.
 bool fused_decode_pair_pays(int64_t T, int D);
-hipError_t launch_fused_decode_pair(int n_codewords, const float* values_codebook, const FusedTensor& values, const float* keys_codebook,
-                                    const FusedTensor& keys, int64_t T, int D, bool wide, hipStream_t stream);
+int64_t fused_decode_pair_rows(int D);      // the most rows for which it does
+// Decode of n = 1 or 2 (where fused_decode_pair_pays) such tensors, with attention over a layer recovered before on the CUs that it
+// leaves idle or free early (bf16; no pieces: none).  n = 1: where fused_decode_attend_fits.
+struct AttendCacheArgs;
+bool fused_decode_attend_fits(int64_t T, int D);
+hipError_t launch_fused_decode_attend(int n_codewords, const FusedTensor* tensors, const float* const* codebooks, int n, int64_t T, int D,
+                                      bool wide, const AttendCacheArgs& attend, hipStream_t stream);
 hipError_t launch_fused_layer(bool encode, int n_codewords, const float* codebook, const void* table, const FusedTensor& keys,
                               const FusedTensor& values, void* sums, int64_t T, int D, bool wide, hipStream_t stream);
 

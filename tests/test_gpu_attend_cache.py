@@ -142,3 +142,42 @@ def test_values_and_next_keys_recovered_together(n, rht_group):
             if l >= count - 2:
                 for a, b in zip(hat[2 * (l & 1):2 * (l & 1) + 2], (K[4:4 + c], V[4:4 + c])):
                     assert torch.equal(a.view(torch.int16), b.contiguous().view(torch.int16)), l
+
+
+@pytest.mark.parametrize("H,QH,lengths,rht_group", [
+    (8, 24, [69], None), (8, 8, [130, 700], 1024),              # two tensors on tiles of 32 and of 64 rows
+    (1, 3, [4229], None),                                       # 67 pieces, two to a workgroup: the last one has one
+    (8, 64, [3300], 1024), (8, 32, [2600, 4, 2300], None)])     # one tensor on tiles of 128 and of 256 rows
+def test_attention_beside_the_recovery_of_the_next_layer(H, QH, lengths, rht_group):
+    """Same bits as with attention in launches of its own, which a workspace without the third place for keys gives where two tensors are
+    recovered at once; attention over the tensors of the sweep in every case."""
+    from paper_2501_19392_amd import binding as B
+    from paper_2501_19392_amd.cache import AquaKVCache
+    print(f"case attention beside recovery H={H} QH={QH} lengths={lengths} group={rht_group}", flush=True)
+    L, NB, n, D = 5, len(lengths), max(lengths), H * 128
+    gen = torch.Generator().manual_seed(n)
+    kw = {"rht_group": rht_group} if rht_group else {}
+    layers, kv, qs = [], [], []
+    for l in range(L):
+        w = [None, None] if l == 0 else [0.3 * torch.randn(D, d, generator=gen) / d ** 0.5 for d in (D, 2 * D)]
+        layers.append(U.make_layers(H, "bf16", 256 if l == 0 else 16, layer_idx=l, w_k=w[0], w_v=w[1], **kw)[1])
+        kv.append(tuple(torch.randn(NB, n, H, 128, generator=gen).bfloat16().cuda() for _ in range(2)))
+        qs.append(torch.randn(NB, QH, 128, generator=gen).bfloat16().cuda())
+    cache = AquaKVCache(layers, max_tokens=n, sink_tokens=4, buffer_tokens=64, batch=NB)
+    cache.append(kv, lengths=lengths)
+    got = [o.clone() for o in cache.attend(qs, 128 ** -0.5)]
+    compressed, row = sum(c for c in (cache.n_compressed if NB > 1 else [cache.n_compressed])), D * 2
+    A = cache._attend
+    third = -(-min(NB * cache._C, 192 // H * 128) * row // 256) * 256
+    A["ws"] = A["ws"][:B.aquakv_attend_cache_workspace_bytes(A["layers"], A["shape"]) - third]
+    one = (sum(-(-t // 64) for t in lengths) * QH * 130 * 4 + 255) // 256 * 256
+    codec = max(lay.alloc_workspace(compressed).numel() for lay in layers)
+    if compressed <= 192 // H * 128:                             # no room for the third place beside one layer's partial results
+        A["ws"] = A["ws"][:(codec + 255) // 256 * 256 + one]
+    again = [o.clone() for o in cache.attend(qs, 128 ** -0.5)]
+    for l in range(L):
+        assert torch.equal(got[l], again[l]), l
+    for b in range(NB):
+        for l, K, V in cache.sweep(b):
+            want = plain_attention(qs[l][b], K, V, 128 ** -0.5, None)
+            assert float((got[l][b].double() - want).abs().max() / V.double().square().mean().sqrt()) < 1e-5, (b, l)
