@@ -423,6 +423,32 @@ typedef struct aquakv_copy_range {
 int aquakv_copy_ranges(const aquakv_copy_range* ranges, int32_t n, void* stream);
 
 /*
+ * aquakv_encode_layers -- the same rows of a stack of layers, encoded from the first to the last as aquakv_encode_layer calls would,
+ * every layer from the reconstructions of the one before (Alg. "Inference": what a full buffer, or a prompt, goes through): same codes,
+ * scales and reconstructions.  The keys of a layer need the keys before, not its values, so the values of layer l and the keys of
+ * layer l + 1 share launches where few rows leave CUs idle.  layers[l].layer = NULL: the layer is not encoded, its K and V are what the
+ * next layer's predictors read.  `hat`: HOST array of four device buffers, K and V of even layers, K and V of odd layers, [tokens,
+ * kv_heads, 128] each: layer l is reconstructed into pair l % 2.  Predictors, if a layer has any, take the vectors of one layer
+ * (d_in_k = kv_heads * 128, d_in_v = twice that), and kv_heads and dtype are those of all layers.
+ * `workspace`: the most that aquakv_workspace_bytes(layer, tokens) is over the layers; with groups across the heads and up to 4096
+ * rows, room for the fp32 predictions of both tensors in halves (2 * tokens * kv_heads * 128 * 2 bytes) lets these share launches too.
+ * Nothing that the call writes (codes, scales, hat, the workspace) may overlap anything else it is given: AQUAKV_EINVAL, like every
+ * other fault in the arguments before anything is launched (of a layer and the next one; a caller may give layers l and l + 2 the same
+ * codes or inputs).
+ */
+typedef struct aquakv_encode_entry {
+  const aquakv_layer* layer;
+  const void* K;                          /* [tokens, kv_heads, 128] */
+  const void* V;
+  uint8_t* k_codes;                       /* as aquakv_encode_layer writes them */
+  uint16_t* k_scales;
+  uint8_t* v_codes;
+  uint16_t* v_scales;
+} aquakv_encode_entry;
+int aquakv_encode_layers(const aquakv_encode_entry* layers, int32_t n_layers, int64_t tokens, void* const* hat, void* workspace,
+                         size_t workspace_bytes, void* stream);
+
+/*
  * aquakv_attend_cache -- attention of one new token per sequence over a whole cache (Alg. "Inference", Sect. 3.3): for every
  * layer in order, recover the compressed ranges of all sequences, then out = softmax(score_scale * q K^T) V over sinks,
  * compressed past and recent tokens of the query's own sequence, whose token t has position t.  n_sink, n_compressed, n_recent:

@@ -41,7 +41,7 @@ EXPORTS = [
     "aquakv_encode_keys", "aquakv_encode_values", "aquakv_decode_values",
     "aquakv_fit_workspace_bytes", "aquakv_fit_predictor",
     "aquakv_softmax", "aquakv_weighted_workspace_bytes", "aquakv_decode_values_weighted", "aquakv_decode_values_attend",
-    "aquakv_attend_raw", "aquakv_copy_ranges", "aquakv_attend_cache_workspace_bytes", "aquakv_attend_cache",
+    "aquakv_attend_raw", "aquakv_copy_ranges", "aquakv_encode_layers", "aquakv_attend_cache_workspace_bytes", "aquakv_attend_cache",
 ]
 
 
@@ -110,11 +110,12 @@ _lib.aquakv_decode_values_weighted.argtypes = [_LP, ctypes.c_int32, ctypes.c_int
 _lib.aquakv_decode_values_attend.argtypes = [_LP, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32] + [_P] * 9 + [ctypes.c_size_t, _P]
 _lib.aquakv_attend_raw.argtypes = [ctypes.c_int32] * 5 + [_P, _P, _P, _P, _P, ctypes.c_float, _P, _P, ctypes.c_int32, _P]
 _lib.aquakv_copy_ranges.argtypes = [_P, ctypes.c_int32, _P]
+_lib.aquakv_encode_layers.argtypes = [_P, ctypes.c_int32, ctypes.c_int64, _P, _P, ctypes.c_size_t, _P]
 _CLP, _CSP = ctypes.POINTER(aquakv_cache_layer), ctypes.POINTER(aquakv_cache_shape)
 _lib.aquakv_attend_cache_workspace_bytes.restype = ctypes.c_size_t
 _lib.aquakv_attend_cache_workspace_bytes.argtypes = [_CLP, ctypes.c_int32, _CSP]
 _lib.aquakv_attend_cache.argtypes = [_CLP, ctypes.c_int32, _CSP] + [_P] * 5 + [ctypes.c_float, _P, _P, ctypes.c_size_t, _P]
-for _n in ("aquakv_attend_cache", "aquakv_copy_ranges", "aquakv_attend_raw", "aquakv_softmax", "aquakv_decode_values_weighted", "aquakv_decode_values_attend", "aquakv_predict", "aquakv_quantize", "aquakv_dequantize", "aquakv_encode_layer", "aquakv_decode_layer",
+for _n in ("aquakv_attend_cache", "aquakv_encode_layers", "aquakv_copy_ranges", "aquakv_attend_raw", "aquakv_softmax", "aquakv_decode_values_weighted", "aquakv_decode_values_attend", "aquakv_predict", "aquakv_quantize", "aquakv_dequantize", "aquakv_encode_layer", "aquakv_decode_layer",
            "aquakv_decode_attn_scores", "aquakv_decode_attn_scores_rope", "aquakv_decode_attn_scores_folded",
            "aquakv_decode_attn_scores_folded_static", "aquakv_encode_keys", "aquakv_encode_values",
            "aquakv_decode_values", "aquakv_fit_predictor"):
@@ -392,6 +393,18 @@ def aquakv_copy_ranges(ranges, stream=None) -> None:
     """ranges: flat sequence of addresses and sizes, (dst, src, bytes) per copy."""
     flat = array.array("Q", ranges)
     _check(_lib.aquakv_copy_ranges(flat.buffer_info()[0], len(flat) // 3, _stream(stream)))
+
+
+def aquakv_encode_layers(entries, tokens: int, hat, workspace, stream=None) -> None:
+    """entries: per layer (Layer or None, K, V, k_codes, k_scales, v_codes, v_scales), tensors or addresses (a layer given as None: 0 or
+    None for the last four); hat: four of them."""
+    flat = array.array("Q")
+    for layer, *bufs in entries:
+        flat.append(0 if layer is None else ctypes.addressof(layer.c if isinstance(layer, Layer) else layer))
+        flat.extend([x if x.__class__ is int else _ptr(x) or 0 for x in bufs])
+    to = array.array("Q", [x if x.__class__ is int else _ptr(x) for x in hat])
+    wp, wn = _ws(workspace)
+    _check(_lib.aquakv_encode_layers(flat.buffer_info()[0], len(flat) // 7, tokens, to.buffer_info()[0], wp, wn, _stream(stream)))
 
 
 def cache_layers(entries):

@@ -15,8 +15,8 @@ layer the soft-max attention of that token's queries over everything cached, in 
 sequences (`aquakv_attend_cache`).
 
 Batch.  Every sequence has its own sinks, buffer and compressed range (lengths may differ).  All sequences whose
-buffer fills during one `append` are quantized together: ONE `aquakv_encode_layer` per layer over
-(number of full buffers) x r tokens; whole buffers' worth of a prompt go from the caller's tensors to the compressed
+buffer fills during one `append` are quantized together: ONE `aquakv_encode_layer` per layer (or one `aquakv_encode_layers`
+for all, where no tokens have to be gathered) over (number of full buffers) x r tokens; whole buffers' worth of a prompt go from the caller's tensors to the compressed
 range directly.  Codes of a sequence are contiguous in its own range of the code tensors; `attend` recovers a layer of
 all sequences at once, from codes that are first put one behind the other in a staging range unless they already are
 (codes are an eighth of the bytes the recovery moves).
@@ -60,7 +60,8 @@ class AquaKVCache:
         self.buf = pairs(raws(2 * L, batch, buf))
         # sequence b owns tokens [b * C, (b + 1) * C) of the code tensors (and of the 16-bit tensors of a layer given as None)
         self.codes = self._alloc_codes(batch * C, device)
-        raw = iter(pairs(raws(2 * sum(l is None for l in self.layers), batch * C)))
+        kept = sum(l is None for l in self.layers)
+        raw = iter(pairs(raws(2 * kept, batch * C)) if kept else ())
         self.raw = [next(raw) if l is None else None for l in self.layers]
         # flush: reconstructions of the flushed tokens, two ping-pong pairs (layer l - 1 feeds layer l); with several
         # sequences also the gathered buffers and the codes before they are scattered to their sequences
@@ -74,6 +75,11 @@ class AquaKVCache:
         self._view_ws = self._alloc_workspace(batch * C, device)
         self._staged = self._alloc_codes(batch * C, device) if batch > 1 else [None] * L
         self._ns, self._nc, self._nb = [0] * batch, [0] * batch, [0] * batch
+        # all layers of a flush, or of a prompt, in one native call (aquakv_encode_layers) where their tokens lie one behind the other;
+        # fp32 layers, and predictors of other widths, layer by layer
+        D = H * g
+        self._one_call = dt == torch.bfloat16 and all(l is None or (l.kv_heads * l.head_dim == D and l.c.d_in_k in (0, D) and
+                                                                    l.c.d_in_v in (0, 2 * D)) for l in self.layers)
         self._attend = None                 # buffers of attend(), sized on first use (they depend on the query heads)
         self._device = device
 
@@ -286,6 +292,12 @@ class AquaKVCache:
         chunks, hat, stage, staged, _ = plan                           # layer l - 1 feeds layer l: two pairs of hat and stage
         for c in chunks:
             N = sum(p[3] for p in c)
+            if self._one_call and len(c) == 1:
+                b, pos, at, _ = c[0]
+                Xs = [x + b * seq + pos * row for x, seq in src]
+                self._encode_layers(N, Xs, [None if lay is None else [p + at * size for p, size in self._codes_at(l)]
+                                            for l, lay in enumerate(self.layers)], hat, self._view_ws, [(at, N)])
+                continue
             Kp = Vp = None
             for l, lay in enumerate(self.layers):
                 Xs = [x + c[0][0] * seq + c[0][1] * row for x, seq in src[2 * l:2 * l + 2]]
@@ -309,6 +321,18 @@ class AquaKVCache:
                     self._scatter(stores, out, [p[2:] for p in c])
                 Kp, Vp = Kh, Vh
 
+    def _encode_layers(self, N: int, Xs: List[int], outs: list, hat, ws, parts: List[Tuple[int, int]]) -> None:
+        """N tokens whose K and V lie at addresses Xs[2 l], Xs[2 l + 1], one behind the other: codes and scales to outs[l], the rows of
+        a layer kept in 16 bits to its ranges `parts`."""
+        B.aquakv_encode_layers([(lay, *Xs[2 * l:2 * l + 2], *(outs[l] or (0, 0, 0, 0))) for l, lay in enumerate(self.layers)], N,
+                               [x for pair in hat for x in pair], ws)
+        jobs: List[int] = []
+        for l, lay in enumerate(self.layers):
+            if lay is None:
+                self._scatter([(t.data_ptr(), self._row_bytes) for t in self.raw[l]], Xs[2 * l:2 * l + 2], parts, jobs)
+        if jobs:
+            B.aquakv_copy_ranges(jobs)
+
     @staticmethod
     def _scatter(stores, sources, parts: List[Tuple[int, int]], jobs: Optional[List[int]] = None) -> None:
         """The rows at address sources[k], part after part, to rows at ... of stores[k] = (address, bytes per row); added to
@@ -330,6 +354,16 @@ class AquaKVCache:
         whole = n == self.batch                              # the buffers of all sequences are one contiguous tensor
         parts = [(b * C + at, r) for b, at in full]
         scatter: List[int] = []
+        if whole and self._one_call:
+            outs = [None if lay is None else [p + full[0][1] * size for p, size in self._codes_at(l)] if single
+                    else self._addresses(self._flush_codes[l]) for l, lay in enumerate(self.layers)]
+            self._encode_layers(n * r, self._addresses(self.buf), outs, self._flush_hat, self._flush_ws, parts)
+            for l, lay in enumerate(self.layers):
+                if not single and lay is not None:
+                    self._scatter(self._codes_at(l), outs[l], parts, scatter)
+            if scatter:                                      # the codes of all layers in one go
+                B.aquakv_copy_ranges(scatter)
+            return
         Kp = Vp = None
         for l, lay in enumerate(self.layers):
             if whole:
@@ -354,7 +388,7 @@ class AquaKVCache:
             if not single:
                 self._scatter(self._codes_at(l), out, parts, scatter)
             Kp, Vp = Kh, Vh
-        if scatter:                                          # the codes of all layers in one go
+        if scatter:
             B.aquakv_copy_ranges(scatter)
 
     # ------------------------------------------------------------------ recovery of one sequence

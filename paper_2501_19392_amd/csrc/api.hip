@@ -630,6 +630,149 @@ int aquakv_decode_layer(const aquakv_layer* L, int64_t tokens, const uint8_t* k_
   return AQUAKV_OK;
 }
 
+// ---- a stack of layers ------------------------------------------------------------------------------------------
+namespace {
+// What aquakv_encode_layers checks of its arguments
+int check_encode_layers(const aquakv_encode_entry* layers, int32_t n_layers, int64_t tokens, void* const* hat, const void* workspace,
+                        size_t workspace_bytes) {
+  if (layers == nullptr || hat == nullptr) return fail(AQUAKV_ENULL, "layers / hat is NULL");
+  if (n_layers < 1) return fail(AQUAKV_EINVAL, "n_layers=%d", n_layers);
+  if (tokens < 0) return fail(AQUAKV_EINVAL, "tokens=%lld", (long long)tokens);
+  const aquakv_layer* first = nullptr;
+  for (int32_t l = 0; l < n_layers; ++l) {
+    const aquakv_encode_entry& c = layers[l];
+    const aquakv_layer* const L = c.layer;
+    CHECK(check_ptr(c.K, "K", true));
+    CHECK(check_ptr(c.V, "V", true));
+    if (L == nullptr) continue;
+    CHECK(check_layer(L));
+    if (first == nullptr) first = L;
+    const int D = L->kv_heads * L->head_dim;
+    if (L->kv_heads != first->kv_heads || L->dtype != first->dtype)
+      return fail(AQUAKV_EINVAL, "layer %d: kv_heads=%d dtype=%d differ from those before", l, L->kv_heads, L->dtype);
+    if ((L->d_in_k != 0 && L->d_in_k != D) || (L->d_in_v != 0 && L->d_in_v != 2 * D))
+      return fail(AQUAKV_EINVAL, "layer %d: predictors of %d and %d inputs, layers of %d heads need %d and %d", l, L->d_in_k, L->d_in_v,
+                  L->kv_heads, D, 2 * D);
+    if (l == 0 && (L->d_in_k != 0 || L->d_in_v != 0)) return fail(AQUAKV_ENULL, "layer 0 has predictors, but no layer comes before it");
+    CHECK(check_ptr(c.k_codes, "k_codes", true));
+    CHECK(check_scales(L, c.k_scales, "k_scales", true));
+    CHECK(check_ptr(c.v_codes, "v_codes", true));
+    CHECK(check_scales(L, c.v_scales, "v_scales", true));
+  }
+  if (first == nullptr || tokens == 0) return AQUAKV_OK;
+  for (int i = 0; i < 4; ++i) CHECK(check_ptr(hat[i], "hat", true));
+  CHECK(check_ptr(workspace, "workspace", true));
+  const size_t t = (size_t)tokens, row = (size_t)first->kv_heads * first->head_dim * elem_bytes(first->dtype);
+  for (int32_t l = 0; l < n_layers; ++l) {
+    if (layers[l].layer == nullptr) continue;
+    const Plan pl = make_plan(layers[l].layer, tokens);
+    if (workspace_bytes < pl.p_bytes + pl.khat_bytes)
+      return fail(AQUAKV_EWORKSPACE, "workspace %zu B < required %zu B", workspace_bytes, pl.p_bytes + pl.khat_bytes);
+  }
+  for (int32_t l = 0; l < n_layers; ++l) {                   // a layer and the next one, with everything the call writes for all
+    CacheRange r[4 + 1 + 2 * 6];
+    int n = 0;
+    const auto add = [&](const void* p, size_t bytes, const char* name, int32_t layer, bool written) {
+      const uintptr_t begin = reinterpret_cast<uintptr_t>(p);
+      if (bytes != 0) r[n++] = {begin, begin + bytes, name, layer, written};
+    };
+    for (int i = 0; i < 4; ++i) add(hat[i], t * row, "hat", i >> 1, true);
+    add(workspace, workspace_bytes, "workspace", l, true);
+    for (int32_t m = l; m < n_layers && m < l + 2; ++m) {
+      const aquakv_encode_entry& c = layers[m];
+      add(c.K, t * row, "K", m, false);
+      add(c.V, t * row, "V", m, false);
+      if (c.layer == nullptr) continue;
+      const size_t crow = make_plan(c.layer, 1).code_row, srow = scale_row_bytes(c.layer);
+      add(c.k_codes, t * crow, "k_codes", m, true);
+      add(c.k_scales, t * srow, "k_scales", m, true);
+      add(c.v_codes, t * crow, "v_codes", m, true);
+      add(c.v_scales, t * srow, "v_scales", m, true);
+    }
+    CHECK(check_disjoint(r, n));
+  }
+  return AQUAKV_OK;
+}
+}  // namespace
+
+int aquakv_encode_layers(const aquakv_encode_entry* layers, int32_t n_layers, int64_t tokens, void* const* hat, void* workspace,
+                         size_t workspace_bytes, void* stream_) {
+  CHECK(check_encode_layers(layers, n_layers, tokens, hat, workspace, workspace_bytes));
+  if (tokens == 0) return AQUAKV_OK;
+  hipStream_t stream = static_cast<hipStream_t>(stream_);
+  float* const ws = static_cast<float*>(workspace);
+  // values of layer l and keys of layer l + 1 at once: bf16, one quantizer, few rows
+  const auto with_next = [&](int32_t l) {
+    const aquakv_layer *a = layers[l].layer, *b = l + 1 < n_layers ? layers[l + 1].layer : nullptr;
+    if (a == nullptr || b == nullptr || a->dtype != AQUAKV_BF16 || a->d_in_v == 0 || b->d_in_k == 0 ||
+        quantizer_id(a) != quantizer_id(b) || is_wide(a) != is_wide(b))
+      return false;
+    const int D = a->kv_heads * 128;
+    if (!is_wide(a)) return aquakv::fused_encode_pair_pays(tokens, D);
+    return tokens <= aquakv::tile_predict_pair_rows(D) && workspace_bytes >= 2 * (size_t)tokens * D * elem_bytes(a->dtype);
+  };
+  const auto keys_hat = [&](int32_t l) { return hat[2 * (l & 1)]; };
+  const auto values_hat = [&](int32_t l) { return hat[2 * (l & 1) + 1]; };
+  const void *Kp = nullptr, *Vp = nullptr;                   // of the layer before
+  const auto key_tensor = [&](int32_t l, const void* prev) {
+    const aquakv_encode_entry& c = layers[l];
+    return aquakv::FusedTensor{prev, nullptr, c.layer->d_in_k, 0, c.layer->w_k, c.layer->b_k, c.layer->signs_k, c.K, c.k_codes, c.k_scales,
+                               keys_hat(l)};
+  };
+  bool have_keys = false;                                    // of this layer, encoded with the values of the one before
+  for (int32_t l = 0; l < n_layers; ++l) {
+    const aquakv_encode_entry& c = layers[l];
+    const aquakv_layer* const L = c.layer;
+    if (L == nullptr) {
+      Kp = c.K; Vp = c.V;
+      continue;
+    }
+    const int D = L->kv_heads * L->head_dim;
+    const Plan pl = make_plan(L, tokens);
+    void *const K = keys_hat(l), *const V = values_hat(l);
+    const bool pair = with_next(l);
+    if (!have_keys && !pair) {
+      CHECK(aquakv_encode_layer(L, tokens, c.K, c.V, Kp, Vp, c.k_codes, c.k_scales, c.v_codes, c.v_scales, K, V, workspace,
+                                workspace_bytes, stream));
+    } else {
+      const size_t row = (size_t)D * pl.eb;
+      for (int64_t r0 = 0; r0 < tokens && !have_keys; r0 += pl.chunk)
+        CHECK(encode_keys_chunk(L, pl, r0, tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk, c.K, Kp, c.k_codes, c.k_scales,
+                                at(K, r0, row), ws, workspace_bytes, stream));
+      if (!pair) {
+        for (int64_t r0 = 0; r0 < tokens; r0 += pl.chunk)
+          CHECK(encode_values_chunk(L, pl, r0, tokens - r0 < pl.chunk ? tokens - r0 : pl.chunk, c.V, Vp, at(K, r0, row), c.v_codes,
+                                    c.v_scales, V, ws, workspace_bytes, stream));
+      } else {
+        const aquakv_layer* const N = layers[l + 1].layer;
+        const aquakv::FusedTensor t[2] = {
+            {Vp, K, D, D, L->w_v, L->b_v, L->signs_v, c.V, c.v_codes, c.v_scales, V}, key_tensor(l + 1, K)};
+        const float* const codebooks[2] = {L->codebook, N->codebook};
+        const void* const tables[2] = {L->search_table, N->search_table};
+        if (!is_wide(L)) {
+          HIP_TRY(aquakv::launch_fused_encode_pair(quantizer_id(L), t, codebooks, tables, tokens, D, stream));
+        } else {
+          // predictions in fp32, the upper heads' in the workspace and the others' in the rows that the quantizer will write
+          aquakv::Prediction P[2];
+          aquakv::QuantizeIo io[2];
+          for (int i = 0; i < 2; ++i) {
+            P[i] = {static_cast<float*>(t[i].Xhat), ws + i * tokens * (D / 2), D / 2, D / 2};
+            io[i] = {t[i].X, t[i].signs, t[i].codes, t[i].scales, t[i].Xhat};
+          }
+          HIP_TRY(aquakv::launch_tile_predict_pair(t, P, tokens, D, stream));
+          const bool one = is_rtn(L) || (codebooks[0] == codebooks[1] && tables[0] == tables[1]);
+          for (int i = 0; i < (one ? 1 : 2); ++i)
+            HIP_TRY(aquakv::launch_quantize(L->dtype, quantizer_id(L), io + i, one ? 2 : 1, P + i, codebooks[i], tables[i], tokens,
+                                            L->kv_heads, true, stream));
+        }
+      }
+    }
+    have_keys = pair;
+    Kp = K; Vp = V;
+  }
+  return AQUAKV_OK;
+}
+
 // ---- the two halves of Alg. "encode" / "decode" as calls of their own -------------------------------------------
 // The key chain of a layer stack depends on keys only, the value chain on the previous values and this layer's keys,
 // so a caller can run them on two streams (events between them) and overlap the kernels of neighbouring layers.

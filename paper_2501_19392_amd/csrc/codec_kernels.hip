@@ -24,7 +24,8 @@ constexpr int kGroupsPerBlock = kThreads / kLanesPerGroup;   // 64
 
 // ------------------------------------------------------------------ quantize
 // blockIdx.y: which of the one or two tensors of the launch (QuantizeIo in kernels.h; the keys and the values of a layer
-// without predictors do not depend on each other, and together they fill the chip better).
+// without predictors do not depend on each other, nor do the values of a layer and the keys of the next one, and together they fill
+// the chip better).
 //
 // Bound by vector issue and, with it, by how many waves a SIMD holds to cover the look-ups' LDS latency, hence 16 values per
 // lane: 113 to 120 registers = four waves per SIMD without a prediction (PRED false), 147 to 154 = three with one.  With 32 values
@@ -39,13 +40,14 @@ constexpr int kGroupsPerBlock = kThreads / kLanesPerGroup;   // 64
 // Which launches: codes_pay.
 template <typename T, int NCW, bool WIDE, bool PRED, bool CODES>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PRED || CODES ? 3 : 4))) void quantize_kernel(
-    const QuantizeIo io0, const QuantizeIo io1, const Prediction P, const float* __restrict__ codebook,
+    const QuantizeIo io0, const QuantizeIo io1, const Prediction P0, const Prediction P1, const float* __restrict__ codebook,
     const uint32_t* __restrict__ table, int64_t n_groups, int H, bool fixed_head) {
   const T* const X = static_cast<const T*>(blockIdx.y ? io1.X : io0.X);
   T* const Xhat = CODES ? nullptr : static_cast<T*>(blockIdx.y ? io1.Xhat : io0.Xhat);
   const int8_t* const signs = blockIdx.y ? io1.signs : io0.signs;
   uint8_t* const codes = blockIdx.y ? io1.codes : io0.codes;
   uint16_t* const scales = blockIdx.y ? io1.scales : io0.scales;
+  const Prediction P = {blockIdx.y ? P1.first : P0.first, blockIdx.y ? P1.second : P0.second, P0.stride, P0.split};
   __shared__ Lds lds;
   stage_lds<NCW>(lds, codebook, table);
   constexpr int N = CODES ? kCodesVals : kQuantizeVals, kLanes = kGroup / N, kGroups = kThreads / kLanes;       // lanes per group, groups per round
@@ -433,8 +435,10 @@ hipError_t launch_quantize(int dtype, int n_codewords, const QuantizeIo* io, int
                            const float* codebook, const void* table, int64_t T_, int H, bool wide, hipStream_t stream) {
   const int64_t n_groups = T_ * H;
   if (n_groups == 0) return hipSuccess;
-  if (tensors != 1 && P != nullptr) return hipErrorInvalidValue;
-  if (P != nullptr && !wide && P->second != P->first + P->split) return hipErrorInvalidValue;      // (read as contiguous)
+  for (int i = 0; i < tensors && P != nullptr; ++i) {
+    if (P[i].stride != P[0].stride || P[i].split != P[0].split) return hipErrorInvalidValue;
+    if (!wide && P[i].second != P[i].first + P[i].split) return hipErrorInvalidValue;             // (read as contiguous)
+  }
   const QuantizeIo& other = io[tensors - 1];
   const uint32_t* tab = static_cast<const uint32_t*>(table);
   const bool codes_only = is_rtn(n_codewords) && dtype == kBF16 && P == nullptr && io[0].Xhat == nullptr && other.Xhat == nullptr &&
@@ -442,17 +446,18 @@ hipError_t launch_quantize(int dtype, int n_codewords, const QuantizeIo* io, int
   const int per_cu = P != nullptr ? kQuantizeWgPerCu : codes_only ? kCodesWgPerCu : kQuantizePlainWgPerCu;
   const Rounds r = rounds_for(n_groups, kThreads * (codes_only ? kCodesVals : kQuantizeVals) / kGroup, H, per_cu, tensors);
   const dim3 grid(r.blocks, (unsigned)tensors);
-#define AQUAKV_QUANTIZE(T, N, W, PRED, CODES, P) \
-  quantize_kernel<T, N, W, PRED, CODES><<<grid, kThreads, 0, stream>>>(io[0], other, P, codebook, tab, n_groups, H, r.fixed_head)
+  const Prediction p0 = P != nullptr ? P[0] : Prediction{}, p1 = P != nullptr ? P[tensors - 1] : Prediction{};
+#define AQUAKV_QUANTIZE(T, N, W, PRED, CODES) \
+  quantize_kernel<T, N, W, PRED, CODES><<<grid, kThreads, 0, stream>>>(io[0], other, p0, p1, codebook, tab, n_groups, H, r.fixed_head)
   if (codes_only) {
-    if (n_codewords == kRtn2 && wide) AQUAKV_QUANTIZE(bf16_t, kRtn2, true, false, true, Prediction{});
-    else if (n_codewords == kRtn2) AQUAKV_QUANTIZE(bf16_t, kRtn2, false, false, true, Prediction{});
-    else if (wide) AQUAKV_QUANTIZE(bf16_t, kRtn4, true, false, true, Prediction{});
-    else AQUAKV_QUANTIZE(bf16_t, kRtn4, false, false, true, Prediction{});
+    if (n_codewords == kRtn2 && wide) AQUAKV_QUANTIZE(bf16_t, kRtn2, true, false, true);
+    else if (n_codewords == kRtn2) AQUAKV_QUANTIZE(bf16_t, kRtn2, false, false, true);
+    else if (wide) AQUAKV_QUANTIZE(bf16_t, kRtn4, true, false, true);
+    else AQUAKV_QUANTIZE(bf16_t, kRtn4, false, false, true);
   } else if (P != nullptr) {
-    AQUAKV_DISPATCH(dtype, n_codewords, wide, (AQUAKV_QUANTIZE(T, N, W, true, false, *P)));
+    AQUAKV_DISPATCH(dtype, n_codewords, wide, (AQUAKV_QUANTIZE(T, N, W, true, false)));
   } else {
-    AQUAKV_DISPATCH(dtype, n_codewords, wide, (AQUAKV_QUANTIZE(T, N, W, false, false, Prediction{})));
+    AQUAKV_DISPATCH(dtype, n_codewords, wide, (AQUAKV_QUANTIZE(T, N, W, false, false)));
   }
 #undef AQUAKV_QUANTIZE
   return hipGetLastError();

@@ -470,6 +470,51 @@ hipError_t launch_fused_decode_attend(int n_codewords, const FusedTensor* tensor
   return hipGetLastError();
 }
 
+namespace {
+// The same for encoding, where a tile's epilogue weighs more.  Stack of 8 layers, 16 points, us, a layer at a time / values and next keys
+// together: 128 rows 142 / 105, 512 151 / 114, 1024 176 / 145, 1100 194 / 178, 2048 223 / 204, 2304 (288 tiles of 128 rows) 296 / 266,
+// 2700 (352) 299 / 300.
+int encode_pair_rows(int64_t T, int D) {
+  const int64_t H = D / BN;
+  for (const int rows : {32, 64, 128})
+    if (2 * ((T + rows - 1) / rows) * H <= (rows == 128 ? 320 : 256)) return rows;
+  return 0;
+}
+}  // namespace
+bool fused_encode_pair_pays(int64_t T, int D) { return encode_pair_rows(T, D) != 0; }
+hipError_t launch_fused_encode_pair(int n_codewords, const FusedTensor* tensors, const float* const* codebooks, const void* const* tables,
+                                    int64_t T, int D, hipStream_t stream) {
+  if (T == 0) return hipSuccess;
+  TileArgs jobs[2];
+  for (int i = 0; i < 2; ++i) {
+    jobs[i] = tensor_args(tensors[i], codebooks[i], T, D);
+    jobs[i].table = static_cast<const uint32_t*>(tables[i]);
+  }
+  const int rows = encode_pair_rows(T, D);
+  if (rows == 32) return launch_pair_32(kTileEncode, n_codewords, false, jobs[0], jobs[1], stream);
+  if (rows == 64) return launch_tile_two_64(kTileEncode, n_codewords, jobs, stream);
+  if (rows == 128) return launch_tile_two_128(kTileEncode, n_codewords, jobs, stream);
+  return hipErrorInvalidValue;
+}
+
+// Predictions of two tensors (groups across the heads): a tile is a main loop and its stores, and two launches of the predictor and two of
+// the quantizer become one each, so it pays up to two rounds of tiles of 128 rows.  Stack of 8 layers, 16 points, us, a layer at a time /
+// together: 128 rows 222 / 143, 512 236 / 164, 1100 282 / 224 (on 128 rows 235), 1400 291 / 240 (on 64 rows 250), 2304 405 / 338,
+// 3072 420 / 384, 4096 490 / 469.
+int64_t tile_predict_pair_rows(int D) { return 512 / 2 / (D / BN) * 128; }
+hipError_t launch_tile_predict_pair(const FusedTensor* tensors, const Prediction* out, int64_t T, int D, hipStream_t stream) {
+  if (T == 0) return hipSuccess;
+  TileArgs jobs[2];
+  for (int i = 0; i < 2; ++i) {
+    jobs[i] = tensor_args(tensors[i], nullptr, T, D);
+    jobs[i].P = out[i];
+  }
+  const auto tiles = [&](int64_t rows) { return 2 * ((T + rows - 1) / rows) * (D / BN); };
+  if (tiles(32) <= 256) return launch_tile_two_32(kTilePredict, 16, jobs, stream);
+  if (tiles(64) <= 320) return launch_tile_two_64(kTilePredict, 16, jobs, stream);
+  return launch_tile_two_128(kTilePredict, 16, jobs, stream);
+}
+
 // Tiles of 32 rows for both products on the CUs at once.  With tiles of 64 rows for the first launch, up to twice the rows,
 // 600 tokens of 8 heads take 24.3 us to encode against 22.9 one after the other, 1000 tokens 25.5 against 23.8.
 bool fused_layer_fits(int64_t T, int D) { return 2 * ((T + 31) / 32) * (D / BN) <= 256; }

@@ -269,6 +269,12 @@ __global__ __launch_bounds__(Tile<1>::kThreads) __attribute__((amdgpu_waves_per_
   __shared__ __attribute__((aligned(16))) unsigned char smem[TileEpilogue<MODE, 1>::kLdsBytes];
   fused_tile_of_pair<NCW, MODE, 1, WIDE, kKeepSums>(0, pair.blocks, (int)gridDim.x, smem);
 }
+// Two tensors that are encoded, or predicted (MODE)
+template <int NCW, int MODE, int MB>
+__global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(MB == 1 ? 1 : 2))) void fused_tile_two_kernel(const TilePair pair) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[TileEpilogue<MODE, MB>::kLdsBytes];
+  fused_tile_of_pair<NCW, MODE, MB, false, kNoSums>(0, pair.blocks, (int)gridDim.x, smem);
+}
 // The pieces of a launch that workgroup `block` of those behind its tiles takes: one per kAttendThreads threads.
 template <int THREADS>
 __device__ __forceinline__ void attend_behind_tiles(AttendCacheParam& a, int block, unsigned char* smem) {
@@ -306,6 +312,11 @@ hipError_t launch_pair_32(int mode, int n_codewords, bool wide, const TileArgs& 
 AQUAKV_TILE_ATTEND_LAUNCHER(32);
 AQUAKV_TILE_ATTEND_LAUNCHER(64);
 AQUAKV_TILE_ATTEND_LAUNCHER(128);
+// Encode or prediction of two jobs of one quantizer (tiles of 32 rows: prediction; launch_pair_32 encodes).
+#define AQUAKV_TILE_TWO_LAUNCHER(ROWS) hipError_t launch_tile_two_##ROWS(int mode, int n_codewords, const TileArgs* jobs, hipStream_t stream)
+AQUAKV_TILE_TWO_LAUNCHER(32);
+AQUAKV_TILE_TWO_LAUNCHER(64);
+AQUAKV_TILE_TWO_LAUNCHER(128);
 // Tiles of 32 rows, encode or decode: a product that goes on from stored sums.
 hipError_t launch_tile_rest(int mode, int n_codewords, bool wide, const TileArgs& a, hipStream_t stream);
 
@@ -358,6 +369,23 @@ hipError_t launch_tile_attend(int n_codewords, bool wide, const TileArgs* jobs, 
 #define AQUAKV_TILE(N, MODE, WIDE) fused_tile_attend_kernel<N, MB, WIDE><<<blocks, S::kThreads, 0, stream>>>(args)
   if (wide) AQUAKV_TILE_N(kTileDecode, true);
   else AQUAKV_TILE_N(kTileDecode, false);
+#undef AQUAKV_TILE
+  return hipGetLastError();
+}
+
+template <int MB>
+hipError_t launch_tile_two(int mode, int n_codewords, const TileArgs* jobs, hipStream_t stream) {
+  TilePair pair;
+  const unsigned blocks = (unsigned)pair_jobs<MB>(pair, jobs, 2);
+#define AQUAKV_TILE(N, MODE, WIDE) fused_tile_two_kernel<N, MODE, MB><<<blocks, Tile<MB>::kThreads, 0, stream>>>(pair)
+  if (mode == kTilePredict) {
+    AQUAKV_TILE(16, kTilePredict, false);
+  } else if constexpr (MB > 1) {
+    if (mode != kTileEncode) return hipErrorInvalidValue;
+    AQUAKV_TILE_N(kTileEncode, false);
+  } else {
+    return hipErrorInvalidValue;
+  }
 #undef AQUAKV_TILE
   return hipGetLastError();
 }

@@ -7,4 +7,6 @@ AQUAKV_TILE_LAUNCHER(128) { return launch_tile<4>(mode, n_codewords, wide, n_seq
 
 AQUAKV_TILE_ATTEND_LAUNCHER(128) { return launch_tile_attend<4>(n_codewords, wide, jobs, n, attend, stream); }
 
+AQUAKV_TILE_TWO_LAUNCHER(128) { return launch_tile_two<4>(mode, n_codewords, jobs, stream); }
+
 }  // namespace aquakv

@@ -34,4 +34,6 @@ hipError_t launch_tile_rest(int mode, int n_codewords, bool wide, const TileArgs
   return hipGetLastError();
 }
 
+AQUAKV_TILE_TWO_LAUNCHER(32) { return launch_tile_two<1>(mode, n_codewords, jobs, stream); }
+
 }  // namespace aquakv

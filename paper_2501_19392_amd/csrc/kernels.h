@@ -30,7 +30,7 @@ struct Prediction {
     return {const_cast<float*>(P), const_cast<float*>(P) + D / 2, D, D / 2};
   }
 };
-// Q(X - P): codes, scales and (optionally) the reconstruction of io[0 .. tensors - 1] (1 or 2; 2 only without P), T rows each.
+// Q(X - P): codes, scales and (optionally) the reconstruction of io[0 .. tensors - 1] (1 or 2, P likewise, in one layout), T rows each.
 // wide: rotation groups of 1024 = the whole token (H must be 8), scales [T] instead of [T, H].
 // `table` (nullable): nearest-grid-point search table from launch_build_search_table.
 // wide: P may share its rows with Xhat (2 T D bytes of it, in the halves form): a wave reads its token's before it writes it.
@@ -101,6 +101,13 @@ bool fused_decode_pair_pays(int64_t T, int D);
 int64_t fused_decode_pair_rows(int D);      // the most rows for which it does
 // Decode of n = 1 or 2 (where fused_decode_pair_pays) such tensors, with attention over a layer recovered before on the CUs that it
 // leaves idle or free early (bf16; no pieces: none).  n = 1: where fused_decode_attend_fits.
+// The same two tensors encoded (bf16): fused with the quantizer in one launch where it pays, tables and codebooks of their own; and the
+// predictions of both in one launch (`out` as in launch_tile_predict), of up to tile_predict_pair_rows() rows.
+bool fused_encode_pair_pays(int64_t T, int D);
+hipError_t launch_fused_encode_pair(int n_codewords, const FusedTensor* tensors, const float* const* codebooks, const void* const* tables,
+                                    int64_t T, int D, hipStream_t stream);
+int64_t tile_predict_pair_rows(int D);
+hipError_t launch_tile_predict_pair(const FusedTensor* tensors, const Prediction* out, int64_t T, int D, hipStream_t stream);
 struct AttendCacheArgs;
 bool fused_decode_attend_fits(int64_t T, int D);
 hipError_t launch_fused_decode_attend(int n_codewords, const FusedTensor* tensors, const float* const* codebooks, int n, int64_t T, int D,
