@@ -10,6 +10,7 @@
 // forward substitution costs no launches of its own), and the backward substitution leaves W in the layout it is stored in.
 // Both take one launch per block column: a launch brings everything behind the column that was finished last up to date, and
 // the workgroups of the next column go on to finish that one.
+// The Gram products of bf16 data are formed in integers where sizes and data allow (exact_gram.hip), those of fp32 data and all others here.
 // 65536 tokens, 2048 inputs, 1024 outputs: 8.3 ms for the Gram products, 0.75 ms forward (23 us a launch), 0.30 ms backward;
 // 13.6 ms and 10.9 ms for the rest with scalar 64 x 64 factorisations and five launches per block column.
 #include "device_utils.h"
@@ -75,7 +76,8 @@ template <> struct Quad<float> {
 template <typename T>
 __global__ __launch_bounds__(kGramWaves * 64) void gram_kernel(const T* __restrict__ x0, int d0, const T* __restrict__ x1, int d1,
                                                                const T* __restrict__ Y, int d_out, int64_t tokens,
-                                                               double* __restrict__ G, double* __restrict__ R) {
+                                                               double* __restrict__ G, double* __restrict__ R, const int* __restrict__ wanted) {
+  if (wanted != nullptr && *wanted == 0) return;
   typedef __attribute__((address_space(3))) unsigned char* lptr_t;
   typedef const __attribute__((address_space(1))) char* gptr_t;
   constexpr int kRows = kGramRows<T>, kRowBytes = kNb * (int)sizeof(T);      // 128 or 256 bytes
@@ -626,8 +628,13 @@ hipError_t fit(int64_t tokens, const T* x0, int d0, const T* x1, int d1, const T
   int* status = reinterpret_cast<int*>(mean + d + d_out);
   const int tiles = nb * (nb + 1) / 2 + nb * nr;
   const int64_t n_all = (int64_t)d * (d + d_out);
-  zero_kernel<<<1024, 256, 0, stream>>>(reinterpret_cast<f64x2*>(G), n_all / 2);
-  gram_kernel<T><<<gram_grid(tiles), kGramWaves * 64, 0, stream>>>(x0, d0, x1, d1, Y, d_out, tokens, G, R);
+  // bf16: in integers, and by gram_kernel only if the data turns out not to allow it (the flag behind the status word)
+  const bool exact = std::is_same<T, bf16_t>::value && exact_gram_fits(tokens, d0, d1, d_out);
+  int* const flag = status + 1;
+  zero_kernel<<<1024, 256, 0, stream>>>(reinterpret_cast<f64x2*>(G), (n_all + d + d_out) / 2 + 1);      // the whole workspace
+  if (exact)
+    if (const hipError_t e = launch_exact_gram(tokens, x0, d0, x1, d1, Y, d_out, G, mean, flag, stream)) return e;
+  gram_kernel<T><<<gram_grid(tiles), kGramWaves * 64, 0, stream>>>(x0, d0, x1, d1, Y, d_out, tokens, G, R, exact ? flag : nullptr);
   if (bias != nullptr) {       // intercept: regress the centred Y on the centred X
     column_mean_kernel<T><<<nb + nr, kFitThreads, 0, stream>>>(x0, d0, x1, d1, Y, d_out, tokens, mean);
     centre_kernel<<<(unsigned)((n_all + 255) / 256), 256, 0, stream>>>(G, R, mean, d, d_out, (double)tokens);

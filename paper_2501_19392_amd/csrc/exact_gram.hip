@@ -1,0 +1,441 @@
+// The Gram products of the least-squares fit (calibrate.hip) over bf16 data, exactly, on the 8-bit integer matrix cores.
+//
+// bf16 values have 8 significant bits, and those of one column mostly lie within a few powers of two of the largest one.  With the
+// column's unit set 13 binades below its largest exponent almost every value is an integer q of at most 22 bits, which three signed
+// digits of 8 bits hold: q = d0 + 2^8 d1 + 2^16 d2.  The nine digit products of two columns are summed in int32 by
+// v_mfma_i32_32x32x32_i8 and put together in int64, where no sum of up to 2^20 tokens rounds or overflows, and which comes out the same in any
+// order of additions.  Values more than 13 binades below their column's largest (of Gaussian columns 3 to 6 in 10000) are rounded to the
+// nearest q; what is left of them is listed per column and enters in fp64 with the single rounding of the sum (finish_kernel).  So the result is closer
+// to the exact one than a sum in fp64, whose every step rounds.  Where a list would overflow, or a column holds infinities, NaNs or nothing
+// but values too small to be scaled, a flag sends the whole product to the fp64 kernel of calibrate.hip.
+//
+// Nine 8-bit products at 64 times the rate of an fp64 one: a fit of 65536 tokens, 2048 inputs and 1024 outputs 9.20 -> 4.16 ms (Gram products
+// 8.1 -> 3.1 with everything around them), 65536 x 1024 inputs 3.58 -> 1.77, 16384 x 2048 3.13 -> 1.82, 4096 x 1024 0.72 -> 0.66.
+#include "device_utils.h"
+#include "kernels.h"
+
+namespace aquakv {
+namespace {
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+
+constexpr int kBinades = 13;                 // between the unit of a column and its largest exponent: |q| <= 255 << 13
+constexpr int kGramXcds = 8;
+
+// [x0 | x1 | Y] as one row of d + d_out columns; 128 neighbouring ones, from a multiple of 128, lie in one of the three
+struct Columns {
+  const bf16_t *x0, *x1, *Y;
+  int d0, d1, d_out;
+  __device__ __forceinline__ const bf16_t* at(int c, int& ld) const {
+    if (c < d0) { ld = d0; return x0 + c; }
+    c -= d0;
+    if (c < d1) { ld = d1; return x1 + c; }
+    ld = d_out;
+    return Y + (c - d1);
+  }
+};
+
+// The lists of a fit: entries of 4 bytes in the blocks of G above the diagonal ones, which hold nothing until the factorisation.  A row of
+// a 64 x 64 block is a piece of 128 entries; column c of n has pieces c, c + n, c + 2 n ...
+constexpr int kPieceEntries = 128, kMaxListed = 1024;
+__host__ __device__ __forceinline__ int listed_room(int d, int columns) {
+  const int nb = d / 64, pieces = nb * (nb - 1) / 2 * 64 / columns;
+  return pieces * kPieceEntries < kMaxListed ? pieces * kPieceEntries : kMaxListed;
+}
+__device__ __forceinline__ uint32_t* listed(double* G, int d, int columns, int c, int n) {
+  const int piece = c + n / kPieceEntries * columns, block = piece >> 6;
+  int bj = (int)((1.f + sqrtf(8.f * (float)block + 1.f)) * 0.5f);      // block column bj holds blocks bj (bj - 1) / 2 ...
+  while (bj * (bj - 1) / 2 > block) --bj;
+  while (bj * (bj + 1) / 2 <= block) ++bj;
+  const int bi = block - bj * (bj - 1) / 2;
+  return reinterpret_cast<uint32_t*>(G + (int64_t)(bi * 64 + (piece & 63)) * d + bj * 64) + n % kPieceEntries;
+}
+
+// A column's largest magnitude (the bits of the value without its sign) gives the exponent of its scale
+__device__ __forceinline__ int top_exponent(uint32_t largest) { return (int)(largest >> 7) > 1 ? (int)(largest >> 7) : 1; }
+__device__ __forceinline__ int scale_exponent(uint32_t largest) {      // q = value * 2^this
+  const int e = 134 + kBinades - top_exponent(largest);
+  return e < 127 ? e : 127;                                            // (only for columns of zeros: see list_kernel)
+}
+__device__ __forceinline__ float scale_of(uint32_t largest) { return __uint_as_float((uint32_t)(127 + scale_exponent(largest)) << 23); }
+// value * scale rounded to an integer, plus 2^23 + kDigits in the low bits of the float: bytes d0 + 128, d1 + 128, d2 + 64
+constexpr float kMagic = 8388608.f + 4227200.f;                        // 4227200 = 0x408080
+__device__ __forceinline__ float rounded(float value, float scale) { return __builtin_fmaf(value, scale, kMagic); }
+
+constexpr int kScanRows = 64;
+// one workgroup: 128 columns, 8 a lane, of kScanRows tokens in each of 16 strands
+template <typename F>
+__device__ __forceinline__ void scan(const Columns& x, int64_t tokens, F&& f) {
+  const int lane = threadIdx.x & 15, strand = threadIdx.x >> 4;        // 16 lanes x 8 columns, 16 strands of tokens
+  const int c = (int)blockIdx.x * 128 + lane * 8;
+  int ld;
+  const bf16_t* p = x.at((int)blockIdx.x * 128, ld) + lane * 8;
+  const int64_t t0 = (int64_t)blockIdx.y * (16 * kScanRows) + strand;
+  f(c, p, ld, t0);
+}
+
+// largest[c] = the largest magnitude of column c (zero before)
+__global__ __launch_bounds__(256) void largest_kernel(const Columns x, int64_t tokens, uint32_t* __restrict__ largest) {
+  __shared__ uint32_t most[16][128 + 4];
+  uint32_t m[8] = {};
+  scan(x, tokens, [&](int, const bf16_t* p, int ld, int64_t t0) {
+#pragma unroll 8
+    for (int n = 0; n < kScanRows; ++n) {
+      const int64_t t = t0 + n * 16 < tokens ? t0 + n * 16 : tokens - 1;
+      const u32x4 v = *reinterpret_cast<const u32x4*>(p + t * ld);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t lo = v[k] & 0x7fffu, hi = (v[k] >> 16) & 0x7fffu;
+        m[2 * k] = lo > m[2 * k] ? lo : m[2 * k];
+        m[2 * k + 1] = hi > m[2 * k + 1] ? hi : m[2 * k + 1];
+      }
+    }
+  });
+  const int lane = threadIdx.x & 15, strand = threadIdx.x >> 4;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) most[strand][lane * 8 + k] = m[k];
+  __syncthreads();
+  if (threadIdx.x < 128) {
+    uint32_t all = 0;
+    for (int s = 0; s < 16; ++s) all = most[s][threadIdx.x] > all ? most[s][threadIdx.x] : all;
+    atomicMax(&largest[blockIdx.x * 128 + threadIdx.x], all);
+  }
+}
+
+// The values that their q does not hold exactly, or may not: tokens to the column's list, in any order.  flag: the fp64 kernel's work.
+__global__ __launch_bounds__(256) void list_kernel(const Columns x, int64_t tokens, const uint32_t* __restrict__ largest,
+                                                   uint32_t* __restrict__ count, double* __restrict__ G, int* __restrict__ flag) {
+  const int d = x.d0 + x.d1, columns = d + x.d_out, room = listed_room(d, columns);
+  scan(x, tokens, [&](int c, const bf16_t* p, int ld, int64_t t0) {
+    uint32_t least[8];                                                 // magnitudes below, but zero, are listed
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const uint32_t m = largest[c + k];
+      const int e = top_exponent(m);
+      bad |= e == 255 || (m != 0 && 134 + kBinades - e > 127);
+      least[k] = (uint32_t)(e > kBinades ? e - kBinades : 0) << 7;
+    }
+    if (bad) *flag = 1;
+#pragma unroll 8
+    for (int n = 0; n < kScanRows; ++n) {
+      const int64_t t = t0 + n * 16;
+      const u32x4 v = *reinterpret_cast<const u32x4*>(p + (t < tokens ? t : tokens - 1) * ld);
+      bool any = false;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const uint32_t m = (k & 1 ? v[k >> 1] >> 16 : v[k >> 1]) & 0x7fffu;
+        any |= m < least[k] && m != 0;
+      }
+      if (any && t < tokens) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const uint32_t m = (k & 1 ? v[k >> 1] >> 16 : v[k >> 1]) & 0x7fffu;
+          if (m < least[k] && m != 0) {
+            const int at = (int)atomicAdd(&count[c + k], 1u);
+            if (at < room) *listed(G, d, columns, c + k, at) = (uint32_t)t;
+            else *flag = 1;
+          }
+        }
+      }
+    }
+  });
+}
+
+// Lists in the order of their tokens, so that the sums over them do not depend on the order of arrival: one workgroup per column
+__global__ __launch_bounds__(256) void sort_kernel(int d, int columns, const uint32_t* __restrict__ count, double* __restrict__ G,
+                                                   const int* __restrict__ flag) {
+  __shared__ uint32_t token[kMaxListed];
+  const int c = blockIdx.x, n = (int)count[c];
+  if (*flag != 0 || n < 2) return;                                     // (n is at most the room where the flag is not set)
+  for (int i = threadIdx.x; i < n; i += 256) token[i] = *listed(G, d, columns, c, i);
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += 256) {
+    int rank = 0;
+    for (int k = 0; k < n; ++k) rank += token[k] < token[i];
+    *listed(G, d, columns, c, rank) = token[i];
+  }
+}
+
+// ------------------------------------------------------------------ the products
+// 128 x 128 outputs per tile: the lower triangle of X^T X by blocks, then Y^T X, in bands of four block rows, column after column, so that
+// neighbouring tiles share their rows and columns.  Every XCD has an equal share of neighbouring tiles: its 32 workgroups take whole ones as
+// long as there are 32 and go through the tokens side by side, reading each column block once from beyond their L2; the tiles
+// left over are cut into 32 equal ranges of steps.  Sums are added to the zeroed output with integer atomics.
+//
+// Step: 64 tokens of the tile's 256 columns.  Wave w takes 16 tokens of 128 columns (two neighbouring ones per lane) from memory, a step
+// ahead, turns them into digits between the matrix instructions of the step before (2.4 instructions a value: one fma that scales and rounds, the bytes
+// of four tokens transposed) and stores them to LDS as the operands that the instructions read: 32 columns x 32 tokens of a digit are 1 KiB, lane l
+// column l % 32, tokens 16 (l / 32) ...; of 32 columns the even ones come first, which makes 16 lanes' stores contiguous.  Each of
+// the 8 waves (two per SIMD) multiplies 64 x 32 outputs: five accumulators (powers of 2^8) of two blocks, 160 registers, 36 instructions of 32 cycles.
+// int32 holds 65535 tokens of any digits: segments of at most kMaxSteps steps.
+constexpr int kExactThreads = 512, kStepTokens = 64, kMaxSteps = 512, kTile = 128;
+__device__ const uint32_t kZeros[64] = {};                             // the row of a token that is none
+constexpr int kUnit = 1024, kStageBytes = 2 * 4 * 3 * 2 * kUnit;       // operand, 32-column block, digit, 32 tokens
+
+__global__ __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void exact_gram_kernel(
+    const Columns x, int64_t tokens, const uint32_t* __restrict__ largest, double* __restrict__ G, const int* __restrict__ flag) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * kStageBytes];
+  if (*flag != 0) return;
+  const int d = x.d0 + x.d1;
+  const int nx = d / kTile, ny = x.d_out / kTile;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int steps = (int)((tokens + kStepTokens - 1) / kStepTokens);
+  const uint32_t lane4 = 4 * lane;
+  uint64_t zeros = reinterpret_cast<uint64_t>(kZeros);
+  asm("" : "+s"(zeros));                                              // held, not computed again at every use
+  const int wm = wave >> 2, wn = wave & 3;                             // multiplied: 64 rows, 32 columns
+  const int operand = wave >> 2, quarter = wave & 3;                   // converted: rows or columns of the tile, 16 tokens of a step
+  // where this lane's even column goes: unit (operand, lane / 16, digit, quarter / 2)
+  unsigned char* const put = smem + ((operand * 4 + (lane >> 4)) * 6 + (quarter >> 1)) * kUnit + (quarter & 1) * 512 + (lane & 15) * 16;
+  const unsigned char* const get_a = smem + wm * 2 * 6 * kUnit + lane * 16;
+  const unsigned char* const get_b = smem + (4 + wn) * 6 * kUnit + lane * 16;
+
+  const auto run = [&](int tile, int first, int last) {
+    int bi = 0, bj = 0;
+    {                                                                  // bands of four block rows, those of G first
+      const int n_sym = nx * (nx + 1) / 2;
+      int rest = tile < n_sym ? tile : tile - n_sym;
+      const int rows = tile < n_sym ? nx : ny, sym = tile < n_sym;
+      int band = 0;
+      for (;; band += 4) {
+        const int h = rows - band < 4 ? rows - band : 4;
+        const int n = sym ? h * band + h * (h + 1) / 2 : h * nx;
+        if (rest < n) break;
+        rest -= n;
+      }
+      const int h = rows - band < 4 ? rows - band : 4;
+      if (!sym || rest < h * band) {
+        bj = rest / h;
+        bi = band + rest % h;
+      } else {
+        rest -= h * band;
+        int col = 0;
+        while (rest >= h - col) { rest -= h - col; ++col; }
+        bj = band + col;
+        bi = band + col + rest;
+      }
+      if (!sym) bi += nx;
+    }
+    int ld;
+    const int c0 = (operand == 0 ? bi : bj) * kTile;
+    const uint64_t base = reinterpret_cast<uint64_t>(x.at(c0, ld));
+    const uint32_t row_bytes = (uint32_t)ld * sizeof(bf16_t);
+    const float scale0 = scale_of(largest[c0 + 2 * lane]), scale1 = scale_of(largest[c0 + 2 * lane + 1]);
+    const int end_token = last * kStepTokens < (int)tokens ? last * kStepTokens : (int)tokens;
+    uint32_t raw[16];
+    const auto load = [&](int s, int from, int n) {                    // rows from ... of a step's 16; behind the range and the tokens zeros
+      const int t0 = s * kStepTokens + quarter * 16 + from;
+      uint64_t row = base + (uint64_t)t0 * row_bytes;
+#pragma unroll
+      for (int r = 0; r < n; ++r) {
+        const uint64_t from_row = t0 + r < end_token ? row : zeros;
+        raw[from + r] = *reinterpret_cast<const uint32_t __attribute__((address_space(1)))*>(from_row + lane4);
+        row += row_bytes;
+      }
+    };
+    // digits of tokens 4 g ... : one word of each digit for both columns
+    const auto convert = [&](int g, u32x4 (&out)[2][3]) {
+      const uint32_t* const r = raw + 4 * g;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        uint32_t w[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          w[k] = __float_as_uint(rounded(__uint_as_float(e ? r[k] & 0xffff0000u : r[k] << 16), e ? scale1 : scale0));
+        const uint32_t lo01 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), lo23 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+        const uint32_t hi = __builtin_amdgcn_perm(w[1], w[0], 0x0c0c0602u) | __builtin_amdgcn_perm(w[3], w[2], 0x06020c0cu);
+        out[e][0][g] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u) ^ 0x80808080u;
+        out[e][1][g] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u) ^ 0x80808080u;
+        out[e][2][g] = (hi + 0x40404040u) ^ 0x80808080u;               // (bytes of 32 to 96: no carry)
+      }
+    };
+    const auto store = [&](int stage, const u32x4 (&out)[2][3]) {
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x4*>(put + stage * kStageBytes + p * 2 * kUnit + e * 256) = out[e][p];
+    };
+    const auto barrier = [] {                                          // this wave's LDS accesses are done; loads stay in flight
+      __builtin_amdgcn_s_waitcnt(0xc07f);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    };
+    i32x16 acc[2][5];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int o = 0; o < 5; ++o)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[m][o][e] = 0;
+
+    {
+      u32x4 out[2][3];
+      load(first, 0, 16);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) convert(g, out);
+      store(0, out);
+      load(first + 1, 0, 16);
+    }
+    barrier();
+    int stage = 0;
+    for (int s = first; s < last; ++s) {
+      u32x4 out[2][3];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        i32x4 a[2][3], b[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          b[p] = *reinterpret_cast<const i32x4*>(get_b + stage * kStageBytes + (p * 2 + kb) * kUnit);
+#pragma unroll
+          for (int m = 0; m < 2; ++m)
+            a[m][p] = *reinterpret_cast<const i32x4*>(get_a + stage * kStageBytes + ((m * 3 + p) * 2 + kb) * kUnit);
+        }
+#pragma unroll
+        for (int n = 0; n < 9; ++n) {
+          const int pa = n / 3, pb = n % 3;
+#pragma unroll
+          for (int m = 0; m < 2; ++m) acc[m][pa + pb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[m][pa], b[pb], acc[m][pa + pb], 0, 0, 0);
+          if (n == 3 || n == 6) {
+            const int g = 2 * kb + (n == 6);
+            convert(g, out);
+            load(s + 2, 4 * g, 4);
+          }
+        }
+      }
+      store(stage ^ 1, out);
+      stage ^= 1;
+      barrier();
+    }
+
+    // sums: register r of lane l is row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32 of a block, in the order the columns were put in
+    if (!(bi < nx && bj * 2 + (wn >> 1) > bi * 2 + wm)) {              // (above the diagonal: nothing is kept there, but lists)
+      const auto placed = [](int p) { return 2 * (p & 15) + (p >> 4); };
+      unsigned long long* const to = reinterpret_cast<unsigned long long*>(G) + (int64_t)(bi * kTile + wm * 64) * d + bj * kTile + wn * 32 + placed(lane & 31);
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          long long v = acc[m][4][r];
+#pragma unroll
+          for (int o = 3; o >= 0; --o) v = v * 256 + acc[m][o][r];
+          const int row = placed(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3));
+          __hip_atomic_fetch_add(to + (int64_t)(m * 32 + row) * d, (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+  };
+  const int n_all = nx * (nx + 1) / 2 + nx * ny;
+  const int xcd = blockIdx.x % kGramXcds, w = blockIdx.x / kGramXcds, per = gridDim.x / kGramXcds;
+  const int first = n_all * xcd / kGramXcds, n = n_all * (xcd + 1) / kGramXcds - first, whole = n / per * per;
+  const int64_t left = (int64_t)(n - whole) * steps, end = left * (w + 1) / per;
+  int64_t at = left * w / per;
+  for (int i = w; i < whole || at < end;) {
+    int tile = first + i, s = 0, last = steps;
+    if (i < whole) {
+      i += per;
+    } else {
+      tile = first + whole + (int)(at / steps);
+      s = (int)(at % steps);
+      last = end - at < steps - s ? s + (int)(end - at) : steps;
+      at += last - s;
+    }
+    for (; s < last; s += kMaxSteps) run(tile, s, last - s < kMaxSteps ? last : s + kMaxSteps);
+  }
+}
+
+// Integer sums -> fp64, with what the lists hold: in units of the two columns, value = q + r, the sum over tokens of
+// value_i value_j is that of q_i q_j (exact), of r_i value_j over i's list and of q_i r_j over j's list.  One workgroup per 64 x 64 block, as in
+// gram_kernel (calibrate.hip); a wave has 4 rows, a lane one column.
+constexpr int kFinishRows = 4;
+__global__ __launch_bounds__(1024) void finish_kernel(const Columns x, const uint32_t* __restrict__ largest, const uint32_t* __restrict__ count,
+                                                      double* G, const int* __restrict__ flag) {
+  if (*flag != 0) return;
+  const int d = x.d0 + x.d1, columns = d + x.d_out, nd = d / 64;
+  int tile = blockIdx.x, bi = 0, bj;
+  if (tile >= nd * (nd + 1) / 2) {
+    tile -= nd * (nd + 1) / 2;
+    bi = nd + tile / nd; bj = tile % nd;
+  } else {
+    while (tile > bi) { tile -= bi + 1; ++bi; }
+    bj = tile;
+  }
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i0 = bi * 64 + wave * kFinishRows, j = bj * 64 + lane;
+  int ldi, ldj;
+  const bf16_t* const pi = x.at(i0 & ~127, ldi) + (i0 & 127);
+  const bf16_t* const pj = x.at(bj * 64 & ~127, ldj) + (bj * 64 & 127) + lane;
+  const int ej = scale_exponent(largest[j]);
+  const float sj = scale_of(largest[j]);
+  const auto parts = [](float v, float scale, int e, double& q, double& r) {
+    q = (double)(rounded(v, scale) - kMagic);
+    r = ldexp((double)v, e) - q;
+  };
+  double corr[kFinishRows];
+#pragma unroll
+  for (int n = 0; n < kFinishRows; ++n) {
+    const int i = i0 + n, ei = scale_exponent(largest[i]), listed_i = (int)count[i];
+    const float si = scale_of(largest[i]);
+    double sum = 0.0;
+    for (int k0 = 0; k0 < listed_i; k0 += 64) {                        // a lane fetches an entry, all lanes go through them
+      const int k = k0 + lane < listed_i ? k0 + lane : listed_i - 1;
+      const int t = (int)*listed(G, d, columns, i, k);
+      double q, r;
+      parts((float)pi[(int64_t)t * ldi + n], si, ei, q, r);
+      const float r32 = (float)r;                                      // |r| <= 1/2 with at most 8 significant bits
+      const int m = listed_i - k0 < 64 ? listed_i - k0 : 64;
+      for (int l = 0; l < m; ++l) {
+        const int tl = __builtin_amdgcn_readlane(t, l);
+        const float rl = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(r32), l));
+        sum += (double)rl * ldexp((double)(float)pj[(int64_t)tl * ldj], ej);
+      }
+    }
+    corr[n] = sum;
+  }
+  const int listed_j = (int)count[j];
+  for (int k = 0; k < listed_j; ++k) {
+    const int64_t t = *listed(G, d, columns, j, k);
+    double qj, rj;
+    parts((float)pj[t * ldj], sj, ej, qj, rj);
+#pragma unroll
+    for (int n = 0; n < kFinishRows; ++n) {
+      double q, r;
+      parts((float)pi[t * ldi + n], scale_of(largest[i0 + n]), 0, q, r);
+      corr[n] += q * rj;
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < kFinishRows; ++n) {
+    double* const o = G + (int64_t)(i0 + n) * d + j;
+    const double sum = (double)*reinterpret_cast<const long long*>(o) + corr[n];
+    *o = ldexp(sum, -scale_exponent(largest[i0 + n]) - ej);
+  }
+}
+
+}  // namespace
+
+// Columns in whole tiles of 128, room for lists at all (none below 256 inputs), and as many tokens as int64 sums hold.  Fewer than 256 tokens
+// are not worth the launches around the product.
+bool exact_gram_fits(int64_t tokens, int d0, int d1, int d_out) {
+  return tokens >= 256 && tokens <= (1 << 20) && d0 % kTile == 0 && d1 % kTile == 0 && d_out % kTile == 0 &&
+         listed_room(d0 + d1, d0 + d1 + d_out) > 0;
+}
+
+hipError_t launch_exact_gram(int64_t tokens, const void* x0, int d0, const void* x1, int d1, const void* Y, int d_out, double* G, void* columns,
+                             int* flag, hipStream_t stream) {
+  const Columns x = {static_cast<const bf16_t*>(x0), static_cast<const bf16_t*>(x1), static_cast<const bf16_t*>(Y), d0, d1, d_out};
+  const int d = d0 + d1, all = d + d_out;
+  uint32_t* const largest = static_cast<uint32_t*>(columns);
+  uint32_t* const count = largest + all;
+  const dim3 grid(all / 128, (unsigned)((tokens + 16 * kScanRows - 1) / (16 * kScanRows)));
+  largest_kernel<<<grid, 256, 0, stream>>>(x, tokens, largest);
+  list_kernel<<<grid, 256, 0, stream>>>(x, tokens, largest, count, G, flag);
+  sort_kernel<<<all, 256, 0, stream>>>(d, all, count, G, flag);
+  exact_gram_kernel<<<256, kExactThreads, 0, stream>>>(x, tokens, largest, G, flag);
+  const int nd = d / 64;
+  finish_kernel<<<nd * (nd + 1) / 2 + nd * (d_out / 64), 1024, 0, stream>>>(x, largest, count, G, flag);
+  return hipGetLastError();
+}
+
+}  // namespace aquakv

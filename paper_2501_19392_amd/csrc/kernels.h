@@ -221,6 +221,13 @@ hipError_t launch_fit_predictor(int dtype, int64_t tokens, const void* x0, int d
                                 int d_out, double rate, void* W, double* W64, float* bias, void* workspace,
                                 hipStream_t stream);
 
+// The Gram products of a fit over bf16 data in integers (exact_gram.hip): blocks of G [d0 + d1 + d_out, d0 + d1] on and below the diagonal, the
+// others are scratch.  G, flag and 8 bytes per column of [x0 | x1 | Y] at `columns` are zero before.  flag != 0 after: G's blocks on and below
+// the diagonal are still zero.
+bool exact_gram_fits(int64_t tokens, int d0, int d1, int d_out);
+hipError_t launch_exact_gram(int64_t tokens, const void* x0, int d0, const void* x1, int d1, const void* Y, int d_out, double* G, void* columns,
+                             int* flag, hipStream_t stream);
+
 // Device-to-device copies of n byte ranges, kCopyRangesPerLaunch per launch (3 KiB of kernel arguments).
 struct CopyRange { void* dst; const void* src; size_t bytes; };
 constexpr int kCopyRangesPerLaunch = 128;

@@ -38,3 +38,65 @@ def test_fit_at_step_and_tile_edges(dtype, T, d0, d1, d_out):
     want = C.fit_predictor(U.np64(X), U.np64(Y), 1e-2)
     rel = np.linalg.norm(got - want) / np.linalg.norm(want)
     assert rel < 1e-9, rel
+
+
+def _columns(kind, T, d, g):
+    """bf16 data of kinds that the integer form of the Gram products treats differently."""
+    x = torch.randn(T, d, generator=g)
+    if kind == "spread":                                       # every column has values 13 and more binades below its largest
+        n = min(T, 40)
+        rows = torch.randperm(T, generator=g)[:n]
+        x[rows] *= torch.exp2(torch.randint(-30, -8, (n, d), generator=g).float())
+        x[:, 5] = 0.0
+    elif kind == "many small":                                 # more such values than the lists hold: the fp64 form
+        x[1:, : d // 2] *= 2.0 ** -20
+    elif kind == "tiny column":                                # no fp32 scale takes its values to integers: the fp64 form
+        x[:, 3] *= 2.0 ** -118
+    return x.to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("kind", ["gauss", "spread", "many small", "tiny column"])
+@pytest.mark.parametrize("T,d0,d1,d_out", [
+    (256, 256, 0, 128), (257, 128, 128, 128), (319, 256, 128, 128), (1025, 512, 512, 256), (4097, 128, 384, 384), (2048, 1024, 1024, 1024),
+    (32769, 256, 0, 128)])
+def test_fit_from_integer_products(T, d0, d1, d_out, kind):
+    """Edges of the steps of 64 tokens, of the 512 steps that int32 sums hold and of the 32 workgroups of an XCD.  The Gram products are
+    exact but for one rounding each (their fp64 form: T), so the solution is off by the condition number, below 1e5 for these data, times 2^-53
+    times the order of the matrix, 2e-8 at worst; 1e-9 is asked, as of the fp64 form above."""
+    from paper_2501_19392_amd import binding as B
+    print(f"case fit integer T={T} d0={d0} d1={d1} d_out={d_out} {kind}", flush=True)
+    d = d0 + d1
+    g = torch.Generator().manual_seed(T + d)
+    X, Y = _columns(kind, T, d, g), _columns("spread" if kind == "spread" else "gauss", T, d_out, g)
+    x1 = X[:, d0:].contiguous().cuda() if d1 else None
+    W = torch.empty(d_out, d, dtype=torch.bfloat16, device="cuda")
+    W64 = torch.empty(d_out, d, dtype=torch.float64, device="cuda")
+    ws = torch.empty(B.aquakv_fit_workspace_bytes(d, d_out), dtype=torch.uint8, device="cuda")
+    bias = torch.empty(d_out, dtype=torch.float32, device="cuda") if d1 else None
+    first = None
+    for _ in range(2):
+        ws.fill_(0xff)
+        B.aquakv_fit_predictor(torch.bfloat16, T, X[:, :d0].contiguous().cuda(), d0, x1, d1, Y.cuda(), d_out, 1e-2, W, W64, ws, bias=bias)
+        torch.cuda.synchronize()
+        got = W64.cpu().numpy()
+        assert first is None or np.array_equal(first, got)
+        first = got
+    want = C.fit_predictor(U.np64(X), U.np64(Y), 1e-2, bias=bias is not None)
+    if bias is not None:
+        want, want_b = want
+        assert np.allclose(bias.cpu().numpy(), want_b, rtol=1e-5, atol=1e-6 * np.abs(want_b).max() + 1e-7)
+    rel = np.linalg.norm(got - want) / np.linalg.norm(want)
+    print("rel", rel, flush=True)
+    assert rel < 1e-9, rel
+
+
+def test_fit_of_infinities_is_nan_in_both_forms():
+    from paper_2501_19392_amd import binding as B
+    T, d, d_out = 512, 256, 128
+    g = torch.Generator().manual_seed(3)
+    X, Y = torch.randn(T, d, generator=g).bfloat16().cuda(), torch.randn(T, d_out, generator=g).bfloat16().cuda()
+    W = torch.zeros(d_out, d, dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(B.aquakv_fit_workspace_bytes(d, d_out), dtype=torch.uint8, device="cuda")
+    X[7, 9] = float("inf")
+    B.aquakv_fit_predictor(torch.bfloat16, T, X, d, None, 0, Y, d_out, 1e-2, W, None, ws)
+    assert W.isnan().all()
