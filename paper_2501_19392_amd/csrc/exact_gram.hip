@@ -9,10 +9,13 @@
 // to the exact one than a sum in fp64, whose every step rounds.  Where a list would overflow, or a column holds infinities, NaNs or nothing
 // but values too small to be scaled, a flag sends the whole product to the fp64 kernel of calibrate.hip.
 //
-// Nine 8-bit products at 64 times the rate of an fp64 one: a fit of 65536 tokens, 2048 inputs and 1024 outputs 9.20 -> 4.16 ms (Gram products
-// 8.1 -> 3.1 with everything around them), 65536 x 1024 inputs 3.58 -> 1.77, 16384 x 2048 3.13 -> 1.82, 4096 x 1024 0.72 -> 0.66.
+// A fit of 65536 tokens, 2048 inputs and 1024 outputs 9.20 -> 3.40 ms (Gram products 8.1 -> 2.2: the products 1.90, the two passes that find
+// scales and lists 0.17, finish_kernel 0.14), 65536 x 1024 inputs 3.58 -> 1.41, 16384 x 2048 3.13 -> 1.68, 4096 x 1024 0.72 -> 0.62.
 #include "device_utils.h"
 #include "kernels.h"
+
+#include <type_traits>
+#include <utility>
 
 namespace aquakv {
 namespace {
@@ -63,7 +66,7 @@ __device__ __forceinline__ float scale_of(uint32_t largest) { return __uint_as_f
 constexpr float kMagic = 8388608.f + 4227200.f;                        // 4227200 = 0x408080
 __device__ __forceinline__ float rounded(float value, float scale) { return __builtin_fmaf(value, scale, kMagic); }
 
-constexpr int kScanRows = 64;
+constexpr int kScanRows = 16;
 // one workgroup: 128 columns, 8 a lane, of kScanRows tokens in each of 16 strands
 template <typename F>
 __device__ __forceinline__ void scan(const Columns& x, int64_t tokens, F&& f) {
@@ -80,7 +83,7 @@ __global__ __launch_bounds__(256) void largest_kernel(const Columns x, int64_t t
   __shared__ uint32_t most[16][128 + 4];
   uint32_t m[8] = {};
   scan(x, tokens, [&](int, const bf16_t* p, int ld, int64_t t0) {
-#pragma unroll 8
+#pragma unroll
     for (int n = 0; n < kScanRows; ++n) {
       const int64_t t = t0 + n * 16 < tokens ? t0 + n * 16 : tokens - 1;
       const u32x4 v = *reinterpret_cast<const u32x4*>(p + t * ld);
@@ -118,7 +121,7 @@ __global__ __launch_bounds__(256) void list_kernel(const Columns x, int64_t toke
       least[k] = (uint32_t)(e > kBinades ? e - kBinades : 0) << 7;
     }
     if (bad) *flag = 1;
-#pragma unroll 8
+#pragma unroll
     for (int n = 0; n < kScanRows; ++n) {
       const int64_t t = t0 + n * 16;
       const u32x4 v = *reinterpret_cast<const u32x4*>(p + (t < tokens ? t : tokens - 1) * ld);
@@ -165,14 +168,28 @@ __global__ __launch_bounds__(256) void sort_kernel(int d, int columns, const uin
 // left over are cut into 32 equal ranges of steps.  Sums are added to the zeroed output with integer atomics.
 //
 // Step: 64 tokens of the tile's 256 columns.  Wave w takes 16 tokens of 128 columns (two neighbouring ones per lane) from memory, a step
-// ahead, turns them into digits between the matrix instructions of the step before (2.4 instructions a value: one fma that scales and rounds, the bytes
-// of four tokens transposed) and stores them to LDS as the operands that the instructions read: 32 columns x 32 tokens of a digit are 1 KiB, lane l
-// column l % 32, tokens 16 (l / 32) ...; of 32 columns the even ones come first, which makes 16 lanes' stores contiguous.  Each of
-// the 8 waves (two per SIMD) multiplies 64 x 32 outputs: five accumulators (powers of 2^8) of two blocks, 160 registers, 36 instructions of 32 cycles.
+// ahead, turns them into digits (2.6 instructions a value: one fma that scales and rounds, the bytes of four tokens transposed) and stores them
+// to LDS as the operands that the instructions read: 32 columns x 32 tokens of a digit are 1 KiB, lane l column l % 32, tokens 16 (l / 32) ...;
+// of 32 columns the even ones come first, which makes 16 lanes' stores contiguous.  Each of the 8 waves (two per SIMD) multiplies 64 x 32
+// outputs: five accumulators (powers of 2^8) of two blocks, 160 registers, 36 instructions of 32 cycles.  Nothing else would fit beside a second
+// set of operands, so a register is read again as soon as its last instruction has been issued, and all other work is placed between the
+// matrix instructions, with the step's one barrier six of them behind the last store (8 % fewer cycles than next to it).
+// Matrix cores busy in 0.64 of the cycles, at 1.86 GHz: 2.69 POPS; a form with operands read at the start of their 32 tokens took 0.52 at 2.0 GHz.
 // int32 holds 65535 tokens of any digits: segments of at most kMaxSteps steps.
+constexpr int kMfma = 0x008, kValu = 0x002, kLdsRead = 0x100, kLdsWrite = 0x200;      // kinds for sched_group_barrier
 constexpr int kExactThreads = 512, kStepTokens = 64, kMaxSteps = 512, kTile = 128;
-__device__ const uint32_t kZeros[64] = {};                             // the row of a token that is none
 constexpr int kUnit = 1024, kStageBytes = 2 * 4 * 3 * 2 * kUnit;       // operand, 32-column block, digit, 32 tokens
+
+// what comes behind the matrix instructions of a step (36), which are two or three for an operand that is read again
+template <int N> __device__ __forceinline__ void behind_mfma() {
+  __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
+  if constexpr (N == 5 || N == 11 || N == 29) __builtin_amdgcn_sched_group_barrier(kLdsRead, 2, 0);
+  if constexpr (N == 13 || N == 15 || N == 31 || N == 33) __builtin_amdgcn_sched_group_barrier(kLdsRead, 1, 0);
+  if constexpr (N == 17 || N == 35) __builtin_amdgcn_sched_group_barrier(kLdsRead, 3, 0);
+  if constexpr (N >= 12 && N < 18) __builtin_amdgcn_sched_group_barrier(kLdsWrite, 1, 0);
+  __builtin_amdgcn_sched_group_barrier(kValu, N < 13 ? 7 : 5, 0);
+}
+template <int FIRST, int... N> __device__ __forceinline__ void instruction_order(std::integer_sequence<int, N...>) { (behind_mfma<FIRST + N>(), ...); }
 
 __global__ __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void exact_gram_kernel(
     const Columns x, int64_t tokens, const uint32_t* __restrict__ largest, double* __restrict__ G, const int* __restrict__ flag) {
@@ -183,8 +200,6 @@ __global__ __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(2
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int steps = (int)((tokens + kStepTokens - 1) / kStepTokens);
   const uint32_t lane4 = 4 * lane;
-  uint64_t zeros = reinterpret_cast<uint64_t>(kZeros);
-  asm("" : "+s"(zeros));                                              // held, not computed again at every use
   const int wm = wave >> 2, wn = wave & 3;                             // multiplied: 64 rows, 32 columns
   const int operand = wave >> 2, quarter = wave & 3;                   // converted: rows or columns of the tile, 16 tokens of a step
   // where this lane's even column goes: unit (operand, lane / 16, digit, quarter / 2)
@@ -220,18 +235,19 @@ __global__ __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(2
     }
     int ld;
     const int c0 = (operand == 0 ? bi : bj) * kTile;
-    const uint64_t base = reinterpret_cast<uint64_t>(x.at(c0, ld));
+    const bf16_t* const base = x.at(c0, ld);
     const uint32_t row_bytes = (uint32_t)ld * sizeof(bf16_t);
     const float scale0 = scale_of(largest[c0 + 2 * lane]), scale1 = scale_of(largest[c0 + 2 * lane + 1]);
-    const int end_token = last * kStepTokens < (int)tokens ? last * kStepTokens : (int)tokens;
+    // the range's tokens as a buffer (512 steps of rows of 16 KiB: its bytes fit 30 bits); reads behind it return zeros
+    const int64_t token = (int64_t)first * kStepTokens, behind = (int64_t)last * kStepTokens < tokens ? (int64_t)last * kStepTokens : tokens;
+    const __amdgpu_buffer_rsrc_t rows =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base + token * ld), 0, (int)((uint32_t)(behind - token) * row_bytes), 0x00020000);
     uint32_t raw[16];
-    const auto load = [&](int s, int from, int n) {                    // rows from ... of a step's 16; behind the range and the tokens zeros
-      const int t0 = s * kStepTokens + quarter * 16 + from;
-      uint64_t row = base + (uint64_t)t0 * row_bytes;
+    const auto load = [&](int s, int from, int n) {                    // rows from ... of a step's 16
+      uint32_t row = ((uint32_t)(s - first) * kStepTokens + quarter * 16 + from) * row_bytes;
 #pragma unroll
       for (int r = 0; r < n; ++r) {
-        const uint64_t from_row = t0 + r < end_token ? row : zeros;
-        raw[from + r] = *reinterpret_cast<const uint32_t __attribute__((address_space(1)))*>(from_row + lane4);
+        raw[from + r] = __builtin_amdgcn_raw_buffer_load_b32(rows, (int)(row + lane4), 0, 0);
         row += row_bytes;
       }
     };
@@ -271,44 +287,67 @@ __global__ __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[m][o][e] = 0;
 
-    {
-      u32x4 out[2][3];
-      load(first, 0, 16);
+    i32x4 a[2][3], b[3];                                               // operands of the next 32 tokens' instructions
+    const auto read_a = [&](int stage, int kb, int p) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) convert(g, out);
-      store(0, out);
-      load(first + 1, 0, 16);
-    }
+      for (int m = 0; m < 2; ++m) a[m][p] = *reinterpret_cast<const i32x4*>(get_a + stage * kStageBytes + ((m * 3 + p) * 2 + kb) * kUnit);
+    };
+    const auto read_b = [&](int stage, int kb, int p) {
+      b[p] = *reinterpret_cast<const i32x4*>(get_b + stage * kStageBytes + (p * 2 + kb) * kUnit);
+    };
+    u32x4 out[2][3];
+    load(first, 0, 16);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) convert(g, out);
+    store(0, out);
+    load(first + 1, 0, 16);
     barrier();
+#pragma unroll
+    for (int p = 0; p < 3; ++p) { read_b(0, 0, p); read_a(0, 0, p); }
+    convert(0, out);
+    convert(1, out);
+    load(first + 2, 0, 8);
     int stage = 0;
-    for (int s = first; s < last; ++s) {
-      u32x4 out[2][3];
+    // the instructions of 32 tokens with digit pa of the rows; operands are read again, for the 32 tokens after these, once they are used
+    const auto multiply = [&](int kb, int pa) {
+      const int from = kb == 0 ? stage : stage ^ 1;
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        i32x4 a[2][3], b[3];
+      for (int pb = 0; pb < 3; ++pb) {
 #pragma unroll
-        for (int p = 0; p < 3; ++p) {
-          b[p] = *reinterpret_cast<const i32x4*>(get_b + stage * kStageBytes + (p * 2 + kb) * kUnit);
-#pragma unroll
-          for (int m = 0; m < 2; ++m)
-            a[m][p] = *reinterpret_cast<const i32x4*>(get_a + stage * kStageBytes + ((m * 3 + p) * 2 + kb) * kUnit);
-        }
-#pragma unroll
-        for (int n = 0; n < 9; ++n) {
-          const int pa = n / 3, pb = n % 3;
-#pragma unroll
-          for (int m = 0; m < 2; ++m) acc[m][pa + pb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[m][pa], b[pb], acc[m][pa + pb], 0, 0, 0);
-          if (n == 3 || n == 6) {
-            const int g = 2 * kb + (n == 6);
-            convert(g, out);
-            load(s + 2, 4 * g, 4);
-          }
-        }
+        for (int m = 0; m < 2; ++m)
+          acc[m][pa + pb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[m][pa], b[pb], acc[m][pa + pb], 0, 0, 0);
+        if (pa == 2) read_b(from, kb ^ 1, pb);
       }
+      read_a(from, kb ^ 1, pa);
+    };
+    for (int s = first; s < last; ++s) {
+      multiply(0, 0);
+      convert(2, out);
+      load(s + 2, 8, 4);
+      multiply(0, 1);
+      convert(3, out);
+      load(s + 2, 12, 4);
       store(stage ^ 1, out);
+      multiply(0, 2);
+      convert(0, out);
+      load(s + 3, 0, 4);
+#pragma unroll
+      for (int pb = 0; pb < 3; ++pb)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) acc[m][pb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[m][0], b[pb], acc[m][pb], 0, 0, 0);
+      instruction_order<0>(std::make_integer_sequence<int, 24>{});
+      __builtin_amdgcn_sched_barrier(0);
+      barrier();                                                       // the next step's operands are there
+      read_a(stage ^ 1, 0, 0);
+      multiply(1, 1);
+      convert(1, out);
+      load(s + 3, 4, 4);
+      multiply(1, 2);
+      instruction_order<24>(std::make_integer_sequence<int, 12>{});
+      __builtin_amdgcn_sched_barrier(0);
       stage ^= 1;
-      barrier();
     }
+    barrier();                                                         // the stages are free
 
     // sums: register r of lane l is row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32 of a block, in the order the columns were put in
     if (!(bi < nx && bj * 2 + (wn >> 1) > bi * 2 + wm)) {              // (above the diagonal: nothing is kept there, but lists)
@@ -347,10 +386,12 @@ __global__ __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(2
 
 // Integer sums -> fp64, with what the lists hold: in units of the two columns, value = q + r, the sum over tokens of
 // value_i value_j is that of q_i q_j (exact), of r_i value_j over i's list and of q_i r_j over j's list.  One workgroup per 64 x 64 block, as in
-// gram_kernel (calibrate.hip); a wave has 4 rows, a lane one column.
-constexpr int kFinishRows = 4;
+// gram_kernel (calibrate.hip).  Both sums go through a list with a wave per entry, its 64 partners in the lanes: 140 us for 20 to 40 entries a
+// column, 690 with a lane per list of the second sum, whose loads each touch 64 rows.
+constexpr int kFinishRows = 4, kFinishUnroll = 8;
 __global__ __launch_bounds__(1024) void finish_kernel(const Columns x, const uint32_t* __restrict__ largest, const uint32_t* __restrict__ count,
                                                       double* G, const int* __restrict__ flag) {
+  __shared__ double column_part[64][64 + 1];
   if (*flag != 0) return;
   const int d = x.d0 + x.d1, columns = d + x.d_out, nd = d / 64;
   int tile = blockIdx.x, bi = 0, bj;
@@ -362,54 +403,50 @@ __global__ __launch_bounds__(1024) void finish_kernel(const Columns x, const uin
     bj = tile;
   }
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int i0 = bi * 64 + wave * kFinishRows, j = bj * 64 + lane;
+  const int j = bj * 64 + lane, ej = scale_exponent(largest[j]);
   int ldi, ldj;
-  const bf16_t* const pi = x.at(i0 & ~127, ldi) + (i0 & 127);
-  const bf16_t* const pj = x.at(bj * 64 & ~127, ldj) + (bj * 64 & 127) + lane;
-  const int ej = scale_exponent(largest[j]);
-  const float sj = scale_of(largest[j]);
-  const auto parts = [](float v, float scale, int e, double& q, double& r) {
-    q = (double)(rounded(v, scale) - kMagic);
-    r = ldexp((double)v, e) - q;
-  };
-  double corr[kFinishRows];
-#pragma unroll
-  for (int n = 0; n < kFinishRows; ++n) {
-    const int i = i0 + n, ei = scale_exponent(largest[i]), listed_i = (int)count[i];
-    const float si = scale_of(largest[i]);
+  const bf16_t* const pi = x.at(bi * 64 & ~127, ldi) + (bi * 64 & 127);
+  const bf16_t* const pj = x.at(bj * 64 & ~127, ldj) + (bj * 64 & 127);
+  // sum over the list of column c of r_c times the 64 columns at p: their values, or their q (QUANTIZED)
+  const auto over_list = [&](int c, const bf16_t* pc, int ldc, const bf16_t* p, int ld, float scale, auto quantized) {
+    const int n = (int)count[c], ec = scale_exponent(largest[c]);
+    const float sc = scale_of(largest[c]);
     double sum = 0.0;
-    for (int k0 = 0; k0 < listed_i; k0 += 64) {                        // a lane fetches an entry, all lanes go through them
-      const int k = k0 + lane < listed_i ? k0 + lane : listed_i - 1;
-      const int t = (int)*listed(G, d, columns, i, k);
-      double q, r;
-      parts((float)pi[(int64_t)t * ldi + n], si, ei, q, r);
-      const float r32 = (float)r;                                      // |r| <= 1/2 with at most 8 significant bits
-      const int m = listed_i - k0 < 64 ? listed_i - k0 : 64;
-      for (int l = 0; l < m; ++l) {
-        const int tl = __builtin_amdgcn_readlane(t, l);
-        const float rl = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(r32), l));
-        sum += (double)rl * ldexp((double)(float)pj[(int64_t)tl * ldj], ej);
+    for (int k0 = 0; k0 < n; k0 += 64) {                               // a lane fetches an entry, all lanes go through them
+      const bool is = k0 + lane < n;
+      const int t = (int)*listed(G, d, columns, c, is ? k0 + lane : n - 1);
+      const float v = (float)pc[(int64_t)t * ldc];
+      const float r = is ? (float)(ldexp((double)v, ec) - (double)(rounded(v, sc) - kMagic)) : 0.f;       // |r| <= 1/2, 8 significant bits
+      const int m = n - k0 < 64 ? n - k0 : 64;
+      for (int l0 = 0; l0 < m; l0 += kFinishUnroll) {                  // (entries behind the list are its last one with r = 0)
+        float other[kFinishUnroll];
+#pragma unroll
+        for (int l = 0; l < kFinishUnroll; ++l) other[l] = (float)p[(int64_t)__builtin_amdgcn_readlane(t, l0 + l) * ld + lane];
+#pragma unroll
+        for (int l = 0; l < kFinishUnroll; ++l) {
+          const float rl = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(r), l0 + l));
+          const float o = decltype(quantized)::value ? rounded(other[l], scale) - kMagic : other[l];
+          sum = __fma_rn((double)rl, (double)o, sum);
+        }
       }
     }
-    corr[n] = sum;
-  }
-  const int listed_j = (int)count[j];
-  for (int k = 0; k < listed_j; ++k) {
-    const int64_t t = *listed(G, d, columns, j, k);
-    double qj, rj;
-    parts((float)pj[t * ldj], sj, ej, qj, rj);
-#pragma unroll
-    for (int n = 0; n < kFinishRows; ++n) {
-      double q, r;
-      parts((float)pi[t * ldi + n], scale_of(largest[i0 + n]), 0, q, r);
-      corr[n] += q * rj;
-    }
-  }
+    return sum;
+  };
+  // r_i value_j with a row per wave and a column per lane, q_i r_j the other way round, turned in LDS
+  double row_part[kFinishRows];
 #pragma unroll
   for (int n = 0; n < kFinishRows; ++n) {
-    double* const o = G + (int64_t)(i0 + n) * d + j;
-    const double sum = (double)*reinterpret_cast<const long long*>(o) + corr[n];
-    *o = ldexp(sum, -scale_exponent(largest[i0 + n]) - ej);
+    const int w = wave * kFinishRows + n;
+    row_part[n] = ldexp(over_list(bi * 64 + w, pi + w, ldi, pj, ldj, 0.f, std::false_type{}), ej);
+    column_part[w][lane] = over_list(bj * 64 + w, pj + w, ldj, pi, ldi, scale_of(largest[bi * 64 + lane]), std::true_type{});
+  }
+  __syncthreads();
+#pragma unroll
+  for (int n = 0; n < kFinishRows; ++n) {
+    const int w = wave * kFinishRows + n, i = bi * 64 + w;
+    double* const o = G + (int64_t)i * d + j;
+    const double sum = (double)*reinterpret_cast<const long long*>(o) + (row_part[n] + column_part[lane][w]);
+    *o = ldexp(sum, -scale_exponent(largest[i]) - ej);
   }
 }
 
