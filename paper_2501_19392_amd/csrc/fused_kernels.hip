@@ -373,7 +373,7 @@ hipError_t launch(int n_codewords, const void* x0, int d0, const void* x1, int d
 // A CU holds one workgroup, so what counts is the rounds of workgroups over the CUs and the rows of a round.  Ranges that
 // fill the chip in one round take the smallest tile that still does: keys and values of 1024 tokens x 8 heads 23.6 us to encode
 // on 32 rows, 27.0 on 64, 38.8 on 128 (decode 19.1, 22.3, 30.7); 2048 tokens 28.7 on 64 against 39.5 on 128 (24.3 against 31.1);
-// 4096 tokens, a tensor at a time: 20.6 / 28.8 on 128 against 26.1 / 35 on 256.  Beyond that 320 rows x one head fill the gap where the tiles of 256
+// 2100 tokens 33.0 on 96 against 39.8 on 128 (30.6 against 34.8), 3072 tokens 35.4 against 41.4 (30.7 against 32.8); 4096 tokens, a tensor at a time: 20.6 / 28.8 on 128 against 26.1 / 35 on 256.  Beyond that 320 rows x one head fill the gap where the tiles of 256
 // rows start a round they hardly use (10007 tokens: 41.1 / 57.8 us against 45.6 / 62.4; 20000 tokens: 81 / 115 against
 // 87 / 122): taken when its rounds cost less, a round being 41 us on 320 rows, 29 us on 256 rows (33 the first) and 54 us on
 // 256 rows x two heads (K = 1024, encode).  Decode has the same proportions, keys and values together, against tiles of 256 rows
@@ -384,7 +384,7 @@ int tile_rows(int64_t n_seq, int64_t seq_len, int D, bool two_heads) {
   const int64_t H = D / BN;
   const auto tiles = [&](int64_t rows) { return n_seq * ((seq_len + rows - 1) / rows) * H; };
   const auto rounds = [&](int64_t t) { return (t + kCUs - 1) / kCUs; };
-  for (const int rows : {32, 64, 128})
+  for (const int rows : {32, 64, 96, 128})
     if (tiles(rows) <= kCUs) return rows;
   const int64_t all = (n_seq * seq_len + BM - 1) / BM;    // tiles of 256 rows may straddle sequences
   int64_t other = 29 * rounds(all * H) + 4;
@@ -394,6 +394,7 @@ int tile_rows(int64_t n_seq, int64_t seq_len, int D, bool two_heads) {
 hipError_t launch_rows(int rows, int mode, int n_codewords, bool wide, int n_seq, const TileArgs& a, hipStream_t stream) {
   if (rows == 32) return launch_tile_32(mode, n_codewords, wide, n_seq, a, stream);
   if (rows == 64) return launch_tile_64(mode, n_codewords, wide, n_seq, a, stream);
+  if (rows == 96) return launch_tile_96(mode, n_codewords, wide, n_seq, a, stream);
   if (rows == 128) return launch_tile_128(mode, n_codewords, wide, n_seq, a, stream);
   return launch_tile_320(mode, n_codewords, wide, n_seq, a, stream);
 }
@@ -418,12 +419,13 @@ TileArgs tensor_args(const FusedTensor& t, const float* codebook, int64_t T, int
 //
 // A launch for one tensor of few rows is bound by the latency of its k-tiles and leaves CUs idle, so the other tensor's tiles come
 // for little: the smallest tile with which both fit the CUs in one round (2048 rows of 8 heads), and tiles of 128 rows up to half a
-// round more.  Attention over a cache of six layers, us a token, apart / together: 300 tokens 145 / 115, 1100 155 / 138, 2000 192 / 177,
+// round more.  Attention over a cache of eight layers, us a token, pieces beside the tiles, on 128 / 96 rows: 1200 tokens 159 / 154, 1500 173 / 163.
+// Attention over a cache of six layers, us a token, apart / together: 300 tokens 145 / 115, 1100 155 / 138, 2000 192 / 177,
 // 2 x 1500 236 / 219.  From there on both tensors in one launch take as many rounds as two launches: 5376 rows are twice 168 tiles of
 // 256 rows, 561 / 582 us for eight layers, or twice 136 of 320, 557 / 570.
 int pair_rows(int64_t T, int D) {
   const int64_t H = D / BN;
-  for (const int rows : {32, 64, 128})
+  for (const int rows : {32, 64, 96, 128})
     if (2 * ((T + rows - 1) / rows) * H <= (rows == 128 ? 384 : 256)) return rows;
   return 0;
 }
@@ -456,6 +458,7 @@ hipError_t launch_fused_decode_attend(int n_codewords, const FusedTensor* tensor
   const int rows = attend_rows(T, D, n);
   if (rows == 32) return launch_tile_attend_32(n_codewords, wide, jobs, n, attend, stream);
   if (rows == 64) return launch_tile_attend_64(n_codewords, wide, jobs, n, attend, stream);
+  if (rows == 96) return launch_tile_attend_96(n_codewords, wide, jobs, n, attend, stream);
   if (rows == 128) return launch_tile_attend_128(n_codewords, wide, jobs, n, attend, stream);
   if (rows != BM) return hipErrorInvalidValue;
   TileAttend args;
@@ -476,7 +479,7 @@ namespace {
 // 2700 (352) 299 / 300.
 int encode_pair_rows(int64_t T, int D) {
   const int64_t H = D / BN;
-  for (const int rows : {32, 64, 128})
+  for (const int rows : {32, 64, 96, 128})
     if (2 * ((T + rows - 1) / rows) * H <= (rows == 128 ? 320 : 256)) return rows;
   return 0;
 }
@@ -493,6 +496,7 @@ hipError_t launch_fused_encode_pair(int n_codewords, const FusedTensor* tensors,
   const int rows = encode_pair_rows(T, D);
   if (rows == 32) return launch_pair_32(kTileEncode, n_codewords, false, jobs[0], jobs[1], stream);
   if (rows == 64) return launch_tile_two_64(kTileEncode, n_codewords, jobs, stream);
+  if (rows == 96) return launch_tile_two_96(kTileEncode, n_codewords, jobs, stream);
   if (rows == 128) return launch_tile_two_128(kTileEncode, n_codewords, jobs, stream);
   return hipErrorInvalidValue;
 }

@@ -1,11 +1,13 @@
 // Fused predictor kernels (Alg. "encode" / "decode" of the AQUA-KV paper: predictor of Sect. 3.2, backbone of Sect. 2) on
-// tiles of 32, 64, 128 or 320 token rows x one kv head (which one: tile_rows in fused_kernels.hip).
+// tiles of 32, 64, 96, 128 or 320 token rows x one kv head (which one: tile_rows in fused_kernels.hip).
 //
 // Same main-loop bits (gemm_tile.h), same group bodies, hence the same results.  The epilogue parks up to 128 rows of the
 // tile at a time and works on them 16 groups per wave, one group per quad of lanes; on tiles of 32 and 64 rows, which would
 // leave half of the waves (32 rows) or one of two per SIMD (64) idle, 8 groups per wave, one group per eight lanes.  A wave alone
 // on its SIMD is bound by latency, so the work per lane is what counts: keys and values of 128 tokens, 16-point grid, 22.9 -> 20.8 us
 // (256 points: 29.8 -> 25.1), decode of 1100 tokens with groups across the heads 27.7 -> 24.4.
+// On 96 rows three waves share a SIMD, 168 registers each: with 16 values per lane and four sub-vectors searched at a time the quantizer takes
+// 105; with eight at a time it spilled (3072 tokens 35.4 us against 39.6; 64 points 38.2 against 45.6).
 #pragma once
 #include "attend_piece.h"
 #include "fused_epilogue.h"
@@ -60,7 +62,7 @@ struct TileAttend {
 // How an epilogue splits a tile, and the LDS it takes
 template <int MODE, int MB> struct TileEpilogue {
   using S = Tile<MB>;
-  static constexpr int kVals = MB <= 2 ? 16 : kValsPerLane;            // values of a group per lane
+  static constexpr int kVals = MB <= 3 ? 16 : kValsPerLane;            // values of a group per lane
   static constexpr int kWaveRows = kVals / 2;                          // groups per wave and pass
   static constexpr int kParkRows = S::kRows < kWaveRows * S::kWaves ? S::kRows : kWaveRows * S::kWaves;   // one pass
   static constexpr int kBytes = MODE != kTilePredict ? (int)sizeof(Lds) + kParkRows * kLdP * 4 : 0;
@@ -231,7 +233,7 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
         if constexpr (kEnc) {
 #pragma unroll
           for (int k = 0; k < kVals / 8; ++k) unpack_bf16x8(in[h & 1].x[k], &v[8 * k]);
-          quantize_group<NCW, false, S::MI < 5 ? 8 : 4>(v, p, sf, q, cl.cb, use_table ? cl.table : nullptr, active, gid, a.codes, a.scales,
+          quantize_group<NCW, false, MB == 3 || S::MI >= 5 ? 4 : 8>(v, p, sf, q, cl.cb, use_table ? cl.table : nullptr, active, gid, a.codes, a.scales,
                               a.Xhat != nullptr);
         } else if constexpr (kWideGrid) {
           dequantize_across_heads<NCW>(wide[h & 1], in[h & 1].w.scale, head, q, p, sf, cl.cb, v);
@@ -249,7 +251,7 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
 }
 
 template <int NCW, int MODE, int MB, bool WIDE, int SUMS>
-__global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(MB == 1 ? 1 : 2))) void fused_tile_kernel(const TileArgs a) {
+__global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(Tile<MB>::kWaves / 4))) void fused_tile_kernel(const TileArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[TileEpilogue<MODE, MB>::kLdsBytes];
   fused_tile<NCW, MODE, MB, WIDE, SUMS>(a, (int)blockIdx.x, (int)gridDim.x, false, smem);
 }
@@ -271,7 +273,7 @@ __global__ __launch_bounds__(Tile<1>::kThreads) __attribute__((amdgpu_waves_per_
 }
 // Two tensors that are encoded, or predicted (MODE)
 template <int NCW, int MODE, int MB>
-__global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(MB == 1 ? 1 : 2))) void fused_tile_two_kernel(const TilePair pair) {
+__global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(Tile<MB>::kWaves / 4))) void fused_tile_two_kernel(const TilePair pair) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[TileEpilogue<MODE, MB>::kLdsBytes];
   fused_tile_of_pair<NCW, MODE, MB, false, kNoSums>(0, pair.blocks, (int)gridDim.x, smem);
 }
@@ -285,7 +287,7 @@ __device__ __forceinline__ void attend_behind_tiles(AttendCacheParam& a, int blo
                        reinterpret_cast<AttendLds*>(smem)[part]);
 }
 template <int NCW, int MB, bool WIDE>
-__global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(MB == 1 ? 1 : 2))) void fused_tile_attend_kernel(const TileAttend job) {
+__global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(Tile<MB>::kWaves / 4))) void fused_tile_attend_kernel(const TileAttend job) {
   constexpr int kTileBytes = TileEpilogue<kTileDecode, MB>::kLdsBytes, kAttendBytes = Tile<MB>::kThreads / kAttendThreads * (int)sizeof(AttendLds);
   __shared__ __attribute__((aligned(16))) unsigned char smem[kTileBytes > kAttendBytes ? kTileBytes : kAttendBytes];
   if ((int)blockIdx.x < job.tiles) {
@@ -296,11 +298,12 @@ __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per
   }
 }
 
-// rows per tile 32, 64, 128 or 320 (one translation unit each); tiles_per_seq is filled in
+// rows per tile 32, 64, 96, 128 or 320 (one translation unit each); tiles_per_seq is filled in
 #define AQUAKV_TILE_LAUNCHER(ROWS) \
   hipError_t launch_tile_##ROWS(int mode, int n_codewords, bool wide, int n_seq, const TileArgs& a, hipStream_t stream)
 AQUAKV_TILE_LAUNCHER(32);
 AQUAKV_TILE_LAUNCHER(64);
+AQUAKV_TILE_LAUNCHER(96);
 AQUAKV_TILE_LAUNCHER(128);
 AQUAKV_TILE_LAUNCHER(320);
 // Two jobs of one mode and quantizer (TilePair), decode or encode, the second for sums if it has a place for them.
@@ -311,11 +314,13 @@ hipError_t launch_pair_32(int mode, int n_codewords, bool wide, const TileArgs& 
                                        hipStream_t stream)
 AQUAKV_TILE_ATTEND_LAUNCHER(32);
 AQUAKV_TILE_ATTEND_LAUNCHER(64);
+AQUAKV_TILE_ATTEND_LAUNCHER(96);
 AQUAKV_TILE_ATTEND_LAUNCHER(128);
 // Encode or prediction of two jobs of one quantizer (tiles of 32 rows: prediction; launch_pair_32 encodes).
 #define AQUAKV_TILE_TWO_LAUNCHER(ROWS) hipError_t launch_tile_two_##ROWS(int mode, int n_codewords, const TileArgs* jobs, hipStream_t stream)
 AQUAKV_TILE_TWO_LAUNCHER(32);
 AQUAKV_TILE_TWO_LAUNCHER(64);
+AQUAKV_TILE_TWO_LAUNCHER(96);
 AQUAKV_TILE_TWO_LAUNCHER(128);
 // Tiles of 32 rows, encode or decode: a product that goes on from stored sums.
 hipError_t launch_tile_rest(int mode, int n_codewords, bool wide, const TileArgs& a, hipStream_t stream);

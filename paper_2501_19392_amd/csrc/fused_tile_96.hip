@@ -1,0 +1,12 @@
+// Fused predictor kernels on tiles of 96 token rows x one kv head (fused_tile.h).
+#include "fused_tile.h"
+
+namespace aquakv {
+
+AQUAKV_TILE_LAUNCHER(96) { return launch_tile<3>(mode, n_codewords, wide, n_seq, a, stream); }
+
+AQUAKV_TILE_ATTEND_LAUNCHER(96) { return launch_tile_attend<3>(n_codewords, wide, jobs, n, attend, stream); }
+
+AQUAKV_TILE_TWO_LAUNCHER(96) { return launch_tile_two<3>(mode, n_codewords, jobs, stream); }
+
+}  // namespace aquakv

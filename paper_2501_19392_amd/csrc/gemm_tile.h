@@ -1,9 +1,9 @@
-// bf16 MFMA main loop of the linear predictors (Sect. 3.2 of the AQUA-KV paper) for tiles of 32, 64, 128 or 320 token
+// bf16 MFMA main loop of the linear predictors (Sect. 3.2 of the AQUA-KV paper) for tiles of 32, 64, 96, 128 or 320 token
 // rows x 128 outputs (one kv head): the shapes a launch picks from so that its tiles fill the CUs evenly.
 //
 // Same instruction (v_mfma_f32_32x32x16_bf16), operand orientation, swizzled LDS layout, direct-to-LDS loads and K order
 // per output as gemm_core.h, hence the same bits.  One workgroup per CU.
-//   * 32 rows: four waves split the 128 columns; 64 rows: eight, each holding 32 of the rows.  Such a tile is bound by the stream of
+//   * 32 rows: four waves split the 128 columns; 64 rows: eight, 96 rows: twelve (three per SIMD), each holding 32 of the rows.  Such a tile is bound by the stream of
 //     operands from L2, (rows + 128) x 128 bytes per k-tile of 64, most of it W: a deep ring of k-tiles in LDS keeps it
 //     coming, and a wave reads the fragments of a whole k-tile ahead (its steps of 16 k are one or two MFMAs long).
 //     Measured with 32 rows: 0.18 us per k-tile = 57 bytes per cycle into a CU, of 64; a 256-row tile takes 0.6 to 0.9.
@@ -14,16 +14,19 @@
 #pragma once
 #include "gemm_core.h"
 
+#include <type_traits>
+
 namespace aquakv {
 
 template <int MB> struct TileShape;                   // MB = 32-row blocks of the tile
 template <> struct TileShape<1> { static constexpr int kStages = 7; };       // x 20 KiB
 template <> struct TileShape<2> { static constexpr int kStages = 6; };       // x 24 KiB: 0.31 us per k-tile; with four waves and 3 stages 0.385
+template <> struct TileShape<3> { static constexpr int kStages = 5; };       // x 28 KiB
 template <> struct TileShape<4> { static constexpr int kStages = 4; };       // x 32 KiB
 template <> struct TileShape<10> { static constexpr int kStages = 2; };      // x 56 KiB
 template <int MB> struct Tile : TileShape<MB> {
   static constexpr int kRows = 32 * MB;
-  static constexpr int WM = MB == 1 ? 1 : 2, WN = 4;
+  static constexpr int WM = MB == 1 ? 1 : MB == 3 ? 3 : 2, WN = 4;
   static constexpr int kWaves = WM * WN, kThreads = kWaves * 64;
   static constexpr int MI = MB / WM;                  // 32-row blocks per wave
   static constexpr int kAhead = MB < 4 ? 4 : 1;       // fragments are read this many steps of 16 k ahead
@@ -57,7 +60,8 @@ __device__ __forceinline__ void TileLoop<MB>::run(unsigned char* lds_base, const
                                                   int ldw, int last, f32x16 (&acc)[S::MI], Start&& start) {
   constexpr int kRowsPerPiece = S::kThreads / 8;      // tile rows one load instruction of the workgroup fills
   constexpr int kPieceBytes = S::kThreads * 16;
-  constexpr int kA = S::kRows / kRowsPerPiece, kB = 128 / kRowsPerPiece, kPieces = kA + kB;
+  constexpr int kA = S::kRows / kRowsPerPiece, kB = (128 + kRowsPerPiece - 1) / kRowsPerPiece, kPieces = kA + kB;
+  constexpr int kPart = 128 % kRowsPerPiece / 8;      // not 0: the last piece of W is a load of the first kPart waves only
   constexpr int kStages = S::kStages, kAhead = S::kAhead, MI = S::MI;
   constexpr int kBufs = kAhead == 1 ? 2 : kAhead;
   static_assert(kA * kRowsPerPiece == S::kRows && kPieces * (kStages - 1) < 64, "whole pieces; vmcnt range");
@@ -67,6 +71,7 @@ __device__ __forceinline__ void TileLoop<MB>::run(unsigned char* lds_base, const
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / S::WN, wn = wave % S::WN;
   const int K = d0 + d1, nk = K / BK;
+  const bool all_pieces = kPart == 0 || wave < kPart;
 
   const int ch16 = ((tid & 7) ^ ((tid >> 4) & 7)) * 16;
   int rowc[kA];
@@ -91,7 +96,7 @@ __device__ __forceinline__ void TileLoop<MB>::run(unsigned char* lds_base, const
       const int ld2 = __builtin_amdgcn_readfirstlane((second ? d1 : d0) * 2);
       const gptr_t xb = uniform_ptr(reinterpret_cast<const char*>(second ? x1 : x0) + (int64_t)(second ? k0 - d0 : k0) * 2);
       __builtin_amdgcn_global_load_lds(xb + ((uint32_t)__umul24(rowc[pc], ld2) + ch16), dst, 16, 0, 0);
-    } else {
+    } else if (pc + 1 < kPieces || all_pieces) {
       const gptr_t wb = uniform_ptr(reinterpret_cast<const char*>(W) + ((int64_t)k0 * 2 + (int64_t)(pc - kA) * kRowsPerPiece * ldw * 2));
       __builtin_amdgcn_global_load_lds(wb + offW, dst, 16, 0, 0);
     }
@@ -129,14 +134,19 @@ __device__ __forceinline__ void TileLoop<MB>::run(unsigned char* lds_base, const
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // at most `tiles` newer k-tiles may still be on their way (loads complete in issue order)
+  // at most N newer k-tiles may still be on their way (loads complete in issue order)
+  auto wait_newer = [&](auto n) {
+    constexpr int N = decltype(n)::value;
+    if (all_pieces) wait_loads<N * kPieces % 64>();
+    else wait_loads<N * (kPieces - 1) % 64>();
+  };
   auto wait_tiles = [&](int tiles) {
-    if (tiles <= 0) wait_loads<0>();
-    else if (tiles == 1) wait_loads<kPieces>();
-    else if (kStages > 4 && tiles == 2) wait_loads<2 * kPieces % 64>();
-    else if (kStages > 5 && tiles == 3) wait_loads<3 * kPieces % 64>();
-    else if (kStages > 6 && tiles == 4) wait_loads<4 * kPieces % 64>();
-    else wait_loads<(kStages - 2) * kPieces>();
+    if (tiles <= 0) wait_newer(std::integral_constant<int, 0>{});
+    else if (tiles == 1) wait_newer(std::integral_constant<int, 1>{});
+    else if (kStages > 4 && tiles == 2) wait_newer(std::integral_constant<int, 2>{});
+    else if (kStages > 5 && tiles == 3) wait_newer(std::integral_constant<int, 3>{});
+    else if (kStages > 6 && tiles == 4) wait_newer(std::integral_constant<int, 4>{});
+    else wait_newer(std::integral_constant<int, kStages - 2>{});
   };
   auto meet = [&] {
     asm volatile("" ::: "memory");
@@ -153,7 +163,7 @@ __device__ __forceinline__ void TileLoop<MB>::run(unsigned char* lds_base, const
       for (int pc = 0; pc < kPieces; ++pc) load_piece(t, t * S::kStage, pc);
     }
   // tile 0 has landed: `first` - 1 newer ones may be out
-  if (first == kStages) wait_loads<(kStages - 1) * kPieces>();
+  if (first == kStages) wait_newer(std::integral_constant<int, kStages - 1>{});
   else wait_tiles(first - 1);
   meet();
   Frag f[kBufs];
@@ -167,7 +177,7 @@ __device__ __forceinline__ void TileLoop<MB>::run(unsigned char* lds_base, const
   // published; by then every wave's reads of tile t have returned, so its stage takes tile t + kStages.
   auto tile = [&](int t, int cur, int nxt, bool has_next, bool steady, bool do_load) {
     const auto publish = [&] {
-      if (steady) wait_loads<(kStages - 2) * kPieces>();
+      if (steady) wait_newer(std::integral_constant<int, kStages - 2>{});
       else wait_tiles(nk - 2 - t);
       meet();
     };

@@ -1,4 +1,4 @@
-"""Tiles of 32, 64, 128 and 320 token rows (short ranges, and ranges that leave a round of the large tiles nearly empty):
+"""Tiles of 32, 64, 96, 128 and 320 token rows (short ranges, and ranges that leave a round of the large tiles nearly empty):
 encode, decode and the scoring call against the stage calls (aquakv_predict, aquakv_quantize, aquakv_dequantize), bit for
 bit, at the edges of every tile, with and without bias, for predictors as narrow as two k-tiles, all quantizers and both groupings."""
 import pytest
@@ -22,7 +22,7 @@ def layer(H, dk, quantizer, rht_group=None, bias=True):
                          w_v=U.random_weights(D, dk + D, 22, 0.7), b_k=bk, b_v=bv, **kw)[1]
 
 
-CASES = [(8, 1024, T) for T in (1, 31, 33, 1024, 1025, 1089, 2048, 2049, 2177, 4096, 4097, 4289, 6144, 6145, 8449)] + [
+CASES = [(8, 1024, T) for T in (1, 31, 33, 1024, 1025, 1089, 2048, 2049, 2177, 2976, 3071, 3072, 3073, 4096, 4097, 4289, 6144, 6145, 8449)] + [
     (3, 128, 2700), (3, 128, 33), (16, 256, 700), (1, 384, 8200), (8, 192 * 2, 129)]
 
 
