@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libaquakv.so")
 SOURCES = ["api.hip", "predict_gemm.hip", "codec_kernels.hip", "fused_kernels.hip", "fused_wide_encode.hip", "fused_two_heads.hip", "folded_scores.hip", "calibrate.hip", "exact_gram.hip",
            "weighted_values.hip", "attend_cache.hip", "copy_ranges.hip",
-           *(f"fused_tile_{rows}.hip" for rows in (32, 64, 96, 128, 320))]
+           *(f"fused_tile_{rows}.hip" for rows in (32, 64, 96, 128, 192, 320))]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed fp32 VALU ops

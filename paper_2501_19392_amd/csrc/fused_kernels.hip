@@ -373,7 +373,9 @@ hipError_t launch(int n_codewords, const void* x0, int d0, const void* x1, int d
 // A CU holds one workgroup, so what counts is the rounds of workgroups over the CUs and the rows of a round.  Ranges that
 // fill the chip in one round take the smallest tile that still does: keys and values of 1024 tokens x 8 heads 23.6 us to encode
 // on 32 rows, 27.0 on 64, 38.8 on 128 (decode 19.1, 22.3, 30.7); 2048 tokens 28.7 on 64 against 39.5 on 128 (24.3 against 31.1);
-// 2100 tokens 33.0 on 96 against 39.8 on 128 (30.6 against 34.8), 3072 tokens 35.4 against 41.4 (30.7 against 32.8); 4096 tokens, a tensor at a time: 20.6 / 28.8 on 128 against 26.1 / 35 on 256.  Beyond that 320 rows x one head fill the gap where the tiles of 256
+// 2100 tokens 33.0 on 96 against 39.8 on 128 (30.6 against 34.8), 3072 tokens 35.4 against 41.4 (30.7 against 32.8); 4096 tokens, a tensor at a time: 20.6 / 28.8 on 128 against 26.1 / 35 on 256.  192 rows fill the CUs better than 256 up to 6144 tokens: encode of 4200
+// tokens 57.4 against 63.3 us, 6144 64.2 against 67.4, decode 47.4 against 50.5 and 52.7 against 52.5; predictions alone, whose large tile has two heads,
+// gain more (groups across the heads, encode of 5376 tokens 82.8 against 100.2, decode 55.5 against 57.9).  Beyond that 320 rows x one head fill the gap where the tiles of 256
 // rows start a round they hardly use (10007 tokens: 41.1 / 57.8 us against 45.6 / 62.4; 20000 tokens: 81 / 115 against
 // 87 / 122): taken when its rounds cost less, a round being 41 us on 320 rows, 29 us on 256 rows (33 the first) and 54 us on
 // 256 rows x two heads (K = 1024, encode).  Decode has the same proportions, keys and values together, against tiles of 256 rows
@@ -384,7 +386,7 @@ int tile_rows(int64_t n_seq, int64_t seq_len, int D, bool two_heads) {
   const int64_t H = D / BN;
   const auto tiles = [&](int64_t rows) { return n_seq * ((seq_len + rows - 1) / rows) * H; };
   const auto rounds = [&](int64_t t) { return (t + kCUs - 1) / kCUs; };
-  for (const int rows : {32, 64, 96, 128})
+  for (const int rows : {32, 64, 96, 128, 192})
     if (tiles(rows) <= kCUs) return rows;
   const int64_t all = (n_seq * seq_len + BM - 1) / BM;    // tiles of 256 rows may straddle sequences
   int64_t other = 29 * rounds(all * H) + 4;
@@ -396,6 +398,7 @@ hipError_t launch_rows(int rows, int mode, int n_codewords, bool wide, int n_seq
   if (rows == 64) return launch_tile_64(mode, n_codewords, wide, n_seq, a, stream);
   if (rows == 96) return launch_tile_96(mode, n_codewords, wide, n_seq, a, stream);
   if (rows == 128) return launch_tile_128(mode, n_codewords, wide, n_seq, a, stream);
+  if (rows == 192) return launch_tile_192(mode, n_codewords, wide, n_seq, a, stream);
   return launch_tile_320(mode, n_codewords, wide, n_seq, a, stream);
 }
 TileArgs tile_args(const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias, const int8_t* signs,
@@ -436,13 +439,14 @@ int pair_rows(int64_t T, int D) {
 // of its own / beside the tiles.  Two tensors: 200 tokens 145 / 98, 1200 215 / 159, 2000 223 / 193, 3000 315 / 269, 8 x 200 161 / 120.
 // One tensor, as long as it leaves an eighth of the CUs without a tile: 3600 tokens (216 tiles of 128 rows) 361 / 347, 8 x 800 476 / 415,
 // 4 x 1800 (168 tiles of 256 rows) 502 / 484, 6000 tokens (184) 458 / 441.  With tiles on all CUs the pieces wait, and then run one or
-// two to a CU instead of four: 4200 tokens (256 tiles of 128 rows) 360 / 389, 8000 (248 of 256 rows) 550 / 559.
+// two to a CU instead of four: 4200 tokens (256 tiles of 128 rows) 360 / 389, 8000 (248 of 256 rows) 550 / 559.  256 rows stay where 192 would
+// do: they leave more CUs to the pieces (4 x 1800 tokens 517 to 532 us against 527 to 536).
 constexpr int64_t kAttendTiles = 224;
 int attend_rows(int64_t T, int D, int n) {
   if (n == 2) return pair_rows(T, D);
   const int rows = tile_rows(1, T, D, true);
   if (rows == 320 || (rows == 0 && two_heads_pays(T, D))) return 0;
-  const int64_t each = rows == 0 ? BM : rows;
+  const int64_t each = rows == 0 || rows == 192 ? BM : rows;
   return (T + each - 1) / each * (D / BN) <= kAttendTiles ? (int)each : 0;
 }
 }  // namespace

@@ -1,12 +1,12 @@
 // Fused predictor kernels (Alg. "encode" / "decode" of the AQUA-KV paper: predictor of Sect. 3.2, backbone of Sect. 2) on
-// tiles of 32, 64, 96, 128 or 320 token rows x one kv head (which one: tile_rows in fused_kernels.hip).
+// tiles of 32, 64, 96, 128, 192 or 320 token rows x one kv head (which one: tile_rows in fused_kernels.hip).
 //
 // Same main-loop bits (gemm_tile.h), same group bodies, hence the same results.  The epilogue parks up to 128 rows of the
 // tile at a time and works on them 16 groups per wave, one group per quad of lanes; on tiles of 32 and 64 rows, which would
 // leave half of the waves (32 rows) or one of two per SIMD (64) idle, 8 groups per wave, one group per eight lanes.  A wave alone
 // on its SIMD is bound by latency, so the work per lane is what counts: keys and values of 128 tokens, 16-point grid, 22.9 -> 20.8 us
 // (256 points: 29.8 -> 25.1), decode of 1100 tokens with groups across the heads 27.7 -> 24.4.
-// On 96 rows three waves share a SIMD, 168 registers each: with 16 values per lane and four sub-vectors searched at a time the quantizer takes
+// On 96 and 192 rows three waves share a SIMD, 168 registers each: with 16 values per lane and four sub-vectors searched at a time the quantizer takes
 // 105; with eight at a time it spilled (3072 tokens 35.4 us against 39.6; 64 points 38.2 against 45.6).
 #pragma once
 #include "attend_piece.h"
@@ -62,7 +62,7 @@ struct TileAttend {
 // How an epilogue splits a tile, and the LDS it takes
 template <int MODE, int MB> struct TileEpilogue {
   using S = Tile<MB>;
-  static constexpr int kVals = MB <= 3 ? 16 : kValsPerLane;            // values of a group per lane
+  static constexpr int kVals = MB <= 3 || MB == 6 ? 16 : kValsPerLane;            // values of a group per lane
   static constexpr int kWaveRows = kVals / 2;                          // groups per wave and pass
   static constexpr int kParkRows = S::kRows < kWaveRows * S::kWaves ? S::kRows : kWaveRows * S::kWaves;   // one pass
   static constexpr int kBytes = MODE != kTilePredict ? (int)sizeof(Lds) + kParkRows * kLdP * 4 : 0;
@@ -233,7 +233,7 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
         if constexpr (kEnc) {
 #pragma unroll
           for (int k = 0; k < kVals / 8; ++k) unpack_bf16x8(in[h & 1].x[k], &v[8 * k]);
-          quantize_group<NCW, false, MB == 3 || S::MI >= 5 ? 4 : 8>(v, p, sf, q, cl.cb, use_table ? cl.table : nullptr, active, gid, a.codes, a.scales,
+          quantize_group<NCW, false, MB % 3 == 0 || S::MI >= 5 ? 4 : 8>(v, p, sf, q, cl.cb, use_table ? cl.table : nullptr, active, gid, a.codes, a.scales,
                               a.Xhat != nullptr);
         } else if constexpr (kWideGrid) {
           dequantize_across_heads<NCW>(wide[h & 1], in[h & 1].w.scale, head, q, p, sf, cl.cb, v);
@@ -298,13 +298,14 @@ __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per
   }
 }
 
-// rows per tile 32, 64, 96, 128 or 320 (one translation unit each); tiles_per_seq is filled in
+// rows per tile 32, 64, 96, 128, 192 or 320 (one translation unit each); tiles_per_seq is filled in
 #define AQUAKV_TILE_LAUNCHER(ROWS) \
   hipError_t launch_tile_##ROWS(int mode, int n_codewords, bool wide, int n_seq, const TileArgs& a, hipStream_t stream)
 AQUAKV_TILE_LAUNCHER(32);
 AQUAKV_TILE_LAUNCHER(64);
 AQUAKV_TILE_LAUNCHER(96);
 AQUAKV_TILE_LAUNCHER(128);
+AQUAKV_TILE_LAUNCHER(192);
 AQUAKV_TILE_LAUNCHER(320);
 // Two jobs of one mode and quantizer (TilePair), decode or encode, the second for sums if it has a place for them.
 hipError_t launch_pair_32(int mode, int n_codewords, bool wide, const TileArgs& a, const TileArgs& b, hipStream_t stream);

@@ -1,0 +1,8 @@
+// Fused predictor kernels on tiles of 192 token rows x one kv head (fused_tile.h).
+#include "fused_tile.h"
+
+namespace aquakv {
+
+AQUAKV_TILE_LAUNCHER(192) { return launch_tile<6>(mode, n_codewords, wide, n_seq, a, stream); }
+
+}  // namespace aquakv

@@ -1,4 +1,4 @@
-// bf16 MFMA main loop of the linear predictors (Sect. 3.2 of the AQUA-KV paper) for tiles of 32, 64, 96, 128 or 320 token
+// bf16 MFMA main loop of the linear predictors (Sect. 3.2 of the AQUA-KV paper) for tiles of 32, 64, 96, 128, 192 or 320 token
 // rows x 128 outputs (one kv head): the shapes a launch picks from so that its tiles fill the CUs evenly.
 //
 // Same instruction (v_mfma_f32_32x32x16_bf16), operand orientation, swizzled LDS layout, direct-to-LDS loads and K order
@@ -10,7 +10,7 @@
 //     The next loads are issued behind the first MFMA of a k-tile, which covers them: ahead of it, where the compiler put them while
 //     that was left to it, with two additions per fragment address, one tensor took 2 to 5 % longer (128 rows, uniform backbone, keys 7.34 -> 6.98 us).
 //   * From 128 rows on: eight waves (two per SIMD) as 2 x 4, wave (wm, wn) holds columns 32 wn ... and every second block
-//     of 32 rows: (MI + 1) / MI operand reads per MFMA, MI = rows / 64.
+//     of 32 rows: (MI + 1) / MI operand reads per MFMA, MI = rows / 64.  192 rows: twelve waves as 3 x 4, MI = 2.
 #pragma once
 #include "gemm_core.h"
 
@@ -23,10 +23,11 @@ template <> struct TileShape<1> { static constexpr int kStages = 7; };       // 
 template <> struct TileShape<2> { static constexpr int kStages = 6; };       // x 24 KiB: 0.31 us per k-tile; with four waves and 3 stages 0.385
 template <> struct TileShape<3> { static constexpr int kStages = 5; };       // x 28 KiB
 template <> struct TileShape<4> { static constexpr int kStages = 4; };       // x 32 KiB
+template <> struct TileShape<6> { static constexpr int kStages = 3; };       // x 40 KiB
 template <> struct TileShape<10> { static constexpr int kStages = 2; };      // x 56 KiB
 template <int MB> struct Tile : TileShape<MB> {
   static constexpr int kRows = 32 * MB;
-  static constexpr int WM = MB == 1 ? 1 : MB == 3 ? 3 : 2, WN = 4;
+  static constexpr int WM = MB == 1 ? 1 : MB % 3 == 0 ? 3 : 2, WN = 4;
   static constexpr int kWaves = WM * WN, kThreads = kWaves * 64;
   static constexpr int MI = MB / WM;                  // 32-row blocks per wave
   static constexpr int kAhead = MB < 4 ? 4 : 1;       // fragments are read this many steps of 16 k ahead
