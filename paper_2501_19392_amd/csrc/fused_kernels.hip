@@ -421,15 +421,16 @@ TileArgs tensor_args(const FusedTensor& t, const float* codebook, int64_t T, int
 // Rows per tile for values and keys of T rows in one launch (launch_fused_decode_pair), 0: two launches are as good.
 //
 // A launch for one tensor of few rows is bound by the latency of its k-tiles and leaves CUs idle, so the other tensor's tiles come
-// for little: the smallest tile with which both fit the CUs in one round (2048 rows of 8 heads), and tiles of 128 rows up to half a
-// round more.  Attention over a cache of eight layers, us a token, pieces beside the tiles, on 128 / 96 rows: 1200 tokens 159 / 154, 1500 173 / 163.
-// Attention over a cache of six layers, us a token, apart / together: 300 tokens 145 / 115, 1100 155 / 138, 2000 192 / 177,
-// 2 x 1500 236 / 219.  From there on both tensors in one launch take as many rounds as two launches: 5376 rows are twice 168 tiles of
+// for little: the smallest tile with which both fit the CUs in one round (3072 rows of 8 heads on 192).  Attention over a cache of six
+// layers, us a token, apart / together: 300 tokens 145 / 115, 1100 155 / 138, 2000 192 / 177, 2 x 1500 236 / 219.  Eight layers, pieces of
+// attention beside the tiles: up to 1536 tokens on 96 rows, 1200 tokens 154 (159 on 128), 1500 163 (173); beyond 2048 tokens on 192
+// rows, 2304 206 (212 with one and an eighth rounds of 128 rows), 2560 213 (245), 2800 221 (248).
+// From there on both tensors in one launch take as many rounds as two launches: 5376 rows are twice 168 tiles of
 // 256 rows, 561 / 582 us for eight layers, or twice 136 of 320, 557 / 570.
 int pair_rows(int64_t T, int D) {
   const int64_t H = D / BN;
-  for (const int rows : {32, 64, 96, 128})
-    if (2 * ((T + rows - 1) / rows) * H <= (rows == 128 ? 384 : 256)) return rows;
+  for (const int rows : {32, 64, 96, 128, 192})
+    if (2 * ((T + rows - 1) / rows) * H <= 256) return rows;
   return 0;
 }
 
@@ -452,7 +453,7 @@ int attend_rows(int64_t T, int D, int n) {
 }  // namespace
 
 bool fused_decode_pair_pays(int64_t T, int D) { return pair_rows(T, D) != 0; }
-int64_t fused_decode_pair_rows(int D) { return 384 / 2 / (D / BN) * 128; }
+int64_t fused_decode_pair_rows(int D) { return 256 / 2 / (D / BN) * 192; }
 bool fused_decode_attend_fits(int64_t T, int D) { return attend_rows(T, D, 1) != 0; }
 hipError_t launch_fused_decode_attend(int n_codewords, const FusedTensor* tensors, const float* const* codebooks, int n, int64_t T, int D,
                                       bool wide, const AttendCacheArgs& attend, hipStream_t stream) {
@@ -464,6 +465,7 @@ hipError_t launch_fused_decode_attend(int n_codewords, const FusedTensor* tensor
   if (rows == 64) return launch_tile_attend_64(n_codewords, wide, jobs, n, attend, stream);
   if (rows == 96) return launch_tile_attend_96(n_codewords, wide, jobs, n, attend, stream);
   if (rows == 128) return launch_tile_attend_128(n_codewords, wide, jobs, n, attend, stream);
+  if (rows == 192) return launch_tile_attend_192(n_codewords, wide, jobs, n, attend, stream);
   if (rows != BM) return hipErrorInvalidValue;
   TileAttend args;
   args.pair.job[0] = args.pair.job[1] = jobs[0];
@@ -477,18 +479,10 @@ hipError_t launch_fused_decode_attend(int n_codewords, const FusedTensor* tensor
   return hipGetLastError();
 }
 
-namespace {
-// The same for encoding, where a tile's epilogue weighs more.  Stack of 8 layers, 16 points, us, a layer at a time / values and next keys
-// together: 128 rows 142 / 105, 512 151 / 114, 1024 176 / 145, 1100 194 / 178, 2048 223 / 204, 2304 (288 tiles of 128 rows) 296 / 266,
-// 2700 (352) 299 / 300.
-int encode_pair_rows(int64_t T, int D) {
-  const int64_t H = D / BN;
-  for (const int rows : {32, 64, 96, 128})
-    if (2 * ((T + rows - 1) / rows) * H <= (rows == 128 ? 320 : 256)) return rows;
-  return 0;
-}
-}  // namespace
-bool fused_encode_pair_pays(int64_t T, int D) { return encode_pair_rows(T, D) != 0; }
+// The same rule for encoding.  Stack of 8 layers, 16 points, us, a layer at a time / values and next keys together: 128 rows 142 / 105,
+// 512 151 / 114, 1024 176 / 145, 1100 194 / 168 (178 on tiles of 128 rows), 2048 223 / 193; on 192 rows / 128: 2304 231 / 248, 2560 237 / 248;
+// on 192 rows / a layer at a time: 2800 244 / 260, 3072 250 / 266.
+bool fused_encode_pair_pays(int64_t T, int D) { return pair_rows(T, D) != 0; }
 hipError_t launch_fused_encode_pair(int n_codewords, const FusedTensor* tensors, const float* const* codebooks, const void* const* tables,
                                     int64_t T, int D, hipStream_t stream) {
   if (T == 0) return hipSuccess;
@@ -497,18 +491,19 @@ hipError_t launch_fused_encode_pair(int n_codewords, const FusedTensor* tensors,
     jobs[i] = tensor_args(tensors[i], codebooks[i], T, D);
     jobs[i].table = static_cast<const uint32_t*>(tables[i]);
   }
-  const int rows = encode_pair_rows(T, D);
+  const int rows = pair_rows(T, D);
   if (rows == 32) return launch_pair_32(kTileEncode, n_codewords, false, jobs[0], jobs[1], stream);
   if (rows == 64) return launch_tile_two_64(kTileEncode, n_codewords, jobs, stream);
   if (rows == 96) return launch_tile_two_96(kTileEncode, n_codewords, jobs, stream);
   if (rows == 128) return launch_tile_two_128(kTileEncode, n_codewords, jobs, stream);
+  if (rows == 192) return launch_tile_two_192(kTileEncode, n_codewords, jobs, stream);
   return hipErrorInvalidValue;
 }
 
 // Predictions of two tensors (groups across the heads): a tile is a main loop and its stores, and two launches of the predictor and two of
 // the quantizer become one each, so it pays up to two rounds of tiles of 128 rows.  Stack of 8 layers, 16 points, us, a layer at a time /
-// together: 128 rows 222 / 143, 512 236 / 164, 1100 282 / 224 (on 128 rows 235), 1400 291 / 240 (on 64 rows 250), 2304 405 / 338,
-// 3072 420 / 384, 4096 490 / 469.
+// together: 128 rows 222 / 143, 512 236 / 164, 1200 282 / 217 (on 64 rows 230), 1400 291 / 215 (on 128 rows 240), 2304 405 / 310 (on 128 rows
+// 316), 3072 420 / 329 (362), 4096 490 / 469.
 int64_t tile_predict_pair_rows(int D) { return 512 / 2 / (D / BN) * 128; }
 hipError_t launch_tile_predict_pair(const FusedTensor* tensors, const Prediction* out, int64_t T, int D, hipStream_t stream) {
   if (T == 0) return hipSuccess;
@@ -519,7 +514,9 @@ hipError_t launch_tile_predict_pair(const FusedTensor* tensors, const Prediction
   }
   const auto tiles = [&](int64_t rows) { return 2 * ((T + rows - 1) / rows) * (D / BN); };
   if (tiles(32) <= 256) return launch_tile_two_32(kTilePredict, 16, jobs, stream);
-  if (tiles(64) <= 320) return launch_tile_two_64(kTilePredict, 16, jobs, stream);
+  if (tiles(64) <= 256) return launch_tile_two_64(kTilePredict, 16, jobs, stream);
+  if (tiles(96) <= 256) return launch_tile_two_96(kTilePredict, 16, jobs, stream);
+  if (tiles(128) > 256 && tiles(192) <= 256) return launch_tile_two_192(kTilePredict, 16, jobs, stream);
   return launch_tile_two_128(kTilePredict, 16, jobs, stream);
 }
 

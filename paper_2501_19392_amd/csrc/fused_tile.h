@@ -317,12 +317,14 @@ AQUAKV_TILE_ATTEND_LAUNCHER(32);
 AQUAKV_TILE_ATTEND_LAUNCHER(64);
 AQUAKV_TILE_ATTEND_LAUNCHER(96);
 AQUAKV_TILE_ATTEND_LAUNCHER(128);
+AQUAKV_TILE_ATTEND_LAUNCHER(192);
 // Encode or prediction of two jobs of one quantizer (tiles of 32 rows: prediction; launch_pair_32 encodes).
 #define AQUAKV_TILE_TWO_LAUNCHER(ROWS) hipError_t launch_tile_two_##ROWS(int mode, int n_codewords, const TileArgs* jobs, hipStream_t stream)
 AQUAKV_TILE_TWO_LAUNCHER(32);
 AQUAKV_TILE_TWO_LAUNCHER(64);
 AQUAKV_TILE_TWO_LAUNCHER(96);
 AQUAKV_TILE_TWO_LAUNCHER(128);
+AQUAKV_TILE_TWO_LAUNCHER(192);
 // Tiles of 32 rows, encode or decode: a product that goes on from stored sums.
 hipError_t launch_tile_rest(int mode, int n_codewords, bool wide, const TileArgs& a, hipStream_t stream);
 

@@ -64,9 +64,9 @@ def test_faults_in_the_arguments_are_refused():
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("rht_group", [None, 1024])
-@pytest.mark.parametrize("tokens", [1, 31, 512, 513, 1025, 2049, 3072, 3073, 4096, 4097])
+@pytest.mark.parametrize("tokens", [1, 31, 512, 513, 1025, 1536, 1537, 2049, 3072, 3073, 4096, 4097])
 def test_a_stack_has_the_bits_of_its_layers(tokens, rht_group):
-    """Both sides of the lines between tiles of 32, 64 and 128 rows and launches of one tensor; layers of other quantizers, a 16-bit
+    """Both sides of the lines between tiles of 32 to 192 rows and launches of one tensor; layers of other quantizers, a 16-bit
     layer and one without predictors in between; grids of their own and a common one; with the least workspace and with room for more."""
     print(f"case encode stack tokens={tokens} group={rht_group}", flush=True)
     gen = torch.Generator().manual_seed(tokens)
