@@ -367,8 +367,8 @@ __global__ __launch_bounds__(1024) void build_overflow_kernel(const float* __res
 }
 
 // Workgroups per CU (256 CUs), the kernels grid-stride.  The quantizer stages 21 KiB of grid and cell table per workgroup,
-// more than the 8 KiB of rows of one round: with at most the resident number of workgroups the staging is paid once and
-// the request of the next round's rows has a next round to run ahead of.  The inverse stages 256 B to 4 KiB; keys and values of
+// more than the 8 KiB of rows of one round: with the resident number of workgroups the staging is paid once and
+// the request of the next round's rows has a next round to run ahead of (more than those where it evens out the CUs: rounds_for).  The inverse stages 256 B to 4 KiB; keys and values of
 // 131072 tokens, 16 points: 171 us with four workgroups per CU, 178 with six or eight (of 8192 tokens 11.1 with any of them).
 // Below that number the rounds are shared out evenly.
 //
@@ -378,6 +378,7 @@ __global__ __launch_bounds__(1024) void build_overflow_kernel(const float* __res
 // only (keys and values: 1000 2.9 / 3.0, 10000 10.8 / 11.3, 16384 15.6 / 15.3, 20000 18.4 / 18.5, 21071 19.5 / 17.8, 131072 104 / 93).
 inline bool codes_pay(int64_t n_groups, bool wide) { return n_groups >= (wide ? 16384 : 262144); }
 constexpr int kQuantizeWgPerCu = 3, kQuantizePlainWgPerCu = 4, kCodesWgPerCu = 3;     // with a prediction, without, codes only
+constexpr int kQuantizeStart = 2;
 constexpr int kDequantizeWgPerCu = 4;
 inline int64_t blocks_of_rounds(int64_t blocks, int64_t cap) {
   const int64_t rounds = (blocks + cap - 1) / cap;
@@ -387,11 +388,26 @@ inline int64_t blocks_of_rounds(int64_t blocks, int64_t cap) {
 // 17.1 us (18.8 with a 64-bit remainder and the signs fetched in every round), quantizer with predictions, 256 points, 70.8 (73.2),
 // which is what 32768 tokens of 8 heads take.
 struct Rounds { unsigned blocks; bool fixed_head; };
-inline Rounds rounds_for(int64_t n_groups, int groups_per_block, int H, int per_cu, int tensors) {
+// start != 0 (quarters of a round that a workgroup's start costs): more workgroups than are resident, of fewer rounds each, where the CUs then
+// have fewer rounds to do.  With the resident number a CU does as many rounds as its busiest place: of 6500 tokens x 2 tensors some CUs have three
+// workgroups of 4 rounds and others four, 36.1 us (256 points); 1626 workgroups of one or two rounds, dealt out as places get free, 31.7.
+// 9000 tokens 45.5 / 41.2; 10007 tokens with predictions 27.6 / 26 a tensor.  Equal shares (8192 tokens) stay as they are.
+inline Rounds rounds_for(int64_t n_groups, int groups_per_block, int H, int per_cu, int tensors, int start = 0) {
   const int64_t need = (n_groups + groups_per_block - 1) / groups_per_block, resident = 256 * per_cu / tensors;
-  const int64_t blocks = blocks_of_rounds(need, resident);
+  int64_t blocks = blocks_of_rounds(need, resident);
   if (blocks == need) return {(unsigned)blocks, true};
   const int64_t step = H / std::gcd(H, groups_per_block);       // blocks whose groups are a multiple of H
+  if (start != 0) {
+    const auto cost = [&](int64_t b) {
+      return (b * tensors + 255) / 256 * (4 * ((need + b - 1) / b) + start);
+    };
+    int64_t best = blocks;
+    for (int64_t r = 1; r * resident < need; ++r) {
+      const int64_t b = ((need + r - 1) / r + step - 1) / step * step;
+      if (cost(b) < cost(best)) best = b;
+    }
+    if (best != blocks) return {(unsigned)best, true};
+  }
   const int64_t whole = (blocks + step - 1) / step * step;
   return whole <= resident ? Rounds{(unsigned)whole, true} : Rounds{(unsigned)blocks, false};
 }
@@ -444,7 +460,7 @@ hipError_t launch_quantize(int dtype, int n_codewords, const QuantizeIo* io, int
   const bool codes_only = is_rtn(n_codewords) && dtype == kBF16 && P == nullptr && io[0].Xhat == nullptr && other.Xhat == nullptr &&
                           codes_pay(n_groups * tensors, wide);
   const int per_cu = P != nullptr ? kQuantizeWgPerCu : codes_only ? kCodesWgPerCu : kQuantizePlainWgPerCu;
-  const Rounds r = rounds_for(n_groups, kThreads * (codes_only ? kCodesVals : kQuantizeVals) / kGroup, H, per_cu, tensors);
+  const Rounds r = rounds_for(n_groups, kThreads * (codes_only ? kCodesVals : kQuantizeVals) / kGroup, H, per_cu, tensors, kQuantizeStart);
   const dim3 grid(r.blocks, (unsigned)tensors);
   const Prediction p0 = P != nullptr ? P[0] : Prediction{}, p1 = P != nullptr ? P[tensors - 1] : Prediction{};
 #define AQUAKV_QUANTIZE(T, N, W, PRED, CODES) \

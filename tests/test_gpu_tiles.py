@@ -304,3 +304,31 @@ def test_groups_across_heads_in_several_pieces(T, quantizer, keys, values, split
         assert torch.equal(sorted_front, lay.sort().values) != split
     else:
         assert bool((arena[weights:] != 0xCD).any()) == split
+
+
+@pytest.mark.parametrize("H,T", [(8, 4097), (8, 6500), (8, 9000), (3, 14000), (16, 3300), (6, 9001)])
+@pytest.mark.parametrize("quantizer,rht_group", [("n16", None), ("n256", 1024), ("rtn4", None)])
+def test_stand_alone_quantizer_in_more_workgroups_than_are_resident(H, T, quantizer, rht_group):
+    """Head counts that a workgroup's 32 groups are and are not a multiple of, token counts that deal rounds out unevenly: the bits of calls
+    of 512 tokens, whose workgroups have one round each."""
+    from paper_2501_19392_amd import binding as B
+    if rht_group and H != 8:
+        pytest.skip("groups across heads are built for 8 heads")
+    print(f"case quantizer rounds H={H} T={T} {quantizer} group={rht_group}", flush=True)
+    kw = dict(rtn_bits=4) if quantizer == "rtn4" else {}
+    if rht_group:
+        kw["rht_group"] = rht_group
+    lg = U.make_layers(H, "bf16", 16 if kw.get("rtn_bits") else int(quantizer[1:]), **kw)[1]
+    g = torch.Generator(device="cuda").manual_seed(T)
+    K, V = (torch.randn(T, H, 128, generator=g, device="cuda").bfloat16() for _ in range(2))
+    got, want = ([*lg.alloc_codes(T), *lg.alloc_codes(T), lg.alloc_kv(T), lg.alloc_kv(T)] for _ in range(2))
+    for t in got + want:
+        t.view(torch.uint8).fill_(0xAB)
+    ws = lg.alloc_workspace(T)
+    B.aquakv_encode_layer(lg, T, K, V, None, None, *got, ws)
+    for a in range(0, T, 512):
+        n = min(512, T - a)
+        B.aquakv_encode_layer(lg, n, K[a:a + n], V[a:a + n], None, None, *(t[a:a + n] for t in want), ws)
+    torch.cuda.synchronize()
+    for name, a, b in zip(("k codes", "k scales", "v codes", "v scales", "K", "V"), got, want):
+        assert torch.equal(bits(a), bits(b)), name
