@@ -392,7 +392,8 @@ int aquakv_decode_values_attend(const aquakv_layer* layer, int32_t batch, int32_
  * predicts Y from X = [x0 | x1] in the least-squares sense,
  *     W = argmin || X W^T - Y ||^2 + lambda ||W||^2,   lambda = rate * trace(X^T X) / d_in   (rate = 0: plain
  *     least squares, X must then have full column rank),
- * solved in fp64 through the normal equations (Gram products, Cholesky, two triangular solves) and rounded once to
+ * solved in fp64 through the normal equations (Gram products, those of bf16 data summed exactly in integers where they allow it,
+ * Cholesky, two triangular solves) and rounded once to
  * `dtype`.  x0 [tokens, d0], x1 [tokens, d1] (NULL iff d1 = 0), Y [tokens, d_out], all `dtype`, row-major;
  * d0, d1, d_out multiples of 64, at most 8192 inputs / outputs.  W [d_out, d0 + d1] out: the layout of
  * aquakv_layer.w_k / w_v (key predictor: x0 = Khat_prev, Y = K; value predictor: x0 = Vhat_prev, x1 = Khat, Y = V).
