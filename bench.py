@@ -392,7 +392,7 @@ def cpu_baseline(cfg, n_codewords, rows, q_heads, n_layers, rtn_bits=0):
                       f"({dt:.1f} s of CPU time; cost is linear in rows and layers)"}
 
 
-PEAK_FP64_TFLOPS = 78.6          # MI355X fp64, vector and matrix
+PEAK_INT8_TOPS = 5000.0           # MI355X dense 8-bit MFMA
 
 
 def calibration_path(args, device):
@@ -438,8 +438,9 @@ def calibration_path(args, device):
     torch.cuda.synchronize()
     fit_ms = a.elapsed_time(b) / reps
     d = 2 * D
-    flops = 2.0 * T * (d * (d + 64) / 2 + d * D) + d ** 3 / 3.0 + 2.0 * d * d * D    # Gram products (G: lower triangle of 64-tiles), Cholesky, two solves
-    achieved = flops / (fit_ms * 1e-3) / 1e12
+    # Gram products (G: lower triangle of tiles of 128) of three 8-bit digits with three; factorisation and solves (fp64) are in the time only
+    ops = 9 * 2.0 * T * (d * (d + 128) / 2 + d * D)
+    achieved = ops / (fit_ms * 1e-3) / 1e12
     return {
         "metric": "predictor calibration, calibration tokens/s per layer", "value": round(T / (dt / (L - 1)), 1),
         "unit": "tokens/s per layer", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -448,9 +449,10 @@ def calibration_path(args, device):
         "config": {"workload": f"calibration of {L - 1} predicted layers of the llama3.2-3b KV shape (8 kv heads x 128, bf16, "
                                f"n={n}) on {T} tokens: per layer key fit (1024 inputs), key encode, value fit (2048 inputs), "
                                f"value encode", "tokens": T, "layers": L - 1},
-        "roofline": {"kernel": "aquakv_fit_predictor, value predictor (gram_kernel and the block factorisation / solve kernels)",
-                     "bound": "alu", "achieved": round(achieved, 2), "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
-                     "frac": round(achieved / PEAK_FP64_TFLOPS, 4), "traffic": None, "fit_ms": round(fit_ms, 3)},
+        "roofline": {"kernel": "aquakv_fit_predictor, value predictor (exact_gram_kernel, operations of its 8-bit products; the time is the "
+                               "whole call's, with the fp64 factorisation and solve kernels)",
+                     "bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_INT8_TOPS, "unit": "TOP/s",
+                     "frac": round(achieved / PEAK_INT8_TOPS, 4), "traffic": None, "fit_ms": round(fit_ms, 3)},
     }
 
 
