@@ -452,11 +452,14 @@ __global__ __launch_bounds__(1024) void finish_kernel(const Columns x, const uin
 
 }  // namespace
 
-// Columns in whole tiles of 128, room for lists at all (none below 256 inputs), and as many tokens as int64 sums hold.  Fewer than 256 tokens
-// are not worth the launches around the product.
+// Columns in whole tiles of 128, room for lists at all (none below 256 inputs), and as many tokens as int64 sums hold.  Few tokens are not worth
+// the launches around the product.  Whole fits, us, fp64 / integers: 2048 inputs and 1024 outputs, 512 tokens 1185 / 1188, 1024 tokens
+// 1242 / 1207; 1024 and 1024, 1024 tokens 566 / 574, 1536 tokens 590 / 578; 512 and 512, 2048 tokens 286 / 295, 3072 tokens 319 / 300;
+// 256 and 128, 2048 tokens 171 / 160, 3072 tokens 202 / 162.
 bool exact_gram_fits(int64_t tokens, int d0, int d1, int d_out) {
-  return tokens >= 256 && tokens <= (1 << 20) && d0 % kTile == 0 && d1 % kTile == 0 && d_out % kTile == 0 &&
-         listed_room(d0 + d1, d0 + d1 + d_out) > 0;
+  const int64_t columns = (int64_t)d0 + d1 + d_out;
+  return (tokens >= 2560 || tokens * columns >= 2600000) && tokens <= (1 << 20) && d0 % kTile == 0 && d1 % kTile == 0 && d_out % kTile == 0 &&
+         listed_room(d0 + d1, (int)columns) > 0;
 }
 
 hipError_t launch_exact_gram(int64_t tokens, const void* x0, int d0, const void* x1, int d1, const void* Y, int d_out, double* G, void* columns,

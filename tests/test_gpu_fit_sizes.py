@@ -57,10 +57,10 @@ def _columns(kind, T, d, g):
 
 @pytest.mark.parametrize("kind", ["gauss", "spread", "many small", "tiny column"])
 @pytest.mark.parametrize("T,d0,d1,d_out", [
-    (256, 256, 0, 128), (257, 128, 128, 128), (319, 256, 128, 128), (1025, 512, 512, 256), (4097, 128, 384, 384), (2048, 1024, 1024, 1024),
-    (32769, 256, 0, 128)])
+    (2559, 256, 0, 128), (2560, 256, 0, 128), (2561, 128, 128, 128), (2623, 256, 128, 128), (4097, 128, 384, 384), (847, 1024, 1024, 1024),
+    (2048, 1024, 1024, 1024), (32769, 256, 0, 128)])
 def test_fit_from_integer_products(T, d0, d1, d_out, kind):
-    """Edges of the steps of 64 tokens, of the 512 steps that int32 sums hold and of the 32 workgroups of an XCD.  The Gram products are
+    """Edges of the sizes that are formed in integers, of the steps of 64 tokens, of the 512 steps that int32 sums hold and of the 32 workgroups of an XCD.  The Gram products are
     exact but for one rounding each (their fp64 form: T), so the solution is off by the condition number, below 1e5 for these data, times 2^-53
     times the order of the matrix, 2e-8 at worst; 1e-9 is asked, as of the fp64 form above."""
     from paper_2501_19392_amd import binding as B
@@ -92,7 +92,7 @@ def test_fit_from_integer_products(T, d0, d1, d_out, kind):
 
 def test_fit_of_infinities_is_nan_in_both_forms():
     from paper_2501_19392_amd import binding as B
-    T, d, d_out = 512, 256, 128
+    T, d, d_out = 2560, 256, 128
     g = torch.Generator().manual_seed(3)
     X, Y = torch.randn(T, d, generator=g).bfloat16().cuda(), torch.randn(T, d_out, generator=g).bfloat16().cuda()
     W = torch.zeros(d_out, d, dtype=torch.bfloat16, device="cuda")
