@@ -433,9 +433,9 @@ int aquakv_copy_ranges(const aquakv_copy_range* ranges, int32_t n, void* stream)
  * (d_in_k = kv_heads * 128, d_in_v = twice that), and kv_heads and dtype are those of all layers.
  * `workspace`: the most that aquakv_workspace_bytes(layer, tokens) is over the layers; with groups across the heads and up to 4096
  * rows, room for the fp32 predictions of both tensors in halves (2 * tokens * kv_heads * 128 * 2 bytes) lets these share launches too.
- * Nothing that the call writes (codes, scales, hat, the workspace) may overlap anything else it is given: AQUAKV_EINVAL, like every
- * other fault in the arguments before anything is launched (of a layer and the next one; a caller may give layers l and l + 2 the same
- * codes or inputs).
+ * Nothing that the call writes (codes, scales, hat, all of the workspace) may overlap anything else it is given, the layers' parameters
+ * among it: AQUAKV_EINVAL, like every other fault in the arguments before anything is launched (codes and inputs: of a layer and the
+ * next one; a caller may give layers l and l + 2 the same codes or inputs).
  */
 typedef struct aquakv_encode_entry {
   const aquakv_layer* layer;

@@ -141,19 +141,19 @@ int check_no_alias(const Range* outs, int n_out, const Range* ins, int n_in, con
   return AQUAKV_OK;
 }
 
-// The same over the many buffers of a call on a whole cache: no buffer that is written may overlap any other one.  In order of
-// address, a range overlaps an earlier one iff it starts before the furthest end so far, of any range if it is written itself,
-// else of the written ones.
+// The same over the many buffers of a call on a whole cache: no buffer that is written may overlap any other one (`shared`: but those
+// written may overlap one another).  In order of address, a range overlaps an earlier one iff it starts before the furthest end so far,
+// of any range (shared: of those read) if it is written itself, else of the written ones.
 struct CacheRange { uintptr_t begin, end; const char* name; int32_t layer; bool written; };
-int check_disjoint(CacheRange* r, int64_t n) {
+int check_disjoint(CacheRange* r, int64_t n, bool shared = false) {
   std::sort(r, r + n, [](const CacheRange& a, const CacheRange& b) { return a.begin < b.begin; });
-  const CacheRange *any = nullptr, *written = nullptr;      // the ones that reach furthest
+  const CacheRange *read = nullptr, *written = nullptr;     // the ones that reach furthest
   for (int64_t i = 0; i < n; ++i) {
-    const CacheRange* before = r[i].written ? any : written;
-    if (before != nullptr && r[i].begin < before->end)
-      return fail(AQUAKV_EINVAL, "%s of layer %d overlaps %s of layer %d", r[i].name, r[i].layer, before->name, before->layer);
-    if (any == nullptr || r[i].end > any->end) any = r + i;
-    if (r[i].written && (written == nullptr || r[i].end > written->end)) written = r + i;
+    for (const CacheRange* before : {r[i].written ? read : nullptr, r[i].written && shared ? nullptr : written})
+      if (before != nullptr && r[i].begin < before->end)
+        return fail(AQUAKV_EINVAL, "%s of layer %d overlaps %s of layer %d", r[i].name, r[i].layer, before->name, before->layer);
+    const CacheRange*& furthest = r[i].written ? written : read;
+    if (furthest == nullptr || r[i].end > furthest->end) furthest = r + i;
   }
   return AQUAKV_OK;
 }
@@ -203,14 +203,20 @@ Plan make_plan(const aquakv_layer* L, int64_t tokens) {
 // CUs, and up to how many left over from its rounds may be quantized from fp32 predictions (wide_split_rows).
 constexpr int64_t kWideRoundRows = 16384, kWideSplitRows = 12288;
 
+// The parameters that calls on a layer read.
+struct Params { Range r[8]; };
+Params params_of(const aquakv_layer* L) {
+  const size_t D = (size_t)L->kv_heads * L->head_dim, eb = elem_bytes(L->dtype), points = is_rtn(L) ? 0 : (size_t)L->n_codewords;
+  return {{{L->w_k, D * L->d_in_k * eb, "w_k"}, {L->w_v, D * L->d_in_v * eb, "w_v"},
+           {L->b_k, L->d_in_k ? D * sizeof(float) : 0, "b_k"}, {L->b_v, L->d_in_v ? D * sizeof(float) : 0, "b_v"},
+           {L->signs_k, points ? D : 0, "signs_k"}, {L->signs_v, points ? D : 0, "signs_v"},
+           {L->codebook, points * 2 * sizeof(float), "codebook"},
+           {L->search_table, points ? aquakv::kSearchTableBytes : 0, "search_table"}}};
+}
+
 // Whether `all` lies over none of the call's buffers (outs: without the workspace it is part of) nor the layer's parameters.
-bool clear_of(const aquakv_layer* L, const Plan& pl, const Range& all, const Range* outs, int n_out, const Range* ins, int n_in) {
-  const size_t D = (size_t)pl.D, points = is_rtn(L) ? 0 : (size_t)L->n_codewords;
-  const Range params[] = {{L->w_k, D * L->d_in_k * pl.eb, ""}, {L->w_v, D * L->d_in_v * pl.eb, ""}, {L->b_k, D * sizeof(float), ""},
-                          {L->b_v, D * sizeof(float), ""}, {L->signs_k, points ? D : 0, ""}, {L->signs_v, points ? D : 0, ""},
-                          {L->codebook, points * 2 * sizeof(float), ""},
-                          {L->search_table, points ? aquakv::kSearchTableBytes : 0, ""}};
-  for (const Range& r : params)
+bool clear_of(const aquakv_layer* L, const Range& all, const Range* outs, int n_out, const Range* ins, int n_in) {
+  for (const Range& r : params_of(L).r)
     if (overlap(all, r)) return false;
   for (int i = 0; i < n_out; ++i)
     if (overlap(all, outs[i])) return false;
@@ -229,7 +235,7 @@ size_t usable_workspace(const aquakv_layer* L, const Plan& pl, int64_t tokens, v
   const size_t all = need + (size_t)tokens * pl.D * sizeof(float);
   const size_t most = tokens > kWideSplitRows ? need : bytes < all ? bytes : all;
   for (const size_t n : {most, need})
-    if (n > sure && clear_of(L, pl, {workspace, n, ""}, outs, n_out, ins, n_in)) return n;
+    if (n > sure && clear_of(L, {workspace, n, ""}, outs, n_out, ins, n_in)) return n;
   return sure;
 }
 // Keys and values of `tokens` rows can run as launch_fused_layer, given room for half of its sums and, in Vhat, for the other half.
@@ -536,7 +542,7 @@ int aquakv_encode_layer(const aquakv_layer* L, int64_t tokens, const void* K, co
                               workspace_bytes, outs, 6, ins, 4);
     // (half of the sums goes where a temporary Khat would lie)
     at_once = Khat != nullptr && !is_wide(L) && layer_at_once(L, pl, tokens, V, Vhat) &&
-              clear_of(L, pl, {workspace, t * row, ""}, outs, 6, ins, 4);
+              clear_of(L, {workspace, t * row, ""}, outs, 6, ins, 4);
   }
 
   hipStream_t stream = static_cast<hipStream_t>(stream_);
@@ -601,7 +607,7 @@ int aquakv_decode_layer(const aquakv_layer* L, int64_t tokens, const uint8_t* k_
                          {k_codes, t * crow, "k_codes"}, {v_codes, want_v ? t * crow : 0, "v_codes"},
                          {k_scales, t * srow, "k_scales"}, {v_scales, want_v ? t * srow : 0, "v_scales"}};
     CHECK(check_no_alias(outs, 3, ins, 6));
-    at_once = layer_at_once(L, pl, tokens, nullptr, Vhat) && clear_of(L, pl, {workspace, t * row, ""}, outs, 2, ins, 6);
+    at_once = layer_at_once(L, pl, tokens, nullptr, Vhat) && clear_of(L, {workspace, t * row, ""}, outs, 2, ins, 6);
   }
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   float* Pbuf = static_cast<float*>(workspace);
@@ -669,29 +675,49 @@ int check_encode_layers(const aquakv_encode_entry* layers, int32_t n_layers, int
     if (workspace_bytes < pl.p_bytes + pl.khat_bytes)
       return fail(AQUAKV_EWORKSPACE, "workspace %zu B < required %zu B", workspace_bytes, pl.p_bytes + pl.khat_bytes);
   }
+  const auto add = [](CacheRange* r, int64_t& n, const void* p, size_t bytes, const char* name, int32_t layer, bool written) {
+    const uintptr_t begin = reinterpret_cast<uintptr_t>(p);
+    if (p != nullptr && bytes != 0) r[n++] = {begin, begin + bytes, name, layer, written};
+  };
+  const auto add_codes = [&](CacheRange* r, int64_t& n, int32_t l) {
+    const aquakv_encode_entry& c = layers[l];
+    const size_t crow = make_plan(c.layer, 1).code_row, srow = scale_row_bytes(c.layer);
+    add(r, n, c.k_codes, t * crow, "k_codes", l, true);
+    add(r, n, c.k_scales, t * srow, "k_scales", l, true);
+    add(r, n, c.v_codes, t * crow, "v_codes", l, true);
+    add(r, n, c.v_scales, t * srow, "v_scales", l, true);
+  };
+  const auto add_common = [&](CacheRange* r, int64_t& n) {
+    for (int i = 0; i < 4; ++i) add(r, n, hat[i], t * row, "hat", i >> 1, true);
+    add(r, n, workspace, workspace_bytes, "workspace", 0, true);
+  };
   for (int32_t l = 0; l < n_layers; ++l) {                   // a layer and the next one, with everything the call writes for all
     CacheRange r[4 + 1 + 2 * 6];
-    int n = 0;
-    const auto add = [&](const void* p, size_t bytes, const char* name, int32_t layer, bool written) {
-      const uintptr_t begin = reinterpret_cast<uintptr_t>(p);
-      if (bytes != 0) r[n++] = {begin, begin + bytes, name, layer, written};
-    };
-    for (int i = 0; i < 4; ++i) add(hat[i], t * row, "hat", i >> 1, true);
-    add(workspace, workspace_bytes, "workspace", l, true);
+    int64_t n = 0;
+    add_common(r, n);
     for (int32_t m = l; m < n_layers && m < l + 2; ++m) {
-      const aquakv_encode_entry& c = layers[m];
-      add(c.K, t * row, "K", m, false);
-      add(c.V, t * row, "V", m, false);
-      if (c.layer == nullptr) continue;
-      const size_t crow = make_plan(c.layer, 1).code_row, srow = scale_row_bytes(c.layer);
-      add(c.k_codes, t * crow, "k_codes", m, true);
-      add(c.k_scales, t * srow, "k_scales", m, true);
-      add(c.v_codes, t * crow, "v_codes", m, true);
-      add(c.v_scales, t * srow, "v_scales", m, true);
+      add(r, n, layers[m].K, t * row, "K", m, false);
+      add(r, n, layers[m].V, t * row, "V", m, false);
+      if (layers[m].layer != nullptr) add_codes(r, n, m);
     }
     CHECK(check_disjoint(r, n));
   }
-  return AQUAKV_OK;
+  // the parameters of all layers against all that is written; what a layer shares with the one before is there already
+  const std::unique_ptr<CacheRange[]> ranges(new (std::nothrow) CacheRange[4 + 1 + (size_t)n_layers * (4 + 8)]);
+  if (ranges == nullptr) return fail(AQUAKV_EINVAL, "no host memory to check %d layers", n_layers);
+  int64_t n = 0;
+  add_common(ranges.get(), n);
+  Params before = {};
+  for (int32_t l = 0; l < n_layers; ++l) {
+    if (layers[l].layer == nullptr) continue;
+    add_codes(ranges.get(), n, l);
+    const Params params = params_of(layers[l].layer);
+    for (int i = 0; i < 8; ++i)
+      if (params.r[i].p != before.r[i].p || params.r[i].n != before.r[i].n)
+        add(ranges.get(), n, params.r[i].p, params.r[i].n, params.r[i].name, l, false);
+    before = params;
+  }
+  return check_disjoint(ranges.get(), n, true);
 }
 }  // namespace
 

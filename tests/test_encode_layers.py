@@ -62,6 +62,22 @@ def test_faults_in_the_arguments_are_refused():
     B.aquakv_encode_layers(s.entries, 0, s.hat, (s.workspace, s.need))
 
 
+PARAMETERS = dict(w_k=D * D * 2, w_v=2 * D * D * 2, b_k=4 * D, b_v=4 * D, signs_k=D, signs_v=D, codebook=16 * 8,
+                  search_table=B.aquakv_search_table_bytes(16))
+
+
+@pytest.mark.parametrize("written", ["hat", "workspace", "k_codes", "v_scales"])
+@pytest.mark.parametrize("name", PARAMETERS)
+def test_nothing_is_written_over_the_parameters(name, written):
+    """The last bytes of a layer's parameter at the first byte of a buffer that the call writes, in the next layer and in one further on."""
+    for owner in (2, 4):
+        s = Stack([layer(first=True), *(layer() for _ in range(4))])
+        at = {"hat": s.hat[1], "workspace": s.workspace, "k_codes": s.entries[1][3], "v_scales": s.entries[1][6]}[written]
+        s.entries[owner][0] = layer(**{name: at - PARAMETERS[name] // 16 * 16 + 16})
+        assert s.status() == B.AQUAKV_EINVAL, owner
+        assert f"{name} of layer {owner}" in B.aquakv_last_error() and "overlaps" in B.aquakv_last_error()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("rht_group", [None, 1024])
 @pytest.mark.parametrize("tokens", [1, 31, 512, 513, 1025, 1536, 1537, 2049, 3072, 3073, 4096, 4097])
