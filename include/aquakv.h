@@ -463,8 +463,8 @@ int aquakv_encode_layers(const aquakv_encode_entry* layers, int32_t n_layers, in
  * tensors, where they are put one behind the other.  `workspace`: aquakv_attend_cache_workspace_bytes() bytes, 0 for an
  * unsupported configuration (less is enough as long as it holds the recovery's workspace and one layer's partial results: the attention of
  * a layer then runs in a launch of its own where it would otherwise run beside the recovery of the next one).  Nothing is kept from call to call.
- * Nothing that the call writes (out, hat, staged, the workspace) may overlap anything else it is given: AQUAKV_EINVAL, like every
- * other fault in the arguments before anything is launched.
+ * Nothing that the call writes (out, hat, staged, the workspace) may overlap anything else it is given, the layers' parameters among it:
+ * AQUAKV_EINVAL, like every other fault in the arguments before anything is launched.
  */
 typedef struct aquakv_cache_layer {
   const aquakv_layer* layer;              /* NULL: the layer's compressed range is held in the storage dtype */

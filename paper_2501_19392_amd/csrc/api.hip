@@ -1286,7 +1286,7 @@ int check_cache_buffers(const aquakv_cache_layer* layers, int32_t n_layers, cons
                         const int32_t* n_compressed, const int32_t* n_recent, const float* rope_cos, const float* rope_sin,
                         void* const* hat, const void* workspace, size_t workspace_used, int64_t compressed, bool adjacent) {
   const size_t row = (size_t)sh->kv_heads * 128 * elem_bytes(sh->dtype);
-  const int64_t most = (int64_t)n_layers * 14 + 7;
+  const int64_t most = (int64_t)n_layers * (14 + 8) + 7;
   const std::unique_ptr<CacheRange[]> ranges(new (std::nothrow) CacheRange[most]);
   if (ranges == nullptr) return fail(AQUAKV_EINVAL, "no host memory to check %d layers", n_layers);
   int64_t n = 0, tokens = 0;
@@ -1310,6 +1310,7 @@ int check_cache_buffers(const aquakv_cache_layer* layers, int32_t n_layers, cons
     tokens = std::max(tokens, (int64_t)n_sink[b] + n_compressed[b] + n_recent[b]);
   const size_t heads = (size_t)sh->batch * sh->q_heads * 128;
   bool hat_used[2] = {false, false};
+  Params before = {};
   for (int32_t l = 0; l < n_layers; ++l) {
     const aquakv_cache_layer& c = layers[l];
     add(c.sink_k, sink.first * row, sink.rows * row, "sink_k", l, false);
@@ -1330,6 +1331,10 @@ int check_cache_buffers(const aquakv_cache_layer* layers, int32_t n_layers, cons
     add(c.k_scales, held.first * srow, held.rows * srow, "k_scales", l, false);
     add(c.v_codes, held.first * crow, held.rows * crow, "v_codes", l, false);
     add(c.v_scales, held.first * srow, held.rows * srow, "v_scales", l, false);
+    const Params params = params_of(c.layer);
+    for (int i = 0; i < 8; ++i)                              // (what a layer shares with the one before is there already)
+      if (params.r[i].p != before.r[i].p || params.r[i].n != before.r[i].n) add(params.r[i].p, 0, params.r[i].n, params.r[i].name, l, false);
+    before = params;
     if (adjacent) continue;
     add(c.staged_k_codes, 0, compressed * crow, "staged_k_codes", l, true);
     add(c.staged_k_scales, 0, compressed * srow, "staged_k_scales", l, true);

@@ -11,7 +11,7 @@ FIELDS = ("k_codes", "k_scales", "v_codes", "v_scales")
 
 
 def layer(first=False, **kw):
-    base = 0x10000                                        # parameters: never compared, never read here
+    base = 0x10000                                        # parameters: apart from all other addresses, never read here
     d = dict(kv_heads=H, head_dim=128, vq_dim=2, n_codewords=16, dtype=B.AQUAKV_BF16, d_in_k=0 if first else D,
              d_in_v=0 if first else 2 * D, rht_group=0, codebook=base, signs_k=base, signs_v=base, w_k=base, b_k=None, w_v=base,
              b_v=None, search_table=None)
@@ -99,6 +99,26 @@ def test_what_is_written_overlaps_nothing(written, other):
     put(other, at - size // 16 * 16 + 16, 1 if other[:3] == "raw" else 0)
     assert c.status() == B.AQUAKV_EINVAL, B.aquakv_last_error()
     assert "overlaps" in B.aquakv_last_error()
+
+
+PARAMETERS = dict(w_k=D * D * 2, w_v=2 * D * D * 2, b_k=4 * D, b_v=4 * D, signs_k=D, signs_v=D, codebook=16 * 8,
+                  search_table=B.aquakv_search_table_bytes(16))
+
+
+@pytest.mark.parametrize("written", ["out", "staged_v_codes", "hat", "workspace"])
+@pytest.mark.parametrize("name", PARAMETERS)
+def test_nothing_is_written_over_the_parameters(name, written):
+    """The last bytes of a layer's parameter at the first byte of a buffer that the call writes."""
+    at = 1 << 45
+    c = Call([layer(first=True), None, layer(**{name: at - PARAMETERS[name] // 16 * 16 + 16}), layer()])
+    if written == "workspace":
+        c.workspace = at
+    elif written == "hat":
+        c.hat[3] = at
+    else:
+        setattr(c.layers[0], written, at)
+    assert c.status() == B.AQUAKV_EINVAL
+    assert f"{name} of layer 2" in B.aquakv_last_error() and "overlaps" in B.aquakv_last_error()
 
 
 @pytest.mark.parametrize("kw,want", [
