@@ -90,6 +90,33 @@ def test_fit_from_integer_products(T, d0, d1, d_out, kind):
     assert rel < 1e-9, rel
 
 
+def test_lists_that_overflow_cost_no_more_than_the_fp64_form():
+    """Half of the columns hold nothing but values that integers of three digits do not hold: counting them takes a workgroup an atomic per
+    column, not an atomic per value, so such a fit takes what one takes whose data is known not to fit before the first of them is counted
+    (the time of both is that of the fp64 form plus two passes over the data, a tenth of it; with an atomic per value it was 3.1 times as
+    long; half as long again is allowed)."""
+    from paper_2501_19392_amd import binding as B
+    T, d, d_out = 16384, 1024, 1024
+    print(f"case fit overflow T={T} d={d} d_out={d_out}", flush=True)
+    W = torch.empty(d_out, d, dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(B.aquakv_fit_workspace_bytes(d, d_out), dtype=torch.uint8, device="cuda")
+    Y = _columns("gauss", T, d_out, torch.Generator().manual_seed(1)).cuda()
+    times = {}
+    for kind in ("tiny column", "many small"):
+        X = _columns(kind, T, d, torch.Generator().manual_seed(2)).cuda()
+        best = []
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            B.aquakv_fit_predictor(torch.bfloat16, T, X, d, None, 0, Y, d_out, 1e-2, W, None, ws)
+            end.record()
+            torch.cuda.synchronize()
+            best.append(start.elapsed_time(end))
+        times[kind] = min(best)
+    print(times, flush=True)
+    assert times["many small"] < 1.5 * times["tiny column"], times
+
+
 def test_fit_of_infinities_is_nan_in_both_forms():
     from paper_2501_19392_amd import binding as B
     T, d, d_out = 2560, 256, 128
