@@ -6,8 +6,9 @@
 // v_mfma_i32_32x32x32_i8 and put together in int64, where no sum of up to 2^20 tokens rounds or overflows, and which comes out the same in any
 // order of additions.  Values more than 13 binades below their column's largest (of Gaussian columns 3 to 6 in 10000) are rounded to the
 // nearest q; what is left of them is listed per column and enters in fp64 with the single rounding of the sum (finish_kernel).  So the result is closer
-// to the exact one than a sum in fp64, whose every step rounds.  Where a list would overflow, or a column holds infinities, NaNs or nothing
-// but values too small to be scaled, a flag sends the whole product to the fp64 kernel of calibrate.hip.
+// to the exact one than a sum in fp64, whose every step rounds.  Where a list would overflow, the lists cost more than the integers gain
+// (list_cost_limit), or a column holds infinities, NaNs or nothing but values too small to be scaled, a flag sends the whole product to the fp64
+// kernel of calibrate.hip.
 //
 // A fit of 65536 tokens, 2048 inputs and 1024 outputs 9.20 -> 3.40 ms (Gram products 8.1 -> 2.2: the products 1.90, the two passes that find
 // scales and lists 0.17, finish_kernel 0.14), 65536 x 1024 inputs 3.58 -> 1.41, 16384 x 2048 3.13 -> 1.68, 4096 x 1024 0.72 -> 0.62.
@@ -164,12 +165,34 @@ __global__ __launch_bounds__(256) void list_kernel(const Columns x, int64_t toke
   });
 }
 
-// Lists in the order of their tokens, so that the sums over them do not depend on the order of arrival: one workgroup per column
+// Lists in the order of their tokens, so that the sums over them do not depend on the order of arrival: one workgroup per column.  The
+// last workgroup finds what finish_kernel will take for all of them; the product is the fp64 kernel's work if that is more than `most`.
+struct ListCost {
+  unsigned long long walks;                                            // entries, each once for every block that goes through its list
+  uint32_t four;                                                       // entries of four neighbouring columns (a wave's in a block)
+};
 __global__ __launch_bounds__(256) void sort_kernel(int d, int columns, const uint32_t* __restrict__ count, double* __restrict__ G,
-                                                   const int* __restrict__ flag) {
+                                                   int* __restrict__ flag, const ListCost most) {
   __shared__ uint32_t token[kMaxListed];
+  if ((int)blockIdx.x == columns) {
+    __shared__ ListCost all;
+    if (threadIdx.x == 0) all = {0, 0};
+    __syncthreads();
+    const uint32_t nd = d / 64, nr = (columns - d) / 64;
+    ListCost own = {0, 0};
+    for (int c = 4 * threadIdx.x; c < columns; c += 4 * 256) {
+      const uint32_t n = count[c] + count[c + 1] + count[c + 2] + count[c + 3];
+      own.walks += (unsigned long long)n * (c < d ? nd + 1 + nr : nd);
+      own.four = n > own.four ? n : own.four;
+    }
+    atomicAdd(&all.walks, own.walks);
+    atomicMax(&all.four, own.four);
+    __syncthreads();
+    if (threadIdx.x == 0 && (all.walks > most.walks || all.four > most.four)) *flag = 1;
+    return;
+  }
   const int c = blockIdx.x, n = (int)count[c];
-  if (*flag != 0 || n < 2) return;                                     // (n is at most the room where the flag is not set)
+  if (n < 2 || n > listed_room(d, columns)) return;                    // (more than the room: the flag is set, and nothing reads the list)
   for (int i = threadIdx.x; i < n; i += 256) token[i] = *listed(G, d, columns, c, i);
   __syncthreads();
   for (int i = threadIdx.x; i < n; i += 256) {
@@ -480,6 +503,19 @@ bool exact_gram_fits(int64_t tokens, int d0, int d1, int d_out) {
          listed_room(d0 + d1, (int)columns) > 0;
 }
 
+// What lists may cost: as much as the integers gain.  The fp64 kernel's and the integer kernel's time differ by 88 ps a token and 64 x 64 block (of
+// at least 256 blocks, as many as there are CUs), less 45 us for the launches around the product.  finish_kernel takes 37 ps for an entry of
+// a list and block (9.5 ns of a CU), and 0.3 us for an entry of four neighbouring columns, which a wave goes through in turn while its block
+// shares the CU with other columns' lists (columns apart from others: 0.1).  Gaussian columns have 2 to 26 entries and stay far below.
+// us, n entries in every column, integers / where the line is / behind it, fp64 sums and the passes in vain (without passes): 16384 tokens, 2048
+// inputs, 1024 outputs 1625 + 4.3 n / n = 290 / 3250 to 3350 (3130); 4096 tokens, 1024 and 1024 600 + 1.4 n / 51 / 741 to 768 (711); 4096 tokens,
+// 256 and 128 162 + 0.9 n / 39 / 252 to 265 (233).  With the room in the lists as the only line 800 entries took 5226 in the first of these.
+static ListCost list_cost_limit(int64_t tokens, int d, int d_out) {
+  const int64_t nd = d / 64, blocks = nd * (nd + 1) / 2 + nd * (d_out / 64);
+  const double us = 88e-6 * (double)tokens * (double)(blocks > 256 ? blocks : 256) - 45.0;
+  return us > 0 ? ListCost{(unsigned long long)(us / 37e-6), (uint32_t)(us / 0.3)} : ListCost{0, 0};
+}
+
 hipError_t launch_exact_gram(int64_t tokens, const void* x0, int d0, const void* x1, int d1, const void* Y, int d_out, double* G, void* columns,
                              int* flag, hipStream_t stream) {
   const Columns x = {static_cast<const bf16_t*>(x0), static_cast<const bf16_t*>(x1), static_cast<const bf16_t*>(Y), d0, d1, d_out};
@@ -489,7 +525,7 @@ hipError_t launch_exact_gram(int64_t tokens, const void* x0, int d0, const void*
   const dim3 grid(all / 128, (unsigned)((tokens + 16 * kScanRows - 1) / (16 * kScanRows)));
   largest_kernel<<<grid, 256, 0, stream>>>(x, tokens, largest);
   list_kernel<<<grid, 256, 0, stream>>>(x, tokens, largest, count, G, flag);
-  sort_kernel<<<all, 256, 0, stream>>>(d, all, count, G, flag);
+  sort_kernel<<<all + 1, 256, 0, stream>>>(d, all, count, G, flag, list_cost_limit(tokens, d, d_out));
   exact_gram_kernel<<<256, kExactThreads, 0, stream>>>(x, tokens, largest, G, flag);
   const int nd = d / 64;
   finish_kernel<<<nd * (nd + 1) / 2 + nd * (d_out / 64), 1024, 0, stream>>>(x, largest, count, G, flag);
