@@ -418,7 +418,7 @@ TileArgs tensor_args(const FusedTensor& t, const float* codebook, int64_t T, int
   return a;
 }
 
-// Rows per tile for values and keys of T rows in one launch (launch_fused_decode_pair), 0: two launches are as good.
+// Rows per tile for values and keys of T rows in one launch (launch_fused_decode_attend with n = 2, launch_fused_encode_pair), 0: two launches are as good.
 //
 // A launch for one tensor of few rows is bound by the latency of its k-tiles and leaves CUs idle, so the other tensor's tiles come
 // for little: the smallest tile with which both fit the CUs in one round (3072 rows of 8 heads on 192).  Attention over a cache of six
@@ -433,6 +433,14 @@ int pair_rows(int64_t T, int D) {
     if (2 * ((T + rows - 1) / rows) * H <= 256) return rows;
   return 0;
 }
+// Decode goes on with one and a half rounds of 128 rows where 192 do not fit, for head counts that are no power of two (for those both end
+// at the same rows).  Eight layers, us a token, 192 rows or none / with them: 3 heads 8068 tokens 204 / 170, 8192 184 / 163; 5 heads, 4804
+// 250 / 221; 6 heads, 4036 228 / 211; 12 heads, 1925 353 / 340, 2048 326 / 335; 24 heads, 1024 635 / 607.  Encoding, 3, 5, 6, 12 and 24
+// heads: 200 / 202, 248 / 255, 261 / 260, 354 / 376, 688 / 657.
+int decode_pair_rows(int64_t T, int D) {
+  const int rows = pair_rows(T, D);
+  return rows == 0 && 2 * ((T + 127) / 128) * (D / BN) <= 384 ? 128 : rows;
+}
 
 // What a decode launch with attention behind its tiles runs on, for n tensors of T rows: rows of a tile, 0: no such launch.
 //
@@ -444,7 +452,7 @@ int pair_rows(int64_t T, int D) {
 // do: they leave more CUs to the pieces (4 x 1800 tokens 517 to 532 us against 527 to 536).
 constexpr int64_t kAttendTiles = 224;
 int attend_rows(int64_t T, int D, int n) {
-  if (n == 2) return pair_rows(T, D);
+  if (n == 2) return decode_pair_rows(T, D);
   const int rows = tile_rows(1, T, D, true);
   if (rows == 320 || (rows == 0 && two_heads_pays(T, D))) return 0;
   const int64_t each = rows == 0 || rows == 192 ? BM : rows;
@@ -452,8 +460,11 @@ int attend_rows(int64_t T, int D, int n) {
 }
 }  // namespace
 
-bool fused_decode_pair_pays(int64_t T, int D) { return pair_rows(T, D) != 0; }
-int64_t fused_decode_pair_rows(int D) { return 256 / 2 / (D / BN) * 192; }
+bool fused_decode_pair_pays(int64_t T, int D) { return decode_pair_rows(T, D) != 0; }
+int64_t fused_decode_pair_rows(int D) {
+  const int64_t H = D / BN, rows_192 = 128 / H * 192, rows_128 = 192 / H * 128;
+  return rows_192 > rows_128 ? rows_192 : rows_128;
+}
 bool fused_decode_attend_fits(int64_t T, int D) { return attend_rows(T, D, 1) != 0; }
 hipError_t launch_fused_decode_attend(int n_codewords, const FusedTensor* tensors, const float* const* codebooks, int n, int64_t T, int D,
                                       bool wide, const AttendCacheArgs& attend, hipStream_t stream) {
@@ -479,7 +490,7 @@ hipError_t launch_fused_decode_attend(int n_codewords, const FusedTensor* tensor
   return hipGetLastError();
 }
 
-// The same rule for encoding.  Stack of 8 layers, 16 points, us, a layer at a time / values and next keys together: 128 rows 142 / 105,
+// pair_rows for encoding.  Stack of 8 layers, 16 points, us, a layer at a time / values and next keys together: 128 rows 142 / 105,
 // 512 151 / 114, 1024 176 / 145, 1100 194 / 168 (178 on tiles of 128 rows), 2048 223 / 193; on 192 rows / 128: 2304 231 / 248, 2560 237 / 248;
 // on 192 rows / a layer at a time: 2800 244 / 260, 3072 250 / 266.
 bool fused_encode_pair_pays(int64_t T, int D) { return pair_rows(T, D) != 0; }

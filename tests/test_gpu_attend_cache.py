@@ -147,6 +147,7 @@ def test_values_and_next_keys_recovered_together(n, rht_group):
 @pytest.mark.parametrize("H,QH,lengths,rht_group", [
     (8, 24, [69], None), (8, 8, [130, 700], 1024),              # two tensors on tiles of 32 and of 64 rows
     (8, 16, [1400], 1024), (8, 32, [2700], None),              # of 96 and of 192 rows
+    (3, 6, [8180], None),                                       # on 128 rows, more tiles than CUs
     (1, 3, [4229], None),                                       # 67 pieces, two to a workgroup: the last one has one
     (8, 64, [3300], 1024), (8, 32, [2600, 4, 2300], None)])     # one tensor on tiles of 128 and of 256 rows
 def test_attention_beside_the_recovery_of_the_next_layer(H, QH, lengths, rht_group):
