@@ -114,9 +114,9 @@ def test_attend_refuses_what_does_not_fit():
 
 
 @pytest.mark.parametrize("rht_group", [None, 1024])
-@pytest.mark.parametrize("n", [1029, 1500, 2150, 3060, 3300])
+@pytest.mark.parametrize("n", [1029, 1500, 1700, 2052, 2150, 3060, 3300])
 def test_values_and_next_keys_recovered_together(n, rht_group):
-    """Few compressed tokens: the values of a layer and the keys of the next one in one launch, on tiles of 64, 96 and 192 rows (and
+    """Few compressed tokens: the values of a layer and the keys of the next one in one launch, on tiles of 64, 96, 128 and 192 rows (and
     not at all at the last length), layers of other quantizers and a 16-bit layer between them: the last two layers' recovered
     tensors have the bits of the sweep, and every layer the attention over the tensors of the sweep."""
     from paper_2501_19392_amd.cache import AquaKVCache
@@ -147,12 +147,13 @@ def test_values_and_next_keys_recovered_together(n, rht_group):
 @pytest.mark.parametrize("H,QH,lengths,rht_group", [
     (8, 24, [69], None), (8, 8, [130, 700], 1024),              # two tensors on tiles of 32 and of 64 rows
     (8, 16, [1400], 1024), (8, 32, [2700], None),              # of 96 and of 192 rows
+    (8, 24, [1800], 1024), (8, 32, [1100, 900], None),          # of 128 rows
     (3, 6, [8180], None),                                       # on 128 rows, more tiles than CUs
     (1, 3, [4229], None),                                       # 67 pieces, two to a workgroup: the last one has one
     (8, 64, [3300], 1024), (8, 32, [2600, 4, 2300], None)])     # one tensor on tiles of 128 and of 256 rows
 def test_attention_beside_the_recovery_of_the_next_layer(H, QH, lengths, rht_group):
-    """Same bits as with attention in launches of its own, which a workspace without the third place for keys gives where two tensors are
-    recovered at once; attention over the tensors of the sweep in every case."""
+    """Two tensors: same bits as with attention in launches of its own, which a workspace without the third place for keys gives.  One
+    tensor (the last two cases): the same call twice.  In every case attention over the tensors of the sweep."""
     from paper_2501_19392_amd import binding as B
     from paper_2501_19392_amd.cache import AquaKVCache
     print(f"case attention beside recovery H={H} QH={QH} lengths={lengths} group={rht_group}", flush=True)
