@@ -114,7 +114,7 @@ __global__ __launch_bounds__(256) void largest_kernel(const Columns x, int64_t t
 // entry, 65536 tokens, 2048 inputs, 1024 outputs, ms, fp64 sums alone / before / now: half of the columns small but for one token 9.21 / 28.9 /
 // 9.36, a tenth of all values small 9.21 / 12.8 / 9.39, an infinity in one column 8.90 / 9.99 / 9.07; nothing but lists of 50 entries 3.38 / 3.43,
 // 4096 tokens, 256 inputs, 128 outputs 0.255 / 0.204.
-__global__ __launch_bounds__(256) void list_kernel(const Columns x, int64_t tokens, const uint32_t* __restrict__ largest,
+__global__ __launch_bounds__(256, 8) void list_kernel(const Columns x, int64_t tokens, const uint32_t* __restrict__ largest,
                                                    uint32_t* __restrict__ count, double* __restrict__ G, int* __restrict__ flag) {
   __shared__ int entries[128], first[128];                             // of the workgroup's columns; where they start in the lists, or -1
   if (threadIdx.x < 128) entries[threadIdx.x] = 0;
@@ -132,14 +132,17 @@ __global__ __launch_bounds__(256) void list_kernel(const Columns x, int64_t toke
     }
     if (bad) *flag = 1;
     uint32_t listed_rows[8] = {};                                      // bit n: row n
+#pragma unroll 1
+    for (int n0 = 0; n0 < kScanRows; n0 += 8) {                        // (16 rows in flight take 88 registers, five waves per SIMD and not eight)
 #pragma unroll
-    for (int n = 0; n < kScanRows; ++n) {
-      const int64_t t = t0 + n * 16;
-      const u32x4 v = *reinterpret_cast<const u32x4*>(p + (t < tokens ? t : tokens - 1) * ld);
+      for (int n = n0; n < n0 + 8; ++n) {
+        const int64_t t = t0 + n * 16;
+        const u32x4 v = *reinterpret_cast<const u32x4*>(p + (t < tokens ? t : tokens - 1) * ld);
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const uint32_t m = (k & 1 ? v[k >> 1] >> 16 : v[k >> 1]) & 0x7fffu;
-        listed_rows[k] |= (m < least[k] && m != 0 && t < tokens ? 1u : 0u) << n;
+        for (int k = 0; k < 8; ++k) {
+          const uint32_t m = (k & 1 ? v[k >> 1] >> 16 : v[k >> 1]) & 0x7fffu;
+          listed_rows[k] |= (m < least[k] && m != 0 && t < tokens ? 1u : 0u) << n;
+        }
       }
     }
     const int column = (int)(threadIdx.x & 15) * 8;
@@ -166,7 +169,7 @@ __global__ __launch_bounds__(256) void list_kernel(const Columns x, int64_t toke
 }
 
 // Lists in the order of their tokens, so that the sums over them do not depend on the order of arrival: one workgroup per column.  The
-// last workgroup finds what finish_kernel will take for all of them; the product is the fp64 kernel's work if that is more than `most`.
+// first workgroup finds what finish_kernel will take for all of them; the product is the fp64 kernel's work if that is more than `most`.
 struct ListCost {
   unsigned long long walks;                                            // entries, each once for every block that goes through its list
   uint32_t four;                                                       // entries of four neighbouring columns (a wave's in a block)
@@ -174,14 +177,16 @@ struct ListCost {
 __global__ __launch_bounds__(256) void sort_kernel(int d, int columns, const uint32_t* __restrict__ count, double* __restrict__ G,
                                                    int* __restrict__ flag, const ListCost most) {
   __shared__ uint32_t token[kMaxListed];
-  if ((int)blockIdx.x == columns) {
+  if (blockIdx.x == 0) {
     __shared__ ListCost all;
     if (threadIdx.x == 0) all = {0, 0};
     __syncthreads();
     const uint32_t nd = d / 64, nr = (columns - d) / 64;
     ListCost own = {0, 0};
+#pragma unroll 4
     for (int c = 4 * threadIdx.x; c < columns; c += 4 * 256) {
-      const uint32_t n = count[c] + count[c + 1] + count[c + 2] + count[c + 3];
+      const u32x4 v = *reinterpret_cast<const u32x4*>(count + c);
+      const uint32_t n = v.x + v.y + v.z + v.w;
       own.walks += (unsigned long long)n * (c < d ? nd + 1 + nr : nd);
       own.four = n > own.four ? n : own.four;
     }
@@ -191,7 +196,7 @@ __global__ __launch_bounds__(256) void sort_kernel(int d, int columns, const uin
     if (threadIdx.x == 0 && (all.walks > most.walks || all.four > most.four)) *flag = 1;
     return;
   }
-  const int c = blockIdx.x, n = (int)count[c];
+  const int c = (int)blockIdx.x - 1, n = (int)count[c];
   if (n < 2 || n > listed_room(d, columns)) return;                    // (more than the room: the flag is set, and nothing reads the list)
   for (int i = threadIdx.x; i < n; i += 256) token[i] = *listed(G, d, columns, c, i);
   __syncthreads();
