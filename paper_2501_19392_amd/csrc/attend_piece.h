@@ -108,8 +108,8 @@ template <> struct Row<float> {
 // CU, where 166 left room for three).  8 kv heads, in a trace: four sequences of up to 1800 tokens, 32 query heads, rotary embedding
 // 11.3 us (13.1 with all four scores in every lane and 166 registers), 8000 tokens of 24 query heads 10.7 (13.7), 8 x 1000 tokens
 // of 64 query heads 17.5 (20.6).  200 tokens: 6.7 us, which is launch and memory latency.
-// `a`: the arguments where the launch put them, found with kernel_args below (a reference to a kernel's parameter would put a copy
-// into scratch, because its arrays are indexed).
+// `a`: the arguments where the launch put them, found with __builtin_amdgcn_kernarg_segment_ptr (a reference to a kernel's parameter would
+// put a copy into scratch, because its arrays are indexed).
 typedef const __attribute__((address_space(4))) AttendCacheArgs AttendCacheParam;
 template <typename T>
 __device__ __forceinline__ void attend_piece(AttendCacheParam& a, int item, int tid, bool active, AttendLds& lds) {

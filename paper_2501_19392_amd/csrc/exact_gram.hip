@@ -4,14 +4,15 @@
 // column's unit set 13 binades below its largest exponent almost every value is an integer q of at most 22 bits, which three signed
 // digits of 8 bits hold: q = d0 + 2^8 d1 + 2^16 d2.  The nine digit products of two columns are summed in int32 by
 // v_mfma_i32_32x32x32_i8 and put together in int64, where no sum of up to 2^20 tokens rounds or overflows, and which comes out the same in any
-// order of additions.  Values more than 13 binades below their column's largest (of Gaussian columns 3 to 6 in 10000) are rounded to the
+// order of additions.  (Products of floating-point matrices by way of slices whose products are exact: Ozaki, Ogita, Oishi and Rump, Numerical
+// Algorithms 59, 2012; on integer matrix units: Ootomo, Ozaki and Yokota, 2024.)  Values more than 13 binades below their column's largest (of Gaussian columns 3 to 6 in 10000) are rounded to the
 // nearest q; what is left of them is listed per column and enters in fp64 with the single rounding of the sum (finish_kernel).  So the result is closer
 // to the exact one than a sum in fp64, whose every step rounds.  Where a list would overflow, the lists cost more than the integers gain
 // (list_cost_limit), or a column holds infinities, NaNs or nothing but values too small to be scaled, a flag sends the whole product to the fp64
 // kernel of calibrate.hip.
 //
-// A fit of 65536 tokens, 2048 inputs and 1024 outputs 9.20 -> 3.40 ms (Gram products 8.1 -> 2.2: the products 1.90, the two passes that find
-// scales and lists 0.17, finish_kernel 0.14), 65536 x 1024 inputs 3.58 -> 1.41, 16384 x 2048 3.13 -> 1.68, 4096 x 1024 0.72 -> 0.62.
+// A fit of 65536 tokens, 2048 inputs and 1024 outputs 9.23 -> 3.24 ms (Gram products 8.1 -> 2.2: the products 1.89, the two passes that find
+// scales and lists 0.17, finish_kernel 0.14), 65536 x 1024 inputs 3.56 -> 1.35, 16384 x 2048 3.13 -> 1.62, 4096 x 1024 0.71 -> 0.61.
 #include "device_utils.h"
 #include "kernels.h"
 
@@ -220,7 +221,8 @@ __global__ __launch_bounds__(256) void sort_kernel(int d, int columns, const uin
 // outputs: five accumulators (powers of 2^8) of two blocks, 160 registers, 36 instructions of 32 cycles.  Nothing else would fit beside a second
 // set of operands, so a register is read again as soon as its last instruction has been issued, and all other work is placed between the
 // matrix instructions, with the step's one barrier six of them behind the last store (8 % fewer cycles than next to it).
-// Matrix cores busy in 0.64 of the cycles, at 1.86 GHz: 2.69 POPS; a form with operands read at the start of their 32 tokens took 0.52 at 2.0 GHz.
+// 16384 tokens, 2048 inputs, 1024 outputs: matrix cores busy in 0.65 of the cycles, at 1.90 GHz, 2.58 POPS; 65536 tokens 2.70 POPS.  A form with operands
+// read at the start of their 32 tokens: busy in 0.52, at 2.0 GHz.
 // int32 holds 65535 tokens of any digits: segments of at most kMaxSteps steps.
 constexpr int kMfma = 0x008, kValu = 0x002, kLdsRead = 0x100, kLdsWrite = 0x200;      // kinds for sched_group_barrier
 constexpr int kExactThreads = 512, kStepTokens = 64, kMaxSteps = 512, kTile = 128;

@@ -371,11 +371,16 @@ hipError_t launch(int n_codewords, const void* x0, int d0, const void* x1, int d
 // 0: the tiles of 256 rows x one or two heads.
 //
 // A CU holds one workgroup, so what counts is the rounds of workgroups over the CUs and the rows of a round.  Ranges that
-// fill the chip in one round take the smallest tile that still does: keys and values of 1024 tokens x 8 heads 23.6 us to encode
-// on 32 rows, 27.0 on 64, 38.8 on 128 (decode 19.1, 22.3, 30.7); 2048 tokens 28.7 on 64 against 39.5 on 128 (24.3 against 31.1);
-// 2100 tokens 33.0 on 96 against 39.8 on 128 (30.6 against 34.8), 3072 tokens 35.4 against 41.4 (30.7 against 32.8); 4096 tokens, a tensor at a time: 20.6 / 28.8 on 128 against 26.1 / 35 on 256.  192 rows fill the CUs better than 256 up to 6144 tokens: encode of 4200
-// tokens 57.4 against 63.3 us, 6144 64.2 against 67.4, decode 47.4 against 50.5 and 52.7 against 52.5; predictions alone, whose large tile has two heads,
-// gain more (groups across the heads, encode of 5376 tokens 82.8 against 100.2, decode 55.5 against 57.9).  Beyond that 320 rows x one head fill the gap where the tiles of 256
+// fill the chip in one round take the smallest tile that still does.  Keys and values x 8 heads, us:
+//   1024 tokens  encode 23.6 on 32 rows, 27.0 on 64, 38.8 on 128 (decode 19.1, 22.3, 30.7)
+//   2048         28.7 on 64, 39.5 on 128 (24.3, 31.1)
+//   2100         34.1 on 96, 39.8 on 128 (28.7, 31.4); 3072 39.2, 41.9 (32.4, 32.7)
+//   4096         a tensor at a time 20.6 / 28.8 on 128, 26.1 / 35 on 256
+//   4200         55.1 on 192, 59.4 on 256 (44.4, 44.7); 6144 61.9, 66.2 (51.5, 50.8); groups across the heads, whose predictions have a large
+//                tile of two heads, 76.6, 98.0 (49.6, 52.9) and 86.0, 101.4 (57.1, 58.6)
+// The scoring calls gain on all of them, a sequence or many: 2600 tokens with the rotary embedding 13.7 on 96, 15.5 on 128, 32 x 96 14.8, 15.8, 4 x 700
+// 14.4, 14.9; 4200 tokens 21.0 on 192, 23.6 on 256, 6144 24.1, 25.1, 4 x 1300 22.8, 26.5, 16 x 384 24.5, 27.0; groups across the heads 5 to 20 %.
+// Beyond that 320 rows x one head fill the gap where the tiles of 256
 // rows start a round they hardly use (10007 tokens: 41.1 / 57.8 us against 45.6 / 62.4; 20000 tokens: 81 / 115 against
 // 87 / 122): taken when its rounds cost less, a round being 41 us on 320 rows, 29 us on 256 rows (33 the first) and 54 us on
 // 256 rows x two heads (K = 1024, encode).  Decode has the same proportions, keys and values together, against tiles of 256 rows

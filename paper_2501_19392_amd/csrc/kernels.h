@@ -96,24 +96,25 @@ struct FusedTensor {
   void* Xhat;
 };
 bool fused_layer_fits(int64_t T, int D);
-// Values of one layer and keys of the next one (which need nothing of those values), decoded in one launch; same quantizer.
+hipError_t launch_fused_layer(bool encode, int n_codewords, const float* codebook, const void* table, const FusedTensor& keys,
+                              const FusedTensor& values, void* sums, int64_t T, int D, bool wide, hipStream_t stream);
+// Values of one layer and keys of the next one (which need nothing of those values), of one quantizer (bf16).
+// Decode of both in one launch where it pays:
 bool fused_decode_pair_pays(int64_t T, int D);
 int64_t fused_decode_pair_rows(int D);      // the most rows for which it does
-// Decode of n = 1 or 2 (where fused_decode_pair_pays) such tensors, with attention over a layer recovered before on the CUs that it
-// leaves idle or free early (bf16; no pieces: none).  n = 1: where fused_decode_attend_fits.
-// The same two tensors encoded (bf16): fused with the quantizer in one launch where it pays, tables and codebooks of their own; and the
-// predictions of both in one launch (`out` as in launch_tile_predict), of up to tile_predict_pair_rows() rows.
-bool fused_encode_pair_pays(int64_t T, int D);
-hipError_t launch_fused_encode_pair(int n_codewords, const FusedTensor* tensors, const float* const* codebooks, const void* const* tables,
-                                    int64_t T, int D, hipStream_t stream);
-int64_t tile_predict_pair_rows(int D);
-hipError_t launch_tile_predict_pair(const FusedTensor* tensors, const Prediction* out, int64_t T, int D, hipStream_t stream);
+// Decode of n = 1 or 2 (where fused_decode_pair_pays) tensors, with attention over a layer recovered before on the CUs that it
+// leaves idle or free early (no pieces: none).  n = 1: where fused_decode_attend_fits.
 struct AttendCacheArgs;
 bool fused_decode_attend_fits(int64_t T, int D);
 hipError_t launch_fused_decode_attend(int n_codewords, const FusedTensor* tensors, const float* const* codebooks, int n, int64_t T, int D,
                                       bool wide, const AttendCacheArgs& attend, hipStream_t stream);
-hipError_t launch_fused_layer(bool encode, int n_codewords, const float* codebook, const void* table, const FusedTensor& keys,
-                              const FusedTensor& values, void* sums, int64_t T, int D, bool wide, hipStream_t stream);
+// Encode of both, fused with the quantizer in one launch where it pays, with tables and codebooks of their own:
+bool fused_encode_pair_pays(int64_t T, int D);
+hipError_t launch_fused_encode_pair(int n_codewords, const FusedTensor* tensors, const float* const* codebooks, const void* const* tables,
+                                    int64_t T, int D, hipStream_t stream);
+// The predictions of both in one launch (`out` as in launch_tile_predict), of up to tile_predict_pair_rows() rows:
+int64_t tile_predict_pair_rows(int D);
+hipError_t launch_tile_predict_pair(const FusedTensor* tensors, const Prediction* out, int64_t T, int D, hipStream_t stream);
 
 // The same on tiles of 256 tokens x two heads (D a multiple of 256; wide: decode only): same bits, a faster main
 // loop, half as many workgroups.  launch_fused_encode / _decode / _scores take this form by themselves for ranges that
