@@ -66,20 +66,18 @@ __device__ __forceinline__ void fused_body(
   Lds& cl = *reinterpret_cast<Lds*>(smem);
   unsigned char* const park = smem + sizeof(Lds);          // the parked tile, each wave its own rows
   const bool use_table = MODE == kEncode && table != nullptr;
-  // grid and cell table: requested now, kept in registers while the main loop owns the LDS
+  // grid and cell table: requested from inside the main loop, kept in registers while it owns the LDS
   static_assert(NCW <= WAVES * 64, "one grid point per thread");
   constexpr int kGridPoints = is_rtn(NCW) ? 0 : NCW;
   float cb_a = 0.f, cb_b = 0.f;
   TableRegs<WAVES * 64> table_regs;
-  if (threadIdx.x < kGridPoints) { cb_a = codebook[2 * threadIdx.x]; cb_b = codebook[2 * threadIdx.x + 1]; }
-  if (use_table) table_regs.request(table);
   const auto stage_tables = [&] {
     if (threadIdx.x < kGridPoints) cl.cb[threadIdx.x] = make_float4(cb_a, cb_b, -0.5f * (cb_a * cb_a + cb_b * cb_b), 0.f);
     if (use_table) table_regs.store(cl.table);
   };
 
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int H = D / BN;
   const int logical = remap_block(block, nblocks);
   const int tile_m = logical / H, head = logical % H;
@@ -90,7 +88,6 @@ __device__ __forceinline__ void fused_body(
   constexpr int kRowsPerWave = MI * 32;
   const int q = lane & 3;                          // position in the quad that owns a group
   QueryStage queries = {};                         // scores: the queries of the tile's kv head, via LDS (no cell table in that mode)
-  if constexpr (MODE == kScores) queries.request(qv, m0, BM, T, seq_len, q_heads, head * (q_heads / H), q_heads / H);
 
   // What the epilogue reads from global memory (rows to quantize, or codes and scales) is
   // requested from inside the main loop, when its own last operand loads are out, so the
@@ -123,8 +120,22 @@ __device__ __forceinline__ void fused_body(
   // in the layout of the A operand of the 16x16x32 matrix instruction; slots beyond the group's heads stay zero.
   // The launcher guarantees seq_len % BM == 0, so a tile lies inside one sequence and has no rows beyond T.
   u32x4 wreg[2] = {};
-  f32x16 acc[MI][4];
-  gemm_mainloop<WAVES>(smem, x0, d0, x1, d1, W, T, m0, n0, acc, [&] {
+  using Loop = TileLoop<BM / 32>;
+  using S = Tile<BM / 32>;
+  static_assert(WAVES == S::kWaves && S::kLdsBytes <= kFusedLdsBytes, "the main loop's workgroup");
+  f32x16 acc[S::MI][S::NJ];
+  const int last = (int)(T - 1 - m0 < BM - 1 ? T - 1 - m0 : BM - 1);
+  Loop::run(smem, x0 + m0 * d0, d0, d1 ? x1 + m0 * d1 : x1, d1, W + (int64_t)n0 * (d0 + d1), d0 + d1, last, acc, [&] {
+#pragma unroll
+    for (int i = 0; i < S::MI; ++i)
+#pragma unroll
+      for (int j = 0; j < S::NJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  }, [&] {
+    if (threadIdx.x < kGridPoints) { cb_a = codebook[2 * threadIdx.x]; cb_b = codebook[2 * threadIdx.x + 1]; }
+    if (use_table) table_regs.request(table);
+    if constexpr (MODE == kScores) queries.request(qv, m0, BM, T, seq_len, q_heads, head * (q_heads / H), q_heads / H);
 #pragma unroll
     for (int pass = 0; pass < kPasses; ++pass) fetch(pass, in[pass]);
     if constexpr (kWideGrid) fetch_wide(0, wide_codes);
@@ -140,17 +151,24 @@ __device__ __forceinline__ void fused_body(
     }
   });
 
-  // the LDS is free again: grid and table, then the tile (+ bias) parked row-major in fp32, each wave its own rows
+  // the LDS is free again: grid and table, and the tile (+ bias) parked row-major in fp32
+  __syncthreads();
   stage_tables();
   float* const q_lds = reinterpret_cast<float*>(cl.table);
   if constexpr (MODE == kScores) queries.store(q_lds, q_heads / H);
   float* wl = reinterpret_cast<float*>(park) + wave * kRowsPerWave * kLdP;
-  {
-    float bv[4];
+  if (wave < kMulWaves) {
+    const int wm = wave / S::WN, wn = wave % S::WN, frow = lane & 31, fk = lane >> 5;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) bv[j] = bias != nullptr ? bias[n0 + j * 32 + (lane & 31)] : 0.f;
+    for (int j = 0; j < S::NJ; ++j) {
+      const int col = S::block_col(j, wn) + frow;
+      const float bv = bias != nullptr ? bias[n0 + col] : 0.f;
 #pragma unroll
-    for (int i = 0; i < MI; ++i) park_block(wl + i * 32 * kLdP, acc[i], bv, lane);
+      for (int i = 0; i < S::MI; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          reinterpret_cast<float*>(park)[(S::block_row(i, wm) + (r >> 2) * 8 + fk * 4 + (r & 3)) * kLdP + park_col(col)] = acc[i][j][r] + bv;
+    }
   }
   __syncthreads();
 

@@ -43,6 +43,7 @@ struct TileArgs {
   // sums of a product over the first part of its inputs, in two halves of 16 bits, [T, D] each
   uint16_t* sums_hi;
   uint16_t* sums_lo;
+  int xcd_groups;                  // tile_of
 };
 // Two products in one launch: the first `blocks` workgroups work on job[0], the others on job[1], or (tiles of 32 rows) store the
 // sums of job[1] and nothing else if it has a place for them.
@@ -59,13 +60,40 @@ struct TileAttend {
   int tiles;
   AttendCacheArgs attend;
 };
+// Which tile a workgroup works on.  Consecutive workgroups go to consecutive XCDs, each with an L2 of its own that fetches the x rows and
+// the rows of W of its tiles once.  The row blocks are split into 8 / n groups and the heads into n, one of each to an XCD, n = xcd_head_groups,
+// the split that fetches least; 0 where none comes out even: heads in the plain order.
+inline int xcd_head_groups(int64_t row_blocks, int H, int rows) {
+  int best = 0;
+  int64_t least = 0;
+  for (const int n : {1, 2, 4, 8}) {
+    const int64_t rows_fetched = row_blocks * n / 8 * rows + H / n * kGroup;
+    if (H % n == 0 && row_blocks % (8 / n) == 0 && (best == 0 || rows_fetched < least)) { best = n; least = rows_fetched; }
+  }
+  return best;
+}
+__device__ __forceinline__ void tile_of(int block, int H, int n, int& tile_m, int& head) {
+  if (n == 0) {
+    head = block % H;
+    tile_m = block / H;
+    return;
+  }
+  const int xcd = block & 7, slot = block >> 3, heads = H / n;
+  head = xcd % n * heads + slot % heads;
+  tile_m = slot / heads * (8 / n) + xcd / n;
+}
 // How an epilogue splits a tile, and the LDS it takes
 template <int MODE, int MB> struct TileEpilogue {
   using S = Tile<MB>;
   static constexpr int kVals = MB <= 3 || MB == 6 ? 16 : kValsPerLane;            // values of a group per lane
   static constexpr int kWaveRows = kVals / 2;                          // groups per wave and pass
-  static constexpr int kParkRows = S::kRows < kWaveRows * S::kWaves ? S::kRows : kWaveRows * S::kWaves;   // one pass
-  static constexpr int kBytes = MODE != kTilePredict ? (int)sizeof(Lds) + kParkRows * kLdP * 4 : 0;
+  static constexpr int kPassRows = S::kRows < kWaveRows * S::kWaves ? S::kRows : kWaveRows * S::kWaves;
+  static constexpr int kPasses = (S::kRows + kPassRows - 1) / kPassRows;
+  // Rows parked at a time: all of them where the LDS has room.  (What is not parked stays in the multiplying waves' registers.)
+  static constexpr int kParkPasses = kPasses < 3 ? kPasses : 2, kParkRows = kParkPasses * kPassRows;
+  static constexpr int kParkBlocks = MB < 9 ? MB : 8;              // predictions: row blocks parked at a time
+  static constexpr int kBytes = MODE != kTilePredict ? (int)sizeof(Lds) + kParkRows * kLdP * 4 : kParkBlocks * 32 * kLdP * 4;
+  static_assert(kBytes <= 160 * 1024, "LDS of one CU");
   static constexpr int kLdsBytes = kBytes > S::kLdsBytes ? kBytes : S::kLdsBytes;
 };
 // workgroup `block` of the `nblocks` that work on `a`; smem: TileEpilogue<MODE, MB>::kLdsBytes of LDS
@@ -74,9 +102,7 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
   using S = Tile<MB>;
   static_assert(!WIDE || MODE != kTileEncode, "the quantizer needs the whole group: groups across the heads are not fused");
   using E = TileEpilogue<MODE, MB>;
-  constexpr int kVals = E::kVals, kWaveRows = E::kWaveRows, kParkRows = E::kParkRows;
-  constexpr int kParks = (S::kRows + kParkRows - 1) / kParkRows;
-  constexpr int kParkBlocks = kParkRows / 32 / S::WM;           // blocks of a wave's accumulators per park
+  constexpr int kVals = E::kVals, kWaveRows = E::kWaveRows, kPassRows = E::kPassRows, kPasses = E::kPasses;
   constexpr bool kEpilogue = MODE != kTilePredict;
   Lds& cl = *reinterpret_cast<Lds*>(smem);                      // grid and table at the start of the LDS (codec_core.h)
   float* const park = reinterpret_cast<float*>(smem + sizeof(Lds));
@@ -84,11 +110,8 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int H = a.D / kGroup;
-  // Which tile: while the predictor is larger than the rows (T <= D), the tiles of a head stay together on one XCD
-  // (consecutive workgroups go to consecutive XCDs, so the plain order does that for 8 heads) and each XCD's L2 fetches
-  // one head's slice of W once; beyond that the tiles of a row block stay together (remap_block).
-  const int logical = nblocks * S::kRows <= a.D * H ? block : remap_block(block, nblocks);
-  const int head = logical % H, tile_m = logical / H;
+  int tile_m, head;
+  tile_of(block, H, a.xcd_groups, tile_m, head);
   const int b = tile_m / a.tiles_per_seq, t0 = (tile_m % a.tiles_per_seq) * S::kRows;
   const int left = a.seq_len - t0;
   const int n_rows = left < S::kRows ? left : S::kRows;         // valid rows of this tile
@@ -100,8 +123,7 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
   constexpr bool kEnc = MODE == kTileEncode;
   constexpr bool kWideGrid = WIDE && !is_rtn(NCW) && kEpilogue;
   struct In { u32x4 x[kEnc ? kVals / 8 : 1]; CodeWords w; };
-  // several parks: the inputs of the first are requested ahead of the main loop, those of each next one during the one
-  // before (the accumulators leave no registers for more)
+  // several passes: the inputs of the first are requested from inside the main loop, those of each next one during the one before
   In in[2];
   WideCodes<NCW> wide[kWideGrid ? 2 : 1];
   float cb_a = 0.f, cb_b = 0.f;
@@ -112,7 +134,7 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
   u32x2 qreg = {0, 0};
   const int rep = MODE == kTileScores ? a.q_heads / H : 0;
   const auto fetch = [&](int h) {
-    const int lrow = h * kParkRows + wave * kWaveRows + wrow;
+    const int lrow = h * kPassRows + wave * kWaveRows + wrow;
     const int64_t row = m0 + (lrow < n_rows ? lrow : n_rows - 1);
     if constexpr (kEnc) {
       const u32x4* src = reinterpret_cast<const u32x4*>(a.X + row * a.D + n0 + q * kVals);
@@ -123,73 +145,90 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
       if constexpr (kWideGrid) request_wide_codes<NCW, kVals>(a.codes, row, q, wide[h & 1]);
     }
   };
-  const int wm = wave / S::WN, wn = wave % S::WN;
-  f32x16 acc[S::MI];
+  const int wm = wave / S::WN, wn = wave % S::WN;                // (of the multiplying waves)
+  f32x16 acc[S::MI][S::NJ];
   const int frow = lane & 31, fk = lane >> 5;
-  // element of [T, D] in register r of block i
-  const auto sum_at = [&](int i, int r) {
+  // element of [T, D] in register r of block (i, j)
+  const auto sum_at = [&](int i, int j, int r) {
     const int lrow = S::block_row(i, wm) + (r >> 2) * 8 + fk * 4 + (r & 3);
-    return (m0 + (lrow < n_rows ? lrow : n_rows - 1)) * a.D + n0 + wn * 32 + frow;
+    return (m0 + (lrow < n_rows ? lrow : n_rows - 1)) * a.D + n0 + S::block_col(j, wn) + frow;
   };
-  uint16_t hi[S::MI][16], lo[S::MI][16];
+  uint16_t hi[S::MI][S::NJ][16], lo[S::MI][S::NJ][16];
   if constexpr (SUMS == kUseSums) {
-#pragma unroll
-    for (int i = 0; i < S::MI; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) { hi[i][r] = a.sums_hi[sum_at(i, r)]; lo[i][r] = a.sums_lo[sum_at(i, r)]; }
-  } else {
-#pragma unroll
-    for (int i = 0; i < S::MI; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
-  }
-  if (kEpilogue && !(SUMS == kKeepSums && keep)) {
-    if ((int)threadIdx.x < kGridPoints) { cb_a = a.codebook[2 * threadIdx.x]; cb_b = a.codebook[2 * threadIdx.x + 1]; }
-    if (use_table) table_regs.request(a.table);
-    if constexpr (MODE == kTileScores) {
-      // the queries of this head (at most 8 x 128, adjacent in memory), 4 values per thread
-      if ((int)threadIdx.x * 4 < rep * kGroup)
-        qreg = *reinterpret_cast<const u32x2*>(a.q + ((int64_t)b * a.q_heads + head * rep) * kGroup + threadIdx.x * 4);
-    }
-    fetch(0);
-  }
-  __builtin_amdgcn_sched_barrier(0);
-
-  const int ldw = SUMS == kNoSums ? a.d0 + a.d1 : a.ldw;
-  TileLoop<MB>::run(smem, a.x0 + m0 * a.d0, a.d0, a.d1 ? a.x1 + m0 * a.d1 : a.x1, a.d1, a.W + (int64_t)n0 * ldw, ldw, n_rows - 1,
-                    acc, [&] {
-    if constexpr (SUMS == kUseSums) {
+    if (wave < kMulWaves) {
 #pragma unroll
       for (int i = 0; i < S::MI; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] = __uint_as_float(((uint32_t)hi[i][r] << 16) | lo[i][r]);
+        for (int j = 0; j < S::NJ; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) { hi[i][j][r] = a.sums_hi[sum_at(i, j, r)]; lo[i][j][r] = a.sums_lo[sum_at(i, j, r)]; }
+    }
+  }
+
+  const int ldw = SUMS == kNoSums ? a.d0 + a.d1 : a.ldw;
+  TileLoop<MB>::run(smem, a.x0 + m0 * a.d0, a.d0, a.d1 ? a.x1 + m0 * a.d1 : a.x1, a.d1, a.W + (int64_t)n0 * ldw, ldw, n_rows - 1, acc, [&] {
+#pragma unroll
+    for (int i = 0; i < S::MI; ++i)
+#pragma unroll
+      for (int j = 0; j < S::NJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          acc[i][j][r] = SUMS == kUseSums ? __uint_as_float(((uint32_t)hi[i][j][r] << 16) | lo[i][j][r]) : 0.f;
+  }, [&] {
+    if (kEpilogue && !(SUMS == kKeepSums && keep)) {
+      if ((int)threadIdx.x < kGridPoints) { cb_a = a.codebook[2 * threadIdx.x]; cb_b = a.codebook[2 * threadIdx.x + 1]; }
+      if (use_table) table_regs.request(a.table);
+      if constexpr (MODE == kTileScores) {
+        // the queries of this head (at most 8 x 128, adjacent in memory), 4 values per thread
+        if ((int)threadIdx.x * 4 < rep * kGroup)
+          qreg = *reinterpret_cast<const u32x2*>(a.q + ((int64_t)b * a.q_heads + head * rep) * kGroup + threadIdx.x * 4);
+      }
+      if (wave * kWaveRows < kPassRows) fetch(0);
     }
   });
   if (SUMS == kKeepSums && keep) {
+    if (wave < kMulWaves) {
 #pragma unroll
-    for (int i = 0; i < S::MI; ++i)
+      for (int i = 0; i < S::MI; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const uint32_t u = __float_as_uint(acc[i][r]);
-        if (S::block_row(i, wm) + (r >> 2) * 8 + fk * 4 + (r & 3) < n_rows) {
-          a.sums_hi[sum_at(i, r)] = (uint16_t)(u >> 16);
-          a.sums_lo[sum_at(i, r)] = (uint16_t)u;
-        }
-      }
+        for (int j = 0; j < S::NJ; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const uint32_t u = __float_as_uint(acc[i][j][r]);
+            if (S::block_row(i, wm) + (r >> 2) * 8 + fk * 4 + (r & 3) < n_rows) {
+              a.sums_hi[sum_at(i, j, r)] = (uint16_t)(u >> 16);
+              a.sums_lo[sum_at(i, j, r)] = (uint16_t)u;
+            }
+          }
+    }
     return;
   }
 
-  const float bv = a.bias != nullptr ? a.bias[n0 + wn * 32 + frow] : 0.f;
+  float bv[S::NJ];
+#pragma unroll
+  for (int j = 0; j < S::NJ; ++j) bv[j] = a.bias != nullptr && wave < kMulWaves ? a.bias[n0 + S::block_col(j, wn) + frow] : 0.f;
 
   if constexpr (!kEpilogue) {
-    float* const out = (n0 < a.P.split ? a.P.first + n0 : a.P.second + (n0 - a.P.split)) + wn * 32 + frow;
+    // Parked and stored by all waves, 512 bytes of a row per half wave: the multiplying waves alone store 4 bytes a lane.
+    float* const rows = reinterpret_cast<float*>(smem);
+    float* const out = (n0 < a.P.split ? a.P.first + n0 : a.P.second + (n0 - a.P.split)) + frow * 4;
 #pragma unroll
-    for (int i = 0; i < S::MI; ++i)
+    for (int first = 0; first < MB; first += E::kParkBlocks) {
+      __syncthreads();                                          // the ring, or the rows before, have been read
+      if (wave < kMulWaves) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int lrow = S::block_row(i, wm) + (r >> 2) * 8 + fk * 4 + (r & 3);
-        if (lrow < n_rows) out[(m0 + lrow) * a.P.stride] = acc[i][r] + bv;
+        for (int i = first / S::WM; i < S::MI && i * S::WM < first + E::kParkBlocks; ++i)
+#pragma unroll
+          for (int j = 0; j < S::NJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              rows[(S::block_row(i, wm) - first * 32 + (r >> 2) * 8 + fk * 4 + (r & 3)) * kLdP + S::block_col(j, wn) + frow] = acc[i][j][r] + bv[j];
       }
+      __syncthreads();
+      const int here = (MB - first < E::kParkBlocks ? MB - first : E::kParkBlocks) * 32;
+      for (int row = wave * 2 + fk; row < here && first * 32 + row < n_rows; row += 2 * S::kWaves)
+        *reinterpret_cast<f32x4*>(out + (m0 + first * 32 + row) * a.P.stride) = *reinterpret_cast<const f32x4*>(rows + row * kLdP + frow * 4);
+    }
     return;
   } else {
     float sf[kVals] = {};
@@ -209,21 +248,28 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
       }
     }
 #pragma unroll
-    for (int h = 0; h < kParks; ++h) {
-      if (h > 0) __syncthreads();                               // the previous rows have been consumed
-      const int here = S::kRows - h * kParkRows < kParkRows ? S::kRows - h * kParkRows : kParkRows;   // rows of this park
+    for (int h = 0; h < kPasses; ++h) {
+      constexpr int kParkRows = E::kParkRows, kBlocks = kParkRows / 32;        // row blocks per park; those of a wave lie S::WM apart
+      const int ph = h % E::kParkPasses, first = h / E::kParkPasses * kBlocks;
+      const int here = S::kRows - h * kPassRows < kPassRows ? S::kRows - h * kPassRows : kPassRows;   // rows of this pass
+      if (ph == 0) {
+        if (h > 0) __syncthreads();                             // the previous rows have been consumed
+        static_assert(kBlocks % S::WM == 0, "blocks of a park");
+        if (wave < kMulWaves) {
 #pragma unroll
-      for (int k = 0; k < kParkBlocks; ++k) {
-        const int i = h * kParkBlocks + k;
-        if (i >= S::MI) break;
+          for (int i = first / S::WM; i < S::MI && i * S::WM < first + kBlocks; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          park[(S::block_row(k, wm) + (r >> 2) * 8 + fk * 4 + (r & 3)) * kLdP + park_col<kVals>(wn * 32 + frow)] = acc[i][r] + bv;
+            for (int j = 0; j < S::NJ; ++j)
+#pragma unroll
+              for (int r = 0; r < 16; ++r)
+                park[(S::block_row(i, wm) - first * 32 + (r >> 2) * 8 + fk * 4 + (r & 3)) * kLdP +
+                     park_col<kVals>(S::block_col(j, wn) + frow)] = acc[i][j][r] + bv[j];
+        }
       }
-      if (h + 1 < kParks) fetch(h + 1);
-      __syncthreads();
-      if (wave * kWaveRows < here) {                            // (a park of fewer rows: the first waves)
-        const int prow = wave * kWaveRows + wrow, lrow = h * kParkRows + prow;
+      if (h + 1 < kPasses) fetch(h + 1);
+      if (ph == 0) __syncthreads();
+      if (wave * kWaveRows < here) {                            // (a pass of fewer rows: the first waves)
+        const int prow = ph * kPassRows + wave * kWaveRows + wrow, lrow = h * kPassRows + wave * kWaveRows + wrow;
         const bool active = lrow < n_rows;
         const int64_t rowc = m0 + (active ? lrow : n_rows - 1);
         const int64_t gid = rowc * H + head;
@@ -267,7 +313,7 @@ __device__ __forceinline__ void fused_tile_of_pair(int at, int blocks, int tiles
 }
 // (a kernel of its own: picking the job puts another round of scalar loads ahead of everything, 0.4 us)
 template <int NCW, int MODE, bool WIDE>
-__global__ __launch_bounds__(Tile<1>::kThreads) __attribute__((amdgpu_waves_per_eu(1))) void fused_tile_pair_kernel(const TilePair pair) {
+__global__ __launch_bounds__(Tile<1>::kThreads) __attribute__((amdgpu_waves_per_eu(Tile<1>::kWaves / 4))) void fused_tile_pair_kernel(const TilePair pair) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[TileEpilogue<MODE, 1>::kLdsBytes];
   fused_tile_of_pair<NCW, MODE, 1, WIDE, kKeepSums>(0, pair.blocks, (int)gridDim.x, smem);
 }
@@ -342,6 +388,7 @@ hipError_t launch_tile(int mode, int n_codewords, bool wide, int n_seq, TileArgs
   using S = Tile<MB>;
   a.tiles_per_seq = (a.seq_len + S::kRows - 1) / S::kRows;
   const unsigned blocks = (unsigned)((int64_t)n_seq * a.tiles_per_seq * (a.D / kGroup));
+  a.xcd_groups = xcd_head_groups((int64_t)n_seq * a.tiles_per_seq, a.D / kGroup, S::kRows);
 #define AQUAKV_TILE(N, MODE, WIDE) fused_tile_kernel<N, MODE, MB, WIDE, kNoSums><<<blocks, S::kThreads, 0, stream>>>(a)
   if (mode == kTilePredict) AQUAKV_TILE(16, kTilePredict, false);
   else if (mode == kTileEncode) AQUAKV_TILE_N(kTileEncode, false);
@@ -361,6 +408,7 @@ int pair_jobs(TilePair& pair, const TileArgs* jobs, int n) {
     TileArgs& job = pair.job[i];
     job = jobs[i < n ? i : 0];
     job.tiles_per_seq = (job.seq_len + Tile<MB>::kRows - 1) / Tile<MB>::kRows;
+    job.xcd_groups = xcd_head_groups(job.tiles_per_seq, job.D / kGroup, Tile<MB>::kRows);
     if (i < n) tiles += job.tiles_per_seq * (job.D / kGroup);
     if (i == 0) pair.blocks = tiles;
   }

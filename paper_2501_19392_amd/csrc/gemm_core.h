@@ -198,7 +198,6 @@ __device__ __forceinline__ void gemm_mainloop(unsigned char* lds_base, const bf1
   };
 
   Frag f[4];                                               // one buffer per step of a tile
-  constexpr int kHalf = kPieces / 2;
 #pragma unroll
   for (int pc = 0; pc < kPieces; ++pc) load_piece(0, 0, pc);
 #pragma unroll
@@ -207,30 +206,31 @@ __device__ __forceinline__ void gemm_mainloop(unsigned char* lds_base, const bf1
 
   // iteration t (see the table above): tile t is in the stage at s0; tile t+2 goes to the stage at s2
   auto iteration = [&](int t, int s0, int s2, bool first, bool do_load) {
+    // step i of the iteration: its fragment reads from MFMA slot 0 on, its share of the loads in the last slots
+    const auto loads = [&](int i, int m) {
+#pragma unroll
+      for (int pc = 0, n = 0; pc < kPieces; ++pc) {
+        const int of = pc * 4 / kPieces;
+        int last = pc;                                     // one past the step's pieces
+        while (last < kPieces && last * 4 / kPieces == of) ++last;
+        n = last - pc;
+        if (of == i && m == kMma - n && do_load) load_piece(t + 2, s2, pc);
+      }
+    };
     if (!first) {
-      mma8(f[2], [&](int m) {
-        spread(m, kFragPieces + kHalf, [&](int e) {
-          if (e < kFragPieces) frag_piece(s0, 0, f[0], e);
-          else if (do_load) load_piece(t + 2, s2, e - kFragPieces);
-        });
-      });
-      mma8(f[3], [&](int m) {
-        spread(m, kFragPieces + kHalf, [&](int e) {
-          if (e < kFragPieces) frag_piece(s0, 1, f[1], e);
-          else if (do_load) load_piece(t + 2, s2, kHalf + e - kFragPieces);
-        });
-      });
+      mma8(f[2], [&](int m) { spread(m, kFragPieces, [&](int e) { frag_piece(s0, 0, f[0], e); }); loads(0, m); });
+      mma8(f[3], [&](int m) { spread(m, kFragPieces, [&](int e) { frag_piece(s0, 1, f[1], e); }); loads(1, m); });
     } else {
 #pragma unroll
       for (int pc = 0; pc < kFragPieces; ++pc) { frag_piece(s0, 0, f[0], pc); frag_piece(s0, 1, f[1], pc); }
       if (do_load) {
 #pragma unroll
-        for (int pc = 0; pc < kPieces; ++pc) load_piece(t + 2, s2, pc);
+        for (int pc = 0; pc < kPieces; ++pc) if (pc * 4 / kPieces < 2) load_piece(t + 2, s2, pc);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    mma8(f[0], [&](int m) { spread(m, kFragPieces, [&](int e) { frag_piece(s0, 2, f[2], e); }); });
-    mma8(f[1], [&](int m) { spread(m, kFragPieces, [&](int e) { frag_piece(s0, 3, f[3], e); }); });
+    mma8(f[0], [&](int m) { spread(m, kFragPieces, [&](int e) { frag_piece(s0, 2, f[2], e); }); loads(2, m); });
+    mma8(f[1], [&](int m) { spread(m, kFragPieces, [&](int e) { frag_piece(s0, 3, f[3], e); }); loads(3, m); });
   };
   const auto next_stage = [](int s) { return s + kStageBytes == kMainLoopLdsBytes ? 0 : s + kStageBytes; };
 

@@ -10,6 +10,8 @@
 #pragma once
 #include "gemm_core.h"
 
+#include <type_traits>
+
 namespace aquakv {
 
 constexpr int BM2 = 256, BN2 = 256;                  // block tile; BK as in gemm_core.h
@@ -24,15 +26,15 @@ constexpr int kWaves2 = 8;
 // may reuse the LDS at once.  Requires
 // K = d0 + d1 a multiple of 128, d0 of 64.  `before_drain()` is called once, when the last operand loads are out.
 //
-// Schedule.  k-tile t lives in stage t % 2 and is multiplied in four steps of 16 k (8 MFMAs per wave each) from two
-// fragment buffers: a step's MFMAs run while the next step's fragments are read.  Per tile t:
-//   MFMAs (t, 0)   + fragment reads (t, 1)
-//   MFMAs (t, 1)   + fragment reads (t, 2)
-//   MFMAs (t, 2)   + fragment reads (t, 3)
-//   barrier B_{t+1}: tile t + 1 complete in LDS, every wave done reading tile t
-//   MFMAs (t, 3)   + fragment reads (t + 1, 0) + the 8 loads of tile t + 2 (into the stage tile t leaves)
-// so a load has a whole tile of both waves of a SIMD (about 1 us) to land, the matrix pipe keeps running across the
-// barrier, and the fragments take 48 registers beside the 128 accumulators.
+// Schedule.  The x and W halves of k-tile t live in stage t % 2 of a ring each and are multiplied in four steps of 16 k (8 MFMAs
+// per wave each).  A wave holds its x fragments of a whole k-tile (32 registers, read a k-tile ahead) and its W fragments of two
+// steps (32), so the two halves of a stage are free half a k-tile apart and their loads go out apart as well.  Per tile t:
+//   barrier P_{t+1}: x of tile t + 1 complete in LDS, every wave done reading x of tile t (which it did during tile t - 1)
+//   MFMAs (t, 0)   + W fragments (t, 1), x fragments (t + 1, 0) + loads of x of tile t + 2
+//   MFMAs (t, 1)   + W fragments (t, 2), x fragments (t + 1, 1) + loads of x of tile t + 2
+//   MFMAs (t, 2)   + W fragments (t, 3), x fragments (t + 1, 2)
+//   barrier B_{t+1}: W of tile t + 1 complete in LDS, every wave done reading W of tile t
+//   MFMAs (t, 3)   + W fragments (t + 1, 0), x fragments (t + 1, 3) + loads of W of tile t + 2
 template <typename BeforeDrain>
 __device__ __forceinline__ void gemm_mainloop_two_heads(unsigned char* lds_base, const bf16_t* __restrict__ x0, int d0,
                                                         const bf16_t* __restrict__ x1, int d1,
@@ -44,8 +46,8 @@ __device__ __forceinline__ void gemm_mainloop_two_heads(unsigned char* lds_base,
   constexpr int kBChunks = BN2 * 8 / kThreadsW;    // 4 for W
   constexpr int kPieces = kAChunks + kBChunks;
   constexpr int kPieceBytes = kThreadsW * 16;      // 8 KiB = 64 tile rows
-  constexpr int kFragPieces = MI + 4;
   constexpr int kMma = MI * 4;
+  constexpr int kW = 2 * kATile2Bytes;             // the stages of W lie behind those of x
   typedef __attribute__((address_space(3))) unsigned char* lptr_t;
   typedef const __attribute__((address_space(1))) char* gptr_t;
   const int tid = threadIdx.x;
@@ -54,8 +56,6 @@ __device__ __forceinline__ void gemm_mainloop_two_heads(unsigned char* lds_base,
   const int ws = wave >> 1, wh = wave & 1;
   const int K = d0 + d1;
   const int nk = K / BK;
-
-  struct Frag { bf16x8 v[kFragPieces]; };
 
   const int ch16 = ((tid & 7) ^ ((tid >> 4) & 7)) * 16;
   int rowc[kAChunks];
@@ -81,7 +81,7 @@ __device__ __forceinline__ void gemm_mainloop_two_heads(unsigned char* lds_base,
   const lptr_t lds3 = (lptr_t)lds_base;
   auto load_piece = [&](int kt, int stage_off, int pc) {
     const int k0 = kt * BK;
-    const lptr_t dst = lds3 + (stage_off + pc * kPieceBytes + wave * 1024);   // x pieces fill the A tile, W pieces follow
+    const lptr_t dst = lds3 + (stage_off + (pc < kAChunks ? pc : pc - kAChunks) * kPieceBytes + (pc < kAChunks ? 0 : kW) + wave * 1024);
     if (pc < kAChunks) {
       const bool second = k0 >= d0;
       const int ld2 = __builtin_amdgcn_readfirstlane((second ? d1 : d0) * 2);
@@ -96,10 +96,19 @@ __device__ __forceinline__ void gemm_mainloop_two_heads(unsigned char* lds_base,
   };
   const int frow = lane & 31;
   const int fk = lane >> 5;
-  auto frag_piece = [&](int stage_off, int ks, Frag& f, int pc) {
-    const int off = pc < MI ? lds_off(ws * (MI * 32) + pc * 32 + frow, ks * 2 + fk)
-                            : kATile2Bytes + lds_off(wh * 128 + (pc - MI) * 32 + frow, ks * 2 + fk);
-    f.v[pc] = *reinterpret_cast<const bf16x8*>(lds_base + stage_off + off);
+  int xo[4], wo[4];                                // place of the fragments of step s in a stage, of block 0
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    xo[ks] = lds_off(ws * (MI * 32) + frow, ks * 2 + fk);
+    wo[ks] = kW + lds_off(wh * 128 + frow, ks * 2 + fk);
+    asm("" : "+v"(xo[ks]), "+v"(wo[ks]));
+  }
+  bf16x8 xf[4][MI], wf[2][4];
+  auto read_x = [&](int stage, int ks, int i) {
+    xf[ks][i] = *reinterpret_cast<const bf16x8*>(lds_base + xo[ks] + (stage * kATile2Bytes + i * 32 * kRowBytes));
+  };
+  auto read_w = [&](int stage, int ks, int b, int j) {
+    wf[b][j] = *reinterpret_cast<const bf16x8*>(lds_base + wo[ks] + (stage * kATile2Bytes + j * 32 * kRowBytes));
   };
 
 #pragma unroll
@@ -109,65 +118,71 @@ __device__ __forceinline__ void gemm_mainloop_two_heads(unsigned char* lds_base,
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  auto mma8 = [&](const Frag& f, auto&& extra) {
-#pragma unroll
-    for (int m = 0; m < kMma; ++m) {
-      const int i = m >> 2, j = m & 3;
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v[i], f.v[MI + j], acc[i][j], 0, 0, 0);
-      extra(m);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  auto spread = [&](int m, int n, auto&& item) {
-    if (2 * m < n) item(2 * m);
-    if (2 * m + 1 < n) item(2 * m + 1);
-  };
-  // publish a k-tile: this wave's loads have landed, its LDS reads have returned; then meet the other waves
-  auto publish = [&] {
-    __builtin_amdgcn_s_waitcnt(0x0070);                    // vmcnt(0) lgkmcnt(0)
+  // wait until at most N of this wave's loads are in flight and its LDS reads have returned; then meet the other waves
+  auto meet = [&](auto n) {
+    constexpr int N = decltype(n)::value;
+    __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
+  using Half = std::integral_constant<int, kAChunks>;
+  using None = std::integral_constant<int, 0>;
 
-  Frag f[2];
 #pragma unroll
-  for (int pc = 0; pc < kPieces; ++pc) load_piece(0, 0, pc);
+  for (int t = 0; t < 2; ++t)                      // nk >= 2
 #pragma unroll
-  for (int pc = 0; pc < kPieces; ++pc) load_piece(1, kStage2Bytes, pc);          // nk >= 2
-  __builtin_amdgcn_s_waitcnt(0x0070 | (kPieces & 15) | ((kPieces >> 4) << 14));  // tile 0 has landed, tile 1 may be in flight
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
+    for (int pc = 0; pc < kPieces; ++pc) load_piece(t, t * kATile2Bytes, pc);
+  meet(std::integral_constant<int, kPieces>{});    // tile 0 has landed, tile 1 may be in flight
 #pragma unroll
-  for (int pc = 0; pc < kFragPieces; ++pc) frag_piece(0, 0, f[0], pc);
+  for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+    for (int i = 0; i < MI; ++i) read_x(0, ks, i);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) read_w(0, 0, 0, j);
   __builtin_amdgcn_sched_barrier(0);
 
-  // tile t in the stage at `cur`; `next_tile`: tile t + 1 exists; `do_load`: tile t + 2 exists
-  auto tile = [&](int t, int cur, bool next_tile, bool do_load) {
-    mma8(f[0], [&](int m) { spread(m, kFragPieces, [&](int e) { frag_piece(cur, 1, f[1], e); }); });
-    mma8(f[1], [&](int m) { spread(m, kFragPieces, [&](int e) { frag_piece(cur, 2, f[0], e); }); });
-    mma8(f[0], [&](int m) { spread(m, kFragPieces, [&](int e) { frag_piece(cur, 3, f[1], e); }); });
-    publish();
-    mma8(f[1], [&](int m) {
-      spread(m, kFragPieces + kPieces, [&](int e) {
-        if (e < kFragPieces) { if (next_tile) frag_piece(cur ^ kStage2Bytes, 0, f[0], e); }
-        else if (do_load) load_piece(t + 2, cur, e - kFragPieces);
-      });
-    });
+  // tile t, in stage `st` (a constant); next: tile t + 1 exists; load: tile t + 2 exists
+  auto tile = [&](int t, auto stage, bool next, bool load, auto&& behind_loads) {
+    constexpr int st = decltype(stage)::value;
+    if (next) meet(Half{});                        // (the loads of W of tile t + 1 may be in flight)
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      if (ks == 3) {
+        if (load) meet(Half{});                    // (those of x of tile t + 2)
+        else if (next) meet(None{});
+        else meet(std::integral_constant<int, 63>{});   // (those of the caller)
+        behind_loads();
+      }
+#pragma unroll
+      for (int m = 0; m < kMma; ++m) {
+        const int i = m >> 2, j = m & 3;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[ks][i], wf[ks & 1][j], acc[i][j], 0, 0, 0);
+        if (ks < 3 || next) {
+          if (m < 4) read_w(ks < 3 ? st : st ^ 1, (ks + 1) & 3, (ks + 1) & 1, m);
+        }
+        if (next && (m & 3) == 3) read_x(st ^ 1, ks, i);
+        if (load) {
+          if (ks < 2 && (m & 3) == 2) load_piece(t + 2, st * kATile2Bytes, 2 * ks + i);
+          if (ks == 3 && (m & 1) == 0) load_piece(t + 2, st * kATile2Bytes, kAChunks + m / 2);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
   };
-
-  int cur = 0, t = 0;
-  for (; t + 2 < nk; ++t) {
-    tile(t, cur, true, true);
-    cur ^= kStage2Bytes;
+  using Even = std::integral_constant<int, 0>;
+  using Odd = std::integral_constant<int, 1>;
+  int t = 0;
+  for (; t + 2 < nk; t += 2) {                     // nk is even
+    tile(t, Even{}, true, true, [] {});
+    tile(t + 1, Odd{}, true, true, [] {});
   }
-  before_drain();
-  __builtin_amdgcn_sched_barrier(0);
-  tile(t, cur, true, false);                               // the last two tiles: nothing left to load
-  cur ^= kStage2Bytes;
-  tile(t + 1, cur, false, false);
+  tile(t, Even{}, true, false, [&] {               // the last two tiles: nothing left to load
+    before_drain();
+    __builtin_amdgcn_sched_barrier(0);
+  });
+  tile(t + 1, Odd{}, false, false, [] {});
   settle_accumulators(acc);
 }
 
