@@ -43,122 +43,115 @@ constexpr size_t kFoldBytesPerBatch = (size_t)kUBytesPerBatch + kFoldQ * 128 * 4
 static_assert(kFoldBytesPerBatch == kFoldedBytesPerBatch, "the size the C-ABI layer plans with");
 
 // ------------------------------------------------------------------ query folding
-// grid = batch * kv_heads * 8, 256 threads: block (b, h, cc) owns input channels 128 cc ... + 127 for the
-// query heads of kv head h.  Thread (cg, dp) multiplies 8 consecutive channels by 8 of the 128 predictor
-// rows (one 128-bit load per row, all in flight at once); the 16 row groups are added in a fixed order
-// through LDS.  Blocks with cc == 0 also write q . b and the rotated queries.
+// u = q W_h on the matrix cores: bf16 operands, exact products, fp32 sums.  A workgroup takes the 128 input channels cc of kv head h for
+// up to 32 query heads (`entries` batch entries x rep heads); wave w has channels 32 w ... of them.  W comes in 8 x 8 blocks of (row,
+// channel), one per thread, which turns it in registers into the operands' order (8 rows of a channel) on the way to LDS.
+// Bound by reading W once per 32 query heads (before: once per batch entry, and 400 vector instructions per thread and entry): 64 batch
+// entries x 32 query heads 26.3 -> 5.9 us.  Workgroups with cc == 0 also write q . b and the rotated queries.
 constexpr int kFoldChunks = 8;
+constexpr int kFoldOutLd = 36;                  // padded row of a wave's 32 x 32 results
 __global__ __launch_bounds__(256) void fold_query_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ W,
-                                                         const float* __restrict__ bias,
-                                                         const int8_t* __restrict__ signs, unsigned char* ws,
-                                                         int q_heads, int kv_heads, int r0, int rep) {
+                                                         const float* __restrict__ bias, const int8_t* __restrict__ signs,
+                                                         unsigned char* ws, int q_heads, int r0, int rep, int batch, int entries) {
   // q_heads: query heads of the model; this pass takes query heads r0 ... r0 + rep - 1 (rep <= 4) of every kv head
-  // and numbers them h * rep + r ("row" below)
-  __shared__ float qs[4][128];
-  __shared__ float part[16][4][128 + 4];
-  const int cc = blockIdx.x % kFoldChunks;
-  const int bh = blockIdx.x / kFoldChunks;
-  const int b = bh / kv_heads, h = bh % kv_heads;
-  const int rep_model = q_heads / kv_heads;
-  const int rows = kv_heads * rep;               // rows of this pass that exist
-  const int tid = threadIdx.x;
-  const int cg = tid & 15, dp = tid >> 4;
-  // predictor rows 8 dp ... + 7 of this head, channels 128 cc + 8 cg ... + 7
-  u32x4 wraw[8];
-  const bf16_t* Wc = W + ((size_t)h * 128 + dp * 8) * kFoldK + cc * 128 + cg * 8;
+  // and numbers them h * rep + r
+  constexpr int kHeads = 8;
+  __shared__ u32x4 wt[16 * 128];                  // [8 rows of W][channel, swizzled]
+  __shared__ float out[4][32 * kFoldOutLd];
+  const int cc = blockIdx.x % kFoldChunks, h = blockIdx.x / kFoldChunks % kHeads;
+  const int b0 = blockIdx.x / (kFoldChunks * kHeads) * entries;
+  const int here = batch - b0 < entries ? batch - b0 : entries;        // batch entries of this workgroup
+  const int rep_model = q_heads / kHeads;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const auto q_row = [&](int row) {               // (rows that do not exist: one that does)
+    const int e = row / rep < here ? row / rep : here - 1;
+    return q + ((size_t)(b0 + e) * q_heads + h * rep_model + r0 + row % rep) * 128;
+  };
+  const auto swizzled = [](int chan) { return (chan & ~7) | ((chan ^ (chan >> 3)) & 7); };
+  const int frow = lane & 31, fk = lane >> 5;
+  bf16x8 a[8];
 #pragma unroll
-  for (int d = 0; d < 8; ++d) wraw[d] = *reinterpret_cast<const u32x4*>(Wc + (size_t)d * kFoldK);
-  for (int e = tid; e < rep * 128; e += 256)
-    qs[e >> 7][e & 127] = static_cast<float>(q[((size_t)b * q_heads + h * rep_model + r0 + (e >> 7)) * 128 + (e & 127)]);
-  __syncthreads();
-
-  unsigned char* wsb = ws + (size_t)b * kFoldBytesPerBatch;
-  bf16_t* U = reinterpret_cast<bf16_t*>(wsb);
-  float* qrot = reinterpret_cast<float*>(wsb + kUBytesPerBatch);
-  float* cdot = qrot + kFoldQ * 128;
-
-  // partial u[r][i] = sum over this thread's 8 rows d (ascending) of q[r][d] * W[h * 128 + d][i], fp32
-  float acc[4][8];
+  for (int ks = 0; ks < 8; ++ks) a[ks] = *reinterpret_cast<const bf16x8*>(q_row(frow) + ks * 16 + fk * 8);
+  {
+    const int cg = tid & 15, dp = tid >> 4;       // predictor rows 8 dp ... of this head, channels 128 cc + 8 cg ...
+    const bf16_t* Wc = W + ((size_t)h * 128 + dp * 8) * kFoldK + cc * 128 + cg * 8;
+    u32x4 w[8];
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+    for (int d = 0; d < 8; ++d) w[d] = *reinterpret_cast<const u32x4*>(Wc + (size_t)d * kFoldK);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) acc[r][k] = 0.f;
+    for (int k = 0; k < 8; ++k) {
+      u32x4 t;
 #pragma unroll
-  for (int d = 0; d < 8; ++d) {
-    float w[8];
-    unpack_bf16x8(wraw[d], w);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      if (r < rep) {
-        const float qv = qs[r][dp * 8 + d];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) acc[r][k] = __fmaf_rn(qv, w[k], acc[r][k]);
-      }
+      for (int j = 0; j < 4; ++j) t[j] = __builtin_amdgcn_perm(w[2 * j + 1][k / 2], w[2 * j][k / 2], k & 1 ? 0x07060302u : 0x05040100u);
+      wt[dp * 128 + swizzled(8 * cg + k)] = t;
     }
   }
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int k = 0; k < 8; ++k) part[dp][r][cg * 8 + k] = acc[r][k];
   __syncthreads();
-  {
-    // thread (channel, half) finishes query heads r = half, half + 2: row groups added in ascending order
-    const int col = tid & 127, half = tid >> 7;
-    // operand layout: [wave = i / 128][high, low][k step = (i % 128) / 16][lane = head + 32 * ((i % 16) / 8)][i % 8]
-    const int ks = col >> 4, khalf = (col & 15) >> 3, e = col & 7;
-    const size_t frag = ((size_t)(cc * 2 + 0) * 8 + ks) * (kUFragBytes / 2);
-    const size_t lo_off = 8 * (kUFragBytes / 2);
+  f32x16 acc;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      if (r < rep && (r & 1) == half) {
-        float uv = 0.f;
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-        for (int g = 0; g < 16; ++g) uv += part[g][r][col];
-        const bf16_t hi = static_cast<bf16_t>(uv);
-        const bf16_t lo = static_cast<bf16_t>(uv - static_cast<float>(hi));
-        const size_t pos = (size_t)(h * rep + r + 32 * khalf) * 8 + e;
-        U[frag + pos] = hi;
-        U[frag + lo_off + pos] = lo;
-      }
+  for (int ks = 0; ks < 8; ++ks)
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks], __builtin_bit_cast(bf16x8, wt[(2 * ks + fk) * 128 + swizzled(32 * wave + frow)]), acc, 0, 0, 0);
+  settle_accumulators(acc);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) out[wave][((r >> 2) * 8 + fk * 4 + (r & 3)) * kFoldOutLd + frow] = acc[r];
+  __syncthreads();
+  // operand layout: [wave = i / 128][high, low][k step = (i % 128) / 16][lane = head + 32 * ((i % 16) / 8)][i % 8]
+  const auto operand = [&](int e, int low, int ks, int head, int khalf) {
+    bf16_t* const U = reinterpret_cast<bf16_t*>(ws + (size_t)(b0 + e) * kFoldBytesPerBatch);
+    return reinterpret_cast<u32x4*>(U + ((size_t)(cc * 2 + low) * 8 + ks) * (kUFragBytes / 2) + (head + 32 * khalf) * 8);
+  };
+#pragma unroll
+  for (int it = 0; it < 2; ++it) {                // 8 channels of a query head at a time
+    const int row = (lane >> 2) + 16 * it, chunk = lane & 3;
+    if (row >= here * rep) break;
+    u32x4 hi, lo;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float x = out[wave][row * kFoldOutLd + chunk * 8 + 2 * j], y = out[wave][row * kFoldOutLd + chunk * 8 + 2 * j + 1];
+      hi[j] = Storage<bf16_t>::pack2(x, y);
+      lo[j] = Storage<bf16_t>::pack2(x - __uint_as_float(hi[j] << 16), y - __uint_as_float(hi[j] & 0xffff0000u));
     }
-    // rows of query heads that do not exist multiply as zero: kv head h clears rows q_heads + h, + 8, ...
-    if (half == 0) {
-      for (int qh = rows + h; qh < kFoldQ; qh += kv_heads) {
-        const size_t pos = (size_t)(qh + 32 * khalf) * 8 + e;
-        U[frag + pos] = static_cast<bf16_t>(0.f);
-        U[frag + lo_off + pos] = static_cast<bf16_t>(0.f);
-      }
-    }
+    const int ks = 2 * wave + (chunk >> 1), head = h * rep + row % rep;
+    *operand(row / rep, 0, ks, head, chunk & 1) = hi;
+    *operand(row / rep, 1, ks, head, chunk & 1) = lo;
+  }
+  // rows of query heads that do not exist multiply as zero: kv head h clears rows 8 rep + h, + 8, ... of 32
+  for (int i = tid; i < (4 - rep) * here * 32; i += 256) {
+    const int piece = i & 31, e = i / 32 % here, head = kHeads * (rep + i / 32 / here) + h;
+    *operand(e, piece & 1, piece >> 2, head, (piece >> 1) & 1) = u32x4{0, 0, 0, 0};
   }
   if (cc != 0) return;
+  const auto extras = [&](int e) { return reinterpret_cast<float*>(ws + (size_t)(b0 + e) * kFoldBytesPerBatch + kUBytesPerBatch); };
   // q . b
-  if (tid < rep) {
+  if (tid < here * rep) {
     float c = 0.f;
     if (bias != nullptr) {
+      const bf16_t* const src = q_row(tid);
 #pragma unroll 16
-      for (int d = 0; d < 128; ++d) c = __fmaf_rn(qs[tid][d], bias[h * 128 + d], c);
+      for (int d = 0; d < 128; ++d) c = __fmaf_rn(static_cast<float>(src[d]), bias[h * 128 + d], c);
     }
-    cdot[h * rep + tid] = c;
+    extras(tid / rep)[kFoldQ * 128 + h * rep + tid % rep] = c;
   }
-  // rotated query: one quad of lanes per query head (second wave, so that it overlaps the q . b loop)
-  if (tid >= 64 && tid < 64 + 4 * rep) {
-    const int r = (tid - 64) >> 2, qd = tid & 3;
+  // rotated query: one quad of lanes per query head (other waves, so that they overlap the q . b loop)
+  const int row = (tid - 64) >> 2, qd = tid & 3;
+  if (tid >= 64 && row < here * rep) {
     float v[32];
+    Storage<bf16_t>::load(q_row(row) + 32 * qd, v);
     if (signs != nullptr) {
       float sf[32];
       load_signs(signs, h, qd, sf);
 #pragma unroll
-      for (int k = 0; k < 32; ++k) v[k] = qs[r][32 * qd + k] * sf[k];
+      for (int k = 0; k < 32; ++k) v[k] *= sf[k];
       wht128(v, qd);
       const float norm = quad_sign(qd) * kRsqrtG;
 #pragma unroll
       for (int k = 0; k < 32; ++k) v[k] *= norm;
-    } else {                                   // backbone without a rotation: the code term multiplies q itself
+    }                                             // (backbone without a rotation: the code term multiplies q itself)
+    float* const qrot = extras(row / rep) + (h * rep + row % rep) * 128 + 32 * qd;
 #pragma unroll
-      for (int k = 0; k < 32; ++k) v[k] = qs[r][32 * qd + k];
-    }
-#pragma unroll
-    for (int k = 0; k < 32; ++k) qrot[(h * rep + r) * 128 + 32 * qd + k] = v[k];
+    for (int k = 0; k < 8; ++k) reinterpret_cast<f32x4*>(qrot)[k] = f32x4{v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]};
   }
 }
 
@@ -489,9 +482,9 @@ hipError_t launch_folded_scores(int n_codewords, const void* Khat_prev, const vo
     unsigned char* ws = static_cast<unsigned char*>(workspace) + (size_t)pass * batch * kFoldBytesPerBatch;
     const int r0 = pass * kRepPerPass;
     const int rep = rep_model - r0 < kRepPerPass ? rep_model - r0 : kRepPerPass;
-    fold_query_kernel<<<batch * 8 * kFoldChunks, 256, 0, stream>>>(static_cast<const bf16_t*>(q),
-                                                                    static_cast<const bf16_t*>(W), bias, signs, ws,
-                                                                    q_heads, 8, r0, rep);
+    const int entries = kFoldQ / rep;
+    fold_query_kernel<<<(batch + entries - 1) / entries * 8 * kFoldChunks, 256, 0, stream>>>(
+        static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(W), bias, signs, ws, q_heads, r0, rep, batch, entries);
     if (n_codewords == kRtn2) AQUAKV_FOLDED(kRtn2);
     else if (n_codewords == kRtn4) AQUAKV_FOLDED(kRtn4);
     else if (n_codewords == 16) AQUAKV_FOLDED(16);
