@@ -18,6 +18,8 @@ namespace aquakv {
 
 enum TileMode : int { kTileEncode = 0, kTileDecode = 1, kTileScores = 2, kTilePredict = 3 };
 
+struct XcdSplit { int log2_n, even; uint32_t per_heads, per_all; };   // xcd_split
+
 struct TileArgs {
   const bf16_t* x0;
   const bf16_t* x1;
@@ -43,7 +45,7 @@ struct TileArgs {
   // sums of a product over the first part of its inputs, in two halves of 16 bits, [T, D] each
   uint16_t* sums_hi;
   uint16_t* sums_lo;
-  int xcd_groups;                  // tile_of
+  XcdSplit xcd;                   // tile_of
 };
 // Two products in one launch: the first `blocks` workgroups work on job[0], the others on job[1], or (tiles of 32 rows) store the
 // sums of job[1] and nothing else if it has a place for them.
@@ -61,26 +63,34 @@ struct TileAttend {
   AttendCacheArgs attend;
 };
 // Which tile a workgroup works on.  Consecutive workgroups go to consecutive XCDs, each with an L2 of its own that fetches the x rows and
-// the rows of W of its tiles once.  The row blocks are split into 8 / n groups and the heads into n, one of each to an XCD, n = xcd_head_groups,
-// the split that fetches least; 0 where none comes out even: heads in the plain order.
-inline int xcd_head_groups(int64_t row_blocks, int H, int rows) {
-  int best = 0;
+// the rows of W of its tiles once.  The row blocks are split into 8 / n groups and the heads into n, one of each to an XCD: the n that
+// fetches least.  Row blocks that do not come out even follow in the plain order.  1024
+// tokens on 32 rows: n = 2, 768 rows of 128 bytes per k-tile and XCD where heads in the plain order fetch 1152.  (Row blocks that come out
+// even only with n = 8 must not be split so: 9000 tokens on 320 rows 68 -> 80 us.)
+// n = 1 << log2_n; even: row blocks in the split; per_x: ceil(2^32 / x), 0 for one: a division is some 20 instructions ahead of
+// everything else (flush of 128 tokens 17.5 -> 17.1 us without the seven that were here).
+inline XcdSplit xcd_split(int64_t row_blocks, int H, int rows) {
+  XcdSplit best = {0, 0, 0, 0};
   int64_t least = 0;
-  for (const int n : {1, 2, 4, 8}) {
-    const int64_t rows_fetched = row_blocks * n / 8 * rows + H / n * kGroup;
-    if (H % n == 0 && row_blocks % (8 / n) == 0 && (best == 0 || rows_fetched < least)) { best = n; least = rows_fetched; }
+  for (int l = 0; l < 4; ++l) {
+    const int n = 1 << l;
+    const int64_t even = row_blocks / (8 / n) * (8 / n), rest = row_blocks - even;
+    const int64_t fetched = (even * n / 8 + rest) * rows + (H / n + (rest != 0)) * kGroup;
+    if (H % n == 0 && even != 0 && (best.even == 0 || fetched < least)) { best = {l, (int)even, 0, 0}; least = fetched; }
   }
+  const auto per = [](uint32_t d) { return d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d); };
+  best.per_heads = per(H >> best.log2_n);
+  best.per_all = per(H);
   return best;
 }
-__device__ __forceinline__ void tile_of(int block, int H, int n, int& tile_m, int& head) {
-  if (n == 0) {
-    head = block % H;
-    tile_m = block / H;
-    return;
-  }
-  const int xcd = block & 7, slot = block >> 3, heads = H / n;
-  head = xcd % n * heads + slot % heads;
-  tile_m = slot / heads * (8 / n) + xcd / n;
+__device__ __forceinline__ void tile_of(int block, int H, const XcdSplit& s, int& tile_m, int& head) {
+  const bool plain = block >= s.even * H;
+  const int i = plain ? block : block >> 3, heads = plain ? H : H >> s.log2_n, xcd = plain ? 0 : block & 7;
+  const uint32_t per = plain ? s.per_all : s.per_heads;
+  const int slot = per == 0 ? i : (int)__umulhi((uint32_t)i, per);          // i / heads, exact while i * heads < 2^32
+  const int n_rows = plain ? 1 : 8 >> s.log2_n, group = xcd & ((1 << s.log2_n) - 1);
+  head = group * heads + (i - slot * heads);
+  tile_m = slot * n_rows + (xcd >> s.log2_n);
 }
 // How an epilogue splits a tile, and the LDS it takes
 template <int MODE, int MB> struct TileEpilogue {
@@ -111,8 +121,8 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int H = a.D / kGroup;
   int tile_m, head;
-  tile_of(block, H, a.xcd_groups, tile_m, head);
-  const int b = tile_m / a.tiles_per_seq, t0 = (tile_m % a.tiles_per_seq) * S::kRows;
+  tile_of(block, H, a.xcd, tile_m, head);
+  const int b = tile_m < a.tiles_per_seq ? 0 : tile_m / a.tiles_per_seq, t0 = (tile_m - b * a.tiles_per_seq) * S::kRows;
   const int left = a.seq_len - t0;
   const int n_rows = left < S::kRows ? left : S::kRows;         // valid rows of this tile
   const int64_t m0 = (int64_t)b * a.seq_len + t0;               // its first row
@@ -388,7 +398,7 @@ hipError_t launch_tile(int mode, int n_codewords, bool wide, int n_seq, TileArgs
   using S = Tile<MB>;
   a.tiles_per_seq = (a.seq_len + S::kRows - 1) / S::kRows;
   const unsigned blocks = (unsigned)((int64_t)n_seq * a.tiles_per_seq * (a.D / kGroup));
-  a.xcd_groups = xcd_head_groups((int64_t)n_seq * a.tiles_per_seq, a.D / kGroup, S::kRows);
+  a.xcd = xcd_split((int64_t)n_seq * a.tiles_per_seq, a.D / kGroup, S::kRows);
 #define AQUAKV_TILE(N, MODE, WIDE) fused_tile_kernel<N, MODE, MB, WIDE, kNoSums><<<blocks, S::kThreads, 0, stream>>>(a)
   if (mode == kTilePredict) AQUAKV_TILE(16, kTilePredict, false);
   else if (mode == kTileEncode) AQUAKV_TILE_N(kTileEncode, false);
@@ -408,7 +418,7 @@ int pair_jobs(TilePair& pair, const TileArgs* jobs, int n) {
     TileArgs& job = pair.job[i];
     job = jobs[i < n ? i : 0];
     job.tiles_per_seq = (job.seq_len + Tile<MB>::kRows - 1) / Tile<MB>::kRows;
-    job.xcd_groups = xcd_head_groups(job.tiles_per_seq, job.D / kGroup, Tile<MB>::kRows);
+    job.xcd = xcd_split(job.tiles_per_seq, job.D / kGroup, Tile<MB>::kRows);
     if (i < n) tiles += job.tiles_per_seq * (job.D / kGroup);
     if (i == 0) pair.blocks = tiles;
   }

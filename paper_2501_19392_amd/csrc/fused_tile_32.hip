@@ -24,7 +24,7 @@ hipError_t launch_tile_rest(int mode, int n_codewords, bool wide, const TileArgs
   using S = Tile<1>;
   TileArgs a = args;
   a.tiles_per_seq = (a.seq_len + S::kRows - 1) / S::kRows;
-  a.xcd_groups = xcd_head_groups(a.tiles_per_seq, a.D / kGroup, S::kRows);
+  a.xcd = xcd_split(a.tiles_per_seq, a.D / kGroup, S::kRows);
   const unsigned blocks = (unsigned)(a.tiles_per_seq * (a.D / kGroup));
 #define AQUAKV_TILE(N, MODE, WIDE) fused_tile_kernel<N, MODE, 1, WIDE, kUseSums><<<blocks, S::kThreads, 0, stream>>>(a)
   if (mode == kTileEncode && !wide) AQUAKV_TILE_N(kTileEncode, false);
