@@ -65,7 +65,7 @@ template <> struct Storage<float> {
       v[4 * c] = a.x; v[4 * c + 1] = a.y; v[4 * c + 2] = a.z; v[4 * c + 3] = a.w;
     }
   }
-  template <bool REVERSED, int N> static __device__ __forceinline__ void store(float* row, int pos, const float (&v)[N]) {
+  template <bool REVERSED, int N> static __device__ __forceinline__ void store(float* row, int pos, const float (&v)[N], bool = false) {
     float* const p = row + pos * N;
 #pragma unroll
     for (int c = 0; c < N / 4; ++c) {
@@ -102,7 +102,8 @@ template <> struct Storage<bf16_t> {
   // (32 MiB; 128 MiB: 3.3 against 6.5).  So with 32 values per lane the quad's lanes exchange pieces first, one instruction per
   // value: 64 bytes of a quad per store.  Decode of 32768 tokens 224 -> 212 us, encode 269 / 270 (bound by vector issue).  With 16
   // values, 32 bytes per lane (3.7 and 5.6 TB/s), the exchange costs what it gains.
-  template <bool REVERSED, int N> static __device__ __forceinline__ void store(bf16_t* p, int pos, const float (&v)[N]) {
+  // stream (with 32 values per lane): the launch writes more than its reader will find in L2 (streams()).
+  template <bool REVERSED, int N> static __device__ __forceinline__ void store(bf16_t* p, int pos, const float (&v)[N], bool stream = false) {
     constexpr int kPieces = N / 8;
     u32x4 r[kPieces];
 #pragma unroll
@@ -117,7 +118,15 @@ template <> struct Storage<bf16_t> {
       quad_exchange<2, REVERSED>(r[1], r[3]);
       bf16_t* const at = p + (pos & ~3) * N + (pos & 3) * 8;
 #pragma unroll
-      for (int c = 0; c < kPieces; ++c) *reinterpret_cast<u32x4*>(at + 32 * c) = r[c];
+      for (int c = 0; c < kPieces; ++c) {
+        if (stream) {                                     // (the empty statements keep the compiler from making the two stores one)
+          asm volatile("");
+          __builtin_nontemporal_store(r[c], reinterpret_cast<u32x4*>(at + 32 * c));
+          asm volatile("");
+        } else {
+          *reinterpret_cast<u32x4*>(at + 32 * c) = r[c];
+        }
+      }
     } else {
 #pragma unroll
       for (int c = 0; c < kPieces; ++c) reinterpret_cast<u32x4*>(p + pos * N)[c] = r[c];
@@ -127,6 +136,12 @@ template <> struct Storage<bf16_t> {
     return static_cast<float>(static_cast<bf16_t>(x));
   }
 };
+
+// Whether rows of `elements` bf16 values in all are written past the L2s (32 MiB over the XCDs): from 16 MiB on a launch's reader, the next
+// one, finds little of them there, and dirty lines cost their eviction.  Layer after layer, encode and decode of 8192 tokens 3.90 -> 3.76 ms
+// for 28 layers, of 32768 14.86 -> 14.74 for 32; attention over 8192 tokens 69.8 -> 67.8 us.  Below, the reader is slower: attention over
+// four caches of 5376 compressed rows in all 467 -> 481 us.
+__device__ __forceinline__ bool streams(int64_t elements) { return elements >= ((int64_t)1 << 23); }
 
 // 8 bf16 in a 16-byte register quad -> fp32
 __device__ __forceinline__ void unpack_bf16x8(const u32x4 r, float* v) {

@@ -190,7 +190,7 @@ __device__ __forceinline__ void fused_body(
       for (int k = 0; k < 4; ++k) unpack_bf16x8(in.x[k], &v[8 * k]);
       quantize_group<NCW, false, 8>(v, p, sf, q, cl.cb, use_table ? cl.table : nullptr, active, gid, codes, scales,
                           Xhat != nullptr);
-      if (Xhat != nullptr && active) Storage<bf16_t>::store<false>(Xhat + off, q, v);
+      if (Xhat != nullptr && active) Storage<bf16_t>::store<false>(Xhat + off, q, v, streams(T * D));
     } else {
       if constexpr (!WIDE || is_rtn(NCW)) {
         dequantize_words<NCW>(in.w, p, sf, q, cl.cb, v);
@@ -199,7 +199,7 @@ __device__ __forceinline__ void fused_body(
         if (pass + 1 < kPasses) fetch_wide(pass + 1, wide_codes);
         dequantize_across_heads<NCW>(wc, in.w.scale, head, q, p, sf, cl.cb, v);
       }
-      if (Xhat != nullptr && active) Storage<bf16_t>::store<false>(Xhat + off, q, v);
+      if (Xhat != nullptr && active) Storage<bf16_t>::store<false>(Xhat + off, q, v, streams(T * D));
       if constexpr (MODE == kWeighted) {
         // every parked row of this pass has been read by now (no load may sink below this point): the decoded
         // rows, rounded as they are stored, go where the first pass's rows were

@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kWaves2 * 64) void fused_two_heads_kernel(
       } else {
         dequantize_words<NCW>(ip.w, p, sf, q, cl.cb, v);
       }
-      if (Xhat != nullptr && active) Storage<bf16_t>::store<false>(Xhat + off, q, v);
+      if (Xhat != nullptr && active) Storage<bf16_t>::store<false>(Xhat + off, q, v, streams(T * D));
       if constexpr (MODE == kScores2)
         score_row(v, q, head, H, q_heads, rowc / seq_len, rowc % seq_len, seq_len, active, qv, score_scale, scores, rope_cos, rope_sin,
                   queries.staged ? q_lds + (wave & 1) * (q_heads / H) * kQueryLdsStride : nullptr);
