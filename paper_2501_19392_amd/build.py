@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libaquakv.so")
 SOURCES = ["api.hip", "predict_gemm.hip", "codec_kernels.hip", "fused_kernels.hip", "fused_wide_encode.hip", "fused_two_heads.hip", "folded_scores.hip", "calibrate.hip", "exact_gram.hip",
-           "weighted_values.hip", "attend_cache.hip", "copy_ranges.hip",
+           "weighted_values.hip", "attend_cache.hip", "copy_ranges.hip", "predict_two_tiles.hip",
            *(f"fused_tile_{rows}.hip" for rows in (32, 64, 96, 128, 192, 320))]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",

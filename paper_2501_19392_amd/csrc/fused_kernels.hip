@@ -16,6 +16,8 @@
 #include "gemm_core.h"
 #include "kernels.h"
 
+#include <utility>
+
 namespace aquakv {
 namespace {
 
@@ -546,8 +548,13 @@ hipError_t launch_tile_predict_pair(const FusedTensor* tensors, const Prediction
     jobs[i] = tensor_args(tensors[i], nullptr, T, D);
     jobs[i].P = out[i];
   }
-  const auto tiles = [&](int64_t rows) { return 2 * ((T + rows - 1) / rows) * (D / BN); };
+  const auto of_one = [&](int64_t rows) { return (T + rows - 1) / rows * (D / BN); };
+  const auto tiles = [&](int64_t rows) { return 2 * of_one(rows); };
   if (tiles(32) <= 256) return launch_tile_two_32(kTilePredict, 16, jobs, stream);
+  // The first tensor has the longer product: smaller tiles for it, as long as both fit the CUs in one round.
+  if (jobs[0].d0 + jobs[0].d1 >= 2 * (jobs[1].d0 + jobs[1].d1))
+    for (const auto& r : {std::pair<int, int>{32, 96}, {64, 128}, {64, 192}, {96, 192}, {128, 192}})
+      if (of_one(r.first) + of_one(r.second) <= 256) return launch_predict_two_tiles(r.first, r.second, jobs, stream);
   if (tiles(64) <= 256) return launch_tile_two_64(kTilePredict, 16, jobs, stream);
   if (tiles(96) <= 256) return launch_tile_two_96(kTilePredict, 16, jobs, stream);
   if (tiles(128) > 256 && tiles(192) <= 256) return launch_tile_two_192(kTilePredict, 16, jobs, stream);

@@ -53,6 +53,10 @@ struct TilePair {
   TileArgs job[2];
   int blocks;
 };
+// Job 0 on tiles of MB0 row blocks, job 1 on tiles of MB1
+template <int MB0, int MB1> struct TwoTiles {
+  static constexpr int kWaves = Tile<MB0>::kWaves > Tile<MB1>::kWaves ? Tile<MB0>::kWaves : Tile<MB1>::kWaves;
+};
 // What is done about sums: nothing, the product goes on from those that are there, or `keep` says whether they alone are wanted.
 enum TileSums : int { kNoSums = 0, kUseSums = 1, kKeepSums = 2 };
 // Decode of one or two tensors (job[1] has `tiles` - pair.blocks workgroups) and, on the workgroups behind them, pieces of the attention of
@@ -106,10 +110,11 @@ template <int MODE, int MB> struct TileEpilogue {
   static_assert(kBytes <= 160 * 1024, "LDS of one CU");
   static constexpr int kLdsBytes = kBytes > S::kLdsBytes ? kBytes : S::kLdsBytes;
 };
-// workgroup `block` of the `nblocks` that work on `a`; smem: TileEpilogue<MODE, MB>::kLdsBytes of LDS
-template <int NCW, int MODE, int MB, bool WIDE, int SUMS>
-__device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nblocks, bool keep, unsigned char* smem) {
+// workgroup `block` of those that work on `a`, of WAVES waves; smem: TileEpilogue<MODE, MB>::kLdsBytes of LDS
+template <int NCW, int MODE, int MB, bool WIDE, int SUMS, int WAVES = Tile<MB>::kWaves>
+__device__ __forceinline__ void fused_tile(const TileArgs& a, int block, bool keep, unsigned char* smem) {
   using S = Tile<MB>;
+  static_assert(WAVES == S::kWaves || (MODE == kTilePredict && WAVES > S::kWaves), "an epilogue is split over the tile's own number of waves");
   static_assert(!WIDE || MODE != kTileEncode, "the quantizer needs the whole group: groups across the heads are not fused");
   using E = TileEpilogue<MODE, MB>;
   constexpr int kVals = E::kVals, kWaveRows = E::kWaveRows, kPassRows = E::kPassRows, kPasses = E::kPasses;
@@ -236,7 +241,7 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
       }
       __syncthreads();
       const int here = (MB - first < E::kParkBlocks ? MB - first : E::kParkBlocks) * 32;
-      for (int row = wave * 2 + fk; row < here && first * 32 + row < n_rows; row += 2 * S::kWaves)
+      for (int row = wave * 2 + fk; row < here && first * 32 + row < n_rows; row += 2 * WAVES)
         *reinterpret_cast<f32x4*>(out + (m0 + first * 32 + row) * a.P.stride) = *reinterpret_cast<const f32x4*>(rows + row * kLdP + frow * 4);
     }
     return;
@@ -309,29 +314,41 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, int nbl
 template <int NCW, int MODE, int MB, bool WIDE, int SUMS>
 __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(Tile<MB>::kWaves / 4))) void fused_tile_kernel(const TileArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[TileEpilogue<MODE, MB>::kLdsBytes];
-  fused_tile<NCW, MODE, MB, WIDE, SUMS>(a, (int)blockIdx.x, (int)gridDim.x, false, smem);
+  fused_tile<NCW, MODE, MB, WIDE, SUMS>(a, (int)blockIdx.x, false, smem);
 }
-// Workgroup blockIdx.x of a launch for two jobs, the first `blocks` of the `tiles` on job[0].  The job is read from where it was passed,
-// byte `at` of the kernel's arguments (an index into a copy would put them in scratch).
-template <int NCW, int MODE, int MB, bool WIDE, int SUMS>
-__device__ __forceinline__ void fused_tile_of_pair(int at, int blocks, int tiles, unsigned char* smem) {
-  const int second = (int)blockIdx.x >= blocks;
+// Job `second` of the two at byte `at` of the kernel's arguments: read from where it was passed (an index into a copy would put them in
+// scratch).
+__device__ __forceinline__ TileArgs job_of_pair(int at, int second) {
   TileArgs a;
   __builtin_memcpy(&a, (const char*)__builtin_amdgcn_kernarg_segment_ptr() + at + second * (int)sizeof(TileArgs), sizeof(TileArgs));
-  fused_tile<NCW, MODE, MB, WIDE, SUMS>(a, (int)blockIdx.x - (second ? blocks : 0), second ? tiles - blocks : blocks,
-                                        SUMS == kKeepSums && a.sums_hi != nullptr, smem);
+  return a;
+}
+// Workgroup blockIdx.x of a launch for two jobs, the first `blocks` on job[0].
+template <int NCW, int MODE, int MB, bool WIDE, int SUMS>
+__device__ __forceinline__ void fused_tile_of_pair(int at, int blocks, unsigned char* smem) {
+  const int second = (int)blockIdx.x >= blocks;
+  const TileArgs a = job_of_pair(at, second);
+  fused_tile<NCW, MODE, MB, WIDE, SUMS>(a, (int)blockIdx.x - (second ? blocks : 0), SUMS == kKeepSums && a.sums_hi != nullptr, smem);
 }
 // (a kernel of its own: picking the job puts another round of scalar loads ahead of everything, 0.4 us)
 template <int NCW, int MODE, bool WIDE>
 __global__ __launch_bounds__(Tile<1>::kThreads) __attribute__((amdgpu_waves_per_eu(Tile<1>::kWaves / 4))) void fused_tile_pair_kernel(const TilePair pair) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[TileEpilogue<MODE, 1>::kLdsBytes];
-  fused_tile_of_pair<NCW, MODE, 1, WIDE, kKeepSums>(0, pair.blocks, (int)gridDim.x, smem);
+  fused_tile_of_pair<NCW, MODE, 1, WIDE, kKeepSums>(0, pair.blocks, smem);
 }
 // Two tensors that are encoded, or predicted (MODE)
 template <int NCW, int MODE, int MB>
 __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per_eu(Tile<MB>::kWaves / 4))) void fused_tile_two_kernel(const TilePair pair) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[TileEpilogue<MODE, MB>::kLdsBytes];
-  fused_tile_of_pair<NCW, MODE, MB, false, kNoSums>(0, pair.blocks, (int)gridDim.x, smem);
+  fused_tile_of_pair<NCW, MODE, MB, false, kNoSums>(0, pair.blocks, smem);
+}
+// The predictions of two tensors on tiles of different sizes
+template <int MB0, int MB1, int WAVES = TwoTiles<MB0, MB1>::kWaves>
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVES / 4))) void predict_two_tiles_kernel(const TilePair pair) {
+  constexpr int kLds0 = TileEpilogue<kTilePredict, MB0>::kLdsBytes, kLds1 = TileEpilogue<kTilePredict, MB1>::kLdsBytes;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[kLds0 > kLds1 ? kLds0 : kLds1];
+  if ((int)blockIdx.x < pair.blocks) fused_tile<16, kTilePredict, MB0, false, kNoSums, WAVES>(job_of_pair(0, 0), (int)blockIdx.x, false, smem);
+  else fused_tile<16, kTilePredict, MB1, false, kNoSums, WAVES>(job_of_pair(0, 1), (int)blockIdx.x - pair.blocks, false, smem);
 }
 // The pieces of a launch that workgroup `block` of those behind its tiles takes: one per kAttendThreads threads.
 template <int THREADS>
@@ -347,7 +364,7 @@ __global__ __launch_bounds__(Tile<MB>::kThreads) __attribute__((amdgpu_waves_per
   constexpr int kTileBytes = TileEpilogue<kTileDecode, MB>::kLdsBytes, kAttendBytes = Tile<MB>::kThreads / kAttendThreads * (int)sizeof(AttendLds);
   __shared__ __attribute__((aligned(16))) unsigned char smem[kTileBytes > kAttendBytes ? kTileBytes : kAttendBytes];
   if ((int)blockIdx.x < job.tiles) {
-    fused_tile_of_pair<NCW, kTileDecode, MB, WIDE, kNoSums>((int)offsetof(TileAttend, pair), job.pair.blocks, job.tiles, smem);
+    fused_tile_of_pair<NCW, kTileDecode, MB, WIDE, kNoSums>((int)offsetof(TileAttend, pair), job.pair.blocks, smem);
   } else {
     const char* const args = (const char*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(TileAttend, attend);
     attend_behind_tiles<Tile<MB>::kThreads>(*(AttendCacheParam*)args, (int)blockIdx.x - job.tiles, smem);
@@ -381,6 +398,8 @@ AQUAKV_TILE_TWO_LAUNCHER(64);
 AQUAKV_TILE_TWO_LAUNCHER(96);
 AQUAKV_TILE_TWO_LAUNCHER(128);
 AQUAKV_TILE_TWO_LAUNCHER(192);
+// Predictions of two jobs on tiles of rows0 and rows1 rows: 32 and 96, 64 and 128, 64 and 192, 96 and 192 or 128 and 192.
+hipError_t launch_predict_two_tiles(int rows0, int rows1, const TileArgs* jobs, hipStream_t stream);
 // Tiles of 32 rows, encode or decode: a product that goes on from stored sums.
 hipError_t launch_tile_rest(int mode, int n_codewords, bool wide, const TileArgs& a, hipStream_t stream);
 
@@ -411,14 +430,15 @@ hipError_t launch_tile(int mode, int n_codewords, bool wide, int n_seq, TileArgs
 }
 
 // fills in the jobs' tiles, returns how many there are
-template <int MB>
+template <int MB0, int MB1 = MB0>
 int pair_jobs(TilePair& pair, const TileArgs* jobs, int n) {
   int tiles = 0;
   for (int i = 0; i < 2; ++i) {
+    const int rows = i == 0 ? Tile<MB0>::kRows : Tile<MB1>::kRows;
     TileArgs& job = pair.job[i];
     job = jobs[i < n ? i : 0];
-    job.tiles_per_seq = (job.seq_len + Tile<MB>::kRows - 1) / Tile<MB>::kRows;
-    job.xcd = xcd_split(job.tiles_per_seq, job.D / kGroup, Tile<MB>::kRows);
+    job.tiles_per_seq = (job.seq_len + rows - 1) / rows;
+    job.xcd = xcd_split(job.tiles_per_seq, job.D / kGroup, rows);
     if (i < n) tiles += job.tiles_per_seq * (job.D / kGroup);
     if (i == 0) pair.blocks = tiles;
   }
