@@ -181,20 +181,18 @@ def test_lds_words_requested_by_assembly_are_left_alone(built):
     assert requests >= 2
 
 
-def test_small_tiles_start_their_matrix_instructions_ahead_of_the_next_loads(built):
-    """In the steady loop of the tiles of 32 and 64 rows a wave has one chain of four matrix instructions per k-tile: the loads of a later
-    k-tile are issued behind the first of them, which covers them, and a fragment's address takes one addition."""
+def test_waves_that_multiply_issue_no_loads(built):
+    """In the steady loop of a tile's multiplying waves every load is another wave's: four matrix instructions (k 64) for each block of the
+    wave, its fragments from LDS, one barrier, and at most one address addition for each k step and operand."""
     checked = 0
     for name, code, labels in built:
-        if not re.search(r"fused_tile(_pair)?_kernelILi\d+ELi\dELi[12]E", name):
+        if not (m := re.search(r"fused_tile(_pair)?_kernelILi\d+ELi\dELi(\d+)E", name)):
             continue
         starts = sorted({0, *labels.values(), len(code)})
         for begin, end in zip(starts, starts[1:]):
             ops = [op for op, _ in code[begin:end]]
-            mfma = [i for i, op in enumerate(ops) if op == "v_mfma_f32_32x32x16_bf16"]
-            loads = [i for i, op in enumerate(ops) if op.startswith("global_load_lds")]
-            if len(mfma) == 4 and loads and ops.count("ds_read_b128") == 8:
+            if ops.count("s_barrier") == 1 and ops.count("v_mfma_f32_32x32x16_bf16") == 4 * int(m[2]):
                 checked += 1
-                assert mfma[0] < loads[0], (name, begin)
+                assert not any(op.startswith(("global_load", "buffer_load")) for op in ops), (name, begin)
                 assert ops.count("v_add_u32_e32") <= 8, (name, begin)
-    assert checked > 50
+    assert checked > 150
