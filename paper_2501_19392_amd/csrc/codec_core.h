@@ -277,19 +277,6 @@ struct Lds {
   uint32_t table[kTableWords];
 };
 
-template <int NCW>
-__device__ __forceinline__ void stage_lds(Lds& lds, const float* __restrict__ codebook,
-                                          const uint32_t* __restrict__ table) {
-  load_codebook<NCW>(codebook, lds.cb);
-  if (table != nullptr) {
-    const u32x4* src = reinterpret_cast<const u32x4*>(table);
-    u32x4* dst = reinterpret_cast<u32x4*>(lds.table);
-    for (int i = threadIdx.x; i < kTableWords / 4; i += blockDim.x) dst[i] = src[i];
-  }
-  __syncthreads();
-}
-
-
 // The table on its way from memory to LDS through registers (kernels that request it while their LDS is still in
 // other use): 16-byte chunk t + i * THREADS for thread t.
 template <int THREADS> struct TableRegs {
