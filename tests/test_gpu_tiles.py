@@ -332,3 +332,16 @@ def test_stand_alone_quantizer_in_more_workgroups_than_are_resident(H, T, quanti
     torch.cuda.synchronize()
     for name, a, b in zip(("k codes", "k scales", "v codes", "v scales", "K", "V"), got, want):
         assert torch.equal(bits(a), bits(b)), name
+
+
+@pytest.mark.parametrize("H,dk,T", [(8, 256, 10241), (8, 128, 12288), (8, 128, 12289), (8, 128, 16385), (8, 128, 18432), (8, 128, 18433), (4, 256, 33000),
+                                    (3, 128, 29000)])
+@pytest.mark.parametrize("quantizer,rht_group", [("n16", None), ("rtn2", None), ("n16", 1024), ("n64", 1024)])
+def test_tiles_of_192_rows_in_several_rounds(H, dk, T, quantizer, rht_group):
+    test_tiles_give_the_bits_of_the_stage_calls(H, dk, T, quantizer, rht_group)
+
+
+@pytest.mark.parametrize("batch,S", [(16, 1100), (3, 3500)])
+@pytest.mark.parametrize("quantizer,rht_group", [("n16", None), ("n256", 1024)])
+def test_scores_on_tiles_of_192_rows_in_several_rounds(batch, S, quantizer, rht_group):
+    test_scores_of_a_batch_are_those_of_its_sequences(8, 128, batch, S, quantizer, rht_group)
