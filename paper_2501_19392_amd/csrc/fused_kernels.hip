@@ -9,7 +9,7 @@
 // value side of attention needs (weighted), on those 256 groups as the epilogue.  Against separate kernels this
 // saves writing and re-reading 4 bytes per value of fp32 predictions and a launch.
 //
-// Arithmetic is the same as in the stand-alone kernels (same main loop, same group bodies,
+// Arithmetic is the same as in the stand-alone kernels (same order of K, same group bodies,
 // prediction carried in fp32), so fused and unfused paths give identical bits.
 #include "fused_epilogue.h"
 #include "fused_tile.h"
@@ -30,9 +30,8 @@ constexpr int kEpilogueLdsBytes = kPredBytes + (int)sizeof(Lds);
 constexpr int kFusedLdsBytes = kEpilogueLdsBytes > kMainLoopLdsBytes ? kEpilogueLdsBytes : kMainLoopLdsBytes;
 static_assert(kFusedLdsBytes <= 160 * 1024, "LDS of one CU");
 
-// 8 wavefronts per tile (two per SIMD): the main loop is bound by L2 -> LDS traffic either
-// way, and the second wave fills the issue slots the first leaves in the VALU-heavy epilogue
-// (measured: encode 10 % faster than with 4 wavefronts, decode unchanged).
+// 8 wavefronts per tile: four multiply and four load (gemm_tile.h), and in the VALU-heavy epilogue the second of a SIMD fills
+// the issue slots that the first leaves.
 constexpr int kWaves = 8;
 
 enum Mode : int { kEncode = 0, kDecode = 1, kScores = 2, kWeighted = 3 };
@@ -391,7 +390,8 @@ hipError_t launch(int n_codewords, const void* x0, int d0, const void* x1, int d
 // 0: the tiles of 256 rows x one or two heads.
 //
 // A CU holds one workgroup, so what counts is the rounds of workgroups over the CUs and the rows of a round.  Ranges that
-// fill the chip in one round take the smallest tile that still does.  Keys and values x 8 heads, us:
+// fill the chip in one round take the smallest tile that still does.  Keys and values x 8 heads, us (with main loops whose waves all loaded and
+// multiplied; now a tenth less, and no size between 3100 and 6144 tokens has a tile more than 2 % faster than its own):
 //   1024 tokens  encode 23.6 on 32 rows, 27.0 on 64, 38.8 on 128 (decode 19.1, 22.3, 30.7)
 //   2048         28.7 on 64, 39.5 on 128 (24.3, 31.1)
 //   2100         34.1 on 96, 39.8 on 128 (28.7, 31.4); 3072 39.2, 41.9 (32.4, 32.7)
@@ -549,8 +549,8 @@ hipError_t launch_fused_encode_pair(int n_codewords, const FusedTensor* tensors,
 
 // Predictions of two tensors (groups across the heads): a tile is a main loop and its stores, and two launches of the predictor and two of
 // the quantizer become one each, so it pays up to two rounds of tiles of 128 rows.  Stack of 8 layers, 16 points, us, a layer at a time /
-// together: 128 rows 222 / 143, 512 236 / 164, 1200 282 / 217 (on 64 rows 230), 1400 291 / 215 (on 128 rows 240), 2304 405 / 310 (on 128 rows
-// 316), 3072 420 / 329 (362), 4096 490 / 469.
+// together, with main loops whose waves all loaded and multiplied: 128 rows 222 / 143, 512 236 / 164, 1200 282 / 217 (on 64 rows 230), 1400 291 / 215
+// (on 128 rows 240), 2304 405 / 310 (on 128 rows 316), 3072 420 / 329 (362), 4096 490 / 469.
 int64_t tile_predict_pair_rows(int D) { return 512 / 2 / (D / BN) * 128; }
 hipError_t launch_tile_predict_pair(const FusedTensor* tensors, const Prediction* out, int64_t T, int D, hipStream_t stream) {
   if (T == 0) return hipSuccess;
@@ -562,7 +562,9 @@ hipError_t launch_tile_predict_pair(const FusedTensor* tensors, const Prediction
   const auto of_one = [&](int64_t rows) { return (T + rows - 1) / rows * (D / BN); };
   const auto tiles = [&](int64_t rows) { return 2 * of_one(rows); };
   if (tiles(32) <= 256) return launch_tile_two_32(kTilePredict, 16, jobs, stream);
-  // The first tensor has the longer product: smaller tiles for it, as long as both fit the CUs in one round.
+  // The first tensor has the longer product: smaller tiles for it, as long as both fit the CUs in one round (2304 rows, 192 each 20.8 us, 128 and
+  // 192 17.5).  Tiles that are encoded or decoded stay of one size: the append of a prompt is bound by the host there, and a recovery
+  // needs the CUs that are left for the pieces of attention (1100 rows 102 / 120 us a token of six layers, 2200 145 / 159).
   if (jobs[0].d0 + jobs[0].d1 >= 2 * (jobs[1].d0 + jobs[1].d1))
     for (const auto& r : {std::pair<int, int>{32, 96}, {64, 128}, {64, 192}, {96, 192}, {128, 192}})
       if (of_one(r.first) + of_one(r.second) <= 256) return launch_predict_two_tiles(r.first, r.second, jobs, stream);

@@ -1,11 +1,14 @@
 // Fused predictor kernels (Alg. "encode" / "decode" of the AQUA-KV paper: predictor of Sect. 3.2, backbone of Sect. 2) on
 // tiles of 32, 64, 96, 128, 192 or 320 token rows x one kv head (which one: tile_rows in fused_kernels.hip).
 //
-// Same main-loop bits (gemm_tile.h), same group bodies, hence the same results.  The epilogue parks up to 128 rows of the
-// tile at a time and works on them 16 groups per wave, one group per quad of lanes; on tiles of 32 and 64 rows, which would
+// Same main-loop bits (gemm_tile.h), same group bodies, hence the same results.  Only the four multiplying waves hold accumulators; the
+// epilogue parks them in LDS, all rows where they fit (else 256), and all waves work on them, 16 groups per wave and pass, one
+// group per quad of lanes; on tiles of 32 and 64 rows, which would
 // leave half of the waves (32 rows) or one of two per SIMD (64) idle, 8 groups per wave, one group per eight lanes.  A wave alone
 // on its SIMD is bound by latency, so the work per lane is what counts: keys and values of 128 tokens, 16-point grid, 22.9 -> 20.8 us
-// (256 points: 29.8 -> 25.1), decode of 1100 tokens with groups across the heads 27.7 -> 24.4.
+// (256 points: 29.8 -> 25.1), decode of 1100 tokens with groups across the heads 27.7 -> 24.4 (those with the main loops before: now 17.1 and
+// 21.3).  The encoder's epilogue is bound by vector issue, 41 to 44 instructions a value.  Codes turned back by further waves
+// during the main loop gained nothing: their LDS reads hold up the operands' (4000 tokens across the heads 34.5 -> 48 us).
 // On 96 and 192 rows three waves share a SIMD, 168 registers each: with 16 values per lane and four sub-vectors searched at a time the quantizer takes
 // 105; with eight at a time it spilled (3072 tokens 35.4 us against 39.6; 64 points 38.2 against 45.6).
 #pragma once

@@ -74,7 +74,7 @@ __device__ __forceinline__ void team_post(uint32_t word, uint32_t value) {
 
 // acc[j][i]: outputs n = 64 (lane / 32) + 16 j + 4 blk + r (register 4 blk + r) of token 64 wave + 32 i + lane % 32.
 // `arrive_words`: this team's four words in LDS; `epoch`: this wave's running count of published k-tiles (same in all
-// four waves of the team).  Requirements as gemm_mainloop: K = d0 + d1 a multiple of 128, d0 of 64.
+// four waves of the team).  Requirements: K = d0 + d1 a multiple of 128, d0 of 64.
 // `before_drain()` is called once, when the last operand loads are out.
 template <typename BeforeDrain>
 __device__ __forceinline__ void gemm_team_mainloop(unsigned char* lds_base, const uint32_t* arrive_words, uint32_t& epoch,

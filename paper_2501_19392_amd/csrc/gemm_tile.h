@@ -1,16 +1,18 @@
-// bf16 MFMA main loop of the linear predictors (Sect. 3.2 of the AQUA-KV paper) for tiles of 32, 64, 96, 128, 192 or 320 token
+// bf16 MFMA main loop of the linear predictors (Sect. 3.2 of the AQUA-KV paper) for tiles of 32, 64, 96, 128, 192, 256 or 320 token
 // rows x 128 outputs (one kv head): the shapes a launch picks from so that its tiles fill the CUs evenly.
 //
-// Same instruction (v_mfma_f32_32x32x16_bf16), operand orientation, swizzled LDS layout, direct-to-LDS loads and K order
-// per output as gemm_core.h, hence the same bits.  One workgroup per CU.
-//   * 32 rows: four waves split the 128 columns; 64 rows: eight, 96 rows: twelve (three per SIMD), each holding 32 of the rows.  Such a tile is bound by the stream of
-//     operands from L2, (rows + 128) x 128 bytes per k-tile of 64, most of it W: a deep ring of k-tiles in LDS keeps it
-//     coming, and a wave reads the fragments of a whole k-tile ahead (its steps of 16 k are one or two MFMAs long).
-//     Measured with 32 rows: 0.18 us per k-tile = 57 bytes per cycle into a CU, of 64; a 256-row tile takes 0.6 to 0.9.
-//     The next loads are issued behind the first MFMA of a k-tile, which covers them: ahead of it, where the compiler put them while
-//     that was left to it, with two additions per fragment address, one tensor took 2 to 5 % longer (128 rows, uniform backbone, keys 7.34 -> 6.98 us).
-//   * From 128 rows on: eight waves (two per SIMD) as 2 x 4, wave (wm, wn) holds columns 32 wn ... and every second block
-//     of 32 rows: (MI + 1) / MI operand reads per MFMA, MI = rows / 64.  192 rows: twelve waves as 3 x 4, MI = 2.
+// Operands, LDS layout, K order: gemm_core.h, hence the same bits on every tile.  One workgroup per CU.
+//   * Waves 0 .. 3, one per SIMD, multiply: below 128 rows each takes all rows and a quarter of the columns, from 128 rows on half of either.
+//     Waves 4 .. 7 load, so a multiplying wave issues MFMAs and fragment reads and nothing else: a load's address arithmetic and its
+//     issue, 16 cycles each, are on another wave.  192 and 96 rows have four more waves, for the epilogue (three per SIMD, 168 registers).
+//   * What counts for a wave that is alone with its SIMD's matrix core is that no MFMA waits: fragments are read three steps of 16 k ahead up
+//     to 128 rows (one beyond, where a step has enough MFMAs to cover an LDS read's 60 cycles and the registers are taken), across
+//     the barrier that publishes the next k-tile.
+//   * LDS holds as many k-tiles as fit: from L2 a k-tile takes 1 to 2 us, several times its MFMAs on the small tiles.
+// Cycles per k-tile of 64 at K = 1024, before (all waves load and multiply) and now, 32 cycles per MFMA of a SIMD being the floor:
+//   32 rows 450 -> 331 (128; bound by (rows + 128) x 128 bytes from L2 at 60 bytes a cycle), 64 552 -> 400 (256), 96 707 -> 483 (384),
+//   128 918 -> 608 (512), 192 1217 -> 844 (768), 256 1379 -> 1092 (1024), 320 1878 -> 1709 (1280).
+// 256 rows and more run at 1.55 to 1.75 GHz on random operands (2.4 on zeros): there the power limit binds, not the issue.
 #pragma once
 #include "gemm_core.h"
 
