@@ -124,3 +124,10 @@ def test_a_stack_has_the_bits_of_its_layers(tokens, rht_group):
         for l in (len(layers) - 2, len(layers) - 1):
             for x, y in zip(hat[2 * (l & 1):2 * (l & 1) + 2], hats[l]):
                 assert torch.equal(x.view(torch.int16), y.view(torch.int16)), (l, room)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tokens", [768, 769, 1344, 1345, 1536, 2016, 2017, 2432, 2433])
+def test_predictions_of_two_tensors_on_tiles_of_two_sizes(tokens):
+    """Both sides of the lines between the pairs of sizes (groups across the heads)."""
+    test_a_stack_has_the_bits_of_its_layers(tokens, 1024)

@@ -918,6 +918,13 @@ def test_folded_scores_against_definition(B, n, QH, batch, S, bias):
     assert np.all(np.abs(U.np64(sc2) - want2) <= U.RTOL["bf16"] * 0.25 * mag2 + 1e-30)
 
 
+@pytest.mark.parametrize("QH,batch", [(8, 32), (8, 33), (16, 15), (16, 17), (24, 11), (32, 8), (32, 9), (40, 9), (64, 9)])
+def test_folded_queries_at_the_edges_of_their_blocks(B, QH, batch):
+    """The queries are folded 32 (entry, query head) rows of a kv head at a time: batches around the entries that make 32 rows."""
+    test_folded_scores_against_definition(B, 16, QH, batch, 5, True)
+
+
+
 @pytest.mark.parametrize("dtype,n,with_pred", [("bf16", 16, True), ("bf16", 64, False), ("fp32", 16, True)])
 def test_attn_scores_with_rotary_embedding(B, dtype, n, with_pred):
     """aquakv_decode_attn_scores_rope: keys cached before the rotary embedding are rotated by their position

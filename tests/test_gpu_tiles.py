@@ -345,3 +345,11 @@ def test_tiles_of_192_rows_in_several_rounds(H, dk, T, quantizer, rht_group):
 @pytest.mark.parametrize("quantizer,rht_group", [("n16", None), ("n256", 1024)])
 def test_scores_on_tiles_of_192_rows_in_several_rounds(batch, S, quantizer, rht_group):
     test_scores_of_a_batch_are_those_of_its_sequences(8, 128, batch, S, quantizer, rht_group)
+
+
+@pytest.mark.parametrize("H,dk,T", [(8, 128, 1500), (8, 128, 2500), (8, 128, 3500), (8, 128, 5000), (8, 128, 9000),      # two k-tiles, fewer than LDS holds
+                                    (8, 128, 8191), (8, 128, 8192),                # from 16 MiB on rows are written past the L2s
+                                    (5, 128, 1500), (12, 256, 900), (8, 256, 3600), (2, 128, 20000)])      # row blocks and heads that the XCDs share unevenly
+@pytest.mark.parametrize("quantizer,rht_group", [("n16", None), ("n256", 1024)])
+def test_tiles_of_short_products_and_uneven_shares(H, dk, T, quantizer, rht_group):
+    test_tiles_give_the_bits_of_the_stage_calls(H, dk, T, quantizer, rht_group)
