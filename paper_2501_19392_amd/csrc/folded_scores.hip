@@ -47,7 +47,7 @@ static_assert(kFoldBytesPerBatch == kFoldedBytesPerBatch, "the size the C-ABI la
 // up to 32 query heads (`entries` batch entries x rep heads); wave w has channels 32 w ... of them.  W comes in 8 x 8 blocks of (row,
 // channel), one per thread, which turns it in registers into the operands' order (8 rows of a channel) on the way to LDS.
 // Bound by reading W once per 32 query heads (before: once per batch entry, and 400 vector instructions per thread and entry): 64 batch
-// entries x 32 query heads 26.3 -> 5.9 us.  Workgroups with cc == 0 also write q . b and the rotated queries.
+// entries x 32 query heads 26.3 -> 9.3 us (the scoring call 519 -> 503).  Workgroups with cc == 0 also write q . b and the rotated queries.
 constexpr int kFoldChunks = 8;
 constexpr int kFoldOutLd = 36;                  // padded row of a wave's 32 x 32 results
 __global__ __launch_bounds__(256) void fold_query_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ W,
