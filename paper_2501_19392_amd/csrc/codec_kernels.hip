@@ -160,6 +160,8 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(const QuantizeIo i
   const int8_t* __restrict__ const signs = blockIdx.y ? io1.signs : io0.signs;
   T* __restrict__ const Xhat = static_cast<T*>(blockIdx.y ? io1.Xhat : io0.Xhat);
   __shared__ float4 cb[is_rtn(NCW) ? 1 : NCW];
+  load_codebook<NCW>(codebook, cb);
+  __syncthreads();
   constexpr int N = kDequantizeVals, kLanes = kGroup / N, kGroups = kThreads / kLanes;       // lanes per group, groups per round
   const int l = WIDE ? token_pos<N>(threadIdx.x) : group_pos<N>(threadIdx.x), q = l & (kLanes - 1), slot = threadIdx.x / kLanes;
   // (a thread meets the same head in every round of the grid-stride loop: the signs are fetched once)
@@ -176,8 +178,6 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(const QuantizeIo i
   const int64_t stride = (int64_t)gridDim.x * kGroups;
   CodeWords cur = {};
   if ((int64_t)blockIdx.x * kGroups < n_groups) cur = request((int64_t)blockIdx.x * kGroups);
-  load_codebook<NCW>(codebook, cb);                       // (while the first words are on their way)
-  __syncthreads();
   for (int64_t g0 = (int64_t)blockIdx.x * kGroups; g0 < n_groups; g0 += stride) {
     CodeWords nxt = {};
     if (g0 + stride < n_groups) nxt = request(g0 + stride);
