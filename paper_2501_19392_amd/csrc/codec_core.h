@@ -256,17 +256,45 @@ __device__ __forceinline__ void unpack_codes(const u32x4 raw, int (&idx)[M]) {
   }
 }
 
+// ... -> the byte offsets of the grid points in the LDS copy of the grid (entries of 16 bytes).  Codes of 4 bits: all of a word moved into the upper
+// half of their bytes at once, then one instruction each (a shift and a mask each otherwise; groups across the heads look up 8 heads for every
+// value: decode of 2300 tokens 27.8 -> 27.1 us, 32768 227 -> 220; groups of one head within 1 %).
+template <int NCW, int M>
+__device__ __forceinline__ void unpack_offsets(const u32x4 raw, uint32_t (&off)[M]) {
+  if constexpr (CodeBits<NCW>::c == 4) {
+    const uint32_t d[2] = {raw.x, raw.y};
+#pragma unroll
+    for (int w = 0; w < M / 8; ++w) {
+      uint32_t even = (d[w] << 4) & 0xf0f0f0f0u, odd = d[w] & 0xf0f0f0f0u;
+      asm("" : "+v"(even), "+v"(odd));                       // (the compiler would fold the steps into a shift and a mask each)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        off[8 * w + 2 * k] = (even >> (8 * k)) & 0xffu;
+        off[8 * w + 2 * k + 1] = (odd >> (8 * k)) & 0xffu;
+      }
+    }
+  } else {
+    int idx[M];
+    unpack_codes<NCW>(raw, idx);
+#pragma unroll
+    for (int m = 0; m < M; ++m) off[m] = (uint32_t)idx[m] << 4;
+  }
+}
+__device__ __forceinline__ float2 grid_point(const float4* cb, uint32_t off) {
+  return *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(cb) + off);
+}
+
 __device__ __forceinline__ float half_bits_to_float(uint16_t h) {
   return static_cast<float>(__builtin_bit_cast(_Float16, h));
 }
 
-// indices of the lane's grid points -> the points times `scale` (recon_scale(sigma16, lane): the input of the inverse
+// offsets of the lane's grid points -> the points times `scale` (recon_scale(sigma16, lane): the input of the inverse
 // transform)
 template <int M>
-__device__ __forceinline__ void gather_zhat(const int (&idx)[M], float scale, const float4* cb, float (&z)[2 * M]) {
+__device__ __forceinline__ void gather_zhat(const uint32_t (&off)[M], float scale, const float4* cb, float (&z)[2 * M]) {
 #pragma unroll
   for (int m = 0; m < M; ++m) {
-    const float4 cw = cb[idx[m]];
+    const float2 cw = grid_point(cb, off[m]);
     z[2 * m] = cw.x * scale;
     z[2 * m + 1] = cw.y * scale;
   }
@@ -567,9 +595,9 @@ __device__ __forceinline__ void dequantize_words(const CodeWords& w, const float
   if constexpr (is_rtn(NCW)) {
     rtn_reconstruct<NCW>(w.code, w.scale, p, v);
   } else {
-    int idx[N / 2];
-    unpack_codes<NCW>(w.code, idx);
-    gather_zhat(idx, recon_scale<WIDE>(half_bits_to_float((uint16_t)w.scale), l), cb, v);
+    uint32_t off[N / 2];
+    unpack_offsets<NCW>(w.code, off);
+    gather_zhat(off, recon_scale<WIDE>(half_bits_to_float((uint16_t)w.scale), l), cb, v);
     reconstruct<WIDE>(v, l, sf, p);
   }
 }

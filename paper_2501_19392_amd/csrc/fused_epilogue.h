@@ -63,11 +63,11 @@ __device__ __forceinline__ void dequantize_across_heads(const WideCodes<NCW>& wc
 #pragma unroll
   for (int half = 0; half < N / 16; ++half) {
     const auto zhat_half = [&](int hh, float (&z)[16]) {
-      int idx[N / 2];
-      unpack_codes<NCW>(wc.h[hh], idx);
+      uint32_t off[N / 2];
+      unpack_offsets<NCW>(wc.h[hh], off);
 #pragma unroll
       for (int m = 0; m < 8; ++m) {
-        const float2 cw = *reinterpret_cast<const float2*>(&cb[idx[8 * half + m]]);
+        const float2 cw = grid_point(cb, off[8 * half + m]);
         z[2 * m] = cw.x * s16;
         z[2 * m + 1] = cw.y * s16;
       }
