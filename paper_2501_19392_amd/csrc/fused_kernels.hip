@@ -66,7 +66,7 @@ __device__ __forceinline__ void fused_body(
   static_assert(!WIDE || MODE != kEncode, "the quantizer needs the whole group: groups across the heads are not fused");
   Lds& cl = *reinterpret_cast<Lds*>(smem);
   unsigned char* const park = smem + sizeof(Lds);          // the parked tile, each wave its own rows
-  const bool use_table = MODE == kEncode && table != nullptr;
+  const bool use_table = MODE == kEncode && !is_rtn(NCW) && table != nullptr;     // (a round-to-nearest layer's grid pointers are never read)
   // grid and cell table: requested from inside the main loop, kept in registers while it owns the LDS
   static_assert(NCW <= WAVES * 64, "one grid point per thread");
   constexpr int kGridPoints = is_rtn(NCW) ? 0 : NCW;

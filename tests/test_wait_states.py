@@ -181,6 +181,18 @@ def test_lds_words_requested_by_assembly_are_left_alone(built):
     assert requests >= 2
 
 
+def test_uniform_quantizers_stage_no_search_table(built):
+    """A round-to-nearest layer's grid pointers may hold anything: its encoders do not fetch a search table, whose way to LDS is the only
+    use of 16-byte stores there (a grid's encoders have them)."""
+    stores = {}
+    for name, code, _ in built:
+        if m := re.search(r"(fused_kernel|fused_two_heads_kernel|fused_tile_kernel|fused_tile_two_kernel|fused_tile_pair_kernel)ILi(\d+)ELi0E", name):
+            stores.setdefault((m[1], int(m[2]) in (2, 4)), []).append(sum(op == "ds_write_b128" for op, _ in code))
+    assert len(stores) == 10
+    for (kernel, uniform), counts in stores.items():
+        assert not any(counts) if uniform else all(counts), (kernel, uniform, counts)
+
+
 def test_waves_that_multiply_issue_no_loads(built):
     """In the steady loop of a tile's multiplying waves every load is another wave's: four matrix instructions (k 64) for each block of the
     wave, its fragments from LDS, one barrier, and at most one address addition for each k step and operand."""
