@@ -140,6 +140,9 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, bool ke
   // everything the epilogue reads from memory is requested before the main loop and waits in registers
   constexpr bool kEnc = MODE == kTileEncode;
   constexpr bool kWideGrid = WIDE && !is_rtn(NCW) && kEpilogue;
+  // Codes of 8 heads x 16 bytes beside a wave's 160 accumulators and 56 registers of fragments spilled: requested behind the main loop (10000
+  // tokens, 256 points 92.5 -> 91.6 us).
+  constexpr bool kLate = kWideGrid && NCW == 256 && MB == 10;
   struct In { u32x4 x[kEnc ? kVals / 8 : 1]; CodeWords w; };
   // several passes: the inputs of the first are requested from inside the main loop, those of each next one during the one before
   In in[2];
@@ -201,9 +204,10 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, bool ke
         if ((int)threadIdx.x * 4 < rep * kGroup)
           qreg = *reinterpret_cast<const u32x2*>(a.q + ((int64_t)b * a.q_heads + head * rep) * kGroup + threadIdx.x * 4);
       }
-      if (wave * kWaveRows < kPassRows) fetch(0);
+      if (!kLate && wave * kWaveRows < kPassRows) fetch(0);
     }
   });
+  if constexpr (kLate) fetch(0);
   if (SUMS == kKeepSums && keep) {
     if (wave < kMulWaves) {
 #pragma unroll

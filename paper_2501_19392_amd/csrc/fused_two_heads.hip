@@ -81,6 +81,9 @@ __global__ __launch_bounds__(kWaves2 * 64) void fused_two_heads_kernel(
     request_wide_codes<NCW>(codes, row, q, wc);
   };
   WideCodes<NCW> wide_codes;                         // of the pass at hand; the next pass's are fetched while it runs
+  // Codes of 3 and 4 dwords per head are requested behind the main loop: inside it, beside its fragments, a register spilled.  No time either
+  // way (32768 tokens, 64 points 240.0 / 240.7 us, 256 points 249.7 / 250.1): the block that is parked first covers the request.
+  constexpr bool kLate = kWideGrid && NCW > 16;
 
   f32x16 acc[2][4];
   gemm_mainloop_two_heads(smem, x0, d0, x1, d1, W, T, m0, pair * BN2, acc, [&] {
@@ -89,9 +92,10 @@ __global__ __launch_bounds__(kWaves2 * 64) void fused_two_heads_kernel(
     } else {
 #pragma unroll
       for (int pi = 0; pi < kPasses; ++pi) fetch(pi, in[pi]);
-      if constexpr (kWideGrid) fetch_wide(0, wide_codes);
+      if constexpr (kWideGrid && !kLate) fetch_wide(0, wide_codes);
     }
   });
+  if constexpr (kLate) fetch_wide(0, wide_codes);
 
   // the LDS is free again: the grid (and the encoder's cell table, requested now and stored once the first block is
   // parked), then block after block of the tile (+ bias) parked row-major in fp32
