@@ -102,7 +102,7 @@ template <> struct Storage<bf16_t> {
   // (32 MiB; 128 MiB: 3.3 against 6.5).  So with 32 values per lane the quad's lanes exchange pieces first, one instruction per
   // value: 64 bytes of a quad per store.  Decode of 32768 tokens 224 -> 212 us, encode 269 / 270 (bound by vector issue).  With 16
   // values, 32 bytes per lane (3.7 and 5.6 TB/s), the exchange costs what it gains.
-  // stream (with 32 values per lane): the launch writes more than its reader will find in L2 (streams()).
+  // stream (with 32 values per lane): past the L2s (streams()).
   template <bool REVERSED, int N> static __device__ __forceinline__ void store(bf16_t* p, int pos, const float (&v)[N], bool stream = false) {
     constexpr int kPieces = N / 8;
     u32x4 r[kPieces];
@@ -137,10 +137,13 @@ template <> struct Storage<bf16_t> {
   }
 };
 
-// Whether rows of `elements` bf16 values in all are written past the L2s (32 MiB over the XCDs): from 16 MiB on a launch's reader, the next
-// one, finds little of them there, and dirty lines cost their eviction.  Layer after layer, encode and decode of 8192 tokens 3.90 -> 3.76 ms
-// for 28 layers, of 32768 14.86 -> 14.74 for 32; attention over 8192 tokens 69.8 -> 67.8 us.  Below, the reader is slower: attention over
-// four caches of 5376 compressed rows in all 467 -> 481 us.
+// Whether a launch on tiles of 256 rows, or of whole tokens, writes its rows, `elements` bf16 values in all, past the L2s (32 MiB over the
+// XCDs): from 16 MiB on its reader, the next launch, finds little of them there, and dirty lines cost their eviction.  A stack of layers, us
+// a layer, not / past the L2s: 8192 tokens encode 71.9 / 70.4, decode 54.1 / 55.8, attention 63.9 / 62.6; 38000 tokens 349 / 338, 268 / 264,
+// 312 / 306; 131072 (two heads) 1036 / 1030, 807 / 788, 1002 / 984; whole tokens encode 621 / 612 at 65536.  Below 16 MiB the reader is slower: 6200 tokens
+// encode 62.0 / 64.3, decode 47.5 / 50.1.  The other tiles never ask: on 320 rows their readers are slower at every size (8300 tokens
+// encode 84 / 93, decode 63 / 71, attention 78 / 82; 20000 tokens 182 / 192, 135 / 151, 162 / 172), and so on 192 rows in several rounds, 32 bytes a
+// lane (16500 tokens 158 / 164, 126 / 136, 152 / 154).
 __device__ __forceinline__ bool streams(int64_t elements) { return elements >= ((int64_t)1 << 23); }
 
 // 8 bf16 in a 16-byte register quad -> fp32

@@ -308,7 +308,7 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, bool ke
         } else {
           dequantize_words<NCW>(in[h & 1].w, p, sf, q, cl.cb, v);
         }
-        if (a.Xhat != nullptr && active) Storage<bf16_t>::store<false>(a.Xhat + off, q, v, MB == 10);
+        if (a.Xhat != nullptr && active) Storage<bf16_t>::store<false>(a.Xhat + off, q, v);
         if constexpr (MODE == kTileScores)
           score_row(v, q, head, H, a.q_heads, b, t0 + (active ? lrow : n_rows - 1), a.seq_len, active, a.q, a.score_scale,
                     a.scores, a.rope_cos, a.rope_sin, q_lds);

@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kSlabWaves * 64) void fused_wide_encode_kernel(
         asm volatile("" ::: "memory");
         read_p(prow, p);
         finish_hat<NCW>(v, sf, p);
-        if (active) Storage<bf16_t>::store<true>(Xhat + off, l, v, true);
+        if (active) Storage<bf16_t>::store<true>(Xhat + off, l, v, streams(T * kSlabCols));
       }
       __builtin_amdgcn_sched_barrier(0);
     }

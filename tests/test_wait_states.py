@@ -193,6 +193,21 @@ def test_uniform_quantizers_stage_no_search_table(built):
         assert not any(counts) if uniform else all(counts), (kernel, uniform, counts)
 
 
+def test_rows_written_past_the_caches(built):
+    """Tiles of 256 rows and whole tokens write large launches past the L2s and others through them (a branch of the kernel); the readers of the
+    other tiles' rows are slower for it at every size, so those have no such store."""
+    past = {}
+    for name, code, _ in built:
+        if m := re.search(r"(fused_kernel|fused_two_heads_kernel|fused_wide_encode_kernel|fused_tile_kernel|fused_tile_two_kernel|fused_tile_pair_kernel|"
+                          r"fused_tile_attend_kernel|quantize_kernel)I", name):
+            stores = [args for op, args in code if op == "global_store_dwordx4"]
+            past.setdefault(m[1], []).append((sum(args.endswith(" nt") for args in stores), len(stores)))
+    assert len(past) == 8
+    for kernel, counts in past.items():
+        asks = kernel in ("fused_kernel", "fused_two_heads_kernel", "fused_wide_encode_kernel")
+        assert all(0 < nt < all_stores if asks else nt == 0 for nt, all_stores in counts), (kernel, counts)
+
+
 def test_waves_that_multiply_issue_no_loads(built):
     """In the steady loop of a tile's multiplying waves every load is another wave's: four matrix instructions (k 64) for each block of the
     wave, its fragments from LDS, one barrier, and at most one address addition for each k step and operand."""
