@@ -15,6 +15,7 @@
 #include "fused_tile.h"
 #include "gemm_core.h"
 #include "kernels.h"
+#include "tile_choice.h"
 
 #include <utility>
 
@@ -388,49 +389,6 @@ hipError_t launch(int n_codewords, const void* x0, int d0, const void* x1, int d
   return hipGetLastError();
 }
 
-// Rows per tile (fused_tile.h) of a launch over n_seq sequences of seq_len rows (one sequence for encode and decode);
-// 0: the tiles of 256 rows x one or two heads.
-//
-// A CU holds one workgroup, so what counts is the rounds of workgroups over the CUs and the rows of a round.  Ranges that
-// fill the chip in one round take the smallest tile that still does.  Keys and values x 8 heads, us (with main loops whose waves all loaded and
-// multiplied; now a tenth less, and no size between 3100 and 6144 tokens has a tile more than 2 % faster than its own):
-//   1024 tokens  encode 23.6 on 32 rows, 27.0 on 64, 38.8 on 128 (decode 19.1, 22.3, 30.7)
-//   2048         28.7 on 64, 39.5 on 128 (24.3, 31.1)
-//   2100         34.1 on 96, 39.8 on 128 (28.7, 31.4); 3072 39.2, 41.9 (32.4, 32.7)
-//   4096         a tensor at a time 20.6 / 28.8 on 128, 26.1 / 35 on 256
-//   4200         55.1 on 192, 59.4 on 256 (44.4, 44.7); 6144 61.9, 66.2 (51.5, 50.8); groups across the heads, whose predictions have a large
-//                tile of two heads, 76.6, 98.0 (49.6, 52.9) and 86.0, 101.4 (57.1, 58.6)
-// The scoring calls gain on all of them, a sequence or many: 2600 tokens with the rotary embedding 13.7 on 96, 15.5 on 128, 32 x 96 14.8, 15.8, 4 x 700
-// 14.4, 14.9; 4200 tokens 21.0 on 192, 23.6 on 256, 6144 24.1, 25.1, 4 x 1300 22.8, 26.5, 16 x 384 24.5, 27.0; groups across the heads 5 to 20 %.
-// Beyond that a launch takes several rounds, and the tile is the one whose rounds cost least: 41 on 320 rows, 29 on 256 rows (33 the first),
-// 54 on 256 rows x two heads (us of K = 1024, encode, before the main loops had waves of their own for the loads; they keep their
-// proportions), 26 on 192 rows.  Keys and values, us:
-//   8300 tokens    encode 87 on 320 rows, 116 on 256, 102 on two heads, 91 on 192 (decode 67, 89, 74, 71)
-//   10400          115 on two heads, 98.5 on 192; 12288 106.5, 101.9 (78.2, 74.8; 79.5, 76.0)
-//   13000 - 16384  117 - 126 on two heads, 127 - 135 on 256, 140 - 155 on 192 (89 - 98, 101 - 108, 109 - 124)
-//   16500          165 on 320, 208 on two heads, 144.7 on 192; 18432 166.2, 213.6, 150.7 (127.4, 156.8, 109.0; 133.0, 160.7, 115.3)
-//   20000          183 on 320, 228 on two heads, 196 on 192 (139, 168, 152); 22000 195.5 on 256, 217 on 192 (157, 158)
-// Attention over 17000 tokens 172.6 / 150.5 on 192, groups across the heads 189 / 162 and 11000 tokens (no tile of two heads) 122 / 107.
-// round_192: what a round of 192 rows costs.  Two of them are as good as one of two heads only where a grid is searched: decode 74.8 to 76 and,
-// on a card with a lower clock, 81.2 / 79.3 at 10400 tokens, 81.8 / 86.0 at 12288, uniform encode 88.4 / 93.0.  No round on 192 rows for
-// predictions alone (groups across the heads, encode: 179 / 193 at 16500 tokens) and decode across the heads of 64 or 256 points (within 2 %
-// either way).
-constexpr int kRounds192 = 27, kSearchRounds192 = 26, kNoRounds192 = 1 << 20;
-int decode_rounds_192(int n_codewords, bool wide) { return wide && n_codewords > 16 ? kNoRounds192 : kRounds192; }
-int tile_rows(int64_t n_seq, int64_t seq_len, int D, bool two_heads, int64_t round_192) {
-  constexpr int64_t kCUs = 256;                      // MI355X
-  const int64_t H = D / BN;
-  const auto tiles = [&](int64_t rows) { return n_seq * ((seq_len + rows - 1) / rows) * H; };
-  const auto rounds = [&](int64_t t) { return (t + kCUs - 1) / kCUs; };
-  for (const int rows : {32, 64, 96, 128, 192})
-    if (tiles(rows) <= kCUs) return rows;
-  const int64_t all = (n_seq * seq_len + BM - 1) / BM;    // tiles of 256 rows may straddle sequences
-  int64_t other = 29 * rounds(all * H) + 4;
-  if (two_heads && D % 256 == 0 && 54 * rounds(all * H / 2) < other) other = 54 * rounds(all * H / 2);
-  const int64_t on_320 = 41 * rounds(tiles(320)), on_192 = round_192 * rounds(tiles(192));
-  if (on_192 < on_320 && on_192 < other) return 192;
-  return on_320 < other ? 320 : 0;
-}
 hipError_t launch_rows(int rows, int mode, int n_codewords, bool wide, int n_seq, const TileArgs& a, hipStream_t stream) {
   if (rows == 32) return launch_tile_32(mode, n_codewords, wide, n_seq, a, stream);
   if (rows == 64) return launch_tile_64(mode, n_codewords, wide, n_seq, a, stream);
@@ -491,7 +449,7 @@ int decode_pair_rows(int64_t T, int D) {
 constexpr int64_t kAttendTiles = 224;
 int attend_rows(int64_t T, int D, int n) {
   if (n == 2) return decode_pair_rows(T, D);
-  const int rows = tile_rows(1, T, D, true, kRounds192);
+  const int rows = tile_rows(1, T, D, true, kDecodeRound192);
   if (rows == 320 || (rows == 0 && two_heads_pays(T, D))) return 0;
   const int64_t each = rows == 0 || rows == 192 ? BM : rows;
   return (T + each - 1) / each * (D / BN) <= kAttendTiles ? (int)each : 0;
@@ -604,7 +562,7 @@ hipError_t launch_fused_layer(bool encode, int n_codewords, const float* codeboo
 hipError_t launch_tile_predict(const void* x0, int d0, const void* x1, int d1, const void* W, const float* bias, const Prediction& P,
                                int64_t T, int D, hipStream_t stream) {
   if (T == 0) return hipSuccess;
-  const int rows = tile_rows(1, T, D, true, kNoRounds192);
+  const int rows = tile_rows(1, T, D, true, kNoRound192);
   if (rows == 0) return launch_predict_two_heads(x0, d0, x1, d1, W, bias, P, T, D, stream);
   TileArgs a = tile_args(x0, d0, x1, d1, W, bias, nullptr, nullptr, D);
   a.P = P; a.seq_len = (int)T;
@@ -616,7 +574,7 @@ hipError_t launch_fused_encode(int n_codewords, const void* x0, int d0, const vo
                                const void* X, uint8_t* codes, uint16_t* scales, void* Xhat, int64_t T, int D,
                                hipStream_t stream) {
   if (T == 0) return hipSuccess;
-  if (const int rows = tile_rows(1, T, D, true, is_rtn(n_codewords) ? kRounds192 : kSearchRounds192)) {
+  if (const int rows = tile_rows(1, T, D, true, kEncodeRound192)) {
     TileArgs a = tile_args(x0, d0, x1, d1, W, bias, signs, codebook, D);
     a.table = static_cast<const uint32_t*>(table); a.X = static_cast<const bf16_t*>(X);
     a.codes = codes; a.scales = scales; a.Xhat = static_cast<bf16_t*>(Xhat); a.seq_len = (int)T;
@@ -633,7 +591,7 @@ hipError_t launch_fused_decode(int n_codewords, const void* x0, int d0, const vo
                                const float* bias, const int8_t* signs, const float* codebook, const uint8_t* codes,
                                const uint16_t* scales, void* Xhat, int64_t T, int D, bool wide, hipStream_t stream) {
   if (T == 0) return hipSuccess;
-  if (const int rows = tile_rows(1, T, D, true, decode_rounds_192(n_codewords, wide))) {
+  if (const int rows = tile_rows(1, T, D, true, decode_round_192(n_codewords, wide, false))) {
     TileArgs a = tile_args(x0, d0, x1, d1, W, bias, signs, codebook, D);
     a.codes = const_cast<uint8_t*>(codes); a.scales = const_cast<uint16_t*>(scales);
     a.Xhat = static_cast<bf16_t*>(Xhat); a.seq_len = (int)T;
@@ -653,7 +611,7 @@ hipError_t launch_fused_scores(int n_codewords, const void* x0, int d0, const vo
                                int seq_len, int q_heads, int64_t T, int D, const float* rope_cos, const float* rope_sin,
                                bool wide, hipStream_t stream) {
   if (T == 0) return hipSuccess;
-  if (const int rows = tile_rows(T / seq_len, seq_len, D, !wide, decode_rounds_192(n_codewords, wide))) {
+  if (const int rows = tile_rows(T / seq_len, seq_len, D, !wide, decode_round_192(n_codewords, wide, true))) {
     TileArgs a = tile_args(x0, d0, nullptr, 0, W, bias, signs, codebook, D);
     a.codes = const_cast<uint8_t*>(codes); a.scales = const_cast<uint16_t*>(scales);
     a.Xhat = static_cast<bf16_t*>(Khat_out); a.seq_len = seq_len; a.q = static_cast<const bf16_t*>(q);

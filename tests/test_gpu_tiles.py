@@ -353,3 +353,15 @@ def test_scores_on_tiles_of_192_rows_in_several_rounds(batch, S, quantizer, rht_
 @pytest.mark.parametrize("quantizer,rht_group", [("n16", None), ("n256", 1024)])
 def test_tiles_of_short_products_and_uneven_shares(H, dk, T, quantizer, rht_group):
     test_tiles_give_the_bits_of_the_stage_calls(H, dk, T, quantizer, rht_group)
+
+
+@pytest.mark.parametrize("H,dk,T", [(8, 128, 10241), (8, 256, 12288), (8, 128, 16385), (8, 128, 32769), (8, 128, 36864), (24, 128, 3201)])
+@pytest.mark.parametrize("quantizer,rht_group", [("n16", None), ("n64", 1024), ("n256", 1024), ("rtn2", None), ("rtn4", 1024)])
+def test_ranges_that_rounds_of_192_rows_cost_least_for(H, dk, T, quantizer, rht_group):
+    test_tiles_give_the_bits_of_the_stage_calls(H, dk, T, quantizer, rht_group)
+
+
+@pytest.mark.parametrize("batch,S,quantizer,rht_group", [(16, 1100, "n16", 1024), (3, 3500, "n16", 1024), (16, 1100, "rtn2", 1024), (5, 3300, "n256", 1024),
+                                                         (3, 3500, "n64", 1024), (5, 3300, "n64", None), (5, 3300, "rtn2", None)])
+def test_scores_on_192_rows_in_several_rounds(batch, S, quantizer, rht_group):
+    test_scores_of_a_batch_are_those_of_its_sequences(8, 128, batch, S, quantizer, rht_group)
