@@ -223,3 +223,32 @@ def test_waves_that_multiply_issue_no_loads(built):
                 assert not any(op.startswith(("global_load", "buffer_load")) for op in ops), (name, begin)
                 assert ops.count("v_add_u32_e32") <= 8, (name, begin)
     assert checked > 150
+
+
+# kernels built on the loop with loading waves, and the row blocks of their tiles
+TILE_KERNELS = [(r"fused_tile_kernelILi\d+ELi\dELi(\d+)E", None), (r"fused_tile_two_kernelILi\d+ELi\dELi(\d+)E", None),
+                (r"predict_two_tiles_kernelILi(\d+)ELi(\d+)E", None), (r"fused_tile_pair_kernelILi", 1), (r"fused_kernelILi", 8), (r"fused_attend_kernelILi", 8),
+                (r"fused_tile_attend_kernelILi\d+ELi(\d+)E", None)]
+
+
+def test_steady_loops_of_every_kernel_on_tiles(built):
+    """Every kernel on tiles: in each steady loop of its multiplying waves no load, a k-tile's fragments from LDS (four steps of the wave's blocks
+    of rows and of columns) and nothing more, one barrier."""
+    found = {}
+    for name, code, labels in built:
+        for pattern, fixed in TILE_KERNELS:
+            if not (m := re.search(pattern, name)):
+                continue
+            for blocks in (map(int, m.groups()) if fixed is None else [fixed]):
+                reads = 4 * (blocks + 1 if blocks < 4 else blocks // 2 + 2)
+                loops = 0
+                starts = sorted({0, *labels.values(), len(code)})
+                for begin, end in zip(starts, starts[1:]):
+                    ops = [op for op, _ in code[begin:end]]
+                    if ops.count("s_barrier") == 1 and ops.count("v_mfma_f32_32x32x16_bf16") == 4 * blocks:
+                        loops += 1
+                        assert not any(op.startswith(("global_load", "buffer_load")) for op in ops), (name, begin)
+                        assert ops.count("ds_read_b128") == reads and not any(op.startswith("ds_write") for op in ops), (name, begin, ops.count("ds_read_b128"))
+                assert loops >= 1, (name, blocks)
+                found[pattern] = found.get(pattern, 0) + 1
+    assert len(found) == len(TILE_KERNELS), found
