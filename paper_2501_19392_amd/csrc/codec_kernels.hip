@@ -27,11 +27,14 @@ constexpr int kGroupsPerBlock = kThreads / kLanesPerGroup;   // 64
 // without predictors do not depend on each other, nor do the values of a layer and the keys of the next one, and together they fill
 // the chip better).
 //
-// Bound by vector issue and, with it, by how many waves a SIMD holds to cover the look-ups' LDS latency, hence 16 values per
-// lane: 113 to 120 registers = four waves per SIMD without a prediction (PRED false), 147 to 154 = three with one.  With 32 values
-// per lane it was three and two.  Keys and values of 8192 tokens, 256-point grid, groups of 1024: 36.6 us against 49.6; with
-// predictions in memory, 4096 tokens, 16 points, predictor included, 88.5 against 114.7.  Smaller code for the crowded cells, which
-// would let four or five waves in with a prediction, changed nothing: the issue slots are full.
+// Without a prediction bound by vector issue: the vector pipes are busy in 0.94 of the cycles with 16 points (keys and values of 8192 tokens, groups
+// of 1024, 29.9 us) and in 0.84 with 256 (37.4 us), where LDS is in 0.70, three fifths of that bank conflicts of the grid points' reads.  16 values per
+// lane: 113 to 120 registers = four waves per SIMD (PRED false), 147 to 154 = three with a prediction.  With 32 values per lane it was three and
+// two.  256 points: 36.6 us against 49.6; with predictions in memory, 4096 tokens, 16 points, predictor included, 88.5 against 114.7.
+// With a prediction the vector pipes are busy in 0.73 (16 points) and 0.64 (256): 2.2 to 2.3 waves per SIMD on average do not cover the rest,
+// start and drain of the few rounds and the look-ups' LDS latency (LDS busy in 0.34 and 0.50).  Predictions come from memory once (52.9
+// MB fetched for a tensor of 8192 tokens, 50.3 of it rows and predictions): their second read is served by L2.  Smaller code for the
+// crowded cells, which would let four or five waves in, changed nothing.
 //
 // CODES: no tensor of the launch wants its reconstruction (uniform backbone in bf16, without a prediction).  There is no search to
 // request behind, so the next rows are requested ahead of this round's work, and no scattered store; what counts is the group's

@@ -66,7 +66,7 @@ __device__ __forceinline__ void fused_body(
     float* __restrict__ part) {
   static_assert(!WIDE || MODE != kEncode, "the quantizer needs the whole group: groups across the heads are not fused");
   Lds& cl = *reinterpret_cast<Lds*>(smem);
-  unsigned char* const park = smem + sizeof(Lds);          // the parked tile, each wave its own rows
+  unsigned char* const park = smem + sizeof(Lds);          // the parked tile: the multiplying waves write it, each wave works on rows of its own
   const bool use_table = MODE == kEncode && !is_rtn(NCW) && table != nullptr;     // (a round-to-nearest layer's grid pointers are never read)
   // grid and cell table: requested from inside the main loop, kept in registers while it owns the LDS
   static_assert(NCW <= WAVES * 64, "one grid point per thread");
@@ -418,11 +418,12 @@ TileArgs tensor_args(const FusedTensor& t, const float* codebook, int64_t T, int
 //
 // A launch for one tensor of few rows is bound by the latency of its k-tiles and leaves CUs idle, so the other tensor's tiles come
 // for little: the smallest tile with which both fit the CUs in one round (3072 rows of 8 heads on 192).  Attention over a cache of six
-// layers, us a token, apart / together: 300 tokens 145 / 115, 1100 155 / 138, 2000 192 / 177, 2 x 1500 236 / 219.  Eight layers, pieces of
-// attention beside the tiles: up to 1536 tokens on 96 rows, 1200 tokens 154 (159 on 128), 1500 163 (173); beyond 2048 tokens on 192
-// rows, 2304 206 (212 with one and an eighth rounds of 128 rows), 2560 213 (245), 2800 221 (248).
+// layers, groups across the heads, us a token, apart / together: 300 tokens 110 / 76, 1100 147 / 111, 2000 168 / 136, 2 x 1500 190 / 158 (of one head
+// 106 / 74, 139 / 107, 160 / 127, 178 / 143).  Eight layers: 1200 tokens 129 on 96 rows (147 on 128, 164 on 192), 2304 189 on 192 (206 with one and an eighth
+// rounds of 128 rows), 2560 212 (217), 2800 222 (247), 3000 233 (252).  Two sizes would be better on the next larger tile, which this rule does not
+// say: 1100 tokens of six layers 102 on 96 rows, 1500 of eight 154 on 128 (166 on 96).
 // From there on both tensors in one launch take as many rounds as two launches: 5376 rows are twice 168 tiles of
-// 256 rows, 561 / 582 us for eight layers, or twice 136 of 320, 557 / 570.
+// 256 rows, 561 / 582 us for eight layers, or twice 136 of 320, 557 / 570 (with main loops whose waves all loaded and multiplied).
 int pair_rows(int64_t T, int D) {
   const int64_t H = D / BN;
   for (const int rows : {32, 64, 96, 128, 192})
@@ -430,7 +431,7 @@ int pair_rows(int64_t T, int D) {
   return 0;
 }
 // Decode goes on with one and a half rounds of 128 rows where 192 do not fit, for head counts that are no power of two (for those both end
-// at the same rows).  Eight layers, us a token, 192 rows or none / with them: 3 heads 8068 tokens 204 / 170, 8192 184 / 163; 5 heads, 4804
+// at the same rows).  Eight layers, us a token, 192 rows or none / with them, with main loops whose waves all loaded and multiplied: 3 heads 8068 tokens 204 / 170, 8192 184 / 163; 5 heads, 4804
 // 250 / 221; 6 heads, 4036 228 / 211; 12 heads, 1925 353 / 340, 2048 326 / 335; 24 heads, 1024 635 / 607.  Encoding, 3, 5, 6, 12 and 24
 // heads: 200 / 202, 248 / 255, 261 / 260, 354 / 376, 688 / 657.
 int decode_pair_rows(int64_t T, int D) {
@@ -440,12 +441,12 @@ int decode_pair_rows(int64_t T, int D) {
 
 // What a decode launch with attention behind its tiles runs on, for n tensors of T rows: rows of a tile, 0: no such launch.
 //
-// The tiles come first and the pieces of attention go to CUs without a tile, or whose tile is done.  8 layers, us a token, attention in launches
-// of its own / beside the tiles.  Two tensors: 200 tokens 145 / 98, 1200 215 / 159, 2000 223 / 193, 3000 315 / 269, 8 x 200 161 / 120.
-// One tensor, as long as it leaves an eighth of the CUs without a tile: 3600 tokens (216 tiles of 128 rows) 361 / 347, 8 x 800 476 / 415,
-// 4 x 1800 (168 tiles of 256 rows) 502 / 484, 6000 tokens (184) 458 / 441.  With tiles on all CUs the pieces wait, and then run one or
-// two to a CU instead of four: 4200 tokens (256 tiles of 128 rows) 360 / 389, 8000 (248 of 256 rows) 550 / 559.  256 rows stay where 192 would
-// do: they leave more CUs to the pieces (4 x 1800 tokens 517 to 532 us against 527 to 536).
+// The tiles come first and the pieces of attention go to CUs without a tile, or whose tile is done.  One tensor, as long as it leaves an eighth
+// of the CUs without a tile; 8 layers, us a token, groups across the heads (of one head), attention in launches of its own / beside the tiles:
+// 3600 tokens (216 tiles of 128 rows) 311 / 300 (285 / 273), 8 x 800 379 / 357 (340 / 337), 6000 (184 of 256 rows) 432 / 431 (392 / 384).  With tiles on all CUs
+// the pieces wait, and then run one or two to a CU instead of four: 4200 tokens (256 tiles of 128 rows) 341 / 374 (313 / 346), 8000 (248 of 256
+// rows) 561 / 574 (507 / 521).  256 rows stay where 192 would do: they leave more CUs to the pieces (4 x 1800 tokens 517 to 532 us against 527 to 536,
+// with main loops whose waves all loaded and multiplied).
 constexpr int64_t kAttendTiles = 224;
 int attend_rows(int64_t T, int D, int n) {
   if (n == 2) return decode_pair_rows(T, D);
@@ -486,9 +487,9 @@ hipError_t launch_fused_decode_attend(int n_codewords, const FusedTensor* tensor
   return hipGetLastError();
 }
 
-// pair_rows for encoding.  Stack of 8 layers, 16 points, us, a layer at a time / values and next keys together: 128 rows 142 / 105,
-// 512 151 / 114, 1024 176 / 145, 1100 194 / 168 (178 on tiles of 128 rows), 2048 223 / 193; on 192 rows / 128: 2304 231 / 248, 2560 237 / 248;
-// on 192 rows / a layer at a time: 2800 244 / 260, 3072 250 / 266.
+// pair_rows for encoding.  Stack of 8 layers, 16 points, us, a layer at a time / values and next keys together: 128 rows 123 / 92,
+// 512 135 / 102, 1024 156 / 118, 1100 175 / 132 (153 on tiles of 128 rows), 2048 188 / 167; on 192 rows / 128: 2304 193 / 214, 2560 203 / 217;
+// on 192 rows / a layer at a time: 2800 212 / 225, 3072 211 / 229.
 bool fused_encode_pair_pays(int64_t T, int D) { return pair_rows(T, D) != 0; }
 hipError_t launch_fused_encode_pair(int n_codewords, const FusedTensor* tensors, const float* const* codebooks, const void* const* tables,
                                     int64_t T, int D, hipStream_t stream) {
@@ -509,8 +510,8 @@ hipError_t launch_fused_encode_pair(int n_codewords, const FusedTensor* tensors,
 
 // Predictions of two tensors (groups across the heads): a tile is a main loop and its stores, and two launches of the predictor and two of
 // the quantizer become one each, so it pays up to two rounds of tiles of 128 rows.  Stack of 8 layers, 16 points, us, a layer at a time /
-// together, with main loops whose waves all loaded and multiplied: 128 rows 222 / 143, 512 236 / 164, 1200 282 / 217 (on 64 rows 230), 1400 291 / 215
-// (on 128 rows 240), 2304 405 / 310 (on 128 rows 316), 3072 420 / 329 (362), 4096 490 / 469.
+// together: 128 rows 186 / 123, 512 201 / 142, 1200 247 / 175 (on 96 rows each 179, on 64 183), 1400 253 / 184 (on 96 each 185), 2304 307 / 246, 3072 336 / 281
+// (on 128 rows 300), 4096 408 / 365.
 int64_t tile_predict_pair_rows(int D) { return 512 / 2 / (D / BN) * 128; }
 hipError_t launch_tile_predict_pair(const FusedTensor* tensors, const Prediction* out, int64_t T, int D, hipStream_t stream) {
   if (T == 0) return hipSuccess;
@@ -522,8 +523,8 @@ hipError_t launch_tile_predict_pair(const FusedTensor* tensors, const Prediction
   const auto of_one = [&](int64_t rows) { return (T + rows - 1) / rows * (D / BN); };
   const auto tiles = [&](int64_t rows) { return 2 * of_one(rows); };
   if (tiles(32) <= 256) return launch_tile_two_32(kTilePredict, 16, jobs, stream);
-  // The first tensor has the longer product: smaller tiles for it, as long as both fit the CUs in one round (2304 rows, 192 each 20.8 us, 128 and
-  // 192 17.5).  Tiles that are encoded or decoded stay of one size: the append of a prompt is bound by the host there, and a recovery
+  // The first tensor has the longer product: smaller tiles for it, as long as both fit the CUs in one round (stack of 8 layers
+  // of 2304 rows, 192 each 255 us, 128 and 192 246; 19.9 us a launch in a trace).  Tiles that are encoded or decoded stay of one size: the append of a prompt is bound by the host there, and a recovery
   // needs the CUs that are left for the pieces of attention (1100 rows 102 / 120 us a token of six layers, 2200 145 / 159).
   if (jobs[0].d0 + jobs[0].d1 >= 2 * (jobs[1].d0 + jobs[1].d1))
     for (const auto& r : {std::pair<int, int>{32, 96}, {64, 128}, {64, 192}, {96, 192}, {128, 192}})
@@ -534,8 +535,8 @@ hipError_t launch_tile_predict_pair(const FusedTensor* tensors, const Prediction
   return launch_tile_two_128(kTilePredict, 16, jobs, stream);
 }
 
-// Tiles of 32 rows for both products on the CUs at once.  With tiles of 64 rows for the first launch, up to twice the rows,
-// 600 tokens of 8 heads take 24.3 us to encode against 22.9 one after the other, 1000 tokens 25.5 against 23.8.
+// Tiles of 32 rows for both products on the CUs at once.  With tiles of 64 rows for the first launch, up to twice the rows, 600 tokens of 8
+// heads took 24.3 us to encode against 22.9 one after the other, 1000 tokens 25.5 against 23.8 (main loops whose waves all loaded and multiplied).
 bool fused_layer_fits(int64_t T, int D) { return 2 * ((T + 31) / 32) * (D / BN) <= 256; }
 
 hipError_t launch_fused_layer(bool encode, int n_codewords, const float* codebook, const void* table, const FusedTensor& keys,

@@ -137,7 +137,8 @@ __device__ __forceinline__ void fused_tile(const TileArgs& a, int block, bool ke
   const int n0 = head * kGroup;
   const int q = group_pos<kVals>(lane), wrow = lane / (kGroup / kVals);      // position in the group, group of the wave
 
-  // everything the epilogue reads from memory is requested before the main loop and waits in registers
+  // What the epilogue reads from memory is requested from inside the main loop (by multiplying waves behind their first fragments, by loading
+  // waves behind their last loads) and waits in registers.
   constexpr bool kEnc = MODE == kTileEncode;
   constexpr bool kWideGrid = WIDE && !is_rtn(NCW) && kEpilogue;
   // Codes of 8 heads x 16 bytes beside a wave's 160 accumulators and 56 registers of fragments spilled: requested behind the main loop (10000

@@ -9,16 +9,14 @@ namespace aquakv {
 // 0: the tiles of 256 rows x one or two heads.
 //
 // A CU holds one workgroup, so what counts is the rounds of workgroups over the CUs and the rows of a round.  Ranges that
-// fill the chip in one round take the smallest tile that still does.  Keys and values x 8 heads, us (with main loops whose waves all loaded and
-// multiplied; now a tenth less, and no size between 3100 and 6144 tokens has a tile more than 2 % faster than its own):
-//   1024 tokens  encode 23.6 on 32 rows, 27.0 on 64, 38.8 on 128 (decode 19.1, 22.3, 30.7)
-//   2048         28.7 on 64, 39.5 on 128 (24.3, 31.1)
-//   2100         34.1 on 96, 39.8 on 128 (28.7, 31.4); 3072 39.2, 41.9 (32.4, 32.7)
-//   4096         a tensor at a time 20.6 / 28.8 on 128, 26.1 / 35 on 256
-//   4200         55.1 on 192, 59.4 on 256 (44.4, 44.7); 6144 61.9, 66.2 (51.5, 50.8); groups across the heads, whose predictions have a large
-//                tile of two heads, 76.6, 98.0 (49.6, 52.9) and 86.0, 101.4 (57.1, 58.6)
-// The scoring calls gain on all of them, a sequence or many: 2600 tokens with the rotary embedding 13.7 on 96, 15.5 on 128, 32 x 96 14.8, 15.8, 4 x 700
-// 14.4, 14.9; 4200 tokens 21.0 on 192, 23.6 on 256, 6144 24.1, 25.1, 4 x 1300 22.8, 26.5, 16 x 384 24.5, 27.0; groups across the heads 5 to 20 %.
+// fill the chip in one round take the smallest tile that still does.  Keys and values x 8 heads, a stack of layers, us a layer:
+//   1024 tokens  encode 21.2 on 32 rows, 23.2 on 64, 32.7 on 128 (decode 17.3, 18.6, 24.5)
+//   2048         25.5 on 64, 28.0 on 96, 33.7 on 128 (20.7, 22.3, 25.5)
+//   2100         28.1 on 96, 33.9 on 128 (22.4, 25.6); 3072 30.6, 35.2 (24.8, 26.8)
+//   4096         39.1 on 128, 44.1 on 192, 54.1 on 256 (30.2, 33.3, 39.6)
+//   4200         43.8 on 192, 54.3 on 256 (33.4, 40.0); 6144 50.2, 59.2 (39.5, 44.4)
+// Scores: 2600 tokens 10.3 on 96, 11.4 on 128, 4200 16.0 on 192, 19.5 on 256, 6144 18.2, 21.3; with groups across the heads 11.5, 13.4; 18.3, 23.0;
+// 20.6, 24.7.
 //
 // Beyond that a launch takes several rounds, and the tile is the one whose rounds cost least.  What a round costs, us of an encode of keys and values
 // with 16 points in a stack of layers: 66 to 67 on 256 rows (9 more for the first), 122 to 126 on 256 rows x two heads, 51 to 56 on 192 rows,
