@@ -142,7 +142,8 @@ template <> struct Storage<bf16_t> {
 // a layer, not / past the L2s: 8192 tokens encode 71.9 / 70.4, decode 54.1 / 55.8, attention 63.9 / 62.6; 38000 tokens 349 / 338, 268 / 264,
 // 312 / 306; 131072 (two heads) 1036 / 1030, 807 / 788, 1002 / 984; whole tokens encode 621 / 612 at 65536.  Below 16 MiB the reader is slower: 6200 tokens
 // encode 62.0 / 64.3, decode 47.5 / 50.1.  The other tiles never ask: on 320 rows their readers are slower at every size (8300 tokens
-// encode 84 / 93, decode 63 / 71, attention 78 / 82; 20000 tokens 182 / 192, 135 / 151, 162 / 172), and so on 192 rows in several rounds, 32 bytes a
+// encode 84 / 93, decode 63 / 71, attention 78 / 82; 20000 tokens 182 / 192, 135 / 151, 162 / 172; one layer on three sets of buffers that just fill the 256 MB
+// behind the L2s is the exception, decode of 9600 tokens 77 / 70, where 8300 take 64 / 66), and so on 192 rows in several rounds, 32 bytes a
 // lane (16500 tokens 158 / 164, 126 / 136, 152 / 154).
 __device__ __forceinline__ bool streams(int64_t elements) { return elements >= ((int64_t)1 << 23); }
 

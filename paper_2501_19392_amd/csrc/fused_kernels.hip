@@ -450,7 +450,7 @@ int decode_pair_rows(int64_t T, int D) {
 constexpr int64_t kAttendTiles = 224;
 int attend_rows(int64_t T, int D, int n) {
   if (n == 2) return decode_pair_rows(T, D);
-  const int rows = tile_rows(1, T, D, true, kDecodeRound192);
+  const int rows = tile_rows(1, T, D, true, kRound192);
   if (rows == 320 || (rows == 0 && two_heads_pays(T, D))) return 0;
   const int64_t each = rows == 0 || rows == 192 ? BM : rows;
   return (T + each - 1) / each * (D / BN) <= kAttendTiles ? (int)each : 0;
@@ -575,7 +575,7 @@ hipError_t launch_fused_encode(int n_codewords, const void* x0, int d0, const vo
                                const void* X, uint8_t* codes, uint16_t* scales, void* Xhat, int64_t T, int D,
                                hipStream_t stream) {
   if (T == 0) return hipSuccess;
-  if (const int rows = tile_rows(1, T, D, true, kEncodeRound192)) {
+  if (const int rows = tile_rows(1, T, D, true, is_rtn(n_codewords) ? kRound192 : kSearchRound192)) {
     TileArgs a = tile_args(x0, d0, x1, d1, W, bias, signs, codebook, D);
     a.table = static_cast<const uint32_t*>(table); a.X = static_cast<const bf16_t*>(X);
     a.codes = codes; a.scales = scales; a.Xhat = static_cast<bf16_t*>(Xhat); a.seq_len = (int)T;
@@ -592,7 +592,7 @@ hipError_t launch_fused_decode(int n_codewords, const void* x0, int d0, const vo
                                const float* bias, const int8_t* signs, const float* codebook, const uint8_t* codes,
                                const uint16_t* scales, void* Xhat, int64_t T, int D, bool wide, hipStream_t stream) {
   if (T == 0) return hipSuccess;
-  if (const int rows = tile_rows(1, T, D, true, decode_round_192(n_codewords, wide, false))) {
+  if (const int rows = tile_rows(1, T, D, true, kRound192)) {
     TileArgs a = tile_args(x0, d0, x1, d1, W, bias, signs, codebook, D);
     a.codes = const_cast<uint8_t*>(codes); a.scales = const_cast<uint16_t*>(scales);
     a.Xhat = static_cast<bf16_t*>(Xhat); a.seq_len = (int)T;
@@ -612,7 +612,7 @@ hipError_t launch_fused_scores(int n_codewords, const void* x0, int d0, const vo
                                int seq_len, int q_heads, int64_t T, int D, const float* rope_cos, const float* rope_sin,
                                bool wide, hipStream_t stream) {
   if (T == 0) return hipSuccess;
-  if (const int rows = tile_rows(T / seq_len, seq_len, D, !wide, decode_round_192(n_codewords, wide, true))) {
+  if (const int rows = tile_rows(T / seq_len, seq_len, D, !wide, kRound192)) {
     TileArgs a = tile_args(x0, d0, nullptr, 0, W, bias, signs, codebook, D);
     a.codes = const_cast<uint8_t*>(codes); a.scales = const_cast<uint16_t*>(scales);
     a.Xhat = static_cast<bf16_t*>(Khat_out); a.seq_len = seq_len; a.q = static_cast<const bf16_t*>(q);

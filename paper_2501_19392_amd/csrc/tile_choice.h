@@ -23,24 +23,21 @@ namespace aquakv {
 // 87 to 92 on 320 rows and 100 with five rounds of them (97: above 96 the seven rounds of 256 rows are taken there).  By range, 16 points, keys and
 // values, encode and decode on the tile taken / the next best:
 //   8300 tokens    85 on 320 rows / 92 on 192, 64 / 69
-//   10300          101 on 192 / 116 on two heads, 83 on two heads / 83; 12200 107 / 116, 84 / 83 to 91
+//   10300          101 on 192 / 116 on two heads (uniform 98 on two heads / 93), 83 on two heads / 83; 12200 107 / 116, 84 / 83 to 91
 //   16300          130 on two heads / 140 on 256, 99 / 111
 //   16500          154 on 192 / 172 on 320, 121 / 129; 18400 161 / 175, 124 / 133
 //   18500          175 on 320 / 190 on 192, 132 / 145
 //   20600          202 on 256 / 202 on 192, 157 / 153; 24500 208 / 216, 165 / 164
-//   33000          325 on 192 / 334 on 256 (256 points 371 / 399, uniform 283 / 285), 252 on 256 / 245 to 256; 36800 336 / 342 (385 / 410, 292 / 292)
+//   33000          325 on 192 / 334 on 256 (256 points 371 / 399), 252 on 256 / 245 to 256; 36800 336 / 342 (385 / 410)
 //   49500          475 on 256 / 490 on 320, 364 to 378 / 380
-// What differs is a round on 192 rows: 54 to encode.  Decode and scores of heads apart gain from three rounds and not surely from two or six
-// (12200 tokens 91 / 87 on another card, 33000 one layer again and again 256 / 251): 63.  Across the heads two rounds pay as well where they
-// decode 16 or 256 points (10300 tokens 92 / 100 and 102 / 115 on two heads, 12200 102 / 102 and 112 / 117; three rounds 159 / 188 on 320 with 256 points; six
-// 322 / 324, one layer again 334 / 310) and in scores, which have no tile of two heads there (256 points 47 / 60, 53 / 62): 60.  64 points (113 / 108, 117 / 110)
-// and the uniform backbone (82 / 80, 90 / 85) decode like heads apart.  Predictions alone (groups across the heads, encode) take no round on 192
-// rows: 193 us against 179 at 16500 tokens.
+// What differs is a round on 192 rows: 54 to encode with a grid.  Elsewhere three rounds gain (across the heads with 256 points 159 / 188 on 320 rows at
+// 16500 tokens, one layer on changing buffers 170 / 192) and two or six not surely: 63.  Two rounds against one of two heads, in a stack / one layer on three
+// sets of buffers in turn: uniform encode of 11000 tokens 95 to 98 / 100 to 97, decode of 10800 across the heads with 256 points 107 to 115 / 113 to 108;
+// six against five of 256 rows, decode of 33000 tokens 245 to 252 / 256 to 251.  Scores across the heads have no tile of two heads, and take two
+// rounds as well (10300 tokens, 256 points, 47 / 60 on 256 rows, 12200 52 / 62).  Predictions alone (groups across the heads, encode) take none of several rounds
+// on 192 rows: 193 us against 179 at 16500 tokens.
 constexpr int64_t kRound256 = 67, kFirstRound256 = 9, kRoundTwoHeads = 125, kRound320 = 97;
-constexpr int64_t kEncodeRound192 = 54, kDecodeRound192 = 63, kAcrossRound192 = 60, kNoRound192 = 1 << 20;
-inline int64_t decode_round_192(int n_codewords, bool across, bool scores) {
-  return across && (scores || n_codewords == 16 || n_codewords == 256) ? kAcrossRound192 : kDecodeRound192;
-}
+constexpr int64_t kSearchRound192 = 54, kRound192 = 63, kNoRound192 = 1 << 20;
 inline int tile_rows(int64_t n_seq, int64_t seq_len, int D, bool two_heads, int64_t round_192) {
   constexpr int64_t kCUs = 256;                      // MI355X
   const int64_t H = D / 128;

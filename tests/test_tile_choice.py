@@ -12,13 +12,10 @@ PROGRAM = """
 using namespace aquakv;
 int main() {
   long long n, s;
-  int d, points;
-  char kind;                                       // encode, predictions, decode, scores; the latter two across the heads: D, S
-  while (std::scanf("%lld %lld %d %c %d", &n, &s, &d, &kind, &points) == 5) {
-    const bool across = kind == 'D' || kind == 'S', scores = kind == 's' || kind == 'S';
-    const auto round = kind == 'e' ? kEncodeRound192 : kind == 'p' ? kNoRound192 : decode_round_192(points, across, scores);
-    std::printf("%d\\n", tile_rows(n, s, d, kind != 'S', round));
-  }
+  int d;
+  char kind;                                       // encode with a grid, predictions, others; others without a tile of two heads: O
+  while (std::scanf("%lld %lld %d %c", &n, &s, &d, &kind) == 4)
+    std::printf("%d\\n", tile_rows(n, s, d, kind != 'O', kind == 'e' ? kSearchRound192 : kind == 'p' ? kNoRound192 : kRound192));
 }
 """
 
@@ -41,24 +38,18 @@ UP_TO_8192 = [(1, 32), (1024, 32), (1025, 64), (2048, 64), (2049, 96), (3072, 96
               (8193, 320), (10240, 320)]
 
 
-@pytest.mark.parametrize("kind,points,beyond", [
-    ("e", 16, [(10241, 192), (12288, 192), (12289, 0), (16385, 192), (18433, 320), (20481, 0), (32769, 192), (36864, 192), (36865, 0), (49153, 0)]),
-    ("d", 16, [(10241, 0), (16384, 0), (16385, 192), (18432, 192), (18433, 320), (20480, 320), (20481, 0), (32769, 0), (49153, 0), (65536, 0)]),
-    ("D", 16, [(10241, 192), (12288, 192), (12289, 0), (16385, 192), (18433, 320), (20481, 0), (32769, 0)]),
-    ("D", 64, [(10241, 0), (16385, 192), (18433, 320), (32769, 0)]),
-    ("D", 256, [(10241, 192), (12289, 0), (16385, 192), (18433, 320), (32769, 0)]),
-    ("D", 4, [(10241, 0), (16385, 192)]),
-    ("p", 16, [(10241, 0), (16385, 320), (18433, 320)]),
-    ("s", 16, [(10241, 0), (16385, 192), (32769, 0)]),
-    ("S", 64, [(10241, 192), (12289, 0), (16385, 192), (18433, 320), (24577, 0), (32769, 0)])])
-def test_rows_of_8_heads(rows, kind, points, beyond):
+@pytest.mark.parametrize("kind,beyond", [
+    ("e", [(10241, 192), (12288, 192), (12289, 0), (16385, 192), (18433, 320), (20481, 0), (32769, 192), (36864, 192), (36865, 0), (49153, 0)]),
+    ("o", [(10241, 0), (16384, 0), (16385, 192), (18432, 192), (18433, 320), (20480, 320), (20481, 0), (32769, 0), (49153, 0), (65536, 0)]),
+    ("O", [(10241, 192), (12288, 192), (12289, 0), (16385, 192), (18433, 320), (24577, 0), (32769, 0)]),
+    ("p", [(10241, 0), (16385, 320), (18433, 320)])])
+def test_rows_of_8_heads(rows, kind, beyond):
     """(tokens, rows), 0: 256 rows; 8 heads, at the ends of ranges"""
     edges = UP_TO_8192 + beyond
-    assert rows((1, t, 1024, kind, points) for t, _ in edges) == [r for _, r in edges]
+    assert rows((1, t, 1024, kind) for t, _ in edges) == [r for _, r in edges]
 
 
 def test_rows_of_sequences(rows):
     """The shapes that the tests of scores on 192 rows in several rounds run, and many short sequences"""
-    assert rows([(16, 1100, 1024, "S", 16), (3, 3500, 1024, "S", 16), (16, 1100, 1024, "S", 4), (5, 3300, 1024, "S", 256), (3, 3500, 1024, "S", 64),
-                 (5, 3300, 1024, "s", 64), (5, 3300, 1024, "s", 4)]) == [192] * 7
-    assert rows([(16, 33, 1024, "s", 16), (1000, 33, 1024, "s", 16), (1, 33000, 384, "e", 16)]) == [32, 0, 0]
+    assert rows([(16, 1100, 1024, "O"), (3, 3500, 1024, "O"), (5, 3300, 1024, "O"), (5, 3300, 1024, "o")]) == [192] * 4
+    assert rows([(16, 33, 1024, "o"), (1000, 33, 1024, "o"), (1, 33000, 384, "e")]) == [32, 0, 0]
